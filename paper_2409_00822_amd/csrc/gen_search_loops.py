@@ -1,6 +1,6 @@
 #!/usr/bin/env python3
 """Writes rtopk_search_loops.inc: the hand-scheduled binary-search loops (inline gfx950 assembly) for
-rows held as 2, 4 or 8 values per lane.
+rows held as one to eight values per lane.
 
 Why generated: the loops differ only in how many compare / popcount lines they repeat, and inline
 assembly text cannot be produced by C++ templates.  Run by paper_2409_00822_amd/build.py; the output
@@ -15,7 +15,7 @@ gfx950 has no scalar float add).  The masks of the last threshold are returned f
 import os
 import sys
 
-ELEMS = (2, 4, 8)
+ELEMS = (1, 2, 3, 4, 5, 6, 7, 8)
 
 
 def count_lines(E, t, neg):
@@ -23,7 +23,9 @@ def count_lines(E, t, neg):
     key = x, or -x (a free source modifier) for the smallest-k variant."""
     sign = "-" if neg else ""
     out = [f'"v_cmp_ge_f32 %[m{e}], {sign}%[x{e}], %[{t}]\\n\\t"' for e in range(E)]
-    if E == 4:  # balanced tree: shorter dependent chain
+    if E == 1:
+        out += ['"s_bcnt1_i32_b64 %[c0], %[m0]\\n\\t"']
+    elif E == 4:  # balanced tree: shorter dependent chain
         out += [f'"s_bcnt1_i32_b64 %[c{e}], %[m{e}]\\n\\t"' for e in range(4)]
         out += ['"s_add_i32 %[c0], %[c0], %[c1]\\n\\t"', '"s_add_i32 %[c2], %[c2], %[c3]\\n\\t"',
                 '"s_add_i32 %[c0], %[c0], %[c2]\\n\\t"']

@@ -62,15 +62,15 @@ int run(const void* in, int64_t N, int32_t M, int32_t k, int32_t max_iter, float
   a.smallest = smallest;
   a.out_vals = out_vals;
   a.out_idx = out_idx;
-  a.vec_store = (k % 4 == 0) && aligned(out_vals, 4 * esz) && aligned(out_idx, u8 ? 4 : 16);
+  a.vec_store = aligned(out_vals, 4 * esz) && aligned(out_idx, u8 ? 4 : 16) ? (k % 4 == 0 ? 1 : 2) : 0;
   a.stream = static_cast<hipStream_t>(stream);
 
   const bool plain = dtype == rtopk::kF32 && !smallest && mode != rtopk::kEps;
-  const rtopk::Shape sh = rtopk::classify(M, dtype, plain, addr(in));
+  const rtopk::Shape sh = rtopk::kernel_layout(rtopk::classify(M, dtype, plain, addr(in)), M, dtype, plain, false);
   hipError_t err;
   switch (sh.family) {
     case rtopk::kFamStream:
-      err = rtopk::launch_stream_any(sh.g, mode, smallest, a);
+      err = rtopk::launch_stream_any(mode, smallest, a);
       break;
     case rtopk::kFamBlock:
       err = dtype != rtopk::kF32 ? rtopk::launch_block_h16(dtype, sh.g, sh.ng, sh.w, mode, a)
@@ -87,7 +87,9 @@ int run(const void* in, int64_t N, int32_t M, int32_t k, int32_t max_iter, float
                                     : rtopk::launch_g4_eps(sh.ng, sh.full, a);
       break;
     default:
-      err = rtopk::launch_small(sh.g, sh.ng, sh.full, mode, u8, a);
+      err = mode == rtopk::kExact   ? rtopk::launch_small_exact(sh.g, sh.ng, sh.full, u8, a)
+            : mode == rtopk::kEarly ? rtopk::launch_small_early(sh.g, sh.ng, sh.full, u8, a)
+                                    : rtopk::launch_small_eps(sh.g, sh.ng, sh.full, a);
       break;
   }
   return err == hipSuccess ? RTOPK_OK : RTOPK_ERR_LAUNCH;
@@ -197,7 +199,7 @@ int rtopk_maxk_dense(const float* in, int64_t N, int32_t M, int32_t k, int32_t m
   a.max_iter = max_iter < 0 ? 0 : (max_iter > rtopk::kMaxIterClamp ? rtopk::kMaxIterClamp : max_iter);
   a.out_vals = out;
   a.stream = static_cast<hipStream_t>(stream);
-  const rtopk::Shape sh = rtopk::classify_dense(M, addr(in), addr(out));
+  const rtopk::Shape sh = rtopk::kernel_layout(rtopk::classify_dense(M, addr(in), addr(out)), M, rtopk::kF32, true, true);
   hipError_t err;
   if (sh.family == rtopk::kFamBlock) {
     err = rtopk::launch_block_dense(sh.g, sh.ng, sh.w, mode, a);

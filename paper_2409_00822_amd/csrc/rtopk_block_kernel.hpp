@@ -7,6 +7,8 @@
 //
 // Layout.  Wavefront w, lane l owns NG groups of G consecutive columns:
 //   element e = g*G + c  <->  column ((g*W + w)*64 + l)*G + c
+// (where the row's end falls inside a lane's group, that lane holds the row's last G columns instead, and
+// those of them that the lane before it owns are masked out; see group_col)
 // so every load instruction of a wavefront still covers 64*G*4 contiguous bytes, the W wavefronts of a
 // group step cover W KiB contiguous, and column order is (g, w, lane, c).  W is 4, 8 or 16, chosen so
 // that a lane holds up to 64 values: fewer, fatter wavefronts spread the per-step fixed cost (two
@@ -42,44 +44,6 @@ __device__ __forceinline__ uint32_t row16_sum(uint32_t v) {
   v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, false);  // row_half_mirror
   v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, false);  // row_mirror
   return v;
-}
-
-// In the lanes whose bit is set in `mask` (a subset of the active lanes): the 32-bit (or, for 16-bit
-// rows, the narrowed 16-bit) value goes to vals + off_v bytes and the column to cols + off_c bytes.  Both
-// bases are wave-uniform.  The set of active lanes is saved and put back.
-template <int DT>
-__device__ __forceinline__ void store_pair_masked(uint64_t mask, void* vals, uint32_t off_v, uint32_t value_bits,
-                                                  int32_t* cols, uint32_t off_c, int32_t col) {
-  uint64_t saved;
-  if constexpr (DT == kF32) {
-    asm volatile(
-        "s_and_saveexec_b64 %0, %1\n\t"
-        "global_store_dword %2, %3, %4\n\t"
-        "global_store_dword %5, %6, %7\n\t"
-        "s_mov_b64 exec, %0"
-        : "=&s"(saved)
-        : "s"(mask), "v"(off_v), "v"(value_bits), "s"(vals), "v"(off_c), "v"(col), "s"(cols)
-        : "memory", "scc");
-  } else {
-    asm volatile(
-        "s_and_saveexec_b64 %0, %1\n\t"
-        "global_store_short %2, %3, %4\n\t"
-        "global_store_dword %5, %6, %7\n\t"
-        "s_mov_b64 exec, %0"
-        : "=&s"(saved)
-        : "s"(mask), "v"(off_v), "v"(value_bits), "s"(vals), "v"(off_c), "v"(col), "s"(cols)
-        : "memory", "scc");
-  }
-}
-
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order.
-template <typename F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
 // The lane's candidate bits against t: lane_below_packs' layout, set when key >= t.  The same sign-bit
@@ -152,8 +116,7 @@ __device__ __forceinline__ void store_pair_if_below(uint32_t pos, uint32_t limit
 // with early stopping, so the allocation is left to the compiler.
 // Groups of a row that a workgroup loads ahead, during the ranking of its previous row (16-wavefront
 // shape only: the others are launched with one workgroup per row): RTOPK_BLOCK_AHEAD values per lane,
-// half of the row, which is what the register budget of four wavefronts per SIMD leaves free (not the
-// scalar-load fallback, whose ranking by lane masks needs those registers).
+// half of the row, which is what the register budget of four wavefronts per SIMD leaves free.
 #ifndef RTOPK_BLOCK_AHEAD
 #define RTOPK_BLOCK_AHEAD 32
 #endif
@@ -167,7 +130,7 @@ __device__ __forceinline__ void store_pair_if_below(uint32_t pos, uint32_t limit
 #define RTOPK_BLOCK_PERSIST_MIN_W 16
 #endif
 constexpr bool block_persistent(int W) { return W >= RTOPK_BLOCK_PERSIST_MIN_W; }
-constexpr int block_groups_ahead(int W, int G) { return block_persistent(W) && G > 1 ? RTOPK_BLOCK_AHEAD / G : 0; }
+constexpr int block_groups_ahead(int W, int G) { return block_persistent(W) ? RTOPK_BLOCK_AHEAD / G : 0; }
 
 // One row, by the whole workgroup.  Every wavefront leaves through the same return statement.
 template <int G, int NG, int W, int MODE, bool NEG, int DT, bool DENSE>
@@ -195,7 +158,7 @@ __device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const ElemT* row = static_cast<const ElemT*>(in) + r * (int64_t)M;
 
-  // Loading stage.  Lanes past M load the row's first columns (in bounds, cannot change min or max).
+  // Loading stage.  Lanes past M load the row's last columns (in bounds, cannot change min or max).
   // The first groups may have been loaded already, while the workgroup's previous row was ranked.
   constexpr int AHEAD = block_groups_ahead(W, G) < NG ? block_groups_ahead(W, G) : NG;
   float x[E];
@@ -207,7 +170,7 @@ __device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in
 #pragma unroll
       for (int c = 0; c < G; ++c) v[c] = ahead[g * G + c];
     } else {
-      load_group<DT, G>(row, col0 < M ? col0 : 0, v);
+      load_group<DT, G>(row, min(col0, M - G), v);
     }
 #pragma unroll
     for (int c = 0; c < G; ++c) x[g * G + c] = v[c];
@@ -248,6 +211,18 @@ __device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in
     for (int e = 0; e < E; ++e) {
       const int col0 = (((e / G) * W + wave) * kWave + lane) * G;
       x[e] = col0 < M ? x[e] : (NEG ? __builtin_inff() : -__builtin_inff());
+    }
+    if (M % G != 0) {  // uniform: the straddling lane's leading elements belong to the lane before it
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        const int own = M - ((g * W + wave) * kWave + ln) * G;  // columns of the group that are left in the row
+#pragma unroll
+        for (int c = 0; c + 1 < G; ++c)
+          x[g * G + c] = own > 0 && c + own < G ? (NEG ? __builtin_inff() : -__builtin_inff()) : x[g * G + c];
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
   }
 
@@ -426,11 +401,13 @@ __device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in
   if constexpr (AHEAD > 0) {
     if (r_next < N) {
       const ElemT* next = static_cast<const ElemT*>(in) + r_next * (int64_t)M;
+      int ln = lane;  // opaque: the columns computed for this row's loads are not kept for the next row's
+      asm volatile("" : "+v"(ln));
 #pragma unroll
       for (int g = 0; g < AHEAD; ++g) {
-        const int col0 = ((g * W + wave) * kWave + lane) * G;
+        const int col0 = ((g * W + wave) * kWave + ln) * G;
         float v[G];
-        load_group<DT, G>(next, col0 < M ? col0 : 0, v);
+        load_group<DT, G>(next, min(col0, M - G), v);
 #pragma unroll
         for (int c = 0; c < G; ++c) ahead[g * G + c] = v[c];
       }
@@ -447,12 +424,11 @@ __device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in
   // through one prefix scan over the lanes.  The scan's last lane holds the cell totals, every lane keeps
   // the candidates in lower lanes for part 3.  Against one mask, one scalar popcount and one scalar add per
   // ELEMENT this leaves the scalar unit, which the 16 wavefronts of two rows share, nearly idle.
-  constexpr bool kLaneRank = G > 1;      // the scalar-load fallback (G = 1) keeps the mask form
   constexpr int kScanWords = (NG + 2) / 3;
   uint32_t cand[(E + 31) / 32];          // candidate bits of this lane
   uint32_t lower[kScanWords];            // per group, 10 bits each: candidates of the cell in lower lanes
   uint32_t cell_total[kScanWords];       // the same fields for the whole wavefront (uniform)
-  if (kLaneRank && !has_b) {
+  if (!has_b) {
     lane_bits_at_or_above<E, NEG>(x, tA, cand);
     uint32_t own[kScanWords];
 #pragma unroll
@@ -518,7 +494,7 @@ __device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in
   using OutT = typename std::conditional<DT == kF32, uint32_t, uint16_t>::type;  // value bits as stored
   OutT* ov = static_cast<OutT*>(out_vals) + r * (int64_t)(DENSE ? M : k);
   int32_t* oi = DENSE ? nullptr : out_idx + r * (int64_t)k;
-  if (kLaneRank && !has_b) {
+  if (!has_b) {
     // One class, per lane: rank = cell prefix + candidates of the cell in lower lanes + own earlier
     // candidates in the group.  A lane's non-candidates get rank 0xffffffff, so that the one compare against
     // limA (which also keeps every store inside the row's k slots whatever the input held) decides who
@@ -538,7 +514,7 @@ __device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in
       const uint32_t bits = group_bits<E, G>(cand, g);
       const uint32_t before = (uint32_t)__builtin_amdgcn_readlane(my_cell, g) +
                               __builtin_amdgcn_ubfe(lower[g / 3], (uint32_t)(10 * (g % 3)), 10u);
-      const int col0 = ((g * W + wave) * kWave + ln) * G;
+      const int col = ((g * W + wave) * kWave + ln) * G, col0 = min(col, M - G);
       float y[G];
       auto one = [&](auto cc) {
         constexpr int c = decltype(cc)::value;
@@ -555,45 +531,7 @@ __device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in
         }
       };
       static_for<G>(one);
-      if constexpr (DENSE) {
-        if (col0 < M) store_group<G>(reinterpret_cast<float*>(ov) + col0, y);
-      }
-      if constexpr (NG > 4) __builtin_amdgcn_sched_barrier(0);
-    }
-    return;
-  }
-  if (!has_b) {
-    // One class: rank = cell prefix + chosen elements in lower lanes + own earlier elements.
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      int ln = lane;  // opaque per group: keeps the column numbers of all groups from being hoisted
-      if constexpr (NG > 4) asm volatile("" : "+v"(ln));
-      uint64_t m[G];
-      uint32_t pos = (uint32_t)__builtin_amdgcn_readfirstlane(s_tab[0][g * W + wave]);
-#pragma unroll
-      for (int c = 0; c < G; ++c) {
-        m[c] = __builtin_amdgcn_ballot_w64(keyof<NEG>(x[g * G + c]) >= tA);
-        pos = lanes_below(m[c], pos);
-      }
-      const int col0 = ((g * W + wave) * kWave + ln) * G;
-      float y[G];
-#pragma unroll
-      for (int c = 0; c < G; ++c) {
-        const uint64_t mk = m[c] & __builtin_amdgcn_ballot_w64(pos < (uint32_t)limA);
-        if constexpr (DENSE) {
-          y[c] = keep_where(x[g * G + c], mk);
-        } else {
-          const uint32_t fb = __float_as_uint(x[g * G + c]);
-          uint32_t bits = fb;
-          if constexpr (DT != kF32) bits = narrow_bits<DT>(fb);
-          // most masks are empty when k is a small part of the row: skip their store instructions
-          if (mk != 0) store_pair_masked<DT>(mk, ov, pos * (uint32_t)sizeof(OutT), bits, oi, pos * 4u, col0 + c);
-        }
-        if (c + 1 < G) pos = add_mask_bit(pos, m[c]);
-      }
-      if constexpr (DENSE) {
-        if (col0 < M) store_group<G>(reinterpret_cast<float*>(ov) + col0, y);
-      }
+      if constexpr (DENSE) store_row_group<G>(reinterpret_cast<float*>(ov), col, M, y);
       if constexpr (NG > 4) __builtin_amdgcn_sched_barrier(0);
     }
     return;
@@ -612,7 +550,7 @@ __device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in
       posA = lanes_below(__builtin_amdgcn_ballot_w64(a[c]), posA);
       posB = lanes_below(__builtin_amdgcn_ballot_w64(b[c]), posB);
     }
-    const int col0 = ((g * W + wave) * kWave + lane) * G;
+    const int col = ((g * W + wave) * kWave + lane) * G, col0 = min(col, M - G);
     float y[G];
 #pragma unroll
     for (int c = 0; c < G; ++c) {
@@ -634,9 +572,7 @@ __device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in
       posA += a[c] ? 1u : 0u;
       posB += b[c] ? 1u : 0u;
     }
-    if constexpr (DENSE) {
-      if (col0 < M) store_group<G>(reinterpret_cast<float*>(ov) + col0, y);
-    }
+    if constexpr (DENSE) store_row_group<G>(reinterpret_cast<float*>(ov), col, M, y);
     if constexpr (NG > 4) __builtin_amdgcn_sched_barrier(0);
   }
 }

@@ -18,13 +18,7 @@ hipError_t launch_block_dense(int g, int ng, int w, int mode, const LaunchArgs& 
     if (w == 16) return pick<4, 16, 16>(mode, a);
     return hipErrorInvalidValue;
   }
-  if (g != 1 || w != 16) return hipErrorInvalidValue;
-  switch (ng) {
-#define X(n) case n: return pick<1, n, 16>(mode, a);
-    RTOPK_NG_LIST_BLOCK_G1(X)
-#undef X
-    default: return hipErrorInvalidValue;
-  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace rtopk

@@ -3,7 +3,7 @@
 
 namespace rtopk {
 
-// 128-bit loads bring 8 values; 8 loads per lane (W = 4, 8 or 16), or the scalar-load fallback (W = 16).
+// 128-bit loads bring 8 values; 8 loads per lane (W = 4, 8 or 16).
 template <int G, int NG, int W, int DT>
 static hipError_t pick(int mode, const LaunchArgs& a) {
   if (mode == kExact) return launch_block<G, NG, W, kExact, false, DT>(a);
@@ -20,13 +20,7 @@ static hipError_t pick_shape(int g, int ng, int w, int mode, const LaunchArgs& a
     if (w == 16) return pick<8, 8, 16, DT>(mode, a);
     return hipErrorInvalidValue;
   }
-  if (g != 1 || w != 16) return hipErrorInvalidValue;
-  switch (ng) {
-#define X(n) case n: return pick<1, n, 16, DT>(mode, a);
-    RTOPK_NG_LIST_BLOCK_G1(X)
-#undef X
-    default: return hipErrorInvalidValue;
-  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_block_h16(int dtype, int g, int ng, int w, int mode, const LaunchArgs& a) {

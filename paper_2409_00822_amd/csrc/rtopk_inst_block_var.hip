@@ -3,7 +3,7 @@
 
 namespace rtopk {
 
-// 128-bit loads with 16 loads per lane (W = 4, 8 or 16), or the scalar-load fallback (W = 16).
+// 128-bit loads with 16 loads per lane (W = 4, 8 or 16).
 template <int G, int NG, int W>
 static hipError_t pick(int mode, bool smallest, const LaunchArgs& a) {
   if (smallest) {
@@ -23,13 +23,7 @@ hipError_t launch_block_variant(int g, int ng, int w, int mode, bool smallest, c
     if (w == 16) return pick<4, 16, 16>(mode, smallest, a);
     return hipErrorInvalidValue;
   }
-  if (g != 1 || w != 16) return hipErrorInvalidValue;
-  switch (ng) {
-#define X(n) case n: return pick<1, n, 16>(mode, smallest, a);
-    RTOPK_NG_LIST_BLOCK_G1(X)
-#undef X
-    default: return hipErrorInvalidValue;
-  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace rtopk

@@ -3,17 +3,25 @@
 
 namespace rtopk {
 
+template <int G, int NG, int R, bool FULL>
+static hipError_t pick_mode(int mode, const LaunchArgs& a) {
+  if (mode == kExact) return launch_dense<G, NG, R, FULL, kExact>(a);
+  if (mode == kEarly) return launch_dense<G, NG, R, FULL, kEarly>(a);
+  return hipErrorInvalidValue;
+}
+
 template <int G, int NG, int R>
 static hipError_t pick_rows(bool full, int mode, const LaunchArgs& a) {
-  if (mode == kExact) return full ? launch_dense<G, NG, R, true, kExact>(a) : launch_dense<G, NG, R, false, kExact>(a);
-  if (mode == kEarly) return full ? launch_dense<G, NG, R, true, kEarly>(a) : launch_dense<G, NG, R, false, kEarly>(a);
-  return hipErrorInvalidValue;
+  if constexpr (G != 0) {
+    if (full) return pick_mode<G, NG, R, true>(mode, a);
+  }
+  return pick_mode<G, NG, R, false>(mode, a);
 }
 
 template <int G, int NG>
 static hipError_t pick(bool full, int mode, const LaunchArgs& a) {
-  constexpr int R = (G == 4 && NG == 1) ? kRowsPerWaveFp32M256 : rows_per_wave(G * NG);
-  if constexpr (R > kRowsPerWaveFew && G > 1) {
+  constexpr int E = Layout<G, NG>::E, R = (E == 3 || E == 4) ? kRowsPerWaveFp32M256 : rows_per_wave(E);
+  if constexpr (R > kRowsPerWaveFew) {
     if (a.N < kFewRows) return pick_rows<G, NG, kRowsPerWaveFew>(full, mode, a);
   }
   return pick_rows<G, NG, R>(full, mode, a);
@@ -28,14 +36,10 @@ hipError_t launch_dense_any(int g, int ng, bool full, int mode, const LaunchArgs
       default: return hipErrorInvalidValue;
     }
   }
-  if (g == 2 && ng == 1) return pick<2, 1>(full, mode, a);
-  if (g != 1) return hipErrorInvalidValue;
-  switch (ng) {
-#define X(n) case n: return pick<1, n>(full, mode, a);
-    RTOPK_NG_LIST_G1(X)
+#define X(G, NG) if (g == G && ng == NG) return pick<G, NG>(full, mode, a);
+  RTOPK_LAYOUT_LIST_SMALL(X)
 #undef X
-    default: return hipErrorInvalidValue;
-  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace rtopk

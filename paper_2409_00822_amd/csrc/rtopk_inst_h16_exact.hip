@@ -3,16 +3,21 @@
 
 namespace rtopk {
 
+template <int DT, int G, int NG, int R>
+static hipError_t pick_rows(bool full, const LaunchArgs& a) {
+  if constexpr (G != 0) {
+    if (full) return launch<G, NG, R, true, kExact, int32_t, false, DT>(a);
+  }
+  return launch<G, NG, R, false, kExact, int32_t, false, DT>(a);
+}
+
 template <int DT, int G, int NG>
 static hipError_t pick(bool full, const LaunchArgs& a) {
-  constexpr int R = rows_per_wave(G * NG);
-  if constexpr (R > kRowsPerWaveFew && G > 1) {
-    if (a.N < kFewRows) {
-      return full ? launch<G, NG, kRowsPerWaveFew, true, kExact, int32_t, false, DT>(a)
-                  : launch<G, NG, kRowsPerWaveFew, false, kExact, int32_t, false, DT>(a);
-    }
+  constexpr int R = rows_per_wave(Layout<G, NG>::E);
+  if constexpr (R > kRowsPerWaveFew) {
+    if (a.N < kFewRows) return pick_rows<DT, G, NG, kRowsPerWaveFew>(full, a);
   }
-  return full ? launch<G, NG, R, true, kExact, int32_t, false, DT>(a) : launch<G, NG, R, false, kExact, int32_t, false, DT>(a);
+  return pick_rows<DT, G, NG, R>(full, a);
 }
 
 template <int DT>
@@ -26,14 +31,10 @@ static hipError_t pick_shape(int g, int ng, bool full, const LaunchArgs& a) {
     }
   }
   if (g == 4 && ng == 1) return pick<DT, 4, 1>(full, a);
-  if (g == 2 && ng == 1) return pick<DT, 2, 1>(full, a);
-  if (g != 1) return hipErrorInvalidValue;
-  switch (ng) {
-#define X(n) case n: return pick<DT, 1, n>(full, a);
-    RTOPK_NG_LIST_G1(X)
+#define X(G, NG) if (g == G && ng == NG) return pick<DT, G, NG>(full, a);
+  RTOPK_LAYOUT_LIST_SMALL(X)
 #undef X
-    default: return hipErrorInvalidValue;
-  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_h16_exact(int dtype, int g, int ng, bool full, const LaunchArgs& a) {

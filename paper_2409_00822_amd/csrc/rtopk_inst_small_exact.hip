@@ -1,0 +1,43 @@
+// Instantiations: fp32 rows of up to 448 columns whose lanes hold one, two, three, five, six or seven values, exact mode.
+#include "rtopk_kernel.hpp"
+
+namespace rtopk {
+
+// R rows per wavefront; the column type and the k-smallest variant are picked here.
+template <int G, int NG, int R, bool FULL>
+static hipError_t pick_variant(bool u8, const LaunchArgs& a) {
+  if constexpr (Layout<G, NG>::E <= 4) {
+    if (u8 && !a.smallest) return launch<G, NG, R, FULL, kExact, uint8_t>(a);
+  }
+  if (u8) return hipErrorInvalidValue;
+  return a.smallest ? launch<G, NG, R, FULL, kExact, int32_t, true>(a) : launch<G, NG, R, FULL, kExact, int32_t>(a);
+}
+
+template <int G, int NG, int R>
+static hipError_t pick_rows(bool full, bool u8, const LaunchArgs& a) {
+  if constexpr (G != 0) {
+    if (full) return pick_variant<G, NG, R, true>(u8, a);
+  }
+  return pick_variant<G, NG, R, false>(u8, a);
+}
+
+template <int G, int NG>
+static hipError_t pick(bool full, bool u8, const LaunchArgs& a) {
+  constexpr int E = Layout<G, NG>::E, R = rows_per_wave(E);
+  if constexpr (R > kRowsPerWaveFew) {
+    if (a.N < kFewRows) return pick_rows<G, NG, kRowsPerWaveFew>(full, u8, a);
+  }
+  if constexpr (E == 3) {
+    if (!u8) return pick_rows<G, NG, kRowsPerWaveFp32M256>(full, u8, a);
+  }
+  return pick_rows<G, NG, R>(full, u8, a);
+}
+
+hipError_t launch_small_exact(int g, int ng, bool full, bool u8, const LaunchArgs& a) {
+#define X(G, NG) if (g == G && ng == NG) return pick<G, NG>(full, u8, a);
+  RTOPK_LAYOUT_LIST_SMALL(X)
+#undef X
+  return hipErrorInvalidValue;
+}
+
+}  // namespace rtopk

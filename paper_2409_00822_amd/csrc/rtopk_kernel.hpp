@@ -11,7 +11,10 @@
 // Data layout inside a wavefront.  A lane owns NG groups of G consecutive columns:
 //   element e = g*G + c  (0 <= g < NG, 0 <= c < G)  <->  column (g*64 + lane)*G + c
 // so that every load instruction of a wavefront covers 64*G*4 contiguous bytes (1 KiB for G = 4).
-// Column order is therefore (g, lane, c), which is the order the ranking below follows.
+// Column order is therefore (g, lane, c), which is the order the ranking below follows.  Rows of up to 448
+// columns whose width is no multiple of the uniform layouts use groups of mixed width (see Layout), and a
+// row may start at any element: the loads need no alignment beyond the element's own, and the one lane
+// whose group straddles the row's end loads the row's last columns instead (see group_col).
 //
 // A wavefront handles R consecutive rows.  It issues all R rows' loads before the first search, and
 // stages the R*k selected pairs in LDS so that the final stores are whole 128-bit, fully coalesced
@@ -29,6 +32,69 @@
 namespace rtopk {
 
 constexpr int kWave = 64;
+
+// How the columns of a row are laid over the lanes: group g holds width(g) consecutive columns per lane,
+// starting at element first(g); the group's 64 * width(g) columns follow those of the groups before it, so
+// column = 64 * first(g) + lane * width(g) + c and column order is (g, lane, c).
+//   G > 0:  NG groups of G columns (uniform).
+//   G == 0: NG values per lane in groups of 4, 4, ..., then 2 and 1 as the bits of NG say: rows of 129..192 and
+//           257..448 columns then carry at most 63 columns of padding instead of up to 127 (255 for the old
+//           two groups of four), and both the search (a compare, a popcount and an add per value and step) and
+//           the ranking shrink with it.  100003 x 333, k = 33, f32: eight values per lane 41 us, six 31 us.
+// CERTAIN: the leading groups that lie inside every row the layout is used for (the launchers check it), so
+// that only the groups behind them need column-validity tests.
+template <int G, int NG>
+struct Layout {
+  static constexpr int E = G == 0 ? NG : G * NG;
+  static constexpr int GROUPS = G == 0 ? NG / 4 + ((NG >> 1) & 1) + (NG & 1) : NG;
+  static constexpr int width(int g) {
+    if (G != 0) return G;
+    if (g < NG / 4) return 4;
+    return (g == NG / 4 && (NG & 2) != 0) ? 2 : 1;
+  }
+  static constexpr int first(int g) {
+    if (G != 0) return g * G;
+    return g <= NG / 4 ? 4 * g : 4 * (NG / 4) + 2;
+  }
+  // the next smaller entry of the lists of compiled group counts
+  static constexpr int certain() {
+    if (G == 0) return GROUPS - 1;
+    if (NG <= 4) return NG - 1;
+    return NG == 6 ? 4 : (NG == 8 ? 6 : (NG == 12 ? 8 : (NG == 16 ? 12 : (NG == 24 ? 16 : (NG == 32 ? 24 : 0)))));
+  }
+  static constexpr int CERTAIN = certain();
+  static constexpr int MIN_M = CERTAIN > 0 ? 64 * first(CERTAIN) + 1 : width(0);  // narrowest row the layout takes
+};
+
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>), in order.
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+// Column of the lane's first element in group g, and where the lane loads the group from.  Where the row's end
+// falls inside a lane's group (the width is no multiple of the group's), that lane loads the row's last width(g)
+// columns instead -- in bounds, with the same wide load as every other lane -- and its leading elements, which
+// the lane before it owns, are masked out with the columns past M (element_valid).  Lanes wholly past M load the
+// row's last columns as well.
+template <int G, int NG, bool FULL>
+__device__ __forceinline__ int group_col(int g, int lane, int M) {
+  using L = Layout<G, NG>;
+  const int col = kWave * L::first(g) + lane * L::width(g);
+  return FULL || g < L::CERTAIN ? col : min(col, M - L::width(g));
+}
+// Whether element c of the lane's group g is a column of the row that no other lane holds.
+template <int G, int NG, bool FULL>
+__device__ __forceinline__ bool element_valid(int g, int c, int lane, int M) {
+  using L = Layout<G, NG>;
+  if (FULL || g < L::CERTAIN) return true;
+  const int col = kWave * L::first(g) + lane * L::width(g);
+  return col < M && (L::width(g) == 1 || min(col, M - L::width(g)) + c >= col);
+}
 
 // Wavefronts per workgroup.  The wavefronts of a workgroup share nothing, so the workgroup is only a
 // unit of dispatch; one wavefront each spreads the rows most evenly over the compute units.  Against
@@ -253,36 +319,38 @@ __device__ __forceinline__ int count_ge_wide(const float (&x)[E], float t) {
 // pairs to stage[0 ..).  CUT = false promises that there are at most `limit` candidates.
 // LAZY: the masks are not passed in but formed here, group by group, as x >= t, where t is `t_hi`
 // for columns above `split_col` and `t_lo` for columns up to it (a plain threshold has t_lo == t_hi).
-template <int G, int NG, bool CUT, bool LAZY, bool NEG>
-__device__ __forceinline__ void compact_masks(const float (&x)[G * NG], const uint64_t* mm, float t_hi, float t_lo,
-                                              int split_col, int lane, int limit, uint32_t stage_addr) {
+template <int G, int NG, bool FULL, bool CUT, bool LAZY, bool NEG>
+__device__ __forceinline__ void compact_masks(const float (&x)[Layout<G, NG>::E], const uint64_t* mm, float t_hi,
+                                              float t_lo, int split_col, int lane, int M, int limit,
+                                              uint32_t stage_addr) {
+  using L = Layout<G, NG>;
   uint32_t base = 0;  // wave-uniform: candidates in earlier groups
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
+  static_for<L::GROUPS>([&](auto gc) {
+    constexpr int g = decltype(gc)::value, GW = L::width(g), e0 = L::first(g);
     // An opaque copy of the lane id per group: otherwise the column numbers of all groups, shared by
     // every call site, are computed up front and stay live through the whole search.
     int ln = lane;
-    if constexpr (NG > 4) asm volatile("" : "+v"(ln));
-    if constexpr (CUT && NG > 1) {
-      if (base >= (uint32_t)limit) break;  // the first `limit` candidates are all in earlier groups
+    if constexpr (L::E > 16) asm volatile("" : "+v"(ln));
+    if constexpr (CUT && L::GROUPS > 1) {
+      if (base >= (uint32_t)limit) return;  // the first `limit` candidates are all in earlier groups
     }
-    uint64_t m[G];
+    const int col0 = group_col<G, NG, FULL>(g, ln, M);
+    uint64_t m[GW];
 #pragma unroll
-    for (int c = 0; c < G; ++c) {
+    for (int c = 0; c < GW; ++c) {
       if constexpr (LAZY) {
-        const int col = (g * kWave + ln) * G + c;
-        m[c] = __builtin_amdgcn_ballot_w64(keyof<NEG>(x[g * G + c]) >= (col <= split_col ? t_lo : t_hi));
+        m[c] = __builtin_amdgcn_ballot_w64(keyof<NEG>(x[e0 + c]) >= (col0 + c <= split_col ? t_lo : t_hi));
       } else {
-        m[c] = mm[g * G + c];
+        m[c] = mm[e0 + c];
       }
     }
     uint32_t pos = base;
 #pragma unroll
-    for (int c = 0; c < G; ++c) pos = lanes_below(m[c], pos);
-    if constexpr (G % 4 == 0) {
+    for (int c = 0; c < GW; ++c) pos = lanes_below(m[c], pos);
+    if constexpr (GW % 4 == 0) {
       // four elements at a time: one EXEC restore per four staged pairs
 #pragma unroll
-      for (int h = 0; h < G / 4; ++h) {
+      for (int h = 0; h < GW / 4; ++h) {
         uint64_t mk[4];
         uint32_t addr[4], col[4];
         float val[4];
@@ -292,58 +360,60 @@ __device__ __forceinline__ void compact_masks(const float (&x)[G * NG], const ui
           mk[c] = m[cc];
           if constexpr (CUT) mk[c] &= __builtin_amdgcn_ballot_w64(pos < (uint32_t)limit);
           addr[c] = stage_addr + pos * 8u;
-          val[c] = x[g * G + cc];
-          col[c] = (uint32_t)((g * kWave + ln) * G + cc);
-          if (cc + 1 < G) pos = add_mask_bit(pos, m[cc]);
+          val[c] = x[e0 + cc];
+          col[c] = (uint32_t)(col0 + cc);
+          if (cc + 1 < GW) pos = add_mask_bit(pos, m[cc]);
         }
         lds_store_pairs_masked4(mk, addr, val, col);
       }
     } else {
 #pragma unroll
-      for (int c = 0; c < G; ++c) {
+      for (int c = 0; c < GW; ++c) {
         uint64_t mk = m[c];
         if constexpr (CUT) mk &= __builtin_amdgcn_ballot_w64(pos < (uint32_t)limit);
-        lds_store_pair_masked(mk, stage_addr + pos * 8u, __float_as_uint(x[g * G + c]),
-                              (uint32_t)((g * kWave + ln) * G + c));
-        if (c + 1 < G) pos = add_mask_bit(pos, m[c]);
+        lds_store_pair_masked(mk, stage_addr + pos * 8u, __float_as_uint(x[e0 + c]), (uint32_t)(col0 + c));
+        if (c + 1 < GW) pos = add_mask_bit(pos, m[c]);
       }
     }
-    if (g + 1 < NG) {
+    if constexpr (g + 1 < L::GROUPS) {
 #pragma unroll
-      for (int c = 0; c < G; ++c) base += (uint32_t)__builtin_popcountll(m[c]);
+      for (int c = 0; c < GW; ++c) base += (uint32_t)__builtin_popcountll(m[c]);
     }
     // keep the groups in program order: hoisting every group's compares would hold all masks live
-    if constexpr (NG > 4) __builtin_amdgcn_sched_barrier(0);
-  }
+    if constexpr (L::E > 16) __builtin_amdgcn_sched_barrier(0);
+  });
 }
 
 // Column of the `want`-th (1-based) element, in column order, among those with tb <= x < ta;
 // -1 when want == 0.  Used only after the exact search has converged without cnt == k.
-template <int G, int NG, bool NEG>
-__device__ __forceinline__ int nth_column_in_band(const float (&x)[G * NG], int lane, float ta, float tb, int want) {
+template <int G, int NG, bool FULL, bool NEG>
+__device__ __forceinline__ int nth_column_in_band(const float (&x)[Layout<G, NG>::E], int lane, int M, float ta,
+                                                  float tb, int want) {
+  using L = Layout<G, NG>;
   uint32_t base = 0;  // wave-uniform: band members in earlier groups
   int mine = -1;      // per lane: the wanted column if this lane owns it
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
+  static_for<L::GROUPS>([&](auto gc) {
+    constexpr int g = decltype(gc)::value, GW = L::width(g), e0 = L::first(g);
     int ln = lane;  // opaque per group, see compact_masks
-    if constexpr (NG > 4) asm volatile("" : "+v"(ln));
+    if constexpr (L::E > 16) asm volatile("" : "+v"(ln));
     uint32_t pos = base;
-    bool b[G];
+    bool b[GW];
 #pragma unroll
-    for (int c = 0; c < G; ++c) {
-      const float v = keyof<NEG>(x[g * G + c]);
+    for (int c = 0; c < GW; ++c) {
+      const float v = keyof<NEG>(x[e0 + c]);
       b[c] = (v >= tb) && !(v >= ta);
       const uint64_t mb = __builtin_amdgcn_ballot_w64(b[c]);
       pos = lanes_below(mb, pos);
       base += (uint32_t)__builtin_popcountll(mb);
     }
+    const int col0 = group_col<G, NG, FULL>(g, ln, M);
 #pragma unroll
-    for (int c = 0; c < G; ++c) {
-      if (b[c] && pos + 1u == (uint32_t)want) mine = (g * kWave + ln) * G + c;
+    for (int c = 0; c < GW; ++c) {
+      if (b[c] && pos + 1u == (uint32_t)want) mine = col0 + c;
       pos += b[c] ? 1u : 0u;
     }
-    if constexpr (NG > 4) __builtin_amdgcn_sched_barrier(0);
-  }
+    if constexpr (L::E > 16) __builtin_amdgcn_sched_barrier(0);
+  });
   // exactly one lane (or none) holds a column >= 0: a wavefront maximum returns it
   int v = mine;
   v = max(v, __builtin_amdgcn_update_dpp(-1, v, 0xB1, 0xf, 0xf, false));
@@ -366,63 +436,64 @@ __device__ __forceinline__ float keep_where(float x, uint64_t mask) {
 // Section 1 / Fig. 1): y[e] = x[e] for the chosen elements and +0 for all others, in the row's own
 // register layout, so that the result goes back to memory with the same coalesced accesses the row
 // came in with.  Same candidates, order and cut as compact_masks.
-template <int G, int NG, bool CUT, bool LAZY, bool NEG>
-__device__ __forceinline__ void mask_dense(const float (&x)[G * NG], const uint64_t* mm, float t_hi, float t_lo,
-                                           int split_col, int lane, int limit, float (&y)[G * NG]) {
+template <int G, int NG, bool FULL, bool CUT, bool LAZY, bool NEG>
+__device__ __forceinline__ void mask_dense(const float (&x)[Layout<G, NG>::E], const uint64_t* mm, float t_hi, float t_lo,
+                                           int split_col, int lane, int M, int limit, float (&y)[Layout<G, NG>::E]) {
+  using L = Layout<G, NG>;
   uint32_t base = 0;  // wave-uniform: candidates in earlier groups
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
+  static_for<L::GROUPS>([&](auto gc) {
+    constexpr int g = decltype(gc)::value, GW = L::width(g), e0 = L::first(g);
     int ln = lane;  // opaque per group, see compact_masks
-    if constexpr (NG > 4) asm volatile("" : "+v"(ln));
-    uint64_t m[G];
+    if constexpr (L::E > 16) asm volatile("" : "+v"(ln));
+    uint64_t m[GW];
+    const int col0 = group_col<G, NG, FULL>(g, ln, M);
 #pragma unroll
-    for (int c = 0; c < G; ++c) {
+    for (int c = 0; c < GW; ++c) {
       if constexpr (LAZY) {
-        const int col = (g * kWave + ln) * G + c;
-        m[c] = __builtin_amdgcn_ballot_w64(keyof<NEG>(x[g * G + c]) >= (col <= split_col ? t_lo : t_hi));
+        m[c] = __builtin_amdgcn_ballot_w64(keyof<NEG>(x[e0 + c]) >= (col0 + c <= split_col ? t_lo : t_hi));
       } else {
-        m[c] = mm[g * G + c];
+        m[c] = mm[e0 + c];
       }
     }
     if constexpr (CUT) {
       uint32_t pos = base;
 #pragma unroll
-      for (int c = 0; c < G; ++c) pos = lanes_below(m[c], pos);
+      for (int c = 0; c < GW; ++c) pos = lanes_below(m[c], pos);
 #pragma unroll
-      for (int c = 0; c < G; ++c) {
-        y[g * G + c] = keep_where(x[g * G + c], m[c] & __builtin_amdgcn_ballot_w64(pos < (uint32_t)limit));
-        if (c + 1 < G) pos = add_mask_bit(pos, m[c]);
+      for (int c = 0; c < GW; ++c) {
+        y[e0 + c] = keep_where(x[e0 + c], m[c] & __builtin_amdgcn_ballot_w64(pos < (uint32_t)limit));
+        if (c + 1 < GW) pos = add_mask_bit(pos, m[c]);
       }
-      if (g + 1 < NG) {
+      if constexpr (g + 1 < L::GROUPS) {
 #pragma unroll
-        for (int c = 0; c < G; ++c) base += (uint32_t)__builtin_popcountll(m[c]);
+        for (int c = 0; c < GW; ++c) base += (uint32_t)__builtin_popcountll(m[c]);
       }
     } else {
 #pragma unroll
-      for (int c = 0; c < G; ++c) y[g * G + c] = keep_where(x[g * G + c], m[c]);
+      for (int c = 0; c < GW; ++c) y[e0 + c] = keep_where(x[e0 + c], m[c]);
     }
-    if constexpr (NG > 4) __builtin_amdgcn_sched_barrier(0);
-  }
+    if constexpr (L::E > 16) __builtin_amdgcn_sched_barrier(0);
+  });
 }
 
 // The selection in the form the kernel wants: (value, column) pairs staged in LDS, or the dense row.
-template <int G, int NG, bool CUT, bool LAZY, bool NEG, bool DENSE>
-__device__ __forceinline__ void emit_selection(const float (&x)[G * NG], const uint64_t* mm, float t_hi, float t_lo,
-                                               int split_col, int lane, int limit, uint32_t stage_addr,
-                                               float (&y)[G * NG]) {
+template <int G, int NG, bool FULL, bool CUT, bool LAZY, bool NEG, bool DENSE>
+__device__ __forceinline__ void emit_selection(const float (&x)[Layout<G, NG>::E], const uint64_t* mm, float t_hi,
+                                               float t_lo, int split_col, int lane, int M, int limit,
+                                               uint32_t stage_addr, float (&y)[Layout<G, NG>::E]) {
   if constexpr (DENSE) {
-    mask_dense<G, NG, CUT, LAZY, NEG>(x, mm, t_hi, t_lo, split_col, lane, limit, y);
+    mask_dense<G, NG, FULL, CUT, LAZY, NEG>(x, mm, t_hi, t_lo, split_col, lane, M, limit, y);
   } else {
-    compact_masks<G, NG, CUT, LAZY, NEG>(x, mm, t_hi, t_lo, split_col, lane, limit, stage_addr);
+    compact_masks<G, NG, FULL, CUT, LAZY, NEG>(x, mm, t_hi, t_lo, split_col, lane, M, limit, stage_addr);
   }
 }
 
-// Hand-scheduled search loops for 2, 4 and 8 values per lane: search_exact_asm / search_early_asm
+// Hand-scheduled search loops for one to eight values per lane: search_exact_asm / search_early_asm
 // (generated by gen_search_loops.py; same steps as the generic loops in select_row).
 #include "rtopk_search_loops.inc"
 
 // Per-lane part of the row minimum and maximum: mx = max of the lane's elements, nm = max of their
-// negations.  (Lanes past M hold copies of the row's first columns here, which changes neither.)
+// negations.  (Lanes past M hold copies of the row's last columns here, which changes neither.)
 template <int E>
 __device__ __forceinline__ void lane_max_and_negmin(const float (&xin)[E], float& mx, float& nm) {
   if constexpr (E == 1) {
@@ -727,10 +798,11 @@ constexpr int band_scratch_floats(int E) {
 //   DENSE: the result is y[] (chosen values in place, +0 elsewhere) instead of pairs staged at `stage`.
 //   row_max, row_min: the row's maximum and minimum (Alg. 1 / Alg. 2, first two steps), wave-uniform.
 template <int G, int NG, bool FULL, int MODE, bool NEG, int DT = kF32, bool DENSE = false>
-__device__ __forceinline__ int select_row(const float (&xin)[G * NG], int lane, int M, int k, int max_iter,
-                                          float eps_rel, uint2* stage, float (&y)[G * NG], float row_max,
+__device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], int lane, int M, int k, int max_iter,
+                                          float eps_rel, uint2* stage, float (&y)[Layout<G, NG>::E], float row_max,
                                           float row_min) {
-  constexpr int E = G * NG;
+  using L = Layout<G, NG>;
+  constexpr int E = L::E;
   const uint32_t stage_addr = (uint32_t)(uintptr_t)stage;  // LDS byte address
 
   // lo, hi bound the keys: for the smallest-k variant the keys are the negated values, whose maximum
@@ -740,13 +812,16 @@ __device__ __forceinline__ int select_row(const float (&xin)[G * NG], int lane, 
 
   // From here on columns past M must never be counted or chosen: a key of -inf is below every threshold.
   float x[E];
+  static_for<L::GROUPS>([&](auto gc) {
+    constexpr int g = decltype(gc)::value;
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const bool valid = FULL || ((e / G) * kWave + lane) * G < M;
-    x[e] = valid ? xin[e] : (NEG ? __builtin_inff() : -__builtin_inff());  // key -inf
-  }
+    for (int c = 0; c < L::width(g); ++c) {
+      const int e = L::first(g) + c;
+      x[e] = element_valid<G, NG, FULL>(g, c, lane, M) ? xin[e] : (NEG ? __builtin_inff() : -__builtin_inff());  // key -inf
+    }
+  });
 
-  constexpr bool ASM = (E == 2 || E == 4 || E == 8);  // hand-scheduled loops exist for these widths
+  constexpr bool ASM = E <= 8;  // hand-scheduled loops exist for these widths
   constexpr bool KEEP = E <= 8;                       // masks of the last step stay in scalar registers
   // wider rows: ACC of the E elements are counted per lane, the rest by mask popcount
   constexpr int ACC = KEEP ? 0 : RTOPK_ACC_OF(E);
@@ -865,14 +940,14 @@ __device__ __forceinline__ int select_row(const float (&xin)[G * NG], int lane, 
       }
     }
     if (hit) {
-      emit_selection<G, NG, false, !KEEP, NEG, DENSE>(x, m, thres, thres, -1, lane, k, stage_addr, y);
+      emit_selection<G, NG, FULL, false, !KEEP, NEG, DENSE>(x, m, thres, thres, -1, lane, M, k, stage_addr, y);
     } else {
       // Everything >= hi is taken first (cut at k by column when hi is still the row maximum and k
       // or more tie there); the first k - na members of [lo, hi) follow: all columns up to the
       // (k - na)-th member's column select against lo, the others against hi.
       const int na = count(hi);
-      const int split = nth_column_in_band<G, NG, NEG>(x, lane, hi, lo, k - (na < k ? na : k));
-      emit_selection<G, NG, true, true, NEG, DENSE>(x, nullptr, hi, lo, split, lane, k, stage_addr, y);
+      const int split = nth_column_in_band<G, NG, FULL, NEG>(x, lane, M, hi, lo, k - (na < k ? na : k));
+      emit_selection<G, NG, FULL, true, true, NEG, DENSE>(x, nullptr, hi, lo, split, lane, M, k, stage_addr, y);
     }
     return 0;
   } else if constexpr (MODE == kEps) {
@@ -917,12 +992,12 @@ __device__ __forceinline__ int select_row(const float (&xin)[G * NG], int lane, 
       }
     }
     if (hit) {
-      emit_selection<G, NG, false, !KEEP, NEG, DENSE>(x, m, thres, thres, -1, lane, k, stage_addr, y);
+      emit_selection<G, NG, FULL, false, !KEEP, NEG, DENSE>(x, m, thres, thres, -1, lane, M, k, stage_addr, y);
       return steps;
     }
     const int na = count(hi);
-    const int split = nth_column_in_band<G, NG, NEG>(x, lane, hi, lo, k - (na < k ? na : k));
-    emit_selection<G, NG, true, true, NEG, DENSE>(x, nullptr, hi, lo, split, lane, k, stage_addr, y);
+    const int split = nth_column_in_band<G, NG, FULL, NEG>(x, lane, M, hi, lo, k - (na < k ? na : k));
+    emit_selection<G, NG, FULL, true, true, NEG, DENSE>(x, nullptr, hi, lo, split, lane, M, k, stage_addr, y);
     return steps + 1;
   } else {
     int cnt = -1;
@@ -967,9 +1042,9 @@ __device__ __forceinline__ int select_row(const float (&xin)[G * NG], int lane, 
       if (cnt < k) cnt = count(lo);
     }
     if (cnt == k) {
-      emit_selection<G, NG, false, !KEEP, NEG, DENSE>(x, m, lo, lo, -1, lane, k, stage_addr, y);
+      emit_selection<G, NG, FULL, false, !KEEP, NEG, DENSE>(x, m, lo, lo, -1, lane, M, k, stage_addr, y);
     } else {
-      emit_selection<G, NG, true, !KEEP, NEG, DENSE>(x, m, lo, lo, -1, lane, k, stage_addr, y);
+      emit_selection<G, NG, FULL, true, !KEEP, NEG, DENSE>(x, m, lo, lo, -1, lane, M, k, stage_addr, y);
     }
     return 0;
   }
@@ -997,60 +1072,50 @@ __device__ __forceinline__ uint32_t narrow_bits(uint32_t fbits) {  // fp32 bits 
   }
 }
 
-// One load of G consecutive elements starting at element `col` of the row at `row` (G*4 bytes for
-// fp32, G*2 bytes for 16-bit types; the address is aligned to that size), with the non-temporal
-// hint: every input byte is read exactly once, and keeping it out of the caches' retention policy
-// measurably raises the streaming rate.
+// One load of G consecutive elements starting at element `col` of the row at `row` (G*4 bytes for fp32,
+// G*2 bytes for 16-bit types; the address needs no more than the element's own alignment), with the
+// non-temporal hint: every input byte is read exactly once, and keeping it out of the caches' retention policy
+// measurably raises the streaming rate.  A wide load from any 4-byte boundary streams at the rate of an
+// aligned one (1 GiB, 7.1 TB/s either way), one from an odd 2-byte boundary at 5.6 TB/s -- against a load
+// instruction per element, which such rows used to take (10007 columns: 249 us per 2^26 values).
 template <int DT, int G>
 __device__ __forceinline__ void load_group(const typename std::conditional<DT == kF32, float, uint16_t>::type* row,
                                            int col, float (&dst)[G]) {
-  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-  typedef uint32_t u4 __attribute__((ext_vector_type(4)));
   if constexpr (DT == kF32) {
     const float* p = row + col;
     if constexpr (G == 1) {
       dst[0] = __builtin_nontemporal_load(p);
-    } else if constexpr (G == 2) {
-      typedef float f2 __attribute__((ext_vector_type(2)));
-      const f2 v = __builtin_nontemporal_load(reinterpret_cast<const f2*>(p));
-      dst[0] = v.x;
-      dst[1] = v.y;
     } else {
-      static_assert(G == 4, "fp32 rows load 1, 2 or 4 values at a time");
-      typedef float f4 __attribute__((ext_vector_type(4)));
-      const f4 v = __builtin_nontemporal_load(reinterpret_cast<const f4*>(p));
-      dst[0] = v.x;
-      dst[1] = v.y;
-      dst[2] = v.z;
-      dst[3] = v.w;
+      static_assert(G == 2 || G == 4, "fp32 rows load 1, 2 or 4 values at a time");
+      typedef float fG __attribute__((ext_vector_type(G), aligned(4)));
+      const fG v = __builtin_nontemporal_load(reinterpret_cast<const fG*>(p));
+#pragma unroll
+      for (int c = 0; c < G; ++c) dst[c] = v[c];
     }
   } else {
     const uint16_t* p = row + col;
     if constexpr (G == 1) {
       dst[0] = widen_half<DT>((uint32_t)__builtin_nontemporal_load(p), 0);
     } else if constexpr (G == 2) {
-      const uint32_t w = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(p));
+      typedef uint32_t u1 __attribute__((aligned(2)));
+      const uint32_t w = __builtin_nontemporal_load(reinterpret_cast<const u1*>(p));
       dst[0] = widen_half<DT>(w, 0);
       dst[1] = widen_half<DT>(w, 1);
-    } else if constexpr (G == 4) {
-      const u2 w = __builtin_nontemporal_load(reinterpret_cast<const u2*>(p));
-      dst[0] = widen_half<DT>(w.x, 0);
-      dst[1] = widen_half<DT>(w.x, 1);
-      dst[2] = widen_half<DT>(w.y, 0);
-      dst[3] = widen_half<DT>(w.y, 1);
     } else {
-      static_assert(G == 8, "16-bit rows load 1, 2, 4 or 8 values at a time");
-      const u4 w = __builtin_nontemporal_load(reinterpret_cast<const u4*>(p));
-      dst[0] = widen_half<DT>(w.x, 0);
-      dst[1] = widen_half<DT>(w.x, 1);
-      dst[2] = widen_half<DT>(w.y, 0);
-      dst[3] = widen_half<DT>(w.y, 1);
-      dst[4] = widen_half<DT>(w.z, 0);
-      dst[5] = widen_half<DT>(w.z, 1);
-      dst[6] = widen_half<DT>(w.w, 0);
-      dst[7] = widen_half<DT>(w.w, 1);
+      static_assert(G == 4 || G == 8, "16-bit rows load 1, 2, 4 or 8 values at a time");
+      typedef uint32_t uG __attribute__((ext_vector_type(G / 2), aligned(2)));
+      const uG w = __builtin_nontemporal_load(reinterpret_cast<const uG*>(p));
+#pragma unroll
+      for (int c = 0; c < G; ++c) dst[c] = widen_half<DT>(w[c / 2], c & 1);
     }
   }
+}
+
+// Rows of a wavefront's batch: `left` (at least one) rows remain in the launch, a full batch has R.  In 32 bits and
+// said to be uniform, so that the per-row tests are scalar compares (there is none for 64 bits).
+__device__ __forceinline__ int rows_left(int64_t left, int R) {
+  const uint32_t low = (uint32_t)left, high = (uint32_t)((uint64_t)left >> 32);
+  return __builtin_amdgcn_readfirstlane(high != 0 || low > (uint32_t)R ? R : (int)low);
 }
 
 // Cache-policy bits of the output stores: non-temporal.  What decides is whether a launch's outputs were
@@ -1088,11 +1153,13 @@ __device__ __forceinline__ void store_streaming(uint32_t* p, uint32_t v) {
 // (Rows of 128 values per lane are held to three wavefronts per SIMD and rows of 96 to four: the ragged-width variants would
 // otherwise take a few registers more than that allows and run two.)
 template <int G, int NG, int R, bool FULL, int MODE, bool NEG, typename IdxT, int DT>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G * NG >= 128 ? 3 : (G * NG >= 96 ? 4 : 1))))
+__global__ void __launch_bounds__(256)
+    __attribute__((amdgpu_waves_per_eu(Layout<G, NG>::E >= 128 ? 3 : (Layout<G, NG>::E >= 96 ? 4 : 1))))
     rtopk_wave_kernel(const void* __restrict__ in, int64_t N, int M, int k, int max_iter, float eps_rel,
                       void* __restrict__ out_vals, IdxT* __restrict__ out_idx, int32_t* __restrict__ out_iters,
                       int vec_store) {
-  constexpr int E = G * NG;
+  using L = Layout<G, NG>;
+  constexpr int E = L::E;
   using ElemT = typename std::conditional<DT == kF32, float, uint16_t>::type;
   extern __shared__ uint2 stage_all[];  // [waves per block][R * k] (value bits, column)
 
@@ -1101,7 +1168,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G * NG
   const int waves_per_block = (int)(blockDim.x >> 6);
   const int64_t r0 = ((int64_t)blockIdx.x * waves_per_block + wave) * R;
   if (r0 >= N) return;
-  const int nrows = (N - r0 < R) ? (int)(N - r0) : R;
+  const int nrows = rows_left(N - r0, R);
   // per wavefront: R*k pairs, and at least the band scratch where the exact search of a wide row uses it
   static_assert(!narrows(E, MODE) || R == 1, "the band scratch reuses the staging area of the wavefront's only row");
   constexpr int kMinPairs = band_scratch_floats(E) / 2;
@@ -1110,21 +1177,20 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G * NG
 
   // Loading stage: all R rows' loads are issued before any is consumed.
   float x[R][E];
+  const ElemT* row0 = static_cast<const ElemT*>(in) + r0 * (int64_t)M;
 #pragma unroll
   for (int rr = 0; rr < R; ++rr) {
-    const ElemT* row = static_cast<const ElemT*>(in) + (r0 + (rr < nrows ? rr : 0)) * (int64_t)M;
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      // Lanes whose columns lie past M load the row's first columns instead (in bounds, no branch, so
+    const ElemT* row = row0 + (rr < nrows ? rr * M : 0);
+    static_for<L::GROUPS>([&](auto gc) {
+      // Lanes whose columns lie past M load the row's last columns instead (in bounds, no branch, so
       // all loads of the wavefront stay in flight together).  Duplicates of real elements cannot
       // change the row's minimum or maximum; select_row turns them into -inf before it counts.
-      const int col0 = (g * kWave + lane) * G;
-      const bool valid = FULL || col0 < M;
-      float v[G];
-      load_group<DT, G>(row, valid ? col0 : 0, v);
+      constexpr int g = decltype(gc)::value;
+      float v[L::width(g)];
+      load_group<DT, L::width(g)>(row, group_col<G, NG, FULL>(g, lane, M), v);
 #pragma unroll
-      for (int c = 0; c < G; ++c) x[rr][g * G + c] = v[c];
-    }
+      for (int c = 0; c < L::width(g); ++c) x[rr][L::first(g) + c] = v[c];
+    });
   }
   // Row minima and maxima of all R rows, then the searching and selecting stages row by row.
   float row_max[R], row_min[R];
@@ -1150,35 +1216,50 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G * NG
   using OutT = typename std::conditional<DT == kF32, uint32_t, uint16_t>::type;  // value bits as stored
   OutT* ov = static_cast<OutT*>(out_vals) + r0 * (int64_t)k;
   IdxT* oi = out_idx + r0 * (int64_t)k;
-  if (vec_store) {
+  auto store_quad = [&](uint4 a, uint4 b, OutT* to_v, IdxT* to_i, int q) {  // four pairs to the q-th group of four
+    if constexpr (DT == kF32) {
+      store_streaming(reinterpret_cast<uint4*>(to_v) + q, make_uint4(a.x, a.z, b.x, b.z));
+    } else {
+      store_streaming(reinterpret_cast<uint2*>(to_v) + q,
+                      make_uint2(narrow_bits<DT>(a.x) | (narrow_bits<DT>(a.z) << 16),
+                                 narrow_bits<DT>(b.x) | (narrow_bits<DT>(b.z) << 16)));
+    }
+    if constexpr (sizeof(IdxT) == 4) {
+      store_streaming(reinterpret_cast<uint4*>(to_i) + q, make_uint4(a.y, a.w, b.y, b.w));
+    } else {
+      store_streaming(reinterpret_cast<uint32_t*>(to_i) + q, a.y | (a.w << 8) | (b.y << 16) | (b.w << 24));
+    }
+  };
+  auto store_one = [&](int j) {
+    const uint2 a = stage[j];
+    if constexpr (DT == kF32) {
+      ov[j] = a.x;
+    } else {
+      ov[j] = (uint16_t)narrow_bits<DT>(a.x);
+    }
+    oi[j] = (IdxT)a.y;
+  };
+  if (__builtin_expect(vec_store == 1, 1)) {  // k is a multiple of four: so is every wavefront's first output
 #pragma unroll 1
-    for (int q = lane; q < (total >> 2); q += kWave) {
-      const uint4 a = *reinterpret_cast<const uint4*>(stage + 4 * q);
-      const uint4 b = *reinterpret_cast<const uint4*>(stage + 4 * q + 2);
-      if constexpr (DT == kF32) {
-        store_streaming(reinterpret_cast<uint4*>(ov) + q, make_uint4(a.x, a.z, b.x, b.z));
-      } else {
-        store_streaming(reinterpret_cast<uint2*>(ov) + q,
-                        make_uint2(narrow_bits<DT>(a.x) | (narrow_bits<DT>(a.z) << 16),
-                                   narrow_bits<DT>(b.x) | (narrow_bits<DT>(b.z) << 16)));
-      }
-      if constexpr (sizeof(IdxT) == 4) {
-        store_streaming(reinterpret_cast<uint4*>(oi) + q, make_uint4(a.y, a.w, b.y, b.w));
-      } else {
-        store_streaming(reinterpret_cast<uint32_t*>(oi) + q, a.y | (a.w << 8) | (b.y << 16) | (b.w << 24));
-      }
+    for (int q = lane; q < (total >> 2); q += kWave)
+      store_quad(*reinterpret_cast<const uint4*>(stage + 4 * q), *reinterpret_cast<const uint4*>(stage + 4 * q + 2), ov, oi, q);
+  } else if (vec_store == 2) {
+    // Any other k: the pairs before the first aligned group of four and after the last go one by one.  (A
+    // 128-bit store off its alignment runs at 4.4 TB/s where an aligned one reaches 5.8, and one store per pair
+    // at 4.9: 1 GiB written.)
+    const int head = (int)(0u - (uint32_t)r0 * (uint32_t)k & 3u), first = head < total ? head : total;
+    const int quads = (total - first) >> 2, tail = first + 4 * quads;
+    if (lane < first) store_one(lane);
+    if (lane >= kWave - 4 && tail + (lane - (kWave - 4)) < total) store_one(tail + (lane - (kWave - 4)));
+#pragma unroll 1
+    for (int q = lane; q < quads; q += kWave) {
+      const uint2* p = stage + first + 4 * q;
+      store_quad(make_uint4(p[0].x, p[0].y, p[1].x, p[1].y), make_uint4(p[2].x, p[2].y, p[3].x, p[3].y), ov + first,
+                 oi + first, q);
     }
   } else {
 #pragma unroll 1
-    for (int q = lane; q < total; q += kWave) {
-      const uint2 a = stage[q];
-      if constexpr (DT == kF32) {
-        ov[q] = a.x;
-      } else {
-        ov[q] = (uint16_t)narrow_bits<DT>(a.x);
-      }
-      oi[q] = (IdxT)a.y;
-    }
+    for (int j = lane; j < total; j += kWave) store_one(j);
   }
 }
 
@@ -1197,6 +1278,21 @@ __device__ __forceinline__ void store_group(float* p, const float* v) {
   }
 }
 
+// The lane's group of G columns from `col` on back to the row, as far as the row's M columns go.  v[] holds
+// the columns min(col, M - G) .. (see group_col): the lane that straddles the row's end stores only the
+// elements that are its own.
+template <int G>
+__device__ __forceinline__ void store_row_group(float* row, int col, int M, const float* v) {
+  if (col + G <= M) {
+    store_group<G>(row + col, v);
+  } else if (G > 1 && col < M) {
+#pragma unroll
+    for (int c = 0; c < G; ++c) {
+      if (M - G + c >= col) row[M - G + c] = v[c];
+    }
+  }
+}
+
 // MaxK non-linearity, dense form: out[r][c] = in[r][c] where column c is among the k selected for
 // row r (Algorithm 1 at epsilon = 0, or Algorithm 2), +0 elsewhere.  Same loading, min/max and
 // search as rtopk_wave_kernel; the selection is a register-to-register mask, so nothing passes
@@ -1204,29 +1300,28 @@ __device__ __forceinline__ void store_group(float* p, const float* v) {
 template <int G, int NG, int R, bool FULL, int MODE>
 __global__ void __launch_bounds__(256)
     rtopk_dense_kernel(const float* __restrict__ in, int64_t N, int M, int k, int max_iter, float* __restrict__ out) {
-  constexpr int E = G * NG;
+  using L = Layout<G, NG>;
+  constexpr int E = L::E;
   extern __shared__ uint2 band_scratch[];  // [waves per block][band_regs(E) * 64 floats], wide rows only
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int waves_per_block = (int)(blockDim.x >> 6);
   const int64_t r0 = ((int64_t)blockIdx.x * waves_per_block + wave) * R;
   if (r0 >= N) return;
-  const int nrows = (N - r0 < R) ? (int)(N - r0) : R;
+  const int nrows = rows_left(N - r0, R);
   uint2* scratch = band_scratch + (size_t)wave * (band_scratch_floats(E) / 2);
 
   float x[R][E];
 #pragma unroll
   for (int rr = 0; rr < R; ++rr) {
-    const float* row = in + (r0 + (rr < nrows ? rr : 0)) * (int64_t)M;
+    const float* row = in + r0 * (int64_t)M + (rr < nrows ? rr * M : 0);
+    static_for<L::GROUPS>([&](auto gc) {
+      constexpr int g = decltype(gc)::value;
+      float v[L::width(g)];
+      load_group<kF32, L::width(g)>(row, group_col<G, NG, FULL>(g, lane, M), v);  // lanes past M: see rtopk_wave_kernel
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      const int col0 = (g * kWave + lane) * G;  // lanes past M: see rtopk_wave_kernel
-      const bool valid = FULL || col0 < M;
-      float v[G];
-      load_group<kF32, G>(row, valid ? col0 : 0, v);
-#pragma unroll
-      for (int c = 0; c < G; ++c) x[rr][g * G + c] = v[c];
-    }
+      for (int c = 0; c < L::width(g); ++c) x[rr][L::first(g) + c] = v[c];
+    });
   }
   float row_max[R], row_min[R];
   rows_max_and_min<R, E>(x, row_max, row_min);
@@ -1237,11 +1332,11 @@ __global__ void __launch_bounds__(256)
       select_row<G, NG, FULL, MODE, false, kF32, true>(x[rr], lane, M, k, max_iter, 0.0f, scratch, y, row_max[rr],
                                                        row_min[rr]);
       float* orow = out + (r0 + rr) * (int64_t)M;
-#pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        const int col0 = (g * kWave + lane) * G;
-        if (FULL || col0 < M) store_group<G>(orow + col0, &y[g * G]);
-      }
+      static_for<L::GROUPS>([&](auto gc) {
+        constexpr int g = decltype(gc)::value, GW = L::width(g);
+        const int col = kWave * L::first(g) + lane * GW;
+        store_row_group<GW>(orow, col, FULL || g < L::CERTAIN ? col + GW : M, &y[L::first(g)]);
+      });
     }
   }
 }
@@ -1252,7 +1347,8 @@ hipError_t launch_dense(const LaunchArgs& a) {
   const int64_t batches = (a.N + R - 1) / R;
   const int64_t blocks = (batches + waves - 1) / waves;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-  const size_t lds = (size_t)waves * band_scratch_floats(G * NG) * sizeof(float);
+  if (a.M < Layout<G, NG>::MIN_M || a.M > 64 * Layout<G, NG>::E) return hipErrorInvalidValue;
+  const size_t lds = (size_t)waves * band_scratch_floats(Layout<G, NG>::E) * sizeof(float);
   return launch_kernel(rtopk_dense_kernel<G, NG, R, FULL, MODE>, dim3((unsigned)blocks), dim3(waves * kWave), lds,
                        a.stream, static_cast<const float*>(a.in), a.N, a.M, a.k, a.max_iter,
                        static_cast<float*>(a.out_vals));
@@ -1262,10 +1358,12 @@ hipError_t launch_dense(const LaunchArgs& a) {
 
 template <int G, int NG, int R, bool FULL, int MODE, typename IdxT, bool NEG = false, int DT = kF32>
 hipError_t launch(const LaunchArgs& a) {
+  using L = Layout<G, NG>;
+  if (a.M < L::MIN_M || a.M > 64 * L::E) return hipErrorInvalidValue;
   // LDS per wavefront: R*k staged pairs of 8 bytes; at most 64 KiB per block.
   size_t per_wave = (size_t)R * (size_t)a.k * sizeof(uint2);
   // the exact search of wide rows gathers its band through the (not yet used) staging area
-  if (per_wave < band_scratch_floats(G * NG) * sizeof(float)) per_wave = band_scratch_floats(G * NG) * sizeof(float);
+  if (per_wave < band_scratch_floats(L::E) * sizeof(float)) per_wave = band_scratch_floats(L::E) * sizeof(float);
   // one wavefront per workgroup, except where a wavefront stages 8 KiB or more of pairs: there four
   // per workgroup measured 7 % faster (2^20 x 256, k = 128: 387 -> 360 us), while at 4 KiB and below
   // one per workgroup is the faster by 3-11 %

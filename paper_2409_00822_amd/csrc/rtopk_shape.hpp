@@ -4,9 +4,14 @@
 //
 // A layout is (g, ng, w): a lane owns ng groups of g consecutive columns, and a row is spread over w
 // wavefronts (w = 1: one wavefront per row, rtopk_kernel.hpp; w > 1: one workgroup per row,
-// rtopk_block_kernel.hpp), so a layout holds rows of up to 64 * g * ng * w columns.  Which (g, ng, w) are
-// compiled is fixed by the lists below; the instantiation tables (rtopk_inst_*.hip) expand the same lists,
-// so a layout this header can return always has a kernel behind it.
+// rtopk_block_kernel.hpp), so a layout holds rows of up to 64 * g * ng * w columns.
+//
+// Two steps.  classify() names a call by family and by the widest load that every row's alignment allows
+// (g elements).  kernel_layout() maps that to the layout that is launched: the kernels load vectors from any
+// element boundary at full rate, so what counts there is only how little of a lane's registers a row leaves
+// empty.  Which layouts are compiled is fixed by the lists below; the instantiation tables
+// (rtopk_inst_*.hip) expand the same lists, so a layout that kernel_layout() returns always has a kernel
+// behind it, and with it every layout that classify() returns.
 #pragma once
 
 #include <stdint.h>
@@ -14,8 +19,12 @@
 // Groups per lane that are instantiated, per load width.  X(n) is expanded once per entry, ascending.
 #define RTOPK_NG_LIST_G4(X) X(1) X(2) X(3) X(4) X(6) X(8) X(12) X(16) X(24) X(32)   /* fp32, 128-bit loads */
 #define RTOPK_NG_LIST_H8(X) X(1) X(2) X(3) X(4) X(6) X(8) X(12) X(16)               /* 16-bit rows, 128-bit loads */
-#define RTOPK_NG_LIST_G1(X) X(1) X(2) X(4) X(8) X(16) X(32) X(64) X(128)            /* scalar-load fallback */
-#define RTOPK_NG_LIST_BLOCK_G1(X) X(16) X(32) X(64)                                 /* scalar-load fallback, 16 wavefronts */
+// Rows of up to 448 columns, X(g, ng): one or two values per lane, and (g = 0) three, five, six or seven in
+// groups of mixed width (Layout in rtopk_kernel.hpp); four are (4, 1) of the lists above, eight (4, 2) or (8, 1).
+#define RTOPK_LAYOUT_LIST_SMALL(X) X(1, 1) X(2, 1) X(0, 3) X(0, 5) X(0, 6) X(0, 7)
+// Unaligned rows as classify() names them (the kernels behind them: kernel_layout).
+#define RTOPK_NG_LIST_G1(X) X(1) X(2) X(4) X(8) X(16) X(32) X(64) X(128)
+#define RTOPK_NG_LIST_BLOCK_G1(X) X(16) X(32) X(64)
 
 namespace rtopk {
 
@@ -39,7 +48,7 @@ constexpr int kMaxWaveM = 8192;      // widest row one wavefront holds in regist
 constexpr int kBackwardRowsM = 2048;  // backward edge: widest row assembled whole in a wavefront's LDS (8 KiB)
 
 enum Family : int {
-  kFamSmall = 0,  // launch_small: even M <= 128 (g = 2) and the scalar-load fallback (g = 1)
+  kFamSmall = 0,  // launch_small_*: fp32 rows of up to 448 columns whose lanes do not hold exactly four values
   kFamG4 = 1,     // launch_g4_*: fp32, 128-bit loads
   kFamH16 = 2,    // launch_h16_*: half / bfloat16 rows, one wavefront per row
   kFamBlock = 3,  // launch_block_*: one workgroup per row, the row in registers
@@ -55,7 +64,7 @@ struct Shape {
 
 inline bool is_aligned(uintptr_t p, uintptr_t a) { return p % a == 0; }
 
-// Smallest listed ng with 64 * g * ng >= M; `fallback` (the list's largest) when none is.
+// Smallest listed ng with 64 * g * ng >= M.
 inline int pick_ng_g4(int M) {
 #define X(n) if (M <= 256 * n) return n;
   RTOPK_NG_LIST_G4(X)
@@ -176,8 +185,42 @@ inline Shape classify_dense(int M, uintptr_t in, uintptr_t out) {
   return s;
 }
 
-// True when (g, ng, w) is in the compiled set of its family (the same lists the instantiation tables
-// expand).  `plain` and `dense` as above.
+// The layout that is launched for a shape that classify() or classify_dense() returned (dtype, plain as
+// there; dense: the dense-output form).  g = 0: groups of mixed width, ng values per lane.
+inline Shape kernel_layout(Shape s, int M, int dtype, bool plain, bool dense) {
+  if (s.family == kFamStream) {
+    s.g = 4;  // 128-bit loads from any 4-byte boundary
+    return s;
+  }
+  if (s.family == kFamBlock) {
+    s.w = block_waves(M);
+    s.g = dtype == kF32 ? 4 : 8;
+    s.ng = dtype != kF32 ? 8 : ((plain && !dense && M <= 64 * s.w * 4 * 12) ? 12 : 16);
+  } else if (M > 512) {
+    s.g = dtype == kF32 ? 4 : 8;
+    s.ng = dtype == kF32 ? pick_ng_g4(M) : pick_ng_h8(M);
+    if (dtype == kF32) s.family = kFamG4;
+  } else {
+    // exactly as many values per lane as the row needs
+    const int E = (M + 63) / 64;
+    if (dtype == kF32) s.family = kFamSmall;
+    if (E == 1 || E == 2) {
+      s.g = E;
+      s.ng = 1;
+    } else if (E == 4 || E == 8) {
+      s.g = dtype != kF32 && E == 8 ? 8 : 4;
+      s.ng = E / s.g;
+      if (dtype == kF32) s.family = kFamG4;
+    } else {
+      s.g = 0;
+      s.ng = E;
+    }
+  }
+  s.full = s.g != 0 && M == s.capacity();
+  return s;
+}
+
+// True when (g, ng, w) is a layout of its family's lists above.  `plain` and `dense` as above.
 inline bool instantiated(const Shape& s, int dtype, bool plain, bool dense) {
   auto in_list = [](int n, int which) {
     bool hit = false;

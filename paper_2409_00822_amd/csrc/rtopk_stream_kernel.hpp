@@ -25,8 +25,10 @@
 // write; only if those lists overflow as well is the row read once more to rank and write.
 //
 // Layout: wavefront w of 16 walks the w-th sixteenth of the row, lane l owning G consecutive columns of
-// each 64*G-column load (G = 4: 128-bit loads), so that a wavefront meets its columns in ascending order.
-// Loads are ordinary cached loads: the row is read again by the next pass.
+// each 64*G-column load (G = 4: 128-bit loads, from any element boundary), so that a wavefront meets its
+// columns in ascending order; the last M % G columns are loaded one per lane by the last wavefront when it is
+// through with its share.  Loads of the search passes are ordinary cached loads: the row is read again by the
+// next pass.
 //
 // Nothing but registers and LDS is used; the library still allocates nothing.  One workgroup per row
 // means that a launch of fewer rows than the GPU has compute units leaves the rest idle.
@@ -50,15 +52,10 @@ constexpr int kKeptPerWave = 256;  // at least one load of a wavefront (the firs
 
 template <int G>
 __device__ __forceinline__ void stream_load(const float* p, float (&v)[G]) {
-  if constexpr (G == 4) {
-    const float4 q = *reinterpret_cast<const float4*>(p);
-    v[0] = q.x;
-    v[1] = q.y;
-    v[2] = q.z;
-    v[3] = q.w;
-  } else {
-    v[0] = *p;
-  }
+  typedef float fG __attribute__((ext_vector_type(G), aligned(4)));
+  const fG q = *reinterpret_cast<const fG*>(p);
+#pragma unroll
+  for (int c = 0; c < G; ++c) v[c] = q[c];
 }
 
 template <int G, int MODE, bool NEG>
@@ -104,7 +101,10 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
   };
 
   constexpr int kUnit = kWave * G;  // columns a wavefront covers per load
-  const int units = (M + kUnit - 1) / kUnit;
+  const int rest = M % G, Mv = M - rest;  // the last `rest` columns: one per lane of the last wavefront
+  const bool has_rest = rest != 0 && wave == kStreamWaves - 1;
+  const bool my_rest = has_rest && lane < rest;
+  const int units = (Mv + kUnit - 1) / kUnit;
   const int u0 = (int)((int64_t)units * wave / kStreamWaves), u1 = (int)((int64_t)units * (wave + 1) / kStreamWaves);
   const int trips = (units + kStreamWaves - 1) / kStreamWaves;  // no wavefront has more loads than this
   // A wavefront keeps kAhead loads in flight in a ring of registers: a slot is worked on, then loaded again
@@ -115,14 +115,14 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
     // looked at; a conditional load would make the compiler wait for all loads in flight at every use)
     const int u = u0 + i;
     const int c0 = u * kUnit + lane * G;
-    stream_load<G>(row + ((u < u1 && c0 < M) ? c0 : 0), slot);
+    stream_load<G>(row + ((u < u1 && c0 < Mv) ? c0 : 0), slot);
   };
   // The same with the non-temporal hint, for pass 0: as a rule the row is not read again, and streaming
   // loads that do not displace each other's lines from the caches run faster (see rtopk_kernel.hpp).
   auto load_slot_once = [&](int i, float (&slot)[G]) {
     const int u = u0 + i;
     const int c0 = u * kUnit + lane * G;
-    load_group<kF32, G>(row, (u < u1 && c0 < M) ? c0 : 0, slot);
+    load_group<kF32, G>(row, (u < u1 && c0 < Mv) ? c0 : 0, slot);
   };
   uint2* kept = &s_kept[wave][0];
   if (tid < 2 * kLeaves) s_parts[tid >> kLevels][tid & (kLeaves - 1)] = 0;  // the third is cleared by the first raise
@@ -146,24 +146,24 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
   bool void0 = false;      // the list ran full: no selection from lists for this row
   {
     float mx = -__builtin_inff(), nm = -__builtin_inff();
-    auto take = [&](const float (&v)[G], int u) {  // one load of the wavefront, already in registers
+    // One load of the wavefront, already in registers: B columns from c0 on in the lanes where `valid`.
+    auto take = [&](const auto& v, int c0, bool valid) {
       // No branch before the one that skips the list: every branch between a load's issue and its use
       // makes the compiler wait for all loads in flight instead of this one.
-      const int c0 = u * kUnit + lane * G;
-      const bool valid = u < u1 && c0 < M;
-      bool keep[G], any_keep = false;
+      constexpr int B = sizeof(v) / sizeof(float);
+      bool keep[B], any_keep = false;
 #pragma unroll
-      for (int c = 0; c < G; ++c) {
+      for (int c = 0; c < B; ++c) {
         mx = vmax(mx, valid ? v[c] : -__builtin_inff());
         nm = vmax_an(nm, valid ? v[c] : __builtin_inff());
         keep[c] = valid && keyof<NEG>(v[c]) >= T0;
         any_keep = any_keep || keep[c];
       }
       if (void0 || __builtin_amdgcn_ballot_w64(any_keep) == 0) return;
-      uint64_t m[G];
+      uint64_t m[B];
       uint32_t pos = n0, total = 0;
 #pragma unroll
-      for (int c = 0; c < G; ++c) {
+      for (int c = 0; c < B; ++c) {
         m[c] = __builtin_amdgcn_ballot_w64(keep[c]);
         pos = lanes_below(m[c], pos);
         total += (uint32_t)__builtin_popcountll(m[c]);
@@ -173,7 +173,7 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
         return;
       }
 #pragma unroll
-      for (int c = 0; c < G; ++c) {
+      for (int c = 0; c < B; ++c) {
         if (keep[c]) kept[pos] = make_uint2(__float_as_uint(v[c]), (uint32_t)(c0 + c));
         pos += keep[c] ? 1u : 0u;
       }
@@ -282,7 +282,8 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
     for (int i = 0; i < trips; i += kAhead) {
 #pragma unroll
       for (int j = 0; j < kAhead; ++j) {
-        take(ring[j], u0 + i + j);
+        const int u = u0 + i + j, c0 = u * kUnit + lane * G;
+        take(ring[j], c0, u < u1 && c0 < Mv);
         load_slot_once(i + j + kAhead, ring[j]);
         const int done = i + j + 1;
         if (done < trips && (done == 1 || done == next_raise)) {
@@ -290,6 +291,10 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
           raise_floor();
         }
       }
+    }
+    if (has_rest) {  // uniform over the wavefront
+      const float v[1] = {row[my_rest ? Mv + lane : 0]};
+      take(v, Mv + lane, my_rest);
     }
     float wmax, wmin;
     wave_max_and_negmin(mx, nm, wmax, wmin);
@@ -318,12 +323,13 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
   auto count_pass = [&](float t) -> int {
     int mine = 0;
 #pragma unroll 4
-    for (int c0 = tid * G; c0 < M; c0 += kChunk) {
+    for (int c0 = tid * G; c0 < Mv; c0 += kChunk) {
       float v[G];
       stream_load<G>(row + c0, v);
 #pragma unroll
       for (int c = 0; c < G; ++c) mine += keyof<NEG>(v[c]) >= t ? 1 : 0;
     }
+    if (my_rest) mine += keyof<NEG>(row[Mv + lane]) >= t ? 1 : 0;
     mine = wave_sum(mine);
     __syncthreads();  // s_above may still be read from an earlier use
     if (lane == 0) s_above[wave] = mine;
@@ -536,17 +542,13 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
         }
       }
     };
-    // One load of the wavefront (64 * G columns from unit u on), already in registers.
-    auto process = [&](const float (&v)[G], int u) {
-      // (this early exit makes the compiler wait for all loads in flight here; leaving it out, as pass 0
-      // does, costs this pass registers it does not have: 18 spill, 1024 x 262144 with k = 2000 700 -> 779 us)
-      if (u >= u1) return;  // uniform over the wavefront
-      const int c0 = u * kUnit + lane * G;
-      const bool valid = c0 < M;
-      bool keep[G];
+    // One load of the wavefront, already in registers: B columns from c0 on in the lanes where `valid`.
+    auto process = [&](const auto& v, int c0, bool valid) {
+      constexpr int B = sizeof(v) / sizeof(float);
+      bool keep[B];
       bool any_keep = false;
 #pragma unroll
-      for (int c = 0; c < G; ++c) {
+      for (int c = 0; c < B; ++c) {
         const float key = keyof<NEG>(v[c]);
         above += (valid && key >= hi) ? 1 : 0;
         keep[c] = valid && key >= bstar;
@@ -554,10 +556,10 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
       }
       // once bstar has risen most loads of a wavefront hold no such key at all: one scalar branch
       if (__builtin_amdgcn_ballot_w64(any_keep) == 0) return;
-      uint64_t m[G];
+      uint64_t m[B];
       uint32_t pos = 0, total = 0;
 #pragma unroll
-      for (int c = 0; c < G; ++c) {
+      for (int c = 0; c < B; ++c) {
         m[c] = __builtin_amdgcn_ballot_w64(keep[c]);
         pos = lanes_below(m[c], pos);
         total += (uint32_t)__builtin_popcountll(m[c]);
@@ -572,7 +574,7 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
       }
       pos += n_kept;
 #pragma unroll
-      for (int c = 0; c < G; ++c) {
+      for (int c = 0; c < B; ++c) {
         if (keep[c]) kept[pos] = make_uint2(__float_as_uint(v[c]), (uint32_t)(c0 + c));
         pos += keep[c] ? 1u : 0u;
       }
@@ -586,7 +588,11 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
     for (int i = 0; i < trips; i += kAhead) {
 #pragma unroll
       for (int j = 0; j < kAhead; ++j) {
-        process(ring[j], u0 + i + j);
+        const int u = u0 + i + j, c0 = u * kUnit + lane * G;
+        // (skipping a load beyond the wavefront's share makes the compiler wait for all loads in flight here; going
+        // through with it, as pass 0 does, costs this pass registers it does not have: 18 spill, 1024 x 262144 with
+        // k = 2000 700 -> 779 us)
+        if (u < u1) process(ring[j], c0, c0 < Mv);  // uniform over the wavefront
         load_slot(i + j + kAhead, ring[j]);
         const int done = i + j + 1;
         if (done < trips && (done == 1 || done == next_sync)) {
@@ -594,6 +600,10 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
           raise_bstar();
         }
       }
+    }
+    if (has_rest) {  // uniform over the wavefront
+      const float v[1] = {row[my_rest ? Mv + lane : 0]};
+      process(v, Mv + lane, my_rest);
     }
     count_pending();
     kept_valid = true;
@@ -747,41 +757,47 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
   if (k <= kStreamWaves * kListPerWave) {
     uint2* list = reinterpret_cast<uint2*>(&s_hist[wave][0]);
     uint32_t wn = 0;  // candidates met by this wavefront
+    auto scan = [&](const auto& v, int c0, bool valid) {
+      constexpr int B = sizeof(v) / sizeof(float);
+      bool cand[B], any = false;
+#pragma unroll
+      for (int c = 0; c < B; ++c) {
+        const float key = keyof<NEG>(v[c]);
+        cand[c] = valid && (key >= tA || (limB > 0 && key >= tB));
+        any = any || cand[c];
+      }
+      if (__builtin_amdgcn_ballot_w64(any) == 0) return;  // most loads of a wide row hold no candidate
+      uint64_t m[B];
+      uint32_t pos = wn;
+#pragma unroll
+      for (int c = 0; c < B; ++c) {
+        m[c] = __builtin_amdgcn_ballot_w64(cand[c]);
+        pos = lanes_below(m[c], pos);
+      }
+#pragma unroll
+      for (int c = 0; c < B; ++c) {
+        if (cand[c] && pos < (uint32_t)kListPerWave) list[pos] = make_uint2(__float_as_uint(v[c]), (uint32_t)(c0 + c));
+        pos += cand[c] ? 1u : 0u;
+        wn += (uint32_t)__builtin_popcountll(m[c]);
+      }
+    };
     float ring[kAhead][G];
 #pragma unroll
     for (int j = 0; j < kAhead; ++j) load_slot(j, ring[j]);
     for (int i = 0; i < u1 - u0 && wn <= (uint32_t)kListPerWave; i += kAhead) {  // an overflowing list ends the attempt
 #pragma unroll
       for (int j = 0; j < kAhead; ++j) {
-        const int u = u0 + i + j;
-        const int c0 = u * kUnit + lane * G;
-        const bool valid = u < u1 && c0 < M;
+        const int u = u0 + i + j, c0 = u * kUnit + lane * G;
         float v[G];
-        bool cand[G], any = false;
 #pragma unroll
-        for (int c = 0; c < G; ++c) {
-          v[c] = ring[j][c];
-          const float key = keyof<NEG>(v[c]);
-          cand[c] = valid && (key >= tA || (limB > 0 && key >= tB));
-          any = any || cand[c];
-        }
+        for (int c = 0; c < G; ++c) v[c] = ring[j][c];
         load_slot(i + j + kAhead, ring[j]);
-        if (__builtin_amdgcn_ballot_w64(any) != 0) {  // most loads of a wide row hold no candidate
-          uint64_t m[G];
-          uint32_t pos = wn;
-#pragma unroll
-          for (int c = 0; c < G; ++c) {
-            m[c] = __builtin_amdgcn_ballot_w64(cand[c]);
-            pos = lanes_below(m[c], pos);
-          }
-#pragma unroll
-          for (int c = 0; c < G; ++c) {
-            if (cand[c] && pos < (uint32_t)kListPerWave) list[pos] = make_uint2(__float_as_uint(v[c]), (uint32_t)(c0 + c));
-            pos += cand[c] ? 1u : 0u;
-            wn += (uint32_t)__builtin_popcountll(m[c]);
-          }
-        }
+        scan(v, c0, u < u1 && c0 < Mv);
       }
+    }
+    if (has_rest) {  // uniform over the wavefront
+      const float v[1] = {row[my_rest ? Mv + lane : 0]};
+      scan(v, Mv + lane, my_rest);
     }
     if (write_from_lists(list, wn, (uint32_t)kListPerWave, true)) return;
   }
@@ -789,8 +805,6 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
   // General form: chunk by chunk, the candidates' ranks through one barrier per chunk.
   uint32_t baseA = 0, baseB = 0;  // candidates of either class in earlier chunks (uniform)
   int parity = 0;
-  float nv[G];  // loaded one chunk ahead
-  if (tid * G < M) stream_load<G>(row + tid * G, nv);
   for (int cb = 0; cb < M; cb += kChunk) {
     const uint32_t selA0 = baseA < (uint32_t)limA ? baseA : (uint32_t)limA;
     const uint32_t selB0 = baseB < (uint32_t)limB ? baseB : (uint32_t)limB;
@@ -799,20 +813,18 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
     float v[G];
     bool a[G], b[G];
     uint32_t mine = 0;  // own candidates: A in the low half, B in the high half
-    if (c0 < M) {
-#pragma unroll
-      for (int c = 0; c < G; ++c) v[c] = nv[c];
-      if (c0 + kChunk < M) stream_load<G>(row + c0 + kChunk, nv);
-#pragma unroll
-      for (int c = 0; c < G; ++c) {
-        const float key = keyof<NEG>(v[c]);
-        a[c] = key >= tA;
-        b[c] = limB > 0 && key >= tB && !a[c];
-        mine += (a[c] ? 1u : 0u) + (b[c] ? 0x10000u : 0u);
-      }
+    if (c0 < Mv) {
+      stream_load<G>(row + c0, v);
     } else {
 #pragma unroll
-      for (int c = 0; c < G; ++c) a[c] = b[c] = false;
+      for (int c = 0; c < G; ++c) v[c] = row[c0 + c < M ? c0 + c : 0];
+    }
+#pragma unroll
+    for (int c = 0; c < G; ++c) {
+      const float key = keyof<NEG>(v[c]);
+      a[c] = c0 + c < M && key >= tA;
+      b[c] = c0 + c < M && limB > 0 && key >= tB && !a[c];
+      mine += (a[c] ? 1u : 0u) + (b[c] ? 0x10000u : 0u);
     }
     const uint32_t incl = wave_inclusive_scan_dpp(mine);
     if (lane == kWave - 1) s_pre[parity][wave] = (int)incl;
@@ -843,10 +855,10 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
   }
 }
 
-template <int G, int MODE, bool NEG>
+template <int MODE, bool NEG>
 hipError_t launch_stream(const LaunchArgs& a) {
   if (a.N > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-  return launch_kernel(rtopk_stream_kernel<G, MODE, NEG>, dim3((unsigned)a.N), dim3(kStreamThreads), 0, a.stream,
+  return launch_kernel(rtopk_stream_kernel<4, MODE, NEG>, dim3((unsigned)a.N), dim3(kStreamThreads), 0, a.stream,
                        static_cast<const float*>(a.in), a.N, a.M, a.k, a.max_iter, a.eps_rel,
                        static_cast<float*>(a.out_vals), static_cast<int32_t*>(a.out_idx), a.out_iters);
 }
