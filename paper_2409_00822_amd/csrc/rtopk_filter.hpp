@@ -1,0 +1,399 @@
+// Selection of a wide row from the few elements that can matter (gfx950).  Included by rtopk_kernel.hpp, inside
+// namespace rtopk, behind the cross-lane helpers; used by rtopk_block_kernel.hpp.
+//
+// Algorithms 1 and 2 (RTop-K, arXiv 2409.00822, Section 3.1) look at a count only to compare it with k.  For any
+// floor T0 with more than k keys at or above it, the count at a threshold t <= T0 is therefore known to exceed k,
+// and the count at t > T0 needs only the keys at or above T0.  A floor close to the k-th key costs almost nothing:
+// every lane's maximum over a group of 16 elements is one element of the row, so the (k + 1)-th largest of those
+// maxima has at least k + 1 keys at or above it -- and, being one of every 16th element's best, only about
+// 1.2 to 1.4 k in all.  Finding it takes a bisection over E / 16 registers instead of E.  Then:
+//   1. the floor: every wavefront bisects its own group maxima for its share of the k + 1 (no barrier), the row's
+//      floor is the smallest of the wavefronts' floors (one exchange, the one that the minimum and maximum need);
+//   2. the quads (four consecutive elements) with a key at or above the floor go to a list in LDS, any order: a
+//      lane's quads are the set bits of one word, the lanes' counts are scanned, and every quad is stored -- members
+//      to the lane's next slot, the others to a dummy slot of the lane -- with no lane mask and no branch;
+//   3. their elements at or above the floor go to a list of (value, column) singles;
+//   4. one wavefront runs the search on the singles, 64 to a register, with no barrier;
+//   5. the winners' places in column order come from a bitmap over the row's columns: prefix popcounts.
+// Thresholds, branches, exit iteration and result are those of the search over the whole row.  What a list does not
+// hold (a row whose values crowd, k too large for the lists, a last threshold below the floor) is left to the
+// caller's full-width search.
+//
+// What bounds it: a row's elements are touched twice (maxima, then quad maxima against the floor; 5 vector
+// instructions per four elements in all, and 8 plus two LDS writes per quad to store it) where the search over the
+// whole row takes two instructions per element and STEP, 6 to 9 steps of them, a gather and a ranking of every
+// element.  Issue time per wavefront of 64 values per lane falls from about 6000 cycles to about 1200.
+
+// max of the keys a, b, c; of the key k and the keys a, b; and the same of the negated keys
+template <bool NEG>
+__device__ __forceinline__ float key_max3(float a, float b, float c) {
+  return NEG ? vmax3_nnn(a, b, c) : vmax3(a, b, c);
+}
+template <bool NEG>
+__device__ __forceinline__ float key_max3_on(float m, float a, float b) {
+  return NEG ? vmax3_ann(m, a, b) : vmax3(m, a, b);
+}
+template <bool NEG>
+__device__ __forceinline__ float key_max_on(float m, float a) {
+  return NEG ? vmax_an(m, a) : vmax(m, a);
+}
+
+// Largest of the lane's negated keys (-min).
+template <int E, bool NEG>
+__device__ __forceinline__ float lane_negmin(const float (&x)[E]) {
+  float nm = key_max3<!NEG>(x[0], x[1], x[2]);
+#pragma unroll
+  for (int e = 3; e + 1 < E; e += 2) nm = key_max3_on<!NEG>(nm, x[e], x[e + 1]);
+  return E % 2 == 0 ? key_max_on<!NEG>(nm, x[E - 1]) : nm;
+}
+
+// Group maxima: gm[j] = largest key of elements 16 j .. 16 j + 15.
+constexpr int kFilterGroup = 16;
+template <int E, bool NEG>
+__device__ __forceinline__ void lane_group_maxima(const float (&x)[E], float (&gm)[E / kFilterGroup]) {
+  static_assert(E % kFilterGroup == 0, "whole groups only");
+#pragma unroll
+  for (int j = 0; j < E / kFilterGroup; ++j) {
+    float m = key_max3<NEG>(x[16 * j], x[16 * j + 1], x[16 * j + 2]);
+#pragma unroll
+    for (int c = 3; c + 1 < kFilterGroup; c += 2) m = key_max3_on<NEG>(m, x[16 * j + c], x[16 * j + c + 1]);
+    gm[j] = key_max_on<NEG>(m, x[16 * j + 15]);
+  }
+}
+
+// A floor under at least `need` of the wavefront's group maxima, as close to the need-th as a few bisection steps
+// between `low` (no larger than any key of the wavefront's) and `high` (its largest key) bring it; `above` is left at
+// the lowest bound tried with fewer than `need` maxima at or above it.  With NaN or infinite keys any value may
+// come out.
+template <int J>
+__device__ __forceinline__ float floor_of_maxima(const float (&gm)[J], int need, float low, float high, float& above) {
+  const int enough = need + (need >> 3) + 1;
+  for (int step = 0; step < 12; ++step) {
+    const float mid = (low + high) * 0.5f;
+    int cnt = 0;
+#pragma unroll
+    for (int j = 0; j < J; ++j) cnt += __builtin_popcountll(__builtin_amdgcn_ballot_w64(gm[j] >= mid));
+    if (cnt >= need) {
+      low = mid;
+      if (cnt <= enough) break;
+    } else {
+      high = mid;
+    }
+  }
+  above = high;
+  return low;
+}
+
+// The largest value on the row type's grid (see midpoint_exact) that is not above t.
+template <int DT>
+__device__ __forceinline__ float grid_floor(float t) {
+  if constexpr (DT == kF32) {
+    return t;
+  } else {
+    constexpr uint32_t mask = DT == kBF16 ? 0xffff0000u : 0xffffe000u;
+    const uint32_t u = __float_as_uint(t), m = u & mask;
+    return __uint_as_float(u != m && (u >> 31) != 0 ? m + ~mask + 1u : m);
+  }
+}
+
+// LDS of one row.  CAP: quads, and singles, that the lists hold.  The bitmaps take the quads' place when those
+// have become singles.
+template <int W>
+struct FilterLds {
+  static constexpr int CAP = W == 4 ? 512 : 1024;
+  static constexpr int WORDS = 128 * W;  // bitmap words: two per thread, 64 * 64 * W columns
+  struct Lists {
+    float4 quad[CAP + kWave];    // behind the list: a dummy slot per lane, shared by the wavefronts, never read
+    uint32_t id[CAP + kWave];    // (quad of the lane) << 16 | thread
+  };
+  struct Maps {
+    uint2 cut[WORDS / 2], chosen[WORDS / 2];
+    uint32_t before[WORDS / 2];  // per thread: set bits in lower threads of its wavefront, and those plus its first word's
+  };
+  union {
+    Lists lists;
+    Maps maps;
+  };
+  uint2 single[CAP];             // (value bits, column)
+  int n_quads, n_singles;
+  int wave_bits[W];
+  float thr[2];
+  int info[3];                   // limit of the cut class (0: none), exit iteration, split column
+  int state;
+};
+
+enum FilterResult : int {
+  kFilterDone = 0,      // the pairs are written (or, in the dense form, the thresholds and the split are set)
+  kFilterNoList = 1,    // the lists do not hold the row: the whole search is the caller's
+  kFilterBoundOnly = 2  // the search has run, but its last threshold lies below the floor: the selection is the caller's
+};
+
+// Whether k is small enough for the lists; host and device agree through this rule alone.  Half a list: the floor's
+// candidates are 1.2 to 1.4 k plus the spread of the wavefronts' floors.
+template <int W>
+constexpr int filter_max_k() {
+  return FilterLds<W>::CAP / 2;
+}
+
+// Positions of the set bits of one bitmap: `before` and `wave_bits` for the words of `map`.  Called by the whole
+// workgroup with a barrier before it; contains one.
+template <int W>
+__device__ __forceinline__ void filter_prefix(FilterLds<W>& s, const uint2* map, int lane, int wave) {
+  const int tid = wave * kWave + lane;
+  const uint2 w = map[tid];
+  const uint32_t n0 = (uint32_t)__builtin_popcount(w.x), n = n0 + (uint32_t)__builtin_popcount(w.y);
+  const uint32_t incl = wave_inclusive_scan_dpp(n);
+  s.maps.before[tid] = (incl - n) | ((incl - n + n0) << 16);
+  if (lane == kWave - 1) s.wave_bits[wave] = (int)incl;
+  __syncthreads();
+}
+// Set bits of the map below column `col`.
+template <int W>
+__device__ __forceinline__ uint32_t filter_rank(const FilterLds<W>& s, const uint2* map, int col) {
+  const int word = col >> 5, owner = word >> 1;
+  const uint32_t b = s.maps.before[owner];
+  const uint2 w = map[owner];
+  const uint32_t bits = (word & 1) ? w.y : w.x;
+  uint32_t r = ((word & 1) ? b >> 16 : b & 0xffffu) + (uint32_t)__builtin_popcount(bits & ((1u << (col & 31)) - 1u));
+  const int owner_wave = owner >> 6;
+#pragma unroll
+  for (int w2 = 0; w2 + 1 < W; ++w2) r += w2 < owner_wave ? (uint32_t)s.wave_bits[w2] : 0u;
+  return r;
+}
+
+// Step 4, by one wavefront: the search on the singles.  SR registers per lane hold them.
+template <int SR, int MODE, bool NEG, int DT>
+__device__ __forceinline__ void filter_search(const uint2* single, int n, int lane, int k, int max_iter, float eps,
+                                              float T0, float probe, float& lo, float& hi, float& thres, bool& hit,
+                                              int& steps, int& last_cnt, int& na) {
+  float key[SR];
+#pragma unroll
+  for (int i = 0; i < SR; ++i) {
+    const int j = i * kWave + lane;
+    const uint32_t v = single[j < n ? j : 0].x;
+    key[i] = j < n ? keyof<NEG>(__uint_as_float(v)) : -__builtin_inff();
+  }
+  auto count = [&](float t) -> int {
+    int c = 0;
+#pragma unroll
+    for (int i = 0; i < SR; ++i) c += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[i] >= t));
+    return c;
+  };
+  hit = false;
+  steps = 0;
+  last_cnt = -1;
+  if constexpr (MODE == kEarly) {
+    for (int it = 0; it < max_iter; ++it) {
+      const float mid = (lo + hi) * 0.5f;
+      const int cnt = mid > T0 ? count(mid) : k + 1;  // more than k keys are at or above the floor
+      last_cnt = cnt;
+      move_bound(lo, hi, mid, cnt, k);
+      if (cnt == k) break;
+    }
+  } else {
+    if constexpr (MODE == kExact) {
+      // the answer does not depend on the thresholds: start at the floor, and try first the lowest bound that had
+      // too few group maxima above it, which is usually just above the k-th key
+      lo = grid_floor<DT>(T0);
+      const float p = grid_floor<DT>(probe);
+      if (p > lo && p < hi) {
+        const int cnt = count(p);
+        thres = p;
+        if (cnt == k) hit = true;
+        move_bound(lo, hi, p, cnt, k);
+      }
+    }
+    while (!hit) {
+      if constexpr (MODE == kEps) {
+        if (!(hi - lo > eps)) break;
+      }
+      const float mid = MODE == kEps ? (lo + hi) * 0.5f : midpoint_exact<DT>(lo, hi);
+      if (!(mid > lo && mid < hi)) break;
+      thres = mid;
+      ++steps;
+      const int cnt = mid > T0 ? count(mid) : k + 1;
+      if (cnt == k) hit = true;
+      if (!hit) move_bound(lo, hi, mid, cnt, k);
+    }
+    na = hit ? k : count(hi);  // hi is at or above the floor: it is the largest key or has counted fewer than k
+  }
+}
+
+// Steps 2 to 5 for one row, by the whole workgroup (W wavefronts).  x: the row's elements, masked (a key of -inf past
+// the row's end).  lo, hi: the keys' minimum and maximum; T0 the row's floor, probe see filter_search.  Before the call
+// n_quads and n_singles are zero and a barrier has passed.  column(quad of the lane, thread): the quad's first column.
+// listed(): called once x is no longer needed here.  emit(place, value, column).
+// In the dense form nothing is emitted and thi, tlo, split say which elements stay:
+// key >= (column <= split ? tlo : thi).  Every wavefront takes the same branches.
+template <int E, int W, int MODE, bool NEG, int DT, bool DENSE, typename Column, typename Listed, typename Emit>
+__device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], int lane, int wave, int k, int max_iter,
+                                          float eps, float T0, float probe, float& lo, float hi, float& thi, float& tlo,
+                                          int& split, int& iterations, Column column, Listed listed, Emit emit) {
+  constexpr int CAP = FilterLds<W>::CAP, Q = E / 4;
+  static_assert(Q <= 32, "a lane's quads are the bits of one word");
+  const int tid = wave * kWave + lane;
+
+  // Step 2.  Bit Q - 1 - q of `member`: quad q has a key at or above T0 (the sign of key - T0, see count_ge_wide).
+  {
+    const float tz = T0 == 0.0f ? -0.0f : T0;
+    uint32_t below = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const float m = key_max_on<NEG>(key_max3<NEG>(x[4 * q], x[4 * q + 1], x[4 * q + 2]), x[4 * q + 3]);
+      below = __builtin_amdgcn_alignbit(below, __float_as_uint(m - tz), 31);
+    }
+    uint32_t member = ~below & (Q == 32 ? 0xffffffffu : (1u << Q) - 1u);
+    const uint32_t n_lane = (uint32_t)__builtin_popcount(member);
+    const uint32_t incl = wave_inclusive_scan_dpp(n_lane);
+    const int n_wave = __builtin_amdgcn_readlane((int)incl, kWave - 1);
+    int base = 0;
+    if (lane == 0) base = atomicAdd(&s.n_quads, n_wave);
+    base = __builtin_amdgcn_readfirstlane(base);
+    if (base + n_wave > CAP) member = 0;  // uniform: n_quads says that the list is not whole
+    int slot = base + (int)incl - 1;  // the lane's slots are filled from its last one downwards
+    const int dummy = CAP + lane;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe(member, (uint32_t)(Q - 1 - q), 1u);  // all ones for a member
+      const int to = (int)select_bits(m, (uint32_t)slot, (uint32_t)dummy);
+      s.lists.quad[to] = make_float4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]);
+      s.lists.id[to] = (uint32_t)(q << 16) | (uint32_t)tid;
+      slot += (int)m;
+    }
+  }
+  listed();
+  __syncthreads();
+  const int n_quads = __builtin_amdgcn_readfirstlane(s.n_quads);
+  if (n_quads > CAP) return kFilterNoList;
+
+  // Step 3.
+  for (int j0 = 0; j0 < n_quads; j0 += W * kWave) {
+    if (j0 + wave * kWave >= n_quads) break;  // uniform over the wavefront
+    const int j = j0 + tid;
+    const bool live = j < n_quads;
+    const float4 v = s.lists.quad[live ? j : 0];
+    const uint32_t id = s.lists.id[live ? j : 0];
+    const float e[4] = {v.x, v.y, v.z, v.w};
+    bool keep[4];
+    uint32_t n = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      keep[c] = live && keyof<NEG>(e[c]) >= T0;
+      n += keep[c] ? 1u : 0u;
+    }
+    const uint32_t incl = wave_inclusive_scan_dpp(n);
+    const int n_wave = __builtin_amdgcn_readlane((int)incl, kWave - 1);
+    int base = 0;
+    if (lane == 0) base = atomicAdd(&s.n_singles, n_wave);
+    base = __builtin_amdgcn_readfirstlane(base);
+    int at = base + (int)(incl - n);
+    const int col = column((int)(id >> 16), (int)(id & 0xffffu));
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (keep[c] && at < CAP) s.single[at] = make_uint2(__float_as_uint(e[c]), (uint32_t)(col + c));
+      at += keep[c] ? 1 : 0;
+    }
+  }
+  __syncthreads();
+  const int n = __builtin_amdgcn_readfirstlane(s.n_singles);
+  if (n > CAP || n <= k) return kFilterNoList;  // (n <= k only with NaN or infinite keys)
+
+  // Step 4 by wavefront 0, while every thread clears its words of the bitmaps.
+  s.maps.cut[tid] = make_uint2(0u, 0u);
+  s.maps.chosen[tid] = make_uint2(0u, 0u);
+  if (wave == 0) {
+    float l = lo, h = hi, thres = lo;
+    bool hit = false;
+    int steps = 0, cnt = -1, na = 0;
+    if (n <= 4 * kWave) {
+      filter_search<4, MODE, NEG, DT>(s.single, n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
+    } else if (n <= 8 * kWave || CAP <= 8 * kWave) {
+      filter_search<8, MODE, NEG, DT>(s.single, n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
+    } else {
+      filter_search<CAP / kWave, MODE, NEG, DT>(s.single, n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
+    }
+    // The selection as two thresholds and a limit: everything at or above t_hi, and of [t_lo, t_hi) the first `limit`
+    // in column order (no limit: 0).
+    const float inf = __builtin_inff();
+    float t_hi, t_lo;
+    int limit = 0;
+    bool listed = true;
+    if constexpr (MODE == kEarly) {
+      t_lo = l;
+      t_hi = cnt == k ? l : inf;
+      limit = cnt == k ? 0 : k;
+      listed = l >= T0;
+    } else {
+      if (hit) {
+        t_hi = t_lo = thres;
+      } else if (na >= k) {
+        t_hi = inf;
+        t_lo = h;
+        limit = k;
+      } else {
+        t_hi = h;
+        t_lo = l;
+        limit = k - na;
+        // exact mode has converged: [l, h) holds one value, which is on the list even where l is below the floor
+        if constexpr (MODE == kEps) listed = l >= T0;
+      }
+    }
+    if (lane == 0) {
+      s.thr[0] = MODE == kEarly ? l : t_hi;  // the caller's selection, where the list has none, needs the bound itself
+      s.thr[1] = t_lo;
+      s.info[0] = limit;
+      s.info[1] = hit ? steps : steps + 1;
+      s.info[2] = 0x7fffffff;
+      s.state = (listed ? 0 : 1) | (MODE == kEarly && cnt != k ? 2 : 0);
+    }
+  }
+  __syncthreads();
+  const int state = __builtin_amdgcn_readfirstlane(s.state);
+  tlo = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.thr[1])));
+  thi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.thr[0])));
+  if (MODE == kEarly) thi = (state & 2) != 0 ? __builtin_inff() : thi;
+  const int limit = __builtin_amdgcn_readfirstlane(s.info[0]);
+  iterations = __builtin_amdgcn_readfirstlane(s.info[1]);
+  split = 0x7fffffff;
+  if ((state & 1) != 0) {
+    if (MODE == kEarly) lo = tlo;
+    return kFilterBoundOnly;
+  }
+
+  // Step 5.  The cut class first, where there is one: the column of its limit-th member.
+  if (limit > 0) {
+    for (int j = tid; j < n; j += W * kWave) {
+      const uint2 e = s.single[j];
+      const float key = keyof<NEG>(__uint_as_float(e.x));
+      if (key >= tlo && !(key >= thi)) atomicOr(reinterpret_cast<uint32_t*>(s.maps.cut) + (e.y >> 5), 1u << (e.y & 31));
+    }
+    __syncthreads();
+    filter_prefix<W>(s, s.maps.cut, lane, wave);
+    for (int j = tid; j < n; j += W * kWave) {
+      const uint2 e = s.single[j];
+      const float key = keyof<NEG>(__uint_as_float(e.x));
+      if (key >= tlo && !(key >= thi) && filter_rank<W>(s, s.maps.cut, (int)e.y) == (uint32_t)(limit - 1)) s.info[2] = (int)e.y;
+    }
+    __syncthreads();
+    split = __builtin_amdgcn_readfirstlane(s.info[2]);
+  }
+  if constexpr (!DENSE) {
+    auto is_chosen = [&](const uint2& e) {
+      return keyof<NEG>(__uint_as_float(e.x)) >= ((int)e.y <= split ? tlo : thi);
+    };
+    for (int j = tid; j < n; j += W * kWave) {
+      const uint2 e = s.single[j];
+      if (is_chosen(e)) atomicOr(reinterpret_cast<uint32_t*>(s.maps.chosen) + (e.y >> 5), 1u << (e.y & 31));
+    }
+    __syncthreads();
+    filter_prefix<W>(s, s.maps.chosen, lane, wave);
+    for (int j = tid; j < n; j += W * kWave) {
+      const uint2 e = s.single[j];
+      if (is_chosen(e)) {
+        const uint32_t place = filter_rank<W>(s, s.maps.chosen, (int)e.y);
+        if (place < (uint32_t)k) emit((int)place, e.x, (int)e.y);
+      }
+    }
+  }
+  return kFilterDone;
+}

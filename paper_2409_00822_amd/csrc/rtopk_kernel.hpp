@@ -40,7 +40,7 @@ constexpr int kWave = 64;
 //   G == 0: NG values per lane in groups of 4, 4, ..., then 2 and 1 as the bits of NG say: rows of 129..192 and
 //           257..448 columns then carry at most 63 columns of padding instead of up to 127 (255 for the old
 //           two groups of four), and both the search (a compare, a popcount and an add per value and step) and
-//           the ranking shrink with it.  100003 x 333, k = 33, f32: eight values per lane 41 us, six 31 us.
+//           the ranking shrink with it.  100003 x 333, k = 33, f32: eight values per lane and scalar loads 41.2 us, six 36.4 us.
 // CERTAIN: the leading groups that lie inside every row the layout is used for (the launchers check it), so
 // that only the groups behind them need column-validity tests.
 template <int G, int NG>
@@ -297,7 +297,7 @@ __device__ __forceinline__ int count_ge_wide(const float (&x)[E], float t) {
     uint32_t below = 0, pack = 0;
 #pragma unroll
     for (int e = 0; e < ACC; ++e) {
-      const float d = keyof<NEG>(x[e]) - tz;
+      const float d = NEG ? -tz - x[e] : x[e] - tz;
       pack = __builtin_amdgcn_alignbit(pack, __float_as_uint(d), 31);  // (pack << 1) | sign(d)
       if ((e & 31) == 31 || e + 1 == ACC) {
         below += (uint32_t)__builtin_popcount(pack);
@@ -600,7 +600,7 @@ __device__ __forceinline__ void lane_below_packs(const float (&x)[E], float t, u
   uint32_t pack = 0;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    const float d = keyof<NEG>(x[e]) - tz;
+    const float d = NEG ? -tz - x[e] : x[e] - tz;  // key - t, without a register for the negated value
     pack = __builtin_amdgcn_alignbit(pack, __float_as_uint(d), 31);  // (pack << 1) | sign(d)
     if ((e & 31) == 31 || e + 1 == E) {
       p[e / 32] = pack;
@@ -771,6 +771,8 @@ __device__ __forceinline__ void search_band(const float (&band)[BR], int above, 
     move_bound(lo, hi, thres, cnt, k);
   }
 }
+
+#include "rtopk_filter.hpp"
 
 // How many of a wide row's E values per lane are counted per lane (reduced over the wavefront once per
 // step) rather than by mask popcount on the scalar unit (see count_ge_wide).  From sweeps on MI355X:
