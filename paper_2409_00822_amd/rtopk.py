@@ -1,4 +1,5 @@
-"""ctypes binding with the same names as the C ABI (include/rtopk.h).  Argument marshalling only."""
+"""Python entry points with the same names as the C ABI (include/rtopk.h).  Argument marshalling only: natively
+(csrc/rtopk_torch.cpp) in the usual case, through ctypes for the rest."""
 from __future__ import annotations
 
 import ctypes
@@ -6,7 +7,12 @@ import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "librtopk.so")
+_NATIVE_PATH = os.path.join(_HERE, "_rtopk_torch.so")
 _lib = None
+_fast = None  # the native module, once loaded
+
+# `which` of the native select(): the element type or variant, plus 8 for exact mode
+_F32, _U8, _SMALLEST, _F16, _BF16, _EXACT = 0, 1, 2, 3, 4, 8
 
 
 class RTopKError(RuntimeError):
@@ -58,6 +64,27 @@ def load_library() -> ctypes.CDLL:
     return _lib
 
 
+def _native():
+    """Load _rtopk_torch.so (csrc/rtopk_torch.cpp), which does an entry point's checks, allocation and call natively.
+    Its functions return None, with nothing enqueued, for whatever is not the usual case: the Python code of the
+    entry points below then does the same steps and raises where something is wrong.  Raises if it is missing."""
+    global _fast
+    if _fast is None:
+        import importlib.util
+
+        import torch  # noqa: F401  (the module's own libraries)
+
+        load_library()
+        if not os.path.exists(_NATIVE_PATH):
+            raise FileNotFoundError(
+                f"{_NATIVE_PATH} not found: build it with `python -m paper_2409_00822_amd.build`")
+        spec = importlib.util.spec_from_file_location("_rtopk_torch", _NATIVE_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        _fast = module
+    return _fast
+
+
 def rtopk_status_string(status: int) -> str:
     return load_library().rtopk_status_string(int(status)).decode()
 
@@ -95,6 +122,9 @@ def _prepare(x, k: int, out_vals, out_idx, idx_dtype, val_dtype=None):
 
 def rtopk_rowwise(x, k: int, max_iter: int, out_vals=None, out_idx=None):
     """Algorithm 2 (early stopping).  Returns (values [N,k] f32, columns [N,k] i32)."""
+    done = (_fast or _native()).select(_F32, x, k, max_iter, out_vals, out_idx)
+    if done is not None:
+        return done
     import torch
 
     N, M, out_vals, out_idx, stream = _prepare(x, k, out_vals, out_idx, torch.int32)
@@ -105,6 +135,9 @@ def rtopk_rowwise(x, k: int, max_iter: int, out_vals=None, out_idx=None):
 
 def rtopk_rowwise_exact(x, k: int, out_vals=None, out_idx=None):
     """Algorithm 1 at epsilon = 0 (exact top-k).  Returns (values [N,k] f32, columns [N,k] i32)."""
+    done = (_fast or _native()).select(_F32 | _EXACT, x, k, 0, out_vals, out_idx)
+    if done is not None:
+        return done
     import torch
 
     N, M, out_vals, out_idx, stream = _prepare(x, k, out_vals, out_idx, torch.int32)
@@ -114,6 +147,9 @@ def rtopk_rowwise_exact(x, k: int, out_vals=None, out_idx=None):
 
 def rtopk_rowwise_u8(x, k: int, max_iter: int, out_vals=None, out_idx=None):
     """Algorithm 2 with uint8 columns (M <= 256)."""
+    done = (_fast or _native()).select(_U8, x, k, max_iter, out_vals, out_idx)
+    if done is not None:
+        return done
     import torch
 
     N, M, out_vals, out_idx, stream = _prepare(x, k, out_vals, out_idx, torch.uint8)
@@ -124,6 +160,9 @@ def rtopk_rowwise_u8(x, k: int, max_iter: int, out_vals=None, out_idx=None):
 
 def rtopk_rowwise_exact_u8(x, k: int, out_vals=None, out_idx=None):
     """Exact top-k with uint8 columns (M <= 256)."""
+    done = (_fast or _native()).select(_U8 | _EXACT, x, k, 0, out_vals, out_idx)
+    if done is not None:
+        return done
     import torch
 
     N, M, out_vals, out_idx, stream = _prepare(x, k, out_vals, out_idx, torch.uint8)
@@ -135,6 +174,9 @@ def rtopk_rowwise_exact_u8(x, k: int, out_vals=None, out_idx=None):
 def rtopk_rowwise_eps(x, k: int, eps_rel: float, out_vals=None, out_idx=None, out_iters=None, want_iters: bool = False):
     """Algorithm 1 with precision epsilon = eps_rel * |max(row)|.  Returns (values, columns) or, when
     `want_iters` is set or `out_iters` is given, (values, columns, exit iterations [N] i32)."""
+    done = (_fast or _native()).select_eps(x, k, eps_rel, out_vals, out_idx, out_iters, want_iters)
+    if done is not None:
+        return done
     import torch
 
     N, M, out_vals, out_idx, stream = _prepare(x, k, out_vals, out_idx, torch.int32)
@@ -151,6 +193,9 @@ def rtopk_rowwise_eps(x, k: int, eps_rel: float, out_vals=None, out_idx=None, ou
 
 def rtopk_rowwise_smallest(x, k: int, max_iter: int, out_vals=None, out_idx=None):
     """Algorithm 2 for the k smallest values per row.  Returns (values [N,k] f32, columns [N,k] i32)."""
+    done = (_fast or _native()).select(_SMALLEST, x, k, max_iter, out_vals, out_idx)
+    if done is not None:
+        return done
     import torch
 
     N, M, out_vals, out_idx, stream = _prepare(x, k, out_vals, out_idx, torch.int32)
@@ -161,6 +206,9 @@ def rtopk_rowwise_smallest(x, k: int, max_iter: int, out_vals=None, out_idx=None
 
 def rtopk_rowwise_exact_smallest(x, k: int, out_vals=None, out_idx=None):
     """Exact k smallest values per row.  Returns (values [N,k] f32, columns [N,k] i32)."""
+    done = (_fast or _native()).select(_SMALLEST | _EXACT, x, k, 0, out_vals, out_idx)
+    if done is not None:
+        return done
     import torch
 
     N, M, out_vals, out_idx, stream = _prepare(x, k, out_vals, out_idx, torch.int32)
@@ -183,6 +231,9 @@ def _rowwise_16(name: str, val_dtype, x, k, max_iter, out_vals, out_idx):
 
 def rtopk_rowwise_f16(x, k: int, max_iter: int, out_vals=None, out_idx=None):
     """Algorithm 2 on float16 rows (fp32 arithmetic on the widened row).  Returns (values f16, columns i32)."""
+    done = (_fast or _native()).select(_F16, x, k, max_iter, out_vals, out_idx)
+    if done is not None:
+        return done
     import torch
 
     return _rowwise_16("rtopk_rowwise_f16", torch.float16, x, k, max_iter, out_vals, out_idx)
@@ -190,6 +241,9 @@ def rtopk_rowwise_f16(x, k: int, max_iter: int, out_vals=None, out_idx=None):
 
 def rtopk_rowwise_exact_f16(x, k: int, out_vals=None, out_idx=None):
     """Exact top-k of float16 rows.  Returns (values f16, columns i32)."""
+    done = (_fast or _native()).select(_F16 | _EXACT, x, k, 0, out_vals, out_idx)
+    if done is not None:
+        return done
     import torch
 
     return _rowwise_16("rtopk_rowwise_exact_f16", torch.float16, x, k, None, out_vals, out_idx)
@@ -197,6 +251,9 @@ def rtopk_rowwise_exact_f16(x, k: int, out_vals=None, out_idx=None):
 
 def rtopk_rowwise_bf16(x, k: int, max_iter: int, out_vals=None, out_idx=None):
     """Algorithm 2 on bfloat16 rows (fp32 arithmetic on the widened row).  Returns (values bf16, columns i32)."""
+    done = (_fast or _native()).select(_BF16, x, k, max_iter, out_vals, out_idx)
+    if done is not None:
+        return done
     import torch
 
     return _rowwise_16("rtopk_rowwise_bf16", torch.bfloat16, x, k, max_iter, out_vals, out_idx)
@@ -204,6 +261,9 @@ def rtopk_rowwise_bf16(x, k: int, max_iter: int, out_vals=None, out_idx=None):
 
 def rtopk_rowwise_exact_bf16(x, k: int, out_vals=None, out_idx=None):
     """Exact top-k of bfloat16 rows.  Returns (values bf16, columns i32)."""
+    done = (_fast or _native()).select(_BF16 | _EXACT, x, k, 0, out_vals, out_idx)
+    if done is not None:
+        return done
     import torch
 
     return _rowwise_16("rtopk_rowwise_exact_bf16", torch.bfloat16, x, k, None, out_vals, out_idx)
@@ -212,6 +272,9 @@ def rtopk_rowwise_exact_bf16(x, k: int, out_vals=None, out_idx=None):
 def rtopk_maxk_dense(x, k: int, max_iter: int = -1, out=None):
     """MaxK non-linearity, dense form: the k selected values of each row in place, zero elsewhere.
     max_iter < 0: exact selection; max_iter >= 0: Algorithm 2 with that many steps.  Returns out [N,M] f32."""
+    done = (_fast or _native()).dense(x, k, max_iter, out)
+    if done is not None:
+        return done
     import torch
 
     if not (x.is_cuda and x.dtype == torch.float32 and x.dim() == 2 and x.is_contiguous()):
@@ -239,6 +302,9 @@ def _backward_args(idx, M: int):
 def rtopk_maxk_backward(grad_vals, idx, M: int, grad_in=None):
     """Backward of the MaxK non-linearity, scatter form: gradients of the k kept values [N, k] and the
     saved columns [N, k] (int32 or uint8) -> gradient of the dense row [N, M], zero elsewhere."""
+    done = (_fast or _native()).scatter(grad_vals, idx, M, grad_in)
+    if done is not None:
+        return done
     import torch
 
     u8, stream = _backward_args(idx, M)
@@ -259,6 +325,9 @@ def rtopk_maxk_backward(grad_vals, idx, M: int, grad_in=None):
 def rtopk_maxk_backward_gather(grad_out, idx, grad_vals=None):
     """Backward of the MaxK non-linearity, gather form: dense gradient rows [N, M] and the saved columns
     [N, k] (int32 or uint8) -> the gradient entries at those columns [N, k]."""
+    done = (_fast or _native()).gather(grad_out, idx, grad_vals)
+    if done is not None:
+        return done
     import torch
 
     if not (grad_out.is_cuda and grad_out.dtype == torch.float32 and grad_out.dim() == 2 and grad_out.is_contiguous()):

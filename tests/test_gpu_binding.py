@@ -1,0 +1,92 @@
+"""The Python entry points through the native module: the caller's outputs come back as they are, new ones are new, what
+was refused is refused by the Python code with the same exceptions, and calls follow the current stream and threads."""
+import threading
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2409_00822_amd as R
+
+    R.load_library()
+    return R
+
+
+def test_given_outputs_come_back_and_new_ones_are_new():
+    R = _gpu()
+    x = torch.randn(50, 100, device="cuda")
+    v = torch.empty(50, 7, device="cuda")
+    i = torch.empty(50, 7, dtype=torch.int32, device="cuda")
+    t = torch.empty(50, dtype=torch.int32, device="cuda")
+    a = R.rtopk_rowwise_exact(x, 7, v, i)
+    assert a[0] is v and a[1] is i
+    b = R.rtopk_rowwise_exact(x, 7, out_idx=i)
+    assert b[0] is not v and b[1] is i
+    c = R.rtopk_rowwise_eps(x, 7, 0, v, i, t)  # an int epsilon goes through the Python code
+    assert c[0] is v and c[1] is i and c[2] is t
+    assert len(R.rtopk_rowwise_eps(x, 7, 0.0)) == 2 and len(R.rtopk_rowwise_eps(x, 7, 0.0, want_iters=True)) == 3
+    y = torch.empty_like(x)
+    assert R.rtopk_maxk_dense(x, 7, out=y) is y
+    g = R.rtopk_maxk_backward(v, i, 100)
+    assert R.rtopk_maxk_backward(v, i, 100, g) is g and R.rtopk_maxk_backward_gather(g, i, v) is v
+
+
+def test_what_was_refused_is_refused():
+    R = _gpu()
+    x = torch.randn(50, 100, device="cuda")
+    for bad in (x.cpu(), x.double(), x[:, ::2], x[0], x.half()):
+        with pytest.raises(ValueError):
+            R.rtopk_rowwise_exact(bad, 3)
+        with pytest.raises(ValueError):
+            R.rtopk_maxk_dense(bad, 3)
+    with pytest.raises(ValueError):
+        R.rtopk_rowwise_exact(x, 3, out_vals=torch.empty(50, 4, device="cuda"))
+    with pytest.raises(ValueError):
+        R.rtopk_rowwise_eps(x, 3, 0.1, out_iters=torch.empty(49, dtype=torch.int32, device="cuda"))
+    for k in (0, 101):
+        with pytest.raises(R.RTopKError):
+            R.rtopk_rowwise_exact(x, k)
+    with pytest.raises(R.RTopKError):
+        R.rtopk_rowwise(x, 3, -1)  # not exact mode
+    with pytest.raises(R.RTopKError):
+        R.rtopk_rowwise_eps(x, 3, -1.0)
+    with pytest.raises((TypeError, Exception)):
+        R.rtopk_rowwise_exact(x, 3.0)
+    with pytest.raises(ValueError):
+        R.rtopk_maxk_backward(x, torch.zeros(50, 3, dtype=torch.int64, device="cuda"), 100)
+    with pytest.raises(ValueError):
+        R.rtopk_maxk_backward_gather(x, torch.zeros(49, 3, dtype=torch.int32, device="cuda"))
+
+
+def test_threads_and_streams():
+    R = _gpu()
+    xs = [workloads.normal(300, 200 + 13 * t, seed=5000 + t) for t in range(4)]
+    got = [None] * 4
+
+    def work(t):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            x = torch.from_numpy(xs[t]).cuda()
+            for _ in range(50):
+                got[t] = R.rtopk_rowwise_exact(x, 20 + t)
+        s.synchronize()
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for t in range(4):
+        ev, ei = oracle.topk_exact(xs[t], 20 + t)
+        assert np.array_equal(got[t][1].cpu().numpy(), ei)
+        assert np.array_equal(got[t][0].cpu().numpy().view(np.int32), ev.view(np.int32))
