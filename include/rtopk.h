@@ -114,6 +114,21 @@ int rtopk_rowwise_exact_smallest(const float* in, int64_t N, int32_t M, int32_t 
                                  void* stream);
 
 /*
+ * The fp32 selections above with scratch memory from the caller.  With at least rtopk_workspace_bytes(...) bytes
+ * of device memory (16-byte aligned, sharing no byte with the other buffers) rows of more than 32768 columns are
+ * spread over several workgroups each, which few or very wide rows need to fill the GPU; the work is then a few launches
+ * on `stream` instead of one, and the memory may be used again by later work on that stream.  Without it (NULL, too few
+ * bytes, or a shape for which rtopk_workspace_bytes returns 0) the call is the plain entry point's.  Same results.
+ *   variant   : RTOPK_EARLY (max_iter), RTOPK_EXACT or RTOPK_EPS (eps_rel, optional out_iters; NULL otherwise), with
+ *               RTOPK_SMALLEST added for the k smallest (not with RTOPK_EPS); anything else: RTOPK_ERR_BAD_SHAPE.
+ */
+enum { RTOPK_EARLY = 0, RTOPK_EXACT = 1, RTOPK_EPS = 2, RTOPK_SMALLEST = 4 };
+int64_t rtopk_workspace_bytes(int64_t N, int32_t M, int32_t k, int32_t variant, int32_t max_iter);
+int rtopk_select_ws(const float* in, int64_t N, int32_t M, int32_t k, int32_t variant, int32_t max_iter, float eps_rel,
+                    float* out_vals, int32_t* out_idx, int32_t* out_iters, void* workspace, int64_t workspace_bytes,
+                    void* stream);
+
+/*
  * Rows stored in 16 bits: IEEE half (_f16) or bfloat16 (_bf16), passed as raw uint16_t bit patterns.
  * The paper's method is defined in fp32 (Section 3.1); here each row is widened exactly to fp32 as
  * it is loaded and Algorithm 2 / Algorithm 1 (epsilon = 0) run on the widened row, with fp32

@@ -20,7 +20,8 @@ inline bool aligned(const void* p, uintptr_t a) { return rtopk::is_aligned(addr(
 //   u8:   out_idx is uint8_t[N][k] (requires M <= 256), else int32_t[N][k].
 //   dtype: element type of `in` and `out_vals` (rtopk::kF32, kF16, kBF16).
 int run(const void* in, int64_t N, int32_t M, int32_t k, int32_t max_iter, float eps_rel, int mode, void* out_vals,
-        void* out_idx, int32_t* out_iters, bool u8, void* stream, bool smallest = false, int dtype = rtopk::kF32) {
+        void* out_idx, int32_t* out_iters, bool u8, void* stream, bool smallest = false, int dtype = rtopk::kF32,
+        void* scratch = nullptr, int64_t scratch_bytes = 0) {
   const uintptr_t esz = dtype == rtopk::kF32 ? 4 : 2;
   if (N < 0 || M < 1 || k < 1 || k > M) return RTOPK_ERR_BAD_SHAPE;
   if (mode == rtopk::kEarly && max_iter < 0) return RTOPK_ERR_BAD_MAX_ITER;
@@ -29,16 +30,17 @@ int run(const void* in, int64_t N, int32_t M, int32_t k, int32_t max_iter, float
   if (M > rtopk::kMaxWaveM && N > 0x7fffffffLL) return RTOPK_ERR_BAD_SHAPE;  // one workgroup per row: 2^31 - 1 rows
   if (N == 0) return RTOPK_OK;
   if (!in || !out_vals || !out_idx) return RTOPK_ERR_NULL_POINTER;
-  if (!aligned(in, esz) || !aligned(out_vals, esz) || (!u8 && !aligned(out_idx, 4)) || !aligned(out_iters, 4))
+  if (!aligned(in, esz) || !aligned(out_vals, esz) || (!u8 && !aligned(out_idx, 4)) || !aligned(out_iters, 4) ||
+      !aligned(scratch, 16))
     return RTOPK_ERR_MISALIGNED;
   {
     // the input must not share a byte with any output, nor the outputs with one another
     const uint64_t n_in = (uint64_t)N * (uint64_t)M * esz, n_v = (uint64_t)N * (uint64_t)k * esz;
     const uint64_t n_i = (uint64_t)N * (uint64_t)k * (u8 ? 1 : 4), n_t = out_iters ? (uint64_t)N * 4 : 0;
-    const uintptr_t p[4] = {addr(in), addr(out_vals), addr(out_idx), addr(out_iters)};
-    const uint64_t n[4] = {n_in, n_v, n_i, n_t};
-    for (int i = 0; i < 4; ++i)
-      for (int j = i + 1; j < 4; ++j)
+    const uintptr_t p[5] = {addr(in), addr(out_vals), addr(out_idx), addr(out_iters), addr(scratch)};
+    const uint64_t n[5] = {n_in, n_v, n_i, n_t, scratch ? (uint64_t)scratch_bytes : 0};
+    for (int i = 0; i < 5; ++i)
+      for (int j = i + 1; j < 5; ++j)
         if (rtopk::ranges_overlap(p[i], n[i], p[j], n[j])) return RTOPK_ERR_OVERLAP;
   }
 
@@ -68,6 +70,11 @@ int run(const void* in, int64_t N, int32_t M, int32_t k, int32_t max_iter, float
   const bool plain = dtype == rtopk::kF32 && !smallest && mode != rtopk::kEps;
   const rtopk::Shape sh = rtopk::kernel_layout(rtopk::classify(M, dtype, plain, addr(in)), M, dtype, plain, false);
   hipError_t err;
+  if (scratch && dtype == rtopk::kF32 && !u8) {
+    const int64_t need = rtopk::split_scratch_bytes(N, M, k, mode, max_iter);
+    if (need > 0 && scratch_bytes >= need)
+      return rtopk::launch_split_any(mode, smallest, scratch, a) == hipSuccess ? RTOPK_OK : RTOPK_ERR_LAUNCH;
+  }
   switch (sh.family) {
     case rtopk::kFamStream:
       err = rtopk::launch_stream_any(mode, smallest, a);
@@ -175,6 +182,21 @@ int rtopk_rowwise_bf16(const uint16_t* in, int64_t N, int32_t M, int32_t k, int3
 int rtopk_rowwise_exact_bf16(const uint16_t* in, int64_t N, int32_t M, int32_t k, uint16_t* out_vals,
                              int32_t* out_idx, void* stream) {
   return run(in, N, M, k, 0, 0.0f, rtopk::kExact, out_vals, out_idx, nullptr, false, stream, false, rtopk::kBF16);
+}
+
+int rtopk_select_ws(const float* in, int64_t N, int32_t M, int32_t k, int32_t variant, int32_t max_iter, float eps_rel,
+                    float* out_vals, int32_t* out_idx, int32_t* out_iters, void* workspace, int64_t workspace_bytes,
+                    void* stream) {
+  const int mode = variant & 3;
+  const bool smallest = (variant & RTOPK_SMALLEST) != 0;
+  if ((variant & ~7) != 0 || mode == 3 || (smallest && mode == rtopk::kEps) || workspace_bytes < 0) return RTOPK_ERR_BAD_SHAPE;
+  return run(in, N, M, k, mode == rtopk::kEarly ? max_iter : 0, eps_rel, mode, out_vals, out_idx,
+             mode == rtopk::kEps ? out_iters : nullptr, false, stream, smallest, rtopk::kF32, workspace, workspace_bytes);
+}
+
+int64_t rtopk_workspace_bytes(int64_t N, int32_t M, int32_t k, int32_t variant, int32_t max_iter) {
+  if (N < 1 || M < 1 || M > rtopk::kMaxM || k < 1 || k >= M || (variant & ~7) != 0 || (variant & 3) == 3) return 0;
+  return rtopk::split_scratch_bytes(N, M, k, variant & 3, max_iter);
 }
 
 int rtopk_maxk_dense(const float* in, int64_t N, int32_t M, int32_t k, int32_t max_iter, float* out, void* stream) {

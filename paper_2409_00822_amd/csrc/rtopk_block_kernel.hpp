@@ -130,26 +130,108 @@ __device__ __forceinline__ void store_pair_if_below(uint32_t pos, uint32_t limit
 #define RTOPK_BLOCK_PERSIST_MIN_W 16
 #endif
 constexpr bool block_persistent(int W) { return W >= RTOPK_BLOCK_PERSIST_MIN_W; }
-constexpr int block_groups_ahead(int W, int G, bool filter) { return block_persistent(W) && !filter ? RTOPK_BLOCK_AHEAD / G : 0; }
+// How a row is selected: by the full-width search; through the lists of rtopk_filter.hpp, and by the full-width search
+// where they do not hold it; or through the lists alone.
+enum BlockPath : int { kFullWidth = 0, kListsFirst = 1, kListsOnly = 2 };
+constexpr int block_groups_ahead(int W, int G, int path) { return block_persistent(W) && path == kFullWidth ? RTOPK_BLOCK_AHEAD / G : 0; }
 
-// One row, by the whole workgroup.  Every wavefront leaves through the same return statement.
-// FILTER: the row is first tried through the lists of rtopk_filter.hpp (k is small enough for them); a workgroup
-// that walks several rows then loads the whole next row as soon as the lists stand, into the registers of this one
-// (have_next: x holds the row on entry).  Without it, as much of the next row as fits beside this one is loaded
-// while this one is ranked (ahead).
-template <int G, int NG, int W, int MODE, bool NEG, int DT, bool DENSE, bool FILTER>
-__device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in, int64_t N, int M, int k, int max_iter,
+// Groups FIRST .. LAST - 1 of the row of M columns at `from`.  Lanes past M load the row's last columns (in bounds,
+// cannot change min or max).
+template <int DT, int G, int W, int FIRST, int LAST, int SIZE>
+__device__ __forceinline__ void block_load(const typename std::conditional<DT == kF32, float, uint16_t>::type* from, int M,
+                                           int lane, int wave, float (&to)[SIZE]) {
+  asm volatile("" : "+v"(lane));  // opaque: the columns computed for one row's loads are not kept for the next row's
+#pragma unroll
+  for (int g = FIRST; g < LAST; ++g) {
+    float v[G];
+    load_group<DT, G>(from, min(((g * W + wave) * kWave + lane) * G, M - G), v);
+#pragma unroll
+    for (int c = 0; c < G; ++c) to[g * G + c] = v[c];
+  }
+}
+
+// Columns past M must never be counted or chosen: their key becomes -inf.
+template <int G, int NG, int W, bool NEG>
+__device__ __forceinline__ void block_mask(float (&x)[G * NG], int M, int lane, int wave) {
+  if (M == kWave * G * NG * W) return;  // uniform: full-width rows skip the masking
+  const float none = NEG ? __builtin_inff() : -__builtin_inff();
+  asm volatile("" : "+v"(lane));
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    if ((g + 1) * (W * kWave * G) <= M) continue;  // uniform: the group lies inside the row
+    const int left = M - ((g * W + wave) * kWave + lane) * G;  // columns of the row from the lane's first on
+    // past the end, or (M % G != 0) the straddling lane's leading elements, which the lane before it owns
+#pragma unroll
+    for (int c = 0; c < G; ++c) x[g * G + c] = left < G - c ? none : x[g * G + c];
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// Minimum and maximum of the row's keys and, with FILTER, its floor (rtopk_filter.hpp: at least `need` group maxima of
+// every wavefront at or above it) and the bound above it: per lane, per wavefront, then over the W wavefronts through
+// LDS.  Contains a barrier.  nm: the lane's negated minimum (taken before the columns past M were masked).
+template <int W>
+struct BoundsLds {
+  float hi[W], nlo[W], nt0[W], probe[W];
+};
+template <int E, int W, bool NEG, bool FILTER>
+__device__ __forceinline__ void block_bounds(const float (&x)[E], float nm, int need, int lane, int wave, BoundsLds<W>& s,
+                                             float& lo, float& hi, float& T0, float& probe) {
+  constexpr int J = E / kFilterGroup;
+  float gm[J], wmax, wmin, above = 0.0f, floor_w = 0.0f;
+  lane_group_maxima<E, NEG>(x, gm);
+  float mx = gm[0];
+#pragma unroll
+  for (int j = 1; j < J; ++j) mx = vmax(mx, gm[j]);
+  wave_max_and_negmin(mx, nm, wmax, wmin);
+  if constexpr (FILTER) floor_w = floor_of_maxima<J>(gm, need, wmin, wmax, above);
+  if (lane == 0) {
+    s.hi[wave] = wmax;
+    s.nlo[wave] = -wmin;
+    if constexpr (FILTER) {
+      s.nt0[wave] = -floor_w;
+      s.probe[wave] = above;
+    }
+  }
+  __syncthreads();
+  float a = s.hi[0], b = s.nlo[0], c = 0.0f, d = 0.0f;
+#pragma unroll
+  for (int w = 1; w < W; ++w) {
+    a = vmax(a, s.hi[w]);
+    b = vmax(b, s.nlo[w]);
+  }
+  if constexpr (FILTER) {
+    c = s.nt0[0], d = s.probe[0];
+#pragma unroll
+    for (int w = 1; w < W; ++w) {
+      c = vmax(c, s.nt0[w]);
+      d = vmax(d, s.probe[w]);
+    }
+  }
+  // every lane holds the same values; saying so lets the search loops branch on scalar conditions
+  hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(a)));
+  lo = -__int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(b)));
+  T0 = -__int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(c)));
+  probe = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(d)));
+}
+
+// One row, by the whole workgroup; true when it is done (always, but for kListsOnly).  Every wavefront leaves through the
+// same return statement.  A workgroup that walks several rows through the lists loads the whole next row as soon as the
+// list of quads stands, into the registers of this one (have_next: x holds the row on entry); with the full-width
+// search, as much of the next row as fits beside this one is loaded while this one is ranked (ahead).
+template <int G, int NG, int W, int MODE, bool NEG, int DT, bool DENSE, int PATH>
+__device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in, int64_t N, int M, int k, int max_iter,
                                           float eps_rel, void* __restrict__ out_vals, int32_t* __restrict__ out_idx,
                                           int32_t* __restrict__ out_iters, int64_t r_next, bool& have_ahead,
-                                          float (&ahead)[block_groups_ahead(W, G, FILTER) * G + 1], bool& have_next,
+                                          float (&ahead)[block_groups_ahead(W, G, PATH) * G + 1], bool& have_next,
                                           float (&x)[G * NG]) {
   static_assert(!DENSE || DT == kF32, "the dense form is built for fp32 rows");
   constexpr int E = G * NG;
+  constexpr bool FILTER = PATH != kFullWidth;
   constexpr int T = NG * W;  // (group, wavefront) cells of a row, in column order
   constexpr int CPL = (T + kWave - 1) / kWave;  // cells per lane when one wavefront scans the table
   using ElemT = typename std::conditional<DT == kF32, float, uint16_t>::type;
-  __shared__ float s_hi[W], s_nlo[W];  // per-wavefront maximum and negated minimum of the keys
-  __shared__ float s_nt0[W], s_probe[W];  // per-wavefront negated floor, and the bound above it (rtopk_filter.hpp)
+  __shared__ BoundsLds<W> s_bounds;
   __shared__ typename std::conditional<FILTER, FilterLds<W>, int>::type s_filter;
   __shared__ int s_cnt[2][W];          // per-wavefront counts of a search step, double buffered
   __shared__ int s_tab[2][T];          // candidates per cell of class A / class B, then their exclusive prefixes
@@ -165,104 +247,32 @@ __device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const ElemT* row = static_cast<const ElemT*>(in) + r * (int64_t)M;
 
-  // Loading stage.  Lanes past M load the row's last columns (in bounds, cannot change min or max).
-  // The first groups may have been loaded already, while the workgroup's previous row was ranked.
-  constexpr int AHEAD = block_groups_ahead(W, G, FILTER) < NG ? block_groups_ahead(W, G, FILTER) : NG;
-  auto load_groups = [&](const ElemT* from, auto first, auto last, float* to) {  // groups first .. last - 1
-    int ln = lane;  // opaque: the columns computed for one row's loads are not kept for the next row's
-    asm volatile("" : "+v"(ln));
-#pragma unroll
-    for (int g = decltype(first)::value; g < decltype(last)::value; ++g) {
-      float v[G];
-      load_group<DT, G>(from, min(((g * W + wave) * kWave + ln) * G, M - G), v);
-#pragma unroll
-      for (int c = 0; c < G; ++c) to[g * G + c] = v[c];
-    }
-  };
-  typedef std::integral_constant<int, 0> Begin;
-  typedef std::integral_constant<int, AHEAD> Middle;
-  typedef std::integral_constant<int, NG> End;
+  // Loading stage.  The row, or its first groups, may have been loaded already, while the workgroup's previous row
+  // was ranked.
+  constexpr int AHEAD = block_groups_ahead(W, G, PATH) < NG ? block_groups_ahead(W, G, PATH) : NG;
   if (!FILTER || !have_next) {  // uniform
     if (AHEAD > 0 && have_ahead) {
 #pragma unroll
       for (int e = 0; e < AHEAD * G; ++e) x[e] = ahead[e];
     } else {
-      load_groups(row, Begin(), Middle(), x);
+      block_load<DT, G, W, 0, AHEAD>(row, M, lane, wave, x);
     }
-    load_groups(row, Middle(), End(), x);
+    block_load<DT, G, W, AHEAD, NG>(row, M, lane, wave, x);
   }
   have_next = false;
 
-  // Minimum of the keys per lane, before the columns past M lose their copies of real elements ...
   const float nm = lane_negmin<E, NEG>(x);
-
-  // From here on columns past M must never be counted or chosen: their key is -inf.
-  auto mask_past_end = [&]() {
-    if (M == kWave * G * NG * W) return;  // uniform: full-width rows skip the masking
-    const float none = NEG ? __builtin_inff() : -__builtin_inff();
-    int ln = lane;
-    asm volatile("" : "+v"(ln));
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      if ((g + 1) * (W * kWave * G) <= M) continue;  // uniform: the group lies inside the row
-      const int left = M - ((g * W + wave) * kWave + ln) * G;  // columns of the row from the lane's first on
-      // past the end, or (M % G != 0) the straddling lane's leading elements, which the lane before it owns
-#pragma unroll
-      for (int c = 0; c < G; ++c) x[g * G + c] = left < G - c ? none : x[g * G + c];
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  mask_past_end();
-
-  // ... and their maximum, per group of 16: the group maxima give the row's floor (rtopk_filter.hpp).  Minimum,
-  // maximum and floor of the row: per wavefront, then over the W wavefronts through LDS.
-  float hi, lo, T0, probe;
-  {
-    constexpr int J = E / kFilterGroup;
-    float gm[J], wmax, wmin, above = 0.0f, floor_w = 0.0f;
-    lane_group_maxima<E, NEG>(x, gm);
-    float mx = gm[0];
-#pragma unroll
-    for (int j = 1; j < J; ++j) mx = vmax(mx, gm[j]);
-    wave_max_and_negmin(mx, nm, wmax, wmin);
-    if constexpr (FILTER) floor_w = floor_of_maxima<J>(gm, (k + W) / W, wmin, wmax, above);
-    if (lane == 0) {
-      s_hi[wave] = wmax;
-      s_nlo[wave] = -wmin;
-      if constexpr (FILTER) {
-        s_nt0[wave] = -floor_w;
-        s_probe[wave] = above;
-      }
-    }
-    if (threadIdx.x == 0) {
-      s_tot[0] = 0;
-      s_tot[1] = 0;
-      if constexpr (FILTER) {
-        s_filter.n_quads = 0;
-        s_filter.n_singles = 0;
-      }
-    }
-    __syncthreads();
-    float a = s_hi[0], b = s_nlo[0], c = 0.0f, d = 0.0f;
-#pragma unroll
-    for (int w = 1; w < W; ++w) {
-      a = vmax(a, s_hi[w]);
-      b = vmax(b, s_nlo[w]);
-    }
+  block_mask<G, NG, W, NEG>(x, M, lane, wave);
+  if (threadIdx.x == 0) {
+    s_tot[0] = 0;
+    s_tot[1] = 0;
     if constexpr (FILTER) {
-      c = s_nt0[0], d = s_probe[0];
-#pragma unroll
-      for (int w = 1; w < W; ++w) {
-        c = vmax(c, s_nt0[w]);
-        d = vmax(d, s_probe[w]);
-      }
+      s_filter.n_quads = 0;
+      s_filter.n_singles = 0;
     }
-    // every lane holds the same values; saying so lets the search loops branch on scalar conditions
-    hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(a)));
-    lo = -__int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(b)));
-    T0 = -__int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(c)));
-    probe = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(d)));
   }
+  float hi, lo, T0, probe;
+  block_bounds<E, W, NEG, FILTER>(x, nm, (k + W) / W, lane, wave, s_bounds, lo, hi, T0, probe);
 
   using OutT = typename std::conditional<DT == kF32, uint32_t, uint16_t>::type;  // value bits as stored
   OutT* ov = static_cast<OutT*>(out_vals) + r * (int64_t)(DENSE ? M : k);
@@ -271,7 +281,7 @@ __device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in
   auto next_ahead = [&]() {  // the first groups of the workgroup's next row
     if constexpr (AHEAD > 0) {
       if (r_next < N) {
-        load_groups(static_cast<const ElemT*>(in) + r_next * (int64_t)M, Begin(), Middle(), ahead);
+        block_load<DT, G, W, 0, AHEAD>(static_cast<const ElemT*>(in) + r_next * (int64_t)M, M, lane, wave, ahead);
         have_ahead = true;
       }
     }
@@ -287,9 +297,10 @@ __device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in
     };
     // once the list of quads stands, the whole next row is loaded while this one is searched and written
     auto listed = [&]() {
-      if constexpr (!DENSE && block_persistent(W)) {
+      if constexpr (PATH == kListsOnly && !DENSE) {
         if (r_next < N) {
-          load_groups(static_cast<const ElemT*>(in) + r_next * (int64_t)M, Begin(), End(), x);
+          __builtin_amdgcn_sched_barrier(0);  // not before the list has this row's values
+          block_load<DT, G, W, 0, NG>(static_cast<const ElemT*>(in) + r_next * (int64_t)M, M, lane, wave, x);
           have_next = true;
         }
       }
@@ -321,15 +332,10 @@ __device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in
           __builtin_amdgcn_sched_barrier(0);
         }
       }
-      return;
+      return true;
     }
+    if constexpr (PATH == kListsOnly) return false;
     bound_known = MODE == kEarly && done == kFilterBoundOnly;  // lo is Algorithm 2's final minimum
-    if constexpr (!DENSE && block_persistent(W)) {
-      // rare, and read again rather than kept: the registers of this row are what the next row is loaded into
-      load_groups(row, Begin(), End(), x);
-      mask_past_end();
-      have_next = false;
-    }
   }
 
   // cnt = #{row elements with key >= t}.  Every lane counts its keys below t, the wavefront sums them,
@@ -621,7 +627,7 @@ __device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in
       if constexpr (DENSE) store_row_group<G>(reinterpret_cast<float*>(ov), col, M, y);
       if constexpr (NG > 4) __builtin_amdgcn_sched_barrier(0);
     }
-    return;
+    return true;
   }
   // Two classes (a search that converged on a value tied across the k-th place): rare, kept plain.
 #pragma unroll
@@ -662,28 +668,57 @@ __device__ __forceinline__ void block_row(int64_t r, const void* __restrict__ in
     if constexpr (DENSE) store_row_group<G>(reinterpret_cast<float*>(ov), col, M, y);
     if constexpr (NG > 4) __builtin_amdgcn_sched_barrier(0);
   }
+  return true;
 }
 
 // Workgroup b takes rows b, b + gridDim.x, ...: with as many workgroups as rows each takes one; the widest
 // shape (16 wavefronts, one workgroup to a compute unit) is launched with one workgroup per compute unit
-// instead, which saves the dispatch of a new 1024-thread workgroup between a unit's rows.
+// instead, which saves the dispatch of a new 1024-thread workgroup between a unit's rows.  There the rows that the lists
+// do not hold wait until up to 64 have been through: they are read again then, so that the lists' loop needs registers
+// for no more than one row at a time.
 template <int G, int NG, int W, int MODE, bool NEG, int DT, bool DENSE, bool FILTER>
 __device__ __forceinline__ void block_rows(const void* __restrict__ in, int64_t N, int M, int k, int max_iter,
                                            float eps_rel, void* __restrict__ out_vals, int32_t* __restrict__ out_idx,
                                            int32_t* __restrict__ out_iters) {
   bool have_ahead = false, have_next = false;
-  float ahead[block_groups_ahead(W, G, FILTER) * G + 1], x[G * NG];
-  if constexpr (block_persistent(W)) {
+  if constexpr (block_persistent(W) && FILTER) {
+    float x[G * NG];
+    for (int64_t r0 = blockIdx.x; r0 < N; r0 += 64 * (int64_t)gridDim.x) {
+      uint64_t left = 0;  // uniform: rows for the full-width search
+      have_next = false;
+      for (int j = 0; j < 64; ++j) {
+        const int64_t r = r0 + j * (int64_t)gridDim.x;
+        if (r >= N) break;
+        float none[1];
+        const bool done = block_row<G, NG, W, MODE, NEG, DT, DENSE, kListsOnly>(
+            r, in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, j + 1 < 64 ? r + gridDim.x : N, have_ahead, none,
+            have_next, x);
+        left |= done ? 0ull : 1ull << j;
+        __syncthreads();  // the next row reuses the shared tables
+      }
+      while (left != 0) {
+        const int j = __builtin_ctzll(left);
+        left &= left - 1;
+        float ahead[block_groups_ahead(W, G, kFullWidth) * G + 1];
+        have_ahead = false;
+        block_row<G, NG, W, MODE, NEG, DT, DENSE, kFullWidth>(r0 + j * (int64_t)gridDim.x, in, N, M, k, max_iter, eps_rel,
+                                                              out_vals, out_idx, out_iters, N, have_ahead, ahead, have_next, x);
+        __syncthreads();
+      }
+    }
+  } else if constexpr (block_persistent(W)) {
+    float ahead[block_groups_ahead(W, G, kFullWidth) * G + 1], x[G * NG];
     for (int64_t r = blockIdx.x; r < N; r += gridDim.x) {
-      block_row<G, NG, W, MODE, NEG, DT, DENSE, FILTER>(r, in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters,
-                                                        r + gridDim.x, have_ahead, ahead, have_next, x);
+      block_row<G, NG, W, MODE, NEG, DT, DENSE, kFullWidth>(r, in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters,
+                                                            r + gridDim.x, have_ahead, ahead, have_next, x);
       __syncthreads();  // the next row reuses the shared tables
     }
   } else {
+    float none[1], x[G * NG];
     const int64_t r = blockIdx.x;  // launched with one workgroup per row
     if (r < N)
-      block_row<G, NG, W, MODE, NEG, DT, DENSE, FILTER>(r, in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters,
-                                                        N, have_ahead, ahead, have_next, x);
+      block_row<G, NG, W, MODE, NEG, DT, DENSE, FILTER ? kListsFirst : kFullWidth>(
+          r, in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, N, have_ahead, none, have_next, x);
   }
 }
 

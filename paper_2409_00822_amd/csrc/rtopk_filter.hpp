@@ -98,9 +98,9 @@ __device__ __forceinline__ float grid_floor(float t) {
 
 // LDS of one row.  CAP: quads, and singles, that the lists hold.  The bitmaps take the quads' place when those
 // have become singles.
-template <int W>
+template <int W, int ROOM = W == 4 ? 512 : 1024>
 struct FilterLds {
-  static constexpr int CAP = W == 4 ? 512 : 1024;
+  static constexpr int CAP = ROOM;
   static constexpr int WORDS = 128 * W;  // bitmap words: two per thread, 64 * 64 * W columns
   struct Lists {
     float4 quad[CAP + kWave];    // behind the list: a dummy slot per lane, shared by the wavefronts, never read
@@ -128,17 +128,18 @@ enum FilterResult : int {
   kFilterBoundOnly = 2  // the search has run, but its last threshold lies below the floor: the selection is the caller's
 };
 
-// Whether k is small enough for the lists; host and device agree through this rule alone.  Half a list: the floor's
-// candidates are 1.2 to 1.4 k plus the spread of the wavefronts' floors.
+// Whether k is small enough for the lists; host and device agree through this rule alone.  The floor has 1.4 to 1.6 k
+// candidates at such k (1.2 to 1.35 k, and the spread of the wavefronts' floors; 2 k at k = 64): normal rows of 21848
+// columns in 8 wavefronts, k = 512: 824 on average, 1012 at most in 200.
 template <int W>
 constexpr int filter_max_k() {
-  return FilterLds<W>::CAP / 2;
+  return W == 4 ? 256 : 512;
 }
 
 // Positions of the set bits of one bitmap: `before` and `wave_bits` for the words of `map`.  Called by the whole
 // workgroup with a barrier before it; contains one.
-template <int W>
-__device__ __forceinline__ void filter_prefix(FilterLds<W>& s, const uint2* map, int lane, int wave) {
+template <int W, int ROOM>
+__device__ __forceinline__ void filter_prefix(FilterLds<W, ROOM>& s, const uint2* map, int lane, int wave) {
   const int tid = wave * kWave + lane;
   const uint2 w = map[tid];
   const uint32_t n0 = (uint32_t)__builtin_popcount(w.x), n = n0 + (uint32_t)__builtin_popcount(w.y);
@@ -148,8 +149,8 @@ __device__ __forceinline__ void filter_prefix(FilterLds<W>& s, const uint2* map,
   __syncthreads();
 }
 // Set bits of the map below column `col`.
-template <int W>
-__device__ __forceinline__ uint32_t filter_rank(const FilterLds<W>& s, const uint2* map, int col) {
+template <int W, int ROOM>
+__device__ __forceinline__ uint32_t filter_rank(const FilterLds<W, ROOM>& s, const uint2* map, int col) {
   const int word = col >> 5, owner = word >> 1;
   const uint32_t b = s.maps.before[owner];
   const uint2 w = map[owner];
@@ -219,17 +220,14 @@ __device__ __forceinline__ void filter_search(const uint2* single, int n, int la
   }
 }
 
-// Steps 2 to 5 for one row, by the whole workgroup (W wavefronts).  x: the row's elements, masked (a key of -inf past
-// the row's end).  lo, hi: the keys' minimum and maximum; T0 the row's floor, probe see filter_search.  Before the call
-// n_quads and n_singles are zero and a barrier has passed.  column(quad of the lane, thread): the quad's first column.
-// listed(): called once x is no longer needed here.  emit(place, value, column).
-// In the dense form nothing is emitted and thi, tlo, split say which elements stay:
-// key >= (column <= split ? tlo : thi).  Every wavefront takes the same branches.
-template <int E, int W, int MODE, bool NEG, int DT, bool DENSE, typename Column, typename Listed, typename Emit>
-__device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], int lane, int wave, int k, int max_iter,
-                                          float eps, float T0, float probe, float& lo, float hi, float& thi, float& tlo,
-                                          int& split, int& iterations, Column column, Listed listed, Emit emit) {
-  constexpr int CAP = FilterLds<W>::CAP, Q = E / 4;
+// Steps 2 and 3 for one row, by the whole workgroup (W wavefronts): returns how many singles there are, -1 where a
+// list does not hold them.  x: the row's elements, masked (a key of -inf past the row's end).  Before the call n_quads
+// and n_singles are zero and a barrier has passed; the lists are complete for every wavefront on return.
+// column(quad of the lane, thread): the quad's first column.  listed(): called once x is no longer needed here.
+template <int E, int W, bool NEG, int ROOM, typename Column, typename Listed>
+__device__ __forceinline__ int filter_lists(FilterLds<W, ROOM>& s, const float (&x)[E], int lane, int wave, float T0,
+                                            Column column, Listed listed) {
+  constexpr int CAP = ROOM, Q = E / 4;
   static_assert(Q <= 32, "a lane's quads are the bits of one word");
   const int tid = wave * kWave + lane;
 
@@ -264,7 +262,7 @@ __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], 
   listed();
   __syncthreads();
   const int n_quads = __builtin_amdgcn_readfirstlane(s.n_quads);
-  if (n_quads > CAP) return kFilterNoList;
+  if (n_quads > CAP) return -1;
 
   // Step 3.
   for (int j0 = 0; j0 < n_quads; j0 += W * kWave) {
@@ -296,7 +294,20 @@ __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], 
   }
   __syncthreads();
   const int n = __builtin_amdgcn_readfirstlane(s.n_singles);
-  if (n > CAP || n <= k) return kFilterNoList;  // (n <= k only with NaN or infinite keys)
+  return n <= CAP ? n : -1;
+}
+
+// Steps 2 to 5 for one row, by the whole workgroup.  lo, hi: the keys' minimum and maximum; T0 the row's floor, probe
+// see filter_search.  emit(place, value, column).  In the dense form nothing is emitted and thi, tlo, split say which
+// elements stay: key >= (column <= split ? tlo : thi).  Every wavefront takes the same branches.
+template <int E, int W, int MODE, bool NEG, int DT, bool DENSE, typename Column, typename Listed, typename Emit>
+__device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], int lane, int wave, int k, int max_iter,
+                                          float eps, float T0, float probe, float& lo, float hi, float& thi, float& tlo,
+                                          int& split, int& iterations, Column column, Listed listed, Emit emit) {
+  constexpr int CAP = FilterLds<W>::CAP;
+  const int tid = wave * kWave + lane;
+  const int n = filter_lists<E, W, NEG>(s, x, lane, wave, T0, column, listed);
+  if (n <= k) return kFilterNoList;  // (0 <= n <= k only with NaN or infinite keys)
 
   // Step 4 by wavefront 0, while every thread clears its words of the bitmaps.
   s.maps.cut[tid] = make_uint2(0u, 0u);
@@ -368,11 +379,11 @@ __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], 
       if (key >= tlo && !(key >= thi)) atomicOr(reinterpret_cast<uint32_t*>(s.maps.cut) + (e.y >> 5), 1u << (e.y & 31));
     }
     __syncthreads();
-    filter_prefix<W>(s, s.maps.cut, lane, wave);
+    filter_prefix(s, s.maps.cut, lane, wave);
     for (int j = tid; j < n; j += W * kWave) {
       const uint2 e = s.single[j];
       const float key = keyof<NEG>(__uint_as_float(e.x));
-      if (key >= tlo && !(key >= thi) && filter_rank<W>(s, s.maps.cut, (int)e.y) == (uint32_t)(limit - 1)) s.info[2] = (int)e.y;
+      if (key >= tlo && !(key >= thi) && filter_rank(s, s.maps.cut, (int)e.y) == (uint32_t)(limit - 1)) s.info[2] = (int)e.y;
     }
     __syncthreads();
     split = __builtin_amdgcn_readfirstlane(s.info[2]);
@@ -386,11 +397,11 @@ __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], 
       if (is_chosen(e)) atomicOr(reinterpret_cast<uint32_t*>(s.maps.chosen) + (e.y >> 5), 1u << (e.y & 31));
     }
     __syncthreads();
-    filter_prefix<W>(s, s.maps.chosen, lane, wave);
+    filter_prefix(s, s.maps.chosen, lane, wave);
     for (int j = tid; j < n; j += W * kWave) {
       const uint2 e = s.single[j];
       if (is_chosen(e)) {
-        const uint32_t place = filter_rank<W>(s, s.maps.chosen, (int)e.y);
+        const uint32_t place = filter_rank(s, s.maps.chosen, (int)e.y);
         if (place < (uint32_t)k) emit((int)place, e.x, (int)e.y);
       }
     }

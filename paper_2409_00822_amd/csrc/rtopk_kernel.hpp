@@ -1083,8 +1083,9 @@ __device__ __forceinline__ uint32_t narrow_bits(uint32_t fbits) {  // fp32 bits 
 template <int DT, int G>
 __device__ __forceinline__ void load_group(const typename std::conditional<DT == kF32, float, uint16_t>::type* row,
                                            int col, float (&dst)[G]) {
+  // (a scalar row address plus a 32-bit byte offset: no 64-bit address per load and lane)
   if constexpr (DT == kF32) {
-    const float* p = row + col;
+    const float* p = reinterpret_cast<const float*>(reinterpret_cast<const char*>(row) + (uint32_t)col * 4u);
     if constexpr (G == 1) {
       dst[0] = __builtin_nontemporal_load(p);
     } else {
@@ -1095,7 +1096,7 @@ __device__ __forceinline__ void load_group(const typename std::conditional<DT ==
       for (int c = 0; c < G; ++c) dst[c] = v[c];
     }
   } else {
-    const uint16_t* p = row + col;
+    const uint16_t* p = reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(row) + (uint32_t)col * 2u);
     if constexpr (G == 1) {
       dst[0] = widen_half<DT>((uint32_t)__builtin_nontemporal_load(p), 0);
     } else if constexpr (G == 2) {

@@ -1,0 +1,320 @@
+// Rows of more than 32768 columns (fp32) spread over several workgroups, with scratch memory from the caller.
+//
+// One workgroup per row leaves the chip idle when there are few rows, and a row that fills a compute unit's register
+// file by itself (32769 .. 65536 columns) leaves it idle while that row is searched.  Here a row is cut into segments of
+// at most 32768 (or 16384) columns, a workgroup each, in two launches:
+//   rtopk_segment_kernel: every segment's candidates -- the keys at or above a floor with more than k keys of the segment
+//     at or above it (steps 1 to 3 of rtopk_filter.hpp) -- go to the scratch memory in column order, with the floor and the
+//     segment's minimum and maximum;
+//   rtopk_merge_kernel: one workgroup per row.  The largest of the segments' floors has more than k keys of the row at or
+//     above it, and the lists hold all of those, so Algorithms 1 and 2 run on the lists with exact branch decisions (see
+//     rtopk_filter.hpp); the lists follow each other in column order, so places are prefix counts.
+// A row with a segment whose list is not whole (values that crowd), with more candidates than the merging workgroup's
+// registers hold, or whose last threshold lies below the floor is done by that workgroup as a streamed row
+// (rtopk_stream_kernel.hpp).  Results are those of the other kernels.
+//
+// What bounds it: the segments read the row once at the rate of the 32768-column rows (1.15 times the copy rate's time),
+// the lists add 8 bytes per candidate written and read, 1.2 to 1.4 k of them per segment, and the merge costs a launch
+// and about 14 steps of one barrier.  64 x 131072, k = 50: 39.7 us as 64 streamed rows, 14 us in 512 segments.
+#pragma once
+
+#include "rtopk_stream_kernel.hpp"
+
+namespace rtopk {
+
+struct SegmentHead {
+  int n;            // candidates; -1: the list is not whole
+  float floor;      // every key of the segment at or above it is listed
+  float nlo, hi;    // negated minimum, and maximum, of the segment's keys
+};
+constexpr int kMergeRegs = 16;       // candidates per lane of a merging wavefront
+constexpr int kMaxSegments = 1024;   // 2^24 columns in segments of 16384
+
+// How a call is split: `segments` per row of `length` columns (the last may be shorter), lists of `stride` candidates,
+// workgroups of w wavefronts with ng groups per lane, merge_waves wavefronts per row to merge.  segments = 0: not at all.
+struct Split {
+  int segments, length, stride, w, ng, merge_waves;
+  int64_t rows;  // rows per pair of launches, so that the scratch memory stays bounded
+  int64_t bytes() const { return rows * segments * ((int64_t)sizeof(SegmentHead) + (int64_t)stride * 8); }
+};
+
+constexpr int64_t kSplitScratch = 128ll << 20;
+
+// Candidates that a segment's lists hold: with nothing to search there, more than the lists of a whole row.
+constexpr int segment_room(int W) { return W == 4 ? 768 : 1536; }
+
+inline Split split_of(int64_t N, int M, int k, int mode, int max_iter) {
+  Split s{};
+  // Up to 32768 columns one workgroup per row does as well.  Algorithm 2 with few steps: see launch_block.
+  if (M <= 32768 || N < 1 || k > filter_max_k<8>() || (mode == kEarly && max_iter < 8)) return s;
+  // Segments of 32768 columns, unless those would not give every compute unit two workgroups.
+  s.w = 8;
+  if (k <= filter_max_k<4>() && N * ((M + 32767) / 32768) < 2 * 256) s.w = 4;
+  const int most = s.w * 4096;
+  s.segments = (M + most - 1) / most;
+  s.length = ((M + s.segments - 1) / s.segments + 3) & ~3;
+  s.ng = s.length <= s.w * 3072 ? 12 : 16;
+  // A segment's candidates: 1.2 to 1.35 k, and the spread of its wavefronts' floors, which weighs when k is small.  The
+  // lists have room for several times that; the merging workgroup's registers hold what is expected of all segments.
+  s.stride = 4 * k + 256 < segment_room(s.w) ? 4 * k + 256 : segment_room(s.w);
+  int root = 1;
+  while (root * root < k) ++root;
+  const int64_t expected = (int64_t)s.segments * (k + k / 3 + 6 * root + 16);
+  s.merge_waves = expected <= 4 * kWave * kMergeRegs ? 4 : (expected <= 8 * kWave * kMergeRegs ? 8 : 16);
+  if (expected > 16 * kWave * kMergeRegs) s.segments = 0;
+  if (s.segments == 0) return s;
+  const int64_t per_row = s.segments * ((int64_t)sizeof(SegmentHead) + (int64_t)s.stride * 8);
+  s.rows = kSplitScratch / per_row;
+  if (s.rows < 1) s.rows = 1;
+  if (s.rows > N) s.rows = N;
+  return s;
+}
+
+template <int NG, int W, bool NEG>
+__global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(5)))
+    rtopk_segment_kernel(const float* __restrict__ in, int M, int k, int segments, int length, int stride,
+                         SegmentHead* __restrict__ heads, uint2* __restrict__ lists) {
+  constexpr int G = 4, E = G * NG;
+  __shared__ BoundsLds<W> s_bounds;
+  __shared__ FilterLds<W, segment_room(W)> s_filter;
+  const int lane = threadIdx.x & (kWave - 1), tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = (int)blockIdx.x / segments, seg = (int)blockIdx.x % segments;
+  const int first = seg * length, cols = M - first < length ? M - first : length;  // at least G columns (split_of)
+  const float* from = in + (int64_t)r * M + first;
+  float x[E];
+  block_load<kF32, G, W, 0, NG>(from, cols, lane, wave, x);
+  const float nm = lane_negmin<E, NEG>(x);
+  block_mask<G, NG, W, NEG>(x, cols, lane, wave);
+  if (tid == 0) {
+    s_filter.n_quads = 0;
+    s_filter.n_singles = 0;
+  }
+  float lo, hi, T0, probe;
+  block_bounds<E, W, NEG, true>(x, nm, (k + W) / W, lane, wave, s_bounds, lo, hi, T0, probe);
+  auto column = [&](int quad, int thread) -> int { return min((quad * W * kWave + thread) * G, cols - G); };
+  const int n = filter_lists<E, W, NEG>(s_filter, x, lane, wave, T0, column, [] {});
+  const bool whole = n >= 0 && n <= stride;  // uniform
+  if (tid == 0) heads[blockIdx.x] = SegmentHead{whole ? n : -1, T0, -lo, hi};
+  if (!whole) return;
+  // in column order: the places of the singles' bits
+  s_filter.maps.chosen[tid] = make_uint2(0u, 0u);
+  __syncthreads();
+  for (int j = tid; j < n; j += W * kWave) {
+    const uint32_t c = s_filter.single[j].y;
+    atomicOr(reinterpret_cast<uint32_t*>(s_filter.maps.chosen) + (c >> 5), 1u << (c & 31));
+  }
+  __syncthreads();
+  filter_prefix(s_filter, s_filter.maps.chosen, lane, wave);
+  uint2* to = lists + (int64_t)blockIdx.x * stride;
+  for (int j = tid; j < n; j += W * kWave) {
+    const uint2 e = s_filter.single[j];
+    const uint32_t place = filter_rank(s_filter, s_filter.maps.chosen, (int)e.y);
+    if (place < (uint32_t)n) to[place] = make_uint2(e.x, e.y + (uint32_t)first);  // (NaN keys could share a column's bit)
+  }
+}
+
+// One row: its search and selection on the segments' lists.  Returns false, with nothing written, where they do not
+// hold the selection.  Called by the whole workgroup; uniform.
+template <int NW, int MODE, bool NEG>
+__device__ __forceinline__ bool merge_row(int64_t r, int k, int max_iter, float eps_rel, float* __restrict__ out_vals,
+                                          int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters,
+                                          const SegmentHead* __restrict__ heads, const uint2* __restrict__ lists,
+                                          int segments, int stride) {
+  __shared__ int s_first[kMaxSegments + 1];  // candidates in earlier segments
+  __shared__ float s_bound[3];
+  __shared__ int s_total, s_cnt[2][NW], s_cls[2][NW];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // The segments' heads, by one wavefront.
+  if (wave == 0) {
+    float fl = -__builtin_inff(), nlo = -__builtin_inff(), hi = -__builtin_inff();
+    int before = 0;
+    bool whole = true;
+    for (int s0 = 0; s0 < segments; s0 += kWave) {
+      const bool live = s0 + lane < segments;
+      const SegmentHead h = heads[r * segments + (live ? s0 + lane : 0)];
+      const int n = live ? h.n : 0;
+      whole = whole && __builtin_amdgcn_ballot_w64(n < 0) == 0;
+      const uint32_t incl = wave_inclusive_scan_dpp((uint32_t)(n < 0 ? 0 : n));
+      if (live) s_first[s0 + lane] = before + (int)incl - n;
+      before += __builtin_amdgcn_readlane((int)incl, kWave - 1);
+      fl = vmax(fl, h.floor);  // (a lane beyond the last segment repeats the first)
+      nlo = vmax(nlo, h.nlo);
+      hi = vmax(hi, h.hi);
+    }
+    float a, b, c, unused;
+    wave_max_and_negmin(fl, nlo, a, b);
+    wave_max_and_negmin(hi, hi, c, unused);
+    if (lane == 0) {
+      s_first[segments] = before;
+      s_total = whole ? before : -1;
+      s_bound[0] = a;
+      s_bound[1] = b;
+      s_bound[2] = c;
+    }
+  }
+  __syncthreads();
+  const int total = __builtin_amdgcn_readfirstlane(s_total);
+  const float T0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_bound[0])));
+  float lo = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_bound[1])));
+  float hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_bound[2])));
+  if (total <= k || total > NW * kWave * kMergeRegs) return false;
+
+  // The candidates, 64 consecutive ones to a register: number wave * per * 64 + i * 64 + lane.
+  const int per = (total + NW * kWave - 1) / (NW * kWave);
+  float key[kMergeRegs];
+  uint32_t col[kMergeRegs];
+  int top = 1;
+  while (top < segments) top <<= 1;
+#pragma unroll
+  for (int i = 0; i < kMergeRegs; ++i) {
+    key[i] = -__builtin_inff();
+    col[i] = 0;
+    if (i < per) {  // uniform
+      const int e = (wave * per + i) * kWave + lane;
+      if (e < total) {
+        int s = 0;  // the last segment that starts at or before e and is not empty
+        for (int step = top; step > 0; step >>= 1)
+          if (s + step < segments && s_first[s + step] <= e) s += step;
+        const uint2 v = lists[(r * segments + s) * stride + (e - s_first[s])];
+        key[i] = keyof<NEG>(__uint_as_float(v.x));
+        col[i] = v.y;
+      }
+    }
+  }
+  int turn = 0;
+  auto count = [&](float t) -> int {  // one barrier; the halves of s_cnt alternate as in rtopk_block_kernel
+    int mine = 0;
+#pragma unroll
+    for (int i = 0; i < kMergeRegs; ++i)
+      if (i < per) mine += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[i] >= t));
+    const int p = turn & 1;
+    ++turn;
+    if (lane == 0) s_cnt[p][wave] = mine;
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane((int)row16_sum(lane < NW ? (uint32_t)s_cnt[p][lane] : 0u));
+  };
+  if (count(T0) <= k) return false;  // (only with NaN or infinite keys)
+
+  // The search (see filter_search): exact mode may start at the floor, the others follow their thresholds.
+  bool hit = false;
+  float thres = lo;
+  int steps = 0;
+  const float eps = MODE == kEps ? eps_rel * __builtin_fabsf(hi) : 0.0f;
+  if (MODE == kExact) lo = T0;
+  for (;;) {
+    if (MODE == kEarly && steps >= max_iter) break;
+    if (MODE == kEps && !(hi - lo > eps)) break;
+    const float mid = (lo + hi) * 0.5f;
+    if (!(mid > lo && mid < hi)) {
+      // no fp32 value strictly inside (lo, hi): Algorithm 1 ends; Algorithm 2's steps repeat one midpoint, equal to lo
+      // (nothing moves) or to hi (lo moves up to it where hi itself counts k or more)
+      if (MODE == kEarly && mid == hi && hi > lo && count(hi) >= k) lo = hi;
+      break;
+    }
+    const int cnt = mid > T0 ? count(mid) : k + 1;
+    thres = mid;
+    ++steps;
+    if (cnt == k) {
+      hit = true;
+      if (MODE == kEarly) lo = mid;
+      break;
+    }
+    if (cnt < k) hi = mid; else lo = mid;
+  }
+  // Two classes and a limit for each (as in rtopk_block_kernel).
+  float tA, tB = 0.0f;
+  int limA = k, limB = 0;
+  if (MODE == kEarly) {
+    tA = lo;
+    if (!(tA >= T0)) return false;
+  } else if (hit) {
+    tA = thres;
+  } else {
+    const int na = count(hi);
+    tA = hi;
+    tB = lo;
+    limA = na < k ? na : k;
+    limB = k - limA;
+    if (MODE == kEps && limB > 0 && !(tB >= T0)) return false;
+  }
+  if constexpr (MODE == kEps) {
+    if (out_iters != nullptr && tid == 0) out_iters[r] = hit ? steps : steps + 1;
+  }
+
+  uint32_t nA = 0, nB = 0;
+#pragma unroll
+  for (int i = 0; i < kMergeRegs; ++i) {
+    if (i < per) {
+      nA += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(key[i] >= tA));
+      if (limB > 0) nB += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(key[i] >= tB && !(key[i] >= tA)));
+    }
+  }
+  if (lane == 0) {
+    s_cls[0][wave] = (int)nA;
+    s_cls[1][wave] = (int)nB;
+  }
+  __syncthreads();
+  uint32_t posA0 = 0, posB0 = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    posA0 += w < wave ? (uint32_t)s_cls[0][w] : 0u;
+    posB0 += w < wave ? (uint32_t)s_cls[1][w] : 0u;
+  }
+  float* ov = out_vals + r * (int64_t)k;
+  int32_t* oi = out_idx + r * (int64_t)k;
+#pragma unroll
+  for (int i = 0; i < kMergeRegs; ++i) {
+    if (i < per) {
+      const bool a = key[i] >= tA, b = limB > 0 && key[i] >= tB && !a;
+      const uint64_t mA = __builtin_amdgcn_ballot_w64(a), mB = __builtin_amdgcn_ballot_w64(b);
+      const uint32_t posA = lanes_below(mA, posA0), posB = lanes_below(mB, posB0);
+      if ((a && posA < (uint32_t)limA) || (b && posB < (uint32_t)limB)) {
+        const uint32_t pos = (posA < (uint32_t)limA ? posA : (uint32_t)limA) + (posB < (uint32_t)limB ? posB : (uint32_t)limB);
+        ov[pos] = keyof<NEG>(key[i]);
+        oi[pos] = (int32_t)col[i];
+      }
+      posA0 += (uint32_t)__builtin_popcountll(mA);
+      posB0 += (uint32_t)__builtin_popcountll(mB);
+    }
+  }
+  return true;
+}
+
+template <int NW, int MODE, bool NEG>
+__global__ void __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(4)))
+    rtopk_merge_kernel(const float* __restrict__ in, int M, int k, int max_iter, float eps_rel,
+                       float* __restrict__ out_vals, int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters,
+                       const SegmentHead* __restrict__ heads, const uint2* __restrict__ lists, int segments, int stride) {
+  const int64_t r = blockIdx.x;
+  if (merge_row<NW, MODE, NEG>(r, k, max_iter, eps_rel, out_vals, out_idx, out_iters, heads, lists, segments, stride)) return;
+  __syncthreads();
+  stream_row<NW, 4, MODE, NEG>(r, in, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters);
+}
+
+template <int MODE, bool NEG>
+hipError_t launch_split(const Split& s, void* scratch, const LaunchArgs& a) {
+  for (int64_t r0 = 0; r0 < a.N; r0 += s.rows) {
+    const int64_t rows = a.N - r0 < s.rows ? a.N - r0 : s.rows;
+    const float* in = static_cast<const float*>(a.in) + r0 * a.M;
+    SegmentHead* heads = static_cast<SegmentHead*>(scratch);
+    uint2* lists = reinterpret_cast<uint2*>(heads + rows * s.segments);
+    const auto segment = s.w == 4 ? (s.ng == 12 ? &rtopk_segment_kernel<12, 4, NEG> : &rtopk_segment_kernel<16, 4, NEG>)
+                                  : (s.ng == 12 ? &rtopk_segment_kernel<12, 8, NEG> : &rtopk_segment_kernel<16, 8, NEG>);
+    hipError_t err = launch_kernel(segment, dim3((unsigned)(rows * s.segments)), dim3(s.w * kWave), 0, a.stream, in, a.M, a.k,
+                                   s.segments, s.length, s.stride, heads, lists);
+    if (err != hipSuccess) return err;
+    const auto merge = s.merge_waves == 4   ? &rtopk_merge_kernel<4, MODE, NEG>
+                       : s.merge_waves == 8 ? &rtopk_merge_kernel<8, MODE, NEG>
+                                            : &rtopk_merge_kernel<16, MODE, NEG>;
+    err = launch_kernel(merge, dim3((unsigned)rows), dim3(s.merge_waves * kWave), 0, a.stream, in, a.M, a.k, a.max_iter,
+                        a.eps_rel, static_cast<float*>(a.out_vals) + r0 * a.k, static_cast<int32_t*>(a.out_idx) + r0 * a.k,
+                        a.out_iters ? a.out_iters + r0 : nullptr, heads, lists, s.segments, s.stride);
+    if (err != hipSuccess) return err;
+  }
+  return hipSuccess;
+}
+
+}  // namespace rtopk

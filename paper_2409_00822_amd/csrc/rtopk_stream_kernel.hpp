@@ -39,7 +39,6 @@
 namespace rtopk {
 
 constexpr int kStreamWaves = 16;
-constexpr int kStreamThreads = kStreamWaves * kWave;
 constexpr int kLevels = 8;
 constexpr int kLeaves = 1 << kLevels;
 #ifndef RTOPK_STREAM_WAVES_PER_SIMD
@@ -58,10 +57,12 @@ __device__ __forceinline__ void stream_load(const float* p, float (&v)[G]) {
   for (int c = 0; c < G; ++c) v[c] = q[c];
 }
 
-template <int G, int MODE, bool NEG>
-__global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_per_eu(RTOPK_STREAM_WAVES_PER_SIMD)))
-    rtopk_stream_kernel(const float* __restrict__ in, int64_t N, int M, int k, int max_iter, float eps_rel,
-                        float* __restrict__ out_vals, int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters) {
+// One row, by the whole workgroup of NW wavefronts (at least four: the 256 leaves have a thread each).
+template <int NW, int G, int MODE, bool NEG>
+__device__ __forceinline__ void stream_row(const int64_t r, const float* __restrict__ in, int M, int k, int max_iter,
+                                           float eps_rel, float* __restrict__ out_vals, int32_t* __restrict__ out_idx,
+                                           int32_t* __restrict__ out_iters) {
+  constexpr int kStreamWaves = NW, kStreamThreads = NW * kWave;
   __shared__ float s_tab[kLeaves];               // thresholds of the tree's nodes 1..255 (heap order; [0] unused)
   __shared__ float s_bnd[kLeaves + 1];           // the same thresholds in value order, with lo and hi at the ends
   __shared__ int s_hist[kStreamWaves][kLeaves];  // per-wavefront leaf histograms
@@ -78,8 +79,6 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t r = blockIdx.x;
-  if (r >= N) return;
   const float* row = in + r * (int64_t)M;
   constexpr int kChunk = kStreamThreads * G;
 
@@ -125,7 +124,7 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
     load_group<kF32, G>(row, (u < u1 && c0 < Mv) ? c0 : 0, slot);
   };
   uint2* kept = &s_kept[wave][0];
-  if (tid < 2 * kLeaves) s_parts[tid >> kLevels][tid & (kLeaves - 1)] = 0;  // the third is cleared by the first raise
+  for (int i = tid; i < 2 * kLeaves; i += kStreamThreads) s_parts[i >> kLevels][i & (kLeaves - 1)] = 0;  // the third is cleared by the first raise
   __syncthreads();
 
   // ---- pass 0: row minimum and maximum, and the keys that can still be among the k winners -------------
@@ -621,7 +620,7 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
       }
       const int sum = suffix_of(h);
       if (tid < kLeaves) s_suffix[tid] = sum;
-      if (tid == kLeaves) s_suffix[kLeaves] = 0;
+      if (tid == 0) s_suffix[kLeaves] = 0;
       __syncthreads();
     }
     const int above_all = __builtin_amdgcn_readfirstlane((int)row16_sum(lane < kStreamWaves ? (uint32_t)s_above[lane] : 0u));
@@ -855,10 +854,19 @@ __global__ void __launch_bounds__(kStreamThreads) __attribute__((amdgpu_waves_pe
   }
 }
 
+template <int G, int MODE, bool NEG>
+__global__ void __launch_bounds__(kStreamWaves * kWave) __attribute__((amdgpu_waves_per_eu(RTOPK_STREAM_WAVES_PER_SIMD)))
+    rtopk_stream_kernel(const float* __restrict__ in, int64_t N, int M, int k, int max_iter, float eps_rel,
+                        float* __restrict__ out_vals, int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters) {
+  const int64_t r = blockIdx.x;
+  if (r >= N) return;
+  stream_row<kStreamWaves, G, MODE, NEG>(r, in, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters);
+}
+
 template <int MODE, bool NEG>
 hipError_t launch_stream(const LaunchArgs& a) {
   if (a.N > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-  return launch_kernel(rtopk_stream_kernel<4, MODE, NEG>, dim3((unsigned)a.N), dim3(kStreamThreads), 0, a.stream,
+  return launch_kernel(rtopk_stream_kernel<4, MODE, NEG>, dim3((unsigned)a.N), dim3(kStreamWaves * kWave), 0, a.stream,
                        static_cast<const float*>(a.in), a.N, a.M, a.k, a.max_iter, a.eps_rel,
                        static_cast<float*>(a.out_vals), static_cast<int32_t*>(a.out_idx), a.out_iters);
 }

@@ -96,6 +96,21 @@ PyObject* pair(Output& a, Output& b) {
   return t;
 }
 
+// Scratch memory for a shape that can use it (rtopk_workspace_bytes), from torch's allocator: stream-ordered, so it may
+// go back as soon as the call has enqueued its work on the current stream.
+struct Scratch {
+  Tensor tensor;
+  void* data = nullptr;
+  int64_t bytes = 0;
+  Scratch(const Tensor& x, int32_t k, int32_t variant, int32_t max_iter) {
+    bytes = rtopk_workspace_bytes(x.size(0), (int32_t)x.size(1), k, variant, max_iter);
+    if (bytes > 0) {
+      tensor = at::empty({bytes}, at::TensorOptions().dtype(at::kByte).device(x.device()));
+      data = tensor.data_ptr();
+    }
+  }
+};
+
 // select(which, x, k, max_iter, out_vals, out_idx): the entry points that return pairs.  which: 0 fp32, 1 fp32 with
 // byte-wide columns, 2 the k smallest, 3 half, 4 bfloat16; plus 8 for exact mode (max_iter is then not looked at).
 PyObject* select(PyObject*, PyObject* const* args, Py_ssize_t n) {
@@ -116,7 +131,12 @@ PyObject* select(PyObject*, PyObject* const* args, Py_ssize_t n) {
     const void* in = x->data_ptr();
     void *ov = v.tensor.data_ptr(), *oi = i.tensor.data_ptr(), *s = stream_of(*x);
     const int32_t m = (int32_t)M;
+    const int32_t variant = (exact ? RTOPK_EXACT : RTOPK_EARLY) + (which == 2 ? RTOPK_SMALLEST : 0);
+    Scratch w(*x, which == 0 || which == 2 ? k : 0, variant, max_iter);  // (none for k = 0)
     const int status = unlocked([&]() -> int {
+      if (w.bytes > 0)
+        return rtopk_select_ws(static_cast<const float*>(in), N, m, k, variant, max_iter, 0.0f, static_cast<float*>(ov),
+                               static_cast<int32_t*>(oi), nullptr, w.data, w.bytes, s);
       const float* f = static_cast<const float*>(in);
       const uint16_t* h = static_cast<const uint16_t*>(in);
       float* fv = static_cast<float*>(ov);
@@ -156,7 +176,10 @@ PyObject* select_eps(PyObject*, PyObject* const* args, Py_ssize_t n) {
     int32_t* oi = static_cast<int32_t*>(i.tensor.data_ptr());
     int32_t* ot = iters ? static_cast<int32_t*>(t.tensor.data_ptr()) : nullptr;
     void* s = stream_of(*x);
-    const int status = unlocked([&] { return rtopk_rowwise_eps(in, N, (int32_t)M, k, eps, ov, oi, ot, s); });
+    Scratch w(*x, k, RTOPK_EPS, 0);
+    const int status = unlocked([&] {
+      return rtopk_select_ws(in, N, (int32_t)M, k, RTOPK_EPS, 0, eps, ov, oi, ot, w.data, w.bytes, s);
+    });
     if (status != RTOPK_OK) return none();
     if (!iters) return pair(v, i);
     PyObject* r = PyTuple_New(3);

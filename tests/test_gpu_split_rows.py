@@ -1,0 +1,102 @@
+"""GPU parity of rows spread over several workgroups (fp32, more than 32768 columns): segment counts and tails, k around
+the lists' limits, rows whose segments overflow or whose last threshold is below the floor, several batches of rows.
+
+Selections are copies of inputs and their columns: tolerance 0.
+"""
+import ctypes
+
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_filtered_rows import _gpu, _rows, _same
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("M", [32769, 40000, 50001, 65536, 65537, 98304, 131075, 400003])
+def test_every_mode_on_every_kind_of_row(M):
+    R = _gpu()
+    x = _rows(M, 6000 + M)
+    xd = torch.from_numpy(x).cuda()
+    for k in (1, 50, 256, 257, 512, 513):
+        tag = f"M={M} k={k}"
+        _same(R.rtopk_rowwise_exact(xd, k), oracle.topk_exact(x, k), tag + " exact")
+        _same(R.rtopk_rowwise_exact_smallest(xd, k), oracle.topk_exact_smallest(x, k), tag + " smallest")
+        for mi in (7, 8, 13, 1 << 30):
+            _same(R.rtopk_rowwise(xd, k, mi), oracle.topk_earlystop(x, k, min(mi, 600)), tag + f" early {mi}")
+        _same(R.rtopk_rowwise_smallest(xd, k, 10), oracle.topk_earlystop_smallest(x, k, 10), tag + " smallest early")
+        for eps in (1e-2, 1e-5):
+            ev, ei, et = oracle.alg1(x, k, eps_rel=eps)
+            got = R.rtopk_rowwise_eps(xd, k, eps, want_iters=True)
+            _same(got, (ev, ei), tag + f" eps {eps}")
+            assert np.array_equal(got[2].cpu().numpy(), et), tag + " iterations"
+
+
+@pytest.mark.parametrize("N", [1, 3, 130, 700])
+def test_few_and_many_rows(N):
+    R = _gpu()
+    x = np.tile(_rows(34000, 6100), (N // 10 + 1, 1))[:N].copy()
+    x[:, 11] = np.arange(N, dtype=np.float32) * 0.01
+    xd = torch.from_numpy(x).cuda()
+    _same(R.rtopk_rowwise_exact(xd, 40), oracle.topk_exact(x, 40), f"N={N}")
+
+
+def _plain(R, x, k):
+    """The entry point without scratch memory."""
+    lib = R.load_library()
+    v = torch.empty(x.shape[0], k, device="cuda")
+    i = torch.empty(x.shape[0], k, dtype=torch.int32, device="cuda")
+    s = torch.cuda.current_stream().cuda_stream
+    assert lib.rtopk_rowwise_exact(x.data_ptr(), x.shape[0], x.shape[1], k, v.data_ptr(), i.data_ptr(), s) == 0
+    return v, i
+
+
+def test_scratch_memory_in_several_batches_and_refusals():
+    R = _gpu()
+    lib = R.load_library()
+    lib.rtopk_workspace_bytes.restype = ctypes.c_int64
+    lib.rtopk_workspace_bytes.argtypes = [ctypes.c_int64] + [ctypes.c_int32] * 4
+    N, M, k = 9000, 40000, 512
+    need = lib.rtopk_workspace_bytes(N, M, k, 1, 0)
+    assert 0 < need <= 129 << 20  # bounded: the rows go through it in batches
+    assert lib.rtopk_workspace_bytes(N, 32768, k, 1, 0) == 0 and lib.rtopk_workspace_bytes(N, M, 513, 1, 0) == 0
+    assert lib.rtopk_workspace_bytes(N, M, k, 3, 0) == 0 and lib.rtopk_workspace_bytes(0, M, k, 1, 0) == 0
+    x = torch.randn(N, M, device="cuda")
+    v, i = R.rtopk_rowwise_exact(x, k)
+    pv, pi = _plain(R, x, k)
+    assert torch.equal(i, pi) and torch.equal(v, pv)
+    fn = lib.rtopk_select_ws
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int64] + [ctypes.c_int32] * 4 + [ctypes.c_float] + [ctypes.c_void_p] * 4 + [
+        ctypes.c_int64, ctypes.c_void_p]
+    w = torch.empty(need, dtype=torch.uint8, device="cuda")
+    s = torch.cuda.current_stream().cuda_stream
+    args = lambda variant, ws, nb: (x.data_ptr(), N, M, k, variant, 0, 0.0, v.data_ptr(), i.data_ptr(), None, ws, nb, s)  # noqa: E731
+    assert fn(*args(3, w.data_ptr(), need)) == -2 and fn(*args(6, w.data_ptr(), need)) == -2
+    assert fn(*args(1, w.data_ptr() + 4, need - 4)) == -5
+    assert fn(*args(1, v.data_ptr(), need)) == -8
+    v.zero_()
+    assert fn(*args(1, w.data_ptr(), need - 1)) == 0  # too little: the plain entry point's launch
+    assert torch.equal(v, pv) and torch.equal(i, pi)
+
+
+def test_graph_replays_with_new_inputs():
+    R = _gpu()
+    x = torch.randn(20, 70000, device="cuda")
+    R.rtopk_rowwise_exact(x, 30)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        R.rtopk_rowwise_exact(x, 30)
+    side.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        v, i = R.rtopk_rowwise_exact(x, 30)
+    for seed in range(4):
+        torch.manual_seed(seed)
+        x.copy_(torch.randn(20, 70000, device="cuda"))
+        g.replay()
+        torch.cuda.synchronize()
+        _same((v, i), oracle.topk_exact(x.cpu().numpy(), 30), f"replay {seed}")
+        R.rtopk_rowwise_exact(torch.randn(5, 50000, device="cuda"), 9)
