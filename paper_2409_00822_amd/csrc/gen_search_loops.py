@@ -39,11 +39,33 @@ def count_lines(E, t, neg):
     return out
 
 
-def operands(E, extra_out, extra_in):
+# Where the total is compared with k.  A scalar compare takes a slot of the scalar unit (4.8 cycles per SIMD: it serves
+# four SIMDs in turn), which counts the masks and bounds rows stored in 16 bits; there the vector unit compares, into
+# VCC, from three values per lane on (2^27 values, us, exact / eight steps: 512 bfloat16 columns 110.6 -> 100.8 /
+# 94.2 -> 91.7 with the tied rows' shorter path, 256 columns 100.9 -> 97.8 / 95.2 -> 92.3).  fp32 rows wait for memory and
+# keep the scalar compare (256 columns 106.9 against 108.1 us).  Counting masks on the vector unit as well, through the
+# halves of VCC, balances the two units on paper and measured slower: 512 fp32 columns 105 -> 110 us.
+def on_vector(E, dt):
+    return E >= 3 and dt != 0
+
+
+def compare(E, dt, rel):
+    """c0 against k; `rel` ("lt" or "gt")."""
+    return f'"v_cmp_{rel}_i32 vcc, %[c0], %[vk]\\n\\t"' if on_vector(E, dt) else f'"s_cmp_{rel}_i32 %[c0], %[k]\\n\\t"'
+
+
+def branch(E, dt, taken, label):
+    """Branch to `label` if the last compare came out as `taken`."""
+    if on_vector(E, dt):
+        return f'"s_cbranch_vcc{"nz" if taken else "z"} {label}\\n\\t"'
+    return f'"s_cbranch_scc{1 if taken else 0} {label}\\n\\t"'
+
+
+def operands(E, extra_out, extra_in, dt=0):
     outs = ['[lo] "+v"(lo)', '[hi] "+v"(hi)'] + extra_out
     outs += [f'[m{e}] "=&s"(m[{e}])' for e in range(E)]
     outs += [f'[c{i}] "=&s"(c{i})' for i in range(4)]
-    ins = [f'[x{e}] "v"(x[{e}])' for e in range(E)] + ['[k] "s"(k)'] + extra_in
+    ins = [f'[x{e}] "v"(x[{e}])' for e in range(E)] + ['[vk] "v"(k)' if on_vector(E, dt) else '[k] "s"(k)'] + extra_in
     return outs, ins
 
 
@@ -69,9 +91,9 @@ def gen_exact(E, neg, dt=0):
     if tr:
         L += [f'"v_and_b32 %[u], {tr}, %[u]\\n\\t"']
     L += count_lines(E, "u", neg)
-    L += ['"s_cmp_lt_i32 %[c0], %[k]\\n\\t"', '"s_cbranch_scc1 .Lrtopk_bless_%=\\n\\t"',
-          '"s_cmp_gt_i32 %[c0], %[k]\\n\\t"', '"v_mov_b32 %[lo], %[u]\\n\\t"',
-          '"s_cbranch_scc1 .Lrtopk_a_%=\\n\\t"', '"s_branch .Lrtopk_hit_%=\\n\\t"',
+    L += [compare(E, dt, "lt"), branch(E, dt, True, ".Lrtopk_bless_%="),
+          compare(E, dt, "gt"), '"v_mov_b32 %[lo], %[u]\\n\\t"',
+          branch(E, dt, True, ".Lrtopk_a_%="), '"s_branch .Lrtopk_hit_%=\\n\\t"',
           '".Lrtopk_bless_%=:\\n\\t"', '"v_mov_b32 %[hi], %[u]\\n\\t"']
     L += ['// ---- copy A: midpoint in t, compared with copy B\'s (equal or unordered: converged)',
           '".Lrtopk_a_%=:\\n\\t"', '"v_add_f32 %[t], %[lo], %[hi]\\n\\t"', '"v_mul_f32 %[t], 0.5, %[t]\\n\\t"']
@@ -79,13 +101,13 @@ def gen_exact(E, neg, dt=0):
         L += [f'"v_and_b32 %[t], {tr}, %[t]\\n\\t"']
     L += ['"v_cmp_lg_f32 vcc, %[t], %[u]\\n\\t"', '"s_cbranch_vccz .Lrtopk_conv_%=\\n\\t"']
     L += count_lines(E, "t", neg)
-    L += ['"s_cmp_lt_i32 %[c0], %[k]\\n\\t"', '"s_cbranch_scc1 .Lrtopk_aless_%=\\n\\t"',
-          '"s_cmp_gt_i32 %[c0], %[k]\\n\\t"', '"v_mov_b32 %[lo], %[t]\\n\\t"',
-          '"s_cbranch_scc1 .Lrtopk_b_%=\\n\\t"', '"s_branch .Lrtopk_hit_%=\\n\\t"',
+    L += [compare(E, dt, "lt"), branch(E, dt, True, ".Lrtopk_aless_%="),
+          compare(E, dt, "gt"), '"v_mov_b32 %[lo], %[t]\\n\\t"',
+          branch(E, dt, True, ".Lrtopk_b_%="), '"s_branch .Lrtopk_hit_%=\\n\\t"',
           '".Lrtopk_aless_%=:\\n\\t"', '"v_mov_b32 %[hi], %[t]\\n\\t"', '"s_branch .Lrtopk_b_%=\\n\\t"',
           '".Lrtopk_conv_%=:\\n\\t"', '"s_mov_b32 %[hit], 0\\n\\t"', '"s_branch .Lrtopk_end_%=\\n\\t"',
           '".Lrtopk_hit_%=:\\n\\t"', '"s_mov_b32 %[hit], 1\\n\\t"', '".Lrtopk_end_%=:"']
-    outs, ins = operands(E, ['[t] "=&v"(t)', '[u] "=&v"(u)', '[hit] "=&s"(hit)'], [])
+    outs, ins = operands(E, ['[t] "=&v"(t)', '[u] "=&v"(u)', '[hit] "=&s"(hit)'], [], dt)
     what = {0: "", 1: ", half rows (midpoints truncated to 11 bits)", 2: ", bfloat16 rows (midpoints truncated to 8 bits)"}[dt]
     return (f"""// Algorithm 1 at epsilon = 0, {E} values per lane{', keys = negated values' if neg else ''}{what}.  Returns true when a step counted exactly k (m[] then
 // selects the answer); false when the search converged first (lo, hi hold the final bounds).  Steps
@@ -99,22 +121,23 @@ __device__ __forceinline__ bool search_exact_asm(const float (&x)[{E}], float& l
 """ + emit(L, outs, ins) + "  return hit != 0;\n}\n")
 
 
-def gen_early(E, neg):
+def gen_early(E, neg, dt=0):  # dt: 0, or 1 for rows stored in 16 bits
     L = ['"s_mov_b32 %[c0], -1\\n\\t"', '"s_sub_u32 %[it], %[n], 1\\n\\t"', '"s_cbranch_scc1 .Lrtopk_end_%=\\n\\t"',
          '".Lrtopk_top_%=:\\n\\t"', '"v_add_f32 %[t], %[lo], %[hi]\\n\\t"', '"v_mul_f32 %[t], 0.5, %[t]\\n\\t"']
     L += count_lines(E, "t", neg)
-    L += ['"s_cmp_lt_i32 %[c0], %[k]\\n\\t"', '"s_cbranch_scc1 .Lrtopk_less_%=\\n\\t"',
-          '"s_cmp_gt_i32 %[c0], %[k]\\n\\t"', '"v_mov_b32 %[lo], %[t]\\n\\t"',
-          '"s_cbranch_scc0 .Lrtopk_end_%=\\n\\t"', '"s_sub_u32 %[it], %[it], 1\\n\\t"',
+    L += [compare(E, dt, "lt"), branch(E, dt, True, ".Lrtopk_less_%="),
+          compare(E, dt, "gt"), '"v_mov_b32 %[lo], %[t]\\n\\t"',
+          branch(E, dt, False, ".Lrtopk_end_%="), '"s_sub_u32 %[it], %[it], 1\\n\\t"',
           '"s_cbranch_scc0 .Lrtopk_top_%=\\n\\t"', '"s_branch .Lrtopk_end_%=\\n\\t"',
           '".Lrtopk_less_%=:\\n\\t"', '"v_mov_b32 %[hi], %[t]\\n\\t"', '"s_sub_u32 %[it], %[it], 1\\n\\t"',
           '"s_cbranch_scc0 .Lrtopk_top_%=\\n\\t"', '".Lrtopk_end_%=:"']
-    outs, ins = operands(E, ['[t] "=&v"(t)', '[it] "=&s"(it)'], ['[n] "s"(max_iter)'])
-    return (f"""// Algorithm 2, {E} values per lane{', keys = negated values' if neg else ''}: max_iter steps (fewer when a step counts exactly k, after which the
+    outs, ins = operands(E, ['[t] "=&v"(t)', '[it] "=&s"(it)'], ['[n] "s"(max_iter)'], dt)
+    return (f"""// Algorithm 2, {E} values per lane{', keys = negated values' if neg else ''}{', rows stored in 16 bits' if dt else ''}: max_iter steps (fewer when a step counts exactly k, after which the
 // selection cannot change).  Returns the count of the last step, or -1 when no step ran; when it is
 // >= k, m[] holds the masks of x >= lo.
 __device__ __forceinline__ int search_early_asm(const float (&x)[{E}], float& lo, float& hi, int k, int max_iter,
-                                                uint64_t (&m)[{E}], std::{"true" if neg else "false"}_type /*keys negated*/) {{
+                                                uint64_t (&m)[{E}], std::{"true" if neg else "false"}_type /*keys negated*/,
+                                                std::{"true" if dt else "false"}_type /*rows stored in 16 bits*/) {{
   float t;
   int c0, c1, c2, c3, it;
 """ + emit(L, outs, ins) + "  return c0;\n}\n")
@@ -232,6 +255,7 @@ def main():
             text += gen_exact(E, neg) + "\n" + gen_early(E, neg) + "\n"
         for dt in (1, 2):
             text += gen_exact(E, False, dt) + "\n"
+        text += gen_early(E, False, 1) + "\n"
     for R in (2, 4, 8):
         text += gen_minmax(R) + "\n"
     path = os.path.join(here, "rtopk_search_loops.inc")

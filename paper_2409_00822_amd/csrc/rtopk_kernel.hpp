@@ -425,6 +425,26 @@ __device__ __forceinline__ int nth_column_in_band(const float (&x)[Layout<G, NG>
   return __builtin_amdgcn_readlane(v, 63);
 }
 
+// Keeps the first `want` set bits, in column order, of the masks m[] (element e of lane l is bit l of m[e]).
+template <int G, int NG>
+__device__ __forceinline__ void keep_first(uint32_t want, uint64_t (&m)[Layout<G, NG>::E]) {
+  using L = Layout<G, NG>;
+  uint32_t base = 0;  // wave-uniform: set bits in earlier groups
+  static_for<L::GROUPS>([&](auto gc) {
+    constexpr int g = decltype(gc)::value, GW = L::width(g), e0 = L::first(g);
+    uint32_t pos = base;
+#pragma unroll
+    for (int c = 0; c < GW; ++c) pos = lanes_below(m[e0 + c], pos);
+#pragma unroll
+    for (int c = 0; c < GW; ++c) {
+      const uint64_t all = m[e0 + c];
+      if constexpr (g + 1 < L::GROUPS) base += (uint32_t)__builtin_popcountll(all);
+      m[e0 + c] = all & __builtin_amdgcn_ballot_w64(pos < want);
+      if (c + 1 < GW) pos = add_mask_bit(pos, all);
+    }
+  });
+}
+
 // x where bit `lane` of mask is set, +0 elsewhere: one v_cndmask with the lane mask as its condition.
 __device__ __forceinline__ float keep_where(float x, uint64_t mask) {
   float r;
@@ -880,6 +900,31 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
       return gather_band<E, NEG, false, BR>(x, lo, hi, lane, stage_addr, band, nb);
     }
   };
+  // A search that ended without a count of k: everything >= hi (cut at k by column when hi is still the row maximum and
+  // k or more tie there), then the first columns of [lo, hi) up to k.  The masks of both sets are at hand in scalar
+  // registers at these widths, so the band is cut there and the union leaves in one plain pass.  Common for rows stored in
+  // 16 bits (30 % of 256 normal bfloat16 values, k = 32, tie across the k-th place); finding the last band member's column
+  // first and forming each element's threshold from it took three passes over the elements.
+  auto emit_tied = [&]() {
+    if constexpr (KEEP) {
+      uint64_t band[E];
+      int na = 0;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        m[e] = __builtin_amdgcn_ballot_w64(keyof<NEG>(x[e]) >= hi);
+        band[e] = __builtin_amdgcn_ballot_w64(keyof<NEG>(x[e]) >= lo) & ~m[e];
+        na += __builtin_popcountll(m[e]);
+      }
+      if (na >= k) {
+        emit_selection<G, NG, FULL, true, false, NEG, DENSE>(x, m, hi, hi, -1, lane, M, k, stage_addr, y);
+      } else {
+        keep_first<G, NG>((uint32_t)(k - na), band);
+#pragma unroll
+        for (int e = 0; e < E; ++e) m[e] |= band[e];
+        emit_selection<G, NG, FULL, false, false, NEG, DENSE>(x, m, hi, hi, -1, lane, M, k, stage_addr, y);
+      }
+    }
+  };
   if constexpr (MODE == kExact) {
     // The loop ends on cnt == k, or once the fp32 midpoint stops changing: then no representable
     // threshold lies strictly inside (lo, hi).  The latter is tested every second step against the
@@ -947,9 +992,13 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
       // Everything >= hi is taken first (cut at k by column when hi is still the row maximum and k
       // or more tie there); the first k - na members of [lo, hi) follow: all columns up to the
       // (k - na)-th member's column select against lo, the others against hi.
-      const int na = count(hi);
-      const int split = nth_column_in_band<G, NG, FULL, NEG>(x, lane, M, hi, lo, k - (na < k ? na : k));
-      emit_selection<G, NG, FULL, true, true, NEG, DENSE>(x, nullptr, hi, lo, split, lane, M, k, stage_addr, y);
+      if constexpr (KEEP && DT != kF32) {  // fp32 rows hardly ever get here
+        emit_tied();
+      } else {
+        const int na = count(hi);
+        const int split = nth_column_in_band<G, NG, FULL, NEG>(x, lane, M, hi, lo, k - (na < k ? na : k));
+        emit_selection<G, NG, FULL, true, true, NEG, DENSE>(x, nullptr, hi, lo, split, lane, M, k, stage_addr, y);
+      }
     }
     return 0;
   } else if constexpr (MODE == kEps) {
@@ -997,14 +1046,19 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
       emit_selection<G, NG, FULL, false, !KEEP, NEG, DENSE>(x, m, thres, thres, -1, lane, M, k, stage_addr, y);
       return steps;
     }
-    const int na = count(hi);
-    const int split = nth_column_in_band<G, NG, FULL, NEG>(x, lane, M, hi, lo, k - (na < k ? na : k));
-    emit_selection<G, NG, FULL, true, true, NEG, DENSE>(x, nullptr, hi, lo, split, lane, M, k, stage_addr, y);
+    if constexpr (KEEP) {
+      emit_tied();
+    } else {
+      const int na = count(hi);
+      const int split = nth_column_in_band<G, NG, FULL, NEG>(x, lane, M, hi, lo, k - (na < k ? na : k));
+      emit_selection<G, NG, FULL, true, true, NEG, DENSE>(x, nullptr, hi, lo, split, lane, M, k, stage_addr, y);
+    }
     return steps + 1;
   } else {
     int cnt = -1;
     if constexpr (ASM) {
-      cnt = search_early_asm(x, lo, hi, k, max_iter, m, std::integral_constant<bool, NEG>());
+      cnt = search_early_asm(x, lo, hi, k, max_iter, m, std::integral_constant<bool, NEG>(),
+                             std::integral_constant<bool, DT != kF32>());
     } else {
       // narrowing as in Algorithm 1: every midpoint lies in [lo, hi], so the identity behind it holds
       constexpr bool NARROW = narrows(E, MODE);
