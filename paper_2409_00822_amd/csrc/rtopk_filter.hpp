@@ -47,17 +47,18 @@ __device__ __forceinline__ float lane_negmin(const float (&x)[E]) {
   return E % 2 == 0 ? key_max_on<!NEG>(nm, x[E - 1]) : nm;
 }
 
-// Group maxima: gm[j] = largest key of elements 16 j .. 16 j + 15.
-constexpr int kFilterGroup = 16;
-template <int E, bool NEG>
-__device__ __forceinline__ void lane_group_maxima(const float (&x)[E], float (&gm)[E / kFilterGroup]) {
-  static_assert(E % kFilterGroup == 0, "whole groups only");
+// Group maxima: gm[j] = largest key of the j-th of the lane's J groups of consecutive elements.
+constexpr int kFilterGroup = 16;  // elements per group in the workgroup-per-row kernels
+template <int E, bool NEG, int J>
+__device__ __forceinline__ void lane_group_maxima(const float (&x)[E], float (&gm)[J]) {
+  constexpr int S = E / J;
+  static_assert(E % J == 0 && S % 4 == 0, "whole groups of whole quads only");
 #pragma unroll
-  for (int j = 0; j < E / kFilterGroup; ++j) {
-    float m = key_max3<NEG>(x[16 * j], x[16 * j + 1], x[16 * j + 2]);
+  for (int j = 0; j < J; ++j) {
+    float m = key_max3<NEG>(x[S * j], x[S * j + 1], x[S * j + 2]);
 #pragma unroll
-    for (int c = 3; c + 1 < kFilterGroup; c += 2) m = key_max3_on<NEG>(m, x[16 * j + c], x[16 * j + c + 1]);
-    gm[j] = key_max_on<NEG>(m, x[16 * j + 15]);
+    for (int c = 3; c + 1 < S; c += 2) m = key_max3_on<NEG>(m, x[S * j + c], x[S * j + c + 1]);
+    gm[j] = key_max_on<NEG>(m, x[S * j + S - 1]);
   }
 }
 
@@ -403,6 +404,180 @@ __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], 
       if (is_chosen(e)) {
         const uint32_t place = filter_rank(s, s.maps.chosen, (int)e.y);
         if (place < (uint32_t)k) emit((int)place, e.x, (int)e.y);
+      }
+    }
+  }
+  return kFilterDone;
+}
+
+// ---- one wavefront per row ------------------------------------------------------------------------------
+//
+// The same for a row that one wavefront holds (24 to 128 values per lane).  Without other wavefronts to meet, both
+// lists are kept in column order -- a quad's slot is the number of members in lower lanes and earlier groups (a lane
+// mask's prefix count), a single's the scan of its quad's members -- so the winners' places are prefix counts too and no
+// bitmap is needed.  The singles overwrite the quads that have been read.
+
+// Group maxima per lane: 256 per row suffice for a small k; up to 55 % of them may lie above the floor, which then has
+// 1.45 k candidates.  Twice as many for a larger k.
+constexpr int wave_groups(int E, bool many) {
+  return E <= 24 ? E / 4 : (!many ? 4 : (E == 48 ? 12 : 8));
+}
+constexpr int wave_filter_small_k(int E) { return 35 * wave_groups(E, false); }
+// (Rows of up to 16 values per lane keep the full-width search: at k = M / 8 their lists are a fifth of the row, the LDS
+// they take leaves fewer wavefronts in flight, and 65536 x 1024 fp32 went from 62 to 72 us.)
+constexpr int wave_filter_max_k(int E) { return E < 24 ? 0 : 35 * wave_groups(E, true); }
+// Quads, and singles, that the lists of a row hold, and the pairs' worth of LDS they take.
+__host__ __device__ constexpr int wave_filter_room(int k) { return (k + k / 2 + 48 + 63) & ~63; }
+__host__ __device__ constexpr int wave_filter_pairs(int k) { return wave_filter_room(k) * 20 / 8; }
+
+// One row.  x: masked elements; lo, hi: the keys' minimum and maximum; lists: wave_filter_pairs(k) pairs of LDS, 16-byte
+// aligned; stage: where the pairs go (it may be the same memory).  In the dense form thi, tlo, split say which elements
+// stay.  Returns kFilterDone, kFilterNoList, or (Algorithm 2, lo then its last minimum) kFilterBoundOnly.
+template <int G, int NG, bool FULL, int MODE, bool NEG, int DT, bool DENSE>
+__device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E], int lane, int M, int k, int max_iter,
+                                               float eps, float& lo, float hi, uint2* lists, uint2* stage, float& thi,
+                                               float& tlo, int& split, int& iterations) {
+  using L = Layout<G, NG>;
+  constexpr int E = L::E;
+  const int room = wave_filter_room(k);
+  float4* quad = reinterpret_cast<float4*>(lists);
+  uint32_t* id = reinterpret_cast<uint32_t*>(quad + room);  // first column of a quad
+
+  float T0, probe;
+  if (k <= wave_filter_small_k(E)) {  // uniform over the launch
+    float gm[wave_groups(E, false)];
+    lane_group_maxima<E, NEG>(x, gm);
+    T0 = floor_of_maxima(gm, k + 1, lo, hi, probe);
+  } else {
+    float gm[wave_groups(E, true)];
+    lane_group_maxima<E, NEG>(x, gm);
+    T0 = floor_of_maxima(gm, k + 1, lo, hi, probe);
+  }
+
+  // quads with a key at or above the floor, in column order
+  uint32_t nq = 0;  // wave-uniform
+  static_for<L::GROUPS>([&](auto gc) {
+    constexpr int g = decltype(gc)::value, e0 = L::first(g), H = L::width(g) / 4;
+    int ln = lane;  // opaque per group, see compact_masks
+    asm volatile("" : "+v"(ln));
+    uint64_t m[H];
+    uint32_t slot = nq;
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      const int e = e0 + 4 * h;
+      m[h] = __builtin_amdgcn_ballot_w64(key_max_on<NEG>(key_max3<NEG>(x[e], x[e + 1], x[e + 2]), x[e + 3]) >= T0);
+      slot = lanes_below(m[h], slot);
+    }
+    const int col = group_col<G, NG, FULL>(g, ln, M);
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      const int e = e0 + 4 * h;
+      if (((m[h] >> lane) & 1) != 0 && slot < (uint32_t)room) {
+        quad[slot] = make_float4(x[e], x[e + 1], x[e + 2], x[e + 3]);
+        id[slot] = (uint32_t)(col + 4 * h);
+      }
+      nq += (uint32_t)__builtin_popcountll(m[h]);
+      if (h + 1 < H) slot = add_mask_bit(slot, m[h]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  });
+  if (nq > (uint32_t)room) return kFilterNoList;
+
+  // their singles; a round's quads are in registers before it writes, and it writes no further than it has read
+  uint32_t n = 0;
+  for (uint32_t j0 = 0; j0 < nq; j0 += kWave) {
+    const uint32_t j = j0 + (uint32_t)lane;
+    const bool live = j < nq;
+    const float4 v = quad[live ? j : 0];
+    const uint32_t col = id[live ? j : 0];
+    const float e[4] = {v.x, v.y, v.z, v.w};
+    bool keep[4];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      keep[c] = live && keyof<NEG>(e[c]) >= T0;
+      mine += keep[c] ? 1u : 0u;
+    }
+    const uint32_t incl = wave_inclusive_scan_dpp(mine);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+    if (n + total > 2 * (j0 + kWave)) return kFilterNoList;  // uniform: 8 bytes each over quads of 16 already read
+    uint32_t at = n + incl - mine;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (keep[c]) lists[at] = make_uint2(__float_as_uint(e[c]), col + (uint32_t)c);
+      at += keep[c] ? 1u : 0u;
+    }
+    n += total;
+  }
+  constexpr int kMost = 8;  // registers of singles
+  if (n <= (uint32_t)k || n > (uint32_t)(kMost * kWave)) return kFilterNoList;  // (n <= k only with NaN or infinite keys)
+
+  float thres = lo, l = lo, h = hi;
+  bool hit = false;
+  int steps = 0, cnt = -1, na = 0;
+  if (n <= 2 * kWave) {
+    filter_search<2, MODE, NEG, DT>(lists, (int)n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
+  } else if (n <= 4 * kWave) {
+    filter_search<4, MODE, NEG, DT>(lists, (int)n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
+  } else {
+    filter_search<kMost, MODE, NEG, DT>(lists, (int)n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
+  }
+  // the selection as two thresholds and a limit, see filter_row
+  int limit = 0;
+  iterations = hit ? steps : steps + 1;
+  if constexpr (MODE == kEarly) {
+    lo = l;
+    if (!(l >= T0)) return kFilterBoundOnly;
+    tlo = l;
+    thi = cnt == k ? l : __builtin_inff();
+    limit = cnt == k ? 0 : k;
+  } else if (hit) {
+    thi = tlo = thres;
+  } else if (na >= k) {
+    thi = __builtin_inff();
+    tlo = h;
+    limit = k;
+  } else {
+    thi = h;
+    tlo = l;
+    limit = k - na;
+    if (MODE == kEps && !(l >= T0)) return kFilterNoList;
+  }
+  split = 0x7fffffff;
+  if (DENSE && limit == 0) return kFilterDone;
+
+  // All singles go to registers before the first pair is staged: the stage may be the lists' memory.
+  uint2 s[kMost];
+#pragma unroll
+  for (int i = 0; i < kMost; ++i) {
+    if ((uint32_t)(i * kWave) < n) {  // uniform
+      const uint32_t j = (uint32_t)(i * kWave + lane);
+      s[i] = lists[j < n ? j : 0];
+      if (j >= n) s[i].x = __float_as_uint(NEG ? __builtin_inff() : -__builtin_inff());
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const uint32_t stage_addr = (uint32_t)(uintptr_t)stage;
+  uint32_t place = 0, in_band = 0;  // wave-uniform: chosen so far, members of the cut class so far
+#pragma unroll
+  for (int i = 0; i < kMost; ++i) {
+    if ((uint32_t)(i * kWave) < n) {
+      const float key = keyof<NEG>(__uint_as_float(s[i].x));
+      uint64_t m = __builtin_amdgcn_ballot_w64(key >= thi);
+      if (limit > 0) {  // uniform
+        const uint64_t band = __builtin_amdgcn_ballot_w64(key >= tlo) & ~m;
+        const uint64_t first = band & __builtin_amdgcn_ballot_w64(lanes_below(band, in_band) < (uint32_t)limit);
+        in_band += (uint32_t)__builtin_popcountll(band);
+        m |= first;
+        if constexpr (DENSE) {
+          if (first != 0) split = __builtin_amdgcn_readlane((int)s[i].y, 63 - __builtin_clzll(first));
+        }
+      }
+      if constexpr (!DENSE) {
+        const uint32_t pos = lanes_below(m, place);
+        m &= __builtin_amdgcn_ballot_w64(pos < (uint32_t)k);  // (more than k only with NaN or infinite keys)
+        lds_store_pair_masked(m, stage_addr + pos * 8u, s[i].x, s[i].y);
+        place += (uint32_t)__builtin_popcountll(m);
       }
     }
   }

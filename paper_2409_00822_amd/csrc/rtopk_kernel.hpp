@@ -811,6 +811,19 @@ constexpr int band_scratch_floats(int E) {
   return narrows(E, 0) ? band_regs(E) * kWave + (scatter_gathers(E) ? kWave : 0) : 0;
 }
 
+// Pairs of LDS per wavefront of R rows of E values per lane: the staged pairs (whose place the band scratch and, for one
+// row, the lists of rtopk_filter.hpp take before there are any), and behind them the lists of several rows in turn.
+__host__ __device__ constexpr int staged_pairs(int E, int R, int k) {
+  const int band = band_scratch_floats(E) / 2;
+  return ((R * k > band ? R * k : band) + 1) & ~1;
+}
+__host__ __device__ constexpr int wave_pairs(int E, int R, int k) {
+  const int staged = staged_pairs(E, R, k);
+  if (k > wave_filter_max_k(E)) return staged;
+  const int lists = wave_filter_pairs(k);
+  return R > 1 ? staged + lists : (staged > lists ? staged : lists);
+}
+
 // Search and selection for one row held as xin[E] (lanes past column M hold duplicates of real
 // elements on entry).
 //   MODE: kExact = Algorithm 1 at epsilon = 0, kEarly = Algorithm 2 with max_iter steps,
@@ -819,9 +832,10 @@ constexpr int band_scratch_floats(int E) {
 // evaluated when one of them counted exactly k, one more when the loop ended through its guard.
 //   DENSE: the result is y[] (chosen values in place, +0 elsewhere) instead of pairs staged at `stage`.
 //   row_max, row_min: the row's maximum and minimum (Alg. 1 / Alg. 2, first two steps), wave-uniform.
+//   lists: LDS of the candidates' lists (rtopk_filter.hpp), where k is small enough for them.
 template <int G, int NG, bool FULL, int MODE, bool NEG, int DT = kF32, bool DENSE = false>
 __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], int lane, int M, int k, int max_iter,
-                                          float eps_rel, uint2* stage, float (&y)[Layout<G, NG>::E], float row_max,
+                                          float eps_rel, uint2* stage, uint2* lists, float (&y)[Layout<G, NG>::E], float row_max,
                                           float row_min) {
   using L = Layout<G, NG>;
   constexpr int E = L::E;
@@ -900,6 +914,24 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
       return gather_band<E, NEG, false, BR>(x, lo, hi, lane, stage_addr, band, nb);
     }
   };
+  // Rows of 24 or more values per lane: the lists first.  Algorithm 2 with few steps: see launch_block.
+  if constexpr (wave_filter_max_k(E) > 0) {
+    if (k <= wave_filter_max_k(E) && (MODE != kEarly || max_iter >= 5)) {  // uniform over the launch
+      float thi, tlo;
+      int split, iterations = 0;
+      const float eps = MODE == kEps ? eps_rel * __builtin_fabsf(hi) : 0.0f;
+      const int done = filter_wave_row<G, NG, FULL, MODE, NEG, DT, DENSE>(x, lane, M, k, max_iter, eps, lo, hi, lists, stage,
+                                                                          thi, tlo, split, iterations);
+      if (done == kFilterDone) {
+        if constexpr (DENSE) mask_dense<G, NG, FULL, false, true, NEG>(x, nullptr, thi, tlo, split, lane, M, k, y);
+        return iterations;
+      }
+      if (MODE == kEarly && done == kFilterBoundOnly) {  // the search has run, its last threshold is below the floor
+        emit_selection<G, NG, FULL, true, true, NEG, DENSE>(x, nullptr, lo, lo, -1, lane, M, k, stage_addr, y);
+        return 0;
+      }
+    }
+  }
   // A search that ended without a count of k: everything >= hi (cut at k by column when hi is still the row maximum and
   // k or more tie there), then the first columns of [lo, hi) up to k.  The masks of both sets are at hand in scalar
   // registers at these widths, so the band is cut there and the union leaves in one plain pass.  Common for rows stored in
@@ -1218,19 +1250,17 @@ __global__ void __launch_bounds__(256)
   using L = Layout<G, NG>;
   constexpr int E = L::E;
   using ElemT = typename std::conditional<DT == kF32, float, uint16_t>::type;
-  extern __shared__ uint2 stage_all[];  // [waves per block][R * k] (value bits, column)
+  extern __shared__ __attribute__((aligned(16))) uint2 stage_all[];  // [waves per block][wave_pairs] (value bits, column)
 
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int waves_per_block = (int)(blockDim.x >> 6);
   const int64_t r0 = ((int64_t)blockIdx.x * waves_per_block + wave) * R;
   if (r0 >= N) return;
-  const int nrows = rows_left(N - r0, R);
-  // per wavefront: R*k pairs, and at least the band scratch where the exact search of a wide row uses it
+  int nrows = rows_left(N - r0, R);
   static_assert(!narrows(E, MODE) || R == 1, "the band scratch reuses the staging area of the wavefront's only row");
-  constexpr int kMinPairs = band_scratch_floats(E) / 2;
-  const int pairs_per_wave = R * k > kMinPairs ? R * k : kMinPairs;
-  uint2* stage = stage_all + (size_t)wave * pairs_per_wave;
+  uint2* stage = stage_all + (size_t)wave * wave_pairs(E, R, k);
+  uint2* lists = R > 1 ? stage + staged_pairs(E, R, k) : stage;
 
   // Loading stage: all R rows' loads are issued before any is consumed.
   float x[R][E];
@@ -1252,12 +1282,13 @@ __global__ void __launch_bounds__(256)
   // Row minima and maxima of all R rows, then the searching and selecting stages row by row.
   float row_max[R], row_min[R];
   rows_max_and_min<R, E>(x, row_max, row_min);
+  asm volatile("" : "+s"(nrows));  // opaque: the tests below are scalar compares again, not lane masks kept from the loads
 #pragma unroll
   for (int rr = 0; rr < R; ++rr) {
     if (rr < nrows) {
       float unused[E];
       const int it = select_row<G, NG, FULL, MODE, NEG, DT, false>(x[rr], lane, M, k, max_iter, eps_rel,
-                                                                    stage + (size_t)rr * k, unused, row_max[rr],
+                                                                    stage + (size_t)rr * k, lists, unused, row_max[rr],
                                                                     row_min[rr]);
       if constexpr (MODE == kEps) {
         if (out_iters != nullptr && lane == 0) out_iters[r0 + rr] = it;
@@ -1359,14 +1390,14 @@ __global__ void __launch_bounds__(256)
     rtopk_dense_kernel(const float* __restrict__ in, int64_t N, int M, int k, int max_iter, float* __restrict__ out) {
   using L = Layout<G, NG>;
   constexpr int E = L::E;
-  extern __shared__ uint2 band_scratch[];  // [waves per block][band_regs(E) * 64 floats], wide rows only
+  extern __shared__ __attribute__((aligned(16))) uint2 band_scratch[];  // per wavefront: band or lists, wide rows only
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int waves_per_block = (int)(blockDim.x >> 6);
   const int64_t r0 = ((int64_t)blockIdx.x * waves_per_block + wave) * R;
   if (r0 >= N) return;
-  const int nrows = rows_left(N - r0, R);
-  uint2* scratch = band_scratch + (size_t)wave * (band_scratch_floats(E) / 2);
+  int nrows = rows_left(N - r0, R);
+  uint2* scratch = band_scratch + (size_t)wave * wave_pairs(E, 1, k <= wave_filter_max_k(E) ? k : 1);
 
   float x[R][E];
 #pragma unroll
@@ -1382,11 +1413,12 @@ __global__ void __launch_bounds__(256)
   }
   float row_max[R], row_min[R];
   rows_max_and_min<R, E>(x, row_max, row_min);
+  asm volatile("" : "+s"(nrows));  // opaque: the tests below are scalar compares again, not lane masks kept from the loads
 #pragma unroll
   for (int rr = 0; rr < R; ++rr) {
     if (rr < nrows) {
       float y[E];
-      select_row<G, NG, FULL, MODE, false, kF32, true>(x[rr], lane, M, k, max_iter, 0.0f, scratch, y, row_max[rr],
+      select_row<G, NG, FULL, MODE, false, kF32, true>(x[rr], lane, M, k, max_iter, 0.0f, scratch, scratch, y, row_max[rr],
                                                        row_min[rr]);
       float* orow = out + (r0 + rr) * (int64_t)M;
       static_for<L::GROUPS>([&](auto gc) {
@@ -1405,7 +1437,8 @@ hipError_t launch_dense(const LaunchArgs& a) {
   const int64_t blocks = (batches + waves - 1) / waves;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   if (a.M < Layout<G, NG>::MIN_M || a.M > 64 * Layout<G, NG>::E) return hipErrorInvalidValue;
-  const size_t lds = (size_t)waves * band_scratch_floats(Layout<G, NG>::E) * sizeof(float);
+  constexpr int E = Layout<G, NG>::E;
+  const size_t lds = E < 12 ? 0 : (size_t)waves * wave_pairs(E, 1, a.k <= wave_filter_max_k(E) ? a.k : 1) * sizeof(uint2);
   return launch_kernel(rtopk_dense_kernel<G, NG, R, FULL, MODE>, dim3((unsigned)blocks), dim3(waves * kWave), lds,
                        a.stream, static_cast<const float*>(a.in), a.N, a.M, a.k, a.max_iter,
                        static_cast<float*>(a.out_vals));
@@ -1417,14 +1450,12 @@ template <int G, int NG, int R, bool FULL, int MODE, typename IdxT, bool NEG = f
 hipError_t launch(const LaunchArgs& a) {
   using L = Layout<G, NG>;
   if (a.M < L::MIN_M || a.M > 64 * L::E) return hipErrorInvalidValue;
-  // LDS per wavefront: R*k staged pairs of 8 bytes; at most 64 KiB per block.
-  size_t per_wave = (size_t)R * (size_t)a.k * sizeof(uint2);
-  // the exact search of wide rows gathers its band through the (not yet used) staging area
-  if (per_wave < band_scratch_floats(L::E) * sizeof(float)) per_wave = band_scratch_floats(L::E) * sizeof(float);
+  // LDS per wavefront: at most 64 KiB per block
+  size_t per_wave = (size_t)wave_pairs(L::E, R, a.k) * sizeof(uint2);
   // one wavefront per workgroup, except where a wavefront stages 8 KiB or more of pairs: there four
   // per workgroup measured 7 % faster (2^20 x 256, k = 128: 387 -> 360 us), while at 4 KiB and below
   // one per workgroup is the faster by 3-11 %
-  int waves = per_wave >= 8192 ? 4 : RTOPK_WAVES_PER_BLOCK;
+  int waves = (size_t)R * a.k * sizeof(uint2) >= 8192 ? 4 : RTOPK_WAVES_PER_BLOCK;
   while (waves > 1 && per_wave * waves > 65536) waves >>= 1;
   const int64_t batches = (a.N + R - 1) / R;
   const int64_t blocks = (batches + waves - 1) / waves;
