@@ -412,7 +412,7 @@ __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], 
 
 // ---- one wavefront per row ------------------------------------------------------------------------------
 //
-// The same for a row that one wavefront holds (24 to 128 values per lane).  Without other wavefronts to meet, both
+// The same for a row that one wavefront holds (16 to 128 values per lane).  Without other wavefronts to meet, both
 // lists are kept in column order -- a quad's slot is the number of members in lower lanes and earlier groups (a lane
 // mask's prefix count), a single's the scan of its quad's members -- so the winners' places are prefix counts too and no
 // bitmap is needed.  The singles overwrite the quads that have been read.
@@ -423,9 +423,12 @@ constexpr int wave_groups(int E, bool many) {
   return E <= 24 ? E / 4 : (!many ? 4 : (E == 48 ? 12 : 8));
 }
 constexpr int wave_filter_small_k(int E) { return 35 * wave_groups(E, false); }
-// (Rows of up to 16 values per lane keep the full-width search: at k = M / 8 their lists are a fifth of the row, the LDS
-// they take leaves fewer wavefronts in flight, and 65536 x 1024 fp32 went from 62 to 72 us.)
-constexpr int wave_filter_max_k(int E) { return E < 24 ? 0 : 35 * wave_groups(E, true); }
+// Rows of 16 values per lane: only the kernel of one row, see one_row_lists; the precision-bounded mode, whose trajectory
+// starts at the row's minimum, keeps its full-width search there (k = 128 124 -> 135 us, 64 no difference).  Below 16 the
+// full-width search costs no more than the lists do.
+constexpr int wave_filter_max_k(int E, int R, int mode) {
+  return R > 1 || E < (mode == kEps ? 24 : 16) ? 0 : 35 * wave_groups(E, true);
+}
 // Quads, and singles, that the lists of a row hold, and the pairs' worth of LDS they take.
 __host__ __device__ constexpr int wave_filter_room(int k) { return (k + k / 2 + 48 + 63) & ~63; }
 __host__ __device__ constexpr int wave_filter_pairs(int k) { return wave_filter_room(k) * 20 / 8; }
@@ -509,7 +512,7 @@ __device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E
     }
     n += total;
   }
-  constexpr int kMost = 8;  // registers of singles
+  constexpr int kMost = E <= 16 ? 4 : 8;  // registers of singles
   if (n <= (uint32_t)k || n > (uint32_t)(kMost * kWave)) return kFilterNoList;  // (n <= k only with NaN or infinite keys)
 
   float thres = lo, l = lo, h = hi;
@@ -519,7 +522,7 @@ __device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E
     filter_search<2, MODE, NEG, DT>(lists, (int)n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
   } else if (n <= 4 * kWave) {
     filter_search<4, MODE, NEG, DT>(lists, (int)n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
-  } else {
+  } else if (kMost > 4) {
     filter_search<kMost, MODE, NEG, DT>(lists, (int)n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
   }
   // the selection as two thresholds and a limit, see filter_row

@@ -19,6 +19,9 @@ static hipError_t pick_rows(bool full, bool u8, const LaunchArgs& a) {
 template <int NG>
 static hipError_t pick(bool full, bool u8, const LaunchArgs& a) {
   constexpr int R = rows_per_wave(4 * NG);
+  if constexpr (NG == 4) {
+    if (one_row_lists(kExact, false, a)) return pick_rows<NG, 1>(full, u8, a);
+  }
   if constexpr (R > kRowsPerWaveFew) {
     if (a.N < kFewRows) return pick_rows<NG, kRowsPerWaveFew>(full, u8, a);  // every variant, not only int32 columns
   }

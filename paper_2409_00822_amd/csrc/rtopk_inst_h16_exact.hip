@@ -13,7 +13,10 @@ static hipError_t pick_rows(bool full, const LaunchArgs& a) {
 
 template <int DT, int G, int NG>
 static hipError_t pick(bool full, const LaunchArgs& a) {
-  constexpr int R = rows_per_wave(Layout<G, NG>::E);
+  constexpr int E = Layout<G, NG>::E, R = rows_per_wave(E);
+  if constexpr (E == 16) {
+    if (one_row_lists(kExact, true, a)) return pick_rows<DT, G, NG, 1>(full, a);
+  }
   if constexpr (R > kRowsPerWaveFew) {
     if (a.N < kFewRows) return pick_rows<DT, G, NG, kRowsPerWaveFew>(full, a);
   }

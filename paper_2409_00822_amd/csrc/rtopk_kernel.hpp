@@ -812,16 +812,16 @@ constexpr int band_scratch_floats(int E) {
 }
 
 // Pairs of LDS per wavefront of R rows of E values per lane: the staged pairs (whose place the band scratch and, for one
-// row, the lists of rtopk_filter.hpp take before there are any), and behind them the lists of several rows in turn.
+// row, the lists of rtopk_filter.hpp take before there are any).
 __host__ __device__ constexpr int staged_pairs(int E, int R, int k) {
   const int band = band_scratch_floats(E) / 2;
   return ((R * k > band ? R * k : band) + 1) & ~1;
 }
-__host__ __device__ constexpr int wave_pairs(int E, int R, int k) {
+__host__ __device__ constexpr int wave_pairs(int E, int R, int k, int mode) {
   const int staged = staged_pairs(E, R, k);
-  if (k > wave_filter_max_k(E)) return staged;
+  if (k > wave_filter_max_k(E, R, mode)) return staged;
   const int lists = wave_filter_pairs(k);
-  return R > 1 ? staged + lists : (staged > lists ? staged : lists);
+  return staged > lists ? staged : lists;
 }
 
 // Search and selection for one row held as xin[E] (lanes past column M hold duplicates of real
@@ -832,8 +832,8 @@ __host__ __device__ constexpr int wave_pairs(int E, int R, int k) {
 // evaluated when one of them counted exactly k, one more when the loop ended through its guard.
 //   DENSE: the result is y[] (chosen values in place, +0 elsewhere) instead of pairs staged at `stage`.
 //   row_max, row_min: the row's maximum and minimum (Alg. 1 / Alg. 2, first two steps), wave-uniform.
-//   lists: LDS of the candidates' lists (rtopk_filter.hpp), where k is small enough for them.
-template <int G, int NG, bool FULL, int MODE, bool NEG, int DT = kF32, bool DENSE = false>
+//   R: rows of the wavefront; lists: LDS of the candidates' lists (rtopk_filter.hpp), where k is small enough for them.
+template <int G, int NG, int R, bool FULL, int MODE, bool NEG, int DT = kF32, bool DENSE = false>
 __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], int lane, int M, int k, int max_iter,
                                           float eps_rel, uint2* stage, uint2* lists, float (&y)[Layout<G, NG>::E], float row_max,
                                           float row_min) {
@@ -914,9 +914,9 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
       return gather_band<E, NEG, false, BR>(x, lo, hi, lane, stage_addr, band, nb);
     }
   };
-  // Rows of 24 or more values per lane: the lists first.  Algorithm 2 with few steps: see launch_block.
-  if constexpr (wave_filter_max_k(E) > 0) {
-    if (k <= wave_filter_max_k(E) && (MODE != kEarly || max_iter >= 5)) {  // uniform over the launch
+  // Rows of 16 or more values per lane: the lists first.  Algorithm 2 with few steps: see launch_block.
+  if constexpr (wave_filter_max_k(E, R, MODE) > 0) {
+    if (k <= wave_filter_max_k(E, R, MODE) && (MODE != kEarly || max_iter >= 5)) {  // uniform over the launch
       float thi, tlo;
       int split, iterations = 0;
       const float eps = MODE == kEps ? eps_rel * __builtin_fabsf(hi) : 0.0f;
@@ -1259,8 +1259,7 @@ __global__ void __launch_bounds__(256)
   if (r0 >= N) return;
   int nrows = rows_left(N - r0, R);
   static_assert(!narrows(E, MODE) || R == 1, "the band scratch reuses the staging area of the wavefront's only row");
-  uint2* stage = stage_all + (size_t)wave * wave_pairs(E, R, k);
-  uint2* lists = R > 1 ? stage + staged_pairs(E, R, k) : stage;
+  uint2* stage = stage_all + (size_t)wave * wave_pairs(E, R, k, MODE);
 
   // Loading stage: all R rows' loads are issued before any is consumed.
   float x[R][E];
@@ -1287,8 +1286,8 @@ __global__ void __launch_bounds__(256)
   for (int rr = 0; rr < R; ++rr) {
     if (rr < nrows) {
       float unused[E];
-      const int it = select_row<G, NG, FULL, MODE, NEG, DT, false>(x[rr], lane, M, k, max_iter, eps_rel,
-                                                                    stage + (size_t)rr * k, lists, unused, row_max[rr],
+      const int it = select_row<G, NG, R, FULL, MODE, NEG, DT, false>(x[rr], lane, M, k, max_iter, eps_rel,
+                                                                    stage + (size_t)rr * k, stage, unused, row_max[rr],
                                                                     row_min[rr]);
       if constexpr (MODE == kEps) {
         if (out_iters != nullptr && lane == 0) out_iters[r0 + rr] = it;
@@ -1397,7 +1396,7 @@ __global__ void __launch_bounds__(256)
   const int64_t r0 = ((int64_t)blockIdx.x * waves_per_block + wave) * R;
   if (r0 >= N) return;
   int nrows = rows_left(N - r0, R);
-  uint2* scratch = band_scratch + (size_t)wave * wave_pairs(E, 1, k <= wave_filter_max_k(E) ? k : 1);
+  uint2* scratch = band_scratch + (size_t)wave * wave_pairs(E, R, k <= wave_filter_max_k(E, R, MODE) ? k : 1, MODE);
 
   float x[R][E];
 #pragma unroll
@@ -1418,7 +1417,7 @@ __global__ void __launch_bounds__(256)
   for (int rr = 0; rr < R; ++rr) {
     if (rr < nrows) {
       float y[E];
-      select_row<G, NG, FULL, MODE, false, kF32, true>(x[rr], lane, M, k, max_iter, 0.0f, scratch, scratch, y, row_max[rr],
+      select_row<G, NG, R, FULL, MODE, false, kF32, true>(x[rr], lane, M, k, max_iter, 0.0f, scratch, scratch, y, row_max[rr],
                                                        row_min[rr]);
       float* orow = out + (r0 + rr) * (int64_t)M;
       static_for<L::GROUPS>([&](auto gc) {
@@ -1438,7 +1437,7 @@ hipError_t launch_dense(const LaunchArgs& a) {
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   if (a.M < Layout<G, NG>::MIN_M || a.M > 64 * Layout<G, NG>::E) return hipErrorInvalidValue;
   constexpr int E = Layout<G, NG>::E;
-  const size_t lds = E < 12 ? 0 : (size_t)waves * wave_pairs(E, 1, a.k <= wave_filter_max_k(E) ? a.k : 1) * sizeof(uint2);
+  const size_t lds = E < 12 ? 0 : (size_t)waves * wave_pairs(E, R, a.k <= wave_filter_max_k(E, R, MODE) ? a.k : 1, MODE) * sizeof(uint2);
   return launch_kernel(rtopk_dense_kernel<G, NG, R, FULL, MODE>, dim3((unsigned)blocks), dim3(waves * kWave), lds,
                        a.stream, static_cast<const float*>(a.in), a.N, a.M, a.k, a.max_iter,
                        static_cast<float*>(a.out_vals));
@@ -1451,7 +1450,7 @@ hipError_t launch(const LaunchArgs& a) {
   using L = Layout<G, NG>;
   if (a.M < L::MIN_M || a.M > 64 * L::E) return hipErrorInvalidValue;
   // LDS per wavefront: at most 64 KiB per block
-  size_t per_wave = (size_t)wave_pairs(L::E, R, a.k) * sizeof(uint2);
+  size_t per_wave = (size_t)wave_pairs(L::E, R, a.k, MODE) * sizeof(uint2);
   // one wavefront per workgroup, except where a wavefront stages 8 KiB or more of pairs: there four
   // per workgroup measured 7 % faster (2^20 x 256, k = 128: 387 -> 360 us), while at 4 KiB and below
   // one per workgroup is the faster by 3-11 %
@@ -1468,6 +1467,15 @@ hipError_t launch(const LaunchArgs& a) {
 // Rows per wavefront for E = G*NG registers per row, from sweeps at 2^20 rows: 16 for M <= 128,
 // 8 for M = 256, 2 for M = 512..1024 (M = 512 runs 10 % slower with 4), 1 beyond.
 constexpr int rows_per_wave(int E) { return E <= 2 ? 16 : (E <= 4 ? 8 : (E <= 16 ? 2 : 1)); }
+// Rows of 16 values per lane take 1, and their lists (rtopk_filter.hpp), where the lists are short; with more of them the
+// LDS they take leaves fewer wavefronts in flight, and the kernel of two rows stays.  131072 x 1024, two rows without
+// lists -> one with: fp32 exact k = 16 98.6 -> 91.2 us, 64 109.8 -> 104.8, but 128 118 -> 125 (134217 x 1000, k = 100:
+// 117.7 -> 122.0); bfloat16, whose search is the larger part, 106 -> 81, 122 -> 97 and 133 -> 119, with early stopping
+// 91 -> 79, 96 -> 89 and 98 -> 103.  (Lists in the kernel of two rows: bfloat16 106 -> 68 and 121 -> 84, but 2 % slower
+// for every k without lists, fp32 early k = 64 by 5 %; fp32 rows of 12 values per lane lose with one row, 117 -> 121.)
+inline bool one_row_lists(int mode, bool half, const LaunchArgs& a) {
+  return a.k <= (half && mode == kExact ? wave_filter_max_k(16, 1, mode) : 64) && (mode != kEarly || a.max_iter >= 5);
+}
 // fp32 rows of 129..256 columns with int32 columns (and their dense form) take 4 instead: with
 // non-temporal output stores the smaller per-wavefront footprint streams better (2^20 x 256: k = 32
 // 221 -> 215 us, k = 64 254 -> 247 us, k = 128 356 -> 345 us, dense 346 -> 339 us; with no search steps at

@@ -49,13 +49,13 @@ def _same(got, want, tag):
 
 
 # widths of one wavefront per row (24, 32, 48, 64, 96 and 128 values per lane) and of one workgroup per row
-@pytest.mark.parametrize("M", [1025, 1536, 2048, 3071, 3072, 4096, 6141, 8192,
+@pytest.mark.parametrize("M", [769, 1000, 1023, 1024, 1025, 1536, 2048, 3071, 3072, 4096, 6141, 8192,
                                8193, 12288, 16384, 16385, 24576, 32768, 32771, 49152, 65536])
 def test_rows_the_lists_hold_and_rows_they_do_not(M):
     R = _gpu()
     x = _rows(M, 4000 + M)
     xd = torch.from_numpy(x).cuda()
-    for k in (1, 2, 33, 140, 141, 210, 211, 280, 281, 420, 421) if M <= 8192 else (1, 2, 33, 255, 256, 257, 511, 512, 513):
+    for k in (1, 2, 33, 64, 65, 140, 141, 210, 211, 280, 281, 420, 421) if M <= 8192 else (1, 2, 33, 255, 256, 257, 511, 512, 513):
         tag = f"M={M} k={k}"
         _same(R.rtopk_rowwise_exact(xd, k), oracle.topk_exact(x, k), tag + " exact")
         _same(R.rtopk_rowwise_exact_smallest(xd, k), oracle.topk_exact_smallest(x, k), tag + " smallest")
@@ -72,7 +72,7 @@ def test_rows_the_lists_hold_and_rows_they_do_not(M):
 
 
 @pytest.mark.parametrize("kind", ("f16", "bf16"))
-@pytest.mark.parametrize("M", [1030, 2047, 4096, 8192, 8200, 16384, 32768, 40003, 65536])
+@pytest.mark.parametrize("M", [513, 770, 1001, 1024, 1030, 2047, 4096, 8192, 8200, 16384, 32768, 40003, 65536])
 def test_16bit_rows_tie_across_the_kth_place(kind, M):
     R = _gpu()
     x = _rows(M, 4100 + M)
