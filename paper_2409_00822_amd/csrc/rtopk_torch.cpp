@@ -66,11 +66,14 @@ struct Output {
 
 void* stream_of(const Tensor& t) { return c10::hip::getCurrentHIPStream(t.device().index()).stream(); }
 
-// f() with C++ exceptions turned into Python's.
+// f() with C++ exceptions turned into Python's.  Without memory for an output the caller gets None, so that it makes the
+// allocation itself and the user sees torch's own exception.
 template <typename F>
 PyObject* guarded(F f) {
   try {
     return f();
+  } catch (const c10::OutOfMemoryError& e) {
+    Py_RETURN_NONE;
   } catch (const std::exception& e) {
     if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, e.what());
     return nullptr;
@@ -97,7 +100,8 @@ PyObject* pair(Output& a, Output& b) {
 }
 
 // Scratch memory for a shape that can use it (rtopk_workspace_bytes), from torch's allocator: stream-ordered, so it may
-// go back as soon as the call has enqueued its work on the current stream.
+// go back as soon as the call has enqueued its work on the current stream.  Where there is no memory for it the call does
+// without.
 struct Scratch {
   Tensor tensor;
   void* data = nullptr;
@@ -105,8 +109,12 @@ struct Scratch {
   Scratch(const Tensor& x, int32_t k, int32_t variant, int32_t max_iter) {
     bytes = rtopk_workspace_bytes(x.size(0), (int32_t)x.size(1), k, variant, max_iter);
     if (bytes > 0) {
-      tensor = at::empty({bytes}, at::TensorOptions().dtype(at::kByte).device(x.device()));
-      data = tensor.data_ptr();
+      try {
+        tensor = at::empty({bytes}, at::TensorOptions().dtype(at::kByte).device(x.device()));
+        data = tensor.data_ptr();
+      } catch (const c10::OutOfMemoryError&) {
+        bytes = 0;
+      }
     }
   }
 };

@@ -90,3 +90,22 @@ def test_threads_and_streams():
         ev, ei = oracle.topk_exact(xs[t], 20 + t)
         assert np.array_equal(got[t][1].cpu().numpy(), ei)
         assert np.array_equal(got[t][0].cpu().numpy().view(np.int32), ev.view(np.int32))
+
+
+def test_without_memory_for_scratch_the_call_does_without_and_for_outputs_it_raises():
+    R = _gpu()
+    x = torch.randn((512, 131072), device="cuda")
+    k = 400  # 25 MB of scratch: a segment of the allocator's own
+    vals, cols = R.rtopk_rowwise_exact(x, k)
+    v, i = torch.empty_like(vals), torch.empty_like(cols)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction(torch.cuda.memory_reserved() / total)
+    try:
+        R.rtopk_rowwise_exact(x, k, v, i)
+        with pytest.raises(torch.cuda.OutOfMemoryError):
+            R.rtopk_rowwise_exact(x, 20000)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(v, vals) and torch.equal(i, cols)
