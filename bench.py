@@ -408,10 +408,12 @@ def main():
 
     if backward:
         kernel = ("maxk_scatter_" if args.op == "backward" else "maxk_gather_") + ("rows_kernel" if M <= 2048 else "block_kernel")
+    elif M > 32768 and not dense and args.dtype == "f32" and k <= 512:
+        kernel = "rtopk_segment_kernel"  # and rtopk_merge_kernel
     elif M > 65536:
         kernel = "rtopk_stream_kernel"
     elif M > 8192:
-        kernel = "rtopk_block_kernel"
+        kernel = "rtopk_filter_kernel" if k <= (256 if M <= 16384 else 512) else "rtopk_block_kernel"
     else:
         kernel = "rtopk_dense_kernel" if dense else "rtopk_wave_kernel"
     prof = profile_name(kernel, args.workload, k, args.dtype, args.op)

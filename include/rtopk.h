@@ -11,8 +11,8 @@
  *    frees, copies to the host or synchronises.  Work is enqueued on `stream` (a hipStream_t passed
  *    as void*; NULL means the default stream) and the call returns at once.
  *  - `in`       : [N][M] fp32, dense, row-major, row stride M, read-only, 4-byte aligned.
- *                 Rows are processed fastest when `in` is 16-byte aligned and M is a multiple of 4;
- *                 other shapes take a scalar-load path with the same results.
+ *                 Any M and any such alignment take vector loads; the outputs leave in 128-bit stores where
+ *                 k is a multiple of 4, and for any k when they are 16-byte aligned.
  *  - `out_vals` : [N][k] fp32, row-major.  out_vals[r][j] is the bit pattern of in[r][out_idx[r][j]].
  *  - `out_idx`  : [N][k] column indices, 0-based, strictly ascending within a row
  *                 (int32_t, or uint8_t in the *_u8 variants, which require M <= 256: this is the
@@ -35,7 +35,7 @@
  *    when k is up to about a thousand and the winners are not crowded into one sixteenth of the row,
  *    otherwise once for the minimum and maximum, once per eight search steps and, for k in the
  *    thousands, once more to write the result; a launch of fewer such rows than twice the number of
- *    compute units leaves some of them idle.
+ *    compute units leaves some of them idle, unless rtopk_select_ws (below) spreads each over several.
  */
 #ifndef RTOPK_H_
 #define RTOPK_H_

@@ -15,6 +15,9 @@
 // cross-lane sums, the LDS round trip, the barrier) over more elements, and narrower workgroups leave
 // room for more rows per compute unit, whose load and search phases then overlap.
 //
+// That is rtopk_block_kernel, the full-width search.  rtopk_filter_kernel, which launch_block prefers for small k, searches a
+// list of candidates above a floor instead (rtopk_filter.hpp) and comes here only for rows whose list does not hold.
+//
 // Every wavefront evaluates the same thresholds on the same totals, so all of them take the same
 // branches and reach the same barriers; the trip count of the search is uniform over the workgroup.
 //

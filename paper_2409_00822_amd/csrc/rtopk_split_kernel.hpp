@@ -15,7 +15,9 @@
 //
 // What bounds it: the segments read the row once at the rate of the 32768-column rows (1.15 times the copy rate's time),
 // the lists add 8 bytes per candidate written and read, 1.2 to 1.4 k of them per segment, and the merge costs a launch
-// and about 14 steps of one barrier.  64 x 131072, k = 50: 39.7 us as 64 streamed rows, 14 us in 512 segments.
+// and about 14 steps of one barrier.  Kernel time, one workgroup per row -> split:
+// 64 x 131072, k = 50: 39.5 -> 19.4 us in 512 segments; 1 x 131072: 36.5 -> 12.2; 1024 x 131072, k = 64: 131 -> 95;
+// 2048 x 50000, k = 100, registers of one workgroup -> split: 135 -> 87; 512 x 262144, k = 512: 118 -> 116.
 #pragma once
 
 #include "rtopk_stream_kernel.hpp"
