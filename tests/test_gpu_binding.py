@@ -1,5 +1,6 @@
 """The Python entry points through the native module: the caller's outputs come back as they are, new ones are new, what
 was refused is refused by the Python code with the same exceptions, and calls follow the current stream and threads."""
+import gc
 import threading
 
 import numpy as np
@@ -60,7 +61,7 @@ def test_what_was_refused_is_refused():
         R.rtopk_rowwise(x, 3, -1)  # not exact mode
     with pytest.raises(R.RTopKError):
         R.rtopk_rowwise_eps(x, 3, -1.0)
-    with pytest.raises((TypeError, Exception)):
+    with pytest.raises(TypeError):
         R.rtopk_rowwise_exact(x, 3.0)
     with pytest.raises(ValueError):
         R.rtopk_maxk_backward(x, torch.zeros(50, 3, dtype=torch.int64, device="cuda"), 100)
@@ -94,18 +95,27 @@ def test_threads_and_streams():
 
 def test_without_memory_for_scratch_the_call_does_without_and_for_outputs_it_raises():
     R = _gpu()
+    gc.collect()
+    torch.cuda.empty_cache()
     x = torch.randn((512, 131072), device="cuda")
-    k = 400  # 25 MB of scratch: a segment of the allocator's own
+    k, scratch = 400, 24 << 20  # 2048 segments of 12 KiB and a head each
     vals, cols = R.rtopk_rowwise_exact(x, k)
     v, i = torch.empty_like(vals), torch.empty_like(cols)
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
     total = torch.cuda.get_device_properties(0).total_memory
     torch.cuda.set_per_process_memory_fraction(torch.cuda.memory_reserved() / total)
+    hog = []  # whatever is free inside the segments that tests before this one left behind
     try:
+        with pytest.raises(torch.cuda.OutOfMemoryError):
+            while True:
+                hog.append(torch.empty(2 << 20, dtype=torch.uint8, device="cuda"))
+        with pytest.raises(torch.cuda.OutOfMemoryError):
+            torch.empty(scratch, dtype=torch.uint8, device="cuda")
         R.rtopk_rowwise_exact(x, k, v, i)
         with pytest.raises(torch.cuda.OutOfMemoryError):
             R.rtopk_rowwise_exact(x, 20000)
     finally:
+        del hog
         torch.cuda.set_per_process_memory_fraction(1.0)
     assert torch.equal(v, vals) and torch.equal(i, cols)
