@@ -218,7 +218,14 @@ __device__ __forceinline__ void block_bounds(const float (&x)[E], float nm, int 
   probe = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(d)));
 }
 
-// One row, by the whole workgroup; true when it is done (always, but for kListsOnly).  Every wavefront leaves through the
+// What is known of a search before a row's full-width pass: where Algorithm 2, or Algorithm 1 with precision, has ended.
+struct KnownBounds {
+  int known;  // 0: nothing
+  float lo, hi;
+  int iterations;
+};
+
+// One row, by the whole workgroup; true when it is done (always, but for kListsOnly, which leaves in `bounds` what it knows).  Every wavefront leaves through the
 // same return statement.  A workgroup that walks several rows through the lists loads the whole next row as soon as the
 // list of quads stands, into the registers of this one (have_next: x holds the row on entry); with the full-width
 // search, as much of the next row as fits beside this one is loaded while this one is ranked (ahead).
@@ -227,7 +234,7 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
                                           float eps_rel, void* __restrict__ out_vals, int32_t* __restrict__ out_idx,
                                           int32_t* __restrict__ out_iters, int64_t r_next, bool& have_ahead,
                                           float (&ahead)[block_groups_ahead(W, G, PATH) * G + 1], bool& have_next,
-                                          float (&x)[G * NG]) {
+                                          float (&x)[G * NG], KnownBounds& bounds) {
   static_assert(!DENSE || DT == kF32, "the dense form is built for fp32 rows");
   constexpr int E = G * NG;
   constexpr bool FILTER = PATH != kFullWidth;
@@ -289,10 +296,9 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
       }
     }
   };
-  bool bound_known = false;
   if constexpr (FILTER) {
     float thi, tlo;
-    int split, iterations;
+    int split, iterations = 0;
     const float eps = MODE == kEps ? eps_rel * __builtin_fabsf(hi) : 0.0f;
     auto column = [&](int quad, int thread) -> int {
       const int g = quad / (G / 4);
@@ -337,8 +343,15 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
       }
       return true;
     }
+    bounds.known = MODE != kExact && done == kFilterBoundOnly ? 1 : 0;
+    bounds.lo = lo;
+    bounds.hi = hi;
+    bounds.iterations = iterations;
     if constexpr (PATH == kListsOnly) return false;
-    bound_known = MODE == kEarly && done == kFilterBoundOnly;  // lo is Algorithm 2's final minimum
+  }
+  if (MODE != kExact && bounds.known != 0) {
+    lo = bounds.lo;
+    hi = bounds.hi;
   }
 
   // cnt = #{row elements with key >= t}.  Every lane counts its keys below t, the wavefront sums them,
@@ -376,7 +389,7 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
     // there and wavefront 0 finishes the search alone, with no further barriers.
     bool hit = false, narrow = false;
     float thres = lo;
-    int steps = 0, cnt_lo = M, cnt_hi = 0;
+    int steps = MODE == kEps && bounds.known != 0 ? bounds.iterations - 1 : 0, cnt_lo = M, cnt_hi = 0;
     const float eps = MODE == kEps ? eps_rel * __builtin_fabsf(hi) : 0.0f;
     // (Narrowing as soon as the band fits stays the fastest: never narrowing costs 3 % on Laplace rows --
     // 12.3 full-width steps on average at 32768 columns -- and starting only after 8 to 14 steps 7-12 %.
@@ -430,7 +443,7 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
         }
       }
     } else {
-      while (hi - lo > eps) {
+      while (bounds.known == 0 && hi - lo > eps) {
         const float mid = (lo + hi) * 0.5f;
         if (!(mid > lo && mid < hi)) break;
         thres = mid;
@@ -502,7 +515,7 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
     // three counts per element -- gives the same bounds but measured slower, 250 -> 276 us at eight steps on
     // 8192 x 32768: a step is bound by its counting work, not by the barrier.)
 #pragma nounroll
-    for (int it = 0; !bound_known && it < max_iter; ++it) {
+    for (int it = 0; bounds.known == 0 && it < max_iter; ++it) {
       const float thres = (lo + hi) * 0.5f;
       const int cnt = count(thres);
       move_bound(lo, hi, thres, cnt, k);
@@ -684,10 +697,12 @@ __device__ __forceinline__ void block_rows(const void* __restrict__ in, int64_t 
                                            float eps_rel, void* __restrict__ out_vals, int32_t* __restrict__ out_idx,
                                            int32_t* __restrict__ out_iters) {
   bool have_ahead = false, have_next = false;
+  KnownBounds bounds{};
   if constexpr (block_persistent(W) && FILTER) {
+    __shared__ KnownBounds s_known[64];
     float x[G * NG];
     for (int64_t r0 = blockIdx.x; r0 < N; r0 += 64 * (int64_t)gridDim.x) {
-      uint64_t left = 0;  // uniform: rows for the full-width search
+      uint64_t left = 0;  // uniform: rows for the full-width pass
       have_next = false;
       for (int j = 0; j < 64; ++j) {
         const int64_t r = r0 + j * (int64_t)gridDim.x;
@@ -695,8 +710,14 @@ __device__ __forceinline__ void block_rows(const void* __restrict__ in, int64_t 
         float none[1];
         const bool done = block_row<G, NG, W, MODE, NEG, DT, DENSE, kListsOnly>(
             r, in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, j + 1 < 64 ? r + gridDim.x : N, have_ahead, none,
-            have_next, x);
+            have_next, x, bounds);
         left |= done ? 0ull : 1ull << j;
+        if (!done && threadIdx.x == 0) {
+          s_known[j].known = bounds.known;
+          s_known[j].lo = bounds.lo;
+          s_known[j].hi = bounds.hi;
+          s_known[j].iterations = bounds.iterations;
+        }
         __syncthreads();  // the next row reuses the shared tables
       }
       while (left != 0) {
@@ -704,8 +725,13 @@ __device__ __forceinline__ void block_rows(const void* __restrict__ in, int64_t 
         left &= left - 1;
         float ahead[block_groups_ahead(W, G, kFullWidth) * G + 1];
         have_ahead = false;
+        bounds.known = __builtin_amdgcn_readfirstlane(s_known[j].known);
+        bounds.lo = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_known[j].lo)));
+        bounds.hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_known[j].hi)));
+        bounds.iterations = __builtin_amdgcn_readfirstlane(s_known[j].iterations);
         block_row<G, NG, W, MODE, NEG, DT, DENSE, kFullWidth>(r0 + j * (int64_t)gridDim.x, in, N, M, k, max_iter, eps_rel,
-                                                              out_vals, out_idx, out_iters, N, have_ahead, ahead, have_next, x);
+                                                              out_vals, out_idx, out_iters, N, have_ahead, ahead, have_next, x,
+                                                              bounds);
         __syncthreads();
       }
     }
@@ -713,7 +739,7 @@ __device__ __forceinline__ void block_rows(const void* __restrict__ in, int64_t 
     float ahead[block_groups_ahead(W, G, kFullWidth) * G + 1], x[G * NG];
     for (int64_t r = blockIdx.x; r < N; r += gridDim.x) {
       block_row<G, NG, W, MODE, NEG, DT, DENSE, kFullWidth>(r, in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters,
-                                                            r + gridDim.x, have_ahead, ahead, have_next, x);
+                                                            r + gridDim.x, have_ahead, ahead, have_next, x, bounds);
       __syncthreads();  // the next row reuses the shared tables
     }
   } else {
@@ -721,7 +747,7 @@ __device__ __forceinline__ void block_rows(const void* __restrict__ in, int64_t 
     const int64_t r = blockIdx.x;  // launched with one workgroup per row
     if (r < N)
       block_row<G, NG, W, MODE, NEG, DT, DENSE, FILTER ? kListsFirst : kFullWidth>(
-          r, in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, N, have_ahead, none, have_next, x);
+          r, in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, N, have_ahead, none, have_next, x, bounds);
   }
 }
 

@@ -71,9 +71,13 @@ __device__ __forceinline__ void lane_group_maxima(const float (&x)[E], float (&g
 // other values would (12 to 16 steps in all; 27 at most in 60 rows each of eleven kinds).  Exact mode with one entry of -1e9 a row,
 // twelve halvings -> this: 8192 x 4096, k = 64, 74 -> 28 us; 1048 x 32000 102 -> 31; 671 x 50000, k = 100, 398 -> 40.
 // With NaN or infinite keys any value may come out.
+// halvings: 7, or, where low and high are Algorithm 2's own first bounds, its number of steps if that is at least 7 and
+// small: if they all move `low` they are that search, which ends there, below any better floor.
 template <int J>
-__device__ __forceinline__ float floor_of_maxima(const float (&gm)[J], int need, float low, float high, float& above) {
+__device__ __forceinline__ float floor_of_maxima(const float (&gm)[J], int need, float low, float high, float& above,
+                                                 int halvings = 7) {
   const int enough = need + (need >> 3) + 1;
+  const float largest = high;
   bool found = false;
   auto try_bound = [&](float t) {
     int cnt = 0;
@@ -86,7 +90,8 @@ __device__ __forceinline__ float floor_of_maxima(const float (&gm)[J], int need,
       high = t;
     }
   };
-  for (int step = 0; step < 7 && !found; ++step) try_bound((low + high) * 0.5f);
+  for (int step = 0; step < halvings && !found; ++step) try_bound((low + high) * 0.5f);
+  if (halvings != 7) found = found || high == largest;
   for (int step = 0; step < 24 && !found; ++step) {
     // a lane's largest below `high`, or (every other step) its smallest above `low`
     const float inf = __builtin_inff();
@@ -111,6 +116,22 @@ __device__ __forceinline__ float floor_of_maxima(const float (&gm)[J], int need,
   }
   above = high;
   return low;
+}
+
+// The steps of Algorithm 2, or of Algorithm 1 with precision eps, whose thresholds lie at or below the floor T0: each
+// of them counts more than k keys and moves lo up.  Returns whether the search ends among them; then lo is final and hi
+// still the largest key.
+template <int MODE>
+__device__ __forceinline__ bool walk_to_floor(float T0, int max_iter, float eps, float& lo, float hi, int& steps) {
+  steps = 0;
+  for (;;) {
+    if (MODE == kEarly ? steps >= max_iter : !(hi - lo > eps)) return true;
+    const float mid = (lo + hi) * 0.5f;
+    if (MODE == kEps && !(mid > lo && mid < hi)) return true;
+    if (!(mid <= T0)) return false;
+    lo = mid;
+    ++steps;
+  }
 }
 
 // The largest value on the row type's grid (see midpoint_exact) that is not above t.
@@ -154,7 +175,8 @@ struct FilterLds {
 enum FilterResult : int {
   kFilterDone = 0,      // the pairs are written (or, in the dense form, the thresholds and the split are set)
   kFilterNoList = 1,    // the lists do not hold the row: the whole search is the caller's
-  kFilterBoundOnly = 2  // the search has run, but its last threshold lies below the floor: the selection is the caller's
+  kFilterBoundOnly = 2  // the search is over without a count of k, but its last minimum lies below the floor: the selection is
+                        // the caller's, from lo and hi (Algorithm 2: from lo)
 };
 
 // Whether k is small enough for the lists; host and device agree through this rule alone.  The floor has 1.4 to 1.6 k
@@ -191,7 +213,7 @@ __device__ __forceinline__ uint32_t filter_rank(const FilterLds<W, ROOM>& s, con
   return r;
 }
 
-// Step 4, by one wavefront: the search on the singles.  SR registers per lane hold them.
+// Step 4, by one wavefront: the search on the singles.  SR registers per lane hold them; `steps` steps are done already.
 template <int SR, int MODE, bool NEG, int DT>
 __device__ __forceinline__ void filter_search(const uint2* single, int n, int lane, int k, int max_iter, float eps,
                                               float T0, float probe, float& lo, float& hi, float& thres, bool& hit,
@@ -210,10 +232,9 @@ __device__ __forceinline__ void filter_search(const uint2* single, int n, int la
     return c;
   };
   hit = false;
-  steps = 0;
   last_cnt = -1;
   if constexpr (MODE == kEarly) {
-    for (int it = 0; it < max_iter; ++it) {
+    for (int it = steps; it < max_iter; ++it) {
       const float mid = (lo + hi) * 0.5f;
       const int cnt = mid > T0 ? count(mid) : k + 1;  // more than k keys are at or above the floor
       last_cnt = cnt;
@@ -252,10 +273,11 @@ __device__ __forceinline__ void filter_search(const uint2* single, int n, int la
 // Steps 2 and 3 for one row, by the whole workgroup (W wavefronts): returns how many singles there are, -1 where a
 // list does not hold them.  x: the row's elements, masked (a key of -inf past the row's end).  Before the call n_quads
 // and n_singles are zero and a barrier has passed; the lists are complete for every wavefront on return.
-// column(quad of the lane, thread): the quad's first column.  listed(): called once x is no longer needed here.
+// column(quad of the lane, thread): the quad's first column.  listed(): called once x is no longer needed here.  store =
+// false: listed() is called, the lists are not built (-1).
 template <int E, int W, bool NEG, int ROOM, typename Column, typename Listed>
 __device__ __forceinline__ int filter_lists(FilterLds<W, ROOM>& s, const float (&x)[E], int lane, int wave, float T0,
-                                            Column column, Listed listed) {
+                                            Column column, Listed listed, bool store = true) {
   constexpr int CAP = ROOM, Q = E / 4;
   static_assert(Q <= 32, "a lane's quads are the bits of one word");
   const int tid = wave * kWave + lane;
@@ -279,19 +301,21 @@ __device__ __forceinline__ int filter_lists(FilterLds<W, ROOM>& s, const float (
     if (base + n_wave > CAP) member = 0;  // uniform: n_quads says that the list is not whole
     int slot = base + (int)incl - 1;  // the lane's slots are filled from its last one downwards
     const int dummy = CAP + lane;
+    if (store) {  // uniform
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe(member, (uint32_t)(Q - 1 - q), 1u);  // all ones for a member
-      const int to = (int)select_bits(m, (uint32_t)slot, (uint32_t)dummy);
-      s.lists.quad[to] = make_float4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]);
-      s.lists.id[to] = (uint32_t)(q << 16) | (uint32_t)tid;
-      slot += (int)m;
+      for (int q = 0; q < Q; ++q) {
+        const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe(member, (uint32_t)(Q - 1 - q), 1u);  // all ones for a member
+        const int to = (int)select_bits(m, (uint32_t)slot, (uint32_t)dummy);
+        s.lists.quad[to] = make_float4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]);
+        s.lists.id[to] = (uint32_t)(q << 16) | (uint32_t)tid;
+        slot += (int)m;
+      }
     }
   }
   listed();
   __syncthreads();
   const int n_quads = __builtin_amdgcn_readfirstlane(s.n_quads);
-  if (n_quads > CAP) return -1;
+  if (n_quads > CAP || !store) return -1;
 
   // Step 3.
   for (int j0 = 0; j0 < n_quads; j0 += W * kWave) {
@@ -331,20 +355,31 @@ __device__ __forceinline__ int filter_lists(FilterLds<W, ROOM>& s, const float (
 // elements stay: key >= (column <= split ? tlo : thi).  Every wavefront takes the same branches.
 template <int E, int W, int MODE, bool NEG, int DT, bool DENSE, typename Column, typename Listed, typename Emit>
 __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], int lane, int wave, int k, int max_iter,
-                                          float eps, float T0, float probe, float& lo, float hi, float& thi, float& tlo,
+                                          float eps, float T0, float probe, float& lo, float& hi, float& thi, float& tlo,
                                           int& split, int& iterations, Column column, Listed listed, Emit emit) {
   constexpr int CAP = FilterLds<W>::CAP;
   const int tid = wave * kWave + lane;
-  const int n = filter_lists<E, W, NEG>(s, x, lane, wave, T0, column, listed);
+  float low = lo;  // (lo itself stays for the caller's search of a row that the lists do not hold)
+  int walked = 0;
+  bool over = false;
+  if constexpr (MODE != kExact) over = walk_to_floor<MODE>(T0, max_iter, eps, low, hi, walked);
+  // (leaving before the lists are built costs the shape of 16 wavefronts about 90 spilled registers)
+  int n = 0;
+  if (W == 16 || !over) n = filter_lists<E, W, NEG>(s, x, lane, wave, T0, column, listed, !over);
+  if (over) {
+    lo = low;
+    iterations = walked + 1;
+    return kFilterBoundOnly;
+  }
   if (n <= k) return kFilterNoList;  // (0 <= n <= k only with NaN or infinite keys)
 
   // Step 4 by wavefront 0, while every thread clears its words of the bitmaps.
   s.maps.cut[tid] = make_uint2(0u, 0u);
   s.maps.chosen[tid] = make_uint2(0u, 0u);
   if (wave == 0) {
-    float l = lo, h = hi, thres = lo;
+    float l = low, h = hi, thres = low;
     bool hit = false;
-    int steps = 0, cnt = -1, na = 0;
+    int steps = walked, cnt = -1, na = 0;
     if (n <= 4 * kWave) {
       filter_search<4, MODE, NEG, DT>(s.single, n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
     } else if (n <= 8 * kWave || CAP <= 8 * kWave) {
@@ -396,7 +431,8 @@ __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], 
   iterations = __builtin_amdgcn_readfirstlane(s.info[1]);
   split = 0x7fffffff;
   if ((state & 1) != 0) {
-    if (MODE == kEarly) lo = tlo;
+    lo = tlo;
+    if (MODE == kEps) hi = thi;
     return kFilterBoundOnly;
   }
 
@@ -463,10 +499,10 @@ __host__ __device__ constexpr int wave_filter_pairs(int k) { return wave_filter_
 
 // One row.  x: masked elements; lo, hi: the keys' minimum and maximum; lists: wave_filter_pairs(k) pairs of LDS, 16-byte
 // aligned; stage: where the pairs go (it may be the same memory).  In the dense form thi, tlo, split say which elements
-// stay.  Returns kFilterDone, kFilterNoList, or (Algorithm 2, lo then its last minimum) kFilterBoundOnly.
+// stay.  Returns a FilterResult.
 template <int G, int NG, bool FULL, int MODE, bool NEG, int DT, bool DENSE>
 __device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E], int lane, int M, int k, int max_iter,
-                                               float eps, float& lo, float hi, uint2* lists, uint2* stage, float& thi,
+                                               float eps, float& lo, float& hi, uint2* lists, uint2* stage, float& thi,
                                                float& tlo, int& split, int& iterations) {
   using L = Layout<G, NG>;
   constexpr int E = L::E;
@@ -475,14 +511,24 @@ __device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E
   uint32_t* id = reinterpret_cast<uint32_t*>(quad + room);  // first column of a quad
 
   float T0, probe;
+  const int halvings = MODE == kEarly && max_iter >= 7 && max_iter <= 16 ? max_iter : 7;
   if (k <= wave_filter_small_k(E)) {  // uniform over the launch
     float gm[wave_groups(E, false)];
     lane_group_maxima<E, NEG>(x, gm);
-    T0 = floor_of_maxima(gm, k + 1, lo, hi, probe);
+    T0 = floor_of_maxima(gm, k + 1, lo, hi, probe, halvings);
   } else {
     float gm[wave_groups(E, true)];
     lane_group_maxima<E, NEG>(x, gm);
-    T0 = floor_of_maxima(gm, k + 1, lo, hi, probe);
+    T0 = floor_of_maxima(gm, k + 1, lo, hi, probe, halvings);
+  }
+  float low = lo;  // (lo itself stays for the caller's search of a row that the lists do not hold)
+  int walked = 0;
+  if constexpr (MODE != kExact) {
+    if (walk_to_floor<MODE>(T0, max_iter, eps, low, hi, walked)) {
+      lo = low;
+      iterations = walked + 1;
+      return kFilterBoundOnly;
+    }
   }
 
   // quads with a key at or above the floor, in column order
@@ -543,9 +589,9 @@ __device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E
   constexpr int kMost = E <= 16 ? 4 : 8;  // registers of singles
   if (n <= (uint32_t)k || n > (uint32_t)(kMost * kWave)) return kFilterNoList;  // (n <= k only with NaN or infinite keys)
 
-  float thres = lo, l = lo, h = hi;
+  float thres = low, l = low, h = hi;
   bool hit = false;
-  int steps = 0, cnt = -1, na = 0;
+  int steps = walked, cnt = -1, na = 0;
   if (n <= 2 * kWave) {
     filter_search<2, MODE, NEG, DT>(lists, (int)n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
   } else if (n <= 4 * kWave) {
@@ -572,7 +618,11 @@ __device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E
     thi = h;
     tlo = l;
     limit = k - na;
-    if (MODE == kEps && !(l >= T0)) return kFilterNoList;
+    if (MODE == kEps && !(l >= T0)) {
+      lo = l;
+      hi = h;
+      return kFilterBoundOnly;
+    }
   }
   split = 0x7fffffff;
   if (DENSE && limit == 0) return kFilterDone;

@@ -915,6 +915,8 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
     }
   };
   // Rows of 16 or more values per lane: the lists first.  Algorithm 2 with few steps: see launch_block.
+  bool bounds_known = false;  // Algorithm 1 with precision: lo, hi and the iteration count are those of its end
+  int known_iterations = 0;
   if constexpr (wave_filter_max_k(E, R, MODE) > 0) {
     if (k <= wave_filter_max_k(E, R, MODE) && (MODE != kEarly || max_iter >= 5)) {  // uniform over the launch
       float thi, tlo;
@@ -930,6 +932,8 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
         emit_selection<G, NG, FULL, true, true, NEG, DENSE>(x, nullptr, lo, lo, -1, lane, M, k, stage_addr, y);
         return 0;
       }
+      bounds_known = MODE == kEps && done == kFilterBoundOnly;
+      known_iterations = iterations;
     }
   }
   // A search that ended without a count of k: everything >= hi (cut at k by column when hi is still the row maximum and
@@ -1040,13 +1044,13 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
     const float eps = eps_rel * __builtin_fabsf(hi);
     bool hit = false;
     float thres = lo;
-    int steps = 0;
+    int steps = bounds_known ? known_iterations - 1 : 0;
     // narrowing as in the exact mode: same thresholds and counts, hence the same exit iteration
     constexpr bool NARROW = narrows(E, MODE);
     int cnt_lo = M, cnt_hi = 0, above = 0;
     bool narrow = false;
     float band[BR];
-    while (hi - lo > eps) {
+    while (!bounds_known && hi - lo > eps) {
       const float mid = (lo + hi) * 0.5f;
       if (!(mid > lo && mid < hi)) break;
       thres = mid;

@@ -9,9 +9,9 @@
 //   rtopk_merge_kernel: one workgroup per row.  The largest of the segments' floors has more than k keys of the row at or
 //     above it, and the lists hold all of those, so Algorithms 1 and 2 run on the lists with exact branch decisions (see
 //     rtopk_filter.hpp); the lists follow each other in column order, so places are prefix counts.
-// A row with a segment whose list is not whole (values that crowd), with more candidates than the merging workgroup's
-// registers hold, or whose last threshold lies below the floor is done by that workgroup as a streamed row
-// (rtopk_stream_kernel.hpp).  Results are those of the other kernels.
+// A row whose last threshold lies below the floor is written from the row itself.  A row with a segment whose list is not
+// whole (values that crowd), or with more candidates than the merging workgroup's registers hold, is done by that workgroup
+// as a streamed row (rtopk_stream_kernel.hpp).  Results are those of the other kernels.
 //
 // What bounds it: the segments read the row once at the rate of the 32768-column rows (1.15 times the copy rate's time),
 // the lists add 8 bytes per candidate written and read, 1.2 to 1.4 k of them per segment, and the merge costs a launch
@@ -116,10 +116,11 @@ __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(
   }
 }
 
-// One row: its search and selection on the segments' lists.  Returns false, with nothing written, where they do not
-// hold the selection.  Called by the whole workgroup; uniform.
+// One row: its search on the segments' lists, and its selection from them, or, where the search ends on a minimum below
+// the floor, from the row.  Returns false, with nothing written, where the lists do not hold the search.  Called by the
+// whole workgroup; uniform.
 template <int NW, int MODE, bool NEG>
-__device__ __forceinline__ bool merge_row(int64_t r, int k, int max_iter, float eps_rel, float* __restrict__ out_vals,
+__device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ in, int M, int k, int max_iter, float eps_rel, float* __restrict__ out_vals,
                                           int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters,
                                           const SegmentHead* __restrict__ heads, const uint2* __restrict__ lists,
                                           int segments, int stride) {
@@ -231,7 +232,6 @@ __device__ __forceinline__ bool merge_row(int64_t r, int k, int max_iter, float 
   int limA = k, limB = 0;
   if (MODE == kEarly) {
     tA = lo;
-    if (!(tA >= T0)) return false;
   } else if (hit) {
     tA = thres;
   } else {
@@ -240,10 +240,15 @@ __device__ __forceinline__ bool merge_row(int64_t r, int k, int max_iter, float 
     tB = lo;
     limA = na < k ? na : k;
     limB = k - limA;
-    if (MODE == kEps && limB > 0 && !(tB >= T0)) return false;
   }
   if constexpr (MODE == kEps) {
     if (out_iters != nullptr && tid == 0) out_iters[r] = hit ? steps : steps + 1;
+  }
+  float* ov = out_vals + r * (int64_t)k;
+  int32_t* oi = out_idx + r * (int64_t)k;
+  if (MODE != kExact && !((limB > 0 ? tB : tA) >= T0)) {
+    write_by_chunks<NW, 4, NEG, 4>(in + r * (int64_t)M, M, k, tA, tB, limA, limB, ov, oi);
+    return true;
   }
 
   uint32_t nA = 0, nB = 0;
@@ -265,8 +270,6 @@ __device__ __forceinline__ bool merge_row(int64_t r, int k, int max_iter, float 
     posA0 += w < wave ? (uint32_t)s_cls[0][w] : 0u;
     posB0 += w < wave ? (uint32_t)s_cls[1][w] : 0u;
   }
-  float* ov = out_vals + r * (int64_t)k;
-  int32_t* oi = out_idx + r * (int64_t)k;
 #pragma unroll
   for (int i = 0; i < kMergeRegs; ++i) {
     if (i < per) {
@@ -291,7 +294,7 @@ __global__ void __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu
                        float* __restrict__ out_vals, int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters,
                        const SegmentHead* __restrict__ heads, const uint2* __restrict__ lists, int segments, int stride) {
   const int64_t r = blockIdx.x;
-  if (merge_row<NW, MODE, NEG>(r, k, max_iter, eps_rel, out_vals, out_idx, out_iters, heads, lists, segments, stride)) return;
+  if (merge_row<NW, MODE, NEG>(r, in, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, heads, lists, segments, stride)) return;
   __syncthreads();
   stream_row<NW, 4, MODE, NEG>(r, in, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters);
 }

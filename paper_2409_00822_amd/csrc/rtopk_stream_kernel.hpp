@@ -57,6 +57,81 @@ __device__ __forceinline__ void stream_load(const float* p, float (&v)[G]) {
   for (int c = 0; c < G; ++c) v[c] = q[c];
 }
 
+// Writes a selection by reading the row in column order, a chunk of the whole workgroup at a time, until k pairs are
+// written: the first limA elements with a key at or above tA and (limB > 0) the first limB of [tB, tA), limA + limB = k.
+// A chunk is kUnits loads of G columns per thread, in the order (load, wavefront, lane, column); the candidates' ranks pass
+// through one barrier per chunk, so few wavefronts want several loads in flight behind each.  (The streamed kernel, at 64
+// registers, spills 20 more with four.)
+template <int NW, int G, bool NEG, int kUnits>
+__device__ __forceinline__ void write_by_chunks(const float* __restrict__ row, int M, int k, float tA, float tB, int limA,
+                                                int limB, float* __restrict__ ov, int32_t* __restrict__ oi) {
+  constexpr int kSpan = NW * kWave * G, kChunk = kUnits * kSpan;
+  static_assert(kSpan < 0x8000, "a load's candidates are counted in half a word");
+  // per load and wavefront: candidates (A in the low half, B in the high), double buffered
+  __shared__ uint32_t s_chunk[2][kUnits][NW];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int Mv = M - M % G;
+  uint32_t baseA = 0, baseB = 0;  // candidates of either class in earlier chunks (uniform)
+  int parity = 0;
+  for (int cb = 0; cb < M; cb += kChunk) {
+    const uint32_t selA0 = baseA < (uint32_t)limA ? baseA : (uint32_t)limA;
+    const uint32_t selB0 = baseB < (uint32_t)limB ? baseB : (uint32_t)limB;
+    if (selA0 + selB0 >= (uint32_t)k) break;  // all k pairs are written
+    float v[kUnits][G];
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u) {
+      const int c0 = cb + u * kSpan + tid * G;
+      if (c0 < Mv) {
+        stream_load<G>(row + c0, v[u]);
+      } else {
+#pragma unroll
+        for (int c = 0; c < G; ++c) v[u][c] = row[c0 + c < M ? c0 + c : 0];
+      }
+    }
+    auto is_a = [&](int u, int c) { return cb + u * kSpan + tid * G + c < M && keyof<NEG>(v[u][c]) >= tA; };
+    auto is_b = [&](int u, int c) {
+      return limB > 0 && cb + u * kSpan + tid * G + c < M && keyof<NEG>(v[u][c]) >= tB && !(keyof<NEG>(v[u][c]) >= tA);
+    };
+    uint32_t lower[kUnits];  // candidates of the load in lower lanes of this wavefront
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u) {
+      uint32_t mine = 0;
+#pragma unroll
+      for (int c = 0; c < G; ++c) mine += (is_a(u, c) ? 1u : 0u) + (is_b(u, c) ? 0x10000u : 0u);
+      const uint32_t incl = wave_inclusive_scan_dpp(mine);
+      if (lane == kWave - 1) s_chunk[parity][u][wave] = incl;
+      lower[u] = incl - mine;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u) {
+      uint32_t before = lower[u], total = 0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const uint32_t wt = s_chunk[parity][u][w];
+        before += w < wave ? wt : 0u;
+        total += wt;
+      }
+      uint32_t posA = baseA + (before & 0xffffu), posB = baseB + (before >> 16);
+#pragma unroll
+      for (int c = 0; c < G; ++c) {
+        const bool a = is_a(u, c), b = is_b(u, c);
+        if ((a && posA < (uint32_t)limA) || (b && posB < (uint32_t)limB)) {
+          const uint32_t pos = (posA < (uint32_t)limA ? posA : (uint32_t)limA) + (posB < (uint32_t)limB ? posB : (uint32_t)limB);
+          ov[pos] = v[u][c];
+          oi[pos] = cb + u * kSpan + tid * G + c;
+        }
+        posA += a ? 1u : 0u;
+        posB += b ? 1u : 0u;
+      }
+      baseA += total & 0xffffu;
+      baseB += total >> 16;
+    }
+    parity ^= 1;
+  }
+}
+
 // One row, by the whole workgroup of NW wavefronts (at least four: the 256 leaves have a thread each).
 template <int NW, int G, int MODE, bool NEG>
 __device__ __forceinline__ void stream_row(const int64_t r, const float* __restrict__ in, int M, int k, int max_iter,
@@ -801,57 +876,7 @@ __device__ __forceinline__ void stream_row(const int64_t r, const float* __restr
     if (write_from_lists(list, wn, (uint32_t)kListPerWave, true)) return;
   }
 
-  // General form: chunk by chunk, the candidates' ranks through one barrier per chunk.
-  uint32_t baseA = 0, baseB = 0;  // candidates of either class in earlier chunks (uniform)
-  int parity = 0;
-  for (int cb = 0; cb < M; cb += kChunk) {
-    const uint32_t selA0 = baseA < (uint32_t)limA ? baseA : (uint32_t)limA;
-    const uint32_t selB0 = baseB < (uint32_t)limB ? baseB : (uint32_t)limB;
-    if (selA0 + selB0 >= (uint32_t)k) break;  // all k pairs are written
-    const int c0 = cb + tid * G;
-    float v[G];
-    bool a[G], b[G];
-    uint32_t mine = 0;  // own candidates: A in the low half, B in the high half
-    if (c0 < Mv) {
-      stream_load<G>(row + c0, v);
-    } else {
-#pragma unroll
-      for (int c = 0; c < G; ++c) v[c] = row[c0 + c < M ? c0 + c : 0];
-    }
-#pragma unroll
-    for (int c = 0; c < G; ++c) {
-      const float key = keyof<NEG>(v[c]);
-      a[c] = c0 + c < M && key >= tA;
-      b[c] = c0 + c < M && limB > 0 && key >= tB && !a[c];
-      mine += (a[c] ? 1u : 0u) + (b[c] ? 0x10000u : 0u);
-    }
-    const uint32_t incl = wave_inclusive_scan_dpp(mine);
-    if (lane == kWave - 1) s_pre[parity][wave] = (int)incl;
-    __syncthreads();
-    uint32_t before = incl - mine;  // candidates in lower lanes of this wavefront
-    uint32_t chunk_total = 0;
-#pragma unroll
-    for (int w = 0; w < kStreamWaves; ++w) {
-      const uint32_t wt = (uint32_t)s_pre[parity][w];
-      before += w < wave ? wt : 0u;
-      chunk_total += wt;
-    }
-    parity ^= 1;
-    uint32_t posA = baseA + (before & 0xffffu), posB = baseB + (before >> 16);
-#pragma unroll
-    for (int c = 0; c < G; ++c) {
-      const bool chosen = (a[c] && posA < (uint32_t)limA) || (b[c] && posB < (uint32_t)limB);
-      if (chosen) {
-        const uint32_t pos = (posA < (uint32_t)limA ? posA : (uint32_t)limA) + (posB < (uint32_t)limB ? posB : (uint32_t)limB);
-        ov[pos] = v[c];
-        oi[pos] = c0 + c;
-      }
-      posA += a[c] ? 1u : 0u;
-      posB += b[c] ? 1u : 0u;
-    }
-    baseA += chunk_total & 0xffffu;
-    baseB += chunk_total >> 16;
-  }
+  write_by_chunks<NW, G, NEG, 1>(row, M, k, tA, tB, limA, limB, ov, oi);
 }
 
 template <int G, int MODE, bool NEG>
