@@ -225,7 +225,8 @@ struct KnownBounds {
   int iterations;
 };
 
-// One row, by the whole workgroup; true when it is done (always, but for kListsOnly, which leaves in `bounds` what it knows).  Every wavefront leaves through the
+// One row, by the whole workgroup; true when it is done (always, but for kListsOnly, which leaves in `bounds` what it knows; the
+// full-width search leaves the selection's lowest threshold in bounds.lo).  Every wavefront leaves through the
 // same return statement.  A workgroup that walks several rows through the lists loads the whole next row as soon as the
 // list of quads stands, into the registers of this one (have_next: x holds the row on entry); with the full-width
 // search, as much of the next row as fits beside this one is loaded while this one is ranked (ahead).
@@ -523,6 +524,7 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
     }
     tA = lo;
   }
+  if (PATH == kFullWidth) bounds.lo = limB > 0 ? tB : tA;
   // The search is over; what follows needs few registers besides the row.  A workgroup that has another
   // row to do starts that row's first loads now, so that they fly while this row is ranked and stored.
   next_ahead();

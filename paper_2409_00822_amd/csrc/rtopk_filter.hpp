@@ -92,7 +92,7 @@ __device__ __forceinline__ float floor_of_maxima(const float (&gm)[J], int need,
   };
   for (int step = 0; step < halvings && !found; ++step) try_bound((low + high) * 0.5f);
   if (halvings != 7) found = found || high == largest;
-  for (int step = 0; step < 24 && !found; ++step) {
+  for (int step = 0; step < 24 && __builtin_expect(!found, 0); ++step) {
     // a lane's largest below `high`, or (every other step) its smallest above `low`
     const float inf = __builtin_inff();
     uint64_t lanes;

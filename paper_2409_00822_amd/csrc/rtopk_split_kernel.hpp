@@ -5,13 +5,15 @@
 // at most 32768 (or 16384) columns, a workgroup each, in two launches:
 //   rtopk_segment_kernel: every segment's candidates -- the keys at or above a floor with more than k keys of the segment
 //     at or above it (steps 1 to 3 of rtopk_filter.hpp) -- go to the scratch memory in column order, with the floor and the
-//     segment's minimum and maximum;
+//     segment's minimum and maximum.  Where values crowd too much for the list (ties, sorted rows), the full-width search of
+//     rtopk_block_kernel.hpp finds the segment's k + 1 largest keys instead, whose last is the floor: of the keys equal to it
+//     the first in column order are listed, more than the row's selection can take from this segment;
 //   rtopk_merge_kernel: one workgroup per row.  The largest of the segments' floors has more than k keys of the row at or
 //     above it, and the lists hold all of those, so Algorithms 1 and 2 run on the lists with exact branch decisions (see
 //     rtopk_filter.hpp); the lists follow each other in column order, so places are prefix counts.
-// A row whose last threshold lies below the floor is written from the row itself.  A row with a segment whose list is not
-// whole (values that crowd), or with more candidates than the merging workgroup's registers hold, is done by that workgroup
-// as a streamed row (rtopk_stream_kernel.hpp).  Results are those of the other kernels.
+// A row whose last threshold is not above the floor is written from the row itself.  A row with more candidates than the
+// merging workgroup's registers hold (only where `cap` of split_of says that they may) is done by that workgroup as a
+// streamed row (rtopk_stream_kernel.hpp).  Results are those of the other kernels.
 //
 // What bounds it: the segments read the row once at the rate of the 32768-column rows (1.15 times the copy rate's time),
 // the lists add 8 bytes per candidate written and read, 1.2 to 1.4 k of them per segment, and the merge costs a launch
@@ -20,24 +22,25 @@
 // 2048 x 50000, k = 100, registers of one workgroup -> split: 135 -> 87; 512 x 262144, k = 512: 118 -> 116.
 #pragma once
 
+#include "rtopk_block_kernel.hpp"
 #include "rtopk_stream_kernel.hpp"
 
 namespace rtopk {
 
 struct SegmentHead {
-  int n;            // candidates; -1: the list is not whole
+  int n;            // candidates
   float floor;      // every key of the segment at or above it is listed
   float nlo, hi;    // negated minimum, and maximum, of the segment's keys
 };
 constexpr int kMergeRegs = 16;       // candidates per lane of a merging wavefront
 constexpr int kMaxSegments = 1024;   // 2^24 columns in segments of 16384
 
-// How a call is split: `segments` per row of `length` columns (the last may be shorter), lists of `stride` candidates,
+// How a call is split: `segments` per row of `length` columns (the last may be shorter), lists of up to `cap` candidates,
 // workgroups of w wavefronts with ng groups per lane, merge_waves wavefronts per row to merge.  segments = 0: not at all.
 struct Split {
-  int segments, length, stride, w, ng, merge_waves;
+  int segments, length, cap, w, ng, merge_waves;
   int64_t rows;  // rows per pair of launches, so that the scratch memory stays bounded
-  int64_t bytes() const { return rows * segments * ((int64_t)sizeof(SegmentHead) + (int64_t)stride * 8); }
+  int64_t bytes() const { return rows * segments * ((int64_t)sizeof(SegmentHead) + (int64_t)cap * 8); }
 };
 
 constexpr int64_t kSplitScratch = 128ll << 20;
@@ -56,16 +59,21 @@ inline Split split_of(int64_t N, int M, int k, int mode, int max_iter) {
   s.segments = (M + most - 1) / most;
   s.length = ((M + s.segments - 1) / s.segments + 3) & ~3;
   s.ng = s.length <= s.w * 3072 ? 12 : 16;
-  // A segment's candidates: 1.2 to 1.35 k, and the spread of its wavefronts' floors, which weighs when k is small.  The
-  // lists have room for several times that; the merging workgroup's registers hold what is expected of all segments.
-  s.stride = 4 * k + 256 < segment_room(s.w) ? 4 * k + 256 : segment_room(s.w);
+  // A segment's candidates: 1.2 to 1.35 k, and the spread of its wavefronts' floors, which weighs when k is small: `usual` is
+  // seldom exceeded on ordinary rows (k = 64: 176 at most, k = 512: 1012 in one segment of 200).  The merging workgroup's
+  // registers hold what its row can have, unless that is beyond 16 wavefronts: there they hold what is expected of the row.
   int root = 1;
   while (root * root < k) ++root;
-  const int64_t expected = (int64_t)s.segments * (k + k / 3 + 6 * root + 16);
-  s.merge_waves = expected <= 4 * kWave * kMergeRegs ? 4 : (expected <= 8 * kWave * kMergeRegs ? 8 : 16);
-  if (expected > 16 * kWave * kMergeRegs) s.segments = 0;
+  const int usual = k + k / 3 + 10 * root + 24, expected = k + k / 3 + 6 * root + 16;
+  const int64_t need = (int64_t)s.segments * usual, per_wave = kWave * kMergeRegs;
+  s.merge_waves = need <= 4 * per_wave ? 4 : (need <= 8 * per_wave ? 8 : 16);
+  if ((int64_t)s.segments * expected > 16 * per_wave) s.segments = 0;
   if (s.segments == 0) return s;
-  const int64_t per_row = s.segments * ((int64_t)sizeof(SegmentHead) + (int64_t)s.stride * 8);
+  const int share = (int)(s.merge_waves * per_wave / s.segments);
+  s.cap = share > usual ? share : usual;
+  if (s.cap > 4 * k + 640) s.cap = 4 * k + 640;
+  if (s.cap > segment_room(s.w)) s.cap = segment_room(s.w);
+  const int64_t per_row = s.segments * ((int64_t)sizeof(SegmentHead) + (int64_t)s.cap * 8);
   s.rows = kSplitScratch / per_row;
   if (s.rows < 1) s.rows = 1;
   if (s.rows > N) s.rows = N;
@@ -74,7 +82,7 @@ inline Split split_of(int64_t N, int M, int k, int mode, int max_iter) {
 
 template <int NG, int W, bool NEG>
 __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(5)))
-    rtopk_segment_kernel(const float* __restrict__ in, int M, int k, int segments, int length, int stride,
+    rtopk_segment_kernel(const float* __restrict__ in, int M, int k, int segments, int length, int cap,
                          SegmentHead* __restrict__ heads, uint2* __restrict__ lists) {
   constexpr int G = 4, E = G * NG;
   __shared__ BoundsLds<W> s_bounds;
@@ -96,9 +104,34 @@ __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(
   block_bounds<E, W, NEG, true>(x, nm, (k + W) / W, lane, wave, s_bounds, lo, hi, T0, probe);
   auto column = [&](int quad, int thread) -> int { return min((quad * W * kWave + thread) * G, cols - G); };
   const int n = filter_lists<E, W, NEG>(s_filter, x, lane, wave, T0, column, [] {});
-  const bool whole = n >= 0 && n <= stride;  // uniform
-  if (tid == 0) heads[blockIdx.x] = SegmentHead{whole ? n : -1, T0, -lo, hi};
-  if (!whole) return;
+  uint2* to = lists + (int64_t)blockIdx.x * cap;
+  if (n < 0 || n > cap) {  // uniform
+    bool none = false;
+    float ahead[1];
+    KnownBounds end{};
+    // (their values to the first half of the list's memory, their columns to the second; then in pairs like any other list)
+    float* values = reinterpret_cast<float*>(to);
+    int32_t* columns = reinterpret_cast<int32_t*>(to) + cap;
+    block_row<G, NG, W, kExact, NEG, kF32, false, kFullWidth>(0, from, 1, cols, k + 1, 0, 0.0f, values, columns, nullptr, 1,
+                                                              none, ahead, none, x, end);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (it stores through inline asm)
+    __syncthreads();
+    constexpr int kMost = (filter_max_k<W>() + W * kWave) / (W * kWave);  // pairs per thread, k + 1 in all
+    uint2 pair[kMost];
+#pragma unroll
+    for (int i = 0; i < kMost; ++i) {
+      const int j = min(i * W * kWave + tid, k);
+      pair[i] = make_uint2(__float_as_uint(values[j]), (uint32_t)(columns[j] + first));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kMost; ++i) {
+      if (i * W * kWave + tid <= k) to[i * W * kWave + tid] = pair[i];
+    }
+    if (tid == 0) heads[blockIdx.x] = SegmentHead{k + 1, end.lo, -lo, hi};
+    return;
+  }
+  if (tid == 0) heads[blockIdx.x] = SegmentHead{n, T0, -lo, hi};
   // in column order: the places of the singles' bits
   s_filter.maps.chosen[tid] = make_uint2(0u, 0u);
   __syncthreads();
@@ -108,7 +141,6 @@ __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(
   }
   __syncthreads();
   filter_prefix(s_filter, s_filter.maps.chosen, lane, wave);
-  uint2* to = lists + (int64_t)blockIdx.x * stride;
   for (int j = tid; j < n; j += W * kWave) {
     const uint2 e = s_filter.single[j];
     const uint32_t place = filter_rank(s_filter, s_filter.maps.chosen, (int)e.y);
@@ -120,10 +152,10 @@ __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(
 // the floor, from the row.  Returns false, with nothing written, where the lists do not hold the search.  Called by the
 // whole workgroup; uniform.
 template <int NW, int MODE, bool NEG>
-__device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ in, int M, int k, int max_iter, float eps_rel, float* __restrict__ out_vals,
-                                          int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters,
-                                          const SegmentHead* __restrict__ heads, const uint2* __restrict__ lists,
-                                          int segments, int stride) {
+__device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ in, int M, int k, int max_iter, float eps_rel,
+                                          float* __restrict__ out_vals, int32_t* __restrict__ out_idx,
+                                          int32_t* __restrict__ out_iters, const SegmentHead* __restrict__ heads,
+                                          const uint2* __restrict__ lists, int segments, int cap) {
   __shared__ int s_first[kMaxSegments + 1];  // candidates in earlier segments
   __shared__ float s_bound[3];
   __shared__ int s_total, s_cnt[2][NW], s_cls[2][NW];
@@ -134,13 +166,11 @@ __device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ i
   if (wave == 0) {
     float fl = -__builtin_inff(), nlo = -__builtin_inff(), hi = -__builtin_inff();
     int before = 0;
-    bool whole = true;
     for (int s0 = 0; s0 < segments; s0 += kWave) {
       const bool live = s0 + lane < segments;
       const SegmentHead h = heads[r * segments + (live ? s0 + lane : 0)];
       const int n = live ? h.n : 0;
-      whole = whole && __builtin_amdgcn_ballot_w64(n < 0) == 0;
-      const uint32_t incl = wave_inclusive_scan_dpp((uint32_t)(n < 0 ? 0 : n));
+      const uint32_t incl = wave_inclusive_scan_dpp((uint32_t)n);
       if (live) s_first[s0 + lane] = before + (int)incl - n;
       before += __builtin_amdgcn_readlane((int)incl, kWave - 1);
       fl = vmax(fl, h.floor);  // (a lane beyond the last segment repeats the first)
@@ -152,7 +182,7 @@ __device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ i
     wave_max_and_negmin(hi, hi, c, unused);
     if (lane == 0) {
       s_first[segments] = before;
-      s_total = whole ? before : -1;
+      s_total = before;
       s_bound[0] = a;
       s_bound[1] = b;
       s_bound[2] = c;
@@ -181,7 +211,7 @@ __device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ i
         int s = 0;  // the last segment that starts at or before e and is not empty
         for (int step = top; step > 0; step >>= 1)
           if (s + step < segments && s_first[s + step] <= e) s += step;
-        const uint2 v = lists[(r * segments + s) * stride + (e - s_first[s])];
+        const uint2 v = lists[(r * segments + s) * cap + (e - s_first[s])];
         key[i] = keyof<NEG>(__uint_as_float(v.x));
         col[i] = v.y;
       }
@@ -246,7 +276,9 @@ __device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ i
   }
   float* ov = out_vals + r * (int64_t)k;
   int32_t* oi = out_idx + r * (int64_t)k;
-  if (MODE != kExact && !((limB > 0 ? tB : tA) >= T0)) {
+  // (At the floor itself a list may hold some of the keys only.  They are those that exact mode needs, whose class B is one
+  // value; the other modes take the first keys of a whole range.)
+  if (MODE != kExact && !((limB > 0 ? tB : tA) > T0)) {
     write_by_chunks<NW, 4, NEG, 4>(in + r * (int64_t)M, M, k, tA, tB, limA, limB, ov, oi);
     return true;
   }
@@ -292,9 +324,9 @@ template <int NW, int MODE, bool NEG>
 __global__ void __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(4)))
     rtopk_merge_kernel(const float* __restrict__ in, int M, int k, int max_iter, float eps_rel,
                        float* __restrict__ out_vals, int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters,
-                       const SegmentHead* __restrict__ heads, const uint2* __restrict__ lists, int segments, int stride) {
+                       const SegmentHead* __restrict__ heads, const uint2* __restrict__ lists, int segments, int cap) {
   const int64_t r = blockIdx.x;
-  if (merge_row<NW, MODE, NEG>(r, in, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, heads, lists, segments, stride)) return;
+  if (merge_row<NW, MODE, NEG>(r, in, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, heads, lists, segments, cap)) return;
   __syncthreads();
   stream_row<NW, 4, MODE, NEG>(r, in, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters);
 }
@@ -309,14 +341,14 @@ hipError_t launch_split(const Split& s, void* scratch, const LaunchArgs& a) {
     const auto segment = s.w == 4 ? (s.ng == 12 ? &rtopk_segment_kernel<12, 4, NEG> : &rtopk_segment_kernel<16, 4, NEG>)
                                   : (s.ng == 12 ? &rtopk_segment_kernel<12, 8, NEG> : &rtopk_segment_kernel<16, 8, NEG>);
     hipError_t err = launch_kernel(segment, dim3((unsigned)(rows * s.segments)), dim3(s.w * kWave), 0, a.stream, in, a.M, a.k,
-                                   s.segments, s.length, s.stride, heads, lists);
+                                   s.segments, s.length, s.cap, heads, lists);
     if (err != hipSuccess) return err;
     const auto merge = s.merge_waves == 4   ? &rtopk_merge_kernel<4, MODE, NEG>
                        : s.merge_waves == 8 ? &rtopk_merge_kernel<8, MODE, NEG>
                                             : &rtopk_merge_kernel<16, MODE, NEG>;
     err = launch_kernel(merge, dim3((unsigned)rows), dim3(s.merge_waves * kWave), 0, a.stream, in, a.M, a.k, a.max_iter,
                         a.eps_rel, static_cast<float*>(a.out_vals) + r0 * a.k, static_cast<int32_t*>(a.out_idx) + r0 * a.k,
-                        a.out_iters ? a.out_iters + r0 : nullptr, heads, lists, s.segments, s.stride);
+                        a.out_iters ? a.out_iters + r0 : nullptr, heads, lists, s.segments, s.cap);
     if (err != hipSuccess) return err;
   }
   return hipSuccess;
