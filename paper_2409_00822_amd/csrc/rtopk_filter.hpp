@@ -71,28 +71,47 @@ __device__ __forceinline__ void lane_group_maxima(const float (&x)[E], float (&g
 // other values would (12 to 16 steps in all; 27 at most in 60 rows each of eleven kinds).  Exact mode with one entry of -1e9 a row,
 // twelve halvings -> this: 8192 x 4096, k = 64, 74 -> 28 us; 1048 x 32000 102 -> 31; 671 x 50000, k = 100, 398 -> 40.
 // With NaN or infinite keys any value may come out.
-// halvings: 7, or, where low and high are Algorithm 2's own first bounds, its number of steps if that is at least 7 and
+// halvings: 0, or, where low and high are Algorithm 2's own first bounds, its number of steps if that is at least 7 and
 // small: if they all move `low` they are that search, which ends there, below any better floor.
 template <int J>
 __device__ __forceinline__ float floor_of_maxima(const float (&gm)[J], int need, float low, float high, float& above,
-                                                 int halvings = 7) {
+                                                 int halvings = 0) {
   const int enough = need + (need >> 3) + 1;
   const float largest = high;
-  bool found = false;
-  auto try_bound = [&](float t) {
+  auto at_or_above = [&](float t) -> int {
     int cnt = 0;
 #pragma unroll
     for (int j = 0; j < J; ++j) cnt += __builtin_popcountll(__builtin_amdgcn_ballot_w64(gm[j] >= t));
-    if (cnt >= need) {
+    return cnt;
+  };
+#pragma unroll  // (rolled, the steps of rows of 16 to 32 values per lane cost up to a tenth of their time)
+  for (int step = 0; step < 7; ++step) {
+    const float mid = (low + high) * 0.5f;
+    const int cnt = at_or_above(mid);
+    const bool enough_above = cnt >= need;  // (selects and one branch: a branch for each side costs 3 % at 16 values per lane)
+    low = enough_above ? mid : low;
+    high = enough_above ? high : mid;
+    if ((uint32_t)(cnt - need) <= (uint32_t)(enough - need)) {
+      above = high;
+      return low;
+    }
+  }
+  // (A floor that is itself one of the keys leaves no room below the k-th for a precision-bounded search to end in, so
+  // from here on two more maxima than needed: 7168 columns, k = 8, precision 1e-4 37 -> 27.)
+  const int wanted = need + 2 + (need >> 4), at_most = enough + 3 + (need >> 4);
+  bool found = false;
+  auto try_bound = [&](float t) {
+    const int cnt = at_or_above(t);
+    if (cnt >= wanted) {
       low = t;
-      found = cnt <= enough;
+      found = cnt <= at_most;
     } else {
       high = t;
     }
   };
-  for (int step = 0; step < halvings && !found; ++step) try_bound((low + high) * 0.5f);
-  if (halvings != 7) found = found || high == largest;
-  for (int step = 0; step < 24 && __builtin_expect(!found, 0); ++step) {
+  for (int step = 7; step < halvings && !found; ++step) try_bound((low + high) * 0.5f);
+  if (halvings != 0 && high == largest) found = true;
+  for (int step = 0; step < 24 && !found; ++step) {
     // a lane's largest below `high`, or (every other step) its smallest above `low`
     const float inf = __builtin_inff();
     uint64_t lanes;
@@ -120,10 +139,14 @@ __device__ __forceinline__ float floor_of_maxima(const float (&gm)[J], int need,
 
 // The steps of Algorithm 2, or of Algorithm 1 with precision eps, whose thresholds lie at or below the floor T0: each
 // of them counts more than k keys and moves lo up.  Returns whether the search ends among them; then lo is final and hi
-// still the largest key.
+// still the largest key.  They are taken only if they may well be all there are -- if all steps but the last, halving [lo, hi] towards
+// hi, or a last minimum within eps of hi, come out no higher than the floor: otherwise none is taken, and false returned,
+// because the search on the lists takes them just as fast (16 values per lane, bfloat16, eight steps: 5 %).
 template <int MODE>
 __device__ __forceinline__ bool walk_to_floor(float T0, int max_iter, float eps, float& lo, float hi, int& steps) {
   steps = 0;
+  const float reached = MODE == kEarly ? hi - __builtin_ldexpf(hi - lo, 1 - max_iter) : hi - eps;
+  if (reached > T0) return false;
   for (;;) {
     if (MODE == kEarly ? steps >= max_iter : !(hi - lo > eps)) return true;
     const float mid = (lo + hi) * 0.5f;
@@ -511,7 +534,7 @@ __device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E
   uint32_t* id = reinterpret_cast<uint32_t*>(quad + room);  // first column of a quad
 
   float T0, probe;
-  const int halvings = MODE == kEarly && max_iter >= 7 && max_iter <= 16 ? max_iter : 7;
+  const int halvings = MODE == kEarly && max_iter >= 7 && max_iter <= 16 ? max_iter : 0;
   if (k <= wave_filter_small_k(E)) {  // uniform over the launch
     float gm[wave_groups(E, false)];
     lane_group_maxima<E, NEG>(x, gm);

@@ -279,7 +279,7 @@ __device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ i
   // (At the floor itself a list may hold some of the keys only.  They are those that exact mode needs, whose class B is one
   // value; the other modes take the first keys of a whole range.)
   if (MODE != kExact && !((limB > 0 ? tB : tA) > T0)) {
-    write_by_chunks<NW, 4, NEG, 4>(in + r * (int64_t)M, M, k, tA, tB, limA, limB, ov, oi);
+    write_by_chunks<NW, 4, NEG, 2>(in + r * (int64_t)M, M, k, tA, tB, limA, limB, ov, oi);
     return true;
   }
 

@@ -116,6 +116,7 @@ __device__ __forceinline__ void write_by_chunks(const float* __restrict__ row, i
       uint32_t posA = baseA + (before & 0xffffu), posB = baseB + (before >> 16);
 #pragma unroll
       for (int c = 0; c < G; ++c) {
+        asm volatile("" : "+v"(v[u][c]));  // opaque: the lane masks of all loads are not kept over the barrier
         const bool a = is_a(u, c), b = is_b(u, c);
         if ((a && posA < (uint32_t)limA) || (b && posB < (uint32_t)limB)) {
           const uint32_t pos = (posA < (uint32_t)limA ? posA : (uint32_t)limA) + (posB < (uint32_t)limB ? posB : (uint32_t)limB);
@@ -127,6 +128,7 @@ __device__ __forceinline__ void write_by_chunks(const float* __restrict__ row, i
       }
       baseA += total & 0xffffu;
       baseB += total >> 16;
+      __builtin_amdgcn_sched_barrier(0);
     }
     parity ^= 1;
   }
