@@ -510,12 +510,22 @@ constexpr int wave_groups(int E, bool many) {
   return E <= 24 ? E / 4 : (!many ? 4 : (E == 48 ? 12 : 8));
 }
 constexpr int wave_filter_small_k(int E) { return 35 * wave_groups(E, false); }
+// The largest k that takes the lists.  Beyond it a row's candidates fill eight registers of singles and more, and the LDS of
+// the lists leaves fewer wavefronts in flight; 2^25 values, full-width search -> lists (us; exact mode): 1280 columns
+// k = 140 43 -> 43, 175 43 -> 45; 2048 columns 175 31 -> 28, 245 30 -> 34; 3072 columns 245 31 -> 28, 280 31 -> 30, 420 31 -> 63
+// (the lists never hold); 6146 columns 245 40 -> 33, 280 40 -> 46.  The dense form, bound by its stores, gains nothing
+// from the lists and loses what wavefronts they cost: 8192 columns k = 64 47 -> 48, 140 50 -> 54, 280 51 -> 59.
 // Rows of 16 values per lane: only the kernel of one row, see one_row_lists; the precision-bounded mode, whose trajectory
 // starts at the row's minimum, keeps its full-width search there (k = 128 124 -> 135 us, 64 no difference).  Below 16 the
 // full-width search costs no more than the lists do.
-constexpr int wave_filter_max_k(int E, int R, int mode) {
-  return R > 1 || E < (mode == kEps ? 24 : 16) ? 0 : 35 * wave_groups(E, true);
+constexpr int wave_filter_max_k(int E, int R, int mode, bool dense = false) {
+  if (R > 1 || E < (mode == kEps ? 24 : 16)) return 0;
+  if (dense) return E <= 24 ? 100 : (E <= 64 ? 175 : 48);
+  return E <= 24 ? 140 : (E == 32 ? 175 : 245);
 }
+// Algorithm 2 with fewer steps than this searches the full width: the last threshold of few steps lies below the floor, and
+// each step saved is worth the less the narrower the row (1280 columns, bfloat16, five steps, k = 140: 38 -> 43 us, 100 38 -> 37).
+constexpr int wave_filter_min_steps(int E, int k) { return E <= 32 && k > 100 ? 6 : 5; }
 // Quads, and singles, that the lists of a row hold, and the pairs' worth of LDS they take.
 __host__ __device__ constexpr int wave_filter_room(int k) { return (k + k / 2 + 48 + 63) & ~63; }
 __host__ __device__ constexpr int wave_filter_pairs(int k) { return wave_filter_room(k) * 20 / 8; }

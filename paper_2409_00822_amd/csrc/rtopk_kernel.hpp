@@ -817,9 +817,9 @@ __host__ __device__ constexpr int staged_pairs(int E, int R, int k) {
   const int band = band_scratch_floats(E) / 2;
   return ((R * k > band ? R * k : band) + 1) & ~1;
 }
-__host__ __device__ constexpr int wave_pairs(int E, int R, int k, int mode) {
+__host__ __device__ constexpr int wave_pairs(int E, int R, int k, int mode, int max_iter) {
   const int staged = staged_pairs(E, R, k);
-  if (k > wave_filter_max_k(E, R, mode)) return staged;
+  if (k > wave_filter_max_k(E, R, mode) || (mode == kEarly && max_iter < wave_filter_min_steps(E, k))) return staged;
   const int lists = wave_filter_pairs(k);
   return staged > lists ? staged : lists;
 }
@@ -914,11 +914,11 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
       return gather_band<E, NEG, false, BR>(x, lo, hi, lane, stage_addr, band, nb);
     }
   };
-  // Rows of 16 or more values per lane: the lists first.  Algorithm 2 with few steps: see launch_block.
+  // Rows of 16 or more values per lane: the lists first.
   bool bounds_known = false;  // Algorithm 1 with precision: lo, hi and the iteration count are those of its end
   int known_iterations = 0;
   if constexpr (wave_filter_max_k(E, R, MODE) > 0) {
-    if (k <= wave_filter_max_k(E, R, MODE) && (MODE != kEarly || max_iter >= 5)) {  // uniform over the launch
+    if (k <= wave_filter_max_k(E, R, MODE, DENSE) && (MODE != kEarly || max_iter >= wave_filter_min_steps(E, k))) {  // uniform over the launch
       float thi, tlo;
       int split, iterations = 0;
       const float eps = MODE == kEps ? eps_rel * __builtin_fabsf(hi) : 0.0f;
@@ -1263,7 +1263,7 @@ __global__ void __launch_bounds__(256)
   if (r0 >= N) return;
   int nrows = rows_left(N - r0, R);
   static_assert(!narrows(E, MODE) || R == 1, "the band scratch reuses the staging area of the wavefront's only row");
-  uint2* stage = stage_all + (size_t)wave * wave_pairs(E, R, k, MODE);
+  uint2* stage = stage_all + (size_t)wave * wave_pairs(E, R, k, MODE, max_iter);
 
   // Loading stage: all R rows' loads are issued before any is consumed.
   float x[R][E];
@@ -1400,7 +1400,7 @@ __global__ void __launch_bounds__(256)
   const int64_t r0 = ((int64_t)blockIdx.x * waves_per_block + wave) * R;
   if (r0 >= N) return;
   int nrows = rows_left(N - r0, R);
-  uint2* scratch = band_scratch + (size_t)wave * wave_pairs(E, R, k <= wave_filter_max_k(E, R, MODE) ? k : 1, MODE);
+  uint2* scratch = band_scratch + (size_t)wave * wave_pairs(E, R, k <= wave_filter_max_k(E, R, MODE, true) ? k : 1, MODE, max_iter);
 
   float x[R][E];
 #pragma unroll
@@ -1441,7 +1441,7 @@ hipError_t launch_dense(const LaunchArgs& a) {
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   if (a.M < Layout<G, NG>::MIN_M || a.M > 64 * Layout<G, NG>::E) return hipErrorInvalidValue;
   constexpr int E = Layout<G, NG>::E;
-  const size_t lds = E < 12 ? 0 : (size_t)waves * wave_pairs(E, R, a.k <= wave_filter_max_k(E, R, MODE) ? a.k : 1, MODE) * sizeof(uint2);
+  const size_t lds = E < 12 ? 0 : (size_t)waves * wave_pairs(E, R, a.k <= wave_filter_max_k(E, R, MODE, true) ? a.k : 1, MODE, a.max_iter) * sizeof(uint2);
   return launch_kernel(rtopk_dense_kernel<G, NG, R, FULL, MODE>, dim3((unsigned)blocks), dim3(waves * kWave), lds,
                        a.stream, static_cast<const float*>(a.in), a.N, a.M, a.k, a.max_iter,
                        static_cast<float*>(a.out_vals));
@@ -1454,7 +1454,7 @@ hipError_t launch(const LaunchArgs& a) {
   using L = Layout<G, NG>;
   if (a.M < L::MIN_M || a.M > 64 * L::E) return hipErrorInvalidValue;
   // LDS per wavefront: at most 64 KiB per block
-  size_t per_wave = (size_t)wave_pairs(L::E, R, a.k, MODE) * sizeof(uint2);
+  size_t per_wave = (size_t)wave_pairs(L::E, R, a.k, MODE, a.max_iter) * sizeof(uint2);
   // one wavefront per workgroup, except where a wavefront stages 8 KiB or more of pairs: there four
   // per workgroup measured 7 % faster (2^20 x 256, k = 128: 387 -> 360 us), while at 4 KiB and below
   // one per workgroup is the faster by 3-11 %
@@ -1477,8 +1477,12 @@ constexpr int rows_per_wave(int E) { return E <= 2 ? 16 : (E <= 4 ? 8 : (E <= 16
 // 117.7 -> 122.0); bfloat16, whose search is the larger part, 106 -> 81, 122 -> 97 and 133 -> 119, with early stopping
 // 91 -> 79, 96 -> 89 and 98 -> 103.  (Lists in the kernel of two rows: bfloat16 106 -> 68 and 121 -> 84, but 2 % slower
 // for every k without lists, fp32 early k = 64 by 5 %; fp32 rows of 12 values per lane lose with one row, 117 -> 121.)
+// The narrower the row, the fewer group maxima there are for a floor: 16-bit exact rows take 35 of 64 of them at most (2^25
+// values, bfloat16, k = 130: 600 columns 53 -> 62 us, 1024 columns 53 -> 43; k = 90 at 514 columns 55 -> 52), those with early stopping
+// 24 of 64, in seven steps or more (600 columns, k = 64: six 31 -> 35, seven 34 -> 35, eight 37 -> 37); fp32 rows six or more.
 inline bool one_row_lists(int mode, bool half, const LaunchArgs& a) {
-  return a.k <= (half && mode == kExact ? wave_filter_max_k(16, 1, mode) : 64) && (mode != kEarly || a.max_iter >= 5);
+  if (mode == kExact) return a.k <= (half ? min(wave_filter_max_k(16, 1, mode), 35 * a.M / 256) : 64);
+  return a.k <= (half ? min(64, 24 * a.M / 256) : 64) && a.max_iter >= (half ? 7 : 6);
 }
 // fp32 rows of 129..256 columns with int32 columns (and their dense form) take 4 instead: with
 // non-temporal output stores the smaller per-wavefront footprint streams better (2^20 x 256: k = 32
