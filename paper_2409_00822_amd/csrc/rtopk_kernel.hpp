@@ -1489,7 +1489,10 @@ inline bool one_row_lists(int mode, bool half, const LaunchArgs& a) {
 // 221 -> 215 us, k = 64 254 -> 247 us, k = 128 356 -> 345 us, dense 346 -> 339 us; with no search steps at
 // all, 2 rows per wavefront reach 200 us but the search then costs 47 us more).  The variants that are
 // bound by instruction issue rather than by memory keep 8, which amortises the per-wavefront work over
-// more rows: rows stored in 16 bits (192 against 202 us) and byte-wide columns (2.4M rows: 475 against 483 us).
+// more rows: rows stored in 16 bits (192 against 202 us) and byte-wide columns of ragged rows (1.34M rows of 200
+// columns, k = 24: 235 against 250 us).  Byte-wide columns of exactly 256 take 4 as well since row addresses within a
+// batch are 32-bit offsets, which cost eight rows 2 % and gain four 1 %: 2.4M rows, eight steps, k = 32 482 -> 461 us (473 with
+// eight rows and 64-bit addresses), and with the scatter of their gradients behind it 968 -> 943; 2^20 rows, k = 64 239 -> 222.
 constexpr int kRowsPerWaveFp32M256 = 4;
 
 // Few rows: with 8 or 16 rows per wavefront a launch of less than ~32768 rows does not even put two
