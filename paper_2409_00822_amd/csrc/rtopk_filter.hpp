@@ -65,14 +65,16 @@ __device__ __forceinline__ void lane_group_maxima(const float (&x)[E], float (&g
 // A floor under at least `need` of the wavefront's group maxima, as close to the need-th as a few steps bring it, between
 // `low` (no larger than any key of the wavefront's) and `high` (its largest key); `above` is left at the lowest bound
 // tried with fewer than `need` maxima at or above it.  Halving the range of values gets there in five to seven steps on
-// ordinary rows (normal, Laplace, uniform) but not where one entry, or a masked part of the row, lies far from the
-// others: from -1e9 twelve steps end at -2.4e5, below every other key, and the row would not fit the lists.  So the
-// steps after the seventh take one of the group maxima between the bounds instead, which needs no more of them than any
-// other values would (12 to 16 steps in all; 27 at most in 60 rows each of eleven kinds).  Exact mode with one entry of -1e9 a row,
-// twelve halvings -> this: 8192 x 4096, k = 64, 74 -> 28 us; 1048 x 32000 102 -> 31; 671 x 50000, k = 100, 398 -> 40.
+// ordinary rows (normal, Laplace, uniform; up to ten on squared distances) but not where one entry, or a masked part of the
+// row, lies far from the others: from -1e9 twelve steps end at -2.4e5, below every other key, and the row would not fit the
+// lists.  So the steps after the tenth take one of the group maxima between the bounds instead, which needs no more of
+// them than any other values would (five to nine, 20 at most in 60 rows each of eleven kinds).  Exact mode with one entry of -1e9 a
+// row, twelve halvings -> this: 8192 x 4096, k = 64, 74 -> 28 us; 1048 x 32000 102 -> 31; 671 x 50000, k = 100, 398 -> 40.
+// (After seven halvings already: 2048 x 50000 squared distances, k = 100, 86.6 -> 89.6; now 87.5.)
 // With NaN or infinite keys any value may come out.
-// halvings: 0, or, where low and high are Algorithm 2's own first bounds, its number of steps if that is at least 7 and
-// small: if they all move `low` they are that search, which ends there, below any better floor.
+// halvings: 0, or, where low and high are Algorithm 2's own first bounds, its number of steps if that is small: if they all
+// move `low` they are that search, which ends there, below any better floor.
+constexpr int kFloorHalvings = 10;
 template <int J>
 __device__ __forceinline__ float floor_of_maxima(const float (&gm)[J], int need, float low, float high, float& above,
                                                  int halvings = 0) {
@@ -85,7 +87,7 @@ __device__ __forceinline__ float floor_of_maxima(const float (&gm)[J], int need,
     return cnt;
   };
 #pragma unroll  // (rolled, the steps of rows of 16 to 32 values per lane cost up to a tenth of their time)
-  for (int step = 0; step < 7; ++step) {
+  for (int step = 0; step < kFloorHalvings; ++step) {
     const float mid = (low + high) * 0.5f;
     const int cnt = at_or_above(mid);
     const bool enough_above = cnt >= need;  // (selects and one branch: a branch for each side costs 3 % at 16 values per lane)
@@ -109,7 +111,7 @@ __device__ __forceinline__ float floor_of_maxima(const float (&gm)[J], int need,
       high = t;
     }
   };
-  for (int step = 7; step < halvings && !found; ++step) try_bound((low + high) * 0.5f);
+  for (int step = kFloorHalvings; step < halvings && !found; ++step) try_bound((low + high) * 0.5f);
   if (halvings != 0 && high == largest) found = true;
   for (int step = 0; step < 24 && !found; ++step) {
     // a lane's largest below `high`, or (every other step) its smallest above `low`
@@ -544,7 +546,7 @@ __device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E
   uint32_t* id = reinterpret_cast<uint32_t*>(quad + room);  // first column of a quad
 
   float T0, probe;
-  const int halvings = MODE == kEarly && max_iter >= 7 && max_iter <= 16 ? max_iter : 0;
+  const int halvings = MODE == kEarly && max_iter <= 16 ? max_iter : 0;
   if (k <= wave_filter_small_k(E)) {  // uniform over the launch
     float gm[wave_groups(E, false)];
     lane_group_maxima<E, NEG>(x, gm);

@@ -1479,10 +1479,11 @@ constexpr int rows_per_wave(int E) { return E <= 2 ? 16 : (E <= 4 ? 8 : (E <= 16
 // for every k without lists, fp32 early k = 64 by 5 %; fp32 rows of 12 values per lane lose with one row, 117 -> 121.)
 // The narrower the row, the fewer group maxima there are for a floor: 16-bit exact rows take 35 of 64 of them at most (2^25
 // values, bfloat16, k = 130: 600 columns 53 -> 62 us, 1024 columns 53 -> 43; k = 90 at 514 columns 55 -> 52), those with early stopping
-// 24 of 64, in seven steps or more (600 columns, k = 64: six 31 -> 35, seven 34 -> 35, eight 37 -> 37); fp32 rows six or more.
+// 24 of 64, in seven steps or more (600 columns, k = 64: six 31 -> 35, seven 34 -> 35, eight 37 -> 37); fp32 rows five or more from
+// 896 columns on (1024 columns, k = 48: 29 -> 26), six below (770, k = 64: five 30 -> 33, six 32 -> 33).
 inline bool one_row_lists(int mode, bool half, const LaunchArgs& a) {
   if (mode == kExact) return a.k <= (half ? min(wave_filter_max_k(16, 1, mode), 35 * a.M / 256) : 64);
-  return a.k <= (half ? min(64, 24 * a.M / 256) : 64) && a.max_iter >= (half ? 7 : 6);
+  return a.k <= (half ? min(64, 24 * a.M / 256) : 64) && a.max_iter >= (half ? 7 : (a.M >= 896 ? 5 : 6));
 }
 // fp32 rows of 129..256 columns with int32 columns (and their dense form) take 4 instead: with
 // non-temporal output stores the smaller per-wavefront footprint streams better (2^20 x 256: k = 32
