@@ -22,14 +22,34 @@ using at::Tensor;
 // A tensor argument; nullptr where it is none.
 const Tensor* tensor_of(PyObject* o) { return THPVariable_Check(o) ? &THPVariable_Unpack(o) : nullptr; }
 
-// A Python int that fits 32 bits.
+// A whole number that fits 32 bits: a Python int, or whatever counts as an index (NumPy's integers).  What does not, or
+// raises, is left to the Python code, with no exception set.
 bool int32_of(PyObject* o, int32_t& v) {
-  if (!PyLong_Check(o)) return false;
+  PyObject* made = nullptr;
+  if (!PyLong_Check(o)) {
+    if (!PyIndex_Check(o) || !(made = PyNumber_Index(o))) {
+      PyErr_Clear();
+      return false;
+    }
+    o = made;
+  }
   int overflow = 0;
   const long long x = PyLong_AsLongLongAndOverflow(o, &overflow);
+  Py_XDECREF(made);
   if (overflow != 0 || x < std::numeric_limits<int32_t>::min() || x > std::numeric_limits<int32_t>::max()) return false;
   v = (int32_t)x;
   return true;
+}
+
+// A number as a float: a Python float or int, or whatever converts to one.
+bool float_of(PyObject* o, float& v) {
+  const double x = PyFloat_Check(o) ? PyFloat_AS_DOUBLE(o) : (PyUnicode_Check(o) ? -1.0 : PyFloat_AsDouble(o));
+  if (x == -1.0 && PyErr_Occurred()) {
+    PyErr_Clear();
+    return false;
+  }
+  v = (float)x;
+  return !PyUnicode_Check(o);
 }
 
 bool is_matrix(const Tensor& t, at::ScalarType type) {
@@ -168,28 +188,29 @@ PyObject* select(PyObject*, PyObject* const* args, Py_ssize_t n) {
 PyObject* select_eps(PyObject*, PyObject* const* args, Py_ssize_t n) {
   return guarded([&]() -> PyObject* {
     int32_t k;
-    if (n != 7 || !int32_of(args[1], k) || k < 0 || !PyFloat_Check(args[2]) || !PyBool_Check(args[6])) return none();
+    float eps;
+    if (n != 7 || !int32_of(args[1], k) || k < 0 || !float_of(args[2], eps)) return none();
+    const int iters = args[5] != Py_None ? 1 : PyObject_IsTrue(args[6]);
+    if (iters < 0) return nullptr;
     const Tensor* x = tensor_of(args[0]);
     if (!x || !is_matrix(*x, at::kFloat)) return none();
     const int64_t N = x->size(0), M = x->size(1);
     if (M > std::numeric_limits<int32_t>::max()) return none();
-    const float eps = (float)PyFloat_AS_DOUBLE(args[2]);
-    const bool iters = args[5] != Py_None || args[6] == Py_True;
     Output v, i, t;
     if (!v.set(args[3], at::kFloat, {N, k}, x->device()) || !i.set(args[4], at::kInt, {N, k}, x->device()) ||
-        (iters && !t.set(args[5], at::kInt, {N}, x->device())))
+        (iters != 0 && !t.set(args[5], at::kInt, {N}, x->device())))
       return PyErr_Occurred() ? nullptr : none();
     const float* in = static_cast<const float*>(x->data_ptr());
     float* ov = static_cast<float*>(v.tensor.data_ptr());
     int32_t* oi = static_cast<int32_t*>(i.tensor.data_ptr());
-    int32_t* ot = iters ? static_cast<int32_t*>(t.tensor.data_ptr()) : nullptr;
+    int32_t* ot = iters != 0 ? static_cast<int32_t*>(t.tensor.data_ptr()) : nullptr;
     void* s = stream_of(*x);
     Scratch w(*x, k, RTOPK_EPS, 0);
     const int status = unlocked([&] {
       return rtopk_select_ws(in, N, (int32_t)M, k, RTOPK_EPS, 0, eps, ov, oi, ot, w.data, w.bytes, s);
     });
     if (status != RTOPK_OK) return none();
-    if (!iters) return pair(v, i);
+    if (iters == 0) return pair(v, i);
     PyObject* r = PyTuple_New(3);
     if (!r) return nullptr;
     PyTuple_SET_ITEM(r, 0, v.release());

@@ -119,3 +119,28 @@ def test_without_memory_for_scratch_the_call_does_without_and_for_outputs_it_rai
         del hog
         torch.cuda.set_per_process_memory_fraction(1.0)
     assert torch.equal(v, vals) and torch.equal(i, cols)
+
+
+def test_numbers_of_any_kind_take_the_same_path():
+    # rows of more than 32768 columns: only the native module lends the scratch memory that splits them
+    R = _gpu()
+    from paper_2409_00822_amd import rtopk as binding
+
+    fast = binding._native()
+    x = torch.randn(3, 40000, device="cuda")
+    want = R.rtopk_rowwise_exact(x, 50)
+    early = R.rtopk_rowwise(x, 50, 8)
+    eps = R.rtopk_rowwise_eps(x, 50, 1.0, want_iters=True)
+    for whole in (np.int64, np.int32, np.uint8, lambda v: torch.tensor(v)):
+        got = fast.select(binding._F32 | binding._EXACT, x, whole(50), 0, None, None)
+        assert got is not None and all(torch.equal(a, b) for a, b in zip(got, want))
+        got = fast.select(binding._F32, x, whole(50), whole(8), None, None)
+        assert got is not None and all(torch.equal(a, b) for a, b in zip(got, early))
+        got = fast.select_eps(x, whole(50), whole(1), None, None, None, 1)
+        assert got is not None and all(torch.equal(a, b) for a, b in zip(got, eps))
+    assert len(R.rtopk_rowwise_eps(x, np.int64(50), np.float64(1.0), want_iters=np.bool_(False))) == 2
+    assert len(R.rtopk_rowwise_eps(x, 50, "1.0")) == 2  # Python's float() takes it, so the call does
+    for bad in (3.0, "3", None, np.float32(3.0)):
+        assert fast.select(binding._F32 | binding._EXACT, x, bad, 0, None, None) is None
+    with pytest.raises(TypeError):
+        R.rtopk_rowwise_exact(x, "3")
