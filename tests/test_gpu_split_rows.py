@@ -100,3 +100,28 @@ def test_graph_replays_with_new_inputs():
         torch.cuda.synchronize()
         _same((v, i), oracle.topk_exact(x.cpu().numpy(), 30), f"replay {seed}")
         R.rtopk_rowwise_exact(torch.randn(5, 50000, device="cuda"), 9)
+
+
+def test_threads_and_streams_share_the_allocator():
+    import threading
+
+    R = _gpu()
+    xs = [_rows(33000 + 4099 * t, 6200 + t) for t in range(4)]
+    got = [None] * 4
+
+    def work(t):
+        s = torch.cuda.Stream()
+        with torch.cuda.stream(s):
+            x = torch.from_numpy(xs[t]).cuda()
+            got[t] = [R.rtopk_rowwise_exact(x, 20 + 7 * t) for _ in range(30)]  # scratch and outputs come and go
+        s.synchronize()
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for t in range(4):
+        want = oracle.topk_exact(xs[t], 20 + 7 * t)
+        for j, pair in enumerate(got[t]):
+            _same(pair, want, f"thread {t} call {j}")
