@@ -794,7 +794,7 @@ hipError_t launch_block(const LaunchArgs& a) {
   // Algorithm 2 with few steps ends on a threshold far below the k-th key, which the lists do not reach: the search
   // is then wasted, and in the persistent shape the row is read again (50000 columns, k = 256, four steps: 134 us
   // against 88 us; 32768 columns 56.6 against 56.1).  From eight (five) steps on the lists win as in exact mode.
-  const bool lists = a.k <= filter_max_k<W>() && (MODE != kEarly || a.max_iter >= (block_persistent(W) ? 8 : 5));
+  const bool lists = a.k <= filter_max_k(W) && (MODE != kEarly || a.max_iter >= (block_persistent(W) ? 8 : 5));
   const auto kernel = lists ? &rtopk_filter_kernel<G, NG, W, MODE, NEG, DT, DENSE>
                                                : &rtopk_block_kernel<G, NG, W, MODE, NEG, DT, DENSE>;
   return launch_kernel(kernel, dim3((unsigned)grid), dim3(W * kWave), 0,

@@ -204,13 +204,9 @@ enum FilterResult : int {
                         // the caller's, from lo and hi (Algorithm 2: from lo)
 };
 
-// Whether k is small enough for the lists; host and device agree through this rule alone.  The floor has 1.4 to 1.6 k
-// candidates at such k (1.2 to 1.35 k, and the spread of the wavefronts' floors; 2 k at k = 64): normal rows of 21848
-// columns in 8 wavefronts, k = 512: 824 on average, 1012 at most in 200.
-template <int W>
-constexpr int filter_max_k() {
-  return W == 4 ? 256 : 512;
-}
+// (filter_max_k of rtopk_shape.hpp: the largest k for the lists.  The floor has 1.4 to 1.6 k candidates at such k -- 1.2 to
+// 1.35 k, and the spread of the wavefronts' floors; 2 k at k = 64: normal rows of 21848 columns in 8 wavefronts, k = 512: 824
+// on average, 1012 at most in 200.)
 
 // Positions of the set bits of one bitmap: `before` and `wave_bits` for the words of `map`.  Called by the whole
 // workgroup with a barrier before it; contains one.

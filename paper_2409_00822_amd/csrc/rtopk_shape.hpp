@@ -6,12 +6,10 @@
 // wavefronts (w = 1: one wavefront per row, rtopk_kernel.hpp; w > 1: one workgroup per row,
 // rtopk_block_kernel.hpp), so a layout holds rows of up to 64 * g * ng * w columns.
 //
-// Two steps.  classify() names a call by family and by the widest load that every row's alignment allows
-// (g elements).  kernel_layout() maps that to the layout that is launched: the kernels load vectors from any
-// element boundary at full rate, so what counts there is only how little of a lane's registers a row leaves
-// empty.  Which layouts are compiled is fixed by the lists below; the instantiation tables
-// (rtopk_inst_*.hip) expand the same lists, so a layout that kernel_layout() returns always has a kernel
-// behind it, and with it every layout that classify() returns.
+// The kernels load vectors from any element boundary at full rate, so what counts is only how little of a lane's
+// registers a row leaves empty: kernel_layout() goes by width, type and form, not by alignment.  Which layouts
+// are compiled is fixed by the lists below; the instantiation tables (rtopk_inst_*.hip) expand the same lists, so a
+// layout that kernel_layout() returns always has a kernel behind it.
 #pragma once
 
 #include <stdint.h>
@@ -22,9 +20,6 @@
 // Rows of up to 448 columns, X(g, ng): one or two values per lane, and (g = 0) three, five, six or seven in
 // groups of mixed width (Layout in rtopk_kernel.hpp); four are (4, 1) of the lists above, eight (4, 2) or (8, 1).
 #define RTOPK_LAYOUT_LIST_SMALL(X) X(1, 1) X(2, 1) X(0, 3) X(0, 5) X(0, 6) X(0, 7)
-// Unaligned rows as classify() names them (the kernels behind them: kernel_layout).
-#define RTOPK_NG_LIST_G1(X) X(1) X(2) X(4) X(8) X(16) X(32) X(64) X(128)
-#define RTOPK_NG_LIST_BLOCK_G1(X) X(16) X(32) X(64)
 
 namespace rtopk {
 
@@ -57,9 +52,10 @@ enum Family : int {
 
 struct Shape {
   int family;
-  int g, ng, w;
-  bool full;  // M == 64 * g * ng * w: the kernel needs no column-validity tests
-  int capacity() const { return 64 * g * ng * w; }
+  int g, ng, w;  // g = 0: groups of mixed width, ng values per lane
+  bool full;     // M == 64 * g * ng * w: the kernel needs no column-validity tests
+  int values() const { return g == 0 ? ng : g * ng; }  // per lane
+  int capacity() const { return 64 * values() * w; }
 };
 
 inline bool is_aligned(uintptr_t p, uintptr_t a) { return p % a == 0; }
@@ -77,133 +73,35 @@ inline int pick_ng_h8(int M) {
 #undef X
   return 16;
 }
-inline int pick_ng_g1(int M) {
-#define X(n) if (M <= 64 * n) return n;
-  RTOPK_NG_LIST_G1(X)
-#undef X
-  return 128;
-}
-
 // Wavefronts per row of the workgroup-per-row kernel: a lane holds up to 64 values.
 inline int block_waves(int M) { return M <= 16384 ? 4 : (M <= 32768 ? 8 : 16); }
 
-// Layout for the pair-output entry points.  `in` is the address of the input matrix (its alignment
-// decides the load width); `plain` = fp32 rows, the k largest, Algorithm 2 or exact mode (the variants
-// that have the 12-groups-per-lane workgroup kernels).  Requires 1 <= M <= kMaxM (kMaxBlockM for 16-bit rows).
-inline Shape classify(int M, int dtype, bool plain, uintptr_t in) {
+// The layout of a call.  dtype: element type of the rows; plain: fp32 rows, the k largest, Algorithm 2 or exact mode (the
+// variants that have the 12-groups-per-lane workgroup kernels); dense: the dense-output form (fp32).  Requires
+// 1 <= M <= kMaxM (kMaxBlockM for 16-bit rows and the dense form).
+inline Shape kernel_layout(int M, int dtype, bool plain, bool dense) {
   Shape s{};
   s.w = 1;
   if (M > kMaxBlockM) {
     // streamed: nothing is held, so the "layout" is only the load width (full is never claimed)
     s.family = kFamStream;
-    s.g = (M % 4 == 0 && is_aligned(in, 16)) ? 4 : 1;
-    s.ng = 0;
+    s.g = 4;
     s.w = 16;
-    s.full = false;
     return s;
   }
   if (M > kMaxWaveM) {
     s.family = kFamBlock;
-    if (dtype == kF32 && M % 4 == 0 && is_aligned(in, 16)) {
-      s.g = 4;
-      s.w = block_waves(M);
-      s.ng = (plain && M <= 64 * s.w * 4 * 12) ? 12 : 16;
-    } else if (dtype != kF32 && M % 8 == 0 && is_aligned(in, 16)) {
-      s.g = 8;
-      s.w = block_waves(M);
-      s.ng = 8;
-    } else {
-      s.g = 1;
-      s.w = 16;
-      s.ng = 16;
-      while (1024 * s.ng < M) s.ng <<= 1;
-    }
-  } else if (dtype != kF32) {
-    // 16-bit rows: the widest load whose 64 lanes the row still fills, else the scalar-load fallback
-    s.family = kFamH16;
-    if (M > 256 && M % 8 == 0 && is_aligned(in, 16)) {
-      s.g = 8;
-      s.ng = pick_ng_h8(M);
-    } else if (M > 128 && M <= 256 && M % 4 == 0 && is_aligned(in, 8)) {
-      s.g = 4;
-      s.ng = 1;
-    } else if (M > 64 && M <= 128 && M % 2 == 0 && is_aligned(in, 4)) {
-      s.g = 2;
-      s.ng = 1;
-    } else {
-      s.g = 1;
-      s.ng = pick_ng_g1(M);
-    }
-  } else if (M > 128 && M % 4 == 0 && is_aligned(in, 16)) {
-    s.family = kFamG4;
-    s.g = 4;
-    s.ng = pick_ng_g4(M);
-  } else if (M > 64 && M <= 128 && M % 2 == 0 && is_aligned(in, 8)) {
-    s.family = kFamSmall;
-    s.g = 2;
-    s.ng = 1;
-  } else {
-    s.family = kFamSmall;
-    s.g = 1;
-    s.ng = pick_ng_g1(M);
-  }
-  s.full = (M == s.capacity());
-  return s;
-}
-
-// Layout for the dense-output entry point (fp32): the row is stored with the accesses it was loaded
-// with, so the output's alignment counts as well.
-inline Shape classify_dense(int M, uintptr_t in, uintptr_t out) {
-  Shape s{};
-  s.w = 1;
-  if (M > kMaxWaveM) {
-    s.family = kFamBlock;
-    if (M % 4 == 0 && is_aligned(in, 16) && is_aligned(out, 16)) {
-      s.g = 4;
-      s.w = block_waves(M);
-      s.ng = 16;
-    } else {
-      s.g = 1;
-      s.w = 16;
-      s.ng = 16;
-      while (1024 * s.ng < M) s.ng <<= 1;
-    }
-  } else if (M > 128 && M % 4 == 0 && is_aligned(in, 16) && is_aligned(out, 16)) {
-    s.family = kFamG4;
-    s.g = 4;
-    s.ng = pick_ng_g4(M);
-  } else if (M > 64 && M <= 128 && M % 2 == 0 && is_aligned(in, 8) && is_aligned(out, 8)) {
-    s.family = kFamSmall;
-    s.g = 2;
-    s.ng = 1;
-  } else {
-    s.family = kFamSmall;
-    s.g = 1;
-    s.ng = pick_ng_g1(M);
-  }
-  s.full = (M == s.capacity());
-  return s;
-}
-
-// The layout that is launched for a shape that classify() or classify_dense() returned (dtype, plain as
-// there; dense: the dense-output form).  g = 0: groups of mixed width, ng values per lane.
-inline Shape kernel_layout(Shape s, int M, int dtype, bool plain, bool dense) {
-  if (s.family == kFamStream) {
-    s.g = 4;  // 128-bit loads from any 4-byte boundary
-    return s;
-  }
-  if (s.family == kFamBlock) {
     s.w = block_waves(M);
     s.g = dtype == kF32 ? 4 : 8;
     s.ng = dtype != kF32 ? 8 : ((plain && !dense && M <= 64 * s.w * 4 * 12) ? 12 : 16);
   } else if (M > 512) {
+    s.family = dtype == kF32 ? kFamG4 : kFamH16;
     s.g = dtype == kF32 ? 4 : 8;
     s.ng = dtype == kF32 ? pick_ng_g4(M) : pick_ng_h8(M);
-    if (dtype == kF32) s.family = kFamG4;
   } else {
     // exactly as many values per lane as the row needs
     const int E = (M + 63) / 64;
-    if (dtype == kF32) s.family = kFamSmall;
+    s.family = dtype == kF32 ? kFamSmall : kFamH16;
     if (E == 1 || E == 2) {
       s.g = E;
       s.ng = 1;
@@ -222,34 +120,86 @@ inline Shape kernel_layout(Shape s, int M, int dtype, bool plain, bool dense) {
 
 // True when (g, ng, w) is a layout of its family's lists above.  `plain` and `dense` as above.
 inline bool instantiated(const Shape& s, int dtype, bool plain, bool dense) {
-  auto in_list = [](int n, int which) {
-    bool hit = false;
-#define X(v) hit = hit || (n == v);
-    if (which == 0) { RTOPK_NG_LIST_G4(X) }
-    if (which == 1) { RTOPK_NG_LIST_H8(X) }
-    if (which == 2) { RTOPK_NG_LIST_G1(X) }
-    if (which == 3) { RTOPK_NG_LIST_BLOCK_G1(X) }
+  bool small = false, g4 = false, h8 = false;
+#define X(G, NG) small = small || (s.g == G && s.ng == NG);
+  RTOPK_LAYOUT_LIST_SMALL(X)
 #undef X
-    return hit;
-  };
+#define X(n) g4 = g4 || (s.g == 4 && s.ng == n);
+  RTOPK_NG_LIST_G4(X)
+#undef X
+#define X(n) h8 = h8 || (s.g == 8 && s.ng == n);
+  RTOPK_NG_LIST_H8(X)
+#undef X
   switch (s.family) {
     case kFamSmall:
-      return s.w == 1 && ((s.g == 2 && s.ng == 1) || (s.g == 1 && in_list(s.ng, 2)));
+      return dtype == kF32 && s.w == 1 && small;
     case kFamG4:
-      return s.w == 1 && s.g == 4 && dtype == kF32 && in_list(s.ng, 0);
+      return dtype == kF32 && s.w == 1 && g4;
     case kFamH16:
-      if (s.w != 1 || dtype == kF32) return false;
-      return (s.g == 8 && in_list(s.ng, 1)) || ((s.g == 4 || s.g == 2) && s.ng == 1) || (s.g == 1 && in_list(s.ng, 2));
-    case kFamStream:
-      return dtype == kF32 && !dense && s.w == 16 && (s.g == 4 || s.g == 1);
+      return dtype != kF32 && !dense && s.w == 1 && (small || h8 || (s.g == 4 && s.ng == 1));
     case kFamBlock:
-      if (s.g == 1) return s.w == 16 && in_list(s.ng, 3);
       if (s.w != 4 && s.w != 8 && s.w != 16) return false;
       if (dtype != kF32) return !dense && s.g == 8 && s.ng == 8;
       return s.g == 4 && (s.ng == 16 || (s.ng == 12 && plain && !dense));
+    case kFamStream:
+      return dtype == kF32 && !dense && s.w == 16 && s.g == 4;
     default:
       return false;
   }
+}
+
+// ---- rows spread over several workgroups ---------------------------------------------------------
+// (rtopk_split_kernel.hpp)  Largest k that the lists of a workgroup of w wavefronts take (rtopk_filter.hpp).
+constexpr int filter_max_k(int w) { return w == 4 ? 256 : 512; }
+// Candidates that a segment's lists hold: with nothing to search there, more than the lists of a whole row.
+constexpr int segment_room(int w) { return w == 4 ? 768 : 1536; }
+constexpr int kMergeRegs = 16;                // candidates per lane of a merging wavefront
+constexpr int kMergeMost = 16 * 64 * kMergeRegs;  // candidates that 16 merging wavefronts hold
+constexpr int kSegmentLeast = 1 + 6 + 16;     // expected of a segment at k = 1, see split_of
+constexpr int kMaxSegments = kMergeMost / kSegmentLeast;
+constexpr int kSegmentHeadBytes = 16;
+constexpr int64_t kSplitScratch = 128ll << 20;
+
+// How a call is split: `segments` per row of `length` columns (the last may be shorter), lists of up to `cap` candidates,
+// workgroups of w wavefronts with ng groups per lane, merge_waves wavefronts per row to merge.  segments = 0: not at all.
+struct Split {
+  int segments, length, cap, w, ng, merge_waves;
+  int64_t rows;  // rows per pair of launches, so that the scratch memory stays bounded
+  int64_t bytes() const { return rows * segments * (kSegmentHeadBytes + (int64_t)cap * 8); }
+};
+
+inline Split split_of(int64_t N, int M, int k, int mode, int max_iter) {
+  Split s{};
+  // Up to 32768 columns one workgroup per row does as well.  Algorithm 2 with few steps: see launch_block.
+  if (M <= 32768 || N < 1 || k > filter_max_k(8) || (mode == kEarly && max_iter < 8)) return s;
+  // A segment's candidates: 1.2 to 1.35 k, and the spread of its wavefronts' floors, which weighs when k is small: `usual` is
+  // seldom exceeded on ordinary rows (k = 64: 176 at most, k = 512: 1012 in one segment of 200).  The merging workgroup's
+  // registers hold what its row can have, unless that is beyond 16 wavefronts: there they hold what is expected of the row.
+  int root = 1;
+  while (root * root < k) ++root;
+  const int usual = k + k / 3 + 10 * root + 24, expected = k + k / 3 + 6 * root + 16;
+  // Segments of 32768 columns, unless those would not give every compute unit two workgroups.
+  s.w = 8;
+  if (k <= filter_max_k(4) && N * ((M + 32767) / 32768) < 2 * 256) s.w = 4;
+  const int most = s.w * 4096;
+  s.segments = (M + most - 1) / most;
+  if ((int64_t)s.segments * expected > kMergeMost) {
+    s.segments = 0;
+    return s;
+  }
+  s.length = ((M + s.segments - 1) / s.segments + 3) & ~3;
+  s.ng = s.length <= s.w * 3072 ? 12 : 16;
+  const int64_t need = (int64_t)s.segments * usual, per_wave = 64 * kMergeRegs;
+  s.merge_waves = need <= 4 * per_wave ? 4 : (need <= 8 * per_wave ? 8 : 16);
+  const int share = (int)(s.merge_waves * per_wave / s.segments);
+  s.cap = share > usual ? share : usual;
+  if (s.cap > 4 * k + 640) s.cap = 4 * k + 640;
+  if (s.cap > segment_room(s.w)) s.cap = segment_room(s.w);
+  const int64_t per_row = s.segments * (kSegmentHeadBytes + (int64_t)s.cap * 8);
+  s.rows = kSplitScratch / per_row;
+  if (s.rows < 1) s.rows = 1;
+  if (s.rows > N) s.rows = N;
+  return s;
 }
 
 // Largest max_iter that is evaluated literally.  Each step of Algorithm 2 halves hi - lo, so on finite

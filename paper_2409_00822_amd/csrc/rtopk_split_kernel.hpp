@@ -32,53 +32,7 @@ struct SegmentHead {
   float floor;      // every key of the segment at or above it is listed
   float nlo, hi;    // negated minimum, and maximum, of the segment's keys
 };
-constexpr int kMergeRegs = 16;       // candidates per lane of a merging wavefront
-constexpr int kMaxSegments = 1024;   // 2^24 columns in segments of 16384
-
-// How a call is split: `segments` per row of `length` columns (the last may be shorter), lists of up to `cap` candidates,
-// workgroups of w wavefronts with ng groups per lane, merge_waves wavefronts per row to merge.  segments = 0: not at all.
-struct Split {
-  int segments, length, cap, w, ng, merge_waves;
-  int64_t rows;  // rows per pair of launches, so that the scratch memory stays bounded
-  int64_t bytes() const { return rows * segments * ((int64_t)sizeof(SegmentHead) + (int64_t)cap * 8); }
-};
-
-constexpr int64_t kSplitScratch = 128ll << 20;
-
-// Candidates that a segment's lists hold: with nothing to search there, more than the lists of a whole row.
-constexpr int segment_room(int W) { return W == 4 ? 768 : 1536; }
-
-inline Split split_of(int64_t N, int M, int k, int mode, int max_iter) {
-  Split s{};
-  // Up to 32768 columns one workgroup per row does as well.  Algorithm 2 with few steps: see launch_block.
-  if (M <= 32768 || N < 1 || k > filter_max_k<8>() || (mode == kEarly && max_iter < 8)) return s;
-  // Segments of 32768 columns, unless those would not give every compute unit two workgroups.
-  s.w = 8;
-  if (k <= filter_max_k<4>() && N * ((M + 32767) / 32768) < 2 * 256) s.w = 4;
-  const int most = s.w * 4096;
-  s.segments = (M + most - 1) / most;
-  s.length = ((M + s.segments - 1) / s.segments + 3) & ~3;
-  s.ng = s.length <= s.w * 3072 ? 12 : 16;
-  // A segment's candidates: 1.2 to 1.35 k, and the spread of its wavefronts' floors, which weighs when k is small: `usual` is
-  // seldom exceeded on ordinary rows (k = 64: 176 at most, k = 512: 1012 in one segment of 200).  The merging workgroup's
-  // registers hold what its row can have, unless that is beyond 16 wavefronts: there they hold what is expected of the row.
-  int root = 1;
-  while (root * root < k) ++root;
-  const int usual = k + k / 3 + 10 * root + 24, expected = k + k / 3 + 6 * root + 16;
-  const int64_t need = (int64_t)s.segments * usual, per_wave = kWave * kMergeRegs;
-  s.merge_waves = need <= 4 * per_wave ? 4 : (need <= 8 * per_wave ? 8 : 16);
-  if ((int64_t)s.segments * expected > 16 * per_wave) s.segments = 0;
-  if (s.segments == 0) return s;
-  const int share = (int)(s.merge_waves * per_wave / s.segments);
-  s.cap = share > usual ? share : usual;
-  if (s.cap > 4 * k + 640) s.cap = 4 * k + 640;
-  if (s.cap > segment_room(s.w)) s.cap = segment_room(s.w);
-  const int64_t per_row = s.segments * ((int64_t)sizeof(SegmentHead) + (int64_t)s.cap * 8);
-  s.rows = kSplitScratch / per_row;
-  if (s.rows < 1) s.rows = 1;
-  if (s.rows > N) s.rows = N;
-  return s;
-}
+static_assert(sizeof(SegmentHead) == kSegmentHeadBytes, "split_of counts it");
 
 template <int NG, int W, bool NEG>
 __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(5)))
@@ -116,7 +70,7 @@ __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(
                                                               none, ahead, none, x, end);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (it stores through inline asm)
     __syncthreads();
-    constexpr int kMost = (filter_max_k<W>() + W * kWave) / (W * kWave);  // pairs per thread, k + 1 in all
+    constexpr int kMost = (filter_max_k(W) + W * kWave) / (W * kWave);  // pairs per thread, k + 1 in all
     uint2 pair[kMost];
 #pragma unroll
     for (int i = 0; i < kMost; ++i) {

@@ -1,14 +1,16 @@
 // CPU-only sanitizer target (built and run by tests/test_sanitize_cpu.py with
-// -fsanitize=address,undefined): the oracle, the input generator and the library's host-side shape
-// classification, exercised in one process so that any out-of-bounds access, use of an uninitialised
+// -fsanitize=address,undefined): the oracle, the input generator and the library's host-side
+// choice of layouts and splits, exercised in one process so that any out-of-bounds access, use of an uninitialised
 // index, signed overflow or misaligned access in them aborts the test.
 //
 //   1. the Algorithm 2 hand traces of tests/golden/alg2_handtrace.txt against the sanitized oracle;
 //   2. brute force (a stable sort written out here) against the oracle's exact mode, Algorithm 1 at
 //      epsilon = 0 and the k-smallest variant on tiny tie-heavy rows from the sanitized generator;
-//   3. the shape classification for every row width 1..65536 (and a sample of the streamed widths up to
-//      2^24), every element type, both kernel variants and a set of pointer alignments: the layout
-//      returned must be compiled and must hold the row.
+//   3. the layout that is launched for every row width 1..65536 (and a sample of the streamed widths up to
+//      2^24), every element type, both kernel variants and the dense form: it must be compiled, hold the row and
+//      be no wider than its kernels take for granted;
+//   4. how rows are spread over several workgroups, over widths, k, row counts and modes: segments, lists and
+//      scratch memory within what the kernels and the merge hold.
 //
 // Usage: sanitize_main <path to alg2_handtrace.txt>.  Exit code 0 = all checks passed.
 #include <stdint.h>
@@ -150,60 +152,88 @@ static int run_brute_force() {
   return rows_checked;
 }
 
-// ---- 3. shape classification ---------------------------------------------------------------------
+// ---- 3. the layouts that are launched --------------------------------------------------------------
 static long run_shape_sweep() {
   long n = 0;
-  const uintptr_t base = 0x7f0000000000ull;  // never dereferenced: only its alignment is looked at
-  const uintptr_t offs[] = {0, 2, 4, 6, 8, 12, 16, 20, 24, 32};
   for (int M = 1; M <= rtopk::kMaxBlockM; ++M) {
     for (int dtype : {rtopk::kF32, rtopk::kF16, rtopk::kBF16}) {
-      const uintptr_t esz = dtype == rtopk::kF32 ? 4 : 2;
-      for (uintptr_t off : offs) {
-        if (off % esz) continue;  // the entry points reject pointers not aligned to the element size
-        for (int plain = 0; plain <= (dtype == rtopk::kF32 ? 1 : 0); ++plain) {
-          const rtopk::Shape s = rtopk::classify(M, dtype, plain != 0, base + off);
-          CHECK(rtopk::instantiated(s, dtype, plain != 0, false), "M=%d dtype=%d off=%d plain=%d: (%d,%d,%d) family %d not compiled",
-                M, dtype, (int)off, plain, s.g, s.ng, s.w, s.family);
+      for (int plain = 0; plain <= (dtype == rtopk::kF32 ? 1 : 0); ++plain) {
+        for (int dense = 0; dense <= (dtype == rtopk::kF32 ? 1 : 0); ++dense) {
+          const rtopk::Shape s = rtopk::kernel_layout(M, dtype, plain != 0, dense != 0);
+          CHECK(rtopk::instantiated(s, dtype, plain != 0, dense != 0), "M=%d dtype=%d plain=%d dense=%d: (%d,%d,%d) family %d not compiled",
+                M, dtype, plain, dense, s.g, s.ng, s.w, s.family);
           CHECK(s.capacity() >= M, "M=%d: layout (%d,%d,%d) holds only %d", M, s.g, s.ng, s.w, s.capacity());
-          CHECK(s.full == (s.capacity() == M), "M=%d: full flag", M);
-          CHECK(M % s.g == 0 && (base + off) % (esz * (uintptr_t)s.g) == 0, "M=%d off=%d: load width %d not usable", M,
-                (int)off, s.g);
+          CHECK(s.full == (s.g != 0 && s.capacity() == M), "M=%d: full flag", M);
           CHECK((s.w == 1) == (M <= rtopk::kMaxWaveM), "M=%d: wavefronts per row %d", M, s.w);
-          CHECK(s.w == 1 ? s.g * s.ng <= 128 : s.g * s.ng <= 64, "M=%d: %d values per lane", M, s.g * s.ng);
+          CHECK(s.w == 1 ? s.values() <= 128 : s.values() <= 64, "M=%d: %d values per lane", M, s.values());
+          // the vector loads stay inside the row, and the groups that the kernels take for whole are: up to 512
+          // columns the row fills all but the last value of a lane, beyond them no shorter layout of the list holds it
+          CHECK(M >= (s.g == 0 ? 4 : s.g), "M=%d: narrower than a load of %d", M, s.g);
+          if (M <= 512) {
+            CHECK(s.values() == (M + 63) / 64, "M=%d: %d values per lane", M, s.values());
+          } else if (s.w == 1) {
+            rtopk::Shape less = s;
+            while (--less.ng > 0 && !rtopk::instantiated(less, dtype, plain != 0, dense != 0)) {
+            }
+            CHECK(less.ng == 0 || less.capacity() < M, "M=%d: (%d,%d) would do", M, less.g, less.ng);
+          } else {
+            CHECK(64 * s.w * s.values() / 2 < M, "M=%d: (%d,%d,%d) is half empty", M, s.g, s.ng, s.w);
+          }
           ++n;
         }
       }
     }
-    for (uintptr_t oi : {0, 4, 8, 16})
-      for (uintptr_t oo : {0, 4, 8, 16}) {
-        const rtopk::Shape s = rtopk::classify_dense(M, base + oi, base + 0x100000 + oo);
-        CHECK(rtopk::instantiated(s, rtopk::kF32, false, true), "dense M=%d: (%d,%d,%d) not compiled", M, s.g, s.ng, s.w);
-        CHECK(s.capacity() >= M && s.full == (s.capacity() == M), "dense M=%d capacity", M);
-        CHECK(M % s.g == 0 && (base + oi) % (4u * (uintptr_t)s.g) == 0 && (base + oo) % (4u * (uintptr_t)s.g) == 0,
-              "dense M=%d: load width %d not usable", M, s.g);
-        ++n;
-      }
   }
-  // beyond the widest row a workgroup holds: fp32 rows are streamed, with 128-bit loads where they can be
+  // beyond the widest row a workgroup holds: fp32 rows are streamed
   for (int64_t M = rtopk::kMaxBlockM + 1; M <= rtopk::kMaxM; M += (M < 70000 ? 1 : 9973)) {
-    for (uintptr_t off : offs) {
-      if (off % 4) continue;
-      for (int plain = 0; plain <= 1; ++plain) {
-        const rtopk::Shape s = rtopk::classify((int)M, rtopk::kF32, plain != 0, base + off);
-        CHECK(s.family == rtopk::kFamStream && rtopk::instantiated(s, rtopk::kF32, plain != 0, false), "M=%ld: not streamed", (long)M);
-        CHECK((s.g == 4) == (M % 4 == 0 && (base + off) % 16 == 0) && (s.g == 4 || s.g == 1), "M=%ld off=%d: load width %d", (long)M,
-              (int)off, s.g);
-        ++n;
+    for (int plain = 0; plain <= 1; ++plain) {
+      const rtopk::Shape s = rtopk::kernel_layout((int)M, rtopk::kF32, plain != 0, false);
+      CHECK(s.family == rtopk::kFamStream && rtopk::instantiated(s, rtopk::kF32, plain != 0, false), "M=%ld: not streamed", (long)M);
+      ++n;
+    }
+  }
+  return n;
+}
+
+// ---- 4. rows spread over several workgroups ---------------------------------------------------------
+static long run_split_sweep() {
+  long n = 0;
+  for (int64_t M = 32760; M <= rtopk::kMaxM; M += (M < 33000 || (M > 65500 && M < 65600)) ? 1 : M / 61 + 1) {
+    for (int k : {1, 2, 7, 33, 64, 100, 200, 255, 256, 257, 400, 511, 512, 513, 1000}) {
+      for (int64_t N : {(int64_t)1, (int64_t)2, (int64_t)15, (int64_t)16, (int64_t)64, (int64_t)255, (int64_t)256, (int64_t)1000, (int64_t)100000}) {
+        for (int mode : {(int)rtopk::kExact, (int)rtopk::kEarly, (int)rtopk::kEps}) {
+          const rtopk::Split s = rtopk::split_of(N, (int)M, k, mode, 8);
+          ++n;
+          if (s.segments == 0) continue;
+          CHECK(M > 32768 && k <= 512, "M=%ld k=%d is split", (long)M, k);
+          CHECK(s.segments >= 2 && s.segments <= rtopk::kMaxSegments, "M=%ld k=%d: %d segments", (long)M, k, s.segments);
+          CHECK(s.w == 4 || s.w == 8, "M=%ld: %d wavefronts", (long)M, s.w);
+          CHECK(k <= rtopk::filter_max_k(s.w), "M=%ld k=%d: lists of %d wavefronts", (long)M, k, s.w);
+          CHECK(s.length % 4 == 0 && s.length <= 64 * s.w * 4 * s.ng && (s.ng == 12 || s.ng == 16), "M=%ld: length %d", (long)M, s.length);
+          const int64_t last = M - (int64_t)(s.segments - 1) * s.length;
+          CHECK(last > 0 && last <= s.length, "M=%ld: last segment of %ld", (long)M, (long)last);
+          // every wavefront has group maxima (of 16 values per lane) for its share of the floor
+          CHECK(last >= 64 * s.w * 4 * 4 + 64 * s.w * 4, "M=%ld: last segment of %ld in %d wavefronts", (long)M, (long)last, s.w);
+          CHECK(s.cap > k && s.cap <= rtopk::segment_room(s.w), "M=%ld k=%d: lists of %d", (long)M, k, s.cap);
+          CHECK(s.merge_waves == 4 || s.merge_waves == 8 || s.merge_waves == 16, "M=%ld: %d merging", (long)M, s.merge_waves);
+          if (s.merge_waves < 16)
+            CHECK((int64_t)s.segments * s.cap <= (int64_t)s.merge_waves * 64 * rtopk::kMergeRegs, "M=%ld k=%d: more than the merge holds", (long)M, k);
+          CHECK(s.rows >= 1 && s.rows <= N && s.rows * s.segments <= 0x7fffffff, "M=%ld N=%ld: %ld rows", (long)M, (long)N, (long)s.rows);
+          CHECK(s.rows == 1 || s.bytes() <= rtopk::kSplitScratch, "M=%ld N=%ld: %ld bytes", (long)M, (long)N, (long)s.bytes());
+        }
       }
     }
   }
+  return n;
+}
+
+static void run_overlaps() {
   // range overlap helper
   CHECK(!rtopk::ranges_overlap(100, 10, 110, 10), "adjacent ranges do not overlap");
   CHECK(rtopk::ranges_overlap(100, 11, 110, 10), "one shared byte");
   CHECK(rtopk::ranges_overlap(100, 50, 120, 5), "containment");
   CHECK(!rtopk::ranges_overlap(100, 0, 100, 10), "empty range");
   CHECK(!rtopk::ranges_overlap(~(uintptr_t)0 - 7, 8, 0, 8), "top of the address space");
-  return n;
 }
 
 int main(int argc, char** argv) {
@@ -214,7 +244,8 @@ int main(int argc, char** argv) {
   const int traces = run_hand_traces(argv[1]);
   if (traces < 0) return 2;
   const int rows = run_brute_force();
-  const long shapes = run_shape_sweep();
-  std::printf("hand traces %d, brute-force rows %d, shapes %ld, failures %d\n", traces, rows, shapes, g_failures);
+  const long shapes = run_shape_sweep(), splits = run_split_sweep();
+  run_overlaps();
+  std::printf("hand traces %d, brute-force rows %d, shapes %ld, splits %ld, failures %d\n", traces, rows, shapes, splits, g_failures);
   return g_failures == 0 ? 0 : 1;
 }
