@@ -178,9 +178,12 @@ inline Split split_of(int64_t N, int M, int k, int mode, int max_iter) {
   int root = 1;
   while (root * root < k) ++root;
   const int usual = k + k / 3 + 10 * root + 24, expected = k + k / 3 + 6 * root + 16;
-  // Segments of 32768 columns, unless those would not give every compute unit two workgroups.
+  // Segments of 32768 columns, unless those would not give every compute unit two workgroups (and those of 16384, which
+  // have twice the candidates in all, still fit the merge).
   s.w = 8;
-  if (k <= filter_max_k(4) && N * ((M + 32767) / 32768) < 2 * 256) s.w = 4;
+  if (k <= filter_max_k(4) && N * ((M + 32767) / 32768) < 2 * 256 &&
+      (int64_t)((M + 16383) / 16384) * expected <= kMergeMost)
+    s.w = 4;
   const int most = s.w * 4096;
   s.segments = (M + most - 1) / most;
   if ((int64_t)s.segments * expected > kMergeMost) {

@@ -204,7 +204,10 @@ static long run_split_sweep() {
         for (int mode : {(int)rtopk::kExact, (int)rtopk::kEarly, (int)rtopk::kEps}) {
           const rtopk::Split s = rtopk::split_of(N, (int)M, k, mode, 8);
           ++n;
-          if (s.segments == 0) continue;
+          if (s.segments == 0) {
+            CHECK(rtopk::split_of(1 << 20, (int)M, k, mode, 8).segments == 0, "M=%ld k=%d: split for many rows but not for %ld", (long)M, k, (long)N);
+            continue;
+          }
           CHECK(M > 32768 && k <= 512, "M=%ld k=%d is split", (long)M, k);
           CHECK(s.segments >= 2 && s.segments <= rtopk::kMaxSegments, "M=%ld k=%d: %d segments", (long)M, k, s.segments);
           CHECK(s.w == 4 || s.w == 8, "M=%ld: %d wavefronts", (long)M, s.w);

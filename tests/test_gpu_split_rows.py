@@ -125,3 +125,15 @@ def test_threads_and_streams_share_the_allocator():
         want = oracle.topk_exact(xs[t], 20 + 7 * t)
         for j, pair in enumerate(got[t]):
             _same(pair, want, f"thread {t} call {j}")
+
+
+def test_few_very_wide_rows_are_split_into_the_longer_segments():
+    R = _gpu()
+    lib = R.load_library()
+    lib.rtopk_workspace_bytes.restype = ctypes.c_int64
+    lib.rtopk_workspace_bytes.argtypes = [ctypes.c_int64] + [ctypes.c_int32] * 4
+    assert lib.rtopk_workspace_bytes(2, 1 << 20, 200, 1, 0) > 0  # twice the candidates in the shorter ones would not fit
+    x = _rows(1 << 20, 6300)[:4]
+    xd = torch.from_numpy(x).cuda()
+    _same(R.rtopk_rowwise_exact(xd, 200), oracle.topk_exact(x, 200), "exact")
+    _same(R.rtopk_rowwise(xd, 200, 9), oracle.topk_earlystop(x, 200, 9), "early")
