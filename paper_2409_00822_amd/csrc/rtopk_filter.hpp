@@ -519,11 +519,17 @@ constexpr int wave_filter_small_k(int E) { return 35 * wave_groups(E, false); }
 constexpr int wave_filter_max_k(int E, int R, int mode, bool dense = false) {
   if (R > 1 || E < (mode == kEps ? 24 : 16)) return 0;
   if (dense) return E <= 24 ? 100 : (E <= 64 ? 175 : 48);
-  return E <= 24 ? 140 : (E == 32 ? 175 : 245);
+  return E <= 24 ? 140 : (E == 32 ? 175 : 280);
 }
-// Algorithm 2 with fewer steps than this searches the full width: the last threshold of few steps lies below the floor, and
-// each step saved is worth the less the narrower the row (1280 columns, bfloat16, five steps, k = 140: 38 -> 43 us, 100 38 -> 37).
-constexpr int wave_filter_min_steps(int E, int k) { return E <= 32 && k > 100 ? 6 : 5; }
+// Whether a call takes them (uniform over the launch).  Above k = 245 only where k is at most 68 % of the row's group maxima: a
+// row that leaves its layout a quarter empty has too few (k = 280: 4096 columns 33 -> 28 us, 3584 35 -> 34, 3074 40 -> 47).
+// Algorithm 2 with few steps searches the full width: the last threshold of few steps lies below the floor, and each step
+// saved is worth the less the narrower the row (1280 columns, bfloat16, five steps, k = 140: 38 -> 43 us, 100 38 -> 37).
+__host__ __device__ constexpr bool wave_filter_takes(int E, int R, int mode, bool dense, int M, int k, int max_iter) {
+  const int least = k > 245 ? 8 : (E <= 32 && k > 100 ? 6 : 5);
+  return k <= wave_filter_max_k(E, R, mode, dense) && (k <= 245 || 100 * k * (E / wave_groups(E, true)) <= 68 * M) &&
+         (mode != kEarly || max_iter >= least);
+}
 // Quads, and singles, that the lists of a row hold, and the pairs' worth of LDS they take.
 __host__ __device__ constexpr int wave_filter_room(int k) { return (k + k / 2 + 48 + 63) & ~63; }
 __host__ __device__ constexpr int wave_filter_pairs(int k) { return wave_filter_room(k) * 20 / 8; }

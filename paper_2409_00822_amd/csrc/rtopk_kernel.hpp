@@ -817,9 +817,9 @@ __host__ __device__ constexpr int staged_pairs(int E, int R, int k) {
   const int band = band_scratch_floats(E) / 2;
   return ((R * k > band ? R * k : band) + 1) & ~1;
 }
-__host__ __device__ constexpr int wave_pairs(int E, int R, int k, int mode, int max_iter) {
-  const int staged = staged_pairs(E, R, k);
-  if (k > wave_filter_max_k(E, R, mode) || (mode == kEarly && max_iter < wave_filter_min_steps(E, k))) return staged;
+__host__ __device__ constexpr int wave_pairs(int E, int R, int mode, bool dense, int M, int k, int max_iter) {
+  const int staged = staged_pairs(E, R, dense ? 1 : k);
+  if (!wave_filter_takes(E, R, mode, dense, M, k, max_iter)) return staged;
   const int lists = wave_filter_pairs(k);
   return staged > lists ? staged : lists;
 }
@@ -918,7 +918,7 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
   bool bounds_known = false;  // Algorithm 1 with precision: lo, hi and the iteration count are those of its end
   int known_iterations = 0;
   if constexpr (wave_filter_max_k(E, R, MODE) > 0) {
-    if (k <= wave_filter_max_k(E, R, MODE, DENSE) && (MODE != kEarly || max_iter >= wave_filter_min_steps(E, k))) {  // uniform over the launch
+    if (wave_filter_takes(E, R, MODE, DENSE, M, k, max_iter)) {
       float thi, tlo;
       int split, iterations = 0;
       const float eps = MODE == kEps ? eps_rel * __builtin_fabsf(hi) : 0.0f;
@@ -1263,7 +1263,7 @@ __global__ void __launch_bounds__(256)
   if (r0 >= N) return;
   int nrows = rows_left(N - r0, R);
   static_assert(!narrows(E, MODE) || R == 1, "the band scratch reuses the staging area of the wavefront's only row");
-  uint2* stage = stage_all + (size_t)wave * wave_pairs(E, R, k, MODE, max_iter);
+  uint2* stage = stage_all + (size_t)wave * wave_pairs(E, R, MODE, false, M, k, max_iter);
 
   // Loading stage: all R rows' loads are issued before any is consumed.
   float x[R][E];
@@ -1400,7 +1400,7 @@ __global__ void __launch_bounds__(256)
   const int64_t r0 = ((int64_t)blockIdx.x * waves_per_block + wave) * R;
   if (r0 >= N) return;
   int nrows = rows_left(N - r0, R);
-  uint2* scratch = band_scratch + (size_t)wave * wave_pairs(E, R, k <= wave_filter_max_k(E, R, MODE, true) ? k : 1, MODE, max_iter);
+  uint2* scratch = band_scratch + (size_t)wave * wave_pairs(E, R, MODE, true, M, k, max_iter);
 
   float x[R][E];
 #pragma unroll
@@ -1441,7 +1441,7 @@ hipError_t launch_dense(const LaunchArgs& a) {
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   if (a.M < Layout<G, NG>::MIN_M || a.M > 64 * Layout<G, NG>::E) return hipErrorInvalidValue;
   constexpr int E = Layout<G, NG>::E;
-  const size_t lds = E < 12 ? 0 : (size_t)waves * wave_pairs(E, R, a.k <= wave_filter_max_k(E, R, MODE, true) ? a.k : 1, MODE, a.max_iter) * sizeof(uint2);
+  const size_t lds = E < 12 ? 0 : (size_t)waves * wave_pairs(E, R, MODE, true, a.M, a.k, a.max_iter) * sizeof(uint2);
   return launch_kernel(rtopk_dense_kernel<G, NG, R, FULL, MODE>, dim3((unsigned)blocks), dim3(waves * kWave), lds,
                        a.stream, static_cast<const float*>(a.in), a.N, a.M, a.k, a.max_iter,
                        static_cast<float*>(a.out_vals));
@@ -1454,7 +1454,7 @@ hipError_t launch(const LaunchArgs& a) {
   using L = Layout<G, NG>;
   if (a.M < L::MIN_M || a.M > 64 * L::E) return hipErrorInvalidValue;
   // LDS per wavefront: at most 64 KiB per block
-  size_t per_wave = (size_t)wave_pairs(L::E, R, a.k, MODE, a.max_iter) * sizeof(uint2);
+  size_t per_wave = (size_t)wave_pairs(L::E, R, MODE, false, a.M, a.k, a.max_iter) * sizeof(uint2);
   // one wavefront per workgroup, except where a wavefront stages 8 KiB or more of pairs: there four
   // per workgroup measured 7 % faster (2^20 x 256, k = 128: 387 -> 360 us), while at 4 KiB and below
   // one per workgroup is the faster by 3-11 %

@@ -17,8 +17,8 @@ torch = pytest.importorskip("torch")
 
 
 @pytest.mark.parametrize("M,limits", [(769, (64,)), (1024, (64,)), (1025, (100, 140)), (1536, (100, 140)), (1537, (100, 175)),
-                                      (2048, (100, 175)), (2049, (175, 245)), (3072, (175, 245)), (3073, (175, 245)),
-                                      (4097, (48, 245)), (6145, (48, 245)), (8192, (48, 245))])
+                                      (2048, (100, 175)), (2049, (175, 245, 280)), (3072, (175, 245, 280)), (3073, (175, 245)),
+                                      (3200, (245, 272, 280)), (3840, (245, 280)), (4097, (48, 245)), (6145, (48, 245)), (8192, (48, 245, 280))])
 def test_fp32_rows_around_the_limits(M, limits):
     R = _gpu()
     x = workloads.normal(9, M, seed=9700 + M)
@@ -27,7 +27,7 @@ def test_fp32_rows_around_the_limits(M, limits):
         tag = f"M={M} k={k}"
         _same(R.rtopk_rowwise_exact(xd, k), oracle.topk_exact(x, k), tag + " exact")
         _same(R.rtopk_rowwise_exact_smallest(xd, k), oracle.topk_exact_smallest(x, k), tag + " smallest")
-        for mi in (0, 4, 5, 6, 7, 16):
+        for mi in (0, 4, 5, 6, 7, 8, 16):
             _same(R.rtopk_rowwise(xd, k, mi), oracle.topk_earlystop(x, k, mi), tag + f" early {mi}")
         ev, ei, et = oracle.alg1(x, k, eps_rel=1e-4)
         got = R.rtopk_rowwise_eps(xd, k, 1e-4, want_iters=True)
