@@ -58,6 +58,8 @@ def load_library() -> ctypes.CDLL:
                      "rtopk_maxk_backward_gather_u8"):
             getattr(lib, name).argtypes = [vp, vp, i64, i32, i32, vp, vp]
             getattr(lib, name).restype = ctypes.c_int
+        lib.rtopk_workspace_bytes.argtypes = [i64, i32, i32, i32, i32]
+        lib.rtopk_workspace_bytes.restype = i64
         lib.rtopk_status_string.argtypes = [ctypes.c_int]
         lib.rtopk_status_string.restype = ctypes.c_char_p
         _lib = lib
