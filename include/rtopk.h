@@ -11,8 +11,9 @@
  *    frees, copies to the host or synchronises.  Work is enqueued on `stream` (a hipStream_t passed
  *    as void*; NULL means the default stream) and the call returns at once.
  *  - `in`       : [N][M] fp32, dense, row-major, row stride M, read-only, 4-byte aligned.
- *                 Any M and any such alignment take vector loads; the outputs leave in 128-bit stores where
- *                 k is a multiple of 4, and for any k when they are 16-byte aligned.
+ *                 Any M and any such alignment take vector loads.  Where the outputs are 16-byte aligned (8-byte for
+ *                 16-bit values, 4-byte for byte-wide columns) rows of up to 8192 columns leave in whole groups of four
+ *                 pairs, whatever k is; otherwise, and beyond 8192 columns, every pair is stored by itself.
  *  - `out_vals` : [N][k] fp32, row-major.  out_vals[r][j] is the bit pattern of in[r][out_idx[r][j]].
  *  - `out_idx`  : [N][k] column indices, 0-based, strictly ascending within a row
  *                 (int32_t, or uint8_t in the *_u8 variants, which require M <= 256: this is the
@@ -25,7 +26,8 @@
  *    still terminates and writes only inside the output buffers.
  *  - Return value: RTOPK_OK (0) when the work was enqueued (or N == 0: nothing to do), otherwise a
  *    negative RTOPK_ERR_* code; every argument check happens on the host before any launch, and on
- *    error nothing was enqueued.  A pending error of the caller's own earlier HIP calls is neither
+ *    error nothing was enqueued (but for RTOPK_ERR_LAUNCH from rtopk_select_ws, which makes several launches: the
+ *    earlier ones may then run, and the outputs are to be taken as unwritten).  A pending error of the caller's own earlier HIP calls is neither
  *    reported nor cleared.  Faults of the asynchronous work surface at the caller's next
  *    synchronisation, as with any HIP launch.
  *  - Limits: 1 <= k <= M <= rtopk_max_m() = 2^24 for fp32 rows with int32 columns (65536 for rows stored

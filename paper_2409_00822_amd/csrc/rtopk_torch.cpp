@@ -1,7 +1,8 @@
 // CPython module between the Python entry points and the C ABI: the checks, the output allocation, the current
 // stream and the call, for the arguments that a program passes in the usual case.  Anything else -- a wrong type, a
-// wrong shape, a status other than RTOPK_OK -- makes the functions return None with nothing enqueued, and the Python
-// code behind the same entry point then raises what it always raised.
+// wrong shape, a status other than RTOPK_OK -- makes the functions return None, and the Python code behind the same entry
+// point then raises what it always raised (or makes the call without scratch memory, whose launch writes every output, should
+// a launch of a split call have been refused).
 //
 // Why native: at the sizes of a sampled mini-batch the kernel takes 3 us and the Python form of these steps (ten
 // attribute reads, two torch.empty, a stream lookup, a ctypes call of eight arguments) took 10 us.

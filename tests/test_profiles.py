@@ -22,6 +22,13 @@ def test_the_headline_profile_exists_and_is_what_bench_reads():
     assert traffic is not None and 0.98 * algo <= traffic <= 1.05 * algo
 
 
+def test_every_profile_is_of_a_kernel_that_bench_can_name():
+    # (which of them a workload gets: rtopk_workspace_bytes for split rows, the list limits for one workgroup per row)
+    for path in FILES:
+        kernel = re.match(r"(rtopk_(?:wave|dense|block|filter|segment|stream)_kernel|maxk_(?:scatter|gather)_(?:rows|block)_kernel)_", os.path.basename(path))
+        assert kernel and kernel.group(1).replace("maxk_scatter_", "").replace("maxk_gather_", "") in open(os.path.join(ROOT, "bench.py")).read(), path
+
+
 @pytest.mark.parametrize("path", FILES, ids=[os.path.basename(f) for f in FILES])
 def test_profile_summary_parses_and_is_self_consistent(path):
     text = open(path).read()
