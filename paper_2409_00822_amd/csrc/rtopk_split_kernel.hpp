@@ -265,7 +265,7 @@ __device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ i
       if ((a && posA < (uint32_t)limA) || (b && posB < (uint32_t)limB)) {
         const uint32_t pos = (posA < (uint32_t)limA ? posA : (uint32_t)limA) + (posB < (uint32_t)limB ? posB : (uint32_t)limB);
         ov[pos] = keyof<NEG>(key[i]);
-        oi[pos] = (int32_t)col[i];
+        oi[pos] = (int32_t)min(col[i], (uint32_t)(M - 1));  // (NaN keys can leave list entries unwritten)
       }
       posA0 += (uint32_t)__builtin_popcountll(mA);
       posB0 += (uint32_t)__builtin_popcountll(mB);

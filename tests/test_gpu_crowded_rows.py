@@ -75,3 +75,22 @@ def test_what_they_cost(N, M, k, kind):
         y = torch.randint(0, 64, (N, M), device="cuda").float()
     plain, crowded = _time(lambda: R.rtopk_rowwise_exact(x, k)), _time(lambda: R.rtopk_rowwise_exact(y, k))
     assert crowded < 4.0 * plain, f"{crowded:.1f} us against {plain:.1f}"
+
+
+def test_columns_stay_inside_the_row_whatever_the_values_are():
+    # the selection is unspecified with NaN or infinities, but a column that was never listed must not come out
+    R = _gpu()
+    M, k = 40000, 50
+    g = np.random.Generator(np.random.Philox(9600))
+    x = np.full((8, M), np.nan, dtype=np.float32)
+    for r in range(8):
+        at = g.integers(0, M, 40 * (r + 1))
+        x[r, at] = -np.inf if r % 2 == 0 else g.standard_normal(at.size).astype(np.float32)
+    x[4:, ::97] = np.inf
+    xd = torch.from_numpy(x).cuda()
+    for fn in (lambda v, i: R.rtopk_rowwise_exact(xd, k, v, i), lambda v, i: R.rtopk_rowwise(xd, k, 9, v, i),
+               lambda v, i: R.rtopk_rowwise_exact_smallest(xd, k, v, i), lambda v, i: R.rtopk_rowwise_eps(xd, k, 1e-3, v, i)):
+        torch.full((1 << 20,), 0x7F7F7F7F, dtype=torch.int32, device="cuda")  # what the scratch memory may hold
+        v, i = torch.zeros(8, k, device="cuda"), torch.zeros(8, k, dtype=torch.int32, device="cuda")
+        fn(v, i)
+        assert int(i.min()) >= 0 and int(i.max()) < M
