@@ -1,5 +1,6 @@
 // Selection of a wide row from the few elements that can matter (gfx950).  Included by rtopk_kernel.hpp, inside
-// namespace rtopk, behind the cross-lane helpers; used by rtopk_block_kernel.hpp.
+// namespace rtopk, behind the cross-lane helpers; used by rtopk_kernel.hpp, rtopk_block_kernel.hpp and
+// rtopk_split_kernel.hpp.
 //
 // Algorithms 1 and 2 (RTop-K, arXiv 2409.00822, Section 3.1) look at a count only to compare it with k.  For any
 // floor T0 with more than k keys at or above it, the count at a threshold t <= T0 is therefore known to exceed k,
@@ -16,8 +17,8 @@
 //   4. one wavefront runs the search on the singles, 64 to a register, with no barrier;
 //   5. the winners' places in column order come from a bitmap over the row's columns: prefix popcounts.
 // Thresholds, branches, exit iteration and result are those of the search over the whole row.  What a list does not
-// hold (a row whose values crowd, k too large for the lists, a last threshold below the floor) is left to the
-// caller's full-width search.
+// hold (a row whose values crowd, k too large for the lists) is left to the caller's full-width search; where a search ends
+// below the floor its bounds are the caller's, who selects by them.
 //
 // What bounds it: a row's elements are touched twice (maxima, then quad maxima against the floor; 5 vector
 // instructions per four elements in all, and 8 plus two LDS writes per quad to store it) where the search over the
