@@ -418,7 +418,7 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
     if constexpr (MODE == kExact) {
       float seen = lo;
       for (;;) {
-        thres = midpoint_exact<DT>(lo, hi);
+        thres = midpoint_of_row<DT>(lo, hi);
         if (!(thres < seen || thres > seen)) break;
         seen = thres;
         int cnt = count(thres);
@@ -431,7 +431,7 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
           narrow = true;
           break;
         }
-        thres = midpoint_exact<DT>(lo, hi);
+        thres = midpoint_of_row<DT>(lo, hi);
         cnt = count(thres);
         if (cnt == k) {
           hit = true;

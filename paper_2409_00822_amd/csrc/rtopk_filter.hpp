@@ -80,7 +80,7 @@ template <int J>
 __device__ __forceinline__ float floor_of_maxima(const float (&gm)[J], int need, float low, float high, float& above,
                                                  int halvings = 0) {
   const int enough = need + (need >> 3) + 1;
-  const float largest = high;
+  const float largest = high, least = low;
   auto at_or_above = [&](float t) -> int {
     int cnt = 0;
 #pragma unroll
@@ -96,7 +96,7 @@ __device__ __forceinline__ float floor_of_maxima(const float (&gm)[J], int need,
     high = enough_above ? high : mid;
     if ((uint32_t)(cnt - need) <= (uint32_t)(enough - need)) {
       above = high;
-      return low;
+      return low < least ? least : low;  // (the sum of two bounds near the type's lowest value is -inf, which padding reaches too)
     }
   }
   // (A floor that is itself one of the keys leaves no room below the k-th for a precision-bounded search to end in, so
@@ -137,7 +137,7 @@ __device__ __forceinline__ float floor_of_maxima(const float (&gm)[J], int need,
     try_bound(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(pick), (__builtin_ctzll(turned) + turn) & 63)));
   }
   above = high;
-  return low;
+  return low < least ? least : low;
 }
 
 // The steps of Algorithm 2, or of Algorithm 1 with precision eps, whose thresholds lie at or below the floor T0: each

@@ -580,6 +580,13 @@ __device__ __forceinline__ float midpoint_exact(float lo, float hi) {
     return __uint_as_float(__float_as_uint(t) & (DT == kBF16 ? 0xffff0000u : 0xffffe000u));
   }
 }
+// The same, never below lo, for searches over a whole row: the sum of two bounds near the type's lowest value is -inf, a
+// threshold that columns past the row's end would reach too.
+template <int DT>
+__device__ __forceinline__ float midpoint_of_row(float lo, float hi) {
+  const float t = midpoint_exact<DT>(lo, hi);
+  return t < lo ? lo : t;
+}
 
 // In the lanes whose bit is set in `mask` (a subset of the active lanes): LDS[addr] = v.
 __device__ __forceinline__ void lds_store_masked(uint64_t mask, uint32_t addr, float v) {
@@ -978,7 +985,7 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
       bool narrow = false;
       float seen = lo;
       for (;;) {
-        thres = midpoint_exact<DT>(lo, hi);
+        thres = midpoint_of_row<DT>(lo, hi);
         if (!(thres < seen || thres > seen)) break;
         seen = thres;
         int cnt = count(thres);
@@ -996,7 +1003,7 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
             break;
           }
         }
-        thres = midpoint_exact<DT>(lo, hi);
+        thres = midpoint_of_row<DT>(lo, hi);
         cnt = count(thres);
         if (cnt == k) {
           hit = true;
