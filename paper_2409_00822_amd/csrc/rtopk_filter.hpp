@@ -172,6 +172,107 @@ __device__ __forceinline__ float grid_floor(float t) {
   }
 }
 
+// ---- the k-th of a list by bins ---------------------------------------------------------------------------
+//
+// Exact mode does not depend on the thresholds, so its search on a list needs none: the keys are counted into 256 equal parts of
+// [floor, largest key], one prefix sum over the parts finds the one with the k-th key, and the few members of that part are
+// ranked against each other, ties by column.  That replaces 9 to 14 dependent steps of a compare, a popcount and an add per
+// register.  The part of a key is a monotonic function of it, so rounding moves no key past another.  On the lists of a
+// workgroup or a wavefront: 256 x 16384, k = 64 9.4 -> 8.2 us, bfloat16 8.1 -> 7.5; 256 x 32000, k = 64 12.0 -> 11.1; 2097 x 32000
+// 48.4 -> 47.2, bfloat16 40.2 -> 37.9; 256 x 4096 6.8 -> 6.3, but 65536 x 4096, bound by its loads, 187 -> 186.  (16-bit rows of
+// one wavefront search by steps: few values, so few steps and many members of a bin; 4096 columns 28.4 -> 28.9 with bins.)
+constexpr int kBins = 256;  // part 0 holds the largest keys
+__device__ __forceinline__ void clear_bins(uint32_t* count, int lane) {  // (16-byte aligned)
+  reinterpret_cast<uint4*>(count)[lane] = make_uint4(0u, 0u, 0u, 0u);
+}
+__device__ __forceinline__ float bins_scale(float low, float high) { return (float)kBins * __builtin_amdgcn_rcpf(high - low); }
+// (A NaN or a negative product converts to 0, one too large saturates.)
+__device__ __forceinline__ int bin_of(float key, float high, float scale) {
+  uint32_t b;
+  asm("v_cvt_u32_f32 %0, %1" : "=v"(b) : "v"((high - key) * scale));
+  return (int)min(b, (uint32_t)kBins - 1u);
+}
+// The part that holds the k-th largest of the counted keys, -1 if there is none; `above`: keys in higher parts, in_bin: keys
+// in it.  Called by whole wavefronts, behind a barrier (for one wavefront a fence).
+__device__ __forceinline__ int find_bin(const uint32_t* count, int lane, int k, int& above, int& in_bin) {
+  const uint4 c = reinterpret_cast<const uint4*>(count)[lane];
+  const uint32_t a1 = c.x, a2 = a1 + c.y, a3 = a2 + c.z, sum = a3 + c.w;
+  const uint32_t incl = wave_inclusive_scan_dpp(sum), before = incl - sum;
+  const uint64_t owner = __builtin_amdgcn_ballot_w64(before < (uint32_t)k && (uint32_t)k <= incl);
+  if (owner == 0) return -1;
+  const int l = __builtin_ctzll(owner);
+  const uint32_t want = (uint32_t)k - before;  // 1 .. sum in the owner
+  const uint32_t part = (want > a1 ? 1u : 0u) + (want > a2 ? 1u : 0u) + (want > a3 ? 1u : 0u);
+  const uint32_t first = want > a3 ? a3 : (want > a2 ? a2 : (want > a1 ? a1 : 0u));
+  const uint32_t held = want > a3 ? c.w : (want > a2 ? c.z : (want > a1 ? c.y : c.x));
+  above = __builtin_amdgcn_readlane((int)(before + first), l);
+  in_bin = __builtin_amdgcn_readlane((int)held, l);
+  return 4 * l + __builtin_amdgcn_readlane((int)part, l);
+}
+// The want-th (1-based) of the n members (key bits, column), at most 64 in any order, by key, then column: its key t and its
+// column; cut: members equal to t rank behind it.  Returns false where there is no such member (NaN keys).
+__device__ __forceinline__ bool rank_members(const uint2* member, int lane, int n, int want, float& t, int& column, bool& cut) {
+  const uint2 e = member[lane < n ? lane : 0];
+  const float key = __uint_as_float(e.x);
+  int rank = lane < n ? 0 : 2 * kWave;
+  for (int q = 0; q < n; ++q) {
+    const float other = __int_as_float(__builtin_amdgcn_readlane((int)e.x, q));
+    const int other_col = __builtin_amdgcn_readlane((int)e.y, q);
+    rank += (other > key || (other == key && other_col < (int)e.y)) ? 1 : 0;
+  }
+  const uint64_t at = __builtin_amdgcn_ballot_w64(rank == want - 1);
+  if (at == 0) return false;
+  const int l = __builtin_ctzll(at);
+  t = __int_as_float(__builtin_amdgcn_readlane((int)e.x, l));
+  column = __builtin_amdgcn_readlane((int)e.y, l);
+  cut = __builtin_amdgcn_ballot_w64(lane < n && key == t && rank >= want) != 0;
+  return true;
+}
+
+// The smallest float above t (of a zero of either sign: the smallest above zero).
+__device__ __forceinline__ float next_above(float t) {
+  const int u = __float_as_int(t);
+  return t == 0.0f ? __int_as_float(1) : __int_as_float(u < 0 ? u - 1 : u + 1);
+}
+// One wavefront: the k-th of the n singles (value bits, column), all at or above T0, hi the largest key.  bins: kBins words of
+// LDS of its own, 16-byte aligned.  The selection is key >= (column <= split ? tlo : thi).  Returns false where it is not
+// found: more than 64 members of its bin, NaN keys.  (The singles are read twice rather than kept: the row is still in
+// registers here, for the search that follows where this one fails.)
+template <bool NEG>
+__device__ __forceinline__ bool kth_by_bins(const uint2* single, int n, int lane, int k, float T0, float hi, uint32_t* bins,
+                                            float& thi, float& tlo, int& split) {
+  clear_bins(bins, lane);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  const float scale = bins_scale(T0, hi);
+  for (int i = 0; i < n; i += kWave) {
+    const int j = i + lane;
+    const int bin = bin_of(keyof<NEG>(__uint_as_float(single[j < n ? j : 0].x)), hi, scale);
+    if (j < n) __hip_atomic_fetch_add(bins + bin, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  int above, in_bin;
+  const int chosen = find_bin(bins, lane, k, above, in_bin);
+  if (chosen < 0 || in_bin > kWave) return false;  // uniform
+  uint2* member = reinterpret_cast<uint2*>(bins);
+  uint32_t members = 0;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  for (int i = 0; i < n; i += kWave) {
+    const int j = i + lane;
+    const uint2 e = single[j < n ? j : 0];
+    const float key = keyof<NEG>(__uint_as_float(e.x));
+    const uint64_t m = __builtin_amdgcn_ballot_w64(j < n && bin_of(key, hi, scale) == chosen);
+    const uint32_t at = lanes_below(m, members);
+    if (((m >> lane) & 1) != 0) member[at] = make_uint2(__float_as_uint(key), e.y);
+    members += (uint32_t)__builtin_popcountll(m);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  bool cut;
+  if (!rank_members(member, lane, in_bin, k - above, tlo, split, cut)) return false;
+  thi = cut ? next_above(tlo) : tlo;
+  if (!cut) split = 0x7fffffff;
+  return true;
+}
+
 // LDS of one row.  CAP: quads, and singles, that the lists hold.  The bitmaps take the quads' place when those
 // have become singles.
 template <int W, int ROOM = W == 4 ? 512 : 1024>
@@ -191,6 +292,7 @@ struct FilterLds {
     Maps maps;
   };
   uint2 single[CAP];             // (value bits, column)
+  alignas(16) uint32_t bins[kBins];
   int n_quads, n_singles;
   int wave_bits[W];
   float thr[2];
@@ -401,8 +503,16 @@ __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], 
   if (wave == 0) {
     float l = low, h = hi, thres = low;
     bool hit = false;
-    int steps = walked, cnt = -1, na = 0;
-    if (n <= 4 * kWave) {
+    int steps = walked, cnt = -1, na = 0, last = 0x7fffffff;
+    float by_bins_hi, by_bins_lo;
+    bool found = false;
+    if constexpr (MODE == kExact) {
+      // (16-bit rows have few values, so a larger k finds many members in its bin: 2048 x 32768, bfloat16, k = 256, 256 rows
+      // 10.4 -> 10.7 us with bins, k = 64 9.9 -> 9.3)
+      if (DT == kF32 || k <= 128) found = kth_by_bins<NEG>(s.single, n, lane, k, T0, hi, s.bins, by_bins_hi, by_bins_lo, last);
+    }
+    if (found) {
+    } else if (n <= 4 * kWave) {
       filter_search<4, MODE, NEG, DT>(s.single, n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
     } else if (n <= 8 * kWave || CAP <= 8 * kWave) {
       filter_search<8, MODE, NEG, DT>(s.single, n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
@@ -421,7 +531,10 @@ __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], 
       limit = cnt == k ? 0 : k;
       listed = l >= T0;
     } else {
-      if (hit) {
+      if (found) {
+        t_hi = by_bins_hi;
+        t_lo = by_bins_lo;
+      } else if (hit) {
         t_hi = t_lo = thres;
       } else if (na >= k) {
         t_hi = inf;
@@ -440,7 +553,7 @@ __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], 
       s.thr[1] = t_lo;
       s.info[0] = limit;
       s.info[1] = hit ? steps : steps + 1;
-      s.info[2] = 0x7fffffff;
+      s.info[2] = found ? last : 0x7fffffff;
       s.state = (listed ? 0 : 1) | (MODE == kEarly && cnt != k ? 2 : 0);
     }
   }
@@ -451,7 +564,7 @@ __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], 
   if (MODE == kEarly) thi = (state & 2) != 0 ? __builtin_inff() : thi;
   const int limit = __builtin_amdgcn_readfirstlane(s.info[0]);
   iterations = __builtin_amdgcn_readfirstlane(s.info[1]);
-  split = 0x7fffffff;
+  split = MODE == kExact ? __builtin_amdgcn_readfirstlane(s.info[2]) : 0x7fffffff;
   if ((state & 1) != 0) {
     lo = tlo;
     if (MODE == kEps) hi = thi;
@@ -628,9 +741,17 @@ __device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E
   if (n <= (uint32_t)k || n > (uint32_t)(kMost * kWave)) return kFilterNoList;  // (n <= k only with NaN or infinite keys)
 
   float thres = low, l = low, h = hi;
-  bool hit = false;
+  bool hit = false, found = false;
   int steps = walked, cnt = -1, na = 0;
-  if (n <= 2 * kWave) {
+  split = 0x7fffffff;
+  if constexpr (MODE == kExact && DT == kF32) {
+    // (the bins at the end of the lists' memory, where no single reaches)
+    const int bytes = room * 20 - kBins * 4;
+    uint32_t* bins = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(lists) + bytes);
+    if ((int)n * 8 <= bytes) found = kth_by_bins<NEG>(lists, (int)n, lane, k, T0, hi, bins, thi, tlo, split);
+  }
+  if (found) {
+  } else if (n <= 2 * kWave) {
     filter_search<2, MODE, NEG, DT>(lists, (int)n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
   } else if (n <= 4 * kWave) {
     filter_search<4, MODE, NEG, DT>(lists, (int)n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
@@ -646,6 +767,7 @@ __device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E
     tlo = l;
     thi = cnt == k ? l : __builtin_inff();
     limit = cnt == k ? 0 : k;
+  } else if (found) {
   } else if (hit) {
     thi = tlo = thres;
   } else if (na >= k) {
@@ -662,7 +784,6 @@ __device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E
       return kFilterBoundOnly;
     }
   }
-  split = 0x7fffffff;
   if (DENSE && limit == 0) return kFilterDone;
 
   // All singles go to registers before the first pair is staged: the stage may be the lists' memory.
@@ -682,7 +803,7 @@ __device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E
   for (int i = 0; i < kMost; ++i) {
     if ((uint32_t)(i * kWave) < n) {
       const float key = keyof<NEG>(__uint_as_float(s[i].x));
-      uint64_t m = __builtin_amdgcn_ballot_w64(key >= thi);
+      uint64_t m = __builtin_amdgcn_ballot_w64(key >= (MODE == kExact && found && (int)s[i].y <= split ? tlo : thi));
       if (limit > 0) {  // uniform
         const uint64_t band = __builtin_amdgcn_ballot_w64(key >= tlo) & ~m;
         const uint64_t first = band & __builtin_amdgcn_ballot_w64(lanes_below(band, in_band) < (uint32_t)limit);

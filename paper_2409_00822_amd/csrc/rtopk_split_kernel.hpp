@@ -10,16 +10,20 @@
 //     the first in column order are listed, more than the row's selection can take from this segment;
 //   rtopk_merge_kernel: one workgroup per row.  The largest of the segments' floors has more than k keys of the row at or
 //     above it, and the lists hold all of those, so Algorithms 1 and 2 run on the lists with exact branch decisions (see
-//     rtopk_filter.hpp); the lists follow each other in column order, so places are prefix counts.
+//     rtopk_filter.hpp; exact mode finds the k-th key by bins instead); the lists follow each other in column order, so
+//     places are prefix counts.
 // A row whose last threshold is not above the floor is written from the row itself.  A row with more candidates than the
 // merging workgroup's registers hold (only where `cap` of split_of says that they may) is done by that workgroup as a
 // streamed row (rtopk_stream_kernel.hpp).  Results are those of the other kernels.
 //
 // What bounds it: the segments read the row once at the rate of the 32768-column rows (1.15 times the copy rate's time),
-// the lists add 8 bytes per candidate written and read, 1.2 to 1.4 k of them per segment, and the merge costs a launch
-// and about 14 steps of one barrier.  Kernel time, one workgroup per row -> split:
-// 64 x 131072, k = 50: 39.5 -> 19.4 us in 512 segments; 1 x 131072: 36.5 -> 12.2; 1024 x 131072, k = 64: 131 -> 95;
-// 2048 x 50000, k = 100, registers of one workgroup -> split: 135 -> 87; 512 x 262144, k = 512: 118 -> 116.
+// the lists add 8 bytes per candidate written and read, 1.2 to 1.4 k of them per segment.  The merge is a launch and a chain of
+// latencies, in which few wavefronts share a SIMD and each instruction takes one of them about seven cycles: so its loads are
+// issued together, no more registers are walked than the row's candidates fill, and exact mode counts each key into a bin
+// once instead of in 10 to 14 steps of a barrier each (one row of 131072 columns, the merge alone: 7.8 -> 4 us).  Kernel
+// time, one workgroup per row -> split with steps -> with bins: 64 x 131072, k = 50: 39.5 -> 19.2 -> 13.5 us; 1 x 131072: 36.5 -> 12.6 ->
+// 8.7; 2048 x 50000, k = 100, registers of one workgroup -> split: 135 -> 88 -> 79; 16 x 2^20, k = 100: 31.0 -> 22.9;
+// 256 x 262144, k = 512: 69 -> 59.
 #pragma once
 
 #include "rtopk_block_kernel.hpp"
@@ -102,88 +106,131 @@ __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(
   }
 }
 
-// One row: its search on the segments' lists, and its selection from them, or, where the search ends on a minimum below
-// the floor, from the row.  Returns false, with nothing written, where the lists do not hold the search.  Called by the
-// whole workgroup; uniform.
-template <int NW, int MODE, bool NEG>
-__device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ in, int M, int k, int max_iter, float eps_rel,
-                                          float* __restrict__ out_vals, int32_t* __restrict__ out_idx,
-                                          int32_t* __restrict__ out_iters, const SegmentHead* __restrict__ heads,
-                                          const uint2* __restrict__ lists, int segments, int cap) {
-  __shared__ int s_first[kMaxSegments + 1];  // candidates in earlier segments
-  __shared__ float s_bound[3];
-  __shared__ int s_total, s_cnt[2][NW], s_cls[2][NW];
+// What the search of a row leaves to be written from the row itself: two classes of keys and a limit for each (as in
+// rtopk_block_kernel.hpp).
+struct RowClasses {
+  float tA, tB;
+  int limA, limB;
+};
+enum MergeResult : int {
+  kMergeDone = 0,     // the pairs are written
+  kMergeNoList = 1,   // the lists do not hold the search
+  kMergeFromRow = 2   // the search is over; the selection reaches below the floor
+};
+
+template <int NW>
+struct MergeLds {
+  int first[kMaxSegments + 1];  // candidates in earlier segments
+  float bound[3];
+  int total, cnt[2][NW], cls[2][NW];
+  alignas(16) uint32_t bins[kBins];
+  uint2 member[kWave];  // of the bin with the k-th key: (key bits, column), any order
+  uint32_t members;
+};
+
+// One row's candidates, KR registers of them per lane, `per` in use: the search and the pairs.  Uniform over the workgroup.
+template <int NW, int KR, int MODE, bool NEG>
+__device__ __forceinline__ MergeResult merge_candidates(MergeLds<NW>& s, int64_t r, int M, int k, int max_iter, float eps_rel,
+                                                        float* __restrict__ ov, int32_t* __restrict__ oi,
+                                                        int32_t* __restrict__ out_iters, const uint2* __restrict__ lists,
+                                                        int segments, int cap, int per, int total, float T0, float lo, float hi,
+                                                        RowClasses& rest) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-
-  // The segments' heads, by one wavefront.
-  if (wave == 0) {
-    float fl = -__builtin_inff(), nlo = -__builtin_inff(), hi = -__builtin_inff();
-    int before = 0;
-    for (int s0 = 0; s0 < segments; s0 += kWave) {
-      const bool live = s0 + lane < segments;
-      const SegmentHead h = heads[r * segments + (live ? s0 + lane : 0)];
-      const int n = live ? h.n : 0;
-      const uint32_t incl = wave_inclusive_scan_dpp((uint32_t)n);
-      if (live) s_first[s0 + lane] = before + (int)incl - n;
-      before += __builtin_amdgcn_readlane((int)incl, kWave - 1);
-      fl = vmax(fl, h.floor);  // (a lane beyond the last segment repeats the first)
-      nlo = vmax(nlo, h.nlo);
-      hi = vmax(hi, h.hi);
+  // 64 consecutive ones to a register: number wave * per * 64 + i * 64 + lane.  All loads are issued together (a lane beyond
+  // the last candidate repeats its load), with 32-bit offsets: a row's lists are less than 2 GiB.
+  float key[KR];
+  uint32_t col[KR];
+  {
+    int seg[KR], e[KR];
+#pragma unroll
+    for (int i = 0; i < KR; ++i) {
+      seg[i] = 0;  // the last segment that starts at or before the candidate and is not empty
+      e[i] = min((wave * per + i) * kWave + lane, total - 1);
     }
-    float a, b, c, unused;
-    wave_max_and_negmin(fl, nlo, a, b);
-    wave_max_and_negmin(hi, hi, c, unused);
-    if (lane == 0) {
-      s_first[segments] = before;
-      s_total = before;
-      s_bound[0] = a;
-      s_bound[1] = b;
-      s_bound[2] = c;
+    for (int step = segments > 1 ? 1 << (31 - __builtin_clz(segments - 1)) : 0; step > 0; step >>= 1) {
+#pragma unroll
+      for (int i = 0; i < KR; ++i) {
+        const int next = min(seg[i] + step, segments);
+        seg[i] = s.first[next] <= e[i] ? next : seg[i];
+      }
+    }
+    uint2 v[KR];
+#pragma unroll
+    for (int i = 0; i < KR; ++i) {
+      const uint32_t at = (uint32_t)(seg[i] * cap + e[i] - s.first[seg[i]]);
+      v[i] = *reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(lists) + at * 8u);
+    }
+#pragma unroll
+    for (int i = 0; i < KR; ++i) {
+      const bool live = i < per && (wave * per + i) * kWave + lane < total;
+      key[i] = live ? keyof<NEG>(__uint_as_float(v[i].x)) : __builtin_nanf("");  // (at or above no threshold)
+      col[i] = v[i].y;
     }
   }
-  __syncthreads();
-  const int total = __builtin_amdgcn_readfirstlane(s_total);
-  const float T0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_bound[0])));
-  float lo = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_bound[1])));
-  float hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_bound[2])));
-  if (total <= k || total > NW * kWave * kMergeRegs) return false;
-
-  // The candidates, 64 consecutive ones to a register: number wave * per * 64 + i * 64 + lane.
-  const int per = (total + NW * kWave - 1) / (NW * kWave);
-  float key[kMergeRegs];
-  uint32_t col[kMergeRegs];
-  int top = 1;
-  while (top < segments) top <<= 1;
+  if constexpr (MODE == kExact) {
+    // the k-th key by bins (see kth_by_bins): every wavefront bins its own, then all find the same bin and rank its members
+    const float scale = bins_scale(T0, hi);
+    int bin[KR];
 #pragma unroll
-  for (int i = 0; i < kMergeRegs; ++i) {
-    key[i] = -__builtin_inff();
-    col[i] = 0;
-    if (i < per) {  // uniform
-      const int e = (wave * per + i) * kWave + lane;
-      if (e < total) {
-        int s = 0;  // the last segment that starts at or before e and is not empty
-        for (int step = top; step > 0; step >>= 1)
-          if (s + step < segments && s_first[s + step] <= e) s += step;
-        const uint2 v = lists[(r * segments + s) * cap + (e - s_first[s])];
-        key[i] = keyof<NEG>(__uint_as_float(v.x));
-        col[i] = v.y;
+    for (int i = 0; i < KR; ++i) {
+      bin[i] = bin_of(key[i], hi, scale);
+      if (key[i] >= T0) atomicAdd(&s.bins[bin[i]], 1u);
+    }
+    __syncthreads();
+    int above, in_bin;
+    const int chosen = find_bin(s.bins, lane, k, above, in_bin);
+    if (chosen >= 0 && in_bin <= kWave) {  // uniform
+#pragma unroll
+      for (int i = 0; i < KR; ++i) {
+        if (key[i] >= T0 && bin[i] == chosen) {
+          const uint32_t at = atomicAdd(&s.members, 1u);
+          if (at < (uint32_t)kWave) s.member[at] = make_uint2(__float_as_uint(key[i]), col[i]);
+        }
+      }
+      __syncthreads();
+      float t;
+      int tcol;
+      bool cut;
+      if (rank_members(s.member, lane, in_bin, k - above, t, tcol, cut)) {
+        uint64_t m[KR];
+        uint32_t mine = 0;
+#pragma unroll
+        for (int i = 0; i < KR; ++i) {
+          m[i] = __builtin_amdgcn_ballot_w64(key[i] > t || (key[i] == t && (int)col[i] <= tcol));
+          mine += (uint32_t)__builtin_popcountll(m[i]);
+        }
+        if (lane == 0) s.cls[0][wave] = (int)mine;
+        __syncthreads();
+        uint32_t place = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) place += w < wave ? (uint32_t)s.cls[0][w] : 0u;
+#pragma unroll
+        for (int i = 0; i < KR; ++i) {
+          const uint32_t at = lanes_below(m[i], place);
+          if (((m[i] >> lane) & 1) != 0 && at < (uint32_t)k) {
+            ov[at] = keyof<NEG>(key[i]);
+            oi[at] = (int32_t)min(col[i], (uint32_t)(M - 1));  // (NaN keys can leave list entries unwritten)
+          }
+          place += (uint32_t)__builtin_popcountll(m[i]);
+        }
+        return kMergeDone;
       }
     }
   }
   int turn = 0;
-  auto count = [&](float t) -> int {  // one barrier; the halves of s_cnt alternate as in rtopk_block_kernel
+  auto count = [&](float t) -> int {  // one barrier; the halves of s.cnt alternate as in rtopk_block_kernel
     int mine = 0;
 #pragma unroll
-    for (int i = 0; i < kMergeRegs; ++i)
+    for (int i = 0; i < KR; ++i)
       if (i < per) mine += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[i] >= t));
     const int p = turn & 1;
     ++turn;
-    if (lane == 0) s_cnt[p][wave] = mine;
+    if (lane == 0) s.cnt[p][wave] = mine;
     __syncthreads();
-    return __builtin_amdgcn_readfirstlane((int)row16_sum(lane < NW ? (uint32_t)s_cnt[p][lane] : 0u));
+    return __builtin_amdgcn_readfirstlane((int)row16_sum(lane < NW ? (uint32_t)s.cnt[p][lane] : 0u));
   };
-  if (count(T0) <= k) return false;  // (only with NaN or infinite keys)
+  if (count(T0) <= k) return kMergeNoList;  // (only with NaN or infinite keys)
 
   // The search (see filter_search): exact mode may start at the floor, the others follow their thresholds.
   bool hit = false;
@@ -228,36 +275,34 @@ __device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ i
   if constexpr (MODE == kEps) {
     if (out_iters != nullptr && tid == 0) out_iters[r] = hit ? steps : steps + 1;
   }
-  float* ov = out_vals + r * (int64_t)k;
-  int32_t* oi = out_idx + r * (int64_t)k;
   // (At the floor itself a list may hold some of the keys only.  They are those that exact mode needs, whose class B is one
   // value; the other modes take the first keys of a whole range.)
   if (MODE != kExact && !((limB > 0 ? tB : tA) > T0)) {
-    write_by_chunks<NW, 4, NEG, 2>(in + r * (int64_t)M, M, k, tA, tB, limA, limB, ov, oi);
-    return true;
+    rest = RowClasses{tA, tB, limA, limB};
+    return kMergeFromRow;
   }
 
   uint32_t nA = 0, nB = 0;
 #pragma unroll
-  for (int i = 0; i < kMergeRegs; ++i) {
+  for (int i = 0; i < KR; ++i) {
     if (i < per) {
       nA += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(key[i] >= tA));
       if (limB > 0) nB += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(key[i] >= tB && !(key[i] >= tA)));
     }
   }
   if (lane == 0) {
-    s_cls[0][wave] = (int)nA;
-    s_cls[1][wave] = (int)nB;
+    s.cls[0][wave] = (int)nA;
+    s.cls[1][wave] = (int)nB;
   }
   __syncthreads();
   uint32_t posA0 = 0, posB0 = 0;
 #pragma unroll
   for (int w = 0; w < NW; ++w) {
-    posA0 += w < wave ? (uint32_t)s_cls[0][w] : 0u;
-    posB0 += w < wave ? (uint32_t)s_cls[1][w] : 0u;
+    posA0 += w < wave ? (uint32_t)s.cls[0][w] : 0u;
+    posB0 += w < wave ? (uint32_t)s.cls[1][w] : 0u;
   }
 #pragma unroll
-  for (int i = 0; i < kMergeRegs; ++i) {
+  for (int i = 0; i < KR; ++i) {
     if (i < per) {
       const bool a = key[i] >= tA, b = limB > 0 && key[i] >= tB && !a;
       const uint64_t mA = __builtin_amdgcn_ballot_w64(a), mB = __builtin_amdgcn_ballot_w64(b);
@@ -271,7 +316,78 @@ __device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ i
       posB0 += (uint32_t)__builtin_popcountll(mB);
     }
   }
-  return true;
+  return kMergeDone;
+}
+
+// One row: its search on the segments' lists, and its selection from them, or, where the search ends on a minimum below
+// the floor, from the row.  Returns false, with nothing written, where the lists do not hold the search.  Called by the
+// whole workgroup; uniform.
+template <int NW, int MODE, bool NEG>
+__device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ in, int M, int k, int max_iter, float eps_rel,
+                                          float* __restrict__ out_vals, int32_t* __restrict__ out_idx,
+                                          int32_t* __restrict__ out_iters, const SegmentHead* __restrict__ heads,
+                                          const uint2* __restrict__ lists, int segments, int cap) {
+  __shared__ MergeLds<NW> s;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // The segments' heads, by one wavefront, while the last clears the bins.
+  if (MODE == kExact && wave == NW - 1) {
+    clear_bins(s.bins, lane);
+    if (lane == 0) s.members = 0;
+  }
+  if (wave == 0) {
+    float fl = -__builtin_inff(), nlo = -__builtin_inff(), hi = -__builtin_inff();
+    int before = 0;
+    for (int s0 = 0; s0 < segments; s0 += kWave) {
+      const bool live = s0 + lane < segments;
+      const SegmentHead h = heads[r * segments + (live ? s0 + lane : 0)];
+      const int n = live ? h.n : 0;
+      const uint32_t incl = wave_inclusive_scan_dpp((uint32_t)n);
+      if (live) s.first[s0 + lane] = before + (int)incl - n;
+      before += __builtin_amdgcn_readlane((int)incl, kWave - 1);
+      fl = vmax(fl, h.floor);  // (a lane beyond the last segment repeats the first)
+      nlo = vmax(nlo, h.nlo);
+      hi = vmax(hi, h.hi);
+    }
+    float a, b, c, unused;
+    wave_max_and_negmin(fl, nlo, a, b);
+    wave_max_and_negmin(hi, hi, c, unused);
+    if (lane == 0) {
+      s.first[segments] = before;
+      s.total = before;
+      s.bound[0] = a;
+      s.bound[1] = b;
+      s.bound[2] = c;
+    }
+  }
+  __syncthreads();
+  const int total = __builtin_amdgcn_readfirstlane(s.total);
+  const float T0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[0])));
+  float lo = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[1])));
+  float hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[2])));
+  if (total <= k || total > NW * kWave * kMergeRegs) return false;
+
+
+  float* ov = out_vals + r * (int64_t)k;
+  int32_t* oi = out_idx + r * (int64_t)k;
+  const int per = (total + NW * kWave - 1) / (NW * kWave);
+  const uint2* of_row = lists + r * segments * cap;
+  RowClasses rest;
+  MergeResult done;
+  if (per <= 4) {  // (as few registers as serve: a wavefront issues an instruction in seven cycles, and few share a SIMD here)
+    done = merge_candidates<NW, 4, MODE, NEG>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters, of_row, segments, cap, per, total, T0,
+                                              lo, hi, rest);
+  } else if (per <= 8) {
+    done = merge_candidates<NW, 8, MODE, NEG>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters, of_row, segments, cap, per, total, T0,
+                                              lo, hi, rest);
+  } else {
+    done = merge_candidates<NW, kMergeRegs, MODE, NEG>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters, of_row, segments, cap, per,
+                                                       total, T0, lo, hi, rest);
+  }
+  if (MODE != kExact && done == kMergeFromRow)
+    write_by_chunks<NW, 4, NEG, 2>(in + r * (int64_t)M, M, k, rest.tA, rest.tB, rest.limA, rest.limB, ov, oi);
+  return done != kMergeNoList;
 }
 
 template <int NW, int MODE, bool NEG>
