@@ -284,6 +284,7 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
   }
   float hi, lo, T0, probe;
   block_bounds<E, W, NEG, FILTER>(x, nm, (k + W) / W, lane, wave, s_bounds, lo, hi, T0, probe);
+  const float least = lo;
 
   using OutT = typename std::conditional<DT == kF32, uint32_t, uint16_t>::type;  // value bits as stored
   OutT* ov = static_cast<OutT*>(out_vals) + r * (int64_t)(DENSE ? M : k);
@@ -418,7 +419,7 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
     if constexpr (MODE == kExact) {
       float seen = lo;
       for (;;) {
-        thres = midpoint_of_row<DT>(lo, hi);
+        thres = midpoint_exact<DT>(lo, hi);
         if (!(thres < seen || thres > seen)) break;
         seen = thres;
         int cnt = count(thres);
@@ -431,7 +432,7 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
           narrow = true;
           break;
         }
-        thres = midpoint_of_row<DT>(lo, hi);
+        thres = midpoint_exact<DT>(lo, hi);
         cnt = count(thres);
         if (cnt == k) {
           hit = true;
@@ -506,7 +507,7 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
     } else {
       const int na = count(hi);
       tA = hi;
-      tB = lo;
+      tB = not_below(lo, least);
       limA = na < k ? na : k;
       limB = k - limA;
     }
@@ -522,7 +523,7 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
       move_bound(lo, hi, thres, cnt, k);
       if (cnt == k) break;
     }
-    tA = lo;
+    tA = not_below(lo, least);
   }
   if (PATH == kFullWidth) bounds.lo = limB > 0 ? tB : tA;
   // The search is over; what follows needs few registers besides the row.  A workgroup that has another

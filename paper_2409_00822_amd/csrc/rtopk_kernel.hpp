@@ -580,13 +580,9 @@ __device__ __forceinline__ float midpoint_exact(float lo, float hi) {
     return __uint_as_float(__float_as_uint(t) & (DT == kBF16 ? 0xffff0000u : 0xffffe000u));
   }
 }
-// The same, never below lo, for searches over a whole row: the sum of two bounds near the type's lowest value is -inf, a
-// threshold that columns past the row's end would reach too.
-template <int DT>
-__device__ __forceinline__ float midpoint_of_row(float lo, float hi) {
-  const float t = midpoint_exact<DT>(lo, hi);
-  return t < lo ? lo : t;
-}
+// A bound that a search has left below the row's smallest key `least`, put back to it: the sum of two bounds near the type's
+// lowest value is -inf, which columns past the row's end would reach too.
+__device__ __forceinline__ float not_below(float lo, float least) { return lo < least ? least : lo; }
 
 // In the lanes whose bit is set in `mask` (a subset of the active lanes): LDS[addr] = v.
 __device__ __forceinline__ void lds_store_masked(uint64_t mask, uint32_t addr, float v) {
@@ -985,7 +981,7 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
       bool narrow = false;
       float seen = lo;
       for (;;) {
-        thres = midpoint_of_row<DT>(lo, hi);
+        thres = midpoint_exact<DT>(lo, hi);
         if (!(thres < seen || thres > seen)) break;
         seen = thres;
         int cnt = count(thres);
@@ -1003,7 +999,7 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
             break;
           }
         }
-        thres = midpoint_of_row<DT>(lo, hi);
+        thres = midpoint_exact<DT>(lo, hi);
         cnt = count(thres);
         if (cnt == k) {
           hit = true;
@@ -1032,6 +1028,7 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
     if (hit) {
       emit_selection<G, NG, FULL, false, !KEEP, NEG, DENSE>(x, m, thres, thres, -1, lane, M, k, stage_addr, y);
     } else {
+      if constexpr (!FULL) lo = not_below(lo, NEG ? -row_max : row_min);
       // Everything >= hi is taken first (cut at k by column when hi is still the row maximum and k
       // or more tie there); the first k - na members of [lo, hi) follow: all columns up to the
       // (k - na)-th member's column select against lo, the others against hi.
@@ -1134,6 +1131,7 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
         }
       }
     }
+    if constexpr (!FULL) lo = not_below(lo, NEG ? -row_max : row_min);
     // The last step lowered hi (or none ran): the kept masks are not those of lo, so they are formed
     // again.  Wide rows keep no masks and rank against lo directly; only when the last step counted
     // exactly k can they skip the cut.
@@ -1503,11 +1501,65 @@ inline bool one_row_lists(int mode, bool half, const LaunchArgs& a) {
 // eight rows and 64-bit addresses), and with the scatter of their gradients behind it 968 -> 943; 2^20 rows, k = 64 239 -> 222.
 constexpr int kRowsPerWaveFp32M256 = 4;
 
-// Few rows: with 8 or 16 rows per wavefront a launch of less than ~32768 rows does not even put two
-// wavefronts on every SIMD, and each of them walks its rows one after the other.  Two rows per wavefront
-// then spread the same work over more wavefronts (M = 256: 4096 rows 10.5 -> 6.6 us, 16384 rows
-// 11.8 -> 9.4 us; no difference from 65536 rows on).
-constexpr int64_t kFewRows = 32768;
-constexpr int kRowsPerWaveFew = 2;
+// Fewer rows take fewer per wavefront, so that the launch still puts wavefronts on every SIMD: a wavefront walks its rows one
+// after the other, and one alone on its SIMD issues an instruction in about seven cycles where eight together issue one in three.
+// One row per wavefront up to `one` rows, two up to `two`, four up to `four`, the layout's own number beyond; each line
+// lies where the kernel times of both sides cross (exact mode, k = M / 8, us):
+//   rows per wavefront 2 -> 1: 64 x 1024 columns, k = 100 9.8 -> 5.3, 4096 rows 14.5 -> 8.9, 32768 37.3 -> 31.8, 131072 113.6 -> 116.9
+//     (k = 128 .. 150, full-width search: 32768 37.4 -> 36.1, 45000 48.4 -> 52.0);
+//     768 columns: 64 rows 7.9 -> 5.6, 16384 19.6 -> 17.8, 65536 49.5 -> 52.1; 512: 64 4.4 -> 3.5, 8192 8.2 -> 7.3, 65536 30.1 -> 31.7;
+//     256: 64 3.5 -> 3.0, 8192 5.7 -> 5.6, 16384 7.5 -> 7.9; 64: 4096 3.5 -> 3.7.
+//   16 -> 2, 4: 128 columns: 32768 rows 13.1 -> 8.4, 8.0; 65536 15.7 -> 13.5, 12.3; 131072 21.8 -> 23.8, 20.4; 262144 35.5 -> 44.5, 36.6;
+//     64 columns: 32768 9.7 -> 7.3, 6.6; 65536 11.4 -> 11.2, 9.5; 131072 15.0 -> 20.0, 15.6.
+//   8 -> 2, 4 (16-bit rows of 256 columns): 32768 14.2 -> 11.4, 11.6; 65536 19.6 -> 18.6, 18.0; 131072 31.2 -> 33.0, 30.2; 262144
+//     53.6 -> 62.0, 54.7.
+// The precision-bounded mode, whose C++ loop takes longer per row, crosses later.
+struct FewRows {
+  int64_t one, two, four;
+};
+enum RowForm : int { kPairs = 0, kBytes = 1, kPairsEps = 2 };  // int32 columns, byte-wide columns, Algorithm 1 with precision
+constexpr FewRows few_rows(int E, RowForm form) {
+  if (form == kPairsEps) {
+    if (E == 1) return {4096, 32768, 196608};
+    if (E <= 3) return {8192, 32768, 393216};
+    return {E <= 7 ? 16384 : 40960, 49152, 0};
+  }
+  if (E == 1) return {0, 16384, 98304};
+  if (E <= 3) return {form == kBytes ? 0 : 4096, 24576, E == 2 ? 196608 : 147456};
+  if (E == 4 && form == kBytes) return {4096, 49152, 147456};
+  return {E <= 6 ? 8192 : (E <= 8 ? 12288 : 32768), 49152, 147456};
+}
+// f(integral_constant<int, rows per wavefront>) for N rows; FULL: the layout's own number.
+template <int E, int FULL, RowForm FORM, typename F>
+hipError_t by_rows(int64_t N, F f) {
+  constexpr FewRows few = few_rows(E, FORM);
+  if constexpr (FULL > 1 && few.one > 0) {
+    if (N < few.one) return f(std::integral_constant<int, 1>());
+  }
+  if constexpr (FULL > 2) {
+    if (N < few.two) return f(std::integral_constant<int, 2>());
+  }
+  if constexpr (FULL > 4 && few.four > few.two) {
+    if (N < few.four) return f(std::integral_constant<int, 4>());
+  }
+  return f(std::integral_constant<int, FULL>());
+}
+// The dense form, bound by its stores, streams best with few rows per wavefront (one -> the numbers of the pair form: 2^18 rows of 512
+// columns 166.8 us, two 170.4; 1024 columns 342, two 379; 256 columns, one 82.4, two 84.2, four 85.8; 128 columns, four 44.5, sixteen 49.5),
+// but 300 columns, one 137.6, two 131.5.
+template <int E, typename F>
+hipError_t by_rows_dense(int64_t N, F f) {
+  if constexpr (E > 8) {
+    return f(std::integral_constant<int, 1>());
+  } else {
+    if (E > 1 && (N < 4096 || (E == 4 && N >= 16384) || (E == 8 && N >= 12288))) return f(std::integral_constant<int, 1>());
+    if (E > 2 || N < 24576) return f(std::integral_constant<int, 2>());
+    if constexpr (E == 1) {
+      if (N >= 196608) return f(std::integral_constant<int, 16>());
+    }
+    if constexpr (E <= 2) return f(std::integral_constant<int, 4>());
+    return hipErrorInvalidValue;  // not reached
+  }
+}
 
 }  // namespace rtopk
