@@ -20,11 +20,7 @@ static hipError_t pick_rows(bool full, int mode, const LaunchArgs& a) {
 
 template <int G, int NG>
 static hipError_t pick(bool full, int mode, const LaunchArgs& a) {
-  constexpr int E = Layout<G, NG>::E, R = (E == 3 || E == 4) ? kRowsPerWaveFp32M256 : rows_per_wave(E);
-  if constexpr (R > kRowsPerWaveFew) {
-    if (a.N < kFewRows) return pick_rows<G, NG, kRowsPerWaveFew>(full, mode, a);
-  }
-  return pick_rows<G, NG, R>(full, mode, a);
+  return by_rows_dense<Layout<G, NG>::E>(a.N, [&](auto r) { return pick_rows<G, NG, decltype(r)::value>(full, mode, a); });
 }
 
 hipError_t launch_dense_any(int g, int ng, bool full, int mode, const LaunchArgs& a) {

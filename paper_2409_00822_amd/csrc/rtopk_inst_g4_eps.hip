@@ -6,13 +6,10 @@ namespace rtopk {
 template <int NG>
 static hipError_t pick(bool full, const LaunchArgs& a) {
   constexpr int R = NG == 1 ? kRowsPerWaveFp32M256 : rows_per_wave(4 * NG);
-  if constexpr (R > kRowsPerWaveFew) {
-    if (a.N < kFewRows) {
-      return full ? launch<4, NG, kRowsPerWaveFew, true, kEps, int32_t>(a)
-                  : launch<4, NG, kRowsPerWaveFew, false, kEps, int32_t>(a);
-    }
-  }
-  return full ? launch<4, NG, R, true, kEps, int32_t>(a) : launch<4, NG, R, false, kEps, int32_t>(a);
+  return by_rows<4 * NG, R, kPairsEps>(a.N, [&](auto r) {
+    constexpr int rows = decltype(r)::value;
+    return full ? launch<4, NG, rows, true, kEps, int32_t>(a) : launch<4, NG, rows, false, kEps, int32_t>(a);
+  });
 }
 
 hipError_t launch_g4_eps(int ng, bool full, const LaunchArgs& a) {

@@ -22,13 +22,12 @@ static hipError_t pick(bool full, bool u8, const LaunchArgs& a) {
   if constexpr (NG == 4) {
     if (one_row_lists(kExact, false, a)) return pick_rows<NG, 1>(full, u8, a);
   }
-  if constexpr (R > kRowsPerWaveFew) {
-    if (a.N < kFewRows) return pick_rows<NG, kRowsPerWaveFew>(full, u8, a);  // every variant, not only int32 columns
-  }
+  auto rows = [&](auto r) { return pick_rows<NG, decltype(r)::value>(full, u8, a); };
   if constexpr (NG == 1) {
-    if (!u8 || full) return pick_rows<NG, kRowsPerWaveFp32M256>(full, u8, a);
+    if (u8) return full ? by_rows<4, kRowsPerWaveFp32M256, kBytes>(a.N, rows) : by_rows<4, R, kBytes>(a.N, rows);
+    return by_rows<4, kRowsPerWaveFp32M256, kPairs>(a.N, rows);
   }
-  return pick_rows<NG, R>(full, u8, a);
+  return by_rows<4 * NG, R, kPairs>(a.N, rows);
 }
 
 hipError_t launch_g4_exact(int ng, bool full, bool u8, const LaunchArgs& a) {

@@ -17,10 +17,7 @@ static hipError_t pick(bool full, const LaunchArgs& a) {
   if constexpr (E == 16) {
     if (one_row_lists(kEarly, true, a)) return pick_rows<DT, G, NG, 1>(full, a);
   }
-  if constexpr (R > kRowsPerWaveFew) {
-    if (a.N < kFewRows) return pick_rows<DT, G, NG, kRowsPerWaveFew>(full, a);
-  }
-  return pick_rows<DT, G, NG, R>(full, a);
+  return by_rows<E, R, kPairs>(a.N, [&](auto r) { return pick_rows<DT, G, NG, decltype(r)::value>(full, a); });
 }
 
 template <int DT>

@@ -24,13 +24,11 @@ static hipError_t pick_rows(bool full, bool u8, const LaunchArgs& a) {
 template <int G, int NG>
 static hipError_t pick(bool full, bool u8, const LaunchArgs& a) {
   constexpr int E = Layout<G, NG>::E, R = rows_per_wave(E);
-  if constexpr (R > kRowsPerWaveFew) {
-    if (a.N < kFewRows) return pick_rows<G, NG, kRowsPerWaveFew>(full, u8, a);
+  auto rows = [&](auto r) { return pick_rows<G, NG, decltype(r)::value>(full, u8, a); };
+  if constexpr (E <= 3) {
+    if (u8) return by_rows<E, R, kBytes>(a.N, rows);
   }
-  if constexpr (E == 3) {
-    if (!u8) return pick_rows<G, NG, kRowsPerWaveFp32M256>(full, u8, a);
-  }
-  return pick_rows<G, NG, R>(full, u8, a);
+  return by_rows<E, E == 3 ? kRowsPerWaveFp32M256 : R, kPairs>(a.N, rows);
 }
 
 hipError_t launch_small_exact(int g, int ng, bool full, bool u8, const LaunchArgs& a) {
