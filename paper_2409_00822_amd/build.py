@@ -56,7 +56,7 @@ def _link_binding(obj: str) -> None:
     import torch
 
     lib = os.path.join(os.path.dirname(torch.__file__), "lib")
-    subprocess.check_call(["g++", "-shared", obj, "-o", BINDING_PATH, "-L" + lib, "-lc10", "-lc10_hip", "-ltorch_cpu",
+    subprocess.check_call(["g++", "-shared", obj, "-o", BINDING_PATH, "-L" + lib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_hip",
                            "-ltorch_python", "-L" + HERE, "-lrtopk", "-Wl,-rpath,$ORIGIN"])
 
 
