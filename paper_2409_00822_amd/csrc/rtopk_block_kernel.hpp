@@ -180,7 +180,7 @@ struct BoundsLds {
 template <int E, int W, bool NEG, bool FILTER>
 __device__ __forceinline__ void block_bounds(const float (&x)[E], float nm, int need, int lane, int wave, BoundsLds<W>& s,
                                              float& lo, float& hi, float& T0, float& probe) {
-  constexpr int J = E / kFilterGroup;
+  constexpr int J = E >= 3 * kFilterGroup ? E / kFilterGroup : 4;
   float gm[J], wmax, wmin, above = 0.0f, floor_w = 0.0f;
   lane_group_maxima<E, NEG>(x, gm);
   float mx = gm[0];

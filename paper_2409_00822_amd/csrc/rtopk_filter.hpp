@@ -49,7 +49,7 @@ __device__ __forceinline__ float lane_negmin(const float (&x)[E]) {
 }
 
 // Group maxima: gm[j] = largest key of the j-th of the lane's J groups of consecutive elements.
-constexpr int kFilterGroup = 16;  // elements per group in the workgroup-per-row kernels
+constexpr int kFilterGroup = 16;  // elements per group in the workgroup-per-row kernels (four groups per lane of narrower ones)
 template <int E, bool NEG, int J>
 __device__ __forceinline__ void lane_group_maxima(const float (&x)[E], float (&gm)[J]) {
   constexpr int S = E / J;
@@ -79,7 +79,9 @@ constexpr int kFloorHalvings = 10;
 template <int J>
 __device__ __forceinline__ float floor_of_maxima(const float (&gm)[J], int need, float low, float high, float& above,
                                                  int halvings = 0) {
-  const int enough = need + (need >> 3) + 1;
+  // (of a few maxima two more than needed will do: the slowest of 16 wavefronts that look for 7 takes 7 steps instead of 10.5,
+  // and one row in ten no pivots, for 3 % more candidates)
+  const int enough = need + (need >> 3) + (need < 32 ? 3 : 1);
   const float largest = high, least = low;
   auto at_or_above = [&](float t) -> int {
     int cnt = 0;
@@ -237,17 +239,25 @@ __device__ __forceinline__ float next_above(float t) {
 // One wavefront: the k-th of the n singles (value bits, column), all at or above T0, hi the largest key.  bins: kBins words of
 // LDS of its own, 16-byte aligned.  The selection is key >= (column <= split ? tlo : thi).  Returns false where it is not
 // found: more than 64 members of its bin, NaN keys.  (The singles are read twice rather than kept: the row is still in
-// registers here, for the search that follows where this one fails.)
-template <bool NEG>
+// registers here, for the search that follows where this one fails.  BATCH: registers of them that are read together.)
+template <int BATCH, bool NEG>
 __device__ __forceinline__ bool kth_by_bins(const uint2* single, int n, int lane, int k, float T0, float hi, uint32_t* bins,
                                             float& thi, float& tlo, int& split) {
   clear_bins(bins, lane);
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   const float scale = bins_scale(T0, hi);
-  for (int i = 0; i < n; i += kWave) {
-    const int j = i + lane;
-    const int bin = bin_of(keyof<NEG>(__uint_as_float(single[j < n ? j : 0].x)), hi, scale);
-    if (j < n) __hip_atomic_fetch_add(bins + bin, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  for (int i0 = 0; i0 < n; i0 += BATCH * kWave) {
+    float key[BATCH];
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      const int j = i0 + i * kWave + lane;
+      key[i] = keyof<NEG>(__uint_as_float(single[j < n ? j : 0].x));
+    }
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      const int bin = bin_of(key[i], hi, scale);
+      if (i0 + i * kWave + lane < n) __hip_atomic_fetch_add(bins + bin, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    }
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   int above, in_bin;
@@ -256,14 +266,23 @@ __device__ __forceinline__ bool kth_by_bins(const uint2* single, int n, int lane
   uint2* member = reinterpret_cast<uint2*>(bins);
   uint32_t members = 0;
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  for (int i = 0; i < n; i += kWave) {
-    const int j = i + lane;
-    const uint2 e = single[j < n ? j : 0];
-    const float key = keyof<NEG>(__uint_as_float(e.x));
-    const uint64_t m = __builtin_amdgcn_ballot_w64(j < n && bin_of(key, hi, scale) == chosen);
-    const uint32_t at = lanes_below(m, members);
-    if (((m >> lane) & 1) != 0) member[at] = make_uint2(__float_as_uint(key), e.y);
-    members += (uint32_t)__builtin_popcountll(m);
+  for (int i0 = 0; i0 < n && members < (uint32_t)in_bin; i0 += BATCH * kWave) {
+    uint2 e[BATCH];
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      const int j = i0 + i * kWave + lane;
+      e[i] = single[j < n ? j : 0];
+    }
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      const float key = keyof<NEG>(__uint_as_float(e[i].x));
+      const uint64_t m = __builtin_amdgcn_ballot_w64(i0 + i * kWave + lane < n && bin_of(key, hi, scale) == chosen);
+      if (m != 0) {  // uniform
+        const uint32_t at = lanes_below(m, members);
+        if (((m >> lane) & 1) != 0) member[at] = make_uint2(__float_as_uint(key), e[i].y);
+        members += (uint32_t)__builtin_popcountll(m);
+      }
+    }
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   bool cut;
@@ -509,7 +528,7 @@ __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], 
     if constexpr (MODE == kExact) {
       // (16-bit rows have few values, so a larger k finds many members in its bin: 2048 x 32768, bfloat16, k = 256, 256 rows
       // 10.4 -> 10.7 us with bins, k = 64 9.9 -> 9.3)
-      if (DT == kF32 || k <= 128) found = kth_by_bins<NEG>(s.single, n, lane, k, T0, hi, s.bins, by_bins_hi, by_bins_lo, last);
+      if (DT == kF32 || k <= 128) found = kth_by_bins<4, NEG>(s.single, n, lane, k, T0, hi, s.bins, by_bins_hi, by_bins_lo, last);
     }
     if (found) {
     } else if (n <= 4 * kWave) {
@@ -748,7 +767,7 @@ __device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E
     // (the bins at the end of the lists' memory, where no single reaches)
     const int bytes = room * 20 - kBins * 4;
     uint32_t* bins = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(lists) + bytes);
-    if ((int)n * 8 <= bytes) found = kth_by_bins<NEG>(lists, (int)n, lane, k, T0, hi, bins, thi, tlo, split);
+    if ((int)n * 8 <= bytes) found = kth_by_bins<1, NEG>(lists, (int)n, lane, k, T0, hi, bins, thi, tlo, split);
   }
   if (found) {
   } else if (n <= 2 * kWave) {

@@ -13,6 +13,8 @@ static hipError_t pick(int mode, const LaunchArgs& a) {
 
 hipError_t launch_block_plain(int g, int ng, int w, int mode, const LaunchArgs& a) {
   if (g == 4) {
+    if (w == 4 && ng == 4) return pick<4, 4, 4>(mode, a);
+    if (w == 4 && ng == 8) return pick<4, 8, 4>(mode, a);
     if (w == 4 && ng == 12) return pick<4, 12, 4>(mode, a);
     if (w == 4 && ng == 16) return pick<4, 16, 4>(mode, a);
     if (w == 8 && ng == 12) return pick<4, 12, 8>(mode, a);

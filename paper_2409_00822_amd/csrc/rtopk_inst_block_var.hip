@@ -17,6 +17,8 @@ static hipError_t pick(int mode, bool smallest, const LaunchArgs& a) {
 
 hipError_t launch_block_variant(int g, int ng, int w, int mode, bool smallest, const LaunchArgs& a) {
   if (g == 4) {
+    if (w == 4 && ng == 4) return pick<4, 4, 4>(mode, smallest, a);
+    if (w == 4 && ng == 8) return pick<4, 8, 4>(mode, smallest, a);
     if (ng != 16) return hipErrorInvalidValue;
     if (w == 4) return pick<4, 16, 4>(mode, smallest, a);
     if (w == 8) return pick<4, 16, 8>(mode, smallest, a);

@@ -1545,13 +1545,17 @@ hipError_t by_rows(int64_t N, F f) {
   return f(std::integral_constant<int, FULL>());
 }
 // The dense form, bound by its stores, streams best with few rows per wavefront (one -> the numbers of the pair form: 2^18 rows of 512
-// columns 166.8 us, two 170.4; 1024 columns 342, two 379; 256 columns, one 82.4, two 84.2, four 85.8; 128 columns, four 44.5, sixteen 49.5),
+// columns 166.8 us, two 170.4; 1024 columns 342, two 379; 256 columns, one 82.4, two 84.2, four 85.8 and 2^22
+// rows 1304 against 1430 with four; 128 columns, four 44.5, sixteen 49.5),
 // but 300 columns, one 137.6, two 131.5.
 template <int E, typename F>
 hipError_t by_rows_dense(int64_t N, F f) {
   if constexpr (E > 8) {
     return f(std::integral_constant<int, 1>());
   } else {
+    if constexpr (E == 4) {
+      if (N > 0x7fffffff) return f(std::integral_constant<int, 4>());  // a grid has no more workgroups than that
+    }
     if (E > 1 && (N < 4096 || (E == 4 && N >= 16384) || (E == 8 && N >= 12288))) return f(std::integral_constant<int, 1>());
     if (E > 2 || N < 24576) return f(std::integral_constant<int, 2>());
     if constexpr (E == 1) {

@@ -118,6 +118,38 @@ inline Shape kernel_layout(int M, int dtype, bool plain, bool dense) {
   return s;
 }
 
+// Most rows of M columns (1537 .. 8192) that take a workgroup of four wavefronts each instead of one wavefront.  A
+// wavefront alone on its SIMD walks its 32 to 128 values in series, and 128 values per lane leave room for three wavefronts on a SIMD,
+// however many rows there are; the workgroup meets at half a dozen barriers instead.  Kernel times, one wavefront -> four
+// (fp32, exact mode unless said otherwise, us):
+//   8192 columns, k = 64: 16 rows 7.3 -> 5.5, 1024 12.5 -> 10.6, 8192 47.7 -> 45.1, 16384 90.7 -> 88.8, 32768 178 -> 180; k = 250: 16 10.8 ->
+//     6.9, 8192 55.3 -> 51.2; early stopping 8192 rows 47.6 -> 45.6; dense 1024 15.3 -> 11.6, 8192 97.6 -> 89.4, 32768 381 -> 358; bfloat16
+//     1024 10.2 -> 8.7, 4096 18.7 -> 17.7, 8192 29.0 -> 29.5, with early stopping 4096 18.3 -> 18.2;
+//   6000: 256 8.2 -> 6.6, 2048 14.4 -> 13.2, 4096 21.7 -> 21.1 (5000 19.3 -> 19.3); early stopping 512 8.4 -> 8.1, eps 9.7 -> 9.7;
+//     dense 1024 11.6 -> 10.4, 2048 17.5 -> 20.7; bfloat16 1024 9.0 -> 8.4, 2048 11.1 -> 11.1;
+//   4096: 16 5.9 -> 5.1, 1024 9.1 -> 8.1, 2048 11.5 -> 11.0, 4096 15.6 -> 17.1; k = 250 2048 15.5 -> 13.1; 3000: 1024 8.0 -> 7.6, 2048 10.2 -> 10.3;
+//     dense 1024 9.5 -> 8.5; bfloat16 512 6.9 -> 6.4, 1024 (3000 columns) 7.2 -> 7.3; early stopping 512 7.2 -> 7.1, eps 8.0 -> 8.4;
+//   2048: k = 140 512 7.7 -> 6.2, 2048 10.1 -> 10.1; k = 64 512 6.6 -> 6.5; 1536: k = 64 512 6.1 -> 6.3.
+inline int64_t workgroup_rows(int M, int k, bool half, int mode, bool dense) {
+  if (M > 6144) return half ? (mode == kExact ? 6144 : 4096) : (dense ? 0x7fffffff : 24576);
+  if (M > 4096) return dense ? 1024 : (mode == kExact ? (half ? 1024 : 3072) : 512);
+  if (M > 2048) return mode != kExact ? 0 : (half ? 512 : (dense ? 1024 : M / 2));
+  return M > 1536 && k >= 100 && mode == kExact && !half && !dense ? 1024 : 0;
+}
+// The layout of a call of N rows: kernel_layout(), but for these.  They take the lists (rtopk_filter.hpp), so only where those serve.
+inline Shape layout_of_call(int64_t N, int M, int k, int dtype, int mode, int max_iter, bool plain, bool dense) {
+  Shape s = kernel_layout(M, dtype, plain, dense);
+  if (M <= kMaxWaveM && k <= 256 && k < M && (mode != kEarly || max_iter >= 5) &&
+      N <= workgroup_rows(M, k, dtype != kF32, mode, dense)) {
+    s.family = kFamBlock;
+    s.w = 4;
+    s.g = dtype == kF32 ? 4 : 8;
+    s.ng = (M <= 4096 ? 16 : 32) / s.g;
+    s.full = M == s.capacity();
+  }
+  return s;
+}
+
 // True when (g, ng, w) is a layout of its family's lists above.  `plain` and `dense` as above.
 inline bool instantiated(const Shape& s, int dtype, bool plain, bool dense) {
   bool small = false, g4 = false, h8 = false;
@@ -139,8 +171,8 @@ inline bool instantiated(const Shape& s, int dtype, bool plain, bool dense) {
       return dtype != kF32 && !dense && s.w == 1 && (small || h8 || (s.g == 4 && s.ng == 1));
     case kFamBlock:
       if (s.w != 4 && s.w != 8 && s.w != 16) return false;
-      if (dtype != kF32) return !dense && s.g == 8 && s.ng == 8;
-      return s.g == 4 && (s.ng == 16 || (s.ng == 12 && plain && !dense));
+      if (dtype != kF32) return !dense && s.g == 8 && (s.ng == 8 || (s.w == 4 && (s.ng == 2 || s.ng == 4)));
+      return s.g == 4 && (s.ng == 16 || (s.w == 4 && (s.ng == 4 || s.ng == 8)) || (s.ng == 12 && plain && !dense));
     case kFamStream:
       return dtype == kF32 && !dense && s.w == 16 && s.g == 4;
     default:
