@@ -171,16 +171,15 @@ __device__ __forceinline__ void block_mask(float (&x)[G * NG], int M, int lane, 
 }
 
 // Minimum and maximum of the row's keys and, with FILTER, its floor (rtopk_filter.hpp: at least `need` group maxima of
-// every wavefront at or above it) and the bound above it: per lane, per wavefront, then over the W wavefronts through
+// every wavefront, J per lane, at or above it) and the bound above it: per lane, per wavefront, then over the W wavefronts through
 // LDS.  Contains a barrier.  nm: the lane's negated minimum (taken before the columns past M were masked).
 template <int W>
 struct BoundsLds {
   float hi[W], nlo[W], nt0[W], probe[W];
 };
-template <int E, int W, bool NEG, bool FILTER>
+template <int E, int W, bool NEG, bool FILTER, int J = (E >= 3 * kFilterGroup ? E / kFilterGroup : 4)>
 __device__ __forceinline__ void block_bounds(const float (&x)[E], float nm, int need, int lane, int wave, BoundsLds<W>& s,
                                              float& lo, float& hi, float& T0, float& probe) {
-  constexpr int J = E >= 3 * kFilterGroup ? E / kFilterGroup : 4;
   float gm[J], wmax, wmin, above = 0.0f, floor_w = 0.0f;
   lane_group_maxima<E, NEG>(x, gm);
   float mx = gm[0];

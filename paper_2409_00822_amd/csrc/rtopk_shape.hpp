@@ -196,6 +196,7 @@ constexpr int64_t kSplitScratch = 128ll << 20;
 // workgroups of w wavefronts with ng groups per lane, merge_waves wavefronts per row to merge.  segments = 0: not at all.
 struct Split {
   int segments, length, cap, w, ng, merge_waves;
+  bool big;  // lists of up to kBigRoom candidates, floors from eight groups per lane
   int64_t rows;  // rows per pair of launches, so that the scratch memory stays bounded
   int64_t bytes() const { return rows * segments * (kSegmentHeadBytes + (int64_t)cap * 8); }
 };
@@ -232,6 +233,39 @@ inline Split split_of(int64_t N, int M, int k, int mode, int max_iter) {
   if (s.cap > segment_room(s.w)) s.cap = segment_room(s.w);
   const int64_t per_row = s.segments * (kSegmentHeadBytes + (int64_t)s.cap * 8);
   s.rows = kSplitScratch / per_row;
+  if (s.rows < 1) s.rows = 1;
+  if (s.rows > N) s.rows = N;
+  return s;
+}
+
+// Rows of more than kMaxBlockM columns that split_of leaves to one streaming workgroup, because k is above its lists' limit or
+// their candidates would not fit the merge: lists of up to kBigRoom candidates, from segments of 32768 columns, or of 65536 where
+// the merge would not hold twice as many lists; 40 candidates per merging lane where 16 would not do.  (16 rows of 131072 columns, k = 600: streamed 46.6 us, split 15.9; 16 rows of 2^20, k = 800:
+// 165 -> 50; 1000 rows of 131072, k = 700: 151 -> 121.)  The floors come from eight groups of eight values per lane here, so a list has 1.1 to 1.35 k candidates at
+// k = 512 .. 1024.  Lists of 16 wavefronts, whose floors spread more, are expected to hold 1.5 k.
+constexpr int kBigMaxK = 1024;
+constexpr int kBigRoom = 1792;
+constexpr int kMergeRegsBig = 40;  // candidates per lane that 16 merging wavefronts hold at most
+inline Split split_big_of(int64_t N, int M, int k, int mode, int max_iter) {
+  Split s{};
+  if (M <= kMaxBlockM || N < 1 || k > kBigMaxK || (mode == kEarly && max_iter < 8)) return s;
+  int root = 1;
+  while (root * root < k) ++root;
+  s.big = true;
+  s.ng = 16;
+  s.merge_waves = 16;
+  int most = kMergeMost;
+  for (int round = 0; round < 3; ++round) {
+    s.w = round == 0 ? 8 : 16;
+    if (round == 2) most = 16 * 64 * kMergeRegsBig;
+    s.segments = (M + s.w * 4096 - 1) / (s.w * 4096);
+    if ((int64_t)s.segments * (k + (s.w == 8 ? k / 3 : k / 2) + 6 * root + 16) <= most) break;
+    s.segments = 0;
+  }
+  if (s.segments < 2) return Split{};
+  s.length = ((M + s.segments - 1) / s.segments + 3) & ~3;
+  s.cap = most / s.segments < kBigRoom ? most / s.segments : kBigRoom;  // no row has more than the merge holds
+  s.rows = kSplitScratch / (s.segments * (kSegmentHeadBytes + (int64_t)s.cap * 8));
   if (s.rows < 1) s.rows = 1;
   if (s.rows > N) s.rows = N;
   return s;

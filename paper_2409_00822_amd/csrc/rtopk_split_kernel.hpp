@@ -14,7 +14,8 @@
 //     places are prefix counts.
 // A row whose last threshold is not above the floor is written from the row itself.  A row with more candidates than the
 // merging workgroup's registers hold (only where `cap` of split_of says that they may) is done by that workgroup as a
-// streamed row (rtopk_stream_kernel.hpp).  Results are those of the other kernels.
+// streamed row (rtopk_stream_kernel.hpp).  Results are those of the other kernels.  Rows of more than 65536 columns whose k or whose
+// number of segments is too large for that take longer lists, and a merge of more of them (split_big_of).
 //
 // What bounds it: the segments read the row once at the rate of the 32768-column rows (1.15 times the copy rate's time),
 // the lists add 8 bytes per candidate written and read, 1.2 to 1.4 k of them per segment.  The merge is a launch and a chain of
@@ -38,13 +39,13 @@ struct SegmentHead {
 };
 static_assert(sizeof(SegmentHead) == kSegmentHeadBytes, "split_of counts it");
 
-template <int NG, int W, bool NEG>
-__global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(5)))
+template <int NG, int W, bool NEG, bool BIG>
+__global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(BIG ? 4 : 5)))
     rtopk_segment_kernel(const float* __restrict__ in, int M, int k, int segments, int length, int cap,
                          SegmentHead* __restrict__ heads, uint2* __restrict__ lists) {
   constexpr int G = 4, E = G * NG;
   __shared__ BoundsLds<W> s_bounds;
-  __shared__ FilterLds<W, segment_room(W)> s_filter;
+  __shared__ FilterLds<W, BIG ? kBigRoom : segment_room(W)> s_filter;
   const int lane = threadIdx.x & (kWave - 1), tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = (int)blockIdx.x / segments, seg = (int)blockIdx.x % segments;
@@ -59,13 +60,13 @@ __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(
     s_filter.n_singles = 0;
   }
   float lo, hi, T0, probe;
-  block_bounds<E, W, NEG, true>(x, nm, (k + W) / W, lane, wave, s_bounds, lo, hi, T0, probe);
+  block_bounds<E, W, NEG, true, BIG ? E / 8 : E / kFilterGroup>(x, nm, (k + W) / W, lane, wave, s_bounds, lo, hi, T0, probe);
   auto column = [&](int quad, int thread) -> int { return min((quad * W * kWave + thread) * G, cols - G); };
   const int n = filter_lists<E, W, NEG>(s_filter, x, lane, wave, T0, column, [] {});
   uint2* to = lists + (int64_t)blockIdx.x * cap;
   if (n < 0 || n > cap) {  // uniform
     bool none = false;
-    float ahead[1];
+    float ahead[block_groups_ahead(W, G, kFullWidth) * G + 1];
     KnownBounds end{};
     // (their values to the first half of the list's memory, their columns to the second; then in pairs like any other list)
     float* values = reinterpret_cast<float*>(to);
@@ -74,7 +75,7 @@ __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(
                                                               none, ahead, none, x, end);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (it stores through inline asm)
     __syncthreads();
-    constexpr int kMost = (filter_max_k(W) + W * kWave) / (W * kWave);  // pairs per thread, k + 1 in all
+    constexpr int kMost = ((BIG ? kBigMaxK : filter_max_k(W)) + W * kWave) / (W * kWave);  // pairs per thread, k + 1 in all
     uint2 pair[kMost];
 #pragma unroll
     for (int i = 0; i < kMost; ++i) {
@@ -141,41 +142,43 @@ __device__ __forceinline__ MergeResult merge_candidates(MergeLds<NW>& s, int64_t
   // the last candidate repeats its load), with 32-bit offsets: a row's lists are less than 2 GiB.
   float key[KR];
   uint32_t col[KR];
-  {
-    int seg[KR], e[KR];
+  constexpr int kBatch = KR <= 16 ? KR : 8;  // (more of them would not fit beside the 40 registers of the largest)
+  const int top = segments > 1 ? 1 << (31 - __builtin_clz(segments - 1)) : 0;
+  auto load = [&](auto from) {
+    constexpr int I0 = decltype(from)::value * kBatch;
+    int seg[kBatch], e[kBatch];
 #pragma unroll
-    for (int i = 0; i < KR; ++i) {
+    for (int i = 0; i < kBatch; ++i) {
       seg[i] = 0;  // the last segment that starts at or before the candidate and is not empty
-      e[i] = min((wave * per + i) * kWave + lane, total - 1);
+      e[i] = min((wave * per + I0 + i) * kWave + lane, total - 1);
     }
-    for (int step = segments > 1 ? 1 << (31 - __builtin_clz(segments - 1)) : 0; step > 0; step >>= 1) {
+    for (int step = top; step > 0; step >>= 1) {
 #pragma unroll
-      for (int i = 0; i < KR; ++i) {
+      for (int i = 0; i < kBatch; ++i) {
         const int next = min(seg[i] + step, segments);
         seg[i] = s.first[next] <= e[i] ? next : seg[i];
       }
     }
-    uint2 v[KR];
+    uint2 v[kBatch];
 #pragma unroll
-    for (int i = 0; i < KR; ++i) {
+    for (int i = 0; i < kBatch; ++i) {
       const uint32_t at = (uint32_t)(seg[i] * cap + e[i] - s.first[seg[i]]);
       v[i] = *reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(lists) + at * 8u);
     }
 #pragma unroll
-    for (int i = 0; i < KR; ++i) {
-      const bool live = i < per && (wave * per + i) * kWave + lane < total;
-      key[i] = live ? keyof<NEG>(__uint_as_float(v[i].x)) : __builtin_nanf("");  // (at or above no threshold)
-      col[i] = v[i].y;
+    for (int i = 0; i < kBatch; ++i) {
+      const bool live = I0 + i < per && (wave * per + I0 + i) * kWave + lane < total;
+      key[I0 + i] = live ? keyof<NEG>(__uint_as_float(v[i].x)) : __builtin_nanf("");  // (at or above no threshold)
+      col[I0 + i] = v[i].y;
     }
-  }
+  };
+  static_for<KR / kBatch>(load);
   if constexpr (MODE == kExact) {
     // the k-th key by bins (see kth_by_bins): every wavefront bins its own, then all find the same bin and rank its members
     const float scale = bins_scale(T0, hi);
-    int bin[KR];
 #pragma unroll
     for (int i = 0; i < KR; ++i) {
-      bin[i] = bin_of(key[i], hi, scale);
-      if (key[i] >= T0) atomicAdd(&s.bins[bin[i]], 1u);
+      if (key[i] >= T0) atomicAdd(&s.bins[bin_of(key[i], hi, scale)], 1u);
     }
     __syncthreads();
     int above, in_bin;
@@ -183,7 +186,8 @@ __device__ __forceinline__ MergeResult merge_candidates(MergeLds<NW>& s, int64_t
     if (chosen >= 0 && in_bin <= kWave) {  // uniform
 #pragma unroll
       for (int i = 0; i < KR; ++i) {
-        if (key[i] >= T0 && bin[i] == chosen) {
+        if constexpr (KR > 16) asm volatile("" : "+v"(key[i]));  // (the bins are not kept in as many registers again)
+        if (key[i] >= T0 && bin_of(key[i], hi, scale) == chosen) {
           const uint32_t at = atomicAdd(&s.members, 1u);
           if (at < (uint32_t)kWave) s.member[at] = make_uint2(__float_as_uint(key[i]), col[i]);
         }
@@ -193,12 +197,17 @@ __device__ __forceinline__ MergeResult merge_candidates(MergeLds<NW>& s, int64_t
       int tcol;
       bool cut;
       if (rank_members(s.member, lane, in_bin, k - above, t, tcol, cut)) {
-        uint64_t m[KR];
+        auto chosen_mask = [&](int i) -> uint64_t {
+          return __builtin_amdgcn_ballot_w64(key[i] > t || (key[i] == t && (int)col[i] <= tcol));
+        };
+        constexpr bool kKeep = KR <= 16;
+        uint64_t kept[kKeep ? KR : 1];
         uint32_t mine = 0;
 #pragma unroll
         for (int i = 0; i < KR; ++i) {
-          m[i] = __builtin_amdgcn_ballot_w64(key[i] > t || (key[i] == t && (int)col[i] <= tcol));
-          mine += (uint32_t)__builtin_popcountll(m[i]);
+          const uint64_t m = chosen_mask(i);
+          if constexpr (kKeep) kept[i] = m;
+          mine += (uint32_t)__builtin_popcountll(m);
         }
         if (lane == 0) s.cls[0][wave] = (int)mine;
         __syncthreads();
@@ -207,12 +216,15 @@ __device__ __forceinline__ MergeResult merge_candidates(MergeLds<NW>& s, int64_t
         for (int w = 0; w < NW; ++w) place += w < wave ? (uint32_t)s.cls[0][w] : 0u;
 #pragma unroll
         for (int i = 0; i < KR; ++i) {
-          const uint32_t at = lanes_below(m[i], place);
-          if (((m[i] >> lane) & 1) != 0 && at < (uint32_t)k) {
+          if constexpr (!kKeep) asm volatile("" : "+v"(key[i]));
+          uint64_t m;
+          if constexpr (kKeep) m = kept[i]; else m = chosen_mask(i);
+          const uint32_t at = lanes_below(m, place);
+          if (((m >> lane) & 1) != 0 && at < (uint32_t)k) {
             ov[at] = keyof<NEG>(key[i]);
             oi[at] = (int32_t)min(col[i], (uint32_t)(M - 1));  // (NaN keys can leave list entries unwritten)
           }
-          place += (uint32_t)__builtin_popcountll(m[i]);
+          place += (uint32_t)__builtin_popcountll(m);
         }
         return kMergeDone;
       }
@@ -366,7 +378,7 @@ __device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ i
   const float T0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[0])));
   float lo = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[1])));
   float hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[2])));
-  if (total <= k || total > NW * kWave * kMergeRegs) return false;
+  if (total <= k || total > NW * kWave * (NW == 16 ? kMergeRegsBig : kMergeRegs)) return false;
 
 
   float* ov = out_vals + r * (int64_t)k;
@@ -381,9 +393,12 @@ __device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ i
   } else if (per <= 8) {
     done = merge_candidates<NW, 8, MODE, NEG>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters, of_row, segments, cap, per, total, T0,
                                               lo, hi, rest);
-  } else {
+  } else if (NW < 16 || per <= kMergeRegs) {
     done = merge_candidates<NW, kMergeRegs, MODE, NEG>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters, of_row, segments, cap, per,
                                                        total, T0, lo, hi, rest);
+  } else {
+    done = merge_candidates<NW, NW == 16 ? kMergeRegsBig : kMergeRegs, MODE, NEG>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters,
+                                                                                  of_row, segments, cap, per, total, T0, lo, hi, rest);
   }
   if (MODE != kExact && done == kMergeFromRow)
     write_by_chunks<NW, 4, NEG, 2>(in + r * (int64_t)M, M, k, rest.tA, rest.tB, rest.limA, rest.limB, ov, oi);
@@ -408,8 +423,9 @@ hipError_t launch_split(const Split& s, void* scratch, const LaunchArgs& a) {
     const float* in = static_cast<const float*>(a.in) + r0 * a.M;
     SegmentHead* heads = static_cast<SegmentHead*>(scratch);
     uint2* lists = reinterpret_cast<uint2*>(heads + rows * s.segments);
-    const auto segment = s.w == 4 ? (s.ng == 12 ? &rtopk_segment_kernel<12, 4, NEG> : &rtopk_segment_kernel<16, 4, NEG>)
-                                  : (s.ng == 12 ? &rtopk_segment_kernel<12, 8, NEG> : &rtopk_segment_kernel<16, 8, NEG>);
+    const auto segment = s.big      ? (s.w == 8 ? &rtopk_segment_kernel<16, 8, NEG, true> : &rtopk_segment_kernel<16, 16, NEG, true>)
+                         : s.w == 4 ? (s.ng == 12 ? &rtopk_segment_kernel<12, 4, NEG, false> : &rtopk_segment_kernel<16, 4, NEG, false>)
+                                    : (s.ng == 12 ? &rtopk_segment_kernel<12, 8, NEG, false> : &rtopk_segment_kernel<16, 8, NEG, false>);
     hipError_t err = launch_kernel(segment, dim3((unsigned)(rows * s.segments)), dim3(s.w * kWave), 0, a.stream, in, a.M, a.k,
                                    s.segments, s.length, s.cap, heads, lists);
     if (err != hipSuccess) return err;
