@@ -177,7 +177,7 @@ template <int W>
 struct BoundsLds {
   float hi[W], nlo[W], nt0[W], probe[W];
 };
-template <int E, int W, bool NEG, bool FILTER, int J = (E >= 3 * kFilterGroup ? E / kFilterGroup : 4)>
+template <int E, int W, bool NEG, bool FILTER, int J>
 __device__ __forceinline__ void block_bounds(const float (&x)[E], float nm, int need, int lane, int wave, BoundsLds<W>& s,
                                              float& lo, float& hi, float& T0, float& probe) {
   float gm[J], wmax, wmin, above = 0.0f, floor_w = 0.0f;
@@ -229,7 +229,7 @@ struct KnownBounds {
 // same return statement.  A workgroup that walks several rows through the lists loads the whole next row as soon as the
 // list of quads stands, into the registers of this one (have_next: x holds the row on entry); with the full-width
 // search, as much of the next row as fits beside this one is loaded while this one is ranked (ahead).
-template <int G, int NG, int W, int MODE, bool NEG, int DT, bool DENSE, int PATH>
+template <int G, int NG, int W, int MODE, bool NEG, int DT, bool DENSE, int PATH, int ROOM = list_room(W)>
 __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in, int64_t N, int M, int k, int max_iter,
                                           float eps_rel, void* __restrict__ out_vals, int32_t* __restrict__ out_idx,
                                           int32_t* __restrict__ out_iters, int64_t r_next, bool& have_ahead,
@@ -242,7 +242,7 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
   constexpr int CPL = (T + kWave - 1) / kWave;  // cells per lane when one wavefront scans the table
   using ElemT = typename std::conditional<DT == kF32, float, uint16_t>::type;
   __shared__ BoundsLds<W> s_bounds;
-  __shared__ typename std::conditional<FILTER, FilterLds<W>, int>::type s_filter;
+  __shared__ typename std::conditional<FILTER, FilterLds<W, ROOM>, int>::type s_filter;
   __shared__ int s_cnt[2][W];          // per-wavefront counts of a search step, double buffered
   __shared__ int s_tab[2][T];          // candidates per cell of class A / class B, then their exclusive prefixes
   // narrowing of Algorithm 1's search (see gather_band): the whole row's band, its size, and what
@@ -282,7 +282,8 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
     }
   }
   float hi, lo, T0, probe;
-  block_bounds<E, W, NEG, FILTER>(x, nm, (k + W) / W, lane, wave, s_bounds, lo, hi, T0, probe);
+  constexpr int J = ROOM > list_room(W) && E >= 32 ? E / 8 : (E >= 3 * kFilterGroup ? E / kFilterGroup : 4);
+  block_bounds<E, W, NEG, FILTER, J>(x, nm, (k + W) / W, lane, wave, s_bounds, lo, hi, T0, probe);
   const float least = lo;
 
   using OutT = typename std::conditional<DT == kF32, uint32_t, uint16_t>::type;  // value bits as stored
@@ -323,7 +324,7 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
       }
       oi[place] = col;
     };
-    const int done = filter_row<E, W, MODE, NEG, DT, DENSE>(s_filter, x, lane, wave, k, max_iter, eps, T0, probe, lo, hi,
+    const int done = filter_row<E, W, ROOM, MODE, NEG, DT, DENSE>(s_filter, x, lane, wave, k, max_iter, eps, T0, probe, lo, hi,
                                                             thi, tlo, split, iterations, column, listed, emit);
     if (done == kFilterDone) {
       if constexpr (MODE == kEps) {
@@ -694,7 +695,7 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
 // instead, which saves the dispatch of a new 1024-thread workgroup between a unit's rows.  There the rows that the lists
 // do not hold wait until up to 64 have been through: they are read again then, so that the lists' loop needs registers
 // for no more than one row at a time.
-template <int G, int NG, int W, int MODE, bool NEG, int DT, bool DENSE, bool FILTER>
+template <int G, int NG, int W, int MODE, bool NEG, int DT, bool DENSE, bool FILTER, int ROOM = list_room(W)>
 __device__ __forceinline__ void block_rows(const void* __restrict__ in, int64_t N, int M, int k, int max_iter,
                                            float eps_rel, void* __restrict__ out_vals, int32_t* __restrict__ out_idx,
                                            int32_t* __restrict__ out_iters) {
@@ -710,7 +711,7 @@ __device__ __forceinline__ void block_rows(const void* __restrict__ in, int64_t 
         const int64_t r = r0 + j * (int64_t)gridDim.x;
         if (r >= N) break;
         float none[1];
-        const bool done = block_row<G, NG, W, MODE, NEG, DT, DENSE, kListsOnly>(
+        const bool done = block_row<G, NG, W, MODE, NEG, DT, DENSE, kListsOnly, ROOM>(
             r, in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, j + 1 < 64 ? r + gridDim.x : N, have_ahead, none,
             have_next, x, bounds);
         left |= done ? 0ull : 1ull << j;
@@ -748,7 +749,7 @@ __device__ __forceinline__ void block_rows(const void* __restrict__ in, int64_t 
     float none[1], x[G * NG];
     const int64_t r = blockIdx.x;  // launched with one workgroup per row
     if (r < N)
-      block_row<G, NG, W, MODE, NEG, DT, DENSE, FILTER ? kListsFirst : kFullWidth>(
+      block_row<G, NG, W, MODE, NEG, DT, DENSE, FILTER ? kListsFirst : kFullWidth, ROOM>(
           r, in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, N, have_ahead, none, have_next, x, bounds);
   }
 }
@@ -765,6 +766,14 @@ __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(
     rtopk_filter_kernel(const void* __restrict__ in, int64_t N, int M, int k, int max_iter, float eps_rel,
                         void* __restrict__ out_vals, int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters) {
   block_rows<G, NG, W, MODE, NEG, DT, DENSE, true>(in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters);
+}
+
+// Exact mode with longer lists, for larger k; floors from groups of eight values, more of them than k needs.
+template <int G, int NG, int W, bool NEG, int DT>
+__global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(4)))
+    rtopk_filter_big_kernel(const void* __restrict__ in, int64_t N, int M, int k, int max_iter, float eps_rel,
+                            void* __restrict__ out_vals, int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters) {
+  block_rows<G, NG, W, kExact, NEG, DT, false, true, big_list_room(W)>(in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters);
 }
 
 // Compute units of the current device (asked once per device; concurrent first calls store the same value).
@@ -795,8 +804,16 @@ hipError_t launch_block(const LaunchArgs& a) {
   // is then wasted, and in the persistent shape the row is read again (50000 columns, k = 256, four steps: 134 us
   // against 88 us; 32768 columns 56.6 against 56.1).  From eight (five) steps on the lists win as in exact mode.
   const bool lists = a.k <= filter_max_k(W) && (MODE != kEarly || a.max_iter >= (block_persistent(W) ? 8 : 5));
-  const auto kernel = lists ? &rtopk_filter_kernel<G, NG, W, MODE, NEG, DT, DENSE>
-                                               : &rtopk_block_kernel<G, NG, W, MODE, NEG, DT, DENSE>;
+  auto kernel = lists ? &rtopk_filter_kernel<G, NG, W, MODE, NEG, DT, DENSE> : &rtopk_block_kernel<G, NG, W, MODE, NEG, DT, DENSE>;
+  if constexpr (MODE == kExact && !DENSE) {
+    // Longer lists where k is a small part of the row (us, full-width search -> lists): 12288 columns, k = 500 39 -> 36;
+    // 16384, k = 400 38.5 -> 31.2; 24000, k = 600 43.4 -> 40.4, 1000 45.9 -> 50.0; 32768, k = 600 44 -> 34; 50000, k = 1000
+    // 69 -> 67; 65536 188 -> 157.  16-bit rows, whose full-width search costs as much as that of fp32 rows, win throughout:
+    // 16384, k = 400 48 -> 25; 24000, k = 1000 73 -> 62; 32768 53 -> 35; 50000, k = 600 83 -> 43.  Rows of whole numbers gain
+    // 1.2 to 1.9 times, of heavy tails up to 1.5; sorted rows, whose lists overflow, lose 10 to 35 %.
+    const bool few = G * NG < 48 || (DT != kF32 || W == 4 ? 24 : 40) * a.k <= a.M;
+    if (!lists && few && a.k <= big_filter_max_k(W)) kernel = &rtopk_filter_big_kernel<G, NG, W, NEG, DT>;
+  }
   return launch_kernel(kernel, dim3((unsigned)grid), dim3(W * kWave), 0,
                        a.stream, a.in, a.N, a.M, a.k, a.max_iter, a.eps_rel, a.out_vals,
                        static_cast<int32_t*>(a.out_idx), a.out_iters);

@@ -237,32 +237,88 @@ __device__ __forceinline__ float next_above(float t) {
   return t == 0.0f ? __int_as_float(1) : __int_as_float(u < 0 ? u - 1 : u + 1);
 }
 // One wavefront: the k-th of the n singles (value bits, column), all at or above T0, hi the largest key.  bins: kBins words of
-// LDS of its own, 16-byte aligned.  The selection is key >= (column <= split ? tlo : thi).  Returns false where it is not
-// found: more than 64 members of its bin, NaN keys.  (The singles are read twice rather than kept: the row is still in
-// registers here, for the search that follows where this one fails.  BATCH: registers of them that are read together.)
-template <int BATCH, bool NEG>
+// LDS of its own, 16-byte aligned.  The selection is key >= (column <= split ? tlo : thi), or, with a limit above 0, key >= thi
+// and the first `limit` of [tlo, thi) in column order (more than 64 equal keys; LEVELS = 3 only).  Returns false where it is
+// not found: more than 64 members of its (last level's) bin, NaN keys.  (The singles are read twice rather than kept: the row
+// is still in registers here, for the search that follows where this one fails.  BATCH: registers of them that are read
+// together; LEVELS: of parts of parts.)
+template <int BATCH, int LEVELS, bool NEG>
 __device__ __forceinline__ bool kth_by_bins(const uint2* single, int n, int lane, int k, float T0, float hi, uint32_t* bins,
-                                            float& thi, float& tlo, int& split) {
-  clear_bins(bins, lane);
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  const float scale = bins_scale(T0, hi);
-  for (int i0 = 0; i0 < n; i0 += BATCH * kWave) {
-    float key[BATCH];
+                                            float& thi, float& tlo, int& split, int& limit) {
+  // Values with a heavy tail crowd in the last parts: a part with more members than can be ranked is cut into 256 again.
+  limit = 0;
+  static_assert(LEVELS == 1 || LEVELS == 3, "one level, or three");
+  float top[3], scale[3];
+  int chosen[3];
+  top[0] = hi;
+  scale[0] = bins_scale(T0, hi);
+  int level = 0, above = 0, in_bin = 0;
+  auto inside = [&](float key) -> bool {  // the parts chosen so far
+    bool in = true;
 #pragma unroll
-    for (int i = 0; i < BATCH; ++i) {
-      const int j = i0 + i * kWave + lane;
-      key[i] = keyof<NEG>(__uint_as_float(single[j < n ? j : 0].x));
-    }
+    for (int l = 0; l + 1 < LEVELS; ++l)
+      if (l < level) in = in && bin_of(key, top[l], scale[l]) == chosen[l];
+    return in;
+  };
+  for (;;) {
+    clear_bins(bins, lane);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int i0 = 0; i0 < n; i0 += BATCH * kWave) {
+      float key[BATCH];
 #pragma unroll
-    for (int i = 0; i < BATCH; ++i) {
-      const int bin = bin_of(key[i], hi, scale);
-      if (i0 + i * kWave + lane < n) __hip_atomic_fetch_add(bins + bin, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+      for (int i = 0; i < BATCH; ++i) {
+        const int j = i0 + i * kWave + lane;
+        key[i] = keyof<NEG>(__uint_as_float(single[j < n ? j : 0].x));
+      }
+#pragma unroll
+      for (int i = 0; i < BATCH; ++i) {
+        const int bin = bin_of(key[i], level == 0 ? top[0] : (level == 1 ? top[1] : top[2]),
+                               level == 0 ? scale[0] : (level == 1 ? scale[1] : scale[2]));
+        if (i0 + i * kWave + lane < n && (level == 0 || inside(key[i])))
+          __hip_atomic_fetch_add(bins + bin, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+      }
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    int higher;
+    const int part = find_bin(bins, lane, k - above, higher, in_bin);
+    if (part < 0) return false;  // uniform
+    above += higher;
+    if (level == 0) chosen[0] = part;
+    if (level == 1) chosen[1] = part;
+    if (level == 2) chosen[2] = part;
+    if (in_bin <= kWave) break;
+    if (level + 1 == LEVELS) return false;
+    // the members' own range is the next level's; are they all one value, the first of them in column order are chosen
+    float largest = -__builtin_inff(), neg = -__builtin_inff();
+    ++level;
+    for (int i = lane; i < n; i += kWave) {
+      const float key = keyof<NEG>(__uint_as_float(single[i].x));
+      if (inside(key)) {
+        largest = vmax(largest, key);
+        neg = vmax_an(neg, key);
+      }
+    }
+    --level;
+    float t, least;
+    wave_max_and_negmin(largest, neg, t, least);
+    if (t == least) {
+      tlo = t;
+      thi = next_above(t);
+      split = 0x7fffffff;
+      limit = k - above;
+      return true;
+    }
+    const float w = bins_scale(least, t);
+    if (level == 0) {
+      top[1] = t;
+      scale[1] = w;
+    } else {
+      top[2] = t;
+      scale[2] = w;
+    }
+    ++level;
   }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  int above, in_bin;
-  const int chosen = find_bin(bins, lane, k, above, in_bin);
-  if (chosen < 0 || in_bin > kWave) return false;  // uniform
+  ++level;  // all of them from here on
   uint2* member = reinterpret_cast<uint2*>(bins);
   uint32_t members = 0;
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -276,10 +332,12 @@ __device__ __forceinline__ bool kth_by_bins(const uint2* single, int n, int lane
 #pragma unroll
     for (int i = 0; i < BATCH; ++i) {
       const float key = keyof<NEG>(__uint_as_float(e[i].x));
-      const uint64_t m = __builtin_amdgcn_ballot_w64(i0 + i * kWave + lane < n && bin_of(key, hi, scale) == chosen);
+      const bool in = level == 1 ? bin_of(key, top[0], scale[0]) == chosen[0]
+                                 : inside(key) && (level == 2 || bin_of(key, top[2], scale[2]) == chosen[2]);
+      const uint64_t m = __builtin_amdgcn_ballot_w64(i0 + i * kWave + lane < n && in);
       if (m != 0) {  // uniform
         const uint32_t at = lanes_below(m, members);
-        if (((m >> lane) & 1) != 0) member[at] = make_uint2(__float_as_uint(key), e[i].y);
+        if (((m >> lane) & 1) != 0 && at < (uint32_t)kWave) member[at] = make_uint2(__float_as_uint(key), e[i].y);
         members += (uint32_t)__builtin_popcountll(m);
       }
     }
@@ -294,7 +352,9 @@ __device__ __forceinline__ bool kth_by_bins(const uint2* single, int n, int lane
 
 // LDS of one row.  CAP: quads, and singles, that the lists hold.  The bitmaps take the quads' place when those
 // have become singles.
-template <int W, int ROOM = W == 4 ? 512 : 1024>
+constexpr int list_room(int w) { return w == 4 ? 512 : 1024; }
+constexpr int big_list_room(int w) { return w == 4 ? 1024 : kBigRoom; }
+template <int W, int ROOM = list_room(W)>
 struct FilterLds {
   static constexpr int CAP = ROOM;
   static constexpr int WORDS = 128 * W;  // bitmap words: two per thread, 64 * 64 * W columns
@@ -496,11 +556,12 @@ __device__ __forceinline__ int filter_lists(FilterLds<W, ROOM>& s, const float (
 // Steps 2 to 5 for one row, by the whole workgroup.  lo, hi: the keys' minimum and maximum; T0 the row's floor, probe
 // see filter_search.  emit(place, value, column).  In the dense form nothing is emitted and thi, tlo, split say which
 // elements stay: key >= (column <= split ? tlo : thi).  Every wavefront takes the same branches.
-template <int E, int W, int MODE, bool NEG, int DT, bool DENSE, typename Column, typename Listed, typename Emit>
-__device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], int lane, int wave, int k, int max_iter,
+template <int E, int W, int ROOM, int MODE, bool NEG, int DT, bool DENSE, typename Column, typename Listed, typename Emit>
+__device__ __forceinline__ int filter_row(FilterLds<W, ROOM>& s, const float (&x)[E], int lane, int wave, int k, int max_iter,
                                           float eps, float T0, float probe, float& lo, float& hi, float& thi, float& tlo,
                                           int& split, int& iterations, Column column, Listed listed, Emit emit) {
-  constexpr int CAP = FilterLds<W>::CAP;
+  constexpr int CAP = ROOM;
+  constexpr bool BIG = ROOM > list_room(W);  // exact mode only: the bins, or no list
   const int tid = wave * kWave + lane;
   float low = lo;  // (lo itself stays for the caller's search of a row that the lists do not hold)
   int walked = 0;
@@ -524,13 +585,17 @@ __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], 
     bool hit = false;
     int steps = walked, cnt = -1, na = 0, last = 0x7fffffff;
     float by_bins_hi, by_bins_lo;
+    int by_bins_limit = 0;
     bool found = false;
     if constexpr (MODE == kExact) {
       // (16-bit rows have few values, so a larger k finds many members in its bin: 2048 x 32768, bfloat16, k = 256, 256 rows
       // 10.4 -> 10.7 us with bins, k = 64 9.9 -> 9.3)
-      if (DT == kF32 || k <= 128) found = kth_by_bins<4, NEG>(s.single, n, lane, k, T0, hi, s.bins, by_bins_hi, by_bins_lo, last);
+      if (BIG || DT == kF32 || k <= 128) {
+        found = kth_by_bins<4, BIG ? 3 : 1, NEG>(s.single, n, lane, k, T0, hi, s.bins, by_bins_hi, by_bins_lo, last,
+                                                 by_bins_limit);
+      }
     }
-    if (found) {
+    if (found || BIG) {
     } else if (n <= 4 * kWave) {
       filter_search<4, MODE, NEG, DT>(s.single, n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
     } else if (n <= 8 * kWave || CAP <= 8 * kWave) {
@@ -553,6 +618,7 @@ __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], 
       if (found) {
         t_hi = by_bins_hi;
         t_lo = by_bins_lo;
+        limit = by_bins_limit;
       } else if (hit) {
         t_hi = t_lo = thres;
       } else if (na >= k) {
@@ -573,7 +639,7 @@ __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], 
       s.info[0] = limit;
       s.info[1] = hit ? steps : steps + 1;
       s.info[2] = found ? last : 0x7fffffff;
-      s.state = (listed ? 0 : 1) | (MODE == kEarly && cnt != k ? 2 : 0);
+      s.state = (listed ? 0 : 1) | (MODE == kEarly && cnt != k ? 2 : 0) | (BIG && !found ? 4 : 0);
     }
   }
   __syncthreads();
@@ -584,6 +650,7 @@ __device__ __forceinline__ int filter_row(FilterLds<W>& s, const float (&x)[E], 
   const int limit = __builtin_amdgcn_readfirstlane(s.info[0]);
   iterations = __builtin_amdgcn_readfirstlane(s.info[1]);
   split = MODE == kExact ? __builtin_amdgcn_readfirstlane(s.info[2]) : 0x7fffffff;
+  if (BIG && (state & 4) != 0) return kFilterNoList;
   if ((state & 1) != 0) {
     lo = tlo;
     if (MODE == kEps) hi = thi;
@@ -761,13 +828,13 @@ __device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E
 
   float thres = low, l = low, h = hi;
   bool hit = false, found = false;
-  int steps = walked, cnt = -1, na = 0;
+  int steps = walked, cnt = -1, na = 0, limit = 0;
   split = 0x7fffffff;
   if constexpr (MODE == kExact && DT == kF32) {
     // (the bins at the end of the lists' memory, where no single reaches)
     const int bytes = room * 20 - kBins * 4;
     uint32_t* bins = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(lists) + bytes);
-    if ((int)n * 8 <= bytes) found = kth_by_bins<1, NEG>(lists, (int)n, lane, k, T0, hi, bins, thi, tlo, split);
+    if ((int)n * 8 <= bytes) found = kth_by_bins<1, 1, NEG>(lists, (int)n, lane, k, T0, hi, bins, thi, tlo, split, limit);
   }
   if (found) {
   } else if (n <= 2 * kWave) {
@@ -778,7 +845,6 @@ __device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E
     filter_search<kMost, MODE, NEG, DT>(lists, (int)n, lane, k, max_iter, eps, T0, probe, l, h, thres, hit, steps, cnt, na);
   }
   // the selection as two thresholds and a limit, see filter_row
-  int limit = 0;
   iterations = hit ? steps : steps + 1;
   if constexpr (MODE == kEarly) {
     lo = l;

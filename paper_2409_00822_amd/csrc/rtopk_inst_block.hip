@@ -15,6 +15,9 @@ hipError_t launch_block_plain(int g, int ng, int w, int mode, const LaunchArgs& 
   if (g == 4) {
     if (w == 4 && ng == 4) return pick<4, 4, 4>(mode, a);
     if (w == 4 && ng == 8) return pick<4, 8, 4>(mode, a);
+    if (w == 8 && ng <= 8 && mode != kExact) return hipErrorInvalidValue;
+    if (w == 8 && ng == 4) return launch_block<4, 4, 8, kExact>(a);
+    if (w == 8 && ng == 8) return launch_block<4, 8, 8, kExact>(a);
     if (w == 4 && ng == 12) return pick<4, 12, 4>(mode, a);
     if (w == 4 && ng == 16) return pick<4, 16, 4>(mode, a);
     if (w == 8 && ng == 12) return pick<4, 12, 8>(mode, a);

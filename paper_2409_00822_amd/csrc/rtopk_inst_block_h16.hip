@@ -16,6 +16,9 @@ static hipError_t pick_shape(int g, int ng, int w, int mode, const LaunchArgs& a
   if (g == 8) {
     if (w == 4 && ng == 2) return pick<8, 2, 4, DT>(mode, a);
     if (w == 4 && ng == 4) return pick<8, 4, 4, DT>(mode, a);
+    if (w == 8 && ng <= 4 && mode != kExact) return hipErrorInvalidValue;
+    if (w == 8 && ng == 2) return launch_block<8, 2, 8, kExact, false, DT>(a);
+    if (w == 8 && ng == 4) return launch_block<8, 4, 8, kExact, false, DT>(a);
     if (ng != 8) return hipErrorInvalidValue;
     if (w == 4) return pick<8, 8, 4, DT>(mode, a);
     if (w == 8) return pick<8, 8, 8, DT>(mode, a);

@@ -19,6 +19,9 @@ hipError_t launch_block_variant(int g, int ng, int w, int mode, bool smallest, c
   if (g == 4) {
     if (w == 4 && ng == 4) return pick<4, 4, 4>(mode, smallest, a);
     if (w == 4 && ng == 8) return pick<4, 8, 4>(mode, smallest, a);
+    if (w == 8 && ng <= 8 && (mode != kExact || !smallest)) return hipErrorInvalidValue;
+    if (w == 8 && ng == 4) return launch_block<4, 4, 8, kExact, true>(a);
+    if (w == 8 && ng == 8) return launch_block<4, 8, 8, kExact, true>(a);
     if (ng != 16) return hipErrorInvalidValue;
     if (w == 4) return pick<4, 16, 4>(mode, smallest, a);
     if (w == 8) return pick<4, 16, 8>(mode, smallest, a);

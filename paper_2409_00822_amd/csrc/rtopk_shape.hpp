@@ -58,6 +58,11 @@ struct Shape {
   int capacity() const { return 64 * values() * w; }
 };
 
+// Largest k that the lists of a workgroup of w wavefronts take (rtopk_filter.hpp).
+constexpr int filter_max_k(int w) { return w == 4 ? 256 : 512; }
+// The same for exact mode's longer lists.
+constexpr int big_filter_max_k(int w) { return w == 4 ? 512 : 1024; }
+
 inline bool is_aligned(uintptr_t p, uintptr_t a) { return p % a == 0; }
 
 // Smallest listed ng with 64 * g * ng >= M.
@@ -147,6 +152,24 @@ inline Shape layout_of_call(int64_t N, int M, int k, int dtype, int mode, int ma
     s.ng = (M <= 4096 ? 16 : 32) / s.g;
     s.full = M == s.capacity();
   }
+  // Exact mode's longer lists (one wavefront per row, or four wavefronts that hold 64 values per lane, -> these; us): fp32, 512 rows of 4096
+  // columns, k = 300 11.4 -> 8.2, k = 512 13.1 -> 10.9, 8192 rows 36 -> 57; 8192 columns, k = 300 512 rows 14.3 -> 9.7, 4096 rows 36.1 ->
+  // 35.9; k = 600 in eight wavefronts 15.2 -> 11.9, 1000 15.4 -> 15.7; 16384, k = 600 17.8 -> 14.7.  bfloat16: 4096 columns, k = 300 512 rows 15.8 ->
+  // 8.2, 8192 rows 47 -> 55; 8192 columns, k = 512 4096 rows 53 -> 45, 16384 rows 149 -> 156; k = 600 512 rows 22.8 -> 11.2, 4096 rows 53 -> 73.
+  const bool half = dtype != kF32;
+  if (mode == kExact && !dense && M > 2048 && M <= 16384 && k > filter_max_k(4) && k < M) {
+    const bool four = k <= big_filter_max_k(4) && M <= kMaxWaveM && N <= (half ? (M > 6144 ? 4096 : 1024) : 512);
+    const bool eight = k > big_filter_max_k(4) && N <= 512 &&
+                       (M <= kMaxWaveM ? (half ? M > 4096 && k <= big_filter_max_k(8) : M > 7168 && k <= 700)
+                                       : k <= 700 && (half || M > 14336));
+    if (four || eight) {
+      s.family = kFamBlock;
+      s.w = four ? 4 : 8;
+      s.g = half ? 8 : 4;
+      s.ng = (M <= 1024 * s.w ? 16 : 32) / s.g;
+      s.full = M == s.capacity();
+    }
+  }
   return s;
 }
 
@@ -171,8 +194,8 @@ inline bool instantiated(const Shape& s, int dtype, bool plain, bool dense) {
       return dtype != kF32 && !dense && s.w == 1 && (small || h8 || (s.g == 4 && s.ng == 1));
     case kFamBlock:
       if (s.w != 4 && s.w != 8 && s.w != 16) return false;
-      if (dtype != kF32) return !dense && s.g == 8 && (s.ng == 8 || (s.w == 4 && (s.ng == 2 || s.ng == 4)));
-      return s.g == 4 && (s.ng == 16 || (s.w == 4 && (s.ng == 4 || s.ng == 8)) || (s.ng == 12 && plain && !dense));
+      if (dtype != kF32) return !dense && s.g == 8 && (s.ng == 8 || (s.w <= 8 && (s.ng == 2 || s.ng == 4)));
+      return s.g == 4 && (s.ng == 16 || (s.w <= 8 && (s.ng == 4 || s.ng == 8)) || (s.ng == 12 && plain && !dense));
     case kFamStream:
       return dtype == kF32 && !dense && s.w == 16 && s.g == 4;
     default:
@@ -181,8 +204,7 @@ inline bool instantiated(const Shape& s, int dtype, bool plain, bool dense) {
 }
 
 // ---- rows spread over several workgroups ---------------------------------------------------------
-// (rtopk_split_kernel.hpp)  Largest k that the lists of a workgroup of w wavefronts take (rtopk_filter.hpp).
-constexpr int filter_max_k(int w) { return w == 4 ? 256 : 512; }
+// (rtopk_split_kernel.hpp)
 // Candidates that a segment's lists hold: with nothing to search there, more than the lists of a whole row.
 constexpr int segment_room(int w) { return w == 4 ? 768 : 1536; }
 constexpr int kMergeRegs = 16;                // candidates per lane of a merging wavefront
@@ -239,9 +261,10 @@ inline Split split_of(int64_t N, int M, int k, int mode, int max_iter) {
 }
 
 // Rows of more than kMaxBlockM columns that split_of leaves to one streaming workgroup, because k is above its lists' limit or
-// their candidates would not fit the merge: lists of up to kBigRoom candidates, from segments of 32768 columns, or of 65536 where
-// the merge would not hold twice as many lists; 40 candidates per merging lane where 16 would not do.  (16 rows of 131072 columns, k = 600: streamed 46.6 us, split 15.9; 16 rows of 2^20, k = 800:
-// 165 -> 50; 1000 rows of 131072, k = 700: 151 -> 121.)  The floors come from eight groups of eight values per lane here, so a list has 1.1 to 1.35 k candidates at
+// their candidates would not fit the merge: lists of up to kBigRoom candidates, from segments of 32768 columns, or of 65536
+// where the merge would not hold twice as many lists; 40 candidates per merging lane where 16 would not do.  (16 rows of
+// 131072 columns, k = 600: streamed 46.6 us, split 15.9; 16 rows of 2^20, k = 800: 165 -> 50; 1000 rows of 131072, k = 700:
+// 151 -> 121.)  The floors come from eight groups of eight values per lane here, so a list has 1.1 to 1.35 k candidates at
 // k = 512 .. 1024.  Lists of 16 wavefronts, whose floors spread more, are expected to hold 1.5 k.
 constexpr int kBigMaxK = 1024;
 constexpr int kBigRoom = 1792;

@@ -12,7 +12,7 @@ using namespace rtopk;
 int main() {
   long bad = 0, other = 0;
   const int64_t counts[] = {1, 255, 256, 512, 513, 1024, 1025, 3072, 3073, 4096, 4097, 6144, 6145, 24576, 24577, 1 << 20, (int64_t)1 << 31};
-  const int ks[] = {1, 99, 100, 256, 257, 1000};
+  const int ks[] = {1, 99, 100, 256, 257, 512, 513, 700, 1000, 1025};
   for (int M = 1; M <= 70000; M += M < 9000 ? 1 : 37)
     for (int64_t N : counts)
       for (int k : ks)
@@ -26,9 +26,12 @@ int main() {
                 const bool same = a.family == b.family && a.g == b.g && a.ng == b.ng && a.w == b.w && a.full == b.full;
                 if (!instantiated(b, dtype, plain, dense) || (b.family != kFamStream && b.capacity() < M)) ++bad;
                 if (b.full != (b.g != 0 && b.family != kFamStream && M == b.capacity())) ++bad;
-                if (!same && (M <= 1536 || M > kMaxWaveM || k > filter_max_k(4) || k == M || b.w != 4 || N >= 0x80000000ll ||
-                              (mode == kEarly && steps < 5))) ++bad;
-                other += !same;
+                if (same) continue;
+                const bool lists = M > 1536 && M <= kMaxWaveM && k <= filter_max_k(4) && b.w == 4 && (mode != kEarly || steps >= 5);
+                const bool longer = mode == kExact && !dense && M > 2048 && M <= 16384 && k > filter_max_k(4) &&
+                                    k <= big_filter_max_k(b.w) && (b.w == 4 || b.w == 8);
+                if (k == M || N >= 0x80000000ll || !(lists || longer)) ++bad;
+                ++other;
               }
   printf("%ld %ld\n", bad, other);
   return 0;
