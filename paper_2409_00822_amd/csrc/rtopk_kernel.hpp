@@ -584,6 +584,16 @@ __device__ __forceinline__ float midpoint_exact(float lo, float hi) {
 // lowest value is -inf, which columns past the row's end would reach too.
 __device__ __forceinline__ float not_below(float lo, float least) { return lo < least ? least : lo; }
 
+// Whether every midpoint of Algorithm 1 lies strictly between its bounds as long as hi - lo > eps, so that the search needs no
+// other guard.  With A = max(|lo|, |hi|) for the first bounds, all later bounds, their sums' halves and the distances' rounding
+// errors are within A and ulp(A) / 2, ulp(A) <= A * 2^-23: a difference that rounds to more than A * 2^-21 is more than 3.9 ulp(A),
+// and its midpoint, with an error of at most ulp(A) / 2, is more than one ulp(A) inside.  Sums stay finite (A < 2^126) and
+// halves exact where it matters (A > 2^-60).  False for NaN.
+__device__ __forceinline__ bool eps_outside_rounding(float lo, float hi, float eps) {
+  const float a = __builtin_fmaxf(__builtin_fabsf(lo), __builtin_fabsf(hi));
+  return eps >= a * 0x1p-21f && a < 0x1p126f && a > 0x1p-60f && lo <= hi;
+}
+
 // In the lanes whose bit is set in `mask` (a subset of the active lanes): LDS[addr] = v.
 __device__ __forceinline__ void lds_store_masked(uint64_t mask, uint32_t addr, float v) {
   uint64_t saved;
@@ -1049,12 +1059,22 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
     bool hit = false;
     float thres = lo;
     int steps = bounds_known ? known_iterations - 1 : 0;
+    bool searched = bounds_known;
+    // The generated loop where the guard on the midpoint cannot fire; its scalar and vector work, beside which the rest is
+    // small, bounds these widths (precision 1e-4, 262144 rows, C++ loop -> this: 64 columns, k = 16 51 -> 36 us; 128 64 -> 45; 256,
+    // k = 32 84 -> 64; 333 122 -> 98; 512, k = 64 149 -> 120; 64 rows of 256 4.9 -> 3.3).
+    if constexpr (ASM && !NEG) {
+      if (eps_outside_rounding(lo, hi, eps)) {
+        hit = search_eps_asm(x, lo, hi, k, eps, m, steps);
+        searched = true;
+      }
+    }
     // narrowing as in the exact mode: same thresholds and counts, hence the same exit iteration
     constexpr bool NARROW = narrows(E, MODE);
     int cnt_lo = M, cnt_hi = 0, above = 0;
     bool narrow = false;
     float band[BR];
-    while (!bounds_known && hi - lo > eps) {
+    while (!searched && hi - lo > eps) {
       const float mid = (lo + hi) * 0.5f;
       if (!(mid > lo && mid < hi)) break;
       thres = mid;
