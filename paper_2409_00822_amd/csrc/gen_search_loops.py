@@ -145,20 +145,31 @@ __device__ __forceinline__ int search_early_asm(const float (&x)[{E}], float& lo
 
 
 def gen_eps(E):
-    L = ['"s_mov_b32 %[hit], 0\\n\\t"',
-         '".Lrtopk_top_%=:\\n\\t"', '"v_sub_f32 %[u], %[hi], %[lo]\\n\\t"', '"v_add_f32 %[t], %[lo], %[hi]\\n\\t"',
-         '"v_cmp_gt_f32 vcc, %[u], %[eps]\\n\\t"', '"v_mul_f32 %[t], 0.5, %[t]\\n\\t"', '"s_cbranch_vccz .Lrtopk_end_%=\\n\\t"']
-    L += count_lines(E, "t", False)
-    L += ['"v_add_u32 %[n], 1, %[n]\\n\\t"',  # (on the vector unit, which has time here)
-          compare(E, 0, "lt"), branch(E, 0, True, ".Lrtopk_less_%="),
-          compare(E, 0, "gt"), '"v_mov_b32 %[lo], %[t]\\n\\t"', branch(E, 0, True, ".Lrtopk_top_%="),
-          '"s_mov_b32 %[hit], 1\\n\\t"', '"s_branch .Lrtopk_end_%=\\n\\t"',
-          '".Lrtopk_less_%=:\\n\\t"', '"v_mov_b32 %[hi], %[t]\\n\\t"', '"s_branch .Lrtopk_top_%=\\n\\t"', '".Lrtopk_end_%=:"']
-    outs, ins = operands(E, ['[t] "=&v"(t)', '[u] "=&v"(u)', '[n] "+v"(n)', '[hit] "=&s"(hit)'], ['[eps] "v"(eps)'])
-    return (f"""// Algorithm 1 with precision eps, {E} values per lane, where every midpoint lies strictly between the bounds as long as
-// hi - lo > eps (see eps_outside_rounding).  Returns true when a step counted exactly k (m[] then selects the answer); steps:
-// the midpoints evaluated.
-__device__ __forceinline__ bool search_eps_asm(const float (&x)[{E}], float& lo, float& hi, int k, float eps,
+    def loop(name, guarded):
+        top, less = f".Lrtopk_{name}_%=", f".Lrtopk_{name}less_%="
+        out = [f'"{top}:\\n\\t"', '"v_sub_f32 %[u], %[hi], %[lo]\\n\\t"', '"v_add_f32 %[t], %[lo], %[hi]\\n\\t"',
+               '"v_cmp_gt_f32 vcc, %[u], %[eps]\\n\\t"', '"v_mul_f32 %[t], 0.5, %[t]\\n\\t"', '"s_cbranch_vccz .Lrtopk_end_%=\\n\\t"']
+        if guarded:
+            out += ['"v_cmp_gt_f32 vcc, %[t], %[lo]\\n\\t"', '"s_cbranch_vccz .Lrtopk_end_%=\\n\\t"',
+                    '"v_cmp_lt_f32 vcc, %[t], %[hi]\\n\\t"', '"s_cbranch_vccz .Lrtopk_end_%=\\n\\t"']
+        out += count_lines(E, "t", False)
+        out += ['"v_add_u32 %[n], 1, %[n]\\n\\t"',  # (on the vector unit, which has time here)
+                compare(E, 0, "lt"), branch(E, 0, True, less),
+                compare(E, 0, "gt"), '"v_mov_b32 %[lo], %[t]\\n\\t"', branch(E, 0, True, top),
+                '"s_mov_b32 %[hit], 1\\n\\t"', '"s_branch .Lrtopk_end_%=\\n\\t"',
+                f'"{less}:\\n\\t"', '"v_mov_b32 %[hi], %[t]\\n\\t"', f'"s_branch {top}\\n\\t"']
+        return out
+
+    L = ['"s_mov_b32 %[hit], 0\\n\\t"', '"v_cmp_ge_f32 vcc, %[eps], %[least]\\n\\t"', '"s_cbranch_vccz .Lrtopk_g_%=\\n\\t"']
+    L += loop("p", False)
+    L += ["// ---- the same, also ending where the midpoint is not strictly between the bounds"] + loop("g", True)
+    L += ['".Lrtopk_end_%=:"']
+    outs, ins = operands(E, ['[t] "=&v"(t)', '[u] "=&v"(u)', '[n] "+v"(n)', '[hit] "=&s"(hit)'],
+                         ['[eps] "v"(eps)', '[least] "v"(least)'])
+    return (f"""// Algorithm 1 with precision eps, {E} values per lane, while hi - lo > eps and the midpoint lies strictly between the bounds,
+// as it always does with eps at or above `least` (see eps_above_rounding).  Returns true when a step counted exactly k (m[] then
+// selects the answer); steps: the midpoints evaluated.
+__device__ __forceinline__ bool search_eps_asm(const float (&x)[{E}], float& lo, float& hi, int k, float eps, float least,
                                                uint64_t (&m)[{E}], int& steps) {{
   float t, u;
   int c0, c1, c2, c3, hit, n = 0;
@@ -166,6 +177,7 @@ __device__ __forceinline__ bool search_eps_asm(const float (&x)[{E}], float& lo,
             "  lo = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(lo)));  // wave-uniform for the compiler, too\n"
             "  hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(hi)));\n"
             "  return hit != 0;\n}\n")
+
 
 # ---------------------------------------------------------------------------------------------------
 # Row minima and maxima of R rows in one transposed reduction.
@@ -280,6 +292,7 @@ def main():
         for dt in (1, 2):
             text += gen_exact(E, False, dt) + "\n"
         text += gen_early(E, False, 1) + "\n"
+    for E in ELEMS + (12,):
         text += gen_eps(E) + "\n"
     for R in (2, 4, 8):
         text += gen_minmax(R) + "\n"

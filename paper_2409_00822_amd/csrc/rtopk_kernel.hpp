@@ -584,14 +584,14 @@ __device__ __forceinline__ float midpoint_exact(float lo, float hi) {
 // lowest value is -inf, which columns past the row's end would reach too.
 __device__ __forceinline__ float not_below(float lo, float least) { return lo < least ? least : lo; }
 
-// Whether every midpoint of Algorithm 1 lies strictly between its bounds as long as hi - lo > eps, so that the search needs no
-// other guard.  With A = max(|lo|, |hi|) for the first bounds, all later bounds, their sums' halves and the distances' rounding
-// errors are within A and ulp(A) / 2, ulp(A) <= A * 2^-23: a difference that rounds to more than A * 2^-21 is more than 3.9 ulp(A),
-// and its midpoint, with an error of at most ulp(A) / 2, is more than one ulp(A) inside.  Sums stay finite (A < 2^126) and
-// halves exact where it matters (A > 2^-60).  False for NaN.
-__device__ __forceinline__ bool eps_outside_rounding(float lo, float hi, float eps) {
+// The least precision eps with which every midpoint of Algorithm 1 lies strictly between its bounds as long as hi - lo > eps,
+// so that the search needs no other guard; infinity where there is none.  With A = max(|lo|, |hi|) for the first bounds, all
+// later bounds, their sums' halves and the distances' rounding errors are within A and ulp(A) / 2, ulp(A) <= A * 2^-23: a
+// difference that rounds to more than A * 2^-21 is more than 3.9 ulp(A), and its midpoint, with an error of at most ulp(A) / 2,
+// is more than one ulp(A) inside.  Sums stay finite (A < 2^126) and halves exact where it matters (A > 2^-60).
+__device__ __forceinline__ float eps_above_rounding(float lo, float hi) {
   const float a = __builtin_fmaxf(__builtin_fabsf(lo), __builtin_fabsf(hi));
-  return eps >= a * 0x1p-21f && a < 0x1p126f && a > 0x1p-60f && lo <= hi;
+  return a < 0x1p126f && a > 0x1p-60f && lo <= hi ? a * 0x1p-21f : __builtin_inff();
 }
 
 // In the lanes whose bit is set in `mask` (a subset of the active lanes): LDS[addr] = v.
@@ -870,8 +870,8 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
     }
   });
 
-  constexpr bool ASM = E <= 8;  // hand-scheduled loops exist for these widths
-  constexpr bool KEEP = E <= 8;                       // masks of the last step stay in scalar registers
+  constexpr bool ASM = E <= 8 || (MODE == kEps && E == 12);  // hand-scheduled loops exist for these widths
+  constexpr bool KEEP = ASM;                                 // masks of the last step stay in scalar registers
   // wider rows: ACC of the E elements are counted per lane, the rest by mask popcount
   constexpr int ACC = KEEP ? 0 : RTOPK_ACC_OF(E);
   constexpr int BR = band_regs(E);  // registers per lane of a gathered band (see gather_band)
@@ -1059,45 +1059,42 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
     bool hit = false;
     float thres = lo;
     int steps = bounds_known ? known_iterations - 1 : 0;
-    bool searched = bounds_known;
-    // The generated loop where the guard on the midpoint cannot fire; its scalar and vector work, beside which the rest is
-    // small, bounds these widths (precision 1e-4, 262144 rows, C++ loop -> this: 64 columns, k = 16 51 -> 36 us; 128 64 -> 45; 256,
-    // k = 32 84 -> 64; 333 122 -> 98; 512, k = 64 149 -> 120; 64 rows of 256 4.9 -> 3.3).
     if constexpr (ASM && !NEG) {
-      if (eps_outside_rounding(lo, hi, eps)) {
-        hit = search_eps_asm(x, lo, hi, k, eps, m, steps);
-        searched = true;
-      }
-    }
-    // narrowing as in the exact mode: same thresholds and counts, hence the same exit iteration
-    constexpr bool NARROW = narrows(E, MODE);
-    int cnt_lo = M, cnt_hi = 0, above = 0;
-    bool narrow = false;
-    float band[BR];
-    while (!searched && hi - lo > eps) {
-      const float mid = (lo + hi) * 0.5f;
-      if (!(mid > lo && mid < hi)) break;
-      thres = mid;
-      ++steps;
-      int cnt;
-      if (NARROW && narrow) {
-        cnt = above + count_band<NEG, BR>(band, thres);
-      } else {
-        cnt = count(thres);
-      }
-      if (cnt == k) {
-        hit = true;
-        break;
-      }
-      move_bound(lo, hi, thres, cnt, k);
-      if constexpr (NARROW) {
-        if (!narrow) {
-          note_bound(cnt);
-          cnt_lo = cnt < k ? cnt_lo : cnt;
-          cnt_hi = cnt < k ? cnt : cnt_hi;
-          if (cnt_lo - cnt_hi <= BR * kWave) {
-            above = gather(band);
-            narrow = true;
+      // The generated loop; its scalar and vector work bounds these widths (precision 1e-4, 262144 rows, C++ loop -> this: 64
+      // columns, k = 16 51 -> 33 us; 128 64 -> 42; 256, k = 32 84 -> 61; 333 122 -> 92; 512, k = 64 149 -> 112; 768, k = 96 190 ->
+      // 164, with its guards on the midpoint 172; 64 rows of 256 4.9 -> 3.2, of 768 9.2 -> 4.1).
+      hit = search_eps_asm(x, lo, hi, k, eps, eps_above_rounding(lo, hi), m, steps);
+    } else {
+      // narrowing as in the exact mode: same thresholds and counts, hence the same exit iteration
+      constexpr bool NARROW = narrows(E, MODE);
+      int cnt_lo = M, cnt_hi = 0, above = 0;
+      bool narrow = false;
+      float band[BR];
+      while (!bounds_known && hi - lo > eps) {
+        const float mid = (lo + hi) * 0.5f;
+        if (!(mid > lo && mid < hi)) break;
+        thres = mid;
+        ++steps;
+        int cnt;
+        if (NARROW && narrow) {
+          cnt = above + count_band<NEG, BR>(band, thres);
+        } else {
+          cnt = count(thres);
+        }
+        if (cnt == k) {
+          hit = true;
+          break;
+        }
+        move_bound(lo, hi, thres, cnt, k);
+        if constexpr (NARROW) {
+          if (!narrow) {
+            note_bound(cnt);
+            cnt_lo = cnt < k ? cnt_lo : cnt;
+            cnt_hi = cnt < k ? cnt : cnt_hi;
+            if (cnt_lo - cnt_hi <= BR * kWave) {
+              above = gather(band);
+              narrow = true;
+            }
           }
         }
       }

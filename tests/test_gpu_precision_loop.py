@@ -1,4 +1,4 @@
-"""GPU parity of the precision-bounded mode at one to eight values per lane: rows whose midpoints cannot round onto a bound
+"""GPU parity of the precision-bounded mode at one to eight and at twelve values per lane: rows whose midpoints cannot round onto a bound
 (one loop without that guard), and rows on the other side of that line -- precisions at and below it, values near the type's
 limits, a maximum far smaller than the minimum's magnitude.
 
@@ -34,7 +34,7 @@ def _rows(M):
     return x
 
 
-@pytest.mark.parametrize("M", [17, 64, 65, 128, 150, 192, 200, 256, 300, 333, 384, 400, 448, 500, 512])
+@pytest.mark.parametrize("M", [17, 64, 65, 128, 150, 192, 200, 256, 300, 333, 384, 400, 448, 500, 512, 513, 600, 768])
 @pytest.mark.parametrize("eps_rel", [0.0, 1e-7, 2.0**-21, 2.0**-20, 1e-6, 1e-4, 1e-2, 0.3])
 def test_iterations_and_selection(M, eps_rel):
     R = _gpu()
