@@ -581,7 +581,7 @@ __device__ __forceinline__ float midpoint_exact(float lo, float hi) {
   }
 }
 // A bound that a search has left below the row's smallest key `least`, put back to it: the sum of two bounds near the type's
-// lowest value is -inf, which columns past the row's end would reach too.
+// lowest value is -inf, which columns past the row's end would reach too (where they are keys of -inf).
 __device__ __forceinline__ float not_below(float lo, float least) { return lo < least ? least : lo; }
 
 // The least precision eps with which every midpoint of Algorithm 1 lies strictly between its bounds as long as hi - lo > eps,
@@ -859,19 +859,23 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
   float lo = NEG ? -row_max : row_min;
   float hi = NEG ? -row_min : row_max;
 
-  // From here on columns past M must never be counted or chosen: a key of -inf is below every threshold.
+  constexpr bool ASM = E <= 8 || (MODE == kEps && E == 12);  // hand-scheduled loops exist for these widths
+  constexpr bool KEEP = ASM;                                 // masks of the last step stay in scalar registers
+
+  // From here on columns past M must never be counted or chosen.  Where all counts and selections compare "at or above", a
+  // NaN is at or above no threshold whatever; a key of -inf, which the sign tests of wider rows and the group maxima of
+  // their lists need, is below every threshold but -inf (see not_below).
+  constexpr float kNone = KEEP ? __builtin_nanf("") : (NEG ? __builtin_inff() : -__builtin_inff());
   float x[E];
   static_for<L::GROUPS>([&](auto gc) {
     constexpr int g = decltype(gc)::value;
 #pragma unroll
     for (int c = 0; c < L::width(g); ++c) {
       const int e = L::first(g) + c;
-      x[e] = element_valid<G, NG, FULL>(g, c, lane, M) ? xin[e] : (NEG ? __builtin_inff() : -__builtin_inff());  // key -inf
+      x[e] = element_valid<G, NG, FULL>(g, c, lane, M) ? xin[e] : kNone;
     }
   });
 
-  constexpr bool ASM = E <= 8 || (MODE == kEps && E == 12);  // hand-scheduled loops exist for these widths
-  constexpr bool KEEP = ASM;                                 // masks of the last step stay in scalar registers
   // wider rows: ACC of the E elements are counted per lane, the rest by mask popcount
   constexpr int ACC = KEEP ? 0 : RTOPK_ACC_OF(E);
   constexpr int BR = band_regs(E);  // registers per lane of a gathered band (see gather_band)
@@ -1038,7 +1042,7 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
     if (hit) {
       emit_selection<G, NG, FULL, false, !KEEP, NEG, DENSE>(x, m, thres, thres, -1, lane, M, k, stage_addr, y);
     } else {
-      if constexpr (!FULL) lo = not_below(lo, NEG ? -row_max : row_min);
+      if constexpr (!FULL && !KEEP) lo = not_below(lo, NEG ? -row_max : row_min);
       // Everything >= hi is taken first (cut at k by column when hi is still the row maximum and k
       // or more tie there); the first k - na members of [lo, hi) follow: all columns up to the
       // (k - na)-th member's column select against lo, the others against hi.
@@ -1148,7 +1152,7 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
         }
       }
     }
-    if constexpr (!FULL) lo = not_below(lo, NEG ? -row_max : row_min);
+    if constexpr (!FULL && !KEEP) lo = not_below(lo, NEG ? -row_max : row_min);
     // The last step lowered hi (or none ran): the kept masks are not those of lo, so they are formed
     // again.  Wide rows keep no masks and rank against lo directly; only when the last step counted
     // exactly k can they skip the cut.
