@@ -171,7 +171,7 @@ __device__ __forceinline__ void block_mask(float (&x)[G * NG], int M, int lane, 
 }
 
 // Minimum and maximum of the row's keys and, with FILTER, its floor (rtopk_filter.hpp: at least `need` group maxima of
-// every wavefront, J per lane, at or above it) and the bound above it: per lane, per wavefront, then over the W wavefronts through
+// the wavefront, J per lane, at or above it) and the bound above it: per lane, per wavefront, then over the W wavefronts through
 // LDS.  Contains a barrier.  nm: the lane's negated minimum (taken before the columns past M were masked).
 template <int W>
 struct BoundsLds {
@@ -228,11 +228,12 @@ struct KnownBounds {
 // full-width search leaves the selection's lowest threshold in bounds.lo).  Every wavefront leaves through the
 // same return statement.  A workgroup that walks several rows through the lists loads the whole next row as soon as the
 // list of quads stands, into the registers of this one (have_next: x holds the row on entry); with the full-width
-// search, as much of the next row as fits beside this one is loaded while this one is ranked (ahead).
+// search, as much of the next row as fits beside this one is loaded while this one is ranked (ahead).  shares: floor_shares(); with
+// kListsOnly the wavefront's own share.
 template <int G, int NG, int W, int MODE, bool NEG, int DT, bool DENSE, int PATH, int ROOM = list_room(W)>
 __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in, int64_t N, int M, int k, int max_iter,
                                           float eps_rel, void* __restrict__ out_vals, int32_t* __restrict__ out_idx,
-                                          int32_t* __restrict__ out_iters, int64_t r_next, bool& have_ahead,
+                                          int32_t* __restrict__ out_iters, uint32_t shares, int64_t r_next, bool& have_ahead,
                                           float (&ahead)[block_groups_ahead(W, G, PATH) * G + 1], bool& have_next,
                                           float (&x)[G * NG], KnownBounds& bounds) {
   static_assert(!DENSE || DT == kF32, "the dense form is built for fp32 rows");
@@ -270,6 +271,13 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
     block_load<DT, G, W, AHEAD, NG>(row, M, lane, wave, x);
   }
   have_next = false;
+  int need = 0;
+  if constexpr (PATH == kListsFirst) {
+    need = floor_share(M, G, W, wave, shares);
+    asm volatile("" : "+s"(need));  // here, while the loads are in flight (after them it costs 0.1 us)
+  } else if constexpr (PATH == kListsOnly) {
+    need = (int)shares;
+  }
 
   const float nm = lane_negmin<E, NEG>(x);
   block_mask<G, NG, W, NEG>(x, M, lane, wave);
@@ -282,8 +290,8 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
     }
   }
   float hi, lo, T0, probe;
-  constexpr int J = ROOM > list_room(W) && E >= 32 ? E / 8 : (E >= 3 * kFilterGroup ? E / kFilterGroup : 4);
-  block_bounds<E, W, NEG, FILTER, J>(x, nm, (k + W) / W, lane, wave, s_bounds, lo, hi, T0, probe);
+  constexpr int J = floor_groups(E, ROOM > list_room(W));
+  block_bounds<E, W, NEG, FILTER, J>(x, nm, need, lane, wave, s_bounds, lo, hi, T0, probe);
   const float least = lo;
 
   using OutT = typename std::conditional<DT == kF32, uint32_t, uint16_t>::type;  // value bits as stored
@@ -698,11 +706,13 @@ __device__ __forceinline__ bool block_row(int64_t r, const void* __restrict__ in
 template <int G, int NG, int W, int MODE, bool NEG, int DT, bool DENSE, bool FILTER, int ROOM = list_room(W)>
 __device__ __forceinline__ void block_rows(const void* __restrict__ in, int64_t N, int M, int k, int max_iter,
                                            float eps_rel, void* __restrict__ out_vals, int32_t* __restrict__ out_idx,
-                                           int32_t* __restrict__ out_iters) {
+                                           int32_t* __restrict__ out_iters, uint32_t shares) {
   bool have_ahead = false, have_next = false;
   KnownBounds bounds{};
   if constexpr (block_persistent(W) && FILTER) {
     __shared__ KnownBounds s_known[64];
+    int need = floor_share(M, G, W, __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), shares);
+    asm volatile("" : "+s"(need));  // once for all rows
     float x[G * NG];
     for (int64_t r0 = blockIdx.x; r0 < N; r0 += 64 * (int64_t)gridDim.x) {
       uint64_t left = 0;  // uniform: rows for the full-width pass
@@ -712,7 +722,7 @@ __device__ __forceinline__ void block_rows(const void* __restrict__ in, int64_t 
         if (r >= N) break;
         float none[1];
         const bool done = block_row<G, NG, W, MODE, NEG, DT, DENSE, kListsOnly, ROOM>(
-            r, in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, j + 1 < 64 ? r + gridDim.x : N, have_ahead, none,
+            r, in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, (uint32_t)need, j + 1 < 64 ? r + gridDim.x : N, have_ahead, none,
             have_next, x, bounds);
         left |= done ? 0ull : 1ull << j;
         if (!done && threadIdx.x == 0) {
@@ -733,7 +743,7 @@ __device__ __forceinline__ void block_rows(const void* __restrict__ in, int64_t 
         bounds.hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s_known[j].hi)));
         bounds.iterations = __builtin_amdgcn_readfirstlane(s_known[j].iterations);
         block_row<G, NG, W, MODE, NEG, DT, DENSE, kFullWidth>(r0 + j * (int64_t)gridDim.x, in, N, M, k, max_iter, eps_rel,
-                                                              out_vals, out_idx, out_iters, N, have_ahead, ahead, have_next, x,
+                                                              out_vals, out_idx, out_iters, 0, N, have_ahead, ahead, have_next, x,
                                                               bounds);
         __syncthreads();
       }
@@ -742,7 +752,7 @@ __device__ __forceinline__ void block_rows(const void* __restrict__ in, int64_t 
     float ahead[block_groups_ahead(W, G, kFullWidth) * G + 1], x[G * NG];
     for (int64_t r = blockIdx.x; r < N; r += gridDim.x) {
       block_row<G, NG, W, MODE, NEG, DT, DENSE, kFullWidth>(r, in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters,
-                                                            r + gridDim.x, have_ahead, ahead, have_next, x, bounds);
+                                                            0, r + gridDim.x, have_ahead, ahead, have_next, x, bounds);
       __syncthreads();  // the next row reuses the shared tables
     }
   } else {
@@ -750,7 +760,7 @@ __device__ __forceinline__ void block_rows(const void* __restrict__ in, int64_t 
     const int64_t r = blockIdx.x;  // launched with one workgroup per row
     if (r < N)
       block_row<G, NG, W, MODE, NEG, DT, DENSE, FILTER ? kListsFirst : kFullWidth, ROOM>(
-          r, in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, N, have_ahead, none, have_next, x, bounds);
+          r, in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, shares, N, have_ahead, none, have_next, x, bounds);
   }
 }
 
@@ -759,21 +769,24 @@ template <int G, int NG, int W, int MODE, bool NEG, int DT, bool DENSE>
 __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(block_persistent(W) ? 4 : 1)))
     rtopk_block_kernel(const void* __restrict__ in, int64_t N, int M, int k, int max_iter, float eps_rel,
                        void* __restrict__ out_vals, int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters) {
-  block_rows<G, NG, W, MODE, NEG, DT, DENSE, false>(in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters);
+  block_rows<G, NG, W, MODE, NEG, DT, DENSE, false>(in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, 0);
 }
 template <int G, int NG, int W, int MODE, bool NEG, int DT, bool DENSE>
 __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(block_persistent(W) ? 4 : 5)))
     rtopk_filter_kernel(const void* __restrict__ in, int64_t N, int M, int k, int max_iter, float eps_rel,
-                        void* __restrict__ out_vals, int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters) {
-  block_rows<G, NG, W, MODE, NEG, DT, DENSE, true>(in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters);
+                        void* __restrict__ out_vals, int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters,
+                        uint32_t shares) {
+  block_rows<G, NG, W, MODE, NEG, DT, DENSE, true>(in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, shares);
 }
 
 // Exact mode with longer lists, for larger k; floors from groups of eight values, more of them than k needs.
 template <int G, int NG, int W, bool NEG, int DT>
 __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(4)))
     rtopk_filter_big_kernel(const void* __restrict__ in, int64_t N, int M, int k, int max_iter, float eps_rel,
-                            void* __restrict__ out_vals, int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters) {
-  block_rows<G, NG, W, kExact, NEG, DT, false, true, big_list_room(W)>(in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters);
+                            void* __restrict__ out_vals, int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters,
+                            uint32_t shares) {
+  block_rows<G, NG, W, kExact, NEG, DT, false, true, big_list_room(W)>(in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters,
+                                                                       shares);
 }
 
 // Compute units of the current device (asked once per device; concurrent first calls store the same value).
@@ -800,23 +813,27 @@ hipError_t launch_block(const LaunchArgs& a) {
     const int64_t resident = (int64_t)compute_units() * (16 / W);  // workgroups that run at the same time
     if (resident > 0 && grid > resident) grid = resident;
   }
-  // Algorithm 2 with few steps ends on a threshold far below the k-th key, which the lists do not reach: the search
-  // is then wasted, and in the persistent shape the row is read again (50000 columns, k = 256, four steps: 134 us
-  // against 88 us; 32768 columns 56.6 against 56.1).  From eight (five) steps on the lists win as in exact mode.
-  const bool lists = a.k <= filter_max_k(W) && (MODE != kEarly || a.max_iter >= (block_persistent(W) ? 8 : 5));
-  auto kernel = lists ? &rtopk_filter_kernel<G, NG, W, MODE, NEG, DT, DENSE> : &rtopk_block_kernel<G, NG, W, MODE, NEG, DT, DENSE>;
-  if constexpr (MODE == kExact && !DENSE) {
-    // Longer lists where k is a small part of the row (us, full-width search -> lists): 12288 columns, k = 500 39 -> 36;
-    // 16384, k = 400 38.5 -> 31.2; 24000, k = 600 43.4 -> 40.4, 1000 45.9 -> 50.0; 32768, k = 600 44 -> 34; 50000, k = 1000
-    // 69 -> 67; 65536 188 -> 157.  16-bit rows, whose full-width search costs as much as that of fp32 rows, win throughout:
-    // 16384, k = 400 48 -> 25; 24000, k = 1000 73 -> 62; 32768 53 -> 35; 50000, k = 600 83 -> 43.  Rows of whole numbers gain
-    // 1.2 to 1.9 times, of heavy tails up to 1.5; sorted rows, whose lists overflow, lose 10 to 35 %.
-    const bool few = G * NG < 48 || (DT != kF32 || W == 4 ? 24 : 40) * a.k <= a.M;
-    if (!lists && few && a.k <= big_filter_max_k(W)) kernel = &rtopk_filter_big_kernel<G, NG, W, NEG, DT>;
+  constexpr int K = kSearchRow | kSearchLists | (MODE == kExact && !DENSE ? kSearchLongLists : 0);
+  static_assert(block_persistent(W) == (W == 16), "block_search knows the shape that walks its rows by its wavefronts");
+  Shape s{};
+  s.g = G;
+  s.ng = NG;
+  s.w = W;
+  const int search = block_search(s, a.M, a.k, DT, MODE, a.max_iter, DENSE);
+  auto launch = [&](auto kernel, auto... shares) {
+    return launch_kernel(kernel, dim3((unsigned)grid), dim3(W * kWave), 0, a.stream, a.in, a.N, a.M, a.k, a.max_iter, a.eps_rel,
+                         a.out_vals, static_cast<int32_t*>(a.out_idx), a.out_iters, shares...);
+  };
+  if constexpr ((K & kSearchRow) != 0) {
+    if (search == kSearchRow) return launch(&rtopk_block_kernel<G, NG, W, MODE, NEG, DT, DENSE>);
   }
-  return launch_kernel(kernel, dim3((unsigned)grid), dim3(W * kWave), 0,
-                       a.stream, a.in, a.N, a.M, a.k, a.max_iter, a.eps_rel, a.out_vals,
-                       static_cast<int32_t*>(a.out_idx), a.out_iters);
+  if constexpr ((K & kSearchLists) != 0) {
+    if (search == kSearchLists) return launch(&rtopk_filter_kernel<G, NG, W, MODE, NEG, DT, DENSE>, floor_shares(a.M, a.k, G));
+  }
+  if constexpr ((K & kSearchLongLists) != 0) {
+    if (search == kSearchLongLists) return launch(&rtopk_filter_big_kernel<G, NG, W, NEG, DT>, floor_shares(a.M, a.k, G));
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace rtopk

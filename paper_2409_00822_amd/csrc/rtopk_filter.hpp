@@ -48,8 +48,7 @@ __device__ __forceinline__ float lane_negmin(const float (&x)[E]) {
   return E % 2 == 0 ? key_max_on<!NEG>(nm, x[E - 1]) : nm;
 }
 
-// Group maxima: gm[j] = largest key of the j-th of the lane's J groups of consecutive elements.
-constexpr int kFilterGroup = 16;  // elements per group in the workgroup-per-row kernels (four groups per lane of narrower ones)
+// Group maxima: gm[j] = largest key of the j-th of the lane's J groups of consecutive elements (see floor_groups, wave_groups).
 template <int E, bool NEG, int J>
 __device__ __forceinline__ void lane_group_maxima(const float (&x)[E], float (&gm)[J]) {
   constexpr int S = E / J;
@@ -350,10 +349,8 @@ __device__ __forceinline__ bool kth_by_bins(const uint2* single, int n, int lane
   return true;
 }
 
-// LDS of one row.  CAP: quads, and singles, that the lists hold.  The bitmaps take the quads' place when those
+// LDS of one row.  CAP: quads, and singles, that the lists hold (list_room, big_list_room).  The bitmaps take the quads' place when those
 // have become singles.
-constexpr int list_room(int w) { return w == 4 ? 512 : 1024; }
-constexpr int big_list_room(int w) { return w == 4 ? 1024 : kBigRoom; }
 template <int W, int ROOM = list_room(W)>
 struct FilterLds {
   static constexpr int CAP = ROOM;

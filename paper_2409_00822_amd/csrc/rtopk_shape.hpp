@@ -62,6 +62,10 @@ struct Shape {
 constexpr int filter_max_k(int w) { return w == 4 ? 256 : 512; }
 // The same for exact mode's longer lists.
 constexpr int big_filter_max_k(int w) { return w == 4 ? 512 : 1024; }
+// Candidates that either hold.
+constexpr int kBigRoom = 1792;
+constexpr int list_room(int w) { return w == 4 ? 512 : 1024; }
+constexpr int big_list_room(int w) { return w == 4 ? 1024 : kBigRoom; }
 
 inline bool is_aligned(uintptr_t p, uintptr_t a) { return p % a == 0; }
 
@@ -141,7 +145,7 @@ inline int64_t workgroup_rows(int M, int k, bool half, int mode, bool dense) {
   if (M > 2048) return mode != kExact ? 0 : (half ? 512 : (dense ? 1024 : M / 2));
   return M > 1536 && k >= 100 && mode == kExact && !half && !dense ? 1024 : 0;
 }
-// The layout of a call of N rows: kernel_layout(), but for these.  They take the lists (rtopk_filter.hpp), so only where those serve.
+// The layout of a call of N rows: kernel_layout(), but for these (how the workgroup then searches: block_search).
 inline Shape layout_of_call(int64_t N, int M, int k, int dtype, int mode, int max_iter, bool plain, bool dense) {
   Shape s = kernel_layout(M, dtype, plain, dense);
   if (M <= kMaxWaveM && k <= 256 && k < M && (mode != kEarly || max_iter >= 5) &&
@@ -152,10 +156,11 @@ inline Shape layout_of_call(int64_t N, int M, int k, int dtype, int mode, int ma
     s.ng = (M <= 4096 ? 16 : 32) / s.g;
     s.full = M == s.capacity();
   }
-  // Exact mode's longer lists (one wavefront per row, or four wavefronts that hold 64 values per lane, -> these; us): fp32, 512 rows of 4096
-  // columns, k = 300 11.4 -> 8.2, k = 512 13.1 -> 10.9, 8192 rows 36 -> 57; 8192 columns, k = 300 512 rows 14.3 -> 9.7, 4096 rows 36.1 ->
-  // 35.9; k = 600 in eight wavefronts 15.2 -> 11.9, 1000 15.4 -> 15.7; 16384, k = 600 17.8 -> 14.7.  bfloat16: 4096 columns, k = 300 512 rows 15.8 ->
-  // 8.2, 8192 rows 47 -> 55; 8192 columns, k = 512 4096 rows 53 -> 45, 16384 rows 149 -> 156; k = 600 512 rows 22.8 -> 11.2, 4096 rows 53 -> 73.
+  // Exact mode with larger k (one wavefront per row, or four wavefronts that hold 64 values per lane, -> these; us): fp32, 512 rows of 4096
+  // columns, k = 300 11.4 -> 8.2, k = 512 11.0 -> 10.9, 8192 rows 36 -> 57; 4100 columns, k = 500 11.2 -> 9.8; 8192 columns, k = 300 512 rows
+  // 14.3 -> 9.7, 4096 rows 36.1 -> 35.9; k = 600 in eight wavefronts 17.5 -> 12.2, 1000 15.4 -> 15.7; 16384, k = 600 17.4 -> 15.4.  bfloat16: 4096
+  // columns, k = 300 512 rows 15.8 -> 8.2, 8192 rows 47 -> 55; 8192 columns, k = 512 4096 rows 53 -> 45, 16384 rows 149 -> 156; 512 rows, k = 600
+  // 22.2 -> 11.9, 1000 22.5 -> 11.9, 4096 rows, k = 600 53 -> 73; 6000 columns, k = 1000 18.4 -> 11.9.
   const bool half = dtype != kF32;
   if (mode == kExact && !dense && M > 2048 && M <= 16384 && k > filter_max_k(4) && k < M) {
     const bool four = k <= big_filter_max_k(4) && M <= kMaxWaveM && N <= (half ? (M > 6144 ? 4096 : 1024) : 512);
@@ -171,6 +176,67 @@ inline Shape layout_of_call(int64_t N, int M, int k, int dtype, int mode, int ma
     }
   }
   return s;
+}
+
+// How a workgroup searches its row (rtopk_block_kernel.hpp, rtopk_filter.hpp): over the whole row, on the lists, on exact mode's
+// longer lists.
+enum BlockSearch : int { kSearchRow = 1, kSearchLists = 2, kSearchLongLists = 4 };
+
+// A row's loads of g columns, and those of wavefront `wave` of its w (load i is lane i % 64 of wavefront i / 64 % w).
+constexpr int loads_of_row(int M, int g) { return (M + g - 1) / g; }
+constexpr int loads_of_wave(int M, int g, int w, int wave) {
+  const uint32_t all = (uint32_t)loads_of_row(M, g), round = 64u * (uint32_t)w;
+  const int rest = (int)(all % round) - 64 * wave;
+  return (int)(all / round) * 64 + (rest < 0 ? 0 : (rest > 64 ? 64 : rest));
+}
+
+// Of the k + 1 group maxima at or above a row's floor (rtopk_filter.hpp), those that a wavefront has to have: by its share of
+// the row's columns.  In equal parts, the wavefronts that a row leaves half empty find theirs far down, and as the row's floor is
+// the lowest of the wavefronts', the lists overflow: normal bfloat16 rows of 3500 columns, k = 437, four wavefronts, had 1710
+// candidates above it, by shares 671; 7600 columns, k = 800, eight wavefronts, 2796 and 1215 (512 rows: 16.0 -> 13.9 us; 256
+// fp32 rows of 20001 columns, k = 500, 15.3 -> 12.1).  floor_shares, from the host: k + 1 maxima per load of the row, in 2^-20.
+// The shares are rounded up, but for what their sum of at most 16 may lack of a whole number: they are k + 1 at least.
+inline uint32_t floor_shares(int M, int k, int g) { return (uint32_t)(((uint64_t)(k + 1) << 20) / (uint32_t)loads_of_row(M, g)); }
+constexpr int floor_share(int M, int g, int w, int wave, uint32_t shares) {
+  const uint32_t share = ((uint32_t)loads_of_wave(M, g, w, wave) * shares + (1u << 20) - (1u << 10)) >> 20;
+  return share > 0 ? (int)share : 1;
+}
+
+// Group maxima for the floor per lane of E values: of 16 values, or of a quarter of the fewer values of a lane; twice as many for
+// the longer lists.
+constexpr int floor_groups(int E, bool longer) { return longer && E >= 32 ? E / 8 : (E >= 48 ? E / 16 : 4); }
+
+// Whether the lists hold ordinary rows of M columns in w wavefronts of E values per lane: with fewer group maxima than twice k
+// (5/3 k for the longer lists, which have more room to spare) the floor has too many candidates, more than any list of a few
+// rows in a hundred (100 normal rows each: 1600 columns, k = 220, 486 of 512 candidates at most, 256 22 % of the rows do not fit; 5000
+// columns, k = 400, 1000 of 1024, 500 53 %; 4100 columns in eight wavefronts, k = 690, 1461 of 1792, 770 17 %).  What the lists
+// do not hold is searched over the whole row behind them, so from there on better at once, whatever its values (16 / 512 rows, with
+// lists -> without: fp32 4100 columns, k = 500 10.3 / 12.6 -> 7.9 / 9.8; bfloat16 6000 columns, k = 1000 11.0 / 15.7 -> 8.6 / 11.9).
+// Lists of more than 1200 candidates, where they hold, are no better than that either (7600 columns, k = 1000, 13.5 / 16.7 -> 8.8 / 12.0).
+// Below the lines the search over the row is as fast on normal rows (4096 columns, k = 256, 6.7 / 7.8 with lists, 6.5 / 8.4 without;
+// 512 9.4 / 10.9 and 6.8 / 8.4) but not on rows with masked entries (8.7 / 10.4 and 15.6 / 18.9; 11.4 / 12.9 and 15.7 / 18.5).
+inline bool lists_hold(int M, int k, int w, int E, bool longer) {
+  const int group = E / floor_groups(E, longer);
+  if (longer) return 5 * k * group <= 3 * M && (w != 8 || E > 16 || k <= 800);
+  return 2 * k * group <= M;
+}
+
+// The search of a call whose layout s is a workgroup's.
+inline int block_search(const Shape& s, int M, int k, int dtype, int mode, int max_iter, bool dense) {
+  const int E = s.values();
+  // Algorithm 2 with few steps ends on a threshold far below the k-th key, which the lists do not reach: the search
+  // is then wasted, and with 16 wavefronts the row is read again (50000 columns, k = 256, four steps: 134 us
+  // against 88 us; 32768 columns 56.6 against 56.1).  From eight (five) steps on the lists win as in exact mode.
+  if (k <= filter_max_k(s.w) && (mode != kEarly || max_iter >= (s.w == 16 ? 8 : 5)))
+    return lists_hold(M, k, s.w, E, false) ? kSearchLists : kSearchRow;
+  if (mode != kExact || dense || k > big_filter_max_k(s.w)) return kSearchRow;
+  if (E < 48) return lists_hold(M, k, s.w, E, true) ? kSearchLongLists : kSearchRow;
+  // Longer lists where k is a small part of the row (us, search over the row -> lists): 12288 columns, k = 500 39 -> 36;
+  // 16384, k = 400 38.5 -> 31.2; 24000, k = 600 43.4 -> 40.4, 1000 45.9 -> 50.0; 32768, k = 600 44 -> 34; 50000, k = 1000
+  // 69 -> 67; 65536 188 -> 157.  16-bit rows, whose search over the row costs as much as that of fp32 rows, win throughout:
+  // 16384, k = 400 48 -> 25; 24000, k = 1000 73 -> 62; 32768 53 -> 35; 50000, k = 600 83 -> 43.  Rows of whole numbers gain
+  // 1.2 to 1.9 times, of heavy tails up to 1.5; sorted rows, whose lists overflow, lose 10 to 35 %.
+  return (dtype != kF32 || s.w == 4 ? 24 : 40) * k <= M ? kSearchLongLists : kSearchRow;
 }
 
 // True when (g, ng, w) is a layout of its family's lists above.  `plain` and `dense` as above.
@@ -267,7 +333,6 @@ inline Split split_of(int64_t N, int M, int k, int mode, int max_iter) {
 // 151 -> 121.)  The floors come from eight groups of eight values per lane here, so a list has 1.1 to 1.35 k candidates at
 // k = 512 .. 1024.  Lists of 16 wavefronts, whose floors spread more, are expected to hold 1.5 k.
 constexpr int kBigMaxK = 1024;
-constexpr int kBigRoom = 1792;
 constexpr int kMergeRegsBig = 40;  // candidates per lane that 16 merging wavefronts hold at most
 inline Split split_big_of(int64_t N, int M, int k, int mode, int max_iter) {
   Split s{};

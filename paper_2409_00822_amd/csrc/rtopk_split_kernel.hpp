@@ -42,7 +42,7 @@ static_assert(sizeof(SegmentHead) == kSegmentHeadBytes, "split_of counts it");
 template <int NG, int W, bool NEG, bool BIG>
 __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(BIG ? 4 : 5)))
     rtopk_segment_kernel(const float* __restrict__ in, int M, int k, int segments, int length, int cap,
-                         SegmentHead* __restrict__ heads, uint2* __restrict__ lists) {
+                         SegmentHead* __restrict__ heads, uint2* __restrict__ lists, uint32_t shares, uint32_t shares_last) {
   constexpr int G = 4, E = G * NG;
   __shared__ BoundsLds<W> s_bounds;
   __shared__ FilterLds<W, BIG ? kBigRoom : segment_room(W)> s_filter;
@@ -53,6 +53,8 @@ __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(
   const float* from = in + (int64_t)r * M + first;
   float x[E];
   block_load<kF32, G, W, 0, NG>(from, cols, lane, wave, x);
+  int need = floor_share(cols, G, W, wave, cols < length ? shares_last : shares);
+  asm volatile("" : "+s"(need));  // here, while the loads are in flight
   const float nm = lane_negmin<E, NEG>(x);
   block_mask<G, NG, W, NEG>(x, cols, lane, wave);
   if (tid == 0) {
@@ -60,7 +62,7 @@ __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(
     s_filter.n_singles = 0;
   }
   float lo, hi, T0, probe;
-  block_bounds<E, W, NEG, true, BIG ? E / 8 : E / kFilterGroup>(x, nm, (k + W) / W, lane, wave, s_bounds, lo, hi, T0, probe);
+  block_bounds<E, W, NEG, true, floor_groups(E, BIG)>(x, nm, need, lane, wave, s_bounds, lo, hi, T0, probe);
   auto column = [&](int quad, int thread) -> int { return min((quad * W * kWave + thread) * G, cols - G); };
   const int n = filter_lists<E, W, NEG>(s_filter, x, lane, wave, T0, column, [] {});
   uint2* to = lists + (int64_t)blockIdx.x * cap;
@@ -71,7 +73,7 @@ __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(
     // (their values to the first half of the list's memory, their columns to the second; then in pairs like any other list)
     float* values = reinterpret_cast<float*>(to);
     int32_t* columns = reinterpret_cast<int32_t*>(to) + cap;
-    block_row<G, NG, W, kExact, NEG, kF32, false, kFullWidth>(0, from, 1, cols, k + 1, 0, 0.0f, values, columns, nullptr, 1,
+    block_row<G, NG, W, kExact, NEG, kF32, false, kFullWidth>(0, from, 1, cols, k + 1, 0, 0.0f, values, columns, nullptr, 0, 1,
                                                               none, ahead, none, x, end);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (it stores through inline asm)
     __syncthreads();
@@ -418,6 +420,7 @@ __global__ void __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu
 
 template <int MODE, bool NEG>
 hipError_t launch_split(const Split& s, void* scratch, const LaunchArgs& a) {
+  const uint32_t shares = floor_shares(s.length, a.k, 4), shares_last = floor_shares(a.M - (s.segments - 1) * s.length, a.k, 4);
   for (int64_t r0 = 0; r0 < a.N; r0 += s.rows) {
     const int64_t rows = a.N - r0 < s.rows ? a.N - r0 : s.rows;
     const float* in = static_cast<const float*>(a.in) + r0 * a.M;
@@ -427,7 +430,7 @@ hipError_t launch_split(const Split& s, void* scratch, const LaunchArgs& a) {
                          : s.w == 4 ? (s.ng == 12 ? &rtopk_segment_kernel<12, 4, NEG, false> : &rtopk_segment_kernel<16, 4, NEG, false>)
                                     : (s.ng == 12 ? &rtopk_segment_kernel<12, 8, NEG, false> : &rtopk_segment_kernel<16, 8, NEG, false>);
     hipError_t err = launch_kernel(segment, dim3((unsigned)(rows * s.segments)), dim3(s.w * kWave), 0, a.stream, in, a.M, a.k,
-                                   s.segments, s.length, s.cap, heads, lists);
+                                   s.segments, s.length, s.cap, heads, lists, shares, shares_last);
     if (err != hipSuccess) return err;
     const auto merge = s.merge_waves == 4   ? &rtopk_merge_kernel<4, MODE, NEG>
                        : s.merge_waves == 8 ? &rtopk_merge_kernel<8, MODE, NEG>
