@@ -813,7 +813,7 @@ hipError_t launch_block(const LaunchArgs& a) {
     const int64_t resident = (int64_t)compute_units() * (16 / W);  // workgroups that run at the same time
     if (resident > 0 && grid > resident) grid = resident;
   }
-  constexpr int K = kSearchRow | kSearchLists | (MODE == kExact && !DENSE ? kSearchLongLists : 0);
+  constexpr int K = block_kernels(G * NG, W, MODE, DENSE, DT != kF32);
   static_assert(block_persistent(W) == (W == 16), "block_search knows the shape that walks its rows by its wavefronts");
   Shape s{};
   s.g = G;

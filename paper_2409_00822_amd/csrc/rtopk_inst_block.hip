@@ -1,9 +1,9 @@
-// Instantiations: one workgroup of W wavefronts per row, for rows wider than 8192 columns -- fp32 pairs, Algorithm 2 and exact mode.
+// Instantiations: one workgroup of W wavefronts per row, for rows wider than 8192 columns and few narrower ones -- fp32 pairs, Algorithm 2 and exact mode.
 #include "rtopk_block_kernel.hpp"
 
 namespace rtopk {
 
-// 128-bit loads: W = 4 up to 16384 columns, 8 up to 32768, 16 up to 65536, with 12 or 16 loads per lane.
+// 128-bit loads: W = 4 up to 16384 columns, 8 up to 32768, 16 up to 65536, with 12 or 16 loads per lane; few rows with 4 or 8.
 template <int G, int NG, int W>
 static hipError_t pick(int mode, const LaunchArgs& a) {
   if (mode == kExact) return launch_block<G, NG, W, kExact>(a);
@@ -15,9 +15,8 @@ hipError_t launch_block_plain(int g, int ng, int w, int mode, const LaunchArgs& 
   if (g == 4) {
     if (w == 4 && ng == 4) return pick<4, 4, 4>(mode, a);
     if (w == 4 && ng == 8) return pick<4, 8, 4>(mode, a);
-    if (w == 8 && ng <= 8 && mode != kExact) return hipErrorInvalidValue;
-    if (w == 8 && ng == 4) return launch_block<4, 4, 8, kExact>(a);
-    if (w == 8 && ng == 8) return launch_block<4, 8, 8, kExact>(a);
+    if (w == 8 && ng == 4) return pick<4, 4, 8>(mode, a);
+    if (w == 8 && ng == 8) return pick<4, 8, 8>(mode, a);
     if (w == 4 && ng == 12) return pick<4, 12, 4>(mode, a);
     if (w == 4 && ng == 16) return pick<4, 16, 4>(mode, a);
     if (w == 8 && ng == 12) return pick<4, 12, 8>(mode, a);

@@ -1,4 +1,4 @@
-// Instantiations: one workgroup of W wavefronts per row, for rows wider than 8192 columns -- fp32 dense output.
+// Instantiations: one workgroup of W wavefronts per row, for rows wider than 8192 columns and few narrower ones -- fp32 dense output.
 #include "rtopk_block_kernel.hpp"
 
 namespace rtopk {

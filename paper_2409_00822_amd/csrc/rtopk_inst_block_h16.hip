@@ -1,9 +1,9 @@
-// Instantiations: one workgroup of W wavefronts per row, for rows wider than 8192 columns -- rows stored as half or bfloat16.
+// Instantiations: one workgroup of W wavefronts per row, for rows wider than 8192 columns and few narrower ones -- rows stored as half or bfloat16.
 #include "rtopk_block_kernel.hpp"
 
 namespace rtopk {
 
-// 128-bit loads bring 8 values; 8 loads per lane (W = 4, 8 or 16).
+// 128-bit loads bring 8 values; 8 loads per lane (W = 4, 8 or 16); few rows with 2 or 4.
 template <int G, int NG, int W, int DT>
 static hipError_t pick(int mode, const LaunchArgs& a) {
   if (mode == kExact) return launch_block<G, NG, W, kExact, false, DT>(a);
@@ -16,9 +16,8 @@ static hipError_t pick_shape(int g, int ng, int w, int mode, const LaunchArgs& a
   if (g == 8) {
     if (w == 4 && ng == 2) return pick<8, 2, 4, DT>(mode, a);
     if (w == 4 && ng == 4) return pick<8, 4, 4, DT>(mode, a);
-    if (w == 8 && ng <= 4 && mode != kExact) return hipErrorInvalidValue;
-    if (w == 8 && ng == 2) return launch_block<8, 2, 8, kExact, false, DT>(a);
-    if (w == 8 && ng == 4) return launch_block<8, 4, 8, kExact, false, DT>(a);
+    if (w == 8 && ng == 2) return pick<8, 2, 8, DT>(mode, a);
+    if (w == 8 && ng == 4) return pick<8, 4, 8, DT>(mode, a);
     if (ng != 8) return hipErrorInvalidValue;
     if (w == 4) return pick<8, 8, 4, DT>(mode, a);
     if (w == 8) return pick<8, 8, 8, DT>(mode, a);

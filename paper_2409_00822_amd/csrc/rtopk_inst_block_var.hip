@@ -1,9 +1,9 @@
-// Instantiations: one workgroup of W wavefronts per row, for rows wider than 8192 columns -- fp32 pairs: precision-bounded mode and the k smallest.
+// Instantiations: one workgroup of W wavefronts per row, for rows wider than 8192 columns and few narrower ones -- fp32 pairs: precision-bounded mode and the k smallest.
 #include "rtopk_block_kernel.hpp"
 
 namespace rtopk {
 
-// 128-bit loads with 16 loads per lane (W = 4, 8 or 16).
+// 128-bit loads with 16 loads per lane (W = 4, 8 or 16); few rows with 4 or 8.
 template <int G, int NG, int W>
 static hipError_t pick(int mode, bool smallest, const LaunchArgs& a) {
   if (smallest) {
@@ -19,9 +19,8 @@ hipError_t launch_block_variant(int g, int ng, int w, int mode, bool smallest, c
   if (g == 4) {
     if (w == 4 && ng == 4) return pick<4, 4, 4>(mode, smallest, a);
     if (w == 4 && ng == 8) return pick<4, 8, 4>(mode, smallest, a);
-    if (w == 8 && ng <= 8 && (mode != kExact || !smallest)) return hipErrorInvalidValue;
-    if (w == 8 && ng == 4) return launch_block<4, 4, 8, kExact, true>(a);
-    if (w == 8 && ng == 8) return launch_block<4, 8, 8, kExact, true>(a);
+    if (w == 8 && ng == 4) return pick<4, 4, 8>(mode, smallest, a);
+    if (w == 8 && ng == 8) return pick<4, 8, 8>(mode, smallest, a);
     if (ng != 16) return hipErrorInvalidValue;
     if (w == 4) return pick<4, 16, 4>(mode, smallest, a);
     if (w == 8) return pick<4, 16, 8>(mode, smallest, a);

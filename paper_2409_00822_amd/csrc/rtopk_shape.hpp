@@ -179,7 +179,7 @@ inline Shape layout_of_call(int64_t N, int M, int k, int dtype, int mode, int ma
 }
 
 // How a workgroup searches its row (rtopk_block_kernel.hpp, rtopk_filter.hpp): over the whole row, on the lists, on exact mode's
-// longer lists.
+// longer lists.  Bits, for block_kernels().
 enum BlockSearch : int { kSearchRow = 1, kSearchLists = 2, kSearchLongLists = 4 };
 
 // A row's loads of g columns, and those of wavefront `wave` of its w (load i is lane i % 64 of wavefront i / 64 % w).
@@ -237,6 +237,15 @@ inline int block_search(const Shape& s, int M, int k, int dtype, int mode, int m
   // 16384, k = 400 48 -> 25; 24000, k = 1000 73 -> 62; 32768 53 -> 35; 50000, k = 600 83 -> 43.  Rows of whole numbers gain
   // 1.2 to 1.9 times, of heavy tails up to 1.5; sorted rows, whose lists overflow, lose 10 to 35 %.
   return (dtype != kF32 || s.w == 4 ? 24 : 40) * k <= M ? kSearchLongLists : kSearchRow;
+}
+
+// The searches that layout_of_call and block_search can ask of a workgroup layout of E values per lane in w wavefronts: those
+// that are compiled.  (Layouts of fewer than 48 values per lane are for few rows only: lists with k <= 256, exact mode with more.)
+constexpr int block_kernels(int E, int w, int mode, bool dense, bool half) {
+  if (E >= 48) return kSearchRow | kSearchLists | (mode == kExact && !dense ? kSearchLongLists : 0);
+  if (w == 8) return mode != kExact || dense ? 0 : (half ? kSearchRow | kSearchLongLists : kSearchLongLists);
+  if (mode == kExact && !dense) return kSearchRow | kSearchLists | kSearchLongLists;
+  return E == 32 || dense ? (E == 16 && mode != kExact ? 0 : kSearchLists) : 0;
 }
 
 // True when (g, ng, w) is a layout of its family's lists above.  `plain` and `dense` as above.
