@@ -722,10 +722,30 @@ constexpr int wave_filter_max_k(int E, int R, int mode, bool dense = false) {
 // row that leaves its layout a quarter empty has too few (k = 280: 4096 columns 33 -> 28 us, 3584 35 -> 34, 3074 40 -> 47).
 // Algorithm 2 with few steps searches the full width: the last threshold of few steps lies below the floor, and each step
 // saved is worth the less the narrower the row (1280 columns, bfloat16, five steps, k = 140: 38 -> 43 us, 100 38 -> 37).
+// Rows of 16 values per lane, whose search over the row is short, are narrower still for their group maxima: k at most 74 % of
+// these and fewer where four registers would not hold the singles; with fewer steps of Algorithm 2 less (one row per wavefront,
+// 4096 / 30000 rows, search over the row -> lists: bfloat16 exact 514 columns, k = 90 10.8 / 36.9 -> 9.0 / 31.7, 110 10.8 / 37.5 -> 11.6 /
+// 39.0; 600, k = 110 11.1 / 38.3 -> 9.4 / 32.8; 700, k = 130 11.2 / 39.0 -> 12.2 / 38.3; fp32 exact 770, k = 130 10.8 / 35.9 -> 9.8 / 34.6, 140
+// 10.9 / 34.3 -> 12.2 / 39.3; eight steps 1000, k = 90 8.7 / 30.8 -> 8.4 / 29.6, 130 8.8 / 31.0 -> 9.1 / 32.4; six 131072 rows of 1000, k = 16
+// 94.5 -> 91.2, 50000 rows, k = 64 42.6 -> 40.9; five 900, k = 64 6.8 / 24.1 -> 7.3 / 25.6; dense, 1000 rows of 770, k = 64 eight 5.7 -> 6.0,
+// twelve 6.6 -> 6.1).  For the host, which tells the kernel: weighed there, the conditions cost the kernels of early stopping 3 to 11 %.
+constexpr bool narrow_lists_hold(int mode, bool dense, int M, int k, int max_iter) {
+  if (mode == kExact || max_iter >= 12) return 27 * k <= 5 * M && 14 * k <= M + 1064;
+  if (max_iter >= 8) return (dense ? 16 : 8) * k <= M;
+  return !dense && max_iter >= 6 && (max_iter == 7 ? 9 : 12) * k <= M;
+}
 __host__ __device__ constexpr bool wave_filter_takes(int E, int R, int mode, bool dense, int M, int k, int max_iter) {
   const int least = k > 245 ? 8 : (E <= 32 && k > 100 ? 6 : 5);
   return k <= wave_filter_max_k(E, R, mode, dense) && (k <= 245 || 100 * k * (E / wave_groups(E, true)) <= 68 * M) &&
          (mode != kEarly || max_iter >= least);
+}
+// What a launch says of it, and the kernel then knows (E = 16 by what it was told).
+constexpr int kTakesLists = 4;  // a bit beside the kind of stores
+inline int lists_flag(int E, int R, int mode, bool dense, int M, int k, int max_iter) {
+  return E == 16 && k <= wave_filter_max_k(E, R, mode, dense) && narrow_lists_hold(mode, dense, M, k, max_iter) ? kTakesLists : 0;
+}
+__host__ __device__ constexpr bool takes_lists(int E, int R, int mode, bool dense, int M, int k, int max_iter, int flags) {
+  return E == 16 ? R == 1 && (flags & kTakesLists) != 0 : wave_filter_takes(E, R, mode, dense, M, k, max_iter);
 }
 // Quads, and singles, that the lists of a row hold, and the pairs' worth of LDS they take.
 __host__ __device__ constexpr int wave_filter_room(int k) { return (k + k / 2 + 48 + 63) & ~63; }

@@ -830,9 +830,9 @@ __host__ __device__ constexpr int staged_pairs(int E, int R, int k) {
   const int band = band_scratch_floats(E) / 2;
   return ((R * k > band ? R * k : band) + 1) & ~1;
 }
-__host__ __device__ constexpr int wave_pairs(int E, int R, int mode, bool dense, int M, int k, int max_iter) {
+__host__ __device__ constexpr int wave_pairs(int E, int R, int mode, bool dense, int M, int k, int max_iter, int flags) {
   const int staged = staged_pairs(E, R, dense ? 1 : k);
-  if (!wave_filter_takes(E, R, mode, dense, M, k, max_iter)) return staged;
+  if (!takes_lists(E, R, mode, dense, M, k, max_iter, flags)) return staged;
   const int lists = wave_filter_pairs(k);
   return staged > lists ? staged : lists;
 }
@@ -845,11 +845,12 @@ __host__ __device__ constexpr int wave_pairs(int E, int R, int mode, bool dense,
 // evaluated when one of them counted exactly k, one more when the loop ended through its guard.
 //   DENSE: the result is y[] (chosen values in place, +0 elsewhere) instead of pairs staged at `stage`.
 //   row_max, row_min: the row's maximum and minimum (Alg. 1 / Alg. 2, first two steps), wave-uniform.
-//   R: rows of the wavefront; lists: LDS of the candidates' lists (rtopk_filter.hpp), where k is small enough for them.
+//   R: rows of the wavefront; lists: LDS of the candidates' lists (rtopk_filter.hpp), where k is small enough for them (flags: see
+//   takes_lists).
 template <int G, int NG, int R, bool FULL, int MODE, bool NEG, int DT = kF32, bool DENSE = false>
 __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], int lane, int M, int k, int max_iter,
                                           float eps_rel, uint2* stage, uint2* lists, float (&y)[Layout<G, NG>::E], float row_max,
-                                          float row_min) {
+                                          float row_min, int flags) {
   using L = Layout<G, NG>;
   constexpr int E = L::E;
   const uint32_t stage_addr = (uint32_t)(uintptr_t)stage;  // LDS byte address
@@ -935,7 +936,7 @@ __device__ __forceinline__ int select_row(const float (&xin)[Layout<G, NG>::E], 
   bool bounds_known = false;  // Algorithm 1 with precision: lo, hi and the iteration count are those of its end
   int known_iterations = 0;
   if constexpr (wave_filter_max_k(E, R, MODE) > 0) {
-    if (wave_filter_takes(E, R, MODE, DENSE, M, k, max_iter)) {
+    if (takes_lists(E, R, MODE, DENSE, M, k, max_iter, flags)) {
       float thi, tlo;
       int split, iterations = 0;
       const float eps = MODE == kEps ? eps_rel * __builtin_fabsf(hi) : 0.0f;
@@ -1276,7 +1277,7 @@ __global__ void __launch_bounds__(256)
     __attribute__((amdgpu_waves_per_eu(Layout<G, NG>::E >= 128 ? 3 : (Layout<G, NG>::E >= 96 ? 4 : 1))))
     rtopk_wave_kernel(const void* __restrict__ in, int64_t N, int M, int k, int max_iter, float eps_rel,
                       void* __restrict__ out_vals, IdxT* __restrict__ out_idx, int32_t* __restrict__ out_iters,
-                      int vec_store) {
+                      int flags) {
   using L = Layout<G, NG>;
   constexpr int E = L::E;
   using ElemT = typename std::conditional<DT == kF32, float, uint16_t>::type;
@@ -1289,7 +1290,7 @@ __global__ void __launch_bounds__(256)
   if (r0 >= N) return;
   int nrows = rows_left(N - r0, R);
   static_assert(!narrows(E, MODE) || R == 1, "the band scratch reuses the staging area of the wavefront's only row");
-  uint2* stage = stage_all + (size_t)wave * wave_pairs(E, R, MODE, false, M, k, max_iter);
+  uint2* stage = stage_all + (size_t)wave * wave_pairs(E, R, MODE, false, M, k, max_iter, flags);
 
   // Loading stage: all R rows' loads are issued before any is consumed.
   float x[R][E];
@@ -1318,7 +1319,7 @@ __global__ void __launch_bounds__(256)
       float unused[E];
       const int it = select_row<G, NG, R, FULL, MODE, NEG, DT, false>(x[rr], lane, M, k, max_iter, eps_rel,
                                                                     stage + (size_t)rr * k, stage, unused, row_max[rr],
-                                                                    row_min[rr]);
+                                                                    row_min[rr], flags);
       if constexpr (MODE == kEps) {
         if (out_iters != nullptr && lane == 0) out_iters[r0 + rr] = it;
       }
@@ -1347,6 +1348,7 @@ __global__ void __launch_bounds__(256)
       store_streaming(reinterpret_cast<uint32_t*>(to_i) + q, a.y | (a.w << 8) | (b.y << 16) | (b.w << 24));
     }
   };
+  const int vec_store = E == 16 && R == 1 ? flags & (kTakesLists - 1) : flags;  // (the other widths are told no more)
   auto store_one = [&](int j) {
     const uint2 a = stage[j];
     if constexpr (DT == kF32) {
@@ -1416,7 +1418,7 @@ __device__ __forceinline__ void store_row_group(float* row, int col, int M, cons
 // through LDS and each row leaves in the layout it arrived in.
 template <int G, int NG, int R, bool FULL, int MODE>
 __global__ void __launch_bounds__(256)
-    rtopk_dense_kernel(const float* __restrict__ in, int64_t N, int M, int k, int max_iter, float* __restrict__ out) {
+    rtopk_dense_kernel(const float* __restrict__ in, int64_t N, int M, int k, int max_iter, float* __restrict__ out, int flags) {
   using L = Layout<G, NG>;
   constexpr int E = L::E;
   extern __shared__ __attribute__((aligned(16))) uint2 band_scratch[];  // per wavefront: band or lists, wide rows only
@@ -1426,7 +1428,7 @@ __global__ void __launch_bounds__(256)
   const int64_t r0 = ((int64_t)blockIdx.x * waves_per_block + wave) * R;
   if (r0 >= N) return;
   int nrows = rows_left(N - r0, R);
-  uint2* scratch = band_scratch + (size_t)wave * wave_pairs(E, R, MODE, true, M, k, max_iter);
+  uint2* scratch = band_scratch + (size_t)wave * wave_pairs(E, R, MODE, true, M, k, max_iter, flags);
 
   float x[R][E];
 #pragma unroll
@@ -1448,7 +1450,7 @@ __global__ void __launch_bounds__(256)
     if (rr < nrows) {
       float y[E];
       select_row<G, NG, R, FULL, MODE, false, kF32, true>(x[rr], lane, M, k, max_iter, 0.0f, scratch, scratch, y, row_max[rr],
-                                                       row_min[rr]);
+                                                       row_min[rr], flags);
       float* orow = out + (r0 + rr) * (int64_t)M;
       static_for<L::GROUPS>([&](auto gc) {
         constexpr int g = decltype(gc)::value, GW = L::width(g);
@@ -1467,10 +1469,11 @@ hipError_t launch_dense(const LaunchArgs& a) {
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   if (a.M < Layout<G, NG>::MIN_M || a.M > 64 * Layout<G, NG>::E) return hipErrorInvalidValue;
   constexpr int E = Layout<G, NG>::E;
-  const size_t lds = E < 12 ? 0 : (size_t)waves * wave_pairs(E, R, MODE, true, a.M, a.k, a.max_iter) * sizeof(uint2);
+  const int flags = lists_flag(E, R, MODE, true, a.M, a.k, a.max_iter);
+  const size_t lds = E < 12 ? 0 : (size_t)waves * wave_pairs(E, R, MODE, true, a.M, a.k, a.max_iter, flags) * sizeof(uint2);
   return launch_kernel(rtopk_dense_kernel<G, NG, R, FULL, MODE>, dim3((unsigned)blocks), dim3(waves * kWave), lds,
                        a.stream, static_cast<const float*>(a.in), a.N, a.M, a.k, a.max_iter,
-                       static_cast<float*>(a.out_vals));
+                       static_cast<float*>(a.out_vals), flags);
 }
 
 // ---- host-side launcher -------------------------------------------------------------------------------
@@ -1480,7 +1483,8 @@ hipError_t launch(const LaunchArgs& a) {
   using L = Layout<G, NG>;
   if (a.M < L::MIN_M || a.M > 64 * L::E) return hipErrorInvalidValue;
   // LDS per wavefront: at most 64 KiB per block
-  size_t per_wave = (size_t)wave_pairs(L::E, R, MODE, false, a.M, a.k, a.max_iter) * sizeof(uint2);
+  const int flags = a.vec_store | lists_flag(L::E, R, MODE, false, a.M, a.k, a.max_iter);
+  size_t per_wave = (size_t)wave_pairs(L::E, R, MODE, false, a.M, a.k, a.max_iter, flags) * sizeof(uint2);
   // one wavefront per workgroup, except where a wavefront stages 8 KiB or more of pairs: there four
   // per workgroup measured 7 % faster (2^20 x 256, k = 128: 387 -> 360 us), while at 4 KiB and below
   // one per workgroup is the faster by 3-11 %
@@ -1491,7 +1495,7 @@ hipError_t launch(const LaunchArgs& a) {
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   return launch_kernel(rtopk_wave_kernel<G, NG, R, FULL, MODE, NEG, IdxT, DT>, dim3((unsigned)blocks),
                        dim3(waves * kWave), per_wave * waves, a.stream, a.in, a.N, a.M, a.k, a.max_iter, a.eps_rel,
-                       a.out_vals, static_cast<IdxT*>(a.out_idx), a.out_iters, a.vec_store);
+                       a.out_vals, static_cast<IdxT*>(a.out_idx), a.out_iters, flags);
 }
 
 // Rows per wavefront for E = G*NG registers per row, from sweeps at 2^20 rows: 16 for M <= 128,
@@ -1506,7 +1510,9 @@ constexpr int rows_per_wave(int E) { return E <= 2 ? 16 : (E <= 4 ? 8 : (E <= 16
 // The narrower the row, the fewer group maxima there are for a floor: 16-bit exact rows take 35 of 64 of them at most (2^25
 // values, bfloat16, k = 130: 600 columns 53 -> 62 us, 1024 columns 53 -> 43; k = 90 at 514 columns 55 -> 52), those with early stopping
 // 24 of 64, in seven steps or more (600 columns, k = 64: six 31 -> 35, seven 34 -> 35, eight 37 -> 37); fp32 rows five or more from
-// 896 columns on (1024 columns, k = 48: 29 -> 26), six below (770, k = 64: five 30 -> 33, six 32 -> 33).
+// 896 columns on (1024 columns, k = 48: 29 -> 26), six below (770, k = 64: five 30 -> 33, six 32 -> 33).  (That is where many
+// rows take one per wavefront.  Few rows do as well, see few_rows, and the dense form at any number; whether their wavefronts
+// build the lists is narrow_lists_hold's to say, which holds here too but for five steps of fp32 rows.)
 inline bool one_row_lists(int mode, bool half, const LaunchArgs& a) {
   if (mode == kExact) return a.k <= (half ? min(wave_filter_max_k(16, 1, mode), 35 * a.M / 256) : 64);
   return a.k <= (half ? min(64, 24 * a.M / 256) : 64) && a.max_iter >= (half ? 7 : (a.M >= 896 ? 5 : 6));
