@@ -17,7 +17,8 @@ static hipError_t pick(bool full, const LaunchArgs& a) {
   if constexpr (E == 16) {
     if (one_row_lists(kEarly, true, a)) return pick_rows<DT, G, NG, 1>(full, a);
   }
-  return by_rows<E, R, kPairs>(a.N, [&](auto r) { return pick_rows<DT, G, NG, decltype(r)::value>(full, a); });
+  return by_rows<E, R, kPairs>(a.N, [&](auto r) { return pick_rows<DT, G, NG, decltype(r)::value>(full, a); },
+                               few_rows_early<E, kPairs, true>(full, a));
 }
 
 template <int DT>

@@ -1557,17 +1557,34 @@ constexpr FewRows few_rows(int E, RowForm form) {
   if (E == 4 && form == kBytes) return {4096, 49152, 147456};
   return {E <= 6 ? 8192 : (E <= 8 ? 12288 : 32768), 49152, 147456};
 }
+// Algorithm 2 with up to five steps leaves a wavefront less to do per row, and what it does once -- the validity of its columns,
+// widening -- weighs more: of ragged or 16-bit rows, one per wavefront pays up to half as many, four instead of sixteen up to three
+// quarters, of 64 columns and less any kind's (us, four steps unless said otherwise, with the lines above -> with these: 6000 x 300 5.2 -> 4.8, 30000 x 650 20.5 -> 19.3,
+// bfloat16 3000 x 100 3.4 -> 3.2, 10000 x 448 7.0 -> 6.6, 180000 x 100 22.9 -> 20.9, 120000 x 180 19.8 -> 18.7, fp32 90000 x 40 11.2 -> 10.7).
+// 16-bit rows of 16 values per lane that take no lists: one row per wavefront up to 12288 of them, 24576 from six steps on (30000 x 700,
+// four 21.9 -> 20.1, 32000 x 514, eight 29.6 -> 28.4).
+template <int E, RowForm FORM, bool HALF = false>
+inline FewRows few_rows_early(bool full, const LaunchArgs& a) {
+  FewRows few = few_rows(E, FORM);
+  if (E == 16) {
+    if (HALF && a.max_iter < 12 && lists_flag(E, 1, kEarly, false, a.M, a.k, a.max_iter) == 0) few.one = a.max_iter <= 5 ? 12288 : 24576;
+  } else if (a.max_iter <= 5) {
+    if (HALF || !full) few.one /= 2;
+    if (E == 1 ? a.max_iter <= 4 : E <= 3 && (HALF || !full)) few.four -= few.four / 4;
+  }
+  return few;
+}
 // f(integral_constant<int, rows per wavefront>) for N rows; FULL: the layout's own number.
 template <int E, int FULL, RowForm FORM, typename F>
-hipError_t by_rows(int64_t N, F f) {
-  constexpr FewRows few = few_rows(E, FORM);
-  if constexpr (FULL > 1 && few.one > 0) {
+hipError_t by_rows(int64_t N, F f, FewRows few = few_rows(E, FORM)) {
+  constexpr FewRows most = few_rows(E, FORM);  // what is compiled
+  if constexpr (FULL > 1 && most.one > 0) {
     if (N < few.one) return f(std::integral_constant<int, 1>());
   }
   if constexpr (FULL > 2) {
     if (N < few.two) return f(std::integral_constant<int, 2>());
   }
-  if constexpr (FULL > 4 && few.four > few.two) {
+  if constexpr (FULL > 4 && most.four > most.two) {
     if (N < few.four) return f(std::integral_constant<int, 4>());
   }
   return f(std::integral_constant<int, FULL>());

@@ -68,3 +68,21 @@ def test_16bit_rows(kind, M):
         x, tag = _tiled(base.view(np.int16), N).view(dtype), f"{kind} {N} x {M}"
         for got, want in ((exact(x, k), want_exact), (early(x, k, 6), want_early)):
             _check((got[0].view(torch.int16), got[1]), (want[0].view(np.int16), want[1]), tag)
+
+
+@pytest.mark.parametrize("M", [40, 100, 128, 180, 256, 300, 512, 514, 700])
+def test_few_steps(M):
+    """The lines of Algorithm 2 with few steps."""
+    R = _gpu()
+    base = workloads.normal(BASE, M, 9000 + M)
+    half = workloads.to_bits16(base, "bf16")
+    k = max(1, M // 6)
+    for steps in (2, 5, 8):
+        want, want16 = oracle.topk_earlystop(base, k, steps), oracle.topk_earlystop_16(half, "bf16", k, steps)
+        for N in (2049, 4097, 6145, 12289, 16385, 24577, 73729, 110593, 147457):
+            if N * M > 30_000_000:
+                break
+            tag = f"{N} x {M} steps {steps}"
+            _check(R.rtopk_rowwise(_tiled(base, N), k, steps), want, tag)
+            v, i = R.rtopk_rowwise_bf16(_tiled(half.view(np.int16), N).view(torch.bfloat16), k, steps)
+            _check((v.view(torch.int16), i), (want16[0].view(np.int16), want16[1]), tag + " bf16")
