@@ -182,12 +182,11 @@ inline Shape layout_of_call(int64_t N, int M, int k, int dtype, int mode, int ma
 // longer lists.  Bits, for block_kernels().
 enum BlockSearch : int { kSearchRow = 1, kSearchLists = 2, kSearchLongLists = 4 };
 
-// A row's loads of g columns, and those of wavefront `wave` of its w (load i is lane i % 64 of wavefront i / 64 % w).
+// A row's loads of g columns, and those of the wavefronts before `wave` of its w (load i is lane i % 64 of wavefront i / 64 % w).
 constexpr int loads_of_row(int M, int g) { return (M + g - 1) / g; }
-constexpr int loads_of_wave(int M, int g, int w, int wave) {
-  const uint32_t all = (uint32_t)loads_of_row(M, g), round = 64u * (uint32_t)w;
-  const int rest = (int)(all % round) - 64 * wave;
-  return (int)(all / round) * 64 + (rest < 0 ? 0 : (rest > 64 ? 64 : rest));
+constexpr int loads_before(int M, int g, int w, int wave) {
+  const uint32_t all = (uint32_t)loads_of_row(M, g), round = 64u * (uint32_t)w, rest = all % round, part = 64u * (uint32_t)wave;
+  return (int)(all / round * part + (rest < part ? rest : part));
 }
 
 // Of the k + 1 group maxima at or above a row's floor (rtopk_filter.hpp), those that a wavefront has to have: by its share of
@@ -195,10 +194,14 @@ constexpr int loads_of_wave(int M, int g, int w, int wave) {
 // the lowest of the wavefronts', the lists overflow: normal bfloat16 rows of 3500 columns, k = 437, four wavefronts, had 1710
 // candidates above it, by shares 671; 7600 columns, k = 800, eight wavefronts, 2796 and 1215 (512 rows: 16.0 -> 13.9 us; 256
 // fp32 rows of 20001 columns, k = 500, 15.3 -> 12.1).  floor_shares, from the host: k + 1 maxima per load of the row, in 2^-20.
-// The shares are rounded up, but for what their sum of at most 16 may lack of a whole number: they are k + 1 at least.
+// The shares are differences of the rounded sums up to each wavefront, so that together they are k + 1 and no more (each one
+// rounded up, the lists of 7 rows of 665649 columns, k = 23, whose segments leave a wavefront partly empty, overflowed now and then: 12.7
+// -> 13.4 us); the sums' rounding makes up for what floor_shares has cut off.
 inline uint32_t floor_shares(int M, int k, int g) { return (uint32_t)(((uint64_t)(k + 1) << 20) / (uint32_t)loads_of_row(M, g)); }
 constexpr int floor_share(int M, int g, int w, int wave, uint32_t shares) {
-  const uint32_t share = ((uint32_t)loads_of_wave(M, g, w, wave) * shares + (1u << 20) - (1u << 10)) >> 20;
+  constexpr uint32_t up = (1u << 20) - (1u << 10);
+  const uint32_t upto = ((uint32_t)loads_before(M, g, w, wave + 1) * shares + up) >> 20;
+  const uint32_t share = upto - (((uint32_t)loads_before(M, g, w, wave) * shares + up) >> 20);
   return share > 0 ? (int)share : 1;
 }
 
@@ -212,12 +215,14 @@ constexpr int floor_groups(int E, bool longer) { return longer && E >= 32 ? E / 
 // columns, k = 400, 1000 of 1024, 500 53 %; 4100 columns in eight wavefronts, k = 690, 1461 of 1792, 770 17 %).  What the lists
 // do not hold is searched over the whole row behind them, so from there on better at once, whatever its values (16 / 512 rows, with
 // lists -> without: fp32 4100 columns, k = 500 10.3 / 12.6 -> 7.9 / 9.8; bfloat16 6000 columns, k = 1000 11.0 / 15.7 -> 8.6 / 11.9).
-// Lists of more than 1200 candidates, where they hold, are no better than that either (7600 columns, k = 1000, 13.5 / 16.7 -> 8.8 / 12.0).
+// Lists of more than 1200 candidates, where they hold, are no better than that either (7600 columns, k = 1000, 13.5 / 16.7 -> 8.8 / 12.0;
+// heavy tails 6000, k = 750 16.3 / 18.5 -> 9.7 / 13.3).
 // Below the lines the search over the row is as fast on normal rows (4096 columns, k = 256, 6.7 / 7.8 with lists, 6.5 / 8.4 without;
 // 512 9.4 / 10.9 and 6.8 / 8.4) but not on rows with masked entries (8.7 / 10.4 and 15.6 / 18.9; 11.4 / 12.9 and 15.7 / 18.5).
 inline bool lists_hold(int M, int k, int w, int E, bool longer) {
   const int group = E / floor_groups(E, longer);
-  if (longer) return 5 * k * group <= 3 * M && (w != 8 || E > 16 || k <= 800);
+  if (longer && w == 8 && E == 16) return 20 * k * group <= 9 * M && k <= 800;
+  if (longer) return 5 * k * group <= 3 * M;
   return 2 * k * group <= M;
 }
 

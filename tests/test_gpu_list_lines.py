@@ -40,7 +40,7 @@ def test_fp32_rows(M, ks):
 
 @pytest.mark.parametrize("kind", ("f16", "bf16"))
 @pytest.mark.parametrize("M, ks", [(2051, (256, 307, 308)), (3501, (256, 437, 512)), (4099, (308, 512, 513, 614, 615)),
-                                   (5337, (800, 801)), (8191, (800, 801, 1000)), (9001, (675, 676))])
+                                   (5337, (800, 801)), (8191, (800, 801, 1000)), (6000, (675, 676)), (9001, (675, 676))])
 def test_16bit_rows(kind, M, ks):
     R = _gpu()
     exact, dtype = (R.rtopk_rowwise_exact_f16, torch.float16) if kind == "f16" else (R.rtopk_rowwise_exact_bf16, torch.bfloat16)

@@ -48,12 +48,12 @@ int main() {
               }
               for (int w = 0; w < s.w; ++w) {
                 const int share = floor_share(M, s.g, s.w, w, floor_shares(M, k, s.g));
-                if (loads_of_wave(M, s.g, s.w, w) != loads[w] || loads[w] < 64) ++bad;
+                if (loads_before(M, s.g, s.w, w + 1) - loads_before(M, s.g, s.w, w) != loads[w] || loads[w] < 64) ++bad;
                 const double part = share / (double)maxima[w];
                 if (part > 0.75 || M * (1 - pow(1 - part, 1.0 / group)) > 0.75 * room) ++bad;
                 total += share;
               }
-              if (total < k + 1 || total > k + 1 + s.w) ++bad;
+              if (total < k + 1 || total > (k + 1 > s.w ? k + 1 : k + s.w)) ++bad;
             }
   printf("%ld %ld %ld %ld\n", bad, lists, longer, rows);
   return 0;
