@@ -46,3 +46,31 @@ def test_a_dispatch_mode_sees_new_outputs():
     assert seen.count(torch.ops.aten.empty.memory_format) == 2
     w, j = R.rtopk_rowwise_exact(x, 32)
     assert torch.equal(v, w) and torch.equal(i, j)
+
+
+def test_a_trace_and_a_profiler_see_new_outputs():
+    R = _gpu()
+    x = torch.randn(30, 256, device="cuda")
+    R.rtopk_rowwise_exact(x, 32)
+    traced = torch.jit.trace(lambda t: R.rtopk_rowwise_exact(t, 32), (x,), check_trace=False)
+    assert str(traced.graph).count("aten::empty") == 2
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU]) as p:
+        R.rtopk_rowwise_exact(x, 32)
+    assert sum(e.count for e in p.key_averages() if e.key == "aten::empty") == 2
+
+
+def test_new_outputs_are_filled_where_memory_is_to_be():
+    R = _gpu()
+    x = torch.randn(30, 256, device="cuda")
+    seen = []
+    was = torch.are_deterministic_algorithms_enabled()
+    try:
+        torch.use_deterministic_algorithms(True)
+        with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CPU]) as p:
+            v, i = R.rtopk_rowwise_exact(x, 32)
+        seen = [e.key for e in p.key_averages()]
+    finally:
+        torch.use_deterministic_algorithms(was)
+    assert "aten::fill_" in seen
+    w, j = R.rtopk_rowwise_exact(x, 32)
+    assert torch.equal(v, w) and torch.equal(i, j)
