@@ -181,7 +181,9 @@ __device__ __forceinline__ float grid_floor(float t) {
 // register.  The part of a key is a monotonic function of it, so rounding moves no key past another.  On the lists of a
 // workgroup or a wavefront: 256 x 16384, k = 64 9.4 -> 8.2 us, bfloat16 8.1 -> 7.5; 256 x 32000, k = 64 12.0 -> 11.1; 2097 x 32000
 // 48.4 -> 47.2, bfloat16 40.2 -> 37.9; 256 x 4096 6.8 -> 6.3, but 65536 x 4096, bound by its loads, 187 -> 186.  (16-bit rows of
-// one wavefront search by steps: few values, so few steps and many members of a bin; 4096 columns 28.4 -> 28.9 with bins.)
+// one wavefront search by steps: few values, so few steps and many members of a bin; 4096 columns 28.4 -> 28.9 with bins.  Of 16 values
+// per lane likewise for k up to 8, whose lists fill one or two registers: 86037 x 780, k = 1 54.6 with bins, 50.5 by steps, k = 8 59.5
+// and 55.6, k = 16 57 .. 59 either way; 2048 columns, 1000 rows, k = 8 5.8 and 6.1; not the dense form, 381 x 959, k = 7 5.3 and 5.5.)
 constexpr int kBins = 256;  // part 0 holds the largest keys
 __device__ __forceinline__ void clear_bins(uint32_t* count, int lane) {  // (16-byte aligned)
   reinterpret_cast<uint4*>(count)[lane] = make_uint4(0u, 0u, 0u, 0u);
@@ -851,7 +853,7 @@ __device__ __forceinline__ int filter_wave_row(const float (&x)[Layout<G, NG>::E
     // (the bins at the end of the lists' memory, where no single reaches)
     const int bytes = room * 20 - kBins * 4;
     uint32_t* bins = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(lists) + bytes);
-    if ((int)n * 8 <= bytes) found = kth_by_bins<1, 1, NEG>(lists, (int)n, lane, k, T0, hi, bins, thi, tlo, split, limit);
+    if ((int)n * 8 <= bytes && (E > 16 || k > 8 || DENSE)) found = kth_by_bins<1, 1, NEG>(lists, (int)n, lane, k, T0, hi, bins, thi, tlo, split, limit);
   }
   if (found) {
   } else if (n <= 2 * kWave) {
