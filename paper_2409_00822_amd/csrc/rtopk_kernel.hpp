@@ -1546,19 +1546,19 @@ struct FewRows {
   int64_t one, two, four;
 };
 enum RowForm : int { kPairs = 0, kBytes = 1, kPairsEps = 2 };  // int32 columns, byte-wide columns, Algorithm 1 with precision
-constexpr FewRows few_rows(int E, RowForm form) {
+constexpr FewRows few_rows(int E, RowForm form) {  // (five and more values per lane: two rows at most, so `one` alone counts)
   if (form == kPairsEps) {
     if (E == 1) return {4096, 32768, 196608};
     if (E <= 3) return {8192, 32768, 393216};
-    return {E <= 7 ? 16384 : 40960, 49152, 0};
+    return {E <= 7 ? 16384 : 40960, E == 4 ? 49152 : 0, 0};
   }
   if (E == 1) return {0, 16384, 98304};
   if (E <= 3) return {form == kBytes ? 0 : 4096, 24576, E == 2 ? 196608 : 147456};
-  if (E == 4 && form == kBytes) return {4096, 49152, 147456};
-  return {E <= 6 ? 8192 : (E <= 8 ? 12288 : 32768), 49152, 147456};
+  if (E == 4) return {form == kBytes ? 4096 : 8192, 49152, 147456};
+  return {E <= 6 ? 8192 : (E <= 8 ? 12288 : 32768), 0, 0};
 }
 // Algorithm 2 with up to five steps leaves a wavefront less to do per row, and what it does once -- the validity of its columns,
-// widening -- weighs more: of ragged or 16-bit rows, one per wavefront pays up to half as many, four instead of sixteen up to three
+// widening -- weighs more: of ragged or 16-bit rows with int32 columns, one per wavefront pays up to half as many, four instead of sixteen up to three
 // quarters, of 64 columns and less any kind's (us, four steps unless said otherwise, with the lines above -> with these: 6000 x 300 5.2 -> 4.8, 30000 x 650 20.5 -> 19.3,
 // bfloat16 3000 x 100 3.4 -> 3.2, 10000 x 448 7.0 -> 6.6, 180000 x 100 22.9 -> 20.9, 120000 x 180 19.8 -> 18.7, fp32 90000 x 40 11.2 -> 10.7).
 // 16-bit rows of 16 values per lane that take no lists: one row per wavefront up to 12288 of them, 24576 from six steps on (30000 x 700,
@@ -1569,7 +1569,7 @@ inline FewRows few_rows_early(bool full, const LaunchArgs& a) {
   if (E == 16) {
     if (HALF && a.max_iter < 12 && lists_flag(E, 1, kEarly, false, a.M, a.k, a.max_iter) == 0) few.one = a.max_iter <= 5 ? 12288 : 24576;
   } else if (a.max_iter <= 5) {
-    if (HALF || !full) few.one /= 2;
+    if (HALF || (!full && FORM == kPairs)) few.one /= 2;
     if (E == 1 ? a.max_iter <= 4 : E <= 3 && (HALF || !full)) few.four -= few.four / 4;
   }
   return few;
@@ -1599,7 +1599,7 @@ hipError_t by_rows_dense(int64_t N, F f) {
     return f(std::integral_constant<int, 1>());
   } else {
     if constexpr (E == 4) {
-      if (N > 0x7fffffff) return f(std::integral_constant<int, 4>());  // a grid has no more workgroups than that
+      if (N > 0x7fffffff) return f(std::integral_constant<int, 4>());  // (a grid has no more workgroups than that)
     }
     if (E > 1 && (N < 4096 || (E == 4 && N >= 16384) || (E == 8 && N >= 12288))) return f(std::integral_constant<int, 1>());
     if (E > 2 || N < 24576) return f(std::integral_constant<int, 2>());

@@ -2,7 +2,7 @@
 //
 // One workgroup per row leaves the chip idle when there are few rows, and a row that fills a compute unit's register
 // file by itself (32769 .. 65536 columns) leaves it idle while that row is searched.  Here a row is cut into segments of
-// at most 32768 (or 16384) columns, a workgroup each, in two launches:
+// at most 32768 (or 16384, with longer lists up to 65536) columns, a workgroup each, in two launches:
 //   rtopk_segment_kernel: every segment's candidates -- the keys at or above a floor with more than k keys of the segment
 //     at or above it (steps 1 to 3 of rtopk_filter.hpp) -- go to the scratch memory in column order, with the floor and the
 //     segment's minimum and maximum.  Where values crowd too much for the list (ties, sorted rows), the full-width search of
@@ -20,8 +20,8 @@
 // What bounds it: the segments read the row once at the rate of the 32768-column rows (1.15 times the copy rate's time),
 // the lists add 8 bytes per candidate written and read, 1.2 to 1.4 k of them per segment.  The merge is a launch and a chain of
 // latencies, in which few wavefronts share a SIMD and each instruction takes one of them about seven cycles: so its loads are
-// issued together, no more registers are walked than the row's candidates fill, and exact mode counts each key into a bin
-// once instead of in 10 to 14 steps of a barrier each (one row of 131072 columns, the merge alone: 7.8 -> 4 us).  Kernel
+// issued together, the fewest of 4, 8, 16 or 40 registers that hold the row's candidates are walked, and exact mode counts each
+// key into a bin once instead of in 10 to 14 steps of a barrier each (one row of 131072 columns, the merge alone: 7.8 -> 4 us).  Kernel
 // time, one workgroup per row -> split with steps -> with bins: 64 x 131072, k = 50: 39.5 -> 19.2 -> 13.5 us; 1 x 131072: 36.5 -> 12.6 ->
 // 8.7; 2048 x 50000, k = 100, registers of one workgroup -> split: 135 -> 88 -> 79; 16 x 2^20, k = 100: 31.0 -> 22.9;
 // 256 x 262144, k = 512: 69 -> 59.
@@ -140,7 +140,7 @@ __device__ __forceinline__ MergeResult merge_candidates(MergeLds<NW>& s, int64_t
                                                         RowClasses& rest) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // 64 consecutive ones to a register: number wave * per * 64 + i * 64 + lane.  All loads are issued together (a lane beyond
+  // 64 consecutive ones to a register: number wave * per * 64 + i * 64 + lane.  All loads are issued together, of 40 registers eight at a time (a lane beyond
   // the last candidate repeats its load), with 32-bit offsets: a row's lists are less than 2 GiB.
   float key[KR];
   uint32_t col[KR];
