@@ -1483,7 +1483,11 @@ hipError_t launch(const LaunchArgs& a) {
   using L = Layout<G, NG>;
   if (a.M < L::MIN_M || a.M > 64 * L::E) return hipErrorInvalidValue;
   // LDS per wavefront: at most 64 KiB per block
-  const int flags = a.vec_store | lists_flag(L::E, R, MODE, false, a.M, a.k, a.max_iter);
+  // A wavefront with few pairs stores them one by one, without the streaming policy: by that policy part of a line from each of many
+  // wavefronts takes its turn (bytes 3500 x 256, k = 4, one row each 6.6 -> 4.0 us, k = 16 4.6 -> 3.9; fp32 k = 4 4.4 -> 3.7, 200 x 820 4.6 -> 4.1;
+  // from here on the groups of four are as fast or faster: bfloat16 67108 x 1000, k = 16 44.5, one by one 45.6).
+  const bool few_pairs = R * a.k <= (sizeof(IdxT) == 1 ? 28 : 12);
+  const int flags = (few_pairs ? 0 : a.vec_store) | lists_flag(L::E, R, MODE, false, a.M, a.k, a.max_iter);
   size_t per_wave = (size_t)wave_pairs(L::E, R, MODE, false, a.M, a.k, a.max_iter, flags) * sizeof(uint2);
   // one wavefront per workgroup, except where a wavefront stages 8 KiB or more of pairs: there four
   // per workgroup measured 7 % faster (2^20 x 256, k = 128: 387 -> 360 us), while at 4 KiB and below
