@@ -65,13 +65,17 @@ bool is_shape(const Tensor& t, at::ScalarType type, int64_t rows, int64_t cols) 
   return is_matrix(t, type) && t.size(0) == rows && t.size(1) == cols;
 }
 
+// Whether a call is plain: no dispatch key beyond the default ones is switched on for the thread (modes, function transforms,
+// tracing ...), no profiler listens, and new memory is not to be filled.
+bool is_plain() {
+  return (c10::impl::tls_local_dispatch_key_set().included_ - c10::default_included_set).empty() && !at::hasCallbacks() &&
+         !at::globalContext().deterministicAlgorithms();
+}
+
 // A new tensor on the device.  at::empty goes through the dispatcher twice, which is most of its 0.65 us; a plain call makes the
 // tensor directly, by the same allocator (64 x 256, k = 32, two outputs, a call among others: 5.15 -> 4.70 us, the medians of four
-// runs of either in turn, each within 0.05).  Plain: no dispatch key beyond the default ones is switched on for the thread (modes,
-// function transforms, tracing ...), no profiler listens, and new memory is not to be filled.
-Tensor new_tensor(at::IntArrayRef shape, at::ScalarType type, c10::Device device) {
-  const bool plain = (c10::impl::tls_local_dispatch_key_set().included_ - c10::default_included_set).empty() && !at::hasCallbacks() &&
-                     !at::globalContext().deterministicAlgorithms();
+// runs of either in turn, each within 0.05).
+Tensor new_tensor(at::IntArrayRef shape, at::ScalarType type, c10::Device device, bool plain) {
   if (!plain) return at::empty(shape, at::TensorOptions().dtype(type).device(device));
   return Tensor(at::detail::empty_cuda(shape, type, device, std::nullopt));
 }
@@ -81,7 +85,7 @@ struct Output {
   Tensor tensor;
   PyObject* object = nullptr;
   ~Output() { Py_XDECREF(object); }
-  bool set(PyObject* given, at::ScalarType type, at::IntArrayRef shape, c10::Device device) {
+  bool set(PyObject* given, at::ScalarType type, at::IntArrayRef shape, c10::Device device, bool plain) {
     if (given != Py_None) {
       const Tensor* t = tensor_of(given);
       if (!t || !t->is_cuda() || t->scalar_type() != type || !t->is_contiguous() || t->sizes() != shape) return false;
@@ -89,7 +93,7 @@ struct Output {
       object = Py_NewRef(given);
       return true;
     }
-    tensor = new_tensor(shape, type, device);
+    tensor = new_tensor(shape, type, device, plain);
     object = THPVariable_Wrap(tensor);
     return object != nullptr;
   }
@@ -142,11 +146,11 @@ struct Scratch {
   Tensor tensor;
   void* data = nullptr;
   int64_t bytes = 0;
-  Scratch(const Tensor& x, int32_t k, int32_t variant, int32_t max_iter) {
+  Scratch(const Tensor& x, int32_t k, int32_t variant, int32_t max_iter, bool plain) {
     bytes = rtopk_workspace_bytes(x.size(0), (int32_t)x.size(1), k, variant, max_iter);
     if (bytes > 0) {
       try {
-        tensor = new_tensor({bytes}, at::kByte, x.device());
+        tensor = new_tensor({bytes}, at::kByte, x.device(), plain);
         data = tensor.data_ptr();
       } catch (const c10::OutOfMemoryError&) {
         bytes = 0;
@@ -169,14 +173,15 @@ PyObject* select(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (!x || !is_matrix(*x, vt)) return none();
     const int64_t N = x->size(0), M = x->size(1);
     if (M > std::numeric_limits<int32_t>::max()) return none();
+    const bool plain = is_plain();
     Output v, i;
-    if (!v.set(args[4], vt, {N, k}, x->device()) || !i.set(args[5], it, {N, k}, x->device()))
+    if (!v.set(args[4], vt, {N, k}, x->device(), plain) || !i.set(args[5], it, {N, k}, x->device(), plain))
       return PyErr_Occurred() ? nullptr : none();
     const void* in = x->data_ptr();
     void *ov = v.tensor.data_ptr(), *oi = i.tensor.data_ptr(), *s = stream_of(*x);
     const int32_t m = (int32_t)M;
     const int32_t variant = (exact ? RTOPK_EXACT : RTOPK_EARLY) + (which == 2 ? RTOPK_SMALLEST : 0);
-    Scratch w(*x, which == 0 || which == 2 ? k : 0, variant, max_iter);  // (none for k = 0)
+    Scratch w(*x, which == 0 || which == 2 ? k : 0, variant, max_iter, plain);  // (none for k = 0)
     const int status = unlocked([&]() -> int {
       if (w.bytes > 0)
         return rtopk_select_ws(static_cast<const float*>(in), N, m, k, variant, max_iter, 0.0f, static_cast<float*>(ov),
@@ -212,16 +217,17 @@ PyObject* select_eps(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (!x || !is_matrix(*x, at::kFloat)) return none();
     const int64_t N = x->size(0), M = x->size(1);
     if (M > std::numeric_limits<int32_t>::max()) return none();
+    const bool plain = is_plain();
     Output v, i, t;
-    if (!v.set(args[3], at::kFloat, {N, k}, x->device()) || !i.set(args[4], at::kInt, {N, k}, x->device()) ||
-        (iters != 0 && !t.set(args[5], at::kInt, {N}, x->device())))
+    if (!v.set(args[3], at::kFloat, {N, k}, x->device(), plain) || !i.set(args[4], at::kInt, {N, k}, x->device(), plain) ||
+        (iters != 0 && !t.set(args[5], at::kInt, {N}, x->device(), plain)))
       return PyErr_Occurred() ? nullptr : none();
     const float* in = static_cast<const float*>(x->data_ptr());
     float* ov = static_cast<float*>(v.tensor.data_ptr());
     int32_t* oi = static_cast<int32_t*>(i.tensor.data_ptr());
     int32_t* ot = iters != 0 ? static_cast<int32_t*>(t.tensor.data_ptr()) : nullptr;
     void* s = stream_of(*x);
-    Scratch w(*x, k, RTOPK_EPS, 0);
+    Scratch w(*x, k, RTOPK_EPS, 0, plain);
     const int status = unlocked([&] {
       return rtopk_select_ws(in, N, (int32_t)M, k, RTOPK_EPS, 0, eps, ov, oi, ot, w.data, w.bytes, s);
     });
@@ -245,8 +251,9 @@ PyObject* dense(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (!x || !is_matrix(*x, at::kFloat)) return none();
     const int64_t N = x->size(0), M = x->size(1);
     if (M > std::numeric_limits<int32_t>::max()) return none();
+    const bool plain = is_plain();
     Output y;
-    if (!y.set(args[3], at::kFloat, {N, M}, x->device())) return PyErr_Occurred() ? nullptr : none();
+    if (!y.set(args[3], at::kFloat, {N, M}, x->device(), plain)) return PyErr_Occurred() ? nullptr : none();
     const float* in = static_cast<const float*>(x->data_ptr());
     float* out = static_cast<float*>(y.tensor.data_ptr());
     void* s = stream_of(*x);
@@ -266,8 +273,9 @@ PyObject* scatter(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (!is_matrix(*idx, u8 ? at::kByte : at::kInt) || (u8 && M > 256)) return none();
     const int64_t N = idx->size(0), k = idx->size(1);
     if (k > std::numeric_limits<int32_t>::max() || !is_shape(*g, at::kFloat, N, k)) return none();
+    const bool plain = is_plain();
     Output y;
-    if (!y.set(args[3], at::kFloat, {N, M}, idx->device())) return PyErr_Occurred() ? nullptr : none();
+    if (!y.set(args[3], at::kFloat, {N, M}, idx->device(), plain)) return PyErr_Occurred() ? nullptr : none();
     const float* gv = static_cast<const float*>(g->data_ptr());
     const void* ix = idx->data_ptr();
     float* out = static_cast<float*>(y.tensor.data_ptr());
@@ -290,8 +298,9 @@ PyObject* gather(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (!is_matrix(*idx, u8 ? at::kByte : at::kInt) || (u8 && M > 256) || idx->size(0) != N) return none();
     const int64_t k = idx->size(1);
     if (k > std::numeric_limits<int32_t>::max() || M > std::numeric_limits<int32_t>::max()) return none();
+    const bool plain = is_plain();
     Output y;
-    if (!y.set(args[2], at::kFloat, {N, k}, idx->device())) return PyErr_Occurred() ? nullptr : none();
+    if (!y.set(args[2], at::kFloat, {N, k}, idx->device(), plain)) return PyErr_Occurred() ? nullptr : none();
     const float* go = static_cast<const float*>(g->data_ptr());
     const void* ix = idx->data_ptr();
     float* out = static_cast<float*>(y.tensor.data_ptr());
