@@ -303,10 +303,22 @@ struct Split {
   int64_t bytes() const { return rows * segments * (kSegmentHeadBytes + (int64_t)cap * 8); }
 };
 
+// Algorithm 2 with fewer than eight steps usually ends on a threshold far below the lists' floor.  The lists still decide every
+// step (a count at or below the floor is more than k), and the merging workgroup writes the row's first k keys from the row itself, which
+// costs it a pass up to the k-th of them.  A row that one workgroup holds in registers needs no such pass and stays there (512 x 50000,
+// k = 100, four steps 32 us, split 39); a streamed one is read twice by one workgroup in any case (us, streamed -> split: 1 x 131072, k = 50
+// four steps 39 -> 9.6; 64 x 262144, k = 600 three 126 -> 30; 1 x 10^6, k = 300 208 -> 19; 1024 x 131072 two 214 -> 116, six 119 -> 104; masked rows
+// 200 -> 31, sorted ones 228 -> 81).  Enough rows of 2^19 columns and more to stream at the full rate lose 3 to 7 % with one step, or with five and
+// more (512 x 524288, one 188 -> 194, four 331 -> 188, six 184 -> 192; 256 x 10^6, six 178 -> 192).
+inline bool splits_early(int64_t N, int M, int max_iter) {
+  if (max_iter >= 8) return true;
+  if (max_iter < 1 || M <= kMaxBlockM) return false;
+  return (max_iter >= 2 && max_iter <= 4) || M < 1 << 19 || N * M < 1ll << 28;
+}
 inline Split split_of(int64_t N, int M, int k, int mode, int max_iter) {
   Split s{};
-  // Up to 32768 columns one workgroup per row does as well.  Algorithm 2 with few steps: see launch_block.
-  if (M <= 32768 || N < 1 || k > filter_max_k(8) || (mode == kEarly && max_iter < 8)) return s;
+  // Up to 32768 columns one workgroup per row does as well.
+  if (M <= 32768 || N < 1 || k > filter_max_k(8) || (mode == kEarly && !splits_early(N, M, max_iter))) return s;
   // A segment's candidates: 1.2 to 1.35 k, and the spread of its wavefronts' floors, which weighs when k is small: `usual` is
   // seldom exceeded on ordinary rows (k = 64: 176 at most, k = 512: 1012 in one segment of 200).  The merging workgroup's
   // registers hold what its row can have, unless that is beyond 16 wavefronts: there they hold what is expected of the row.
@@ -333,6 +345,7 @@ inline Split split_of(int64_t N, int M, int k, int mode, int max_iter) {
   s.cap = share > usual ? share : usual;
   if (s.cap > 4 * k + 640) s.cap = 4 * k + 640;
   if (s.cap > segment_room(s.w)) s.cap = segment_room(s.w);
+  if (mode == kEarly && max_iter < 8) s.merge_waves = 16;  // for the pass over the row
   const int64_t per_row = s.segments * (kSegmentHeadBytes + (int64_t)s.cap * 8);
   s.rows = kSplitScratch / per_row;
   if (s.rows < 1) s.rows = 1;
@@ -350,7 +363,7 @@ constexpr int kBigMaxK = 1024;
 constexpr int kMergeRegsBig = 40;  // candidates per lane that 16 merging wavefronts hold at most
 inline Split split_big_of(int64_t N, int M, int k, int mode, int max_iter) {
   Split s{};
-  if (M <= kMaxBlockM || N < 1 || k > kBigMaxK || (mode == kEarly && max_iter < 8)) return s;
+  if (M <= kMaxBlockM || N < 1 || k > kBigMaxK || (mode == kEarly && !splits_early(N, M, max_iter))) return s;
   int root = 1;
   while (root * root < k) ++root;
   s.big = true;

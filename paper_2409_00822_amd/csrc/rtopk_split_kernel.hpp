@@ -402,8 +402,8 @@ __device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ i
     done = merge_candidates<NW, NW == 16 ? kMergeRegsBig : kMergeRegs, MODE, NEG>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters,
                                                                                   of_row, segments, cap, per, total, T0, lo, hi, rest);
   }
-  if (MODE != kExact && done == kMergeFromRow)
-    write_by_chunks<NW, 4, NEG, 2>(in + r * (int64_t)M, M, k, rest.tA, rest.tB, rest.limA, rest.limB, ov, oi);
+  if (MODE != kExact && done == kMergeFromRow)  // (latency bound: a barrier per chunk; 16 wavefronts have the registers for four loads each)
+    write_by_chunks<NW, 4, NEG, NW == 16 ? 4 : 2>(in + r * (int64_t)M, M, k, rest.tA, rest.tB, rest.limA, rest.limB, ov, oi);
   return done != kMergeNoList;
 }
 
