@@ -213,8 +213,11 @@ __device__ __forceinline__ int find_bin(const uint32_t* count, int lane, int k, 
   return 4 * l + __builtin_amdgcn_readlane((int)part, l);
 }
 // The want-th (1-based) of the n members (key bits, column), at most 64 in any order, by key, then column: its key t and its
-// column; cut: members equal to t rank behind it.  Returns false where there is no such member (NaN keys).
-__device__ __forceinline__ bool rank_members(const uint2* member, int lane, int n, int want, float& t, int& column, bool& cut) {
+// column; cut: members equal to t rank behind it; NEXT: the key of the one that ranks next, if there is one.  Returns false
+// where there is no such member (NaN keys).
+template <bool NEXT = false>
+__device__ __forceinline__ bool rank_members(const uint2* member, int lane, int n, int want, float& t, int& column, bool& cut,
+                                             float& next) {
   const uint2 e = member[lane < n ? lane : 0];
   const float key = __uint_as_float(e.x);
   int rank = lane < n ? 0 : 2 * kWave;
@@ -229,7 +232,42 @@ __device__ __forceinline__ bool rank_members(const uint2* member, int lane, int 
   t = __int_as_float(__builtin_amdgcn_readlane((int)e.x, l));
   column = __builtin_amdgcn_readlane((int)e.y, l);
   cut = __builtin_amdgcn_ballot_w64(lane < n && key == t && rank >= want) != 0;
+  if constexpr (NEXT) {
+    const uint64_t behind = __builtin_amdgcn_ballot_w64(rank == want);
+    if (behind == 0) return want == n;
+    next = __int_as_float(__builtin_amdgcn_readlane((int)e.x, __builtin_ctzll(behind)));
+  }
   return true;
+}
+
+// The steps of Algorithm 2, or of Algorithm 1 with precision eps, from the k-th and the (k + 1)-th largest key alone: a
+// threshold counts fewer than k keys where it lies above the k-th and more than k where it does not lie above the next, so no
+// step has anything to count.  A step is half a dozen dependent instructions instead of a compare, a popcount and an add for each register
+// of candidates, and in a workgroup a barrier.  steps: taken already, and then in all; hit: the last one, at thres, counted k.
+template <int MODE>
+__device__ __forceinline__ void steps_by_rank(float kth, float next, int max_iter, float eps, float& lo, float& hi,
+                                              float& thres, bool& hit, int& steps) {
+  hit = false;
+  for (;;) {
+    if (MODE == kEarly ? steps >= max_iter : !(hi - lo > eps)) break;
+    const float mid = (lo + hi) * 0.5f;
+    if (!(mid > lo && mid < hi)) {
+      // no fp32 value strictly inside (lo, hi): Algorithm 1 ends; Algorithm 2's steps repeat one midpoint, equal to lo
+      // (nothing moves) or to hi (lo moves up to it where hi itself counts k or more)
+      if (MODE == kEarly && mid == hi && hi > lo && kth >= hi) lo = hi;
+      break;
+    }
+    ++steps;
+    if (mid > kth) {
+      hi = mid;
+    } else {
+      thres = lo = mid;
+      if (mid > next) {
+        hit = true;
+        break;
+      }
+    }
+  }
 }
 
 // The smallest float above t (of a zero of either sign: the smallest above zero).
@@ -345,7 +383,8 @@ __device__ __forceinline__ bool kth_by_bins(const uint2* single, int n, int lane
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   bool cut;
-  if (!rank_members(member, lane, in_bin, k - above, tlo, split, cut)) return false;
+  float unused;
+  if (!rank_members(member, lane, in_bin, k - above, tlo, split, cut, unused)) return false;
   thi = cut ? next_above(tlo) : tlo;
   if (!cut) split = 0x7fffffff;
   return true;

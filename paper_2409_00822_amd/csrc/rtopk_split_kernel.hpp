@@ -10,7 +10,8 @@
 //     the first in column order are listed, more than the row's selection can take from this segment;
 //   rtopk_merge_kernel: one workgroup per row.  The largest of the segments' floors has more than k keys of the row at or
 //     above it, and the lists hold all of those, so Algorithms 1 and 2 run on the lists with exact branch decisions (see
-//     rtopk_filter.hpp; exact mode finds the k-th key by bins instead); the lists follow each other in column order, so
+//     rtopk_filter.hpp; exact mode finds the k-th key by bins instead, and so do the others where they have steps enough, which
+//     the k-th and the next key then decide without a count); the lists follow each other in column order, so
 //     places are prefix counts.
 // A row whose last threshold is not above the floor is written from the row itself.  A row with more candidates than the
 // merging workgroup's registers hold (only where `cap` of split_of says that they may) is done by that workgroup as a
@@ -129,10 +130,11 @@ struct MergeLds {
   alignas(16) uint32_t bins[kBins];
   uint2 member[kWave];  // of the bin with the k-th key: (key bits, column), any order
   uint32_t members;
+  float below[NW];  // per wavefront: its largest key in lower bins
 };
 
 // One row's candidates, KR registers of them per lane, `per` in use: the search and the pairs.  Uniform over the workgroup.
-template <int NW, int KR, int MODE, bool NEG>
+template <int NW, int KR, int MODE, bool NEG, bool RANK>
 __device__ __forceinline__ MergeResult merge_candidates(MergeLds<NW>& s, int64_t r, int M, int k, int max_iter, float eps_rel,
                                                         float* __restrict__ ov, int32_t* __restrict__ oi,
                                                         int32_t* __restrict__ out_iters, const uint2* __restrict__ lists,
@@ -175,8 +177,13 @@ __device__ __forceinline__ MergeResult merge_candidates(MergeLds<NW>& s, int64_t
     }
   };
   static_for<KR / kBatch>(load);
-  if constexpr (MODE == kExact) {
-    // the k-th key by bins (see kth_by_bins): every wavefront bins its own, then all find the same bin and rank its members
+  // RANK: the k-th key by bins (see kth_by_bins): every wavefront bins its own, then all find the same bin and rank its members.
+  // Exact mode takes the keys above it and the first of those equal to it; the other modes' steps are decided by it and
+  // the next one (steps_by_rank).
+  bool ranked = false;
+  float kth = 0.0f, next = 0.0f;
+  const float eps = MODE == kEps ? eps_rel * __builtin_fabsf(hi) : 0.0f;
+  if constexpr (RANK) {
     const float scale = bins_scale(T0, hi);
 #pragma unroll
     for (int i = 0; i < KR; ++i) {
@@ -186,21 +193,37 @@ __device__ __forceinline__ MergeResult merge_candidates(MergeLds<NW>& s, int64_t
     int above, in_bin;
     const int chosen = find_bin(s.bins, lane, k, above, in_bin);
     if (chosen >= 0 && in_bin <= kWave) {  // uniform
+      const bool last_in_bin = MODE != kExact && k - above == in_bin;  // the next key is in a lower bin
+      float below = -__builtin_inff();
 #pragma unroll
       for (int i = 0; i < KR; ++i) {
         if constexpr (KR > 16) asm volatile("" : "+v"(key[i]));  // (the bins are not kept in as many registers again)
-        if (key[i] >= T0 && bin_of(key[i], hi, scale) == chosen) {
-          const uint32_t at = atomicAdd(&s.members, 1u);
-          if (at < (uint32_t)kWave) s.member[at] = make_uint2(__float_as_uint(key[i]), col[i]);
+        if (key[i] >= T0) {
+          const int bin = bin_of(key[i], hi, scale);
+          if (bin == chosen) {
+            const uint32_t at = atomicAdd(&s.members, 1u);
+            if (at < (uint32_t)kWave) s.member[at] = make_uint2(__float_as_uint(key[i]), col[i]);
+          }
+          if (MODE != kExact && bin > chosen) below = vmax(below, key[i]);
         }
       }
+      if (last_in_bin) {  // uniform
+        float largest, unused;
+        wave_max_and_negmin(below, below, largest, unused);
+        if (lane == 0) s.below[wave] = largest;
+      }
       __syncthreads();
-      float t;
       int tcol;
       bool cut;
-      if (rank_members(s.member, lane, in_bin, k - above, t, tcol, cut)) {
+      ranked = rank_members<MODE != kExact>(s.member, lane, in_bin, k - above, kth, tcol, cut, next);
+      if (last_in_bin) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) next = w == 0 ? s.below[0] : vmax(next, s.below[w]);
+        ranked = ranked && next > -__builtin_inff();
+      }
+      if (MODE == kExact && ranked) {
         auto chosen_mask = [&](int i) -> uint64_t {
-          return __builtin_amdgcn_ballot_w64(key[i] > t || (key[i] == t && (int)col[i] <= tcol));
+          return __builtin_amdgcn_ballot_w64(key[i] > kth || (key[i] == kth && (int)col[i] <= tcol));
         };
         constexpr bool kKeep = KR <= 16;
         uint64_t kept[kKeep ? KR : 1];
@@ -244,33 +267,35 @@ __device__ __forceinline__ MergeResult merge_candidates(MergeLds<NW>& s, int64_t
     __syncthreads();
     return __builtin_amdgcn_readfirstlane((int)row16_sum(lane < NW ? (uint32_t)s.cnt[p][lane] : 0u));
   };
-  if (count(T0) <= k) return kMergeNoList;  // (only with NaN or infinite keys)
-
-  // The search (see filter_search): exact mode may start at the floor, the others follow their thresholds.
   bool hit = false;
   float thres = lo;
   int steps = 0;
-  const float eps = MODE == kEps ? eps_rel * __builtin_fabsf(hi) : 0.0f;
-  if (MODE == kExact) lo = T0;
-  for (;;) {
-    if (MODE == kEarly && steps >= max_iter) break;
-    if (MODE == kEps && !(hi - lo > eps)) break;
-    const float mid = (lo + hi) * 0.5f;
-    if (!(mid > lo && mid < hi)) {
-      // no fp32 value strictly inside (lo, hi): Algorithm 1 ends; Algorithm 2's steps repeat one midpoint, equal to lo
-      // (nothing moves) or to hi (lo moves up to it where hi itself counts k or more)
-      if (MODE == kEarly && mid == hi && hi > lo && count(hi) >= k) lo = hi;
-      break;
+  if (RANK && MODE != kExact && ranked) {
+    steps_by_rank<MODE>(kth, next, max_iter, eps, lo, hi, thres, hit, steps);
+  } else {
+    if (count(T0) <= k) return kMergeNoList;  // (only with NaN or infinite keys)
+    // The search (see filter_search): exact mode may start at the floor, the others follow their thresholds.
+    if (MODE == kExact) lo = T0;
+    for (;;) {
+      if (MODE == kEarly && steps >= max_iter) break;
+      if (MODE == kEps && !(hi - lo > eps)) break;
+      const float mid = (lo + hi) * 0.5f;
+      if (!(mid > lo && mid < hi)) {
+        // no fp32 value strictly inside (lo, hi): Algorithm 1 ends; Algorithm 2's steps repeat one midpoint, equal to lo
+        // (nothing moves) or to hi (lo moves up to it where hi itself counts k or more)
+        if (MODE == kEarly && mid == hi && hi > lo && count(hi) >= k) lo = hi;
+        break;
+      }
+      const int cnt = mid > T0 ? count(mid) : k + 1;
+      thres = mid;
+      ++steps;
+      if (cnt == k) {
+        hit = true;
+        if (MODE == kEarly) lo = mid;
+        break;
+      }
+      if (cnt < k) hi = mid; else lo = mid;
     }
-    const int cnt = mid > T0 ? count(mid) : k + 1;
-    thres = mid;
-    ++steps;
-    if (cnt == k) {
-      hit = true;
-      if (MODE == kEarly) lo = mid;
-      break;
-    }
-    if (cnt < k) hi = mid; else lo = mid;
   }
   // Two classes and a limit for each (as in rtopk_block_kernel).
   float tA, tB = 0.0f;
@@ -336,17 +361,16 @@ __device__ __forceinline__ MergeResult merge_candidates(MergeLds<NW>& s, int64_t
 // One row: its search on the segments' lists, and its selection from them, or, where the search ends on a minimum below
 // the floor, from the row.  Returns false, with nothing written, where the lists do not hold the search.  Called by the
 // whole workgroup; uniform.
-template <int NW, int MODE, bool NEG>
-__device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ in, int M, int k, int max_iter, float eps_rel,
-                                          float* __restrict__ out_vals, int32_t* __restrict__ out_idx,
+template <int NW, int MODE, bool NEG, bool RANK>
+__device__ __forceinline__ bool merge_row(MergeLds<NW>& s, int64_t r, const float* __restrict__ in, int M, int k, int max_iter,
+                                          float eps_rel, float* __restrict__ out_vals, int32_t* __restrict__ out_idx,
                                           int32_t* __restrict__ out_iters, const SegmentHead* __restrict__ heads,
                                           const uint2* __restrict__ lists, int segments, int cap) {
-  __shared__ MergeLds<NW> s;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
   // The segments' heads, by one wavefront, while the last clears the bins.
-  if (MODE == kExact && wave == NW - 1) {
+  if (RANK && wave == NW - 1) {
     clear_bins(s.bins, lane);
     if (lane == 0) s.members = 0;
   }
@@ -378,44 +402,66 @@ __device__ __forceinline__ bool merge_row(int64_t r, const float* __restrict__ i
   __syncthreads();
   const int total = __builtin_amdgcn_readfirstlane(s.total);
   const float T0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[0])));
-  float lo = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[1])));
-  float hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[2])));
+  const float lo = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[1])));
+  const float hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[2])));
   if (total <= k || total > NW * kWave * (NW == 16 ? kMergeRegsBig : kMergeRegs)) return false;
-
 
   float* ov = out_vals + r * (int64_t)k;
   int32_t* oi = out_idx + r * (int64_t)k;
   const int per = (total + NW * kWave - 1) / (NW * kWave);
   const uint2* of_row = lists + r * segments * cap;
   RowClasses rest;
+  auto candidates = [&](auto regs) -> MergeResult {
+    constexpr int KR = decltype(regs)::value;
+    return merge_candidates<NW, KR, MODE, NEG, RANK>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters, of_row, segments, cap, per, total, T0,
+                                               lo, hi, rest);
+  };
   MergeResult done;
   if (per <= 4) {  // (as few registers as serve: a wavefront issues an instruction in seven cycles, and few share a SIMD here)
-    done = merge_candidates<NW, 4, MODE, NEG>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters, of_row, segments, cap, per, total, T0,
-                                              lo, hi, rest);
+    done = candidates(std::integral_constant<int, 4>());
   } else if (per <= 8) {
-    done = merge_candidates<NW, 8, MODE, NEG>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters, of_row, segments, cap, per, total, T0,
-                                              lo, hi, rest);
+    done = candidates(std::integral_constant<int, 8>());
   } else if (NW < 16 || per <= kMergeRegs) {
-    done = merge_candidates<NW, kMergeRegs, MODE, NEG>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters, of_row, segments, cap, per,
-                                                       total, T0, lo, hi, rest);
+    done = candidates(std::integral_constant<int, kMergeRegs>());
   } else {
-    done = merge_candidates<NW, NW == 16 ? kMergeRegsBig : kMergeRegs, MODE, NEG>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters,
-                                                                                  of_row, segments, cap, per, total, T0, lo, hi, rest);
+    done = candidates(std::integral_constant<int, NW == 16 ? kMergeRegsBig : kMergeRegs>());
   }
   if (MODE != kExact && done == kMergeFromRow)  // (latency bound: a barrier per chunk; 16 wavefronts have the registers for four loads each)
     write_by_chunks<NW, 4, NEG, NW == 16 ? 4 : 2>(in + r * (int64_t)M, M, k, rest.tA, rest.tB, rest.limA, rest.limB, ov, oi);
   return done != kMergeNoList;
 }
 
-template <int NW, int MODE, bool NEG>
+template <int NW, int MODE, bool NEG, bool RANK>
 __global__ void __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(4)))
     rtopk_merge_kernel(const float* __restrict__ in, int M, int k, int max_iter, float eps_rel,
                        float* __restrict__ out_vals, int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters,
                        const SegmentHead* __restrict__ heads, const uint2* __restrict__ lists, int segments, int cap) {
   const int64_t r = blockIdx.x;
-  if (merge_row<NW, MODE, NEG>(r, in, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, heads, lists, segments, cap)) return;
+  __shared__ union {
+    MergeLds<NW> merge;
+    StreamLds<NW> stream;
+  } s;
+  if (merge_row<NW, MODE, NEG, RANK>(s.merge, r, in, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, heads, lists, segments, cap)) return;
   __syncthreads();
-  stream_row<NW, 4, MODE, NEG>(r, in, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters);
+  stream_row<NW, 4, MODE, NEG>(s.stream, r, in, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters);
+}
+
+// Whether the merge finds the k-th key, from which every step follows, rather than count in each step.  Exact mode always; the other
+// modes from about eight steps above the lists' floor on (us, steps counted -> by rank: precision 1e-6 36 x 63680, k = 82 14.1 -> 13.0, 1e-4
+// 64 x 50000, k = 200 16.1 -> 15.0, 1e-2 14.0 -> 14.2; 64 x 50000 40 steps 16.0 -> 14.4, 16 15.5 -> 14.2, 8 13.2 -> 13.5; 8 x 10^6, k = 300, 16
+// 28.1 -> 26.2), but not the longest lists, whose bins hold many (16 x 131072, k = 900, 16 steps 21.0 -> 21.8).
+inline bool ranks(const Split& s, int mode, const LaunchArgs& a) {
+  return mode == kExact || (!s.big && (mode == kEarly ? a.max_iter >= 12 : a.eps_rel < 0x1p-10f));
+}
+template <int MODE, bool NEG, bool RANK>
+hipError_t launch_merge(const Split& s, int64_t rows, const SegmentHead* heads, const uint2* lists, const LaunchArgs& a, int64_t r0) {
+  const auto merge = s.merge_waves == 4   ? &rtopk_merge_kernel<4, MODE, NEG, RANK>
+                     : s.merge_waves == 8 ? &rtopk_merge_kernel<8, MODE, NEG, RANK>
+                                          : &rtopk_merge_kernel<16, MODE, NEG, RANK>;
+  return launch_kernel(merge, dim3((unsigned)rows), dim3(s.merge_waves * kWave), 0, a.stream, static_cast<const float*>(a.in) + r0 * a.M,
+                       a.M, a.k, a.max_iter, a.eps_rel, static_cast<float*>(a.out_vals) + r0 * a.k,
+                       static_cast<int32_t*>(a.out_idx) + r0 * a.k, a.out_iters ? a.out_iters + r0 : nullptr, heads, lists, s.segments,
+                       s.cap);
 }
 
 template <int MODE, bool NEG>
@@ -432,12 +478,9 @@ hipError_t launch_split(const Split& s, void* scratch, const LaunchArgs& a) {
     hipError_t err = launch_kernel(segment, dim3((unsigned)(rows * s.segments)), dim3(s.w * kWave), 0, a.stream, in, a.M, a.k,
                                    s.segments, s.length, s.cap, heads, lists, shares, shares_last);
     if (err != hipSuccess) return err;
-    const auto merge = s.merge_waves == 4   ? &rtopk_merge_kernel<4, MODE, NEG>
-                       : s.merge_waves == 8 ? &rtopk_merge_kernel<8, MODE, NEG>
-                                            : &rtopk_merge_kernel<16, MODE, NEG>;
-    err = launch_kernel(merge, dim3((unsigned)rows), dim3(s.merge_waves * kWave), 0, a.stream, in, a.M, a.k, a.max_iter,
-                        a.eps_rel, static_cast<float*>(a.out_vals) + r0 * a.k, static_cast<int32_t*>(a.out_idx) + r0 * a.k,
-                        a.out_iters ? a.out_iters + r0 : nullptr, heads, lists, s.segments, s.cap);
+    hipError_t (*const merge)(const Split&, int64_t, const SegmentHead*, const uint2*, const LaunchArgs&, int64_t) =
+        ranks(s, MODE, a) ? &launch_merge<MODE, NEG, true> : &launch_merge<MODE, NEG, MODE == kExact>;
+    err = merge(s, rows, heads, lists, a, r0);
     if (err != hipSuccess) return err;
   }
   return hipSuccess;

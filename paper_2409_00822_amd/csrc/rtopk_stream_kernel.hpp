@@ -134,24 +134,43 @@ __device__ __forceinline__ void write_by_chunks(const float* __restrict__ row, i
   }
 }
 
+// What the workgroup of a streamed row keeps in LDS.
+template <int NW>
+struct StreamLds {
+  float tab[kLeaves];       // thresholds of the tree's nodes 1..255 (heap order; [0] unused)
+  float bnd[kLeaves + 1];   // the same thresholds in value order, with lo and hi at the ends
+  int hist[NW][kLeaves];    // per-wavefront leaf histograms
+  int suffix[kLeaves + 1];  // suffix[j] = band members in leaves j..255
+  float hi[NW], nlo[NW];
+  int above[NW];
+  alignas(16) int parts[3][kLeaves];  // pass 0: kept keys per part of [floor, largest key seen)
+  float top[2][NW];                   // pass 0: per-wavefront largest key seen, exchanged by a raise for the next one
+  int voided[NW];                     // per wavefront: its list of pass 0 ran full
+  int cnt[2][NW];                     // per-wavefront counts of a search step on the lists, double buffered
+  int pre[2][NW];                     // per-wavefront candidate counts of a chunk (A in the low half, B in the high), double buffered
+  alignas(8) uint2 kept[NW][kKeptPerWave];  // per wavefront, in column order: (value bits, column) of the keys at or above the floor
+                                            // of pass 0, later at or above bstar of a search pass
+};
+
 // One row, by the whole workgroup of NW wavefronts (at least four: the 256 leaves have a thread each).
 template <int NW, int G, int MODE, bool NEG>
-__device__ __forceinline__ void stream_row(const int64_t r, const float* __restrict__ in, int M, int k, int max_iter,
-                                           float eps_rel, float* __restrict__ out_vals, int32_t* __restrict__ out_idx,
-                                           int32_t* __restrict__ out_iters) {
+__device__ __forceinline__ void stream_row(StreamLds<NW>& lds, const int64_t r, const float* __restrict__ in, int M, int k,
+                                           int max_iter, float eps_rel, float* __restrict__ out_vals,
+                                           int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters) {
   constexpr int kStreamWaves = NW, kStreamThreads = NW * kWave;
-  __shared__ float s_tab[kLeaves];               // thresholds of the tree's nodes 1..255 (heap order; [0] unused)
-  __shared__ float s_bnd[kLeaves + 1];           // the same thresholds in value order, with lo and hi at the ends
-  __shared__ int s_hist[kStreamWaves][kLeaves];  // per-wavefront leaf histograms
-  __shared__ int s_suffix[kLeaves + 1];          // suffix[j] = band members in leaves j..255
-  __shared__ float s_hi[kStreamWaves], s_nlo[kStreamWaves];
-  __shared__ int s_above[kStreamWaves];
-  __shared__ __attribute__((aligned(16))) int s_parts[3][kLeaves];  // pass 0: kept keys per part of [floor, largest key seen)
-  __shared__ float s_top[2][kStreamWaves];  // pass 0: per-wavefront largest key seen, exchanged by a raise for the next one
-  __shared__ int s_void[kStreamWaves];    // per wavefront: its list of pass 0 ran full
-  __shared__ int s_cnt[2][kStreamWaves];  // per-wavefront counts of a search step on the lists, double buffered
-  __shared__ int s_pre[2][kStreamWaves];  // per-wavefront candidate counts of a chunk (A in the low half, B in the high), double buffered
-  __shared__ uint2 s_kept[kStreamWaves][kKeptPerWave];  // per wavefront, in column order: (value bits, column) of the keys at or above the floor of pass 0, later at or above bstar of a search pass
+  auto& s_tab = lds.tab;
+  auto& s_bnd = lds.bnd;
+  auto& s_hist = lds.hist;
+  auto& s_suffix = lds.suffix;
+  auto& s_hi = lds.hi;
+  auto& s_nlo = lds.nlo;
+  auto& s_above = lds.above;
+  auto& s_parts = lds.parts;
+  auto& s_top = lds.top;
+  auto& s_void = lds.voided;
+  auto& s_cnt = lds.cnt;
+  auto& s_pre = lds.pre;
+  auto& s_kept = lds.kept;
 
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
@@ -887,7 +906,8 @@ __global__ void __launch_bounds__(kStreamWaves * kWave) __attribute__((amdgpu_wa
                         float* __restrict__ out_vals, int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters) {
   const int64_t r = blockIdx.x;
   if (r >= N) return;
-  stream_row<kStreamWaves, G, MODE, NEG>(r, in, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters);
+  __shared__ StreamLds<kStreamWaves> lds;
+  stream_row<kStreamWaves, G, MODE, NEG>(lds, r, in, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters);
 }
 
 template <int MODE, bool NEG>
