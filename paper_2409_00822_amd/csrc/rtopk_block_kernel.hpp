@@ -779,14 +779,14 @@ __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(
   block_rows<G, NG, W, MODE, NEG, DT, DENSE, true>(in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, shares);
 }
 
-// Exact mode with longer lists, for larger k; floors from groups of eight values, more of them than k needs.
-template <int G, int NG, int W, bool NEG, int DT>
+// Longer lists, for larger k; floors from groups of eight values, more of them than k needs.
+template <int G, int NG, int W, bool NEG, int DT, int MODE>
 __global__ void __launch_bounds__(W * kWave) __attribute__((amdgpu_waves_per_eu(4)))
     rtopk_filter_big_kernel(const void* __restrict__ in, int64_t N, int M, int k, int max_iter, float eps_rel,
                             void* __restrict__ out_vals, int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters,
                             uint32_t shares) {
-  block_rows<G, NG, W, kExact, NEG, DT, false, true, big_list_room(W)>(in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters,
-                                                                       shares);
+  block_rows<G, NG, W, MODE, NEG, DT, false, true, big_list_room(W)>(in, N, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters,
+                                                                     shares);
 }
 
 // Compute units of the current device (asked once per device; concurrent first calls store the same value).
@@ -819,7 +819,7 @@ hipError_t launch_block(const LaunchArgs& a) {
   s.g = G;
   s.ng = NG;
   s.w = W;
-  const int search = block_search(s, a.M, a.k, DT, MODE, a.max_iter, DENSE);
+  const int search = block_search(s, a.M, a.k, DT, MODE, a.max_iter, DENSE, a.N, a.eps_rel);
   auto launch = [&](auto kernel, auto... shares) {
     return launch_kernel(kernel, dim3((unsigned)grid), dim3(W * kWave), 0, a.stream, a.in, a.N, a.M, a.k, a.max_iter, a.eps_rel,
                          a.out_vals, static_cast<int32_t*>(a.out_idx), a.out_iters, shares...);
@@ -831,7 +831,7 @@ hipError_t launch_block(const LaunchArgs& a) {
     if (search == kSearchLists) return launch(&rtopk_filter_kernel<G, NG, W, MODE, NEG, DT, DENSE>, floor_shares(a.M, a.k, G));
   }
   if constexpr ((K & kSearchLongLists) != 0) {
-    if (search == kSearchLongLists) return launch(&rtopk_filter_big_kernel<G, NG, W, NEG, DT>, floor_shares(a.M, a.k, G));
+    if (search == kSearchLongLists) return launch(&rtopk_filter_big_kernel<G, NG, W, NEG, DT, MODE>, floor_shares(a.M, a.k, G));
   }
   return hipErrorInvalidValue;
 }

@@ -390,6 +390,29 @@ __device__ __forceinline__ bool kth_by_bins(const uint2* single, int n, int lane
   return true;
 }
 
+// #{singles with a key at or above t}, and the largest key below t (-inf if there is none), by one wavefront.
+template <bool NEG>
+__device__ __forceinline__ int count_singles(const uint2* single, int n, int lane, float t, float& below) {
+  float neg = __builtin_inff(), largest = -__builtin_inff();
+  int count = 0;
+  for (int i0 = 0; i0 < n; i0 += 4 * kWave) {
+    float key[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int j = i0 + i * kWave + lane;
+      key[i] = keyof<NEG>(__uint_as_float(single[j < n ? j : 0].x));
+      if (j >= n) key[i] = -__builtin_inff();
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      count += __builtin_popcountll(__builtin_amdgcn_ballot_w64(key[i] >= t));
+      largest = key[i] < t ? vmax(largest, key[i]) : largest;
+    }
+  }
+  wave_max_and_negmin(largest, neg, below, neg);
+  return count;
+}
+
 // LDS of one row.  CAP: quads, and singles, that the lists hold (list_room, big_list_room).  The bitmaps take the quads' place when those
 // have become singles.
 template <int W, int ROOM = list_room(W)>
@@ -599,7 +622,7 @@ __device__ __forceinline__ int filter_row(FilterLds<W, ROOM>& s, const float (&x
                                           float eps, float T0, float probe, float& lo, float& hi, float& thi, float& tlo,
                                           int& split, int& iterations, Column column, Listed listed, Emit emit) {
   constexpr int CAP = ROOM;
-  constexpr bool BIG = ROOM > list_room(W);  // exact mode only: the bins, or no list
+  constexpr bool BIG = ROOM > list_room(W);  // the bins, or no list
   const int tid = wave * kWave + lane;
   float low = lo;  // (lo itself stays for the caller's search of a row that the lists do not hold)
   int walked = 0;
@@ -624,13 +647,26 @@ __device__ __forceinline__ int filter_row(FilterLds<W, ROOM>& s, const float (&x
     int steps = walked, cnt = -1, na = 0, last = 0x7fffffff;
     float by_bins_hi, by_bins_lo;
     int by_bins_limit = 0;
-    bool found = false;
+    bool found = false, ranked = false;
     if constexpr (MODE == kExact) {
       // (16-bit rows have few values, so a larger k finds many members in its bin: 2048 x 32768, bfloat16, k = 256, 256 rows
       // 10.4 -> 10.7 us with bins, k = 64 9.9 -> 9.3)
       if (BIG || DT == kF32 || k <= 128) {
         found = kth_by_bins<4, BIG ? 3 : 1, NEG>(s.single, n, lane, k, T0, hi, s.bins, by_bins_hi, by_bins_lo, last,
                                                  by_bins_limit);
+      }
+    } else if constexpr (BIG) {
+      // the k-th key and the next, and the steps that they decide.  (On the shorter lists one wavefront counts a step in 150 cycles, and the ten
+      // to twelve that end on a count of k cost less than bins and two passes: 64 x 16384, k = 250, 1e-4 10.4 -> 11.2 us, 16 steps 9.6 -> 11.0.)
+      if (kth_by_bins<4, 3, NEG>(s.single, n, lane, k, T0, hi, s.bins, by_bins_hi, by_bins_lo, last, by_bins_limit)) {
+        const float kth = by_bins_lo;
+        float next;
+        if (count_singles<NEG>(s.single, n, lane, kth, next) > k) next = kth;
+        steps_by_rank<MODE>(kth, next, max_iter, eps, l, h, thres, hit, steps);
+        cnt = hit ? k : -1;
+        float unused;
+        if (MODE == kEps && !hit) na = count_singles<NEG>(s.single, n, lane, h, unused);
+        ranked = true;
       }
     }
     if (found || BIG) {
@@ -677,7 +713,7 @@ __device__ __forceinline__ int filter_row(FilterLds<W, ROOM>& s, const float (&x
       s.info[0] = limit;
       s.info[1] = hit ? steps : steps + 1;
       s.info[2] = found ? last : 0x7fffffff;
-      s.state = (listed ? 0 : 1) | (MODE == kEarly && cnt != k ? 2 : 0) | (BIG && !found ? 4 : 0);
+      s.state = (listed ? 0 : 1) | (MODE == kEarly && cnt != k ? 2 : 0) | (BIG && !found && !ranked ? 4 : 0);
     }
   }
   __syncthreads();

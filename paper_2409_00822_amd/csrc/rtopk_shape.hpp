@@ -60,7 +60,7 @@ struct Shape {
 
 // Largest k that the lists of a workgroup of w wavefronts take (rtopk_filter.hpp).
 constexpr int filter_max_k(int w) { return w == 4 ? 256 : 512; }
-// The same for exact mode's longer lists.
+// The same for the longer lists of exact mode and the precision-bounded one.
 constexpr int big_filter_max_k(int w) { return w == 4 ? 512 : 1024; }
 // Candidates that either hold.
 constexpr int kBigRoom = 1792;
@@ -226,15 +226,21 @@ inline bool lists_hold(int M, int k, int w, int E, bool longer) {
   return 2 * k * group <= M;
 }
 
-// The search of a call whose layout s is a workgroup's.
-inline int block_search(const Shape& s, int M, int k, int dtype, int mode, int max_iter, bool dense) {
+// The search of a call whose layout s is a workgroup's.  N, eps_rel: what the precision-bounded mode goes by besides.
+inline int block_search(const Shape& s, int M, int k, int dtype, int mode, int max_iter, bool dense, int64_t N = 1 << 20,
+                        float eps_rel = 0.0f) {
   const int E = s.values();
   // Algorithm 2 with few steps ends on a threshold far below the k-th key, which the lists do not reach: the search
   // is then wasted, and with 16 wavefronts the row is read again (50000 columns, k = 256, four steps: 134 us
   // against 88 us; 32768 columns 56.6 against 56.1).  From eight (five) steps on the lists win as in exact mode.
   if (k <= filter_max_k(s.w) && (mode != kEarly || max_iter >= (s.w == 16 ? 8 : 5)))
     return lists_hold(M, k, s.w, E, false) ? kSearchLists : kSearchRow;
-  if (mode != kExact || dense || k > big_filter_max_k(s.w)) return kSearchRow;
+  if (dense || mode == kEarly || k > big_filter_max_k(s.w)) return kSearchRow;
+  // The precision-bounded mode's steps follow from the k-th key and the next (steps_by_rank), and a search over the row that ends without
+  // a count of k ranks its band by one lane mask after another (us, over the row -> lists: 103 x 9312, k = 360, 1e-2 15.5 -> 13.0, 1e-4 16.4 ->
+  // 13.4, 1e-6 11.8 -> 12.5; 2000 x 9000, k = 300 48 -> 31, 39 -> 30, 33 -> 29; 64 x 30000, k = 750 20.3 -> 18.6, 20.8 -> 18.4, 15.8 -> 17.1; 200
+  // x 25000, k = 520, 1e-6 17.7 -> 16.0).
+  if (mode == kEps && (E < 48 || (N < 200 && eps_rel < 1e-5f))) return kSearchRow;
   if (E < 48) return lists_hold(M, k, s.w, E, true) ? kSearchLongLists : kSearchRow;
   // Longer lists where k is a small part of the row (us, search over the row -> lists): 12288 columns, k = 500 39 -> 36;
   // 16384, k = 400 38.5 -> 31.2; 24000, k = 600 43.4 -> 40.4, 1000 45.9 -> 50.0; 32768, k = 600 44 -> 34; 50000, k = 1000
@@ -247,7 +253,7 @@ inline int block_search(const Shape& s, int M, int k, int dtype, int mode, int m
 // The searches that layout_of_call and block_search can ask of a workgroup layout of E values per lane in w wavefronts: those
 // that are compiled.  (Layouts of fewer than 48 values per lane are for few rows only: lists with k <= 256, exact mode with more.)
 constexpr int block_kernels(int E, int w, int mode, bool dense, bool half) {
-  if (E >= 48) return kSearchRow | kSearchLists | (mode == kExact && !dense ? kSearchLongLists : 0);
+  if (E >= 48) return kSearchRow | kSearchLists | (mode != kEarly && !dense ? kSearchLongLists : 0);
   if (w == 8) return mode != kExact || dense ? 0 : (half ? kSearchRow | kSearchLongLists : kSearchLongLists);
   if (mode == kExact && !dense) return kSearchRow | kSearchLists | kSearchLongLists;
   return E == 32 || dense ? (E == 16 && mode != kExact ? 0 : kSearchLists) : 0;

@@ -61,3 +61,13 @@ def _check(R, x, k, steps, precisions, tag):
 def test_split_rows(M, k):
     x = np.concatenate([_rows(M, M + 1), _gap_rows(M, k, M + k)])
     _check(_gpu(), x, k, (11, 12, 13, 30, 400), (1e-3, 9e-4, 1e-5, 0.0), f"M={M} k={k}")
+
+
+@pytest.mark.parametrize("M, k", [(8200, 257), (9312, 360), (12289, 400), (16384, 512), (16400, 513), (24577, 700), (30000, 1000),
+                                  (32768, 1024)])
+def test_longer_lists_of_a_workgroup(M, k):
+    """The longer lists of the precision-bounded mode; rows that they do not hold; few rows at 1e-6, which take the search over the row."""
+    x = np.concatenate([_rows(M, M + 1), _gap_rows(M, k, M + k)])
+    x = np.concatenate([x] * (200 // len(x) + 1))
+    _check(_gpu(), x, k, (12,), (0.05, 1e-3, 1e-5, 0.0), f"M={M} k={k}")
+    _check(_gpu(), x[:40], k, (12,), (1e-2, 1e-6, 0.0), f"M={M} k={k} few")
