@@ -14,10 +14,12 @@ hipError_t launch_block_dense(int g, int ng, int w, int mode, const LaunchArgs& 
   if (g == 4) {
     if (w == 4 && ng == 4) return pick<4, 4, 4>(mode, a);
     if (w == 4 && ng == 8) return pick<4, 8, 4>(mode, a);
-    if (ng != 16) return hipErrorInvalidValue;
-    if (w == 4) return pick<4, 16, 4>(mode, a);
-    if (w == 8) return pick<4, 16, 8>(mode, a);
-    if (w == 16) return pick<4, 16, 16>(mode, a);
+    if (w == 4 && ng == 12) return pick<4, 12, 4>(mode, a);
+    if (w == 4 && ng == 16) return pick<4, 16, 4>(mode, a);
+    if (w == 8 && ng == 12) return pick<4, 12, 8>(mode, a);
+    if (w == 8 && ng == 16) return pick<4, 16, 8>(mode, a);
+    if (w == 16 && ng == 12) return pick<4, 12, 16>(mode, a);
+    if (w == 16 && ng == 16) return pick<4, 16, 16>(mode, a);
     return hipErrorInvalidValue;
   }
   return hipErrorInvalidValue;

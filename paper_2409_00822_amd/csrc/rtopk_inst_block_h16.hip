@@ -3,7 +3,7 @@
 
 namespace rtopk {
 
-// 128-bit loads bring 8 values; 8 loads per lane (W = 4, 8 or 16); few rows with 2 or 4.
+// 128-bit loads bring 8 values; 6 or 8 loads per lane (W = 4, 8 or 16); few rows with 2 or 4.
 template <int G, int NG, int W, int DT>
 static hipError_t pick(int mode, const LaunchArgs& a) {
   if (mode == kExact) return launch_block<G, NG, W, kExact, false, DT>(a);
@@ -18,10 +18,12 @@ static hipError_t pick_shape(int g, int ng, int w, int mode, const LaunchArgs& a
     if (w == 4 && ng == 4) return pick<8, 4, 4, DT>(mode, a);
     if (w == 8 && ng == 2) return pick<8, 2, 8, DT>(mode, a);
     if (w == 8 && ng == 4) return pick<8, 4, 8, DT>(mode, a);
-    if (ng != 8) return hipErrorInvalidValue;
-    if (w == 4) return pick<8, 8, 4, DT>(mode, a);
-    if (w == 8) return pick<8, 8, 8, DT>(mode, a);
-    if (w == 16) return pick<8, 8, 16, DT>(mode, a);
+    if (w == 4 && ng == 6) return pick<8, 6, 4, DT>(mode, a);
+    if (w == 4 && ng == 8) return pick<8, 8, 4, DT>(mode, a);
+    if (w == 8 && ng == 6) return pick<8, 6, 8, DT>(mode, a);
+    if (w == 8 && ng == 8) return pick<8, 8, 8, DT>(mode, a);
+    if (w == 16 && ng == 6) return pick<8, 6, 16, DT>(mode, a);
+    if (w == 16 && ng == 8) return pick<8, 8, 16, DT>(mode, a);
     return hipErrorInvalidValue;
   }
   return hipErrorInvalidValue;

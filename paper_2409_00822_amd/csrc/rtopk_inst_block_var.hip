@@ -3,7 +3,7 @@
 
 namespace rtopk {
 
-// 128-bit loads with 16 loads per lane (W = 4, 8 or 16); few rows with 4 or 8.
+// 128-bit loads with 12 or 16 loads per lane (W = 4, 8 or 16); few rows with 4 or 8.
 template <int G, int NG, int W>
 static hipError_t pick(int mode, bool smallest, const LaunchArgs& a) {
   if (smallest) {
@@ -21,10 +21,12 @@ hipError_t launch_block_variant(int g, int ng, int w, int mode, bool smallest, c
     if (w == 4 && ng == 8) return pick<4, 8, 4>(mode, smallest, a);
     if (w == 8 && ng == 4) return pick<4, 4, 8>(mode, smallest, a);
     if (w == 8 && ng == 8) return pick<4, 8, 8>(mode, smallest, a);
-    if (ng != 16) return hipErrorInvalidValue;
-    if (w == 4) return pick<4, 16, 4>(mode, smallest, a);
-    if (w == 8) return pick<4, 16, 8>(mode, smallest, a);
-    if (w == 16) return pick<4, 16, 16>(mode, smallest, a);
+    if (w == 4 && ng == 12) return pick<4, 12, 4>(mode, smallest, a);
+    if (w == 4 && ng == 16) return pick<4, 16, 4>(mode, smallest, a);
+    if (w == 8 && ng == 12) return pick<4, 12, 8>(mode, smallest, a);
+    if (w == 8 && ng == 16) return pick<4, 16, 8>(mode, smallest, a);
+    if (w == 16 && ng == 12) return pick<4, 12, 16>(mode, smallest, a);
+    if (w == 16 && ng == 16) return pick<4, 16, 16>(mode, smallest, a);
     return hipErrorInvalidValue;
   }
   return hipErrorInvalidValue;

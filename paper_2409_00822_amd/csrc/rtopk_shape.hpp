@@ -85,10 +85,9 @@ inline int pick_ng_h8(int M) {
 // Wavefronts per row of the workgroup-per-row kernel: a lane holds up to 64 values.
 inline int block_waves(int M) { return M <= 16384 ? 4 : (M <= 32768 ? 8 : 16); }
 
-// The layout of a call.  dtype: element type of the rows; plain: fp32 rows, the k largest, Algorithm 2 or exact mode (the
-// variants that have the 12-groups-per-lane workgroup kernels); dense: the dense-output form (fp32).  Requires
-// 1 <= M <= kMaxM (kMaxBlockM for 16-bit rows and the dense form).
-inline Shape kernel_layout(int M, int dtype, bool plain, bool dense) {
+// The layout of a call.  dtype: element type of the rows; plain: fp32 rows, the k largest, Algorithm 2 or exact mode; dense: the
+// dense-output form (fp32) (neither makes a difference).  Requires 1 <= M <= kMaxM (kMaxBlockM for 16-bit rows and the dense form).
+inline Shape kernel_layout(int M, int dtype, bool /*plain*/, bool /*dense*/) {
   Shape s{};
   s.w = 1;
   if (M > kMaxBlockM) {
@@ -102,7 +101,11 @@ inline Shape kernel_layout(int M, int dtype, bool plain, bool dense) {
     s.family = kFamBlock;
     s.w = block_waves(M);
     s.g = dtype == kF32 ? 4 : 8;
-    s.ng = dtype != kF32 ? 8 : ((plain && !dense && M <= 64 * s.w * 4 * 12) ? 12 : 16);
+    // 48 or 64 values per lane: a lane's empty quarter costs as much in every pass over its values as a full one, and registers that another
+    // workgroup of the compute unit could use (64 -> 48 values, us: 2000 x 20000, k = 30 precision 1e-4 40.6 -> 30.5, the k smallest 37.0 -> 28.7,
+    // bfloat16 31.6 -> 23.2, dense 61.8 -> 58.5; 1000 x 9000, k = 100 13.7 -> 12.7, 12.1 -> 11.1, 10.2 -> 9.2, 15.4 -> 13.4; dense 22 x 40504, k = 56
+    // 14.7 -> 12.5; nowhere slower).
+    s.ng = (M <= 64 * s.w * 48 ? 48 : 64) / s.g;
   } else if (M > 512) {
     s.family = dtype == kF32 ? kFamG4 : kFamH16;
     s.g = dtype == kF32 ? 4 : 8;
@@ -260,7 +263,7 @@ constexpr int block_kernels(int E, int w, int mode, bool dense, bool half) {
 }
 
 // True when (g, ng, w) is a layout of its family's lists above.  `plain` and `dense` as above.
-inline bool instantiated(const Shape& s, int dtype, bool plain, bool dense) {
+inline bool instantiated(const Shape& s, int dtype, bool /*plain*/, bool dense) {
   bool small = false, g4 = false, h8 = false;
 #define X(G, NG) small = small || (s.g == G && s.ng == NG);
   RTOPK_LAYOUT_LIST_SMALL(X)
@@ -280,8 +283,8 @@ inline bool instantiated(const Shape& s, int dtype, bool plain, bool dense) {
       return dtype != kF32 && !dense && s.w == 1 && (small || h8 || (s.g == 4 && s.ng == 1));
     case kFamBlock:
       if (s.w != 4 && s.w != 8 && s.w != 16) return false;
-      if (dtype != kF32) return !dense && s.g == 8 && (s.ng == 8 || (s.w <= 8 && (s.ng == 2 || s.ng == 4)));
-      return s.g == 4 && (s.ng == 16 || (s.w <= 8 && (s.ng == 4 || s.ng == 8)) || (s.ng == 12 && plain && !dense));
+      if (dtype != kF32 && dense) return false;
+      return s.g == (dtype == kF32 ? 4 : 8) && (s.values() >= 48 ? s.values() == 48 || s.values() == 64 : s.w <= 8 && (s.values() == 16 || s.values() == 32));
     case kFamStream:
       return dtype == kF32 && !dense && s.w == 16 && s.g == 4;
     default:
