@@ -20,7 +20,9 @@
 //
 // What bounds it: the segments read the row once at the rate of the 32768-column rows (1.15 times the copy rate's time),
 // the lists add 8 bytes per candidate written and read, 1.2 to 1.4 k of them per segment.  The merge is a launch and a chain of
-// latencies, in which few wavefronts share a SIMD and each instruction takes one of them about seven cycles: so its loads are
+// latencies, in which few wavefronts share a SIMD and each instruction takes one of them about seven cycles: so every wavefront finds
+// its registers' lists from the heads by itself (a search for each candidate's list through LDS, behind a barrier, took 1 x 671792, k = 80, 41 lists,
+// 13.7 us in all, 12.0 without; 64 x 131072 13.5 and 13.1), the loads are
 // issued together, the fewest of 4, 8, 16 or 40 registers that hold the row's candidates are walked, and exact mode counts each
 // key into a bin once instead of in 10 to 14 steps of a barrier each (one row of 131072 columns, the merge alone: 7.8 -> 4 us).  Kernel
 // time, one workgroup per row -> split with steps -> with bins: 64 x 131072, k = 50: 39.5 -> 19.2 -> 13.5 us; 1 x 131072: 36.5 -> 12.6 ->
@@ -133,19 +135,44 @@ struct MergeLds {
   float below[NW];  // per wavefront: its largest key in lower bins
 };
 
-// One row's candidates, KR registers of them per lane, `per` in use: the search and the pairs.  Uniform over the workgroup.
-template <int NW, int KR, int MODE, bool NEG, bool RANK>
-__device__ __forceinline__ MergeResult merge_candidates(MergeLds<NW>& s, int64_t r, int M, int k, int max_iter, float eps_rel,
-                                                        float* __restrict__ ov, int32_t* __restrict__ oi,
-                                                        int32_t* __restrict__ out_iters, const uint2* __restrict__ lists,
-                                                        int segments, int cap, int per, int total, float T0, float lo, float hi,
-                                                        RowClasses& rest) {
-  const int tid = threadIdx.x, lane = tid & (kWave - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // 64 consecutive ones to a register: number wave * per * 64 + i * 64 + lane.  All loads are issued together, of 40 registers eight at a time (a lane beyond
-  // the last candidate repeats its load), with 32-bit offsets: a row's lists are less than 2 GiB.
-  float key[KR];
-  uint32_t col[KR];
+// One row's candidates, KR registers of them per lane, `per` in use.  All loads are issued together, of 40 registers eight at a
+// time, with 32-bit offsets: a row's lists are less than 2 GiB.
+//
+// By lists, up to 64 of them: a register holds 64 consecutive candidates of one list, so what it loads is the same for all lanes: lane s
+// knows where list s starts among the registers of the row (`start`), and the list of a register is the number of lanes that start at or
+// before it.  key = NaN (at or above no threshold) behind a list's end.
+template <int NW, int KR, bool NEG>
+__device__ __forceinline__ void load_by_lists(const uint2* __restrict__ lists, int segments, int cap, int start, int n, int per,
+                                              float (&key)[KR], uint32_t (&col)[KR]) {
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  constexpr int kBatch = KR <= 16 ? KR : 8;
+  auto load = [&](auto from) {
+    constexpr int I0 = decltype(from)::value * kBatch;
+    uint2 v[kBatch];
+    int left[kBatch];
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const int u = wave * per + I0 + i;
+      const int seg = max(__builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < segments && start <= u)) - 1, 0);
+      const int first = (u - __builtin_amdgcn_readlane(start, seg)) * kWave;  // beyond the last list's end where there are no more
+      left[i] = I0 + i < per ? __builtin_amdgcn_readlane(n, seg) - first : 0;
+      const uint32_t at = (uint32_t)(seg * cap + (left[i] > 0 ? first + min(lane, left[i] - 1) : 0));
+      v[i] = *reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(lists) + at * 8u);
+    }
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      key[I0 + i] = lane < left[i] ? keyof<NEG>(__uint_as_float(v[i].x)) : __builtin_nanf("");
+      col[I0 + i] = v[i].y;
+    }
+  };
+  static_for<KR / kBatch>(load);
+}
+// By number, 64 consecutive ones of the row to a register: number wave * per * 64 + i * 64 + lane (a lane beyond the last candidate
+// repeats its load); s.first: candidates in earlier lists.
+template <int NW, int KR, bool NEG>
+__device__ __forceinline__ void load_by_number(const MergeLds<NW>& s, const uint2* __restrict__ lists, int segments, int cap, int per,
+                                               int total, float (&key)[KR], uint32_t (&col)[KR]) {
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   constexpr int kBatch = KR <= 16 ? KR : 8;  // (more of them would not fit beside the 40 registers of the largest)
   const int top = segments > 1 ? 1 << (31 - __builtin_clz(segments - 1)) : 0;
   auto load = [&](auto from) {
@@ -177,13 +204,26 @@ __device__ __forceinline__ MergeResult merge_candidates(MergeLds<NW>& s, int64_t
     }
   };
   static_for<KR / kBatch>(load);
+}
+
+// The search and the pairs from the candidates in registers (in column order: by wavefront, register and lane).  Bins and members
+// are cleared and a barrier has passed.  Uniform over the workgroup.
+template <int NW, int KR, int MODE, bool NEG, bool RANK>
+__device__ __forceinline__ MergeResult merge_candidates(MergeLds<NW>& s, int64_t r, int M, int k, int max_iter, float eps_rel,
+                                                        float* __restrict__ ov, int32_t* __restrict__ oi,
+                                                        int32_t* __restrict__ out_iters, float (&key)[KR], uint32_t (&col)[KR],
+                                                        int per, float T0, float lo, float hi, RowClasses& rest) {
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // RANK: the k-th key by bins (see kth_by_bins): every wavefront bins its own, then all find the same bin and rank its members.
   // Exact mode takes the keys above it and the first of those equal to it; the other modes' steps are decided by it and
   // the next one (steps_by_rank).
   bool ranked = false;
   float kth = 0.0f, next = 0.0f;
   const float eps = MODE == kEps ? eps_rel * __builtin_fabsf(hi) : 0.0f;
-  if constexpr (RANK) {
+  // (not where the steps hardly reach the floor, as from a mask's -1e9: 1 x 65860, k = 76, 16 steps 12.5 us, ranked first 13.4)
+  const float last_width = MODE == kEarly ? __builtin_ldexpf(hi - lo, -max_iter) : eps;
+  if (RANK && (MODE == kExact || last_width * 16.0f < hi - T0)) {  // uniform
     const float scale = bins_scale(T0, hi);
 #pragma unroll
     for (int i = 0; i < KR; ++i) {
@@ -365,66 +405,100 @@ template <int NW, int MODE, bool NEG, bool RANK>
 __device__ __forceinline__ bool merge_row(MergeLds<NW>& s, int64_t r, const float* __restrict__ in, int M, int k, int max_iter,
                                           float eps_rel, float* __restrict__ out_vals, int32_t* __restrict__ out_idx,
                                           int32_t* __restrict__ out_iters, const SegmentHead* __restrict__ heads,
-                                          const uint2* __restrict__ lists, int segments, int cap) {
+                                          const uint2* __restrict__ lists, int segments, int cap, int by_lists) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-
-  // The segments' heads, by one wavefront, while the last clears the bins.
   if (RANK && wave == NW - 1) {
     clear_bins(s.bins, lane);
     if (lane == 0) s.members = 0;
   }
-  if (wave == 0) {
-    float fl = -__builtin_inff(), nlo = -__builtin_inff(), hi = -__builtin_inff();
-    int before = 0;
-    for (int s0 = 0; s0 < segments; s0 += kWave) {
-      const bool live = s0 + lane < segments;
-      const SegmentHead h = heads[r * segments + (live ? s0 + lane : 0)];
-      const int n = live ? h.n : 0;
-      const uint32_t incl = wave_inclusive_scan_dpp((uint32_t)n);
-      if (live) s.first[s0 + lane] = before + (int)incl - n;
-      before += __builtin_amdgcn_readlane((int)incl, kWave - 1);
-      fl = vmax(fl, h.floor);  // (a lane beyond the last segment repeats the first)
-      nlo = vmax(nlo, h.nlo);
-      hi = vmax(hi, h.hi);
-    }
-    float a, b, c, unused;
-    wave_max_and_negmin(fl, nlo, a, b);
-    wave_max_and_negmin(hi, hi, c, unused);
-    if (lane == 0) {
-      s.first[segments] = before;
-      s.total = before;
-      s.bound[0] = a;
-      s.bound[1] = b;
-      s.bound[2] = c;
-    }
-  }
-  __syncthreads();
-  const int total = __builtin_amdgcn_readfirstlane(s.total);
-  const float T0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[0])));
-  const float lo = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[1])));
-  const float hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[2])));
-  if (total <= k || total > NW * kWave * (NW == 16 ? kMergeRegsBig : kMergeRegs)) return false;
-
   float* ov = out_vals + r * (int64_t)k;
   int32_t* oi = out_idx + r * (int64_t)k;
-  const int per = (total + NW * kWave - 1) / (NW * kWave);
   const uint2* of_row = lists + r * segments * cap;
   RowClasses rest;
-  auto candidates = [&](auto regs) -> MergeResult {
-    constexpr int KR = decltype(regs)::value;
-    return merge_candidates<NW, KR, MODE, NEG, RANK>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters, of_row, segments, cap, per, total, T0,
-                                               lo, hi, rest);
-  };
   MergeResult done;
-  if (per <= 4) {  // (as few registers as serve: a wavefront issues an instruction in seven cycles, and few share a SIMD here)
-    done = candidates(std::integral_constant<int, 4>());
-  } else if (per <= 8) {
-    done = candidates(std::integral_constant<int, 8>());
-  } else if (NW < 16 || per <= kMergeRegs) {
-    done = candidates(std::integral_constant<int, kMergeRegs>());
-  } else {
-    done = candidates(std::integral_constant<int, NW == 16 ? kMergeRegsBig : kMergeRegs>());
+  bool by_number = !by_lists;
+  if (!by_number) {  // uniform
+    // every wavefront reads the heads, lane s that of segment s: nothing to exchange before the bins
+    const SegmentHead h = heads[r * segments + min(lane, segments - 1)];
+    const int n = lane < segments ? h.n : 0, regs = (n + kWave - 1) / kWave;
+    const uint32_t upto = wave_inclusive_scan_dpp((uint32_t)regs);
+    const int start = (int)upto - regs, all = __builtin_amdgcn_readlane((int)upto, kWave - 1);
+    float T0, lo, hi, unused;
+    wave_max_and_negmin(h.floor, h.nlo, T0, lo);  // (a lane beyond the last segment repeats it)
+    wave_max_and_negmin(h.hi, h.hi, hi, unused);
+    const int per = (all + NW - 1) / NW;
+    auto listed = [&](auto regs_of) -> MergeResult {
+      constexpr int KR = decltype(regs_of)::value;
+      float key[KR];
+      uint32_t col[KR];
+      load_by_lists<NW, KR, NEG>(of_row, segments, cap, start, n, per, key, col);
+      __syncthreads();
+      return merge_candidates<NW, KR, MODE, NEG, RANK>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters, key, col, per, T0, lo, hi, rest);
+    };
+    by_number = per > (NW == 16 ? kMergeRegsBig : kMergeRegs);  // (many short lists: half a register of each may be empty)
+    if (by_number) {
+    } else if (per <= 4) {  // (as few registers as serve: a wavefront issues an instruction in seven cycles, and few share a SIMD here)
+      done = listed(std::integral_constant<int, 4>());
+    } else if (per <= 8) {
+      done = listed(std::integral_constant<int, 8>());
+    } else if (NW < 16 && per <= 12) {
+      done = listed(std::integral_constant<int, NW < 16 ? 12 : 8>());
+    } else if (NW < 16 || per <= kMergeRegs) {
+      done = listed(std::integral_constant<int, kMergeRegs>());
+    } else {
+      done = listed(std::integral_constant<int, NW == 16 ? kMergeRegsBig : kMergeRegs>());
+    }
+  }
+  if (by_number) {  // uniform
+    if (wave == 0) {
+      float fl = -__builtin_inff(), nlo = -__builtin_inff(), hi = -__builtin_inff();
+      int before = 0;
+      for (int s0 = 0; s0 < segments; s0 += kWave) {
+        const bool live = s0 + lane < segments;
+        const SegmentHead h = heads[r * segments + (live ? s0 + lane : 0)];
+        const int n = live ? h.n : 0;
+        const uint32_t incl = wave_inclusive_scan_dpp((uint32_t)n);
+        if (live) s.first[s0 + lane] = before + (int)incl - n;
+        before += __builtin_amdgcn_readlane((int)incl, kWave - 1);
+        fl = vmax(fl, h.floor);  // (a lane beyond the last segment repeats the first)
+        nlo = vmax(nlo, h.nlo);
+        hi = vmax(hi, h.hi);
+      }
+      float a, b, c, unused;
+      wave_max_and_negmin(fl, nlo, a, b);
+      wave_max_and_negmin(hi, hi, c, unused);
+      if (lane == 0) {
+        s.first[segments] = before;
+        s.total = before;
+        s.bound[0] = a;
+        s.bound[1] = b;
+        s.bound[2] = c;
+      }
+    }
+    __syncthreads();
+    const int total = __builtin_amdgcn_readfirstlane(s.total);
+    const float T0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[0])));
+    const float lo = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[1])));
+    const float hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[2])));
+    if (total <= k || total > NW * kWave * (NW == 16 ? kMergeRegsBig : kMergeRegs)) return false;
+    const int per = (total + NW * kWave - 1) / (NW * kWave);
+    auto numbered = [&](auto regs_of) -> MergeResult {
+      constexpr int KR = decltype(regs_of)::value;
+      float key[KR];
+      uint32_t col[KR];
+      load_by_number<NW, KR, NEG>(s, of_row, segments, cap, per, total, key, col);
+      return merge_candidates<NW, KR, MODE, NEG, RANK>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters, key, col, per, T0, lo, hi, rest);
+    };
+    if (NW < 16 && per <= 4) {
+      done = numbered(std::integral_constant<int, NW < 16 ? 4 : kMergeRegs>());
+    } else if (NW < 16 && per <= 8) {
+      done = numbered(std::integral_constant<int, NW < 16 ? 8 : kMergeRegs>());
+    } else if (NW < 16 || per <= kMergeRegs) {
+      done = numbered(std::integral_constant<int, kMergeRegs>());
+    } else {
+      done = numbered(std::integral_constant<int, NW == 16 ? kMergeRegsBig : kMergeRegs>());
+    }
   }
   if (MODE != kExact && done == kMergeFromRow)  // (latency bound: a barrier per chunk; 16 wavefronts have the registers for four loads each)
     write_by_chunks<NW, 4, NEG, NW == 16 ? 4 : 2>(in + r * (int64_t)M, M, k, rest.tA, rest.tB, rest.limA, rest.limB, ov, oi);
@@ -435,13 +509,15 @@ template <int NW, int MODE, bool NEG, bool RANK>
 __global__ void __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(4)))
     rtopk_merge_kernel(const float* __restrict__ in, int M, int k, int max_iter, float eps_rel,
                        float* __restrict__ out_vals, int32_t* __restrict__ out_idx, int32_t* __restrict__ out_iters,
-                       const SegmentHead* __restrict__ heads, const uint2* __restrict__ lists, int segments, int cap) {
+                       const SegmentHead* __restrict__ heads, const uint2* __restrict__ lists, int segments, int cap,
+                       int by_lists) {
   const int64_t r = blockIdx.x;
   __shared__ union {
     MergeLds<NW> merge;
     StreamLds<NW> stream;
   } s;
-  if (merge_row<NW, MODE, NEG, RANK>(s.merge, r, in, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, heads, lists, segments, cap)) return;
+  if (merge_row<NW, MODE, NEG, RANK>(s.merge, r, in, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters, heads, lists, segments, cap,
+                                        by_lists)) return;
   __syncthreads();
   stream_row<NW, 4, MODE, NEG>(s.stream, r, in, M, k, max_iter, eps_rel, out_vals, out_idx, out_iters);
 }
@@ -453,15 +529,18 @@ __global__ void __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu
 inline bool ranks(const Split& s, int mode, const LaunchArgs& a) {
   return mode == kExact || (!s.big && (mode == kEarly ? a.max_iter >= 12 : a.eps_rel < 0x1p-10f));
 }
+// Lists of less than half a register each are better numbered through (four wavefronts' floors leave 26 candidates at k = 8, 38 at 17; 2 x
+// 655360, k = 8, 40 lists: by number 10.6 us, by lists 12.2; 2 x 983040, k = 17, 60 lists 11.8 and 10.9).
 template <int MODE, bool NEG, bool RANK>
 hipError_t launch_merge(const Split& s, int64_t rows, const SegmentHead* heads, const uint2* lists, const LaunchArgs& a, int64_t r0) {
+  const bool by_lists = s.segments <= kWave && (s.w > 4 || a.k >= 16 || s.segments <= 8);
   const auto merge = s.merge_waves == 4   ? &rtopk_merge_kernel<4, MODE, NEG, RANK>
                      : s.merge_waves == 8 ? &rtopk_merge_kernel<8, MODE, NEG, RANK>
                                           : &rtopk_merge_kernel<16, MODE, NEG, RANK>;
   return launch_kernel(merge, dim3((unsigned)rows), dim3(s.merge_waves * kWave), 0, a.stream, static_cast<const float*>(a.in) + r0 * a.M,
                        a.M, a.k, a.max_iter, a.eps_rel, static_cast<float*>(a.out_vals) + r0 * a.k,
                        static_cast<int32_t*>(a.out_idx) + r0 * a.k, a.out_iters ? a.out_iters + r0 : nullptr, heads, lists, s.segments,
-                       s.cap);
+                       s.cap, by_lists ? 1 : 0);
 }
 
 template <int MODE, bool NEG>

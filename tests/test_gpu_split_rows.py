@@ -137,3 +137,20 @@ def test_few_very_wide_rows_are_split_into_the_longer_segments():
     xd = torch.from_numpy(x).cuda()
     _same(R.rtopk_rowwise_exact(xd, 200), oracle.topk_exact(x, 200), "exact")
     _same(R.rtopk_rowwise(xd, 200, 9), oracle.topk_earlystop(x, 200, 9), "early")
+
+
+@pytest.mark.parametrize("M, k", [(60 * 16384, 17), (64 * 16384, 10), (65 * 16384 + 5, 9), (50 * 16384, 40)])
+def test_many_short_lists(M, k):
+    # a register of the merge holds candidates of one list: lists of a few more than 64 take two, more in all than four
+    # wavefronts have, and rows of more than 64 lists are numbered through
+    R = _gpu()
+    g = np.random.default_rng(M + k)
+    x = g.standard_normal((3, M)).astype(np.float32)
+    x[1] = np.round(x[1] * 64) / 64
+    xd = torch.from_numpy(x).cuda()
+    _same(R.rtopk_rowwise_exact(xd, k), oracle.topk_exact(x, k), f"M={M} k={k}")
+    _same(R.rtopk_rowwise(xd, k, 14), oracle.topk_earlystop(x, k, 14), f"M={M} k={k} early")
+    ev, ei, et = oracle.alg1(x, k, eps_rel=1e-4)
+    got = R.rtopk_rowwise_eps(xd, k, 1e-4, want_iters=True)
+    _same(got, (ev, ei), f"M={M} k={k} eps")
+    assert np.array_equal(got[2].cpu().numpy(), et)
