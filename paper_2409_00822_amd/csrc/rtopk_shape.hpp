@@ -334,11 +334,15 @@ inline Split split_of(int64_t N, int M, int k, int mode, int max_iter) {
   int root = 1;
   while (root * root < k) ++root;
   const int usual = k + k / 3 + 10 * root + 24, expected = k + k / 3 + 6 * root + 16;
-  // Segments of 32768 columns, unless those would not give every compute unit two workgroups (and those of 16384, which
-  // have twice the candidates in all, still fit the merge).
+  // Segments of 32768 columns, unless those would not give every compute unit two workgroups and those of 16384, which have
+  // twice the candidates in all, still fit the merge; or, where these fit a merge of four wavefronts, four workgroups (eight with few
+  // segments to a row): more of the smaller workgroups share a compute unit, and the last round of them is shorter (us, 32768 -> 16384
+  // columns: 129 x 164776, k = 55 24.2 -> 21.6; 93 x 281245, k = 16 25.3 -> 23.8; 300 x 108960, k = 29 29.6 -> 27.6; 946 x 63250 46.5 -> 43.6; but
+  // 85 x 457696, k = 12, 28 segments 33.4 -> 34.1, 16 x 2^20, k = 100 22.7 -> 27.2).
   s.w = 8;
-  if (k <= filter_max_k(4) && N * ((M + 32767) / 32768) < 2 * 256 &&
-      (int64_t)((M + 16383) / 16384) * expected <= kMergeMost)
+  const int64_t wide = N * ((M + 32767) / 32768), narrow = (M + 16383) / 16384;
+  if (k <= filter_max_k(4) && (wide < 2 * 256 ? narrow * expected <= kMergeMost
+                                              : wide < (narrow <= 8 ? 8 : 4) * 256 && narrow * usual <= 4 * 64 * kMergeRegs))
     s.w = 4;
   const int most = s.w * 4096;
   s.segments = (M + most - 1) / most;
