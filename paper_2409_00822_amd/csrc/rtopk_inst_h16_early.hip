@@ -13,7 +13,7 @@ static hipError_t pick_rows(bool full, const LaunchArgs& a) {
 
 template <int DT, int G, int NG>
 static hipError_t pick(bool full, const LaunchArgs& a) {
-  constexpr int E = Layout<G, NG>::E, R = rows_per_wave(E);
+  constexpr int E = Layout<G, NG>::E, R = most_rows(E, kPairs, true);
   if constexpr (E == 16) {
     if (one_row_lists(kEarly, true, a)) return pick_rows<DT, G, NG, 1>(full, a);
   }

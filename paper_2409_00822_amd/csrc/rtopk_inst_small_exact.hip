@@ -23,12 +23,12 @@ static hipError_t pick_rows(bool full, bool u8, const LaunchArgs& a) {
 
 template <int G, int NG>
 static hipError_t pick(bool full, bool u8, const LaunchArgs& a) {
-  constexpr int E = Layout<G, NG>::E, R = rows_per_wave(E);
+  constexpr int E = Layout<G, NG>::E, R = most_rows(E, kPairs);
   auto rows = [&](auto r) { return pick_rows<G, NG, decltype(r)::value>(full, u8, a); };
   if constexpr (E <= 3) {
     if (u8) return by_rows<E, R, kBytes>(a.N, rows);
   }
-  return by_rows<E, E == 3 ? kRowsPerWaveFp32M256 : R, kPairs>(a.N, rows);
+  return by_rows<E, E == 3 ? kRowsPerWaveFp32M256 : R, kPairs>(a.N, rows, few_rows_of<E, kPairs>(a));
 }
 
 hipError_t launch_small_exact(int g, int ng, bool full, bool u8, const LaunchArgs& a) {

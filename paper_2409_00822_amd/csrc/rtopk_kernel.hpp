@@ -1550,7 +1550,7 @@ struct FewRows {
   int64_t one, two, four;
 };
 enum RowForm : int { kPairs = 0, kBytes = 1, kPairsEps = 2 };  // int32 columns, byte-wide columns, Algorithm 1 with precision
-constexpr FewRows few_rows(int E, RowForm form) {  // (five and more values per lane: two rows at most, so `one` alone counts)
+constexpr FewRows few_rows(int E, RowForm form) {  // (five and more values per lane: many_rows says where two end)
   if (form == kPairsEps) {
     if (E == 1) return {4096, 32768, 196608};
     if (E <= 3) return {8192, 32768, 393216};
@@ -1560,6 +1560,28 @@ constexpr FewRows few_rows(int E, RowForm form) {  // (five and more values per 
   if (E <= 3) return {form == kBytes ? 0 : 4096, 24576, E == 2 ? 196608 : 147456};
   if (E == 4) return {form == kBytes ? 4096 : 8192, 49152, 147456};
   return {E <= 6 ? 8192 : (E <= 8 ? 12288 : 32768), 0, 0};
+}
+// Many rows of 257 to 512 columns: four per wavefront instead of two.  A wavefront pays for its columns' validity, the reduction of its rows' bounds
+// and its output's two ends once for all its rows, and has twice the loads in flight (us, two -> four: 100003 x 333, k = 33 35.1 -> 32.0; 600001 x 333
+// 188 -> 166, x 257, k = 26 175 -> 139, x 300, k = 32 157 -> 140, eight steps 163 -> 146; precision 1e-4 400000 x 333, k = 41 140 -> 124, x 512, k = 64
+// 173 -> 164; bfloat16 400000 x 333, k = 41 130 -> 114, x 512, k = 64 152 -> 142; eight to a wavefront: 25000 rows -20 %, 400000 -8 to +4 %).  Few
+// rows then leave SIMDs idle: at 25000 and 40000 rows -12 to 0 %, 50000 -3 to +3, 70000 +1 to +7.  Where copying bounds it, fewer rows in flight
+// stream better: fp32 rows wider than 416 columns but for a precision (512 columns, k = 64 158 -> 176, 448 144 -> 153), k above a sixth of the row
+// (280000 x 400, k = 133 -6 %), a tenth with up to five steps (280000 x 333, k = 47 -4 %); 16-bit rows until the outputs staged in LDS
+// leave room for fewer wavefronts (512 columns, k = 170 -7 to 0 %, 400 columns, k = 133 +10).
+constexpr bool many_rows_form(int E, RowForm form, bool half) { return E >= 5 && E <= (half || form == kPairsEps ? 8 : 7); }
+constexpr int most_rows(int E, RowForm form, bool half = false) { return many_rows_form(E, form, half) ? 4 : rows_per_wave(E); }
+template <int E, RowForm FORM, bool HALF = false>
+inline FewRows many_rows(FewRows few, int most_of_row, const LaunchArgs& a) {
+  if constexpr (many_rows_form(E, FORM, HALF)) {
+    const bool holds = HALF ? a.k <= 128 : most_of_row * a.k <= a.M && (FORM == kPairsEps || a.M <= 416);
+    few.two = holds ? 61440 : INT64_MAX;
+  }
+  return few;
+}
+template <int E, RowForm FORM, bool HALF = false>
+inline FewRows few_rows_of(const LaunchArgs& a) {
+  return many_rows<E, FORM, HALF>(few_rows(E, FORM), 6, a);
 }
 // Algorithm 2 with up to five steps leaves a wavefront less to do per row, and what it does once -- the validity of its columns,
 // widening -- weighs more: of ragged or 16-bit rows with int32 columns, one per wavefront pays up to half as many, four instead of sixteen up to three
@@ -1576,7 +1598,7 @@ inline FewRows few_rows_early(bool full, const LaunchArgs& a) {
     if (HALF || (!full && FORM == kPairs)) few.one /= 2;
     if (E == 1 ? a.max_iter <= 4 : E <= 3 && (HALF || !full)) few.four -= few.four / 4;
   }
-  return few;
+  return many_rows<E, FORM, HALF>(few, a.max_iter <= 5 ? 10 : 6, a);
 }
 // f(integral_constant<int, rows per wavefront>) for N rows; FULL: the layout's own number.
 template <int E, int FULL, RowForm FORM, typename F>
