@@ -26,7 +26,7 @@ static hipError_t pick(bool full, bool u8, const LaunchArgs& a) {
   if constexpr (NG == 1) {
     const FewRows few = few_rows_early<4, kBytes>(full, a);
     if (u8) return full ? by_rows<4, kRowsPerWaveFp32M256, kBytes>(a.N, rows, few) : by_rows<4, R, kBytes>(a.N, rows, few);
-    return by_rows<4, kRowsPerWaveFp32M256, kPairs>(a.N, rows, few_rows_early<4, kPairs>(full, a));
+    return by_rows<4, R, kPairs>(a.N, rows, few_rows_early<4, kPairs>(full, a));
   }
   return by_rows<4 * NG, R, kPairs>(a.N, rows, few_rows_early<4 * NG, kPairs>(full, a));
 }

@@ -5,7 +5,7 @@ namespace rtopk {
 
 template <int NG>
 static hipError_t pick(bool full, const LaunchArgs& a) {
-  constexpr int R = NG == 1 ? kRowsPerWaveFp32M256 : most_rows(4 * NG, kPairsEps);
+  constexpr int R = most_rows(4 * NG, kPairsEps);
   return by_rows<4 * NG, R, kPairsEps>(a.N, [&](auto r) {
     constexpr int rows = decltype(r)::value;
     return full ? launch<4, NG, rows, true, kEps, int32_t>(a) : launch<4, NG, rows, false, kEps, int32_t>(a);

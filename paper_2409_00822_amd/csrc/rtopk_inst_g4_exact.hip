@@ -25,7 +25,7 @@ static hipError_t pick(bool full, bool u8, const LaunchArgs& a) {
   auto rows = [&](auto r) { return pick_rows<NG, decltype(r)::value>(full, u8, a); };
   if constexpr (NG == 1) {
     if (u8) return full ? by_rows<4, kRowsPerWaveFp32M256, kBytes>(a.N, rows) : by_rows<4, R, kBytes>(a.N, rows);
-    return by_rows<4, kRowsPerWaveFp32M256, kPairs>(a.N, rows);
+    return by_rows<4, R, kPairs>(a.N, rows, few_rows_of<4, kPairs>(a));
   }
   return by_rows<4 * NG, R, kPairs>(a.N, rows);
 }

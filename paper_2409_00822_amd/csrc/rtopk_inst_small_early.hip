@@ -28,7 +28,7 @@ static hipError_t pick(bool full, bool u8, const LaunchArgs& a) {
   if constexpr (E <= 3) {
     if (u8) return by_rows<E, R, kBytes>(a.N, rows, few_rows_early<E, kBytes>(full, a));
   }
-  return by_rows<E, E == 3 ? kRowsPerWaveFp32M256 : R, kPairs>(a.N, rows, few_rows_early<E, kPairs>(full, a));
+  return by_rows<E, R, kPairs>(a.N, rows, few_rows_early<E, kPairs>(full, a));
 }
 
 hipError_t launch_small_early(int g, int ng, bool full, bool u8, const LaunchArgs& a) {

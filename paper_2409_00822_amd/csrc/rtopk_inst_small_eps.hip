@@ -13,7 +13,7 @@ static hipError_t pick_rows(bool full, const LaunchArgs& a) {
 
 template <int G, int NG>
 static hipError_t pick(bool full, const LaunchArgs& a) {
-  constexpr int E = Layout<G, NG>::E, R = E == 3 ? kRowsPerWaveFp32M256 : most_rows(E, kPairsEps);
+  constexpr int E = Layout<G, NG>::E, R = most_rows(E, kPairsEps);
   return by_rows<E, R, kPairsEps>(a.N, [&](auto r) { return pick_rows<G, NG, decltype(r)::value>(full, a); },
                                few_rows_of<E, kPairsEps>(a));
 }

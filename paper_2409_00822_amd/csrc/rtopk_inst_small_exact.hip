@@ -28,7 +28,7 @@ static hipError_t pick(bool full, bool u8, const LaunchArgs& a) {
   if constexpr (E <= 3) {
     if (u8) return by_rows<E, R, kBytes>(a.N, rows);
   }
-  return by_rows<E, E == 3 ? kRowsPerWaveFp32M256 : R, kPairs>(a.N, rows, few_rows_of<E, kPairs>(a));
+  return by_rows<E, R, kPairs>(a.N, rows, few_rows_of<E, kPairs>(a));
 }
 
 hipError_t launch_small_exact(int g, int ng, bool full, bool u8, const LaunchArgs& a) {

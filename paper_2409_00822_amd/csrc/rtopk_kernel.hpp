@@ -1521,7 +1521,7 @@ inline bool one_row_lists(int mode, bool half, const LaunchArgs& a) {
   if (mode == kExact) return a.k <= (half ? min(wave_filter_max_k(16, 1, mode), 35 * a.M / 256) : 64);
   return a.k <= (half ? min(64, 24 * a.M / 256) : 64) && a.max_iter >= (half ? 7 : (a.M >= 896 ? 5 : 6));
 }
-// fp32 rows of 129..256 columns with int32 columns (and their dense form) take 4 instead: with
+// fp32 rows of 129..256 columns with int32 columns take 4 instead, unless there are many narrower than 240 (many_rows): with
 // non-temporal output stores the smaller per-wavefront footprint streams better (2^20 x 256: k = 32
 // 221 -> 215 us, k = 64 254 -> 247 us, k = 128 356 -> 345 us, dense 346 -> 339 us; with no search steps at
 // all, 2 rows per wavefront reach 200 us but the search then costs 47 us more).  The variants that are
@@ -1554,7 +1554,7 @@ constexpr FewRows few_rows(int E, RowForm form) {  // (five and more values per 
   if (form == kPairsEps) {
     if (E == 1) return {4096, 32768, 196608};
     if (E <= 3) return {8192, 32768, 393216};
-    return {E <= 7 ? 16384 : 40960, E == 4 ? 49152 : 0, 0};
+    return {E <= 7 ? 16384 : 40960, E == 4 ? 49152 : 0, E == 4 ? 262144 : 0};
   }
   if (E == 1) return {0, 16384, 98304};
   if (E <= 3) return {form == kBytes ? 0 : 4096, 24576, E == 2 ? 196608 : 147456};
@@ -1569,6 +1569,9 @@ constexpr FewRows few_rows(int E, RowForm form) {  // (five and more values per 
 // stream better: fp32 rows wider than 416 columns but for a precision (512 columns, k = 64 158 -> 176, 448 144 -> 153), k above a sixth of the row
 // (280000 x 400, k = 133 -6 %), a tenth with up to five steps (280000 x 333, k = 47 -4 %); 16-bit rows until the outputs staged in LDS
 // leave room for fewer wavefronts (512 columns, k = 170 -7 to 0 %, 400 columns, k = 133 +10).
+// fp32 rows of 129 to 240 columns (256 for a precision) take eight instead of four for the same reasons (us, four -> eight: 10^6 x 130, k = 16 148 ->
+// 133, x 200, k = 25 190 -> 175, x 150, eight steps 171 -> 154, x 224, 1e-4 217 -> 203; 200000 x 160 34.0 -> 32.9; but 10^6 x 256, k = 32 -9 %, 251 -2,
+// 10^6 x 192, k = 64 -4, 160000 x 224 -4 to +1; 16-bit rows, which have eight, with sixteen -15 %).
 constexpr bool many_rows_form(int E, RowForm form, bool half) { return E >= 5 && E <= (half || form == kPairsEps ? 8 : 7); }
 constexpr int most_rows(int E, RowForm form, bool half = false) { return many_rows_form(E, form, half) ? 4 : rows_per_wave(E); }
 template <int E, RowForm FORM, bool HALF = false>
@@ -1576,6 +1579,9 @@ inline FewRows many_rows(FewRows few, int most_of_row, const LaunchArgs& a) {
   if constexpr (many_rows_form(E, FORM, HALF)) {
     const bool holds = HALF ? a.k <= 128 : most_of_row * a.k <= a.M && (FORM == kPairsEps || a.M <= 416);
     few.two = holds ? 61440 : INT64_MAX;
+  } else if constexpr ((E == 3 || E == 4) && FORM != kBytes && !HALF) {
+    const bool holds = most_of_row * a.k <= a.M && (FORM == kPairsEps || a.M <= 240);
+    few.four = holds ? (FORM == kPairsEps ? 262144 : 196608) : INT64_MAX;
   }
   return few;
 }
