@@ -117,10 +117,9 @@ int run_backward(bool gather, const float* dense, const float* pairs, const void
   if (rtopk::ranges_overlap(addr(dense), n_d, addr(pairs), n_p) || rtopk::ranges_overlap(addr(dense), n_d, addr(idx), n_i) ||
       (gather && rtopk::ranges_overlap(addr(pairs), n_p, addr(idx), n_i)))
     return RTOPK_ERR_OVERLAP;
-  const bool vec = M % 4 == 0 && aligned(dense, 16);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const hipError_t err = gather ? rtopk::launch_maxk_backward_gather(dense, idx, u8, N, M, k, const_cast<float*>(pairs), vec, s)
-                                : rtopk::launch_maxk_backward(pairs, idx, u8, N, M, k, const_cast<float*>(dense), vec, s);
+  const hipError_t err = gather ? rtopk::launch_maxk_backward_gather(dense, idx, u8, N, M, k, const_cast<float*>(pairs), s)
+                                : rtopk::launch_maxk_backward(pairs, idx, u8, N, M, k, const_cast<float*>(dense), s);
   return err == hipSuccess ? RTOPK_OK : RTOPK_ERR_LAUNCH;
 }
 

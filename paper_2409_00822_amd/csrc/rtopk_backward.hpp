@@ -20,98 +20,117 @@
 
 namespace rtopk {
 
-// How the lanes of a wavefront are laid over (row, j) pairs of an [rows][k] array: when k <= 32, 64 >> kshift
-// rows share one instruction (lane = sub_row * 2^kshift + j); otherwise one row at a time, j strided by 64.
-struct PairLanes {
-  int kshift;  // log2 of the lanes given to one row (6 when k > 32)
-};
-inline PairLanes pair_lanes(int k) {
-  int s = 0;
-  while ((1 << s) < k && s < 6) ++s;
-  return PairLanes{s};
+// The rows of a wavefront are contiguous in the dense matrix (`rows` * M floats) and their pairs in the [N][k] arrays, so both kernels
+// walk the pairs as one list, 64 neighbours to an instruction, whatever k is: BATCH instructions' worth in registers, as many as the wavefront has or 16,
+// loaded together, while the rows are cleared or loaded.  All loads are unconditional (lanes past the end repeat the last): behind a
+// branch each would be waited for alone.  What bounds both is HBM, given enough loads in flight.  Measured against 2, 4, 8 or 16 whole rows
+// with the lanes divided among them, dword accesses where M is no multiple of four and a loop over the row for k > 64, us, inputs cold: 1048576
+// x 251, k = 31 scatter 340 -> 213, gather 536 -> 230; x 250, k = 100 685 -> 273, 728 -> 293; x 256, k = 32 210 -> 207, 201 -> 206, k = 128 645 -> 294, 371
+// -> 282; 262144 x 777, k = 40 265 -> 161, 310 -> 154; 131072 x 2048, k = 100 261 -> 222, 190 -> 192 (byte columns up to 256).
+// n / d for n up to 3 * 2048 and d up to 2048, exactly: n * (by - 2^32 / d) < 2^32 / d.  by: ceil(2^32 / d), 0 where that is 2^32.
+__device__ __forceinline__ int quotient(int n, uint32_t by) { return by == 0 ? n : (int)__umulhi((uint32_t)n, by); }
+inline uint32_t divisor(int d) { return 0xffffffffu / (uint32_t)d + 1; }
+
+// An element of a pair.  STREAM: with the non-temporal hint, which keeps what is read once out of the caches' way; not where wavefronts share lines,
+// which are then read again from memory (the scatter with rows that a chunk cuts, inputs cold: 1048576 x 251, k = 31 243 -> 213 us without it, 131072 x
+// 2048, k = 100 250 -> 220; 1048576 x 256, k = 32, where none are shared, 225 without, 219 with).
+template <bool STREAM, typename T>
+__device__ __forceinline__ T load_pair(const T* p) {
+  return STREAM ? __builtin_nontemporal_load(p) : *p;
 }
 
-// ---- scatter, narrow rows: one wavefront per R rows, rows assembled in LDS ------------------------------
+// out[0..n) = image[pad..pad + n), by `threads` threads of which this is number `tid`.  pad: floats that `out` lies behind a 16-byte boundary, so that
+// whole quads of the image leave as aligned 128-bit stores; what precedes and follows them goes one by one.  ALIGNED: pad is 0, n a multiple of four.
+// Floats that p lies behind a boundary of n of them.
+__device__ __host__ __forceinline__ int floats_behind(const float* p, int n) { return (int)((reinterpret_cast<uintptr_t>(p) >> 2) & (n - 1)); }
+template <bool ALIGNED>
+__device__ __forceinline__ void store_image(float* __restrict__ out, const float* image, int n, int pad, int tid, int threads) {
+  const uint4* quads = reinterpret_cast<const uint4*>(image);
+  if constexpr (ALIGNED) {
+    for (int q = tid; q < (n >> 2); q += threads) store_streaming(reinterpret_cast<uint4*>(out) + q, quads[q]);
+  } else {
+    const int q0 = pad != 0 ? 1 : 0, q1 = (pad + n) >> 2;
+    for (int q = q0 + tid; q < q1; q += threads) store_streaming(reinterpret_cast<uint4*>(out - pad + 4 * q), quads[q]);
+    const int head = pad != 0 ? min(4 - pad, n) : 0, tail = max(4 * q1 - pad, head);
+    if (tid < head) out[tid] = image[pad + tid];
+    if (tid < n - tail) out[tail + tid] = image[pad + tail + tid];
+  }
+}
+__device__ __forceinline__ void wavefront_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// ---- scatter, narrow rows: one wavefront per chunk of the output, which is assembled in LDS ---------------
 //
-// The wavefront's R rows are contiguous in grad_in (R * M floats).  They are built in LDS -- zero fill,
-// then one 4-byte LDS write per saved column -- and leave as whole 128-bit stores (VEC) that cover the R
-// rows back to back, so HBM sees each output byte written once, in order.  The LDS queue of a wavefront
-// is served in order, so the three phases need no barrier.
-template <typename IdxT, int R, bool VEC>
-__global__ void __launch_bounds__(256)
-    maxk_scatter_rows_kernel(const float* __restrict__ grad_vals, const IdxT* __restrict__ idx, int64_t N, int M, int k,
-                             int kshift, float* __restrict__ grad_in) {
-  extern __shared__ __attribute__((aligned(16))) float s_rows[];  // [waves per block][R * M]
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int waves_per_block = (int)(blockDim.x >> 6);
-  const int64_t r0 = ((int64_t)blockIdx.x * waves_per_block + wave) * R;
-  if (r0 >= N) return;
-  const int nrows = (N - r0 < R) ? (int)(N - r0) : R;
-  float* rows = s_rows + (size_t)wave * R * M;
-  const int total = nrows * M;
-
-  // the saved columns and their gradients: issued first, consumed after the zero fill
-  const int lanes_per_row = 1 << kshift;
-  const int rows_per_step = kWave >> kshift;
-  const int sub = lane >> kshift, j0 = lane & (lanes_per_row - 1);
-  // (row, j) pairs of step s: rows s * rows_per_step + sub; R steps cover the R rows even at one row a step
-  float g[R];
-  int c[R];
-  const bool one_pass = k <= lanes_per_row;  // every (row, j) of a step has a lane of its own
-  if (one_pass) {
+// Zero fill, one 4-byte LDS write per saved column, then the image leaves back to back: HBM sees each output byte written once, in order. The
+// output is cut at 128-byte boundaries, not between rows: a line that two wavefronts write parts of costs two writes (1048576 x 251, k = 31, whole
+// rows per wavefront 263 us, chunks 233); of the rows that a chunk cuts both sides load the pairs and keep their own.
+template <typename IdxT, int BATCH, bool STREAM>
+__global__ void __launch_bounds__(kWave)
+    maxk_scatter_rows_kernel(const float* __restrict__ grad_vals, const IdxT* __restrict__ idx, int64_t elements, int M, int k, int chunk,
+                             int skew, int whole, uint32_t by, uint32_t by_m, double per_m, float* __restrict__ grad_in) {
+  extern __shared__ __attribute__((aligned(16))) float s_rows[];  // [chunk]
+  const int lane = threadIdx.x;
+  // The chunk's elements are [start, start + chunk) of the matrix as far as it goes; the first chunk starts `skew` before it.
+  const int64_t start = (int64_t)blockIdx.x * chunk - skew;
+  const int from = start < 0 ? skew : 0, to = elements - start < chunk ? (int)(elements - start) : chunk;
+  const int64_t begin = start + from;
+  int64_t r0;
+  if (whole > 0) {  // rows that every chunk holds: none is cut (the arithmetic below comes before the first load: 2 %)
+    r0 = (int64_t)blockIdx.x * whole;
+  } else {
+    r0 = (int64_t)((double)begin * per_m);  // begin / M, or one off
+    const int64_t rem = begin - r0 * M;
+    r0 += rem < 0 ? -1 : (rem >= M ? 1 : 0);
+    r0 = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)((uint64_t)r0 >> 32)) << 32) |
+                   (uint32_t)__builtin_amdgcn_readfirstlane((int)r0));
+  }
+  const int at_row = (int)(r0 * M - start);  // where row r0 starts in the chunk, up to M - 1 before it
+  const int pairs = (quotient(to - 1 - at_row, by_m) + 1) * k;
+  const float* gv = grad_vals + r0 * (int64_t)k;
+  const IdxT* ix = idx + r0 * (int64_t)k;
+  float g[BATCH];
+  int c[BATCH];
+  auto load = [&](int p0) {
 #pragma unroll
-    for (int s = 0; s < R; ++s) {
-      c[s] = -1;
-      g[s] = 0.0f;
-      if (s * rows_per_step < nrows) {  // uniform over the wavefront
-        const int rr = s * rows_per_step + sub;
-        const bool live = rr < nrows && j0 < k;
-        const int64_t e = (r0 + (live ? rr : 0)) * (int64_t)k + (live ? j0 : 0);
-        g[s] = __builtin_nontemporal_load(grad_vals + e);
-        c[s] = live ? (int)__builtin_nontemporal_load(idx + e) : -1;
-      }
+    for (int i = 0; i < BATCH; ++i) {
+      const int at = min(p0 + i * kWave + lane, pairs - 1);
+      g[i] = load_pair<STREAM>(gv + at);
+      c[i] = (int)load_pair<STREAM>(ix + at);
     }
-  }
-
-  if constexpr (VEC) {
-    float4* rows4 = reinterpret_cast<float4*>(rows);
-    for (int q = lane; q < (total >> 2); q += kWave) rows4[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  } else {
-    for (int q = lane; q < total; q += kWave) rows[q] = 0.0f;
-  }
-
-  if (one_pass) {
+  };
+  load(0);
+  for (int q = lane; q < chunk >> 2; q += kWave) reinterpret_cast<float4*>(s_rows)[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  wavefront_lds_order();
+  for (int p0 = 0;;) {
 #pragma unroll
-    for (int s = 0; s < R; ++s) {
-      const int rr = s * rows_per_step + sub;
-      if ((unsigned)c[s] < (unsigned)M) rows[rr * M + c[s]] = g[s];
+    for (int i = 0; i < BATCH; ++i) asm volatile("" : "+v"(g[i]), "+v"(c[i]));  // (or the loads move to their uses)
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      const int p = p0 + i * kWave + lane, at = at_row + quotient(p, by) * M + c[i];
+      if (p < pairs && (unsigned)c[i] < (unsigned)M && (unsigned)at < (unsigned)chunk) s_rows[at] = g[i];
     }
-  } else {
-    for (int rr = 0; rr < nrows; ++rr) {
-      for (int j = lane; j < k; j += kWave) {
-        const int64_t e = (r0 + rr) * (int64_t)k + j;
-        const int col = (int)idx[e];
-        if ((unsigned)col < (unsigned)M) rows[rr * M + col] = grad_vals[e];
-      }
-    }
+    p0 += BATCH * kWave;
+    if (p0 >= pairs) break;
+    load(p0);
   }
-
-  float* out = grad_in + r0 * (int64_t)M;
-  if constexpr (VEC) {
-    const uint4* rows4 = reinterpret_cast<const uint4*>(rows);
+  wavefront_lds_order();
+  float* out = grad_in + start;
+  if (to - from == chunk) {  // uniform
 #pragma unroll 1
-    for (int q = lane; q < (total >> 2); q += kWave) store_streaming(reinterpret_cast<uint4*>(out) + q, rows4[q]);
-  } else {
+    for (int q = lane; q < chunk >> 2; q += kWave) store_streaming(reinterpret_cast<uint4*>(out) + q, reinterpret_cast<const uint4*>(s_rows)[q]);
+  } else {  // the first or the last
 #pragma unroll 1
-    for (int q = lane; q < total; q += kWave) out[q] = rows[q];
+    for (int j = from + lane; j < to; j += kWave) out[j] = s_rows[j];
   }
 }
 
 // ---- scatter, wide rows: one workgroup per row, the row assembled in LDS chunk by chunk -----------------
 constexpr int kScatterChunk = 8192;  // columns per chunk (32 KiB of LDS)
 
-template <typename IdxT, bool VEC>
+template <typename IdxT, bool ALIGNED>
 __global__ void __launch_bounds__(256)
     maxk_scatter_block_kernel(const float* __restrict__ grad_vals, const IdxT* __restrict__ idx, int64_t N, int M, int k,
                               float* __restrict__ grad_in) {
@@ -121,68 +140,87 @@ __global__ void __launch_bounds__(256)
   const float* gv = grad_vals + r * (int64_t)k;
   const IdxT* ix = idx + r * (int64_t)k;
   float* out = grad_in + r * (int64_t)M;
-  for (int c0 = 0; c0 < M; c0 += kScatterChunk) {
-    const int width = M - c0 < kScatterChunk ? M - c0 : kScatterChunk;
-    for (int q = threadIdx.x; q < width; q += blockDim.x) s_chunk[q] = 0.0f;
+  int pad = ALIGNED ? 0 : floats_behind(out, 4);  // the first chunk is that much shorter, so that the others start on a boundary
+  for (int c0 = 0; c0 < M;) {
+    const int width = min(M - c0, kScatterChunk - pad);
+    for (int q = threadIdx.x; q < pad + width; q += blockDim.x) s_chunk[q] = 0.0f;
     __syncthreads();
     for (int j = threadIdx.x; j < k; j += blockDim.x) {
       const int col = (int)ix[j] - c0;
-      if ((unsigned)col < (unsigned)width) s_chunk[col] = gv[j];
+      if ((unsigned)col < (unsigned)width) s_chunk[pad + col] = gv[j];
     }
     __syncthreads();
-    if constexpr (VEC) {  // M % 4 == 0, so every chunk width is a multiple of 4
-      const uint4* c4 = reinterpret_cast<const uint4*>(s_chunk);
-      for (int q = threadIdx.x; q < (width >> 2); q += blockDim.x)
-        store_streaming(reinterpret_cast<uint4*>(out + c0) + q, c4[q]);
-    } else {
-      for (int q = threadIdx.x; q < width; q += blockDim.x) out[c0 + q] = s_chunk[q];
-    }
+    store_image<ALIGNED>(out + c0, s_chunk, width, pad, (int)threadIdx.x, (int)blockDim.x);
     __syncthreads();  // the chunk buffer is zeroed again by the next round
+    c0 += width;
+    pad = 0;
   }
 }
 
 // ---- gather: the dense gradient row is read once, through LDS, with 128-bit loads ------------------------
 //
-// One wavefront per R rows.  The R rows (contiguous: R * M floats) are copied to LDS with whole
-// 128-bit loads, the k saved columns of each row are then read from LDS, and the R * k results -- again
-// contiguous in the output -- are stored coalesced.
-template <typename IdxT, int R, bool VEC>
-__global__ void __launch_bounds__(256)
-    maxk_gather_rows_kernel(const float* __restrict__ grad_out, const IdxT* __restrict__ idx, int64_t N, int M, int k,
-                            int kshift, float* __restrict__ grad_vals) {
-  extern __shared__ __attribute__((aligned(16))) float s_rows[];  // [waves per block][R * M]
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int waves_per_block = (int)(blockDim.x >> 6);
-  const int64_t r0 = ((int64_t)blockIdx.x * waves_per_block + wave) * R;
+// One wavefront per `rows` rows, at most kBackwardRowsM floats in all: 128-bit loads (from any 4-byte boundary, see load_group), four per lane at a
+// time (eight: 2^20 x 256, k = 32 225 -> 219 us, 2^18 x 512 111.5 -> 109.2), then the saved columns' entries are read from LDS, and the results, again
+// contiguous in the output, are stored coalesced.
+template <typename IdxT, int BATCH>
+__global__ void __launch_bounds__(kWave)
+    maxk_gather_rows_kernel(const float* __restrict__ grad_out, const IdxT* __restrict__ idx, int64_t N, int M, int k, int rows,
+                            uint32_t by, float* __restrict__ grad_vals) {
+  extern __shared__ __attribute__((aligned(16))) float s_rows[];  // [rows * M], in whole quads
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
+  const int lane = threadIdx.x;
+  const int64_t r0 = (int64_t)blockIdx.x * rows;
   if (r0 >= N) return;
-  const int nrows = (N - r0 < R) ? (int)(N - r0) : R;
-  float* rows = s_rows + (size_t)wave * R * M;
-  const int total = nrows * M;
+  const int nrows = rows_left(N - r0, rows), total = nrows * M, pairs = nrows * k, quads = total >> 2;
   const float* src = grad_out + r0 * (int64_t)M;
-
-  if constexpr (VEC) {
-    typedef float f4 __attribute__((ext_vector_type(4)));
-    const f4* src4 = reinterpret_cast<const f4*>(src);
-    f4* rows4 = reinterpret_cast<f4*>(rows);
-#pragma unroll 4
-    for (int q = lane; q < (total >> 2); q += kWave) rows4[q] = __builtin_nontemporal_load(src4 + q);
-  } else {
-    for (int q = lane; q < total; q += kWave) rows[q] = __builtin_nontemporal_load(src + q);
-  }
-
-  const int lanes_per_row = 1 << kshift;
-  const int rows_per_step = kWave >> kshift;
-  const int sub = lane >> kshift, j0 = lane & (lanes_per_row - 1);
-  for (int rr0 = 0; rr0 < nrows; rr0 += rows_per_step) {
-    const int rr = rr0 + sub;
-    if (rr < nrows) {
-      for (int j = j0; j < k; j += lanes_per_row) {
-        const int64_t e = (r0 + rr) * (int64_t)k + j;
-        const int col = (int)__builtin_nontemporal_load(idx + e);
-        grad_vals[e] = (unsigned)col < (unsigned)M ? rows[rr * M + col] : 0.0f;
+  const IdxT* ix = idx + r0 * (int64_t)k;
+  float* to = grad_vals + r0 * (int64_t)k;
+  constexpr int kQuads = kBackwardRowsM / 4 / kWave;
+  int c[BATCH];
+  auto load = [&](int p0) {
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) c[i] = (int)__builtin_nontemporal_load(ix + min(p0 + i * kWave + lane, pairs - 1));
+  };
+  float rest = 0.0f;
+  if (lane < total - 4 * quads) rest = src[4 * quads + lane];
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    if (half * (kQuads / 2) * kWave < quads) {  // uniform
+      f4 v[kQuads / 2];
+#pragma unroll
+      for (int i = 0; i < kQuads / 2; ++i)
+        v[i] = __builtin_nontemporal_load(reinterpret_cast<const f4_any*>(src) + min((half * (kQuads / 2) + i) * kWave + lane, quads - 1));
+#pragma unroll
+      for (int i = 0; i < kQuads / 2; ++i) asm volatile("" : "+v"(v[i]));  // (or the loads move to their uses)
+#pragma unroll
+      for (int i = 0; i < kQuads / 2; ++i) {
+        const int q = (half * (kQuads / 2) + i) * kWave + lane;
+        if (q < quads) reinterpret_cast<f4*>(s_rows)[q] = v[i];
       }
     }
+  }
+  load(0);
+  if (lane < total - 4 * quads) s_rows[4 * quads + lane] = rest;
+  wavefront_lds_order();
+  for (int p0 = 0;;) {
+    float g[BATCH];
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      const bool inside = (unsigned)c[i] < (unsigned)M;
+      const float read = s_rows[inside ? quotient(min(p0 + i * kWave + lane, pairs - 1), by) * M + c[i] : 0];
+      g[i] = inside ? read : 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) asm volatile("" : "+v"(g[i]));
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      const int p = p0 + i * kWave + lane;
+      if (p < pairs) to[p] = g[i];
+    }
+    p0 += BATCH * kWave;
+    if (p0 >= pairs) break;
+    load(p0);
   }
 }
 
@@ -204,48 +242,61 @@ __global__ void __launch_bounds__(256)
 // ---- host side --------------------------------------------------------------------------------------------
 
 
-// rows per wavefront of the rows-in-LDS kernels: about 8 KiB of LDS per wavefront
-inline int backward_rows_per_wave(int M) { return M <= 128 ? 16 : (M <= 256 ? 8 : (M <= 512 ? 4 : (M <= 1024 ? 2 : 1))); }
+// Rows per wavefront of the gather: 8 KiB of LDS, fewer where that would leave compute units with less than eight wavefronts.
+inline int backward_rows_per_wave(int64_t N, int M) {
+  const int64_t fill = N / 2048;
+  const int rows = kBackwardRowsM / M;
+  return fill >= rows ? rows : (fill < 1 ? 1 : (int)fill);
+}
 
-template <typename IdxT, bool VEC>
+// f(integral_constant<int, BATCH>) for a wavefront of up to `pairs` pairs.  No more than it has: a load whose lanes are all past the end costs as
+// much as another (1048576 x 256, k = 32, eight instructions of which four past the end 241 us, four 219).
+template <typename F>
+hipError_t by_pairs(int pairs, F f) {
+  const int need = (pairs + kWave - 1) / kWave, times = (need + 15) / 16, each = (need + times - 1) / times;
+#define X(n) if (each <= n) return f(std::integral_constant<int, n>());
+  X(1) X(2) X(3) X(4) X(5) X(6) X(8) X(10) X(13) X(16)
+#undef X
+  return hipErrorInvalidValue;  // not reached
+}
+
+template <typename IdxT>
 hipError_t launch_scatter(const float* gv, const IdxT* idx, int64_t N, int M, int k, float* gin, hipStream_t stream) {
   if (M > kBackwardRowsM) {
     if (N > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    return launch_kernel(maxk_scatter_block_kernel<IdxT, VEC>, dim3((unsigned)N), dim3(256), 0, stream, gv, idx, N, M, k,
-                         gin);
+    const bool whole = M % 4 == 0 && floats_behind(gin, 4) == 0;  // (every row starts and ends on a boundary: 65536 x 3000 130 us, 137 without)
+    return launch_kernel(whole ? maxk_scatter_block_kernel<IdxT, true> : maxk_scatter_block_kernel<IdxT, false>, dim3((unsigned)N), dim3(256), 0,
+                         stream, gv, idx, N, M, k, gin);
   }
-  const int R = backward_rows_per_wave(M);
-  const int kshift = pair_lanes(k).kshift;
-  const int64_t blocks = (N + R - 1) / R;
+  const int64_t elements = N * M;
+  int chunk = kBackwardRowsM;  // 8 KiB of LDS, less where that would leave compute units with less than eight wavefronts
+  while (chunk > 512 && elements / chunk < 2048 - 2048 / 8) chunk >>= 1;
+  const int skew = floats_behind(gin, 32);
+  const int64_t blocks = (elements + skew + chunk - 1) / chunk;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-  const size_t lds = (size_t)R * M * sizeof(float);
-  switch (R) {
-    case 16: return launch_kernel(maxk_scatter_rows_kernel<IdxT, 16, VEC>, dim3((unsigned)blocks), dim3(kWave), lds, stream, gv, idx, N, M, k, kshift, gin);
-    case 8: return launch_kernel(maxk_scatter_rows_kernel<IdxT, 8, VEC>, dim3((unsigned)blocks), dim3(kWave), lds, stream, gv, idx, N, M, k, kshift, gin);
-    case 4: return launch_kernel(maxk_scatter_rows_kernel<IdxT, 4, VEC>, dim3((unsigned)blocks), dim3(kWave), lds, stream, gv, idx, N, M, k, kshift, gin);
-    case 2: return launch_kernel(maxk_scatter_rows_kernel<IdxT, 2, VEC>, dim3((unsigned)blocks), dim3(kWave), lds, stream, gv, idx, N, M, k, kshift, gin);
-    default: return launch_kernel(maxk_scatter_rows_kernel<IdxT, 1, VEC>, dim3((unsigned)blocks), dim3(kWave), lds, stream, gv, idx, N, M, k, kshift, gin);
-  }
+  const int whole = skew == 0 && chunk % M == 0 ? chunk / M : 0;
+  const int rows = whole > 0 ? whole : (chunk + M - 2) / M + 1;  // that a chunk meets at most
+  return by_pairs(rows * k, [&](auto batch) {
+    constexpr int B = decltype(batch)::value;
+    const bool stream_pairs = whole > 0 && whole * k * sizeof(IdxT) % 128 == 0;
+    return launch_kernel(stream_pairs ? maxk_scatter_rows_kernel<IdxT, B, true> : maxk_scatter_rows_kernel<IdxT, B, false>,
+                         dim3((unsigned)blocks), dim3(kWave), chunk * sizeof(float), stream, gv, idx, elements, M, k, chunk, skew, whole, divisor(k), divisor(M), 1.0 / M, gin);
+  });
 }
 
-template <typename IdxT, bool VEC>
+template <typename IdxT>
 hipError_t launch_gather(const float* gout, const IdxT* idx, int64_t N, int M, int k, float* gv, hipStream_t stream) {
   if (M > kBackwardRowsM) {
     if (N > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     return launch_kernel(maxk_gather_block_kernel<IdxT>, dim3((unsigned)N), dim3(256), 0, stream, gout, idx, N, M, k, gv);
   }
-  const int R = backward_rows_per_wave(M);
-  const int kshift = pair_lanes(k).kshift;
-  const int64_t blocks = (N + R - 1) / R;
+  const int rows = backward_rows_per_wave(N, M);
+  const int64_t blocks = (N + rows - 1) / rows;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-  const size_t lds = (size_t)R * M * sizeof(float);
-  switch (R) {
-    case 16: return launch_kernel(maxk_gather_rows_kernel<IdxT, 16, VEC>, dim3((unsigned)blocks), dim3(kWave), lds, stream, gout, idx, N, M, k, kshift, gv);
-    case 8: return launch_kernel(maxk_gather_rows_kernel<IdxT, 8, VEC>, dim3((unsigned)blocks), dim3(kWave), lds, stream, gout, idx, N, M, k, kshift, gv);
-    case 4: return launch_kernel(maxk_gather_rows_kernel<IdxT, 4, VEC>, dim3((unsigned)blocks), dim3(kWave), lds, stream, gout, idx, N, M, k, kshift, gv);
-    case 2: return launch_kernel(maxk_gather_rows_kernel<IdxT, 2, VEC>, dim3((unsigned)blocks), dim3(kWave), lds, stream, gout, idx, N, M, k, kshift, gv);
-    default: return launch_kernel(maxk_gather_rows_kernel<IdxT, 1, VEC>, dim3((unsigned)blocks), dim3(kWave), lds, stream, gout, idx, N, M, k, kshift, gv);
-  }
+  return by_pairs(rows * k, [&](auto batch) {
+    return launch_kernel(maxk_gather_rows_kernel<IdxT, decltype(batch)::value>, dim3((unsigned)blocks), dim3(kWave),
+                         ((size_t)rows * M + 3) / 4 * 16, stream, gout, idx, N, M, k, rows, divisor(k), gv);
+  });
 }
 
 }  // namespace rtopk

@@ -52,10 +52,10 @@ hipError_t launch_split_any(int mode, bool smallest, void* scratch, const Launch
 hipError_t launch_dense_any(int g, int ng, bool full, int mode, const LaunchArgs& a);
 
 // Backward edge of the MaxK non-linearity (rtopk_backward.hpp).  idx is int32_t[N][k] or, with u8,
-// uint8_t[N][k]; vec = M % 4 == 0 and the dense [N][M] array 16-byte aligned (128-bit accesses).
+// uint8_t[N][k].
 hipError_t launch_maxk_backward(const float* grad_vals, const void* idx, bool u8, int64_t N, int M, int k, float* grad_in,
-                                bool vec, hipStream_t stream);
+                                hipStream_t stream);
 hipError_t launch_maxk_backward_gather(const float* grad_out, const void* idx, bool u8, int64_t N, int M, int k,
-                                       float* grad_vals, bool vec, hipStream_t stream);
+                                       float* grad_vals, hipStream_t stream);
 
 }  // namespace rtopk

@@ -4,27 +4,15 @@
 namespace rtopk {
 
 hipError_t launch_maxk_backward(const float* grad_vals, const void* idx, bool u8, int64_t N, int M, int k, float* grad_in,
-                                bool vec, hipStream_t stream) {
-  if (u8) {
-    const uint8_t* ix = static_cast<const uint8_t*>(idx);
-    return vec ? launch_scatter<uint8_t, true>(grad_vals, ix, N, M, k, grad_in, stream)
-               : launch_scatter<uint8_t, false>(grad_vals, ix, N, M, k, grad_in, stream);
-  }
-  const int32_t* ix = static_cast<const int32_t*>(idx);
-  return vec ? launch_scatter<int32_t, true>(grad_vals, ix, N, M, k, grad_in, stream)
-             : launch_scatter<int32_t, false>(grad_vals, ix, N, M, k, grad_in, stream);
+                                hipStream_t stream) {
+  return u8 ? launch_scatter(grad_vals, static_cast<const uint8_t*>(idx), N, M, k, grad_in, stream)
+            : launch_scatter(grad_vals, static_cast<const int32_t*>(idx), N, M, k, grad_in, stream);
 }
 
 hipError_t launch_maxk_backward_gather(const float* grad_out, const void* idx, bool u8, int64_t N, int M, int k,
-                                       float* grad_vals, bool vec, hipStream_t stream) {
-  if (u8) {
-    const uint8_t* ix = static_cast<const uint8_t*>(idx);
-    return vec ? launch_gather<uint8_t, true>(grad_out, ix, N, M, k, grad_vals, stream)
-               : launch_gather<uint8_t, false>(grad_out, ix, N, M, k, grad_vals, stream);
-  }
-  const int32_t* ix = static_cast<const int32_t*>(idx);
-  return vec ? launch_gather<int32_t, true>(grad_out, ix, N, M, k, grad_vals, stream)
-             : launch_gather<int32_t, false>(grad_out, ix, N, M, k, grad_vals, stream);
+                                       float* grad_vals, hipStream_t stream) {
+  return u8 ? launch_gather(grad_out, static_cast<const uint8_t*>(idx), N, M, k, grad_vals, stream)
+            : launch_gather(grad_out, static_cast<const int32_t*>(idx), N, M, k, grad_vals, stream);
 }
 
 }  // namespace rtopk

@@ -134,3 +134,40 @@ def test_backward_empty_batch_and_errors():
         R.rtopk_maxk_backward(g, i, 4)  # k > M
     with pytest.raises(ValueError):
         R.rtopk_maxk_backward(g, torch.zeros((4, 8), dtype=torch.uint8, device="cuda"), 300)
+
+
+@pytest.mark.parametrize("M,k", [(1, 1), (2, 1), (31, 31), (33, 3), (100, 65), (129, 1), (251, 100), (256, 129), (257, 5), (683, 300), (1023, 77),
+                                 (1025, 1025), (2047, 1), (2047, 2047), (2049, 40), (8193, 600)])
+def test_backward_at_any_alignment(M, k):
+    """Dense and pair arrays that start anywhere in a 128-byte line; whole and cut chunks, the first and last of the matrix."""
+    import ctypes
+
+    R = _gpu()
+    lib = R.load_library()
+    rng = np.random.default_rng(M * 7 + k)
+    for N in (1, 7, 4100) if M <= 683 else (1, 67):
+        idx = np.argsort(rng.random((N, M)), axis=1)[:, :k].astype(np.int32)  # any order
+        g, w = workloads.normal(N, k, M + N), workloads.normal(N, M, M + N + 1)
+        want, want_gather = oracle.maxk_backward(g, idx, M), oracle.maxk_backward_gather(w, idx)
+        for u8 in (False, True) if M <= 256 else (False,):
+            for shift in (0, 1, 2, 7, 31):
+                dense = torch.full((N * M + 96,), 7.5, device="cuda")
+                pairs = torch.full((N * k + 96,), 7.5, device="cuda")
+                cols = torch.zeros(N * k + 96, device="cuda", dtype=torch.uint8 if u8 else torch.int32)
+                cols[shift:shift + N * k] = torch.from_numpy(idx.ravel()).cuda()
+                pairs[shift:shift + N * k] = torch.from_numpy(g.ravel()).cuda()
+                suffix, ptr = "_u8" if u8 else "", lambda t, s: ctypes.c_void_p(t[s:].data_ptr())
+                stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+                args = (ctypes.c_int64(N), ctypes.c_int32(M), ctypes.c_int32(k))
+                rc = getattr(lib, "rtopk_maxk_backward" + suffix)(ptr(pairs, shift), ptr(cols, shift), *args, ptr(dense, 2 * shift), stream)
+                assert rc == 0
+                got = dense.cpu().numpy()
+                assert np.array_equal(bits(got[2 * shift:2 * shift + N * M]), bits(want.ravel())), (N, shift, u8)
+                assert (got[:2 * shift] == 7.5).all() and (got[2 * shift + N * M:] == 7.5).all(), "wrote outside the matrix"
+                dense[shift:shift + N * M] = torch.from_numpy(w.ravel()).cuda()
+                pairs.fill_(7.5)
+                rc = getattr(lib, "rtopk_maxk_backward_gather" + suffix)(ptr(dense, shift), ptr(cols, shift), *args, ptr(pairs, shift), stream)
+                assert rc == 0
+                got = pairs.cpu().numpy()
+                assert np.array_equal(bits(got[shift:shift + N * k]), bits(want_gather.ravel())), (N, shift, u8)
+                assert (got[:shift] == 7.5).all() and (got[shift + N * k:] == 7.5).all(), "wrote outside the pairs"
