@@ -39,10 +39,10 @@ __device__ __forceinline__ T load_pair(const T* p) {
   return STREAM ? __builtin_nontemporal_load(p) : *p;
 }
 
-// out[0..n) = image[pad..pad + n), by `threads` threads of which this is number `tid`.  pad: floats that `out` lies behind a 16-byte boundary, so that
-// whole quads of the image leave as aligned 128-bit stores; what precedes and follows them goes one by one.  ALIGNED: pad is 0, n a multiple of four.
 // Floats that p lies behind a boundary of n of them.
 __device__ __host__ __forceinline__ int floats_behind(const float* p, int n) { return (int)((reinterpret_cast<uintptr_t>(p) >> 2) & (n - 1)); }
+// out[0..n) = image[pad..pad + n), by `threads` threads of which this is number `tid`.  pad: floats that `out` lies behind a 16-byte boundary, so that
+// whole quads of the image leave as aligned 128-bit stores; what precedes and follows them goes one by one.  ALIGNED: pad is 0, n a multiple of four.
 template <bool ALIGNED>
 __device__ __forceinline__ void store_image(float* __restrict__ out, const float* image, int n, int pad, int tid, int threads) {
   const uint4* quads = reinterpret_cast<const uint4*>(image);
