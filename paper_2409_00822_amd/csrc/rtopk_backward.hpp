@@ -161,8 +161,8 @@ __global__ void __launch_bounds__(256)
 //
 // One wavefront per `rows` rows, at most kBackwardRowsM floats in all: 128-bit loads (from any 4-byte boundary, see load_group), four per lane at a
 // time (eight: 2^20 x 256, k = 32 225 -> 219 us, 2^18 x 512 111.5 -> 109.2), then the saved columns' entries are read from LDS, and the results, again
-// contiguous in the output, are stored coalesced.
-template <typename IdxT, int BATCH>
+// contiguous in the output, are stored coalesced.  FOURS: M is a multiple of four, so that nothing is left beside the 128-bit loads.
+template <typename IdxT, int BATCH, bool FOURS>
 __global__ void __launch_bounds__(kWave)
     maxk_gather_rows_kernel(const float* __restrict__ grad_out, const IdxT* __restrict__ idx, int64_t N, int M, int k, int rows,
                             uint32_t by, float* __restrict__ grad_vals) {
@@ -183,7 +183,7 @@ __global__ void __launch_bounds__(kWave)
     for (int i = 0; i < BATCH; ++i) c[i] = (int)__builtin_nontemporal_load(ix + min(p0 + i * kWave + lane, pairs - 1));
   };
   float rest = 0.0f;
-  if (lane < total - 4 * quads) rest = src[4 * quads + lane];
+  if (!FOURS && lane < total - 4 * quads) rest = src[4 * quads + lane];
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     if (half * (kQuads / 2) * kWave < quads) {  // uniform
@@ -201,7 +201,7 @@ __global__ void __launch_bounds__(kWave)
     }
   }
   load(0);
-  if (lane < total - 4 * quads) s_rows[4 * quads + lane] = rest;
+  if (!FOURS && lane < total - 4 * quads) s_rows[4 * quads + lane] = rest;
   wavefront_lds_order();
   for (int p0 = 0;;) {
     float g[BATCH];
@@ -294,8 +294,9 @@ hipError_t launch_gather(const float* gout, const IdxT* idx, int64_t N, int M, i
   const int64_t blocks = (N + rows - 1) / rows;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   return by_pairs(rows * k, [&](auto batch) {
-    return launch_kernel(maxk_gather_rows_kernel<IdxT, decltype(batch)::value>, dim3((unsigned)blocks), dim3(kWave),
-                         ((size_t)rows * M + 3) / 4 * 16, stream, gout, idx, N, M, k, rows, divisor(k), gv);
+    constexpr int B = decltype(batch)::value;
+    return launch_kernel(M % 4 == 0 ? maxk_gather_rows_kernel<IdxT, B, true> : maxk_gather_rows_kernel<IdxT, B, false>, dim3((unsigned)blocks),
+                         dim3(kWave), ((size_t)rows * M + 3) / 4 * 16, stream, gout, idx, N, M, k, rows, divisor(k), gv);
   });
 }
 
