@@ -25,7 +25,7 @@ namespace rtopk {
 // loaded together, while the rows are cleared or loaded.  All loads are unconditional (lanes past the end repeat the last): behind a
 // branch each would be waited for alone.  What bounds both is HBM, given enough loads in flight.  Measured against 2, 4, 8 or 16 whole rows
 // with the lanes divided among them, dword accesses where M is no multiple of four and a loop over the row for k > 64, us, inputs cold: 1048576
-// x 251, k = 31 scatter 340 -> 213, gather 536 -> 230; x 250, k = 100 685 -> 273, 728 -> 293; x 256, k = 32 210 -> 207, 201 -> 206, k = 128 645 -> 294, 371
+// x 251, k = 31 scatter 340 -> 213, gather 536 -> 230; x 250, k = 100 685 -> 273, 728 -> 293; x 256, k = 32 210 -> 207, 203 -> 204, k = 128 645 -> 294, 371
 // -> 282; 262144 x 777, k = 40 265 -> 161, 310 -> 154; 131072 x 2048, k = 100 261 -> 222, 190 -> 192 (byte columns up to 256).
 // n / d for n up to 3 * 2048 and d up to 2048, exactly: n * (by - 2^32 / d) < 2^32 / d.  by: ceil(2^32 / d), 0 where that is 2^32.
 __device__ __forceinline__ int quotient(int n, uint32_t by) { return by == 0 ? n : (int)__umulhi((uint32_t)n, by); }
