@@ -324,6 +324,24 @@ inline bool splits_early(int64_t N, int M, int max_iter) {
   if (max_iter < 1 || M <= kMaxBlockM) return false;
   return (max_iter >= 2 && max_iter <= 4) || M < 1 << 19 || N * M < 1ll << 28;
 }
+// Columns of each of `segments` segments, and the values per lane of w wavefronts that hold them.
+constexpr int segment_length(int M, int segments) { return ((M + segments - 1) / segments + 3) & ~3; }
+constexpr int segment_values(int length, int w) { return length <= w * 3072 ? 48 : 64; }
+// Segments of 16384 columns where those of 32768, `wide` of them in all, give every compute unit two workgroups or more: of the smaller workgroups five
+// share a compute unit instead of two, but the merge has twice the candidates, so up to four workgroups for each (eight, six from k = 33 on,
+// with up to eight lists to a row), for k up to 128, where a merge of four wavefronts holds the `candidates`.  Not where the longer segments fill
+// their lanes (to 31/32) or hold 48 values there and the shorter ones 64: these then gain nothing for themselves.  Time with 32768-column
+// segments over time with 16384-column ones, at 720, 1100 and 2000 longer segments in all:
+//   k = 64: 50000 columns 1.07 1.12 1.04, 36000 1.04 1.08 1.02, 62000 1.03 1.08 1.00, 80000 1.07 1.07 1.01, 94000 1.07 1.11 1.05, 110000 1.10 1.15 1.07,
+//     126000 1.00 1.06 0.99, 164776 1.04, 230000 1.05; k = 8: 50000 1.08 1.14 1.11, 126000 1.03 1.08 1.02;
+//   left out: full lanes, 65536 1.01 0.99 0.90, 98304 1.00 0.96 0.91, 131072 0.98 0.97 0.89, 262144 0.97; 48 values against 64, 44000 0.99 1.05 1.01, 38000
+//     0.98 1.04 1.00, 70000 0.98 1.00 0.97; k = 150: 56000 1.00 1.03 0.95, 90000 0.98 1.02 0.93; k = 250: 34424 0.94 0.98 0.95, 59000 0.95 0.98 0.94.
+inline bool shorter_segments(int M, int k, int64_t wide, int64_t candidates) {
+  const int long_ones = (M + 32767) / 32768, short_ones = (M + 16383) / 16384;
+  const int length = segment_length(M, long_ones), values = segment_values(length, 8);
+  return k <= 128 && wide < (short_ones > 8 ? 4 : (k <= 32 ? 8 : 6)) * 256 && candidates <= 4 * 64 * kMergeRegs && 32 * length <= 31 * 512 * values &&
+         values >= segment_values(segment_length(M, short_ones), 4);
+}
 inline Split split_of(int64_t N, int M, int k, int mode, int max_iter) {
   Split s{};
   // Up to 32768 columns one workgroup per row does as well.
@@ -335,23 +353,18 @@ inline Split split_of(int64_t N, int M, int k, int mode, int max_iter) {
   while (root * root < k) ++root;
   const int usual = k + k / 3 + 10 * root + 24, expected = k + k / 3 + 6 * root + 16;
   // Segments of 32768 columns, unless those would not give every compute unit two workgroups and those of 16384, which have
-  // twice the candidates in all, still fit the merge; or, where these fit a merge of four wavefronts, four workgroups (eight with few
-  // segments to a row): more of the smaller workgroups share a compute unit, and the last round of them is shorter (us, 32768 -> 16384
-  // columns: 129 x 164776, k = 55 24.2 -> 21.6; 93 x 281245, k = 16 25.3 -> 23.8; 300 x 108960, k = 29 29.6 -> 27.6; 946 x 63250 46.5 -> 43.6; but
-  // 85 x 457696, k = 12, 28 segments 33.4 -> 34.1, 16 x 2^20, k = 100 22.7 -> 27.2).
+  // twice the candidates in all, still fit the merge; or, up to twice that many rows and more, where shorter_segments says so.
   s.w = 8;
   const int64_t wide = N * ((M + 32767) / 32768), narrow = (M + 16383) / 16384;
-  if (k <= filter_max_k(4) && (wide < 2 * 256 ? narrow * expected <= kMergeMost
-                                              : wide < (narrow <= 8 ? 8 : 4) * 256 && narrow * usual <= 4 * 64 * kMergeRegs))
-    s.w = 4;
+  if (k <= filter_max_k(4) && (wide < 2 * 256 ? narrow * expected <= kMergeMost : shorter_segments(M, k, wide, narrow * usual))) s.w = 4;
   const int most = s.w * 4096;
   s.segments = (M + most - 1) / most;
   if ((int64_t)s.segments * expected > kMergeMost) {
     s.segments = 0;
     return s;
   }
-  s.length = ((M + s.segments - 1) / s.segments + 3) & ~3;
-  s.ng = s.length <= s.w * 3072 ? 12 : 16;
+  s.length = segment_length(M, s.segments);
+  s.ng = segment_values(s.length, s.w) / 4;
   const int64_t need = (int64_t)s.segments * usual, per_wave = 64 * kMergeRegs;
   s.merge_waves = need <= 4 * per_wave ? 4 : (need <= 8 * per_wave ? 8 : 16);
   const int share = (int)(s.merge_waves * per_wave / s.segments);
