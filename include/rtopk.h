@@ -121,6 +121,8 @@ int rtopk_rowwise_exact_smallest(const float* in, int64_t N, int32_t M, int32_t 
  * spread over several workgroups each, which few or very wide rows need to fill the GPU; the work is then a few launches
  * on `stream` instead of one, and the memory may be used again by later work on that stream.  Without it (NULL, too few
  * bytes, or a shape for which rtopk_workspace_bytes returns 0) the call is the plain entry point's.  Same results.
+ * Memory that is enough for N rows is enough to spread any smaller number of the same rows (rtopk_workspace_bytes may
+ * return more for these: with as much, they are spread over more workgroups each).
  *   variant   : RTOPK_EARLY (max_iter), RTOPK_EXACT or RTOPK_EPS (eps_rel, optional out_iters; NULL otherwise), with
  *               RTOPK_SMALLEST added for the k smallest (not with RTOPK_EPS); anything else: RTOPK_ERR_BAD_SHAPE.
  */

@@ -71,9 +71,9 @@ int run(const void* in, int64_t N, int32_t M, int32_t k, int32_t max_iter, float
   const rtopk::Shape sh = rtopk::layout_of_call(N, M, k, dtype, mode, max_iter, plain, false);
   hipError_t err;
   if (scratch && dtype == rtopk::kF32 && !u8) {
-    const int64_t need = rtopk::split_scratch_bytes(N, M, k, mode, max_iter);
-    if (need > 0 && scratch_bytes >= need)
-      return rtopk::launch_split_any(mode, smallest, scratch, a) == hipSuccess ? RTOPK_OK : RTOPK_ERR_LAUNCH;
+    const rtopk::Split split = rtopk::split_for(N, M, k, mode, max_iter, scratch_bytes);
+    if (split.segments > 0)
+      return rtopk::launch_split_any(split, mode, smallest, scratch, a) == hipSuccess ? RTOPK_OK : RTOPK_ERR_LAUNCH;
   }
   switch (sh.family) {
     case rtopk::kFamStream:
@@ -195,7 +195,8 @@ int rtopk_select_ws(const float* in, int64_t N, int32_t M, int32_t k, int32_t va
 
 int64_t rtopk_workspace_bytes(int64_t N, int32_t M, int32_t k, int32_t variant, int32_t max_iter) {
   if (N < 1 || M < 1 || M > rtopk::kMaxM || k < 1 || k >= M || (variant & ~7) != 0 || (variant & 3) == 3) return 0;
-  return rtopk::split_scratch_bytes(N, M, k, variant & 3, max_iter);
+  const rtopk::Split split = rtopk::split_for(N, M, k, variant & 3, max_iter);
+  return split.segments > 0 ? split.bytes() : 0;
 }
 
 int rtopk_maxk_dense(const float* in, int64_t N, int32_t M, int32_t k, int32_t max_iter, float* out, void* stream) {

@@ -43,10 +43,8 @@ hipError_t launch_block_h16(int dtype, int g, int ng, int w, int mode, const Lau
 // Rows wider than 65536 columns (fp32, int32 columns, every mode, the k largest or smallest): one
 // workgroup per row, the row streamed.
 hipError_t launch_stream_any(int mode, bool smallest, const LaunchArgs& a);
-// fp32 rows of more than 32768 columns over several workgroups each, in two launches: the scratch memory that takes
-// (0: not for this shape), and the launch.
-int64_t split_scratch_bytes(int64_t N, int M, int k, int mode, int max_iter);
-hipError_t launch_split_any(int mode, bool smallest, void* scratch, const LaunchArgs& a);
+// fp32 rows of more than 32768 columns over several workgroups each, in two launches; s: split_for, not empty.
+hipError_t launch_split_any(const Split& s, int mode, bool smallest, void* scratch, const LaunchArgs& a);
 // Dense-output form (fp32; a.out_vals is the [N][M] output, a.out_idx unused).  g, ng, full as above;
 // mode kEarly or kExact.
 hipError_t launch_dense_any(int g, int ng, bool full, int mode, const LaunchArgs& a);

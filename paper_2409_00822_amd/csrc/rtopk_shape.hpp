@@ -342,7 +342,8 @@ inline bool shorter_segments(int M, int k, int64_t wide, int64_t candidates) {
   return k <= 128 && wide < (short_ones > 8 ? 4 : (k <= 32 ? 8 : 6)) * 256 && candidates <= 4 * 64 * kMergeRegs && 32 * length <= 31 * 512 * values &&
          values >= segment_values(segment_length(M, short_ones), 4);
 }
-inline Split split_of(int64_t N, int M, int k, int mode, int max_iter) {
+// wide_only: segments of 32768 columns whatever the number of rows.
+inline Split split_of(int64_t N, int M, int k, int mode, int max_iter, bool wide_only = false) {
   Split s{};
   // Up to 32768 columns one workgroup per row does as well.
   if (M <= 32768 || N < 1 || k > filter_max_k(8) || (mode == kEarly && !splits_early(N, M, max_iter))) return s;
@@ -356,7 +357,7 @@ inline Split split_of(int64_t N, int M, int k, int mode, int max_iter) {
   // twice the candidates in all, still fit the merge; or, up to twice that many rows and more, where shorter_segments says so.
   s.w = 8;
   const int64_t wide = N * ((M + 32767) / 32768), narrow = (M + 16383) / 16384;
-  if (k <= filter_max_k(4) && (wide < 2 * 256 ? narrow * expected <= kMergeMost : shorter_segments(M, k, wide, narrow * usual))) s.w = 4;
+  if (!wide_only && k <= filter_max_k(4) && (wide < 2 * 256 ? narrow * expected <= kMergeMost : shorter_segments(M, k, wide, narrow * usual))) s.w = 4;
   const int most = s.w * 4096;
   s.segments = (M + most - 1) / most;
   if ((int64_t)s.segments * expected > kMergeMost) {
@@ -410,6 +411,16 @@ inline Split split_big_of(int64_t N, int M, int k, int mode, int max_iter) {
   if (s.rows < 1) s.rows = 1;
   if (s.rows > N) s.rows = N;
   return s;
+}
+
+// The split of a call that is lent `lent` bytes of scratch memory.  Segments of 16384 columns take nearly twice as much as those of 32768, which are
+// what more rows take: memory that serves a batch serves every smaller one, with the longer segments where the shorter ones do not fit (2048 x 50000, k =
+// 100: one workgroup per row, without memory, 135 us, 32768-column segments 79).
+inline Split split_for(int64_t N, int M, int k, int mode, int max_iter, int64_t lent = INT64_MAX) {
+  Split s = split_of(N, M, k, mode, max_iter);
+  if (s.segments > 0 && s.bytes() > lent) s = split_of(N, M, k, mode, max_iter, true);
+  if (s.segments == 0) s = split_big_of(N, M, k, mode, max_iter);
+  return s.segments > 0 && s.bytes() <= lent ? s : Split{};
 }
 
 // Largest max_iter that is evaluated literally.  Each step of Algorithm 2 halves hi - lo, so on finite

@@ -9,8 +9,8 @@
 //   3. the layout that is launched for every row width 1..65536 (and a sample of the streamed widths up to
 //      2^24), every element type, both kernel variants and the dense form: it must be compiled, hold the row and
 //      be no wider than its kernels take for granted;
-//   4. how rows are spread over several workgroups, over widths, k, row counts and modes: segments, lists and
-//      scratch memory within what the kernels and the merge hold.
+//   4. how rows are spread over several workgroups, over widths, k, row counts, modes and steps: segments, lists and
+//      scratch memory within what the kernels and the merge hold, and what is lent for a batch enough for smaller ones.
 //
 // Usage: sanitize_main <path to alg2_handtrace.txt>.  Exit code 0 = all checks passed.
 #include <stdint.h>
@@ -196,33 +196,53 @@ static long run_shape_sweep() {
 }
 
 // ---- 4. rows spread over several workgroups ---------------------------------------------------------
+static void check_split(const rtopk::Split& s, int64_t M, int k, int64_t N) {
+  CHECK(M > 32768 && k <= 512, "M=%ld k=%d is split", (long)M, k);
+  CHECK(s.segments >= 2 && s.segments <= rtopk::kMaxSegments, "M=%ld k=%d: %d segments", (long)M, k, s.segments);
+  CHECK(s.w == 4 || s.w == 8, "M=%ld: %d wavefronts", (long)M, s.w);
+  CHECK(k <= rtopk::filter_max_k(s.w), "M=%ld k=%d: lists of %d wavefronts", (long)M, k, s.w);
+  CHECK(s.length % 4 == 0 && s.length <= 64 * s.w * 4 * s.ng && (s.ng == 12 || s.ng == 16), "M=%ld: length %d", (long)M, s.length);
+  const int64_t last = M - (int64_t)(s.segments - 1) * s.length;
+  CHECK(last > 0 && last <= s.length, "M=%ld: last segment of %ld", (long)M, (long)last);
+  // every wavefront has group maxima (of 16 values per lane) for its share of the floor
+  CHECK(last >= 64 * s.w * 4 * 4 + 64 * s.w * 4, "M=%ld: last segment of %ld in %d wavefronts", (long)M, (long)last, s.w);
+  CHECK(s.cap > k && s.cap <= rtopk::segment_room(s.w), "M=%ld k=%d: lists of %d", (long)M, k, s.cap);
+  CHECK(s.merge_waves == 4 || s.merge_waves == 8 || s.merge_waves == 16, "M=%ld: %d merging", (long)M, s.merge_waves);
+  if (s.merge_waves < 16)
+    CHECK((int64_t)s.segments * s.cap <= (int64_t)s.merge_waves * 64 * rtopk::kMergeRegs, "M=%ld k=%d: more than the merge holds", (long)M, k);
+  CHECK(s.rows >= 1 && s.rows <= N && s.rows * s.segments <= 0x7fffffff, "M=%ld N=%ld: %ld rows", (long)M, (long)N, (long)s.rows);
+  CHECK(s.rows == 1 || s.bytes() <= rtopk::kSplitScratch, "M=%ld N=%ld: %ld bytes", (long)M, (long)N, (long)s.bytes());
+}
+
 static long run_split_sweep() {
+  const int64_t counts[] = {1, 2, 15, 16, 64, 128, 255, 256, 511, 512, 700, 1000, 1023, 1024, 2047, 2048, 100000};
   long n = 0;
   for (int64_t M = 32760; M <= rtopk::kMaxM; M += (M < 33000 || (M > 65500 && M < 65600)) ? 1 : M / 61 + 1) {
     for (int k : {1, 2, 7, 33, 64, 100, 200, 255, 256, 257, 400, 511, 512, 513, 1000}) {
-      for (int64_t N : {(int64_t)1, (int64_t)2, (int64_t)15, (int64_t)16, (int64_t)64, (int64_t)255, (int64_t)256, (int64_t)1000, (int64_t)100000}) {
-        for (int mode : {(int)rtopk::kExact, (int)rtopk::kEarly, (int)rtopk::kEps}) {
-          const rtopk::Split s = rtopk::split_of(N, (int)M, k, mode, 8);
-          ++n;
-          if (s.segments == 0) {
-            CHECK(rtopk::split_of(1 << 20, (int)M, k, mode, 8).segments == 0, "M=%ld k=%d: split for many rows but not for %ld", (long)M, k, (long)N);
-            continue;
+      for (int mode : {(int)rtopk::kExact, (int)rtopk::kEarly, (int)rtopk::kEps}) {
+        for (int steps : {8, 0, 1, 2, 4, 5, 7}) {
+          if (mode != rtopk::kEarly && steps != 8) continue;
+          const bool few = mode == rtopk::kEarly && steps < 8;  // (these go by the number of rows, too)
+          int64_t most = -1;  // memory that serves the batches up to this one, from the largest down
+          for (int c = (int)(sizeof(counts) / sizeof(counts[0])) - 1; c >= 0; --c) {
+            const int64_t N = counts[c];
+            const rtopk::Split s = rtopk::split_of(N, (int)M, k, mode, steps);
+            ++n;
+            if (s.segments == 0) {
+              if (!few) CHECK(rtopk::split_of(1 << 20, (int)M, k, mode, steps).segments == 0, "M=%ld k=%d: split for many rows but not for %ld", (long)M, k, (long)N);
+            } else {
+              CHECK(!few || (steps >= 1 && M > rtopk::kMaxBlockM && s.merge_waves == 16), "M=%ld: %d steps, %d merging", (long)M, steps, s.merge_waves);
+              check_split(s, M, k, N);
+            }
+            const rtopk::Split any = rtopk::split_for(N, (int)M, k, mode, steps);
+            if (any.segments > 0) CHECK(rtopk::split_for(N, (int)M, k, mode, steps, any.bytes() - 1).bytes() < any.bytes(), "M=%ld k=%d N=%ld: more than was lent", (long)M, k, (long)N);
+            if (most > 0) {
+              const rtopk::Split with = rtopk::split_for(N, (int)M, k, mode, steps, most);
+              CHECK(with.segments > 0 && with.bytes() <= most, "M=%ld k=%d: %ld rows not split with the memory of more", (long)M, k, (long)N);
+              if (s.segments > 0) check_split(with, M, k, N);
+            }
+            if (any.segments > 0 && (most < 0 || any.bytes() < most)) most = any.bytes();
           }
-          CHECK(M > 32768 && k <= 512, "M=%ld k=%d is split", (long)M, k);
-          CHECK(s.segments >= 2 && s.segments <= rtopk::kMaxSegments, "M=%ld k=%d: %d segments", (long)M, k, s.segments);
-          CHECK(s.w == 4 || s.w == 8, "M=%ld: %d wavefronts", (long)M, s.w);
-          CHECK(k <= rtopk::filter_max_k(s.w), "M=%ld k=%d: lists of %d wavefronts", (long)M, k, s.w);
-          CHECK(s.length % 4 == 0 && s.length <= 64 * s.w * 4 * s.ng && (s.ng == 12 || s.ng == 16), "M=%ld: length %d", (long)M, s.length);
-          const int64_t last = M - (int64_t)(s.segments - 1) * s.length;
-          CHECK(last > 0 && last <= s.length, "M=%ld: last segment of %ld", (long)M, (long)last);
-          // every wavefront has group maxima (of 16 values per lane) for its share of the floor
-          CHECK(last >= 64 * s.w * 4 * 4 + 64 * s.w * 4, "M=%ld: last segment of %ld in %d wavefronts", (long)M, (long)last, s.w);
-          CHECK(s.cap > k && s.cap <= rtopk::segment_room(s.w), "M=%ld k=%d: lists of %d", (long)M, k, s.cap);
-          CHECK(s.merge_waves == 4 || s.merge_waves == 8 || s.merge_waves == 16, "M=%ld: %d merging", (long)M, s.merge_waves);
-          if (s.merge_waves < 16)
-            CHECK((int64_t)s.segments * s.cap <= (int64_t)s.merge_waves * 64 * rtopk::kMergeRegs, "M=%ld k=%d: more than the merge holds", (long)M, k);
-          CHECK(s.rows >= 1 && s.rows <= N && s.rows * s.segments <= 0x7fffffff, "M=%ld N=%ld: %ld rows", (long)M, (long)N, (long)s.rows);
-          CHECK(s.rows == 1 || s.bytes() <= rtopk::kSplitScratch, "M=%ld N=%ld: %ld bytes", (long)M, (long)N, (long)s.bytes());
         }
       }
     }

@@ -154,3 +154,28 @@ def test_many_short_lists(M, k):
     got = R.rtopk_rowwise_eps(xd, k, 1e-4, want_iters=True)
     _same(got, (ev, ei), f"M={M} k={k} eps")
     assert np.array_equal(got[2].cpu().numpy(), et)
+
+
+@pytest.mark.parametrize("M, k, most, fewer", [(50000, 64, 1024, (1023, 700, 512, 3)), (80000, 64, 512, (511, 380, 2))])
+def test_memory_for_a_batch_serves_smaller_ones(M, k, most, fewer):
+    # the shorter segments of fewer rows need more than the longer ones of more: then these are taken, and the memory is used
+    R = _gpu()
+    lib = R.load_library()
+    lib.rtopk_workspace_bytes.restype = ctypes.c_int64
+    lib.rtopk_workspace_bytes.argtypes = [ctypes.c_int64] + [ctypes.c_int32] * 4
+    fn = lib.rtopk_select_ws
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int64] + [ctypes.c_int32] * 4 + [ctypes.c_float] + [ctypes.c_void_p] * 4 + [
+        ctypes.c_int64, ctypes.c_void_p]
+    lent = lib.rtopk_workspace_bytes(most, M, k, 1, 0)
+    assert any(lib.rtopk_workspace_bytes(N, M, k, 1, 0) > lent for N in fewer)
+    x = torch.randn(max(fewer), M, device="cuda")
+    w = torch.empty(lent, dtype=torch.uint8, device="cuda")
+    s = torch.cuda.current_stream().cuda_stream
+    for N in fewer:
+        v = torch.empty(N, k, device="cuda")
+        i = torch.empty(N, k, dtype=torch.int32, device="cuda")
+        w.fill_(0xA5)
+        assert fn(x.data_ptr(), N, M, k, 1, 0, 0.0, v.data_ptr(), i.data_ptr(), None, w.data_ptr(), lent, s) == 0
+        assert not (w == 0xA5).all(), f"N={N}: not split"
+        pv, pi = _plain(R, x[:N], k)
+        assert torch.equal(v, pv) and torch.equal(i, pi), f"N={N}"
