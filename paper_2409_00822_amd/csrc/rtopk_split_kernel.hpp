@@ -490,10 +490,10 @@ __device__ __forceinline__ bool merge_row(MergeLds<NW>& s, int64_t r, const floa
       load_by_number<NW, KR, NEG>(s, of_row, segments, cap, per, total, key, col);
       return merge_candidates<NW, KR, MODE, NEG, RANK>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters, key, col, per, T0, lo, hi, rest);
     };
-    if (NW < 16 && per <= 4) {
-      done = numbered(std::integral_constant<int, NW < 16 ? 4 : kMergeRegs>());
-    } else if (NW < 16 && per <= 8) {
-      done = numbered(std::integral_constant<int, NW < 16 ? 8 : kMergeRegs>());
+    if (per <= 4) {  // (1 x 2200003, 135 lists: k = 10 19.7 us in 16 registers, 12.9 in 4; k = 20 20.1 and 15.3; 1 x 2^20, k = 8, four steps 16.3 and 11.5)
+      done = numbered(std::integral_constant<int, 4>());
+    } else if (per <= 8) {
+      done = numbered(std::integral_constant<int, 8>());
     } else if (NW < 16 || per <= kMergeRegs) {
       done = numbered(std::integral_constant<int, kMergeRegs>());
     } else {

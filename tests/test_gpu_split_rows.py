@@ -179,3 +179,21 @@ def test_memory_for_a_batch_serves_smaller_ones(M, k, most, fewer):
         assert not (w == 0xA5).all(), f"N={N}: not split"
         pv, pi = _plain(R, x[:N], k)
         assert torch.equal(v, pv) and torch.equal(i, pi), f"N={N}"
+
+
+@pytest.mark.parametrize("M, k", [(65 * 32768 + 3, 2), (2200003, 10), (2200003, 20), (3000001, 50), (100 * 32768 - 5, 90), (1 << 20, 8)])
+def test_sixteen_merging_wavefronts_with_few_candidates(M, k):
+    # rows of more than 64 lists, and early stopping with few steps: 4, 8 or 16 candidates a lane
+    R = _gpu()
+    g = np.random.default_rng(M + k)
+    x = g.standard_normal((2, M)).astype(np.float32)
+    x[1] = np.round(x[1] * 64) / 64
+    xd = torch.from_numpy(x).cuda()
+    _same(R.rtopk_rowwise_exact(xd, k), oracle.topk_exact(x, k), f"M={M} k={k}")
+    _same(R.rtopk_rowwise_exact_smallest(xd, k), oracle.topk_exact_smallest(x, k), f"M={M} k={k} smallest")
+    for steps in (4, 9, 14):
+        _same(R.rtopk_rowwise(xd, k, steps), oracle.topk_earlystop(x, k, steps), f"M={M} k={k} early {steps}")
+    ev, ei, et = oracle.alg1(x, k, eps_rel=1e-4)
+    got = R.rtopk_rowwise_eps(xd, k, 1e-4, want_iters=True)
+    _same(got, (ev, ei), f"M={M} k={k} eps")
+    assert np.array_equal(got[2].cpu().numpy(), et)
