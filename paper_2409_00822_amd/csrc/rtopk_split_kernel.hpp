@@ -23,7 +23,7 @@
 // latencies, in which few wavefronts share a SIMD and each instruction takes one of them about seven cycles: so every wavefront finds
 // its registers' lists from the heads by itself (a search for each candidate's list through LDS, behind a barrier, took 1 x 671792, k = 80, 41 lists,
 // 13.7 us in all, 12.0 without; 64 x 131072 13.5 and 13.1), the loads are
-// issued together, the fewest of 4, 8, 16 or 40 registers that hold the row's candidates are walked, and exact mode counts each
+// issued together, the fewest of 4, 8, 12, 16 or 40 registers that hold the row's candidates are walked, and exact mode counts each
 // key into a bin once instead of in 10 to 14 steps of a barrier each (one row of 131072 columns, the merge alone: 7.8 -> 4 us).  Kernel
 // time, one workgroup per row -> split with steps -> with bins: 64 x 131072, k = 50: 39.5 -> 19.2 -> 13.5 us; 1 x 131072: 36.5 -> 12.6 ->
 // 8.7; 2048 x 50000, k = 100, registers of one workgroup -> split: 135 -> 88 -> 79; 16 x 2^20, k = 100: 31.0 -> 22.9;
@@ -398,6 +398,13 @@ __device__ __forceinline__ MergeResult merge_candidates(MergeLds<NW>& s, int64_t
   return kMergeDone;
 }
 
+// Registers that a lane of NW merging wavefronts walks when it holds `per` candidates (the fewest that serve: a wavefront issues an instruction in
+// seven cycles, and few share a SIMD here).
+template <int NW>
+__device__ __forceinline__ int registers_walked(int per, bool lists) {
+  return per <= 4 ? 4 : (per <= 8 ? 8 : (lists && NW < 16 && per <= 12 ? 12 : (NW < 16 || per <= kMergeRegs ? kMergeRegs : kMergeRegsBig)));
+}
+
 // One row: its search on the segments' lists, and its selection from them, or, where the search ends on a minimum below
 // the floor, from the row.  Returns false, with nothing written, where the lists do not hold the search.  Called by the
 // whole workgroup; uniform.
@@ -417,17 +424,23 @@ __device__ __forceinline__ bool merge_row(MergeLds<NW>& s, int64_t r, const floa
   const uint2* of_row = lists + r * segments * cap;
   RowClasses rest;
   MergeResult done;
+  constexpr int kMost = NW == 16 ? kMergeRegsBig : kMergeRegs;
   bool by_number = !by_lists;
+  int total;
+  float T0, lo, hi;
   if (!by_number) {  // uniform
     // every wavefront reads the heads, lane s that of segment s: nothing to exchange before the bins
     const SegmentHead h = heads[r * segments + min(lane, segments - 1)];
     const int n = lane < segments ? h.n : 0, regs = (n + kWave - 1) / kWave;
-    const uint32_t upto = wave_inclusive_scan_dpp((uint32_t)regs);
-    const int start = (int)upto - regs, all = __builtin_amdgcn_readlane((int)upto, kWave - 1);
-    float T0, lo, hi, unused;
+    static_assert(kWave * kBigRoom < 1 << 17, "the candidates of 64 lists beside their registers");
+    const uint32_t upto = wave_inclusive_scan_dpp((uint32_t)regs << 17 | (uint32_t)n);
+    const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave - 1);
+    const int start = (int)(upto >> 17) - regs;
+    total = (int)(all & 0x1ffffu);
+    float unused;
     wave_max_and_negmin(h.floor, h.nlo, T0, lo);  // (a lane beyond the last segment repeats it)
     wave_max_and_negmin(h.hi, h.hi, hi, unused);
-    const int per = (all + NW - 1) / NW;
+    const int per = ((int)(all >> 17) + NW - 1) / NW, numbered = (total + NW * kWave - 1) / (NW * kWave);
     auto listed = [&](auto regs_of) -> MergeResult {
       constexpr int KR = decltype(regs_of)::value;
       float key[KR];
@@ -436,9 +449,15 @@ __device__ __forceinline__ bool merge_row(MergeLds<NW>& s, int64_t r, const floa
       __syncthreads();
       return merge_candidates<NW, KR, MODE, NEG, RANK>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters, key, col, per, T0, lo, hi, rest);
     };
-    by_number = per > (NW == 16 ? kMergeRegsBig : kMergeRegs);  // (many short lists: half a register of each may be empty)
+    // (lists of a few more than 64, 128 ... candidates leave most of a register empty: numbered through, fewer may do.  By lists -> the fewer of both, us:
+    // 1 x 10^6, k = 700 29.9 -> 26.8, k = 80 15.4 -> 14.4; 1 x 700000, k = 128 15.6 -> 14.5; 24 x 150000, k = 45 11.6 -> 11.3; 1 x 131072, k = 72 9.1 -> 8.8.)
+    by_number = per > kMost || registers_walked<NW>(per, true) > registers_walked<NW>(numbered, false);
     if (by_number) {
-    } else if (per <= 4) {  // (as few registers as serve: a wavefront issues an instruction in seven cycles, and few share a SIMD here)
+      if (wave == 0) {
+        if (lane < segments) s.first[lane] = (int)(upto & 0x1ffffu) - n;
+        if (lane == 0) s.first[segments] = total;
+      }
+    } else if (per <= 4) {
       done = listed(std::integral_constant<int, 4>());
     } else if (per <= 8) {
       done = listed(std::integral_constant<int, 8>());
@@ -447,41 +466,42 @@ __device__ __forceinline__ bool merge_row(MergeLds<NW>& s, int64_t r, const floa
     } else if (NW < 16 || per <= kMergeRegs) {
       done = listed(std::integral_constant<int, kMergeRegs>());
     } else {
-      done = listed(std::integral_constant<int, NW == 16 ? kMergeRegsBig : kMergeRegs>());
+      done = listed(std::integral_constant<int, kMost>());
+    }
+  } else if (wave == 0) {
+    float fl = -__builtin_inff(), nlo = -__builtin_inff(), top = -__builtin_inff();
+    int before = 0;
+    for (int s0 = 0; s0 < segments; s0 += kWave) {
+      const bool live = s0 + lane < segments;
+      const SegmentHead h = heads[r * segments + (live ? s0 + lane : 0)];
+      const int n = live ? h.n : 0;
+      const uint32_t incl = wave_inclusive_scan_dpp((uint32_t)n);
+      if (live) s.first[s0 + lane] = before + (int)incl - n;
+      before += __builtin_amdgcn_readlane((int)incl, kWave - 1);
+      fl = vmax(fl, h.floor);  // (a lane beyond the last segment repeats the first)
+      nlo = vmax(nlo, h.nlo);
+      top = vmax(top, h.hi);
+    }
+    float a, b, c, unused;
+    wave_max_and_negmin(fl, nlo, a, b);
+    wave_max_and_negmin(top, top, c, unused);
+    if (lane == 0) {
+      s.first[segments] = before;
+      s.total = before;
+      s.bound[0] = a;
+      s.bound[1] = b;
+      s.bound[2] = c;
     }
   }
   if (by_number) {  // uniform
-    if (wave == 0) {
-      float fl = -__builtin_inff(), nlo = -__builtin_inff(), hi = -__builtin_inff();
-      int before = 0;
-      for (int s0 = 0; s0 < segments; s0 += kWave) {
-        const bool live = s0 + lane < segments;
-        const SegmentHead h = heads[r * segments + (live ? s0 + lane : 0)];
-        const int n = live ? h.n : 0;
-        const uint32_t incl = wave_inclusive_scan_dpp((uint32_t)n);
-        if (live) s.first[s0 + lane] = before + (int)incl - n;
-        before += __builtin_amdgcn_readlane((int)incl, kWave - 1);
-        fl = vmax(fl, h.floor);  // (a lane beyond the last segment repeats the first)
-        nlo = vmax(nlo, h.nlo);
-        hi = vmax(hi, h.hi);
-      }
-      float a, b, c, unused;
-      wave_max_and_negmin(fl, nlo, a, b);
-      wave_max_and_negmin(hi, hi, c, unused);
-      if (lane == 0) {
-        s.first[segments] = before;
-        s.total = before;
-        s.bound[0] = a;
-        s.bound[1] = b;
-        s.bound[2] = c;
-      }
-    }
     __syncthreads();
-    const int total = __builtin_amdgcn_readfirstlane(s.total);
-    const float T0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[0])));
-    const float lo = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[1])));
-    const float hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[2])));
-    if (total <= k || total > NW * kWave * (NW == 16 ? kMergeRegsBig : kMergeRegs)) return false;
+    if (!by_lists) {  // uniform
+      total = __builtin_amdgcn_readfirstlane(s.total);
+      T0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[0])));
+      lo = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[1])));
+      hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[2])));
+    }
+    if (total <= k || total > NW * kWave * kMost) return false;
     const int per = (total + NW * kWave - 1) / (NW * kWave);
     auto numbered = [&](auto regs_of) -> MergeResult {
       constexpr int KR = decltype(regs_of)::value;
@@ -497,7 +517,7 @@ __device__ __forceinline__ bool merge_row(MergeLds<NW>& s, int64_t r, const floa
     } else if (NW < 16 || per <= kMergeRegs) {
       done = numbered(std::integral_constant<int, kMergeRegs>());
     } else {
-      done = numbered(std::integral_constant<int, NW == 16 ? kMergeRegsBig : kMergeRegs>());
+      done = numbered(std::integral_constant<int, kMost>());
     }
   }
   if (MODE != kExact && done == kMergeFromRow)  // (latency bound: a barrier per chunk; 16 wavefronts have the registers for four loads each)

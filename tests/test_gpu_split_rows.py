@@ -197,3 +197,26 @@ def test_sixteen_merging_wavefronts_with_few_candidates(M, k):
     got = R.rtopk_rowwise_eps(xd, k, 1e-4, want_iters=True)
     _same(got, (ev, ei), f"M={M} k={k} eps")
     assert np.array_equal(got[2].cpu().numpy(), et)
+
+
+@pytest.mark.parametrize("M, k", [(131072, 72), (150000, 45), (262144, 80), (700000, 16), (700000, 128), (1000000, 80), (1000000, 160),
+                                  (1000000, 700)])
+def test_lists_that_would_fill_more_registers_than_their_candidates(M, k):
+    # lists of a few more than 64, 128 ... candidates: by lists or by number, whichever walks fewer registers, row by row
+    R = _gpu()
+    g = np.random.default_rng(M * 3 + k)
+    x = g.standard_normal((6, M)).astype(np.float32)
+    x[1] = np.round(x[1] * 256) / 256
+    x[2] = g.random(M, dtype=np.float32)
+    x[3, : M // 3] += 2  # most candidates in a third of the lists
+    x[4] = np.sort(x[4])
+    x[5, 7:] = -3e38  # fewer than k keys above the mask
+    xd = torch.from_numpy(x).cuda()
+    _same(R.rtopk_rowwise_exact(xd, k), oracle.topk_exact(x, k), f"M={M} k={k}")
+    _same(R.rtopk_rowwise_exact_smallest(xd, k), oracle.topk_exact_smallest(x, k), f"M={M} k={k} smallest")
+    for steps in (3, 8, 16):
+        _same(R.rtopk_rowwise(xd, k, steps), oracle.topk_earlystop(x, k, steps), f"M={M} k={k} early {steps}")
+    ev, ei, et = oracle.alg1(x, k, eps_rel=1e-5)
+    got = R.rtopk_rowwise_eps(xd, k, 1e-5, want_iters=True)
+    _same(got, (ev, ei), f"M={M} k={k} eps")
+    assert np.array_equal(got[2].cpu().numpy(), et)
