@@ -82,7 +82,7 @@ def test_backward_unaligned_pointers_and_guard_bands():
     g = workloads.normal(N, k, seed=52)
     pad = 1024
     buf = torch.full((N * M + 2 * pad + 1,), 7.5, dtype=torch.float32, device="cuda")
-    out = buf[pad + 1:pad + 1 + N * M].view(N, M)  # 4-byte aligned only: the scalar store path
+    out = buf[pad + 1:pad + 1 + N * M].view(N, M)  # 4-byte aligned only: chunks cut rows, and the first and the last chunk are partial
     R.rtopk_maxk_backward(torch.from_numpy(g).cuda(), torch.from_numpy(idx).cuda(), M, out)
     torch.cuda.synchronize()
     assert np.array_equal(bits(out.cpu().numpy()), bits(oracle.maxk_backward(g, idx, M)))
@@ -171,3 +171,37 @@ def test_backward_at_any_alignment(M, k):
                 got = pairs.cpu().numpy()
                 assert np.array_equal(bits(got[shift:shift + N * k]), bits(want_gather.ravel())), (N, shift, u8)
                 assert (got[:shift] == 7.5).all() and (got[shift + N * k:] == 7.5).all(), "wrote outside the pairs"
+
+
+@pytest.mark.parametrize("N,M,k", [(20011, 251, 31), (60001, 100, 12), (8200, 777, 40), (40003, 250, 100), (140001, 33, 4), (70001, 88, 4),
+                                   (16385, 256, 32), (131077, 256, 5), (65541, 512, 7), (16387, 2048, 3), (18000, 1028, 9), (2100, 2047, 33)])
+def test_backward_of_many_rows(N, M, k):
+    """Chunks of 2048 floats that cut rows, gathers of several rows to a wavefront at every kind of width, several loads of pairs."""
+    import ctypes
+
+    R = _gpu()
+    lib = R.load_library()
+    rng = np.random.default_rng(N + M)
+    first = rng.integers(0, M, (N, 1))
+    step = np.array([s for s in range(1, M + 1) if np.gcd(s, M) == 1])[rng.integers(0, 8 if M > 33 else 3, N)][:, None]
+    idx = ((first + step * np.arange(k)) % M).astype(np.int32)  # distinct, any order
+    g, w = workloads.normal(N, k, M + N), workloads.normal(N, M, M + N + 1)
+    want, want_gather = oracle.maxk_backward(g, idx, M), oracle.maxk_backward_gather(w, idx)
+    gd = torch.from_numpy(g).cuda()
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    args = (ctypes.c_int64(N), ctypes.c_int32(M), ctypes.c_int32(k))
+    for u8 in (False, True) if M <= 256 else (False,):
+        cols = torch.from_numpy(idx.astype(np.uint8) if u8 else idx).cuda()
+        suffix, ptr = "_u8" if u8 else "", lambda t, s: ctypes.c_void_p(t.flatten()[s:].data_ptr())
+        for shift in (0, 3):
+            dense = torch.full((N * M + 96,), 7.5, device="cuda")
+            assert getattr(lib, "rtopk_maxk_backward" + suffix)(ptr(gd, 0), ptr(cols, 0), *args, ptr(dense, 32 + shift), stream) == 0
+            got = dense.cpu().numpy()
+            assert np.array_equal(bits(got[32 + shift:32 + shift + N * M]), bits(want.ravel())), (shift, u8)
+            assert (got[:32 + shift] == 7.5).all() and (got[32 + shift + N * M:] == 7.5).all(), "wrote outside the matrix"
+            dense[shift:shift + N * M] = torch.from_numpy(w.ravel()).cuda()
+            pairs = torch.full((N * k + 96,), 7.5, device="cuda")
+            assert getattr(lib, "rtopk_maxk_backward_gather" + suffix)(ptr(dense, shift), ptr(cols, 0), *args, ptr(pairs, 32 + shift), stream) == 0
+            got = pairs.cpu().numpy()
+            assert np.array_equal(bits(got[32 + shift:32 + shift + N * k]), bits(want_gather.ravel())), (shift, u8)
+            assert (got[:32 + shift] == 7.5).all() and (got[32 + shift + N * k:] == 7.5).all(), "wrote outside the pairs"
