@@ -242,11 +242,16 @@ __global__ void __launch_bounds__(256)
 // ---- host side --------------------------------------------------------------------------------------------
 
 
-// Rows per wavefront of the gather: 8 KiB of LDS, fewer where that would leave compute units with less than eight wavefronts.
+// Rows per wavefront of the gather: up to 8 KiB of LDS, fewer where that would leave compute units with less than four wavefronts (eight -> four, us:
+// 3910 x 256, k = 15, byte columns 3.9 -> 3.3, 9824 x 64, k = 3 3.2 -> 3.0), but a 128-bit load for each lane.  A power of two of them where M is a
+// multiple of four: wavefronts then seldom share a line of the rows, or of the results, which both would read, or write part of (as many as fit
+// -> a power of two, us: 320696 x 88, k = 4 23 rows 24.2 -> 16 rows 20.7; 10^6 x 40, k = 2 51 34.2 -> 32 28.8; 500000 x 100, k = 12 20 43.4 -> 16 41.5;
+// 300000 x 200 10 46.5 -> 8 44.2; 100000 x 400 5 29.5 -> 4 27.8; 2^18 x 640 3 132.8 -> 2 128.6; but odd widths, which share lines in any case: 100000 x 333 6
+// 28.0 -> 4 29.0).
 inline int backward_rows_per_wave(int64_t N, int M) {
-  const int64_t fill = N / 2048;
-  const int rows = kBackwardRowsM / M;
-  return fill >= rows ? rows : (fill < 1 ? 1 : (int)fill);
+  const int most = kBackwardRowsM / M, least = 4 * kWave / M > 1 ? 4 * kWave / M : 1;
+  const int rows = N / 1024 >= most ? most : (N / 1024 > least ? (int)(N / 1024) : least);
+  return M % 4 == 0 ? 1 << (31 - __builtin_clz((unsigned)rows)) : rows;
 }
 
 // f(integral_constant<int, BATCH>) for a wavefront of up to `pairs` pairs.  No more than it has: a load whose lanes are all past the end costs as
