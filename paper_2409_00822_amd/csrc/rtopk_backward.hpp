@@ -159,13 +159,20 @@ __global__ void __launch_bounds__(256)
 
 // ---- gather: the dense gradient row is read once, through LDS, with 128-bit loads ------------------------
 //
-// One wavefront per `rows` rows, at most kBackwardRowsM floats in all: 128-bit loads (from any 4-byte boundary, see load_group), four per lane at a
-// time (eight: 2^20 x 256, k = 32 225 -> 219 us, 2^18 x 512 111.5 -> 109.2), then the saved columns' entries are read from LDS, and the results, again
-// contiguous in the output, are stored coalesced.  FOURS: M is a multiple of four, so that nothing is left beside the 128-bit loads.
-template <typename IdxT, int BATCH, bool FOURS>
+// One wavefront per `rows` rows, at most kBackwardRowsM floats in all: 128-bit loads (from any 4-byte boundary, see load_group), `PART` per lane at a
+// time, then the saved columns' entries are read from LDS, and the results, again contiguous in the output, are stored coalesced.
+// KIND: what rows of M columns are.  kAnyRows: four loads at a time (eight: 2^20 x 256, k = 32 225 -> 219 us, 2^18 x 512 111.5 -> 109.2; two, for
+// rows that share lines: 2^20 x 251, k = 31 228 -> 230, 2^18 x 777 155 -> 163).  kFours: M is a multiple of four, so that nothing is left beside the
+// 128-bit loads.  kWholeParts: of 256, where a full wavefront's loads are whole, and wavefronts enough to hide more of them one behind the other: two
+// at a time, without a look at the end (four -> two, us: 2^20 x 256, k = 32 210.7 -> 206.2, byte columns 193.8 -> 192.1, k = 128 353.8 -> 350.5, 2^18 x 1024
+// 210.4 -> 206.5, 2^17 x 2048 193.0 -> 193.2; but 20000 x 256 6.2 -> 6.3, 300 x 2048 3.3 -> 4.0).
+enum GatherRows : int { kAnyRows, kFours, kWholeParts };
+template <typename IdxT, int BATCH, int KIND>
 __global__ void __launch_bounds__(kWave)
     maxk_gather_rows_kernel(const float* __restrict__ grad_out, const IdxT* __restrict__ idx, int64_t N, int M, int k, int rows,
                             uint32_t by, float* __restrict__ grad_vals) {
+  constexpr bool FOURS = KIND != kAnyRows;
+  constexpr int PART = KIND == kWholeParts ? 2 : 4;
   extern __shared__ __attribute__((aligned(16))) float s_rows[];  // [rows * M], in whole quads
   typedef float f4 __attribute__((ext_vector_type(4)));
   typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
@@ -185,18 +192,21 @@ __global__ void __launch_bounds__(kWave)
   float rest = 0.0f;
   if (!FOURS && lane < total - 4 * quads) rest = src[4 * quads + lane];
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    if (half * (kQuads / 2) * kWave < quads) {  // uniform
-      f4 v[kQuads / 2];
+  for (int part = 0; part < kQuads; part += PART) {
+    if (part * kWave < quads) {  // uniform
+      f4 v[PART];
+      const bool whole = KIND == kWholeParts && (part + PART) * kWave <= quads;  // uniform
 #pragma unroll
-      for (int i = 0; i < kQuads / 2; ++i)
-        v[i] = __builtin_nontemporal_load(reinterpret_cast<const f4_any*>(src) + min((half * (kQuads / 2) + i) * kWave + lane, quads - 1));
+      for (int i = 0; i < PART; ++i) {
+        const int q = (part + i) * kWave + lane;
+        v[i] = __builtin_nontemporal_load(reinterpret_cast<const f4_any*>(src) + (whole ? q : min(q, quads - 1)));
+      }
 #pragma unroll
-      for (int i = 0; i < kQuads / 2; ++i) asm volatile("" : "+v"(v[i]));  // (or the loads move to their uses)
+      for (int i = 0; i < PART; ++i) asm volatile("" : "+v"(v[i]));  // (or the loads move to their uses)
 #pragma unroll
-      for (int i = 0; i < kQuads / 2; ++i) {
-        const int q = (half * (kQuads / 2) + i) * kWave + lane;
-        if (q < quads) reinterpret_cast<f4*>(s_rows)[q] = v[i];
+      for (int i = 0; i < PART; ++i) {
+        const int q = (part + i) * kWave + lane;
+        if (whole || q < quads) reinterpret_cast<f4*>(s_rows)[q] = v[i];
       }
     }
   }
@@ -300,8 +310,10 @@ hipError_t launch_gather(const float* gout, const IdxT* idx, int64_t N, int M, i
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   return by_pairs(rows * k, [&](auto batch) {
     constexpr int B = decltype(batch)::value;
-    return launch_kernel(M % 4 == 0 ? maxk_gather_rows_kernel<IdxT, B, true> : maxk_gather_rows_kernel<IdxT, B, false>, dim3((unsigned)blocks),
-                         dim3(kWave), ((size_t)rows * M + 3) / 4 * 16, stream, gout, idx, N, M, k, rows, divisor(k), gv);
+    const auto kernel = M % 256 == 0 && blocks >= 16384 ? maxk_gather_rows_kernel<IdxT, B, kWholeParts>
+                        : M % 4 == 0                    ? maxk_gather_rows_kernel<IdxT, B, kFours>
+                                                        : maxk_gather_rows_kernel<IdxT, B, kAnyRows>;
+    return launch_kernel(kernel, dim3((unsigned)blocks), dim3(kWave), ((size_t)rows * M + 3) / 4 * 16, stream, gout, idx, N, M, k, rows, divisor(k), gv);
   });
 }
 
