@@ -166,8 +166,11 @@ __global__ void __launch_bounds__(256)
 // 128-bit loads.  kWholeParts: of 256, where a full wavefront's loads are whole, and wavefronts enough to hide more of them one behind the other: two
 // at a time, without a look at the end (four -> two, us: 2^20 x 256, k = 32 210.7 -> 206.2, byte columns 193.8 -> 192.1, k = 128 353.8 -> 350.5, 2^18 x 1024
 // 210.4 -> 206.5, 2^17 x 2048 193.0 -> 193.2; but 20000 x 256 6.2 -> 6.3, 300 x 2048 3.3 -> 4.0).
+// FIRST: the columns are loaded before the rows, for launches of few wavefronts, whose latencies stand alone (last -> first, us: 3910 x 256, k = 15, byte
+// columns 3.3 -> 2.9, 20000 x 64 3.2 -> 2.8, 1506 x 1028 4.0 -> 3.5, 48008 x 208 9.9 -> 9.1, 20000 x 256 6.25 -> 6.0); with many, last (first, or between the parts,
+// 2^20 x 256 210.4 -> 212 to 213, 2^20 x 251 226 -> 229).
 enum GatherRows : int { kAnyRows, kFours, kWholeParts };
-template <typename IdxT, int BATCH, int KIND>
+template <typename IdxT, int BATCH, int KIND, bool FIRST>
 __global__ void __launch_bounds__(kWave)
     maxk_gather_rows_kernel(const float* __restrict__ grad_out, const IdxT* __restrict__ idx, int64_t N, int M, int k, int rows,
                             uint32_t by, float* __restrict__ grad_vals) {
@@ -189,6 +192,7 @@ __global__ void __launch_bounds__(kWave)
 #pragma unroll
     for (int i = 0; i < BATCH; ++i) c[i] = (int)__builtin_nontemporal_load(ix + min(p0 + i * kWave + lane, pairs - 1));
   };
+  if constexpr (FIRST) load(0);
   float rest = 0.0f;
   if (!FOURS && lane < total - 4 * quads) rest = src[4 * quads + lane];
 #pragma unroll
@@ -210,7 +214,7 @@ __global__ void __launch_bounds__(kWave)
       }
     }
   }
-  load(0);
+  if constexpr (!FIRST) load(0);
   if (!FOURS && lane < total - 4 * quads) s_rows[4 * quads + lane] = rest;
   wavefront_lds_order();
   for (int p0 = 0;;) {
@@ -310,9 +314,10 @@ hipError_t launch_gather(const float* gout, const IdxT* idx, int64_t N, int M, i
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   return by_pairs(rows * k, [&](auto batch) {
     constexpr int B = decltype(batch)::value;
-    const auto kernel = M % 256 == 0 && blocks >= 16384 ? maxk_gather_rows_kernel<IdxT, B, kWholeParts>
-                        : M % 4 == 0                    ? maxk_gather_rows_kernel<IdxT, B, kFours>
-                                                        : maxk_gather_rows_kernel<IdxT, B, kAnyRows>;
+    const auto kernel = blocks < 16384 ? (M % 4 == 0 ? maxk_gather_rows_kernel<IdxT, B, kFours, true> : maxk_gather_rows_kernel<IdxT, B, kAnyRows, true>)
+                        : M % 256 == 0 ? maxk_gather_rows_kernel<IdxT, B, kWholeParts, false>
+                        : M % 4 == 0   ? maxk_gather_rows_kernel<IdxT, B, kFours, false>
+                                       : maxk_gather_rows_kernel<IdxT, B, kAnyRows, false>;
     return launch_kernel(kernel, dim3((unsigned)blocks), dim3(kWave), ((size_t)rows * M + 3) / 4 * 16, stream, gout, idx, N, M, k, rows, divisor(k), gv);
   });
 }
