@@ -159,23 +159,19 @@ __global__ void __launch_bounds__(256)
 
 // ---- gather: the dense gradient row is read once, through LDS, with 128-bit loads ------------------------
 //
-// One wavefront per `rows` rows, at most kBackwardRowsM floats in all: 128-bit loads (from any 4-byte boundary, see load_group), `PART` per lane at a
-// time, then the saved columns' entries are read from LDS, and the results, again contiguous in the output, are stored coalesced.
-// KIND: what rows of M columns are.  kAnyRows: four loads at a time (eight: 2^20 x 256, k = 32 225 -> 219 us, 2^18 x 512 111.5 -> 109.2; two, for
-// rows that share lines: 2^20 x 251, k = 31 228 -> 230, 2^18 x 777 155 -> 163).  kFours: M is a multiple of four, so that nothing is left beside the
-// 128-bit loads.  kWholeParts: of 256, where a full wavefront's loads are whole, and wavefronts enough to hide more of them one behind the other: two
-// at a time, without a look at the end (four -> two, us: 2^20 x 256, k = 32 210.7 -> 206.2, byte columns 193.8 -> 192.1, k = 128 353.8 -> 350.5, 2^18 x 1024
-// 210.4 -> 206.5, 2^17 x 2048 193.0 -> 193.2; but 20000 x 256 6.2 -> 6.3, 300 x 2048 3.3 -> 4.0).
-// FIRST: the columns are loaded before the rows, for launches of few wavefronts, whose latencies stand alone (last -> first, us: 3910 x 256, k = 15, byte
-// columns 3.3 -> 2.9, 20000 x 64 3.2 -> 2.8, 1506 x 1028 4.0 -> 3.5, 48008 x 208 9.9 -> 9.1, 20000 x 256 6.25 -> 6.0); with many, last (first, or between the parts,
-// 2^20 x 256 210.4 -> 212 to 213, 2^20 x 251 226 -> 229).
-enum GatherRows : int { kAnyRows, kFours, kWholeParts };
-template <typename IdxT, int BATCH, int KIND, bool FIRST>
-__global__ void __launch_bounds__(kWave)
-    maxk_gather_rows_kernel(const float* __restrict__ grad_out, const IdxT* __restrict__ idx, int64_t N, int M, int k, int rows,
-                            uint32_t by, float* __restrict__ grad_vals) {
-  constexpr bool FOURS = KIND != kAnyRows;
-  constexpr int PART = KIND == kWholeParts ? 2 : 4;
+// One wavefront per `rows` rows, at most kBackwardRowsM floats in all: 128-bit loads (from any 4-byte boundary, see load_group), four per lane at a
+// time (eight: 2^20 x 256, k = 32 225 -> 219 us, 2^18 x 512 111.5 -> 109.2), then the saved columns' entries are read from LDS, and the results, again
+// contiguous in the output, are stored coalesced.  FOURS: M is a multiple of four, so that nothing is left beside the 128-bit loads.
+// twos (with rows of a multiple of 256 columns and many wavefronts): a full wavefront's rows are loaded two quads per lane at a time, without a look at
+// the end (four -> two, us: 2^20 x 256, k = 32 210.7 -> 206.2, byte columns 193.8 -> 192.1, k = 128 353.8 -> 350.5, 2^18 x 1024 210.4 -> 206.5, 2^17 x 2048 193.0 ->
+// 193.2; but 2^20 x 64, k = 8 54.0 -> 55.9, byte columns 50.4 -> 53.7, rows that share lines, 2^20 x 251 228 -> 230, 2^18 x 777 155 -> 163, and few
+// wavefronts, 300 x 2048 3.3 -> 4.0).
+// FEW: a launch of few wavefronts, whose latencies stand alone: the columns are loaded before the rows (last -> first, us: 3910 x 256, k = 15, byte columns
+// 3.3 -> 2.9, 20000 x 64 3.2 -> 2.8, 1506 x 1028 4.0 -> 3.5, 48008 x 208 9.9 -> 9.1, 20000 x 256 6.25 -> 6.0; with many, first, or between the rows' loads, 2^20 x
+// 256 210.4 -> 212 to 213, 2^20 x 251 226 -> 229; as a flag to one kernel small launches take 0.03 to 0.05 us more).
+template <typename IdxT, int BATCH, bool FOURS, bool FEW>
+__device__ __forceinline__ void gather_rows(const float* __restrict__ grad_out, const IdxT* __restrict__ idx, int64_t N, int M, int k, int rows,
+                                            int twos, uint32_t by, float* __restrict__ grad_vals) {
   extern __shared__ __attribute__((aligned(16))) float s_rows[];  // [rows * M], in whole quads
   typedef float f4 __attribute__((ext_vector_type(4)));
   typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
@@ -192,29 +188,37 @@ __global__ void __launch_bounds__(kWave)
 #pragma unroll
     for (int i = 0; i < BATCH; ++i) c[i] = (int)__builtin_nontemporal_load(ix + min(p0 + i * kWave + lane, pairs - 1));
   };
-  if constexpr (FIRST) load(0);
+  if constexpr (FEW) load(0);
   float rest = 0.0f;
   if (!FOURS && lane < total - 4 * quads) rest = src[4 * quads + lane];
+  auto copy = [&](auto at_once, auto full) {  // full: the rows fill the image
+    constexpr int PART = decltype(at_once)::value;
+    constexpr bool FULL = decltype(full)::value;
 #pragma unroll
-  for (int part = 0; part < kQuads; part += PART) {
-    if (part * kWave < quads) {  // uniform
-      f4 v[PART];
-      const bool whole = KIND == kWholeParts && (part + PART) * kWave <= quads;  // uniform
+    for (int part = 0; part < kQuads; part += PART) {
+      if (FULL || part * kWave < quads) {  // uniform
+        f4 v[PART];
 #pragma unroll
-      for (int i = 0; i < PART; ++i) {
-        const int q = (part + i) * kWave + lane;
-        v[i] = __builtin_nontemporal_load(reinterpret_cast<const f4_any*>(src) + (whole ? q : min(q, quads - 1)));
-      }
+        for (int i = 0; i < PART; ++i) {
+          const int q = (part + i) * kWave + lane;
+          v[i] = __builtin_nontemporal_load(reinterpret_cast<const f4_any*>(src) + (FULL ? q : min(q, quads - 1)));
+        }
 #pragma unroll
-      for (int i = 0; i < PART; ++i) asm volatile("" : "+v"(v[i]));  // (or the loads move to their uses)
+        for (int i = 0; i < PART; ++i) asm volatile("" : "+v"(v[i]));  // (or the loads move to their uses)
 #pragma unroll
-      for (int i = 0; i < PART; ++i) {
-        const int q = (part + i) * kWave + lane;
-        if (whole || q < quads) reinterpret_cast<f4*>(s_rows)[q] = v[i];
+        for (int i = 0; i < PART; ++i) {
+          const int q = (part + i) * kWave + lane;
+          if (FULL || q < quads) reinterpret_cast<f4*>(s_rows)[q] = v[i];
+        }
       }
     }
+  };
+  if (FOURS && !FEW && twos && quads == kQuads * kWave) {  // uniform
+    copy(std::integral_constant<int, 2>(), std::true_type());
+  } else {
+    copy(std::integral_constant<int, 4>(), std::false_type());
   }
-  if constexpr (!FIRST) load(0);
+  if constexpr (!FEW) load(0);
   if (!FOURS && lane < total - 4 * quads) s_rows[4 * quads + lane] = rest;
   wavefront_lds_order();
   for (int p0 = 0;;) {
@@ -237,6 +241,21 @@ __global__ void __launch_bounds__(kWave)
     load(p0);
   }
 }
+
+template <typename IdxT, int BATCH, bool FOURS>
+__global__ void __launch_bounds__(kWave)
+    maxk_gather_rows_kernel(const float* __restrict__ grad_out, const IdxT* __restrict__ idx, int64_t N, int M, int k, int rows,
+                            int twos, uint32_t by, float* __restrict__ grad_vals) {
+  gather_rows<IdxT, BATCH, FOURS, false>(grad_out, idx, N, M, k, rows, twos, by, grad_vals);
+}
+namespace few {
+template <typename IdxT, int BATCH, bool FOURS>
+__global__ void __launch_bounds__(kWave)
+    maxk_gather_rows_kernel(const float* __restrict__ grad_out, const IdxT* __restrict__ idx, int64_t N, int M, int k, int rows,
+                            int twos, uint32_t by, float* __restrict__ grad_vals) {
+  gather_rows<IdxT, BATCH, FOURS, true>(grad_out, idx, N, M, k, rows, twos, by, grad_vals);
+}
+}  // namespace few
 
 // ---- gather, wide rows: the saved columns are read straight from memory ---------------------------------
 // (k scattered 4-byte reads per row; for k << M this touches far less than the whole row.)
@@ -314,11 +333,11 @@ hipError_t launch_gather(const float* gout, const IdxT* idx, int64_t N, int M, i
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   return by_pairs(rows * k, [&](auto batch) {
     constexpr int B = decltype(batch)::value;
-    const auto kernel = blocks < 16384 ? (M % 4 == 0 ? maxk_gather_rows_kernel<IdxT, B, kFours, true> : maxk_gather_rows_kernel<IdxT, B, kAnyRows, true>)
-                        : M % 256 == 0 ? maxk_gather_rows_kernel<IdxT, B, kWholeParts, false>
-                        : M % 4 == 0   ? maxk_gather_rows_kernel<IdxT, B, kFours, false>
-                                       : maxk_gather_rows_kernel<IdxT, B, kAnyRows, false>;
-    return launch_kernel(kernel, dim3((unsigned)blocks), dim3(kWave), ((size_t)rows * M + 3) / 4 * 16, stream, gout, idx, N, M, k, rows, divisor(k), gv);
+    const bool many = blocks >= 16384;  // (2^20 x 256 has 131072, 48008 x 208 6001: see gather_rows)
+    const auto kernel = M % 4 == 0 ? (many ? maxk_gather_rows_kernel<IdxT, B, true> : few::maxk_gather_rows_kernel<IdxT, B, true>)
+                                   : (many ? maxk_gather_rows_kernel<IdxT, B, false> : few::maxk_gather_rows_kernel<IdxT, B, false>);
+    return launch_kernel(kernel, dim3((unsigned)blocks), dim3(kWave), ((size_t)rows * M + 3) / 4 * 16, stream, gout, idx, N, M, k, rows,
+                         many && M % 256 == 0 ? 1 : 0, divisor(k), gv);
   });
 }
 
