@@ -68,7 +68,7 @@ int run(const void* in, int64_t N, int32_t M, int32_t k, int32_t max_iter, float
   a.stream = static_cast<hipStream_t>(stream);
 
   const bool plain = dtype == rtopk::kF32 && !smallest && mode != rtopk::kEps;
-  const rtopk::Shape sh = rtopk::layout_of_call(N, M, k, dtype, mode, max_iter, plain, false);
+  const rtopk::Shape sh = rtopk::layout_of_call(N, M, k, dtype, mode, max_iter, false);
   hipError_t err;
   if (scratch && dtype == rtopk::kF32 && !u8) {
     const rtopk::Split split = rtopk::split_for(N, M, k, mode, max_iter, scratch_bytes);
@@ -221,7 +221,7 @@ int rtopk_maxk_dense(const float* in, int64_t N, int32_t M, int32_t k, int32_t m
   a.max_iter = max_iter < 0 ? 0 : (max_iter > rtopk::kMaxIterClamp ? rtopk::kMaxIterClamp : max_iter);
   a.out_vals = out;
   a.stream = static_cast<hipStream_t>(stream);
-  const rtopk::Shape sh = rtopk::layout_of_call(N, M, k, rtopk::kF32, mode, a.max_iter, true, true);
+  const rtopk::Shape sh = rtopk::layout_of_call(N, M, k, rtopk::kF32, mode, a.max_iter, true);
   hipError_t err;
   if (sh.family == rtopk::kFamBlock) {
     err = rtopk::launch_block_dense(sh.g, sh.ng, sh.w, mode, a);

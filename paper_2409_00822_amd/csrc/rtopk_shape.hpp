@@ -85,9 +85,8 @@ inline int pick_ng_h8(int M) {
 // Wavefronts per row of the workgroup-per-row kernel: a lane holds up to 64 values.
 inline int block_waves(int M) { return M <= 16384 ? 4 : (M <= 32768 ? 8 : 16); }
 
-// The layout of a call.  dtype: element type of the rows; plain: fp32 rows, the k largest, Algorithm 2 or exact mode; dense: the
-// dense-output form (fp32) (neither makes a difference).  Requires 1 <= M <= kMaxM (kMaxBlockM for 16-bit rows and the dense form).
-inline Shape kernel_layout(int M, int dtype, bool /*plain*/, bool /*dense*/) {
+// The layout of rows of M columns.  dtype: their element type.  Requires 1 <= M <= kMaxM (kMaxBlockM for 16-bit rows and the dense-output form).
+inline Shape kernel_layout(int M, int dtype) {
   Shape s{};
   s.w = 1;
   if (M > kMaxBlockM) {
@@ -149,8 +148,8 @@ inline int64_t workgroup_rows(int M, int k, bool half, int mode, bool dense) {
   return M > 1536 && k >= 100 && mode == kExact && !half && !dense ? 1024 : 0;
 }
 // The layout of a call of N rows: kernel_layout(), but for these (how the workgroup then searches: block_search).
-inline Shape layout_of_call(int64_t N, int M, int k, int dtype, int mode, int max_iter, bool plain, bool dense) {
-  Shape s = kernel_layout(M, dtype, plain, dense);
+inline Shape layout_of_call(int64_t N, int M, int k, int dtype, int mode, int max_iter, bool dense) {
+  Shape s = kernel_layout(M, dtype);
   if (M <= kMaxWaveM && k <= 256 && k < M && (mode != kEarly || max_iter >= 5) &&
       N <= workgroup_rows(M, k, dtype != kF32, mode, dense)) {
     s.family = kFamBlock;
@@ -230,8 +229,7 @@ inline bool lists_hold(int M, int k, int w, int E, bool longer) {
 }
 
 // The search of a call whose layout s is a workgroup's.  N, eps_rel: what the precision-bounded mode goes by besides.
-inline int block_search(const Shape& s, int M, int k, int dtype, int mode, int max_iter, bool dense, int64_t N = 1 << 20,
-                        float eps_rel = 0.0f) {
+inline int block_search(const Shape& s, int M, int k, int dtype, int mode, int max_iter, bool dense, int64_t N, float eps_rel) {
   const int E = s.values();
   // Algorithm 2 with few steps ends on a threshold far below the k-th key, which the lists do not reach: the search
   // is then wasted, and with 16 wavefronts the row is read again (50000 columns, k = 256, four steps: 134 us
@@ -262,8 +260,8 @@ constexpr int block_kernels(int E, int w, int mode, bool dense, bool half) {
   return E == 32 || dense ? (E == 16 && mode != kExact ? 0 : kSearchLists) : 0;
 }
 
-// True when (g, ng, w) is a layout of its family's lists above.  `plain` and `dense` as above.
-inline bool instantiated(const Shape& s, int dtype, bool /*plain*/, bool dense) {
+// True when (g, ng, w) is a layout of its family's lists above.  dense: in the dense-output form.
+inline bool instantiated(const Shape& s, int dtype, bool dense) {
   bool small = false, g4 = false, h8 = false;
 #define X(G, NG) small = small || (s.g == G && s.ng == NG);
   RTOPK_LAYOUT_LIST_SMALL(X)

@@ -7,7 +7,7 @@
 //   2. brute force (a stable sort written out here) against the oracle's exact mode, Algorithm 1 at
 //      epsilon = 0 and the k-smallest variant on tiny tie-heavy rows from the sanitized generator;
 //   3. the layout that is launched for every row width 1..65536 (and a sample of the streamed widths up to
-//      2^24), every element type, both kernel variants and the dense form: it must be compiled, hold the row and
+//      2^24), every element type and the dense form: it must be compiled, hold the row and
 //      be no wider than its kernels take for granted;
 //   4. how rows are spread over several workgroups, over widths, k, row counts, modes and steps: segments, lists and
 //      scratch memory within what the kernels and the merge hold, and what is lent for a batch enough for smaller ones.
@@ -157,40 +157,36 @@ static long run_shape_sweep() {
   long n = 0;
   for (int M = 1; M <= rtopk::kMaxBlockM; ++M) {
     for (int dtype : {rtopk::kF32, rtopk::kF16, rtopk::kBF16}) {
-      for (int plain = 0; plain <= (dtype == rtopk::kF32 ? 1 : 0); ++plain) {
-        for (int dense = 0; dense <= (dtype == rtopk::kF32 ? 1 : 0); ++dense) {
-          const rtopk::Shape s = rtopk::kernel_layout(M, dtype, plain != 0, dense != 0);
-          CHECK(rtopk::instantiated(s, dtype, plain != 0, dense != 0), "M=%d dtype=%d plain=%d dense=%d: (%d,%d,%d) family %d not compiled",
-                M, dtype, plain, dense, s.g, s.ng, s.w, s.family);
-          CHECK(s.capacity() >= M, "M=%d: layout (%d,%d,%d) holds only %d", M, s.g, s.ng, s.w, s.capacity());
-          CHECK(s.full == (s.g != 0 && s.capacity() == M), "M=%d: full flag", M);
-          CHECK((s.w == 1) == (M <= rtopk::kMaxWaveM), "M=%d: wavefronts per row %d", M, s.w);
-          CHECK(s.w == 1 ? s.values() <= 128 : s.values() <= 64, "M=%d: %d values per lane", M, s.values());
-          // the vector loads stay inside the row, and the groups that the kernels take for whole are: up to 512
-          // columns the row fills all but the last value of a lane, beyond them no shorter layout of the list holds it
-          CHECK(M >= (s.g == 0 ? 4 : s.g), "M=%d: narrower than a load of %d", M, s.g);
-          if (M <= 512) {
-            CHECK(s.values() == (M + 63) / 64, "M=%d: %d values per lane", M, s.values());
-          } else if (s.w == 1) {
-            rtopk::Shape less = s;
-            while (--less.ng > 0 && !rtopk::instantiated(less, dtype, plain != 0, dense != 0)) {
-            }
-            CHECK(less.ng == 0 || less.capacity() < M, "M=%d: (%d,%d) would do", M, less.g, less.ng);
-          } else {
-            CHECK(64 * s.w * s.values() / 2 < M, "M=%d: (%d,%d,%d) is half empty", M, s.g, s.ng, s.w);
+      for (int dense = 0; dense <= (dtype == rtopk::kF32 ? 1 : 0); ++dense) {
+        const rtopk::Shape s = rtopk::kernel_layout(M, dtype);
+        CHECK(rtopk::instantiated(s, dtype, dense != 0), "M=%d dtype=%d dense=%d: (%d,%d,%d) family %d not compiled",
+              M, dtype, dense, s.g, s.ng, s.w, s.family);
+        CHECK(s.capacity() >= M, "M=%d: layout (%d,%d,%d) holds only %d", M, s.g, s.ng, s.w, s.capacity());
+        CHECK(s.full == (s.g != 0 && s.capacity() == M), "M=%d: full flag", M);
+        CHECK((s.w == 1) == (M <= rtopk::kMaxWaveM), "M=%d: wavefronts per row %d", M, s.w);
+        CHECK(s.w == 1 ? s.values() <= 128 : s.values() <= 64, "M=%d: %d values per lane", M, s.values());
+        // the vector loads stay inside the row, and the groups that the kernels take for whole are: up to 512
+        // columns the row fills all but the last value of a lane, beyond them no shorter layout of the list holds it
+        CHECK(M >= (s.g == 0 ? 4 : s.g), "M=%d: narrower than a load of %d", M, s.g);
+        if (M <= 512) {
+          CHECK(s.values() == (M + 63) / 64, "M=%d: %d values per lane", M, s.values());
+        } else if (s.w == 1) {
+          rtopk::Shape less = s;
+          while (--less.ng > 0 && !rtopk::instantiated(less, dtype, dense != 0)) {
           }
-          ++n;
+          CHECK(less.ng == 0 || less.capacity() < M, "M=%d: (%d,%d) would do", M, less.g, less.ng);
+        } else {
+          CHECK(64 * s.w * s.values() / 2 < M, "M=%d: (%d,%d,%d) is half empty", M, s.g, s.ng, s.w);
         }
+        ++n;
       }
     }
   }
   // beyond the widest row a workgroup holds: fp32 rows are streamed
   for (int64_t M = rtopk::kMaxBlockM + 1; M <= rtopk::kMaxM; M += (M < 70000 ? 1 : 9973)) {
-    for (int plain = 0; plain <= 1; ++plain) {
-      const rtopk::Shape s = rtopk::kernel_layout((int)M, rtopk::kF32, plain != 0, false);
-      CHECK(s.family == rtopk::kFamStream && rtopk::instantiated(s, rtopk::kF32, plain != 0, false), "M=%ld: not streamed", (long)M);
-      ++n;
-    }
+    const rtopk::Shape s = rtopk::kernel_layout((int)M, rtopk::kF32);
+    CHECK(s.family == rtopk::kFamStream && rtopk::instantiated(s, rtopk::kF32, false), "M=%ld: not streamed", (long)M);
+    ++n;
   }
   return n;
 }

@@ -21,10 +21,9 @@ int main() {
             for (int dense = 0; dense < (dtype == kF32 && mode != kEps ? 2 : 1); ++dense)
               for (int steps = 4; steps < 9; steps += 4) {
                 if (k > M || ((dtype != kF32 || dense) && M > kMaxBlockM)) continue;
-                const bool plain = dtype == kF32 && mode != kEps;
-                const Shape a = kernel_layout(M, dtype, plain, dense), b = layout_of_call(N, M, k, dtype, mode, steps, plain, dense);
+                const Shape a = kernel_layout(M, dtype), b = layout_of_call(N, M, k, dtype, mode, steps, dense);
                 const bool same = a.family == b.family && a.g == b.g && a.ng == b.ng && a.w == b.w && a.full == b.full;
-                if (!instantiated(b, dtype, plain, dense) || (b.family != kFamStream && b.capacity() < M)) ++bad;
+                if (!instantiated(b, dtype, dense) || (b.family != kFamStream && b.capacity() < M)) ++bad;
                 if (b.full != (b.g != 0 && b.family != kFamStream && M == b.capacity())) ++bad;
                 if (same) continue;
                 const bool lists = M > 1536 && M <= kMaxWaveM && k <= filter_max_k(4) && b.w == 4 && (mode != kEarly || steps >= 5);
@@ -50,6 +49,7 @@ def test_layout_of_every_call(tmp_path):
 
 
 SEARCHES = r"""
+#include <initializer_list>
 #include <stdio.h>
 #include "rtopk_shape.hpp"
 using namespace rtopk;
@@ -62,15 +62,17 @@ int main() {
       for (int k = 1; k <= 1200 && k <= M; k += 17)
         for (int half = 0; half < 2; ++half)
           for (int mode = 0; mode < (half ? 2 : 3); ++mode)
-            for (int form = 0; form < (half || mode == kEps ? 1 : 3); ++form)  // pairs, dense, the k smallest
+            for (int form = 0; form < (half || mode == kEps ? 1 : 2); ++form)  // pairs, dense
               for (int steps = 4; steps < 9; steps += 4) {
-                const bool dense = form == 1, plain = !half && mode != kEps && form != 2;
+                const bool dense = form == 1;
                 const int dtype = half ? kBF16 : kF32;
-                const Shape s = layout_of_call(N, M, k, dtype, mode, steps, plain, dense);
+                const Shape s = layout_of_call(N, M, k, dtype, mode, steps, dense);
                 if (s.family != kFamBlock) continue;
-                const int search = block_search(s, M, k, dtype, mode, steps, dense);
-                asked[half][mode][dense][s.values() / 4][s.w] |= search;
-                if ((block_kernels(s.values(), s.w, mode, dense, half) & search) == 0) ++bad;
+                for (float eps : {0.0f, 1e-6f, 1e-2f}) {
+                  const int search = block_search(s, M, k, dtype, mode, steps, dense, N, eps);
+                  asked[half][mode][dense][s.values() / 4][s.w] |= search;
+                  if ((block_kernels(s.values(), s.w, mode, dense, half) & search) == 0) ++bad;
+                }
               }
   for (int half = 0; half < 2; ++half)
     for (int mode = 0; mode < 3; ++mode)
@@ -84,7 +86,7 @@ int main() {
             s.w = w;
             const int dtype = half ? kBF16 : kF32;
             if ((half && (dense || mode == kEps || e % 2)) || (dense && mode == kEps)) continue;
-            if (!instantiated(s, dtype, mode != kEps, dense) && !instantiated(s, dtype, false, dense)) continue;
+            if (!instantiated(s, dtype, dense)) continue;
             const int compiled = block_kernels(4 * e, w, mode, dense, half);
             for (int bit = 1; bit < 8; bit <<= 1) {
               kernels += (compiled & bit) != 0;

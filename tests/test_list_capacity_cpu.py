@@ -16,14 +16,16 @@ using namespace rtopk;
 int main() {
   long bad = 0, lists = 0, longer = 0, rows = 0;
   for (int M = 1; M <= kMaxBlockM; M += M < 8400 ? (M < 1500 ? 499 : 17) : 611)
-    for (int64_t N : {(int64_t)512, (int64_t)4096, (int64_t)100000})
+    for (int64_t N : {(int64_t)64, (int64_t)512, (int64_t)4096, (int64_t)100000})
       for (int k = 1; k <= 1100 && k <= M; k += k < 40 ? 13 : 31)
         for (int dtype : {(int)kF32, (int)kBF16})
           for (int mode = 0; mode < (dtype == kF32 ? 3 : 2); ++mode)
-            for (int dense = 0; dense < (dtype == kF32 && mode != kEps ? 2 : 1); ++dense) {
-              const Shape s = layout_of_call(N, M, k, dtype, mode, 8, dtype == kF32 && mode != kEps, dense);
+            for (int form = 0; form < (dtype == kF32 ? 2 : 1); ++form) {  // pairs, and the dense form or a small precision
+              const bool dense = form == 1 && mode != kEps;
+              const float eps = form == 1 ? 1e-6f : 1e-2f;
+              const Shape s = layout_of_call(N, M, k, dtype, mode, 8, dense);
               if (s.family != kFamBlock) continue;
-              const int search = block_search(s, M, k, dtype, mode, 8, dense), E = s.values();
+              const int search = block_search(s, M, k, dtype, mode, 8, dense, N, eps), E = s.values();
               // as many values per lane as fill twelve loads or more: the lists wherever k is within their limit
               if (E >= 48 && (search == kSearchLists) != (k <= filter_max_k(s.w))) ++bad;
               if (search == kSearchRow) {

@@ -34,5 +34,5 @@ def test_oracle_generator_and_shape_classification_under_asan_ubsan(tmp_path):
     # the sweep really covered every width, the traces and the brute-force rows
     words = run.stdout.replace(",", " ").split()
     assert int(words[words.index("traces") + 1]) >= 16
-    assert int(words[words.index("shapes") + 1]) >= 65536 * 6
+    assert int(words[words.index("shapes") + 1]) >= 65536 * 4  # fp32 and its dense form, half, bfloat16
     assert int(words[words.index("splits") + 1]) > 100000
