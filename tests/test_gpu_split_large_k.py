@@ -56,8 +56,11 @@ int main() {
   for (int64_t M = 32769; M <= kMaxM; M += M < 66000 ? 7 : M / 67 + 1)
     for (int k = 1; k <= 1100; k += k < 20 ? 1 : 17)
       for (int64_t N : {(int64_t)1, (int64_t)64, (int64_t)100000})
-        for (int mode = 0; mode < 3; ++mode) {
-          const Split s = split_big_of(N, (int)M, k, mode, 8);
+        for (int call = 0; call < 9; ++call) {
+          static const int steps_of[] = {8, 0, 1, 2, 4, 5, 7};
+          const int mode = call < 7 ? (int)kEarly : (call == 7 ? (int)kExact : (int)kEps), steps = call < 7 ? steps_of[call] : 0;
+          const Split s = split_big_of(N, (int)M, k, mode, steps);
+          if (mode == kEarly && s.segments != 0 && !splits_early(N, (int)M, steps)) ++bad;
           if (s.segments == 0) continue;
           ++split;
           const int64_t last = M - (int64_t)(s.segments - 1) * s.length;
