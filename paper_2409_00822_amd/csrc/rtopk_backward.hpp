@@ -162,9 +162,9 @@ __global__ void __launch_bounds__(256)
 // One wavefront per `rows` rows, at most kBackwardRowsM floats in all: 128-bit loads (from any 4-byte boundary, see load_group), four per lane at a
 // time (eight: 2^20 x 256, k = 32 225 -> 219 us, 2^18 x 512 111.5 -> 109.2), then the saved columns' entries are read from LDS, and the results, again
 // contiguous in the output, are stored coalesced.  FOURS: M is a multiple of four, so that nothing is left beside the 128-bit loads.
-// twos (with rows of a multiple of 256 columns and many wavefronts): a full wavefront's rows are loaded two quads per lane at a time, without a look at
-// the end (four -> two, us: 2^20 x 256, k = 32 210.7 -> 206.2, byte columns 193.8 -> 192.1, k = 128 353.8 -> 350.5, 2^18 x 1024 210.4 -> 206.5, 2^17 x 2048 193.0 ->
-// 193.2; but 2^20 x 64, k = 8 54.0 -> 55.9, byte columns 50.4 -> 53.7, rows that share lines, 2^20 x 251 228 -> 230, 2^18 x 777 155 -> 163, and few
+// twos (with many wavefronts and rows of 256, 512 or 1024 columns): a full wavefront's rows are loaded two quads per lane at a time, without a look at the
+// end (four -> two, us: 2^20 x 256, k = 32 210.7 -> 206.2, byte columns 193.8 -> 192.1, k = 128 353.8 -> 350.5, 2^18 x 1024 210.4 -> 206.5; but 2^17 x 2048,
+// k = 100, inputs cold, 190.3 -> 192.2, 2^20 x 64, k = 8 54.0 -> 55.9, byte columns 50.4 -> 53.7, rows that share lines, 2^20 x 251 228 -> 230, 2^18 x 777 155 -> 163, and few
 // wavefronts, 300 x 2048 3.3 -> 4.0).
 // FEW: a launch of few wavefronts, whose latencies stand alone: the columns are loaded before the rows (last -> first, us: 3910 x 256, k = 15, byte columns
 // 3.3 -> 2.9, 20000 x 64 3.2 -> 2.8, 1506 x 1028 4.0 -> 3.5, 48008 x 208 9.9 -> 9.1, 20000 x 256 6.25 -> 6.0; with many, first, or between the rows' loads, 2^20 x
@@ -337,7 +337,7 @@ hipError_t launch_gather(const float* gout, const IdxT* idx, int64_t N, int M, i
     const auto kernel = M % 4 == 0 ? (many ? maxk_gather_rows_kernel<IdxT, B, true> : few::maxk_gather_rows_kernel<IdxT, B, true>)
                                    : (many ? maxk_gather_rows_kernel<IdxT, B, false> : few::maxk_gather_rows_kernel<IdxT, B, false>);
     return launch_kernel(kernel, dim3((unsigned)blocks), dim3(kWave), ((size_t)rows * M + 3) / 4 * 16, stream, gout, idx, N, M, k, rows,
-                         many && M % 256 == 0 ? 1 : 0, divisor(k), gv);
+                         many && M % 256 == 0 && M <= 1024 ? 1 : 0, divisor(k), gv);
   });
 }
 
