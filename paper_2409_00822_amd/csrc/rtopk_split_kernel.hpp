@@ -426,8 +426,6 @@ __device__ __forceinline__ bool merge_row(MergeLds<NW>& s, int64_t r, const floa
   MergeResult done;
   constexpr int kMost = NW == 16 ? kMergeRegsBig : kMergeRegs;
   bool by_number = !by_lists;
-  int total;
-  float T0, lo, hi;
   if (!by_number) {  // uniform
     // every wavefront reads the heads, lane s that of segment s: nothing to exchange before the bins
     const SegmentHead h = heads[r * segments + min(lane, segments - 1)];
@@ -436,11 +434,10 @@ __device__ __forceinline__ bool merge_row(MergeLds<NW>& s, int64_t r, const floa
     const uint32_t upto = wave_inclusive_scan_dpp((uint32_t)regs << 17 | (uint32_t)n);
     const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave - 1);
     const int start = (int)(upto >> 17) - regs;
-    total = (int)(all & 0x1ffffu);
-    float unused;
+    float T0, lo, hi, unused;
     wave_max_and_negmin(h.floor, h.nlo, T0, lo);  // (a lane beyond the last segment repeats it)
     wave_max_and_negmin(h.hi, h.hi, hi, unused);
-    const int per = ((int)(all >> 17) + NW - 1) / NW, numbered = (total + NW * kWave - 1) / (NW * kWave);
+    const int total = (int)(all & 0x1ffffu), per = ((int)(all >> 17) + NW - 1) / NW;
     auto listed = [&](auto regs_of) -> MergeResult {
       constexpr int KR = decltype(regs_of)::value;
       float key[KR];
@@ -449,13 +446,21 @@ __device__ __forceinline__ bool merge_row(MergeLds<NW>& s, int64_t r, const floa
       __syncthreads();
       return merge_candidates<NW, KR, MODE, NEG, RANK>(s, r, M, k, max_iter, eps_rel, ov, oi, out_iters, key, col, per, T0, lo, hi, rest);
     };
-    // (lists of a few more than 64, 128 ... candidates leave most of a register empty: numbered through, fewer may do.  By lists -> the fewer of both, us:
-    // 1 x 10^6, k = 700 29.9 -> 26.8, k = 80 15.4 -> 14.4; 1 x 700000, k = 128 15.6 -> 14.5; 24 x 150000, k = 45 11.6 -> 11.3; 1 x 131072, k = 72 9.1 -> 8.8.)
-    by_number = per > kMost || registers_walked<NW>(per, true) > registers_walked<NW>(numbered, false);
+    // (lists of a few more than 64, 128 ... candidates leave most of a register empty: numbered through, half the registers may do.  By lists -> by number,
+    // us: 40 registers to 16, 1 x 10^6, k = 700 37.3 -> 27.2; 16 to 8, k = 80 15.6 -> 14.3; 8 to 4, 16 wavefronts, 1 x 538928, k = 173 -8 %; exact mode,
+    // 14 x 132306, k = 47 -3 %.  But 12 to 8, 1 x 311414, k = 134 13.4 -> 14.0, and 8 to 4 in few wavefronts, whose bins are not needed, 6 x 155042, k = 51,
+    // eight steps 10.6 -> 10.9: then what the lists' places in LDS and the search for them cost is as much.)
+    by_number = per > kMost || (per > (NW == 16 || MODE == kExact ? 4 : 12) &&
+                                registers_walked<NW>(per, true) >= 2 * registers_walked<NW>((total + NW * kWave - 1) / (NW * kWave), false));
     if (by_number) {
       if (wave == 0) {
         if (lane < segments) s.first[lane] = (int)(upto & 0x1ffffu) - n;
-        if (lane == 0) s.first[segments] = total;
+        if (lane == 0) {
+          s.first[segments] = s.total = total;
+          s.bound[0] = T0;
+          s.bound[1] = lo;
+          s.bound[2] = hi;
+        }
       }
     } else if (per <= 4) {
       done = listed(std::integral_constant<int, 4>());
@@ -495,12 +500,10 @@ __device__ __forceinline__ bool merge_row(MergeLds<NW>& s, int64_t r, const floa
   }
   if (by_number) {  // uniform
     __syncthreads();
-    if (!by_lists) {  // uniform
-      total = __builtin_amdgcn_readfirstlane(s.total);
-      T0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[0])));
-      lo = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[1])));
-      hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[2])));
-    }
+    const int total = __builtin_amdgcn_readfirstlane(s.total);
+    const float T0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[0])));
+    const float lo = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[1])));
+    const float hi = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s.bound[2])));
     if (total <= k || total > NW * kWave * kMost) return false;
     const int per = (total + NW * kWave - 1) / (NW * kWave);
     auto numbered = [&](auto regs_of) -> MergeResult {
