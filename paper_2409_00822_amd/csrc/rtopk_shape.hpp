@@ -326,19 +326,38 @@ inline bool splits_early(int64_t N, int M, int max_iter) {
 constexpr int segment_length(int M, int segments) { return ((M + segments - 1) / segments + 3) & ~3; }
 constexpr int segment_values(int length, int w) { return length <= w * 3072 ? 48 : 64; }
 // Segments of 16384 columns where those of 32768, `wide` of them in all, give every compute unit two workgroups or more: of the smaller workgroups five
-// share a compute unit instead of two, but the merge has twice the candidates, so up to four workgroups for each (eight, six from k = 33 on,
-// with up to eight lists to a row), for k up to 128, where a merge of four wavefronts holds the `candidates`.  Not where the longer segments fill
-// their lanes (to 31/32) or hold 48 values there and the shorter ones 64: these then gain nothing for themselves.  Time with 32768-column
-// segments over time with 16384-column ones, at 720, 1100 and 2000 longer segments in all:
-//   k = 64: 50000 columns 1.07 1.12 1.04, 36000 1.04 1.08 1.02, 62000 1.03 1.08 1.00, 80000 1.07 1.07 1.01, 94000 1.07 1.11 1.05, 110000 1.10 1.15 1.07,
-//     126000 1.00 1.06 0.99, 164776 1.04, 230000 1.05; k = 8: 50000 1.08 1.14 1.11, 126000 1.03 1.08 1.02;
-//   left out: full lanes, 65536 1.01 0.99 0.90, 98304 1.00 0.96 0.91, 131072 0.98 0.97 0.89, 262144 0.97; 48 values against 64, 44000 0.99 1.05 1.01, 38000
-//     0.98 1.04 1.00, 70000 0.98 1.00 0.97; k = 150: 56000 1.00 1.03 0.95, 90000 0.98 1.02 0.93; k = 250: 34424 0.94 0.98 0.95, 59000 0.95 0.98 0.94.
-inline bool shorter_segments(int M, int k, int64_t wide, int64_t candidates) {
-  const int long_ones = (M + 32767) / 32768, short_ones = (M + 16383) / 16384;
-  const int length = segment_length(M, long_ones), values = segment_values(length, 8);
-  return k <= 128 && wide < (short_ones > 8 ? 4 : (k <= 32 ? 8 : 6)) * 256 && candidates <= 4 * 64 * kMergeRegs && 32 * length <= 31 * 512 * values &&
-         values >= segment_values(segment_length(M, short_ones), 4);
+// share a compute unit instead of two, but the merge has twice the candidates; where a merge of four wavefronts holds these, up to four workgroups for
+// each compute unit, eight with up to eight lists to a row.  Early stopping with few steps: the shorter segments' floors lie lower, so that fewer rows
+// end below them and are walked again.  Otherwise it pays the less, the fuller the lanes of the longer segments are (to 27/32, to 31/32, beyond, full),
+// the more values they hold in the shorter ones (48 -> 64) and the larger k is; the more, where rows start off 16-byte boundaries.  Time with
+// 32768-column segments over time with 16384-column ones, at 520, 860, 1400 and 2040 longer segments in all (exact mode; eight and sixteen steps and
+// precisions differ from it by 0.02):
+//   lanes to 27/32: 50000, k = 48 1.14 1.13 1.10 1.06, 134 1.12 1.12 1.07 1.02, 200 1.02 1.02 0.99 0.96, 80000, k = 200 1.11 1.06 1.02 0.99, 80001 1.11
+//     1.06 1.01 0.99; to 31/32: 62000, k = 48 1.10 1.09 1.05 1.01, 110 1.11 1.08 1.04 0.98, 134 1.10 1.07 1.02 0.99, 200 1.01 0.99 0.98 0.93, 59999, k = 110
+//     1.12 1.10 1.05 1.01, 160 1.06 1.06 1.03 0.97, 94000, k = 48 1.10 1.12 1.09 1.05; beyond: 128000, k = 48 1.12 1.06 1.01 0.94, 127999 1.11 1.08 1.03
+//     0.97; full: 65536, 98304, 131072, k = 48 1.08 0.97 0.91 0.89, k = 160 1.02 0.94 0.87 0.87, 65535, k = 48 1.11 1.02 0.93 0.90, 160 1.05 1.01 0.91 0.88;
+//   three short segments: 34424, k = 160 1.10 1.05 1.06 1.04, 250 1.02 0.97 0.98 0.96, with 64 values 41000, k = 134 1.05 1.01 1.04 1.03, 160 1.05 1.01 1.01
+//     1.02, 250 0.96 0.94 0.94 0.94; five with 64 values: 70000, k = 48 1.06 1.01 0.99 0.98, 200 1.00 0.98 0.96 0.93, 67571, k = 48 1.04 1.04 1.03 1.03;
+//   four steps: 112484, k = 134 1.45 1.33 1.16 1.11, 98304, k = 134 1.35 1.12 1.01 1.03, 70000, k = 8 1.06 0.95 1.00 0.96.
+inline bool shorter_segments(int M, int k, int mode, int max_iter, int64_t wide, int64_t candidates) {
+  const int short_ones = (M + 16383) / 16384, length = segment_length(M, (M + 32767) / 32768), values = segment_values(length, 8);
+  const int lanes = 512 * values, most = short_ones > 8 ? 4 * 256 : 8 * 256;
+  const bool more_values = segment_values(segment_length(M, short_ones), 4) > values, off = M % 4 != 0;
+  int line = most;
+  if (mode == kEarly && max_iter <= 5) {
+  } else if (1000 * length >= 997 * lanes) {
+    line = off && k <= 112 ? 860 : (k <= 160 ? 640 : 0);
+  } else if (short_ones == 3) {
+    line = k <= (more_values ? 160 : 200) ? most : 0;
+  } else if (more_values) {
+    line = off && k <= 112 ? most : (k <= 160 ? 560 : 0);
+  } else if (32 * length < 27 * lanes) {
+    line = k <= 96 ? most : (k <= 160 ? 1664 : (off ? 1280 : 640));
+  } else {
+    line = k <= (off ? 112 : 56) ? most : (k <= (off ? 160 : 112) ? 1536 : (k <= 160 ? 1280 : (k <= 200 ? 640 : 0)));
+    if (32 * length >= 31 * lanes) line = line < (off ? 1408 : 1280) ? line : (off ? 1408 : 1280);
+  }
+  return wide < (line < most ? line : most) && candidates <= 4 * 64 * kMergeRegs;
 }
 // wide_only: segments of 32768 columns whatever the number of rows.
 inline Split split_of(int64_t N, int M, int k, int mode, int max_iter, bool wide_only = false) {
@@ -355,7 +374,7 @@ inline Split split_of(int64_t N, int M, int k, int mode, int max_iter, bool wide
   // twice the candidates in all, still fit the merge; or, up to twice that many rows and more, where shorter_segments says so.
   s.w = 8;
   const int64_t wide = N * ((M + 32767) / 32768), narrow = (M + 16383) / 16384;
-  if (!wide_only && k <= filter_max_k(4) && (wide < 2 * 256 ? narrow * expected <= kMergeMost : shorter_segments(M, k, wide, narrow * usual))) s.w = 4;
+  if (!wide_only && k <= filter_max_k(4) && (wide < 2 * 256 ? narrow * expected <= kMergeMost : shorter_segments(M, k, mode, max_iter, wide, narrow * usual))) s.w = 4;
   const int most = s.w * 4096;
   s.segments = (M + most - 1) / most;
   if ((int64_t)s.segments * expected > kMergeMost) {

@@ -156,7 +156,7 @@ def test_many_short_lists(M, k):
     assert np.array_equal(got[2].cpu().numpy(), et)
 
 
-@pytest.mark.parametrize("M, k, most, fewer", [(50000, 64, 1024, (1023, 700, 512, 3)), (80000, 64, 512, (511, 380, 2))])
+@pytest.mark.parametrize("M, k, most, fewer", [(50000, 64, 1024, (1023, 700, 512, 3)), (80000, 64, 683, (682, 450, 2))])
 def test_memory_for_a_batch_serves_smaller_ones(M, k, most, fewer):
     # the shorter segments of fewer rows need more than the longer ones of more: then these are taken, and the memory is used
     R = _gpu()
