@@ -165,13 +165,14 @@ __global__ void __launch_bounds__(256)
 // One wavefront per `rows` rows, at most kBackwardRowsM floats in all: 128-bit loads (from any 4-byte boundary, see load_group), four per lane at a
 // time (eight: 2^20 x 256, k = 32 225 -> 219 us, 2^18 x 512 111.5 -> 109.2), then the saved columns' entries are read from LDS, and the results, again
 // contiguous in the output, are stored coalesced.  FOURS: M is a multiple of four, so that nothing is left beside the 128-bit loads.
-// twos (with many wavefronts and rows of 256, 512 or 1024 columns): a full wavefront's rows are loaded two quads per lane at a time, without a look at the
-// end (four -> two, us: 2^20 x 256, k = 32 210.7 -> 206.2, byte columns 193.8 -> 192.1, k = 128 353.8 -> 350.5, 2^18 x 1024 210.4 -> 206.5; but 2^17 x 2048,
-// k = 100, inputs cold, 190.3 -> 192.2, 2^20 x 64, k = 8 54.0 -> 55.9, byte columns 50.4 -> 53.7, rows that share lines, 2^20 x 251 228 -> 230, 2^18 x 777 155 -> 163, and few
-// wavefronts, 300 x 2048 3.3 -> 4.0).
-// FEW: a launch of few wavefronts, whose latencies stand alone: the columns are loaded before the rows (last -> first, us: 3910 x 256, k = 15, byte columns
-// 3.3 -> 2.9, 20000 x 64 3.2 -> 2.8, 1506 x 1028 4.0 -> 3.5, 48008 x 208 9.9 -> 9.1, 20000 x 256 6.25 -> 6.0; with many, first, or between the rows' loads, 2^20 x
-// 256 210.4 -> 212 to 213, 2^20 x 251 226 -> 229; as a flag to one kernel small launches take 0.03 to 0.05 us more).
+// twos: a full wavefront's rows, of 256, 512 or 1024 columns, are loaded two quads per lane at a time, without a look at the end.  With 65536 wavefronts and
+// more and k from an eighth of the row on (four -> two, us: 2^20 x 256, k = 32 210.4 -> 206.6, inputs cold 223 -> 218, k = 128 358 -> 353, 2^18 x 1024 210.4 -> 206.5;
+// but 528693 x 256, k = 11, byte columns 92.0 -> 95.6, 157978 x 256, k = 3 26.3 -> 28.5, 157897 x 512, k = 61 -1 %, 2^17 x 2048, k = 100, inputs cold, 190.3 -> 192.2,
+// 2^20 x 64, k = 8 54.0 -> 55.9, and rows that share lines, 2^20 x 251 228 -> 230, 2^18 x 777 155 -> 163).
+// FEW: a launch of few wavefronts, whose latencies stand alone: the columns are loaded before the rows.  Up to 32768 wavefronts of up to 400 pairs (last ->
+// first, us: 3910 x 256, k = 15, byte columns 3.3 -> 2.9, 20000 x 64 3.2 -> 2.8, 1506 x 1028 4.0 -> 3.5, 48008 x 208 9.9 -> 9.1, 42280 x 256, k = 38 11.0 -> 10.0, of
+// 16384 to 24575 wavefronts -2 % on average, to 32767 -0.5; but to 65535 +0.2, 2^20 x 256 210 -> 212 to 213, 2^20 x 251 226 -> 229, and more columns hold up the
+// rows: 7632 x 832, k = 206 5.8 -> 6.2; as a flag to one kernel small launches take 0.03 to 0.05 us more).
 template <typename IdxT, int BATCH, bool FOURS, bool FEW>
 __device__ __forceinline__ void gather_rows(const float* __restrict__ grad_out, const IdxT* __restrict__ idx, int64_t N, int M, int k, int rows,
                                             int twos, uint32_t by, float* __restrict__ grad_vals) {
@@ -279,15 +280,20 @@ __global__ void __launch_bounds__(256)
 
 
 // Rows per wavefront of the gather: up to 8 KiB of LDS, fewer where that would leave compute units with less than four wavefronts (eight -> four, us:
-// 3910 x 256, k = 15, byte columns 3.9 -> 3.3, 9824 x 64, k = 3 3.2 -> 3.0), but a 128-bit load for each lane.  A power of two of them where M is a
-// multiple of four: wavefronts then seldom share a line of the rows, or of the results, which both would read, or write part of (as many as fit
-// -> a power of two, us: 320696 x 88, k = 4 23 rows 24.2 -> 16 rows 20.7; 10^6 x 40, k = 2 51 34.2 -> 32 28.8; 500000 x 100, k = 12 20 43.4 -> 16 41.5;
-// 300000 x 200 10 46.5 -> 8 44.2; 100000 x 400 5 29.5 -> 4 27.8; 2^18 x 640 3 132.8 -> 2 128.6; but odd widths, which share lines in any case: 100000 x 333 6
-// 28.0 -> 4 29.0).
-inline int backward_rows_per_wave(int64_t N, int M) {
+// 3910 x 256, k = 15, byte columns 3.9 -> 3.3, 9824 x 64, k = 3 3.2 -> 3.0; eight where it has more than 400 pairs, 5098 x 384, k = 121 4.45 -> 4.2), but a
+// 128-bit load for each lane.  A power of two of them where M is a multiple of four: wavefronts then seldom share a line of the rows, or of the results,
+// which both would read, or write part of (as many as fit -> a power of two, us: 320696 x 88, k = 4 23 rows 24.2 -> 16 rows 20.7; 10^6 x 40, k = 2 51 34.2 -> 32 28.8; 500000 x 100, k = 12 20 43.4 -> 16 41.5;
+// 300000 x 200 10 46.5 -> 8 44.2; 100000 x 400 5 29.5 -> 4 27.8; but odd widths, which share lines in any case: 100000 x 333 6 28.0 -> 4 29.0).  Of wider rows
+// than 256 columns not where that takes more than a fifth of them (219907 x 644, k = 67 3 116.8 -> 2 123.8; 747932 x 288, k = 5 7 143 -> 4 150; 215027 x
+// 516, k = 44 3 90.5 -> 2 94.9), unless it alone ends the results on a line (2^18 x 640, k = 80 3 141.9 -> 2 136.3).
+constexpr int kFirstPairs = 400;  // (see gather_rows, too)
+inline int backward_rows_per_wave(int64_t N, int M, int k) {
   const int most = kBackwardRowsM / M, least = 4 * kWave / M > 1 ? 4 * kWave / M : 1;
-  const int rows = N / 1024 >= most ? most : (N / 1024 > least ? (int)(N / 1024) : least);
-  return M % 4 == 0 ? 1 << (31 - __builtin_clz((unsigned)rows)) : rows;
+  auto spread = [&](int64_t wavefronts) { return N / wavefronts >= most ? most : (N / wavefronts > least ? (int)(N / wavefronts) : least); };
+  int rows = spread(1024);
+  if (rows * k > kFirstPairs) rows = spread(2048);
+  const int power = 1 << (31 - __builtin_clz((unsigned)rows));
+  return M % 4 == 0 && (M <= 256 || 5 * power >= 4 * rows || (power * k % 32 == 0 && rows * k % 32 != 0)) ? power : rows;
 }
 
 // f(integral_constant<int, BATCH>) for a wavefront of up to `pairs` pairs.  No more than it has: a load whose lanes are all past the end costs as
@@ -332,16 +338,16 @@ hipError_t launch_gather(const float* gout, const IdxT* idx, int64_t N, int M, i
     if (N > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     return launch_kernel(maxk_gather_block_kernel<IdxT>, dim3((unsigned)N), dim3(256), 0, stream, gout, idx, N, M, k, gv);
   }
-  const int rows = backward_rows_per_wave(N, M);
+  const int rows = backward_rows_per_wave(N, M, k);
   const int64_t blocks = (N + rows - 1) / rows;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   return by_pairs(rows * k, [&](auto batch) {
     constexpr int B = decltype(batch)::value;
-    const bool many = blocks >= 16384;  // (2^20 x 256 has 131072, 48008 x 208 6001: see gather_rows)
-    const auto kernel = M % 4 == 0 ? (many ? maxk_gather_rows_kernel<IdxT, B, true> : few::maxk_gather_rows_kernel<IdxT, B, true>)
-                                   : (many ? maxk_gather_rows_kernel<IdxT, B, false> : few::maxk_gather_rows_kernel<IdxT, B, false>);
+    const bool first = blocks < 32768 && rows * k <= kFirstPairs, twos = blocks >= 65536 && M % 256 == 0 && M <= 1024 && 8 * k >= M;  // (see gather_rows)
+    const auto kernel = M % 4 == 0 ? (first ? few::maxk_gather_rows_kernel<IdxT, B, true> : maxk_gather_rows_kernel<IdxT, B, true>)
+                                   : (first ? few::maxk_gather_rows_kernel<IdxT, B, false> : maxk_gather_rows_kernel<IdxT, B, false>);
     return launch_kernel(kernel, dim3((unsigned)blocks), dim3(kWave), ((size_t)rows * M + 3) / 4 * 16, stream, gout, idx, N, M, k, rows,
-                         many && M % 256 == 0 && M <= 1024 ? 1 : 0, divisor(k), gv);
+                         twos ? 1 : 0, divisor(k), gv);
   });
 }
 

@@ -174,7 +174,8 @@ def test_backward_at_any_alignment(M, k):
 
 
 @pytest.mark.parametrize("N,M,k", [(20011, 251, 31), (60001, 100, 12), (8200, 777, 40), (40003, 250, 100), (140001, 33, 4), (70001, 88, 4),
-                                   (16385, 256, 32), (131077, 256, 5), (65541, 512, 7), (16387, 2048, 3), (18000, 1028, 9), (2100, 2047, 33)])
+                                   (16385, 256, 32), (131077, 256, 5), (65541, 512, 7), (16387, 2048, 3), (18000, 1028, 9), (2100, 2047, 33),
+                                   (32769, 1100, 2), (32771, 1101, 2), (12281, 440, 209), (3001, 384, 121), (30001, 644, 16), (30001, 640, 16)])
 def test_backward_of_many_rows(N, M, k):
     """Chunks of 2048 floats that cut rows, gathers of several rows to a wavefront at every kind of width, several loads of pairs."""
     import ctypes
@@ -205,3 +206,14 @@ def test_backward_of_many_rows(N, M, k):
             got = pairs.cpu().numpy()
             assert np.array_equal(bits(got[32 + shift:32 + shift + N * k]), bits(want_gather.ravel())), (shift, u8)
             assert (got[:32 + shift] == 7.5).all() and (got[32 + shift + N * k:] == 7.5).all(), "wrote outside the pairs"
+
+
+def test_backward_of_most_wavefronts():
+    """65537 wavefronts of whole 8 KiB and one of a single row: two quads per lane at a time, without a look at the end but in the last."""
+    R = _gpu()
+    N, M, k = 524289, 256, 32
+    w = torch.randn(N, M, device="cuda")
+    cols = ((torch.randint(0, M, (N, 1), device="cuda") + 5 * torch.arange(k, device="cuda")) % M).int()
+    want = torch.gather(w, 1, cols.long())
+    for c in (cols, cols.to(torch.uint8)):
+        assert torch.equal(R.rtopk_maxk_backward_gather(w, c), want)
