@@ -319,6 +319,15 @@ hipError_t launch_scatter(const float* gv, const IdxT* idx, int64_t N, int M, in
   int chunk = kBackwardRowsM;  // 8 KiB of LDS, less where that would leave compute units with less than eight wavefronts
   while (chunk > 512 && elements / chunk < 2048 - 2048 / 8) chunk >>= 1;
   const int skew = floats_behind(gin, 32);
+  // Whole rows to a chunk where they end on lines, or where they have so many pairs that loading those of cut rows twice costs more than the lines that
+  // two wavefronts write parts of.  The image is then smaller and the wavefronts are more, which very large outputs pay for (2048 floats -> whole rows,
+  // us, inputs warm: 30774 x 1184, k = 304 35.5 -> 29.9, 25221 x 1600, k = 887 71 % of it, 13M elements 9596 x 1220, k = 631 80 %, 42M 21886 x 1928, k = 657
+  // 79.5 %, k below 1 / 20 of the row 93 to 101 %; but 129M to 263M elements and small k 102 to 104 %, 151634 x 1456, k = 472 243 -> 268; with k from an eighth of
+  // rows of more than 900 columns on 90 to 97 %, unless they leave a quarter of the 2048 floats, 197041 x 1088, k = 312 226.5 -> 242.5; ends beside lines, k =
+  // M / 5 95 to 132 %, 38320 x 1004, k = 288, two rows to a chunk 37.7 -> 44.5).
+  if (skew == 0 && M <= chunk &&
+      (elements < 1 << 26 ? M % 32 == 0 || (M % 4 == 0 && M > 1024 && 4 * k >= M) : M % 32 == 0 && M > 900 && 8 * k >= M && chunk / M * M >= 1536))
+    chunk = chunk / M * M;
   const int64_t blocks = (elements + skew + chunk - 1) / chunk;
   if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   const int whole = skew == 0 && chunk % M == 0 ? chunk / M : 0;

@@ -175,7 +175,8 @@ def test_backward_at_any_alignment(M, k):
 
 @pytest.mark.parametrize("N,M,k", [(20011, 251, 31), (60001, 100, 12), (8200, 777, 40), (40003, 250, 100), (140001, 33, 4), (70001, 88, 4),
                                    (16385, 256, 32), (131077, 256, 5), (65541, 512, 7), (16387, 2048, 3), (18000, 1028, 9), (2100, 2047, 33),
-                                   (32769, 1100, 2), (32771, 1101, 2), (12281, 440, 209), (3001, 384, 121), (30001, 644, 16), (30001, 640, 16)])
+                                   (32769, 1100, 2), (32771, 1101, 2), (12281, 440, 209), (3001, 384, 121), (30001, 644, 16), (30001, 640, 16),
+                                   (9001, 1184, 304), (3001, 1496, 400), (20001, 96, 5), (5001, 1496, 300), (601, 224, 20), (40001, 1760, 220)])
 def test_backward_of_many_rows(N, M, k):
     """Chunks of 2048 floats that cut rows, gathers of several rows to a wavefront at every kind of width, several loads of pairs."""
     import ctypes
