@@ -20,13 +20,15 @@
 
 namespace rtopk {
 
-// The rows of a wavefront are contiguous in the dense matrix (`rows` * M floats) and their pairs in the [N][k] arrays, so both kernels
-// walk the pairs as one list, 64 neighbours to an instruction, whatever k is: BATCH instructions' worth in registers, as many as the wavefront has or 16,
-// loaded together, while the rows are cleared or loaded.  All loads are unconditional (lanes past the end repeat the last): behind a
-// branch each would be waited for alone.  What bounds both is HBM, given enough loads in flight.  Measured against 2, 4, 8 or 16 whole rows
-// with the lanes divided among them, dword accesses where M is no multiple of four and a loop over the row for k > 64, us, inputs cold: 1048576
-// x 251, k = 31 scatter 340 -> 213, gather 536 -> 230; x 250, k = 100 685 -> 273, 728 -> 293; x 256, k = 32 210 -> 207, 203 -> 204, k = 128 645 -> 294, 371
-// -> 282; 262144 x 777, k = 40 265 -> 161, 310 -> 154; 131072 x 2048, k = 100 261 -> 222, 190 -> 192 (byte columns up to 256).
+// A wavefront of the scatter owns a chunk of the dense matrix, which may cut rows, one of the gather whole rows of it; both are contiguous, and so are
+// their pairs in the [N][k] arrays.  So both kernels walk the pairs as one list, 64 neighbours to an instruction, whatever k is: BATCH instructions' worth in
+// registers, as many as the wavefront has or 16, loaded together, while the chunk is cleared or the rows are loaded.  All loads are unconditional (lanes past
+// the end repeat the last): behind a branch each would be waited for alone.  What bounds both is HBM, given enough loads in flight.  Measured against 2, 4, 8
+// or 16 whole rows with the lanes divided among them, dword accesses where M is no multiple of four and a loop over the row for k > 64, us, matrices and
+// pairs from three sets in turn: 1048576 x 251, k = 31 scatter 339 -> 203, gather 537 -> 245; x 250, k = 100 685 -> 263, 726 -> 300; x 256, k = 128 638 -> 290,
+// 371 -> 285, k = 32 207 -> 207, 202 -> 201 (byte columns; int32 ones 228 -> 224, 219 -> 217); 262144 x 777, k = 40 267 -> 147, 309 -> 154; 131072 x 2048, k =
+// 100 189 -> 193, 191 -> 191.
+
 // n / d for n up to 3 * 2048 and d up to 2048, exactly: n * (by - 2^32 / d) < 2^32 / d.  by: ceil(2^32 / d), 0 where that is 2^32.
 __device__ __forceinline__ int quotient(int n, uint32_t by) { return by == 0 ? n : (int)__umulhi((uint32_t)n, by); }
 inline uint32_t divisor(int d) { return 0xffffffffu / (uint32_t)d + 1; }
